@@ -98,9 +98,13 @@ struct Ops {
 
     // The same for lane c of a 32-pixel tile whose address `tile` is the same in every lane:
     // written as uniform base + 32-bit lane offset so that the load takes its base from scalar
-    // registers and a streaming loop spends no vector instruction on addresses.
+    // registers and a streaming loop spends no vector instruction on addresses.  (The offset passes
+    // through the empty asm because its widening to 64 bits would otherwise be hoisted out of the
+    // loop, where the load no longer sees that it is a 32-bit offset and adds it to the base itself:
+    // two vector instructions per load and two more registers.)
     static __device__ __forceinline__ Frag load_tile(const char* tile, uint32_t c, int h) {
-        const uint32_t off = c * (uint32_t)ROW_BYTES + (uint32_t)h * (uint32_t)LANE_BYTES;
+        uint32_t off = c * (uint32_t)ROW_BYTES + (uint32_t)h * (uint32_t)LANE_BYTES;
+        asm volatile("" : "+v"(off));
         Frag f;
 #pragma unroll
         for (int i = 0; i < NV; ++i) f.v[i] = *reinterpret_cast<const uint4*>(tile + (off + 16u * i));
@@ -151,8 +155,10 @@ struct OpsHalf24 {
     // uniform tile address + 32-bit lane offsets (see Ops::load_tile)
     static __device__ __forceinline__ Frag load_tile(const char* tile, uint32_t c, int h) {
         Frag f;
-        f.lo = *reinterpret_cast<const uint4*>(tile + (c * 48u + 16u * (uint32_t)h));
-        f.hi = *reinterpret_cast<const uint2*>(tile + (c * 48u + 32u + 8u * (uint32_t)h));
+        uint32_t lo = c * 48u + 16u * (uint32_t)h, hi = c * 48u + 32u + 8u * (uint32_t)h;
+        asm volatile("" : "+v"(lo), "+v"(hi));
+        f.lo = *reinterpret_cast<const uint4*>(tile + lo);
+        f.hi = *reinterpret_cast<const uint2*>(tile + hi);
         return f;
     }
 

@@ -57,6 +57,50 @@ __device__ __forceinline__ int64_t query_row(const SearchArgs& a, int64_t qbase,
     return min(max(row, (int64_t)0), (int64_t)a.src_rows - 1);  // never read outside the map
 }
 
+// The rows of this lane's query in N consecutive 32-query blocks from slot0 on.  All N index loads
+// are in flight together: taken one by one behind the tests above, each waited for the one
+// before it and for that block's row, two memory latencies per block before a wave could start (one
+// 512x384 pair: first search 37.6 -> 33.4 us, 16 pairs with 1450 queries each 241 -> 228 us, with the
+// waits moved out of the candidate loop, see arrived()).  Slots past the live queries repeat the
+// last one; their results are dropped.
+template <int N>
+__device__ __forceinline__ void query_rows(const SearchArgs& a, int64_t qbase, int slot0, int n_act, int c, int32_t (&row)[N]) {
+    int slot[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) slot[i] = min(slot0 + i * 32 + c, n_act - 1);
+    if (a.q_keys) {
+        uint32_t low[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) low[i] = reinterpret_cast<const uint32_t*>(a.q_keys + qbase + slot[i])[0];
+#pragma unroll
+        for (int i = 0; i < N; ++i) row[i] = (int32_t)min(0xFFFFFFFFu - low[i], (uint32_t)a.src_rows - 1u);
+    } else if (a.q_idx) {
+        int32_t idx[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) idx[i] = a.q_idx[qbase + slot[i]];
+#pragma unroll
+        for (int i = 0; i < N; ++i) row[i] = idx[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) row[i] = slot[i];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) row[i] = min(max(row[i], 0), a.src_rows - 1);  // never read outside the map
+}
+
+// Holds the program at this point until the fragment has arrived.  Without it the waits for the query
+// loads are merged into the candidate loop, where they also drain the ring of tiles in flight down
+// to one on every trip.
+template <typename Frag>
+__device__ __forceinline__ void arrived(Frag& f) {
+    constexpr int WORDS = sizeof(Frag) / 4;
+    struct Words { uint32_t w[WORDS]; };
+    Words x = __builtin_bit_cast(Words, f);
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) asm volatile("" : "+v"(x.w[i]));
+    f = __builtin_bit_cast(Frag, x);
+}
+
 // One unit of pass 1: the query blocks of slots [slot0, slot0 + 32*R*G) against the candidate
 // tiles [t0, t1).  Per query the best score and the 32-candidate TILE that holds it: a lane only
 // keeps a running maximum (3-input max) and, once per tile, notes the tile when the maximum
@@ -90,33 +134,37 @@ __device__ __forceinline__ void search_unit(const SearchArgs& a, const char* src
     int best_tile[G][R];
     bool live[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        live[g] = slot0 + g * 32 * R < n_act;  // uniform
+    for (int g = 0; g < G; ++g) live[g] = slot0 + g * 32 * R < n_act;  // uniform
+    {
+        int32_t row[G * R];
+        query_rows<G * R>(a, qbase, slot0, n_act, c, row);
+#pragma unroll
+        for (int i = 0; i < G * R; ++i) q[i / R][i % R] = O::load(src + (int64_t)row[i] * O::ROW_BYTES, h);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int slot = slot0 + (g * R + r) * 32 + c;
-            const int64_t row = slot < n_act ? query_row(a, qbase, slot) : 0;
-            q[g][r] = O::load(src + row * O::ROW_BYTES, h);
+            arrived(q[g][r]);
             best[g][r] = ninf;
             best_tile[g][r] = 0x7FFFFFFF;
         }
-    }
 
     for (int tb = t0; tb < t1; tb += P) {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             const int t = tb + p;
-            if (t < t1) {  // uniform
+            if (__builtin_expect(t < t1, 1)) {  // uniform
                 const Frag cur = ring[p];
                 if (!EXACT) ring[p] = O::load_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
                 else if (t + P < t1) ring[p] = O::load_tile(tgt + (int64_t)(t + P) * (32 * O::ROW_BYTES), c, h);
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    if (live[g]) {
+                    if (__builtin_expect(live[g], 1)) {
                         f32x16 acc[R];
 #pragma unroll
                         for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[g][r]);
-                        if (t * 32 + 32 > a.m) {  // only the last tile of the map can be partial
+                        if (__builtin_expect(t * 32 + 32 > a.m, 0)) {  // only the last tile of the map can be partial
                             // candidate t*32 + tile_row(v, h) lies past the map; tested against one
                             // lane-dependent bound so that no per-register constants stay resident
                             const int bound = a.m - t * 32 - 4 * h;
@@ -333,19 +381,39 @@ void search_first_kernel(FirstSearchArgs fa) {
         int best_tile[G][R];
         bool live[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            live[g] = slot0 + g * 32 * R < n_act;  // uniform in the wave
+        for (int g = 0; g < G; ++g) live[g] = slot0 + g * 32 * R < n_act;  // uniform in the wave
+        {
+            int32_t row[G * R];
+            query_rows<G * R>(a, qbase, slot0, n_act, c, row);
+            if (fa.raw_queries) {
+                // group by group: a group's raw rows take twice the registers of its fragments
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    typename O::Raw x[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) x[r] = O::load_raw(fa.raw_src.map[b] + (int64_t)row[g * R + r] * fa.raw_src.row_stride, h);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) q[g][r] = O::round_raw(x[r]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < G * R; ++i) q[i / R][i % R] = O::load(src + (int64_t)row[i] * O::ROW_BYTES, h);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const int slot = slot0 + (g * R + r) * 32 + c;
-                const int64_t row = slot < n_act ? query_row(a, qbase, slot) : 0;
-                if (fa.raw_queries) q[g][r] = O::round_raw(O::load_raw(fa.raw_src.map[b] + row * fa.raw_src.row_stride, h));
-                else q[g][r] = O::load(src + row * O::ROW_BYTES, h);
+                arrived(q[g][r]);
                 best[0][g][r] = ninf;
                 best[1][g][r] = ninf;
                 best_tile[g][r] = 0x7FFFFFFF;
             }
-        }
+
+        // The quads of a chunk would all read the same tile at the same moment and queue on one channel of
+        // L2: they start up to 2 us apart instead (every pixel of a 512x384 pair as a query, 128
+        // quads per chunk: 1660 against 1715 us).
+        for (int i = 0; i < (quad & 7); ++i) __builtin_amdgcn_s_sleep(8);
 
         // one turn: stage my tile of the turn, then multiply the four staged tiles
         auto turn = [&](int k, auto slot_tag) {
@@ -361,17 +429,17 @@ void search_first_kernel(FirstSearchArgs fa) {
             for (int j = 0; j < FIRST_TURN; ++j) {
                 const int t = t0 + k * FIRST_TURN + j;
                 const int now = j & 1, then = now ^ 1;
-                if (t < t1) {  // uniform
+                if (__builtin_expect(t < t1, 1)) {  // uniform
                     Frag cur;
                     cur.lo = stage_lo[SLOT][j][lane];
                     cur.hi = stage_hi[SLOT][j][lane];
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
-                        if (live[g]) {
+                        if (__builtin_expect(live[g], 1)) {
                             f32x16 acc[R];
 #pragma unroll
                             for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[g][r]);
-                            if (t * 32 + 32 > a.m) {  // only the last tile of the map can be partial
+                            if (__builtin_expect(t * 32 + 32 > a.m, 0)) {  // only the last tile of the map can be partial
                                 const int bound = a.m - t * 32 - 4 * h;
 #pragma unroll
                                 for (int r = 0; r < R; ++r)
