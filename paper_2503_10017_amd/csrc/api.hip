@@ -78,8 +78,9 @@ RecipLayout carve_recip(Carver& cv, int batch, int64_t n, int64_t m, int d, int6
     L.st.cur_u[1] = (int32_t*)cv.take(per * sizeof(int32_t));
     L.st.seed_id[0] = (int32_t*)cv.take(per * sizeof(int32_t));
     L.st.seed_id[1] = (int32_t*)cv.take(per * sizeof(int32_t));
-    L.st.n_active = (int32_t*)cv.take((size_t)batch * sizeof(int32_t));
+    L.st.n_active[0] = (int32_t*)cv.take((size_t)batch * sizeof(int32_t));
     L.st.word_rank = (int32_t*)cv.take((size_t)batch * L.st.n_words * sizeof(int32_t));
+    L.st.n_active[1] = L.st.word_rank;  // the sort writes its ranks after the last iteration (n > 0, so a word per pair is there)
     return L;
 }
 
@@ -405,13 +406,13 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
         }
         FNN_TRY(launch_search_first(first, batch, opts->compute, s));
         if (fused) {
-            FNN_TRY(launch_resolve_raw(first, batch, opts->compute, out_idx, out_score, s));
+            FNN_TRY(launch_resolve_raw(first, batch, opts->compute, out_idx, out_score, nullptr, s));
             return FNN_OK;
         }
     } else {
         FNN_TRY(launch_search(sa, batch, opts->compute, L.maps.dp, s));
     }
-    FNN_TRY(launch_resolve(sa, batch, opts->compute, L.maps.dp, out_idx, out_score, s));
+    FNN_TRY(launch_resolve(sa, batch, opts->compute, L.maps.dp, out_idx, out_score, nullptr, s));
     return FNN_OK;
 }
 
@@ -529,7 +530,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     extra.seeds = seeds;
     extra.cur_u = L.st.cur_u[0];
     extra.seed_id = L.st.seed_id[0];
-    extra.n_active = L.st.n_active;
+    extra.n_active = L.st.n_active[0];
     extra.n_seeds = ns;
     const char *p1 = (const char*)L.maps.p1, *p2 = (const char*)L.maps.p2;
     int64_t bs1 = L.maps.bstride1, bs2 = L.maps.bstride2;
@@ -548,7 +549,6 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     fwd.src = p1;
     fwd.src_bstride = bs1;
     fwd.src_rows = (int32_t)L.maps.n_pad;
-    fwd.nq_active = L.st.n_active;
     fwd.nq = ns;
     fwd.tgt = p2;
     fwd.tgt_bstride = bs2;
@@ -562,7 +562,6 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     bwd.src_bstride = bs2;
     bwd.src_rows = (int32_t)L.maps.m_pad;
     bwd.q_keys = L.st.keys_f;
-    bwd.nq_active = L.st.n_active;
     bwd.nq = ns;
     bwd.tgt = p1;
     bwd.tgt_bstride = bs1;
@@ -570,8 +569,25 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     bwd.m_tiles = (int32_t)(L.maps.n_pad / 32);
     bwd.out_keys = L.st.keys_b;
 
+    StepArgs step;  // bookkeeping of an iteration, in the launch that resolves its search back
+    memset(&step, 0, sizeof(step));
+    step.keys_f = L.st.keys_f;
+    step.seed_i = seed_i;
+    step.seed_j = seed_j;
+    step.seed_iter = seed_iter;
+
     int which = 0;
-    fwd.q_idx = L.st.cur_u[which];
+    auto take_state = [&](int w) {  // the searches and the bookkeeping read half w of the ping-pong state
+        which = w;
+        fwd.q_idx = L.st.cur_u[w];
+        fwd.nq_active = bwd.nq_active = L.st.n_active[w];
+        step.cur_u = L.st.cur_u[w];
+        step.seed_id = L.st.seed_id[w];
+        step.next_u = L.st.cur_u[w ^ 1];
+        step.next_seed_id = L.st.seed_id[w ^ 1];
+        step.next_active = L.st.n_active[w ^ 1];  // emptied by the resolve pass of the search forward
+    };
+    take_state(0);
     if (fused) {
         FirstSearchArgs first;  // V^0 = NN_2(U^0): queries and candidates still raw; writes the prepared image 2
         first.s = fwd;
@@ -580,19 +596,20 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         fill_raw(first.raw_src, batch, d1);
         first.raw_queries = 1;
         FNN_TRY(launch_search_first(first, batch, compute, s));
-        FNN_TRY(launch_resolve_raw(first, batch, compute, nullptr, nullptr, s));
+        FNN_TRY(launch_resolve_raw(first, batch, compute, nullptr, nullptr, step.next_active, s));
     } else if (staged) {
         FirstSearchArgs first;
         memset(&first, 0, sizeof(first));
         first.s = fwd;
         FNN_TRY(launch_search_first(first, batch, compute, s));
-        FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, s));
+        FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, step.next_active, s));
     } else {
         FNN_TRY(launch_search(fwd, batch, compute, L.maps.dp, s));  // V^0 = NN_2(U^0)
-        FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, s));
+        FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, step.next_active, s));
     }
     if (opts->max_iter == 0) {
-        FNN_TRY(launch_recip_step(L.st, which, ns, batch, 0, 2, seed_i, seed_j, seed_iter, s));
+        step.mode = 2;
+        FNN_TRY(launch_resolve_step(bwd, step, batch, compute, L.maps.dp, s));
     }
     for (int t = 0; t < opts->max_iter; ++t) {
         const bool last = (t == opts->max_iter - 1);
@@ -605,13 +622,13 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         } else {
             FNN_TRY(launch_search(bwd, batch, compute, L.maps.dp, s));  // U^{t+1} = NN_1(V^t)
         }
-        FNN_TRY(launch_resolve(bwd, batch, compute, L.maps.dp, nullptr, nullptr, s));
-        FNN_TRY(launch_recip_step(L.st, which, ns, batch, t, last ? 1 : 0, seed_i, seed_j, seed_iter, s));
+        step.t = t;
+        step.mode = last ? 1 : 0;
+        FNN_TRY(launch_resolve_step(bwd, step, batch, compute, L.maps.dp, s));
         if (last) break;
-        which ^= 1;
-        fwd.q_idx = L.st.cur_u[which];
+        take_state(which ^ 1);
         FNN_TRY(launch_search(fwd, batch, compute, L.maps.dp, s));  // V^{t+1} = NN_2(U^{t+1})
-        FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, s));
+        FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, step.next_active, s));
     }
     FNN_TRY(launch_recip_dedup(L.st, ns, batch, seed_i, seed_j, seed_iter, pairs, n_pairs, s));
     return FNN_OK;

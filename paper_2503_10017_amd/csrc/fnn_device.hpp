@@ -293,6 +293,56 @@ __device__ __forceinline__ int write_lane(int old, int uniform_value) {
 // Candidate offset inside a tile of result register v for lane half h.
 __device__ __forceinline__ constexpr int tile_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 
+__device__ __forceinline__ float max3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
+
+// Largest of `seed` and the 16 scores of one result fragment: eight 3-input max operations.
+__device__ __forceinline__ float fold16(float seed, const f32x16& x) {
+    const float t0 = max3(x[0], x[1], x[2]);
+    const float t1 = max3(x[3], x[4], x[5]);
+    const float t2 = max3(x[6], x[7], x[8]);
+    const float t3 = max3(x[9], x[10], x[11]);
+    const float t4 = max3(x[12], x[13], x[14]);
+    const float t5 = max3(t0, t1, t2);
+    const float t6 = max3(t3, t4, x[15]);
+    return max3(seed, t5, t6);
+}
+
+// Holds the program at this point until the fragment has arrived.  Without it the waits for the query
+// loads are merged into the candidate loop, where they also drain the ring of tiles in flight down
+// to one on every trip.
+template <typename Frag>
+__device__ __forceinline__ void arrived(Frag& f) {
+    constexpr int WORDS = sizeof(Frag) / 4;
+    struct Words { uint32_t w[WORDS]; };
+    Words x = __builtin_bit_cast(Words, f);
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) asm volatile("" : "+v"(x.w[i]));
+    f = __builtin_bit_cast(Frag, x);
+}
+
+// The largest of a tile's 32 scores against one query that every lane of the wave holds in its column
+// (result registers of lanes 0 and 32 together cover the tile), and the lowest candidate that attains it.
+struct Resolved {
+    int32_t idx;
+    float score;
+};
+__device__ __forceinline__ Resolved lowest_at_maximum(f32x16 acc, int tile, int m, int h) {
+    const float ninf = -__builtin_inff();
+    if (tile * 32 + 32 > m) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (tile * 32 + tile_row(v, h) >= m) acc[v] = ninf;
+    }
+    float top = fold16(ninf, acc);
+    top = __builtin_fmaxf(top, __shfl_xor(top, 32));
+    int row = 64;
+#pragma unroll
+    for (int v = 15; v >= 0; --v)
+        if (acc[v] == top) row = tile_row(v, h);
+    row = min(row, __shfl_xor(row, 32));
+    return {tile * 32 + row, top};
+}
+
 // ---------------------------------------------------------------------------------------
 // Exclusive prefix sum of one flag per thread over a block of up to 1024 threads (16
 // waves).  `wave_sums` is 17 ints of shared memory.  Every thread of the block must call
@@ -313,6 +363,29 @@ __device__ __forceinline__ int block_scan_flag(bool flag, int* wave_sums, int& t
     }
     total = sum;
     return offset + before;
+}
+
+// Exclusive prefix sum of one int per thread over the block (same contract as
+// block_scan_flag).
+__device__ __forceinline__ int block_scan_int(int value, int* wave_sums, int& total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = (blockDim.x + 63) >> 6;
+    int x = value;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d);
+        if (lane >= d) x += y;
+    }
+    __syncthreads();
+    if (lane == 63) wave_sums[wave] = x;
+    __syncthreads();
+    int offset = 0, sum = 0;
+    for (int w = 0; w < nwaves; ++w) {
+        const int s = wave_sums[w];
+        if (w < wave) offset += s;
+        sum += s;
+    }
+    total = sum;
+    return offset + x - value;
 }
 
 }  // namespace fnn

@@ -131,11 +131,13 @@ struct FirstSearchArgs {
 bool first_search_applies(int64_t nq, int64_t m, int batch);
 hipError_t launch_search_first(const FirstSearchArgs& a, int batch, int compute, hipStream_t s);
 // launch_resolve with the queries still in the caller's fp32 map
-hipError_t launch_resolve_raw(const FirstSearchArgs& a, int batch, int compute, int32_t* out_idx, float* out_score, hipStream_t s);
+hipError_t launch_resolve_raw(const FirstSearchArgs& a, int batch, int compute, int32_t* out_idx, float* out_score, int32_t* clear_count,
+                              hipStream_t s);
 // Pass 2: out_keys become (best score, lowest candidate index); optionally also stored to
 // out_idx / out_score (either may be NULL).  Queries without any candidate get -1 / -inf.
+// clear_count, if not NULL, is int32[batch] to set to 0.
 hipError_t launch_resolve(const SearchArgs& a, int batch, int compute, int dp, int32_t* out_idx, float* out_score,
-                          hipStream_t s);
+                          int32_t* clear_count, hipStream_t s);
 
 // ---- the paper's blocked schedules with a materialised score block (contrast experiment) ----
 struct BlockedArgs {
@@ -158,17 +160,31 @@ hipError_t run_blocked(const BlockedArgs& a, int compute, int d, int dp, int blo
 struct RecipState {
     int32_t* cur_u[2];   // [batch][n_seeds] ping-pong: U^t of the seeds still moving
     int32_t* seed_id[2]; // [batch][n_seeds] which seed sits in each slot
-    int32_t* n_active;   // [batch]
+    int32_t* n_active[2];  // [batch] seeds still moving; the half not in use is 0 when an iteration's bookkeeping starts
     u64* keys_f;         // [batch][n_seeds] result of the search into image 2 (V^t)
     u64* keys_b;         // [batch][n_seeds] result of the search back into image 1 (U^{t+1})
     uint32_t* bitmap;    // [batch][n_words] one bit per pixel of image 1, for the final sort
-    int32_t* word_rank;  // [batch][n_words] rank of the first bit of each bitmap word
+    int32_t* word_rank;  // [batch][n_words] rank of the first bit of each bitmap word (before the sort: n_active[1])
     int64_t n_words;
 };
-// mode 0: ordinary iteration t; 1: last iteration (survivors are reported as unconverged);
-// 2: no iteration at all (max_iter == 0): every seed is reported unconverged with (U^0, V^0).
-hipError_t launch_recip_step(const RecipState& st, int which, int32_t n_seeds, int batch, int t, int mode,
-                             int32_t* seed_i, int32_t* seed_j, int32_t* seed_iter, hipStream_t s);
+struct StepArgs {
+    const int32_t* cur_u;     // U^t per slot
+    const int32_t* seed_id;
+    int32_t* next_u;          // U^{t+1} of the survivors, compacted
+    int32_t* next_seed_id;
+    int32_t* next_active;     // [batch] their number (0 on entry)
+    u64* keys_f;              // V^t per slot (index field); cleared for the next search
+    int32_t t;
+    int32_t mode;
+    int32_t* seed_i;
+    int32_t* seed_j;
+    int32_t* seed_iter;
+};
+// Pass 2 of the search back (its arguments are `a`; the keys are cleared afterwards) and the
+// bookkeeping of iteration t.  mode 0: ordinary iteration; 1: last iteration (survivors are
+// reported as unconverged); 2: no iteration at all (max_iter == 0; no search back was made):
+// every seed is reported unconverged with (U^0, V^0).
+hipError_t launch_resolve_step(const SearchArgs& a, const StepArgs& st, int batch, int compute, int dp, hipStream_t s);
 hipError_t launch_recip_dedup(const RecipState& st, int32_t n_seeds, int batch,
                               const int32_t* seed_i, const int32_t* seed_j, const int32_t* seed_iter,
                               int32_t* pairs, int32_t* n_pairs, hipStream_t s);

@@ -35,20 +35,6 @@ constexpr int SEARCH_MIN_TILES = 8;
 constexpr int SEARCH_WAVES = 4;       // waves per workgroup
 constexpr int SEARCH_P = 4;           // candidate tiles in flight per wave
 
-__device__ __forceinline__ float max3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
-
-// Largest of `seed` and the 16 scores of one result fragment: eight 3-input max operations.
-__device__ __forceinline__ float fold16(float seed, const f32x16& x) {
-    const float t0 = max3(x[0], x[1], x[2]);
-    const float t1 = max3(x[3], x[4], x[5]);
-    const float t2 = max3(x[6], x[7], x[8]);
-    const float t3 = max3(x[9], x[10], x[11]);
-    const float t4 = max3(x[12], x[13], x[14]);
-    const float t5 = max3(t0, t1, t2);
-    const float t6 = max3(t3, t4, x[15]);
-    return max3(seed, t5, t6);
-}
-
 __device__ __forceinline__ int64_t query_row(const SearchArgs& a, int64_t qbase, int slot) {
     int64_t row;
     if (a.q_keys) row = (int64_t)(0xFFFFFFFFu - (uint32_t)(a.q_keys[qbase + slot] & 0xFFFFFFFFull));
@@ -86,19 +72,6 @@ __device__ __forceinline__ void query_rows(const SearchArgs& a, int64_t qbase, i
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) row[i] = min(max(row[i], 0), a.src_rows - 1);  // never read outside the map
-}
-
-// Holds the program at this point until the fragment has arrived.  Without it the waits for the query
-// loads are merged into the candidate loop, where they also drain the ring of tiles in flight down
-// to one on every trip.
-template <typename Frag>
-__device__ __forceinline__ void arrived(Frag& f) {
-    constexpr int WORDS = sizeof(Frag) / 4;
-    struct Words { uint32_t w[WORDS]; };
-    Words x = __builtin_bit_cast(Words, f);
-#pragma unroll
-    for (int i = 0; i < WORDS; ++i) asm volatile("" : "+v"(x.w[i]));
-    f = __builtin_bit_cast(Frag, x);
 }
 
 // One unit of pass 1: the query blocks of slots [slot0, slot0 + 32*R*G) against the candidate
@@ -488,60 +461,52 @@ void search_first_kernel(FirstSearchArgs fa) {
 
 // Pass 2: one wave per query recomputes the 32 scores of the winning tile with the same
 // matrix instruction (the query replicated into every column, so each score has the bits
-// pass 1 saw) and picks the lowest candidate that attains the maximum.  The key is
-// rewritten with the candidate index; optionally index and score are stored as well.
+// pass 1 saw) and picks the lowest candidate that attains the maximum.
+template <int CT, int DP>
+__device__ __forceinline__ Resolved resolve_tile(const SearchArgs& a, const char* tgt, u64 key, const typename Ops<CT, DP>::Frag& qf,
+                                                 int c, int h) {
+    using O = Ops<CT, DP>;
+    const int tile = max(0, min(key_index(key), a.m_tiles - 1));
+    const typename O::Frag cand = O::load(tgt + ((int64_t)tile * 32 + c) * O::ROW_BYTES, h);
+    return lowest_at_maximum(O::mma(cand, qf), tile, a.m, h);
+}
+
+// The key is rewritten with the candidate index; optionally index and score are stored as well.
+// clear_count: one count per pair that is set to 0 on the way (NULL: none).
 // load_query(b, row, h) supplies the query fragment.
 template <int CT, int DP, typename LoadQuery>
-__device__ __forceinline__ void resolve_body(const SearchArgs& a, int32_t* out_idx, float* out_score, LoadQuery load_query) {
-    using O = Ops<CT, DP>;
-    using Frag = typename O::Frag;
+__device__ __forceinline__ void resolve_body(const SearchArgs& a, int32_t* out_idx, float* out_score, int32_t* clear_count,
+                                             LoadQuery load_query) {
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_waves = gridDim.x * 4;
     const int b = blockIdx.y;
+    if (clear_count && blockIdx.x == 0 && threadIdx.x == 0) clear_count[b] = 0;
     int n_act = a.nq;
     if (a.nq_active) n_act = min(max(a.nq_active[b], 0), a.nq);
     const char* tgt = a.tgt + (int64_t)b * a.tgt_bstride;
     const int64_t qbase = (int64_t)b * a.nq;
-    const float ninf = -__builtin_inff();
 
     for (int slot = wave; slot < n_act; slot += n_waves) {
         const u64 key = a.out_keys[qbase + slot];
-        int32_t idx = -1;
-        float score = ninf;
+        const int64_t qrow = query_row(a, qbase, slot);  // fetched beside the key, not behind the test of it
+        Resolved res = {-1, -__builtin_inff()};
         if (key != 0) {
-            const int tile = min(key_index(key), a.m_tiles - 1);
-            const Frag qf = load_query(b, query_row(a, qbase, slot), h);
-            const Frag cand = O::load(tgt + ((int64_t)tile * 32 + c) * O::ROW_BYTES, h);
-            f32x16 acc = O::mma(cand, qf);
-            if (tile * 32 + 32 > a.m) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    if (tile * 32 + tile_row(v, h) >= a.m) acc[v] = ninf;
-            }
-            float top = fold16(ninf, acc);
-            top = __builtin_fmaxf(top, __shfl_xor(top, 32));
-            int row = 64;
-#pragma unroll
-            for (int v = 15; v >= 0; --v)
-                if (acc[v] == top) row = tile_row(v, h);
-            row = min(row, __shfl_xor(row, 32));
-            idx = tile * 32 + row;
-            score = top;
-            if (lane == 0) a.out_keys[qbase + slot] = pack_key(score, idx);
+            res = resolve_tile<CT, DP>(a, tgt, key, load_query(b, qrow, h), c, h);
+            if (lane == 0) a.out_keys[qbase + slot] = pack_key(res.score, res.idx);
         }
         if (lane == 0 && out_idx) {
-            out_idx[qbase + slot] = idx;
-            if (out_score) out_score[qbase + slot] = score;
+            out_idx[qbase + slot] = res.idx;
+            if (out_score) out_score[qbase + slot] = res.score;
         }
     }
 }
 
 template <int CT, int DP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-void resolve_kernel(SearchArgs a, int32_t* out_idx, float* out_score) {
+void resolve_kernel(SearchArgs a, int32_t* out_idx, float* out_score, int32_t* clear_count) {
     using O = Ops<CT, DP>;
-    resolve_body<CT, DP>(a, out_idx, out_score, [&](int b, int64_t row, int h) {
+    resolve_body<CT, DP>(a, out_idx, out_score, clear_count, [&](int b, int64_t row, int h) {
         return O::load(a.src + (int64_t)b * a.src_bstride + row * O::ROW_BYTES, h);
     });
 }
@@ -550,11 +515,76 @@ void resolve_kernel(SearchArgs a, int32_t* out_idx, float* out_score) {
 // fused first search rounds them).
 template <int CT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-void resolve_raw_kernel(FirstSearchArgs fa, int32_t* out_idx, float* out_score) {
+void resolve_raw_kernel(FirstSearchArgs fa, int32_t* out_idx, float* out_score, int32_t* clear_count) {
     using O = Ops<CT, 24>;
-    resolve_body<CT, 24>(fa.s, out_idx, out_score, [&](int b, int64_t row, int h) {
+    resolve_body<CT, 24>(fa.s, out_idx, out_score, clear_count, [&](int b, int64_t row, int h) {
         return O::round_raw(O::load_raw(fa.raw_src.map[b] + row * fa.raw_src.row_stride, h));
     });
+}
+
+// Pass 2 of the search back into image 1 and, in the same launch, the bookkeeping of the
+// iteration (section 3.2.5, steps 2-3): U^{t+1} is named, compared with U^t, and the seeds still
+// moving are compacted into the other half of the ping-pong state.  A wave takes one slot at a time;
+// a workgroup collects its survivors in LDS and reserves room for them with one atomic add per
+// round (an add and two barriers for every 16 slots took 41 instead of 22 us for the first step of 16
+// pairs), so the survivors' order differs from run to run; every result is filed under its seed's number
+// and the match set is sorted by a kernel of its own, so no output depends on it.  As a launch of its
+// own the bookkeeping took one workgroup per pair 4-16 us of every iteration with live seeds (its
+// share of a 1024x768 call was 30 us) and 1.6 us (2.5 us of host time) of every other.
+constexpr int STEP_WAVES = 16;
+constexpr int STEP_ROUND = 1024;  // slots a workgroup takes before it hands its survivors on (8 KB of LDS)
+template <int CT, int DP>
+__global__ __launch_bounds__(STEP_WAVES * 64)
+void resolve_step_kernel(SearchArgs a, StepArgs st) {
+    using O = Ops<CT, DP>;
+    __shared__ int2 moving[STEP_ROUND];  // survivors of a round: (U^{t+1}, seed number)
+    __shared__ int n_moving, first_pos;
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.y;
+    const int n_act = min(max(a.nq_active[b], 0), a.nq);
+    const char* src = a.src + (int64_t)b * a.src_bstride;
+    const char* tgt = a.tgt + (int64_t)b * a.tgt_bstride;
+    const int64_t base = (int64_t)b * a.nq;
+
+    for (int round = 0; round < n_act; round += gridDim.x * STEP_ROUND) {  // uniform in the launch's workgroups of this pair
+        if (threadIdx.x == 0) n_moving = 0;
+        __syncthreads();
+        // the workgroups take the slots of a round 16 at a time in turn, so that few slots spread over all of them
+        const int end = min(n_act, round + (int)gridDim.x * STEP_ROUND);
+        for (int slot = round + blockIdx.x * STEP_WAVES + wave; slot < end; slot += gridDim.x * STEP_WAVES) {  // uniform in the wave
+            const u64 kf = st.keys_f[base + slot];
+            const u64 kb = a.out_keys[base + slot];
+            const int32_t u = st.cur_u[base + slot];
+            const int32_t sid = st.seed_id[base + slot];
+            const int32_t v = key_index(kf);
+            int32_t u_next = -1;
+            if (kb != 0) {
+                const int64_t qrow = min(max(v, 0), a.src_rows - 1);
+                u_next = resolve_tile<CT, DP>(a, tgt, kb, O::load(src + qrow * O::ROW_BYTES, h), c, h).idx;
+            }
+            const bool converged = st.mode != 2 && u_next == u;
+            if (lane == 0) {
+                if (converged || st.mode != 0) {
+                    st.seed_i[base + sid] = u;
+                    st.seed_j[base + sid] = v;
+                    st.seed_iter[base + sid] = converged ? st.t : -1;
+                } else {
+                    moving[atomicAdd(&n_moving, 1)] = make_int2(u_next, sid);  // a round gives a workgroup at most STEP_ROUND slots
+                }
+                st.keys_f[base + slot] = 0;  // both tables start the next searches empty
+                a.out_keys[base + slot] = 0;
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) first_pos = n_moving ? atomicAdd(&st.next_active[b], n_moving) : 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < n_moving; i += STEP_WAVES * 64) {
+            st.next_u[base + first_pos + i] = moving[i].x;
+            st.next_seed_id[base + first_pos + i] = moving[i].y;
+        }
+        __syncthreads();  // the next round empties the list
+    }
 }
 
 // One resident wave per hardware slot: the grid is exactly what the chip holds at once
@@ -701,44 +731,77 @@ hipError_t launch_search_first(const FirstSearchArgs& a, int batch, int compute,
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_resolve_raw(const FirstSearchArgs& a, int batch, int compute, int32_t* out_idx, float* out_score, hipStream_t s) {
+hipError_t launch_resolve_raw(const FirstSearchArgs& a, int batch, int compute, int32_t* out_idx, float* out_score, int32_t* clear_count,
+                              hipStream_t s) {
     if (a.s.nq <= 0 || batch <= 0) return hipSuccess;
     int wgs = (a.s.nq + 3) / 4;
     const int cap = 2048 / batch > 64 ? 2048 / batch : 64;
     if (wgs > cap) wgs = cap;
-    if (compute == FNN_F16) return launch(TK_RESOLVE, resolve_raw_kernel<CT_F16>, dim3(wgs, batch), dim3(256), 0, s, a, out_idx, out_score);
-    if (compute == FNN_BF16) return launch(TK_RESOLVE, resolve_raw_kernel<CT_BF16>, dim3(wgs, batch), dim3(256), 0, s, a, out_idx, out_score);
+    if (compute == FNN_F16) return launch(TK_RESOLVE, resolve_raw_kernel<CT_F16>, dim3(wgs, batch), dim3(256), 0, s, a, out_idx, out_score, clear_count);
+    if (compute == FNN_BF16) return launch(TK_RESOLVE, resolve_raw_kernel<CT_BF16>, dim3(wgs, batch), dim3(256), 0, s, a, out_idx, out_score, clear_count);
     return hipErrorInvalidValue;
 }
 
 template <int CT, int DP>
-static hipError_t launch_resolve_t(const SearchArgs& a, int batch, int32_t* out_idx, float* out_score, hipStream_t s) {
+static hipError_t launch_resolve_t(const SearchArgs& a, int batch, int32_t* out_idx, float* out_score, int32_t* clear_count,
+                                   hipStream_t s) {
     int wgs = (a.nq + 3) / 4;
     const int cap = 2048 / batch > 64 ? 2048 / batch : 64;  // measured best: more waves only add dispatch time
     if (wgs > cap) wgs = cap;
-    return launch(TK_RESOLVE, resolve_kernel<CT, DP>, dim3(wgs, batch), dim3(256), 0, s, a, out_idx, out_score);
+    return launch(TK_RESOLVE, resolve_kernel<CT, DP>, dim3(wgs, batch), dim3(256), 0, s, a, out_idx, out_score, clear_count);
 }
 
 hipError_t launch_resolve(const SearchArgs& a, int batch, int compute, int dp, int32_t* out_idx, float* out_score,
-                          hipStream_t s) {
+                          int32_t* clear_count, hipStream_t s) {
     if (a.nq <= 0 || batch <= 0) return hipSuccess;
     if (compute == FNN_F16) {
-        if (dp == 16) return launch_resolve_t<CT_F16, 16>(a, batch, out_idx, out_score, s);
-        if (dp == 24) return launch_resolve_t<CT_F16, 24>(a, batch, out_idx, out_score, s);
-        if (dp == 32) return launch_resolve_t<CT_F16, 32>(a, batch, out_idx, out_score, s);
-        if (dp == 48) return launch_resolve_t<CT_F16, 48>(a, batch, out_idx, out_score, s);
-        if (dp == 64) return launch_resolve_t<CT_F16, 64>(a, batch, out_idx, out_score, s);
-        if (dp == 80) return launch_resolve_t<CT_F16, 80>(a, batch, out_idx, out_score, s);
-        if (dp == 96) return launch_resolve_t<CT_F16, 96>(a, batch, out_idx, out_score, s);
+        if (dp == 16) return launch_resolve_t<CT_F16, 16>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 24) return launch_resolve_t<CT_F16, 24>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 32) return launch_resolve_t<CT_F16, 32>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 48) return launch_resolve_t<CT_F16, 48>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 64) return launch_resolve_t<CT_F16, 64>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 80) return launch_resolve_t<CT_F16, 80>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 96) return launch_resolve_t<CT_F16, 96>(a, batch, out_idx, out_score, clear_count, s);
     } else if (compute == FNN_BF16) {
-        if (dp == 16) return launch_resolve_t<CT_BF16, 16>(a, batch, out_idx, out_score, s);
-        if (dp == 24) return launch_resolve_t<CT_BF16, 24>(a, batch, out_idx, out_score, s);
-        if (dp == 32) return launch_resolve_t<CT_BF16, 32>(a, batch, out_idx, out_score, s);
+        if (dp == 16) return launch_resolve_t<CT_BF16, 16>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 24) return launch_resolve_t<CT_BF16, 24>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 32) return launch_resolve_t<CT_BF16, 32>(a, batch, out_idx, out_score, clear_count, s);
     } else {
-        if (dp == 8) return launch_resolve_t<CT_F32, 8>(a, batch, out_idx, out_score, s);
-        if (dp == 16) return launch_resolve_t<CT_F32, 16>(a, batch, out_idx, out_score, s);
-        if (dp == 24) return launch_resolve_t<CT_F32, 24>(a, batch, out_idx, out_score, s);
-        if (dp == 32) return launch_resolve_t<CT_F32, 32>(a, batch, out_idx, out_score, s);
+        if (dp == 8) return launch_resolve_t<CT_F32, 8>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 16) return launch_resolve_t<CT_F32, 16>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 24) return launch_resolve_t<CT_F32, 24>(a, batch, out_idx, out_score, clear_count, s);
+        if (dp == 32) return launch_resolve_t<CT_F32, 32>(a, batch, out_idx, out_score, clear_count, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int CT, int DP>
+static hipError_t launch_resolve_step_t(const SearchArgs& a, const StepArgs& st, int batch, hipStream_t s) {
+    int wgs = (a.nq + STEP_WAVES - 1) / STEP_WAVES;
+    const int cap = 512 / batch > 16 ? 512 / batch : 16;  // two workgroups of 16 waves per compute unit are resident
+    if (wgs > cap) wgs = cap;
+    return launch(TK_RECIP_STEP, resolve_step_kernel<CT, DP>, dim3(wgs, batch), dim3(STEP_WAVES * 64), 0, s, a, st);
+}
+
+hipError_t launch_resolve_step(const SearchArgs& a, const StepArgs& st, int batch, int compute, int dp, hipStream_t s) {
+    if (a.nq <= 0 || batch <= 0) return hipSuccess;
+    if (compute == FNN_F16) {
+        if (dp == 16) return launch_resolve_step_t<CT_F16, 16>(a, st, batch, s);
+        if (dp == 24) return launch_resolve_step_t<CT_F16, 24>(a, st, batch, s);
+        if (dp == 32) return launch_resolve_step_t<CT_F16, 32>(a, st, batch, s);
+        if (dp == 48) return launch_resolve_step_t<CT_F16, 48>(a, st, batch, s);
+        if (dp == 64) return launch_resolve_step_t<CT_F16, 64>(a, st, batch, s);
+        if (dp == 80) return launch_resolve_step_t<CT_F16, 80>(a, st, batch, s);
+        if (dp == 96) return launch_resolve_step_t<CT_F16, 96>(a, st, batch, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 16) return launch_resolve_step_t<CT_BF16, 16>(a, st, batch, s);
+        if (dp == 24) return launch_resolve_step_t<CT_BF16, 24>(a, st, batch, s);
+        if (dp == 32) return launch_resolve_step_t<CT_BF16, 32>(a, st, batch, s);
+    } else {
+        if (dp == 8) return launch_resolve_step_t<CT_F32, 8>(a, st, batch, s);
+        if (dp == 16) return launch_resolve_step_t<CT_F32, 16>(a, st, batch, s);
+        if (dp == 24) return launch_resolve_step_t<CT_F32, 24>(a, st, batch, s);
+        if (dp == 32) return launch_resolve_step_t<CT_F32, 32>(a, st, batch, s);
     }
     return hipErrorInvalidValue;
 }

@@ -171,3 +171,16 @@ def test_hip_graph_capture_and_replay():
         torch.cuda.synchronize()
         for k in want:
             assert np.array_equal(host(again[k]), want[k]), (rep, k, "eager")
+
+
+@pytest.mark.parametrize("batch,n_seeds", [(1, 1537), (33, 16500)])
+def test_bookkeeping_over_several_rounds_of_slots(batch, n_seeds):
+    """The reciprocity test and compaction hand their survivors on once per round of 1024 slots per
+    workgroup: 16 500 seeds in a batch of 33 (16 workgroups per pair) need a second round, 1537 seeds
+    of one pair leave the last workgroup a single slot."""
+    a, b = exact_maps(5 + batch, 2100, 1999, 24)
+    seeds = np.random.default_rng(batch).integers(0, 2100, size=n_seeds).astype(np.int32)
+    ref = oracle.reciprocal(a, b, seeds, 4)
+    got = run_reciprocal([a] * batch, [b] * batch, np.repeat(seeds[None], batch, axis=0), 4, "f16")
+    for p in {0, batch - 1}:
+        check_reciprocal_exact(got, p, ref)
