@@ -522,27 +522,55 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         return FNN_OK;
     }
 
-    // the prepare launch also clears the key tables and the sort bitmap and sets U^0 = seeds
+    // the prepare launch also clears the key tables and the sort bitmap and sets U^0 = seeds (a small
+    // pair's own workgroup keeps all of that in LDS)
+    const bool walk = walk_applies(n, m, n_seeds, opts->max_iter, compute, L.maps.dp);
     PrepExtra extra;
     memset(&extra, 0, sizeof(extra));
-    extra.zero_ptr = L.st.keys_f;
-    extra.zero_count = L.zero_words;
-    extra.seeds = seeds;
-    extra.cur_u = L.st.cur_u[0];
-    extra.seed_id = L.st.seed_id[0];
-    extra.n_active = L.st.n_active[0];
-    extra.n_seeds = ns;
+    if (!walk) {
+        extra.zero_ptr = L.st.keys_f;
+        extra.zero_count = L.zero_words;
+        extra.seeds = seeds;
+        extra.cur_u = L.st.cur_u[0];
+        extra.seed_id = L.st.seed_id[0];
+        extra.n_active = L.st.n_active[0];
+        extra.n_seeds = ns;
+    }
     const char *p1 = (const char*)L.maps.p1, *p2 = (const char*)L.maps.p2;
     int64_t bs1 = L.maps.bstride1, bs2 = L.maps.bstride2;
     const bool direct1 = direct_layout(batch, d1, opts, L.maps.dp, &p1, &bs1);
     const bool direct2 = direct_layout(batch, d2, opts, L.maps.dp, &p2, &bs2);
     // fp32 maps of the paper's shape: no prepare pass; the first forward and the first backward
     // search read the caller's maps and leave the prepared copies behind for the later searches
-    const bool fused = raw_first_search(batch, d1, d2, opts, n_seeds);
+    const bool fused = !walk && raw_first_search(batch, d1, d2, opts, n_seeds);
     // the same LDS-staged kernel serves the first two searches on prepared 24-channel maps
     const bool staged = fused || (L.maps.dp == 24 && opts->compute != FNN_F32 && first_search_applies(n_seeds, n, batch) &&
                                   first_search_applies(n_seeds, m, batch));
     FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
+
+    if (walk) {
+        WalkArgs wa;
+        memset(&wa, 0, sizeof(wa));
+        wa.p1 = p1;
+        wa.p2 = p2;
+        wa.bstride1 = bs1;
+        wa.bstride2 = bs2;
+        wa.rows1 = (int32_t)L.maps.n_pad;
+        wa.rows2 = (int32_t)L.maps.m_pad;
+        wa.n = (int32_t)n;
+        wa.m = (int32_t)m;
+        wa.n_words = (int32_t)L.st.n_words;
+        wa.seeds = seeds;
+        wa.n_seeds = ns;
+        wa.max_iter = opts->max_iter;
+        wa.seed_i = seed_i;
+        wa.seed_j = seed_j;
+        wa.seed_iter = seed_iter;
+        wa.pairs = pairs;
+        wa.n_pairs = n_pairs;
+        FNN_TRY(launch_walk(wa, batch, compute, L.maps.dp, s));
+        return FNN_OK;
+    }
 
     SearchArgs fwd;  // queries in image 1 -> candidates in image 2
     memset(&fwd, 0, sizeof(fwd));

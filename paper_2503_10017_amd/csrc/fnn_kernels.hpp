@@ -189,6 +189,27 @@ hipError_t launch_recip_dedup(const RecipState& st, int32_t n_seeds, int batch,
                               const int32_t* seed_i, const int32_t* seed_j, const int32_t* seed_iter,
                               int32_t* pairs, int32_t* n_pairs, hipStream_t s);
 
+// The whole iteration of a small pair in one workgroup, on prepared maps; all outputs included.
+struct WalkArgs {
+    const char* p1;        // prepared maps of both images
+    const char* p2;
+    int64_t bstride1, bstride2;  // bytes per pair
+    int32_t rows1, rows2;  // rows per pair (row indices are clamped to them)
+    int32_t n, m;          // valid pixels
+    int32_t n_words;       // ceil(n / 32)
+    const int32_t* seeds;  // [batch][n_seeds]
+    int32_t n_seeds;
+    int32_t max_iter;
+    int32_t* seed_i;
+    int32_t* seed_j;
+    int32_t* seed_iter;
+    int32_t* pairs;
+    int32_t* n_pairs;
+};
+// true if a pair is small enough that one workgroup beats the launch sequence
+bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int compute, int dp);
+hipError_t launch_walk(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s);
+
 // ---- dense mutual nearest neighbours -----------------------------------------------------
 constexpr int DENSE_J = 4;      // candidate tiles resident per wave
 constexpr int DENSE_WAVES = 4;  // waves per workgroup

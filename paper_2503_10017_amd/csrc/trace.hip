@@ -95,6 +95,7 @@ const char* fnn_trace_kind_name(int32_t kind) {
         case TK_DENSE_RESOLVE: return "dense_resolve_kernels";
         case TK_BLOCKED: return "blocked_kernels";
         case TK_PIXELS: return "pairs_to_pixels_kernel";
+        case TK_RECIP_WALK: return "recip_walk_kernel";
         default: return "unknown";
     }
 }

@@ -21,7 +21,8 @@ enum TraceKind : int {
     TK_DENSE_RESOLVE = 10,
     TK_BLOCKED = 11,
     TK_PIXELS = 12,
-    TK_COUNT = 13
+    TK_RECIP_WALK = 13,
+    TK_COUNT = 14
 };
 
 // Returns false when no trace is open or it is full; otherwise hands out the next event pair.

@@ -1,0 +1,256 @@
+// The whole FastNN iteration of one image pair in one workgroup (paper section 3.2.5, "FastNN
+// Algorithm", steps 1-4), for pairs so small that the ordinary sequence -- four launches per
+// iteration, enqueued for every iteration the caller allows -- is launches and nothing else: a 64x48
+// pair with 48 seeds took 150 us at ten allowed iterations (43 launches at 2.5 us of host and 1.6 us
+// of device time and up), of which its arithmetic is 2 us.  Here the searches of a pair follow one
+// another behind workgroup barriers, and the loop really ends when no seed is left.
+//
+// What bounds it: at the smallest sizes the latency of a search (query rows, first tiles, LDS merge:
+// about 2 us), at the largest it takes the vector ALU of the one compute unit a pair occupies, which is
+// why the host stops choosing it where walk_applies() says.
+#include "fnn_device.hpp"
+#include "fnn_kernels.hpp"
+#include "trace.hpp"
+
+namespace fnn {
+
+constexpr int WALK_WAVES = 16;
+constexpr int WALK_THREADS = WALK_WAVES * 64;
+constexpr int WALK_MAX_SEEDS = WALK_THREADS;  // the compaction handles one slot per thread
+
+// Query blocks a wave multiplies with each loaded tile and tiles it keeps in flight: 128 registers
+// (four waves per SIMD) hold the query fragments, the results and the ring.
+template <int CT, int DP>
+struct WalkShape {
+    static constexpr int FRAG_REGS = Ops<CT, DP>::ROW_BYTES / 8;
+    static constexpr int R = FRAG_REGS <= 8 ? 2 : 1;
+    static constexpr int P = FRAG_REGS <= 6 ? 4 : 2;
+    static constexpr int Q = FRAG_REGS <= 6 ? 4 : (FRAG_REGS <= 8 ? 2 : 1);  // queries a wave resolves at a time
+};
+
+// Nearest candidate of every live slot: queries are rows[slot] of src, the answers go to found[slot].
+// Two passes as in the search of its own (search.hip): a unit of pass 1 is R query blocks against one
+// chunk of the tiles, shared among the 16 waves and merged in LDS; pass 2 recomputes each query's
+// winning tile, Q queries of a wave at a time so that their loads overlap.  (Tracking the candidate
+// itself in pass 1 needs no second pass but 40 more vector instructions per product: 229 us instead
+// of 142 us per call for a 128x96 pair with 192 seeds.)
+template <int CT, int DP>
+__device__ __forceinline__ void walk_search(const char* src, int src_rows, const int32_t* rows, const char* tgt, int m, int n_act,
+                                            u64* keys, int32_t* found) {
+    using O = Ops<CT, DP>;
+    using Frag = typename O::Frag;
+    constexpr int R = WalkShape<CT, DP>::R, P = WalkShape<CT, DP>::P, Q = WalkShape<CT, DP>::Q;
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float ninf = -__builtin_inff();
+    for (int s = threadIdx.x; s < n_act; s += WALK_THREADS) keys[s] = 0;
+    __syncthreads();  // rows (written by the caller) and the empty keys are visible
+
+    auto query = [&](int slot) {  // slots past the last live one repeat it; their results are dropped
+        const int32_t row = rows[min(slot, n_act - 1)];
+        return O::load(src + (int64_t)min(max(row, 0), src_rows - 1) * O::ROW_BYTES, h);
+    };
+    const int m_tiles = (m + 31) / 32;
+    const int groups = (n_act + 32 * R - 1) / (32 * R);
+    int chunks = max(1, WALK_WAVES / groups);
+    const int per_chunk = (m_tiles + chunks - 1) / chunks;
+    chunks = (m_tiles + per_chunk - 1) / per_chunk;
+    for (int unit = wave; unit < groups * chunks; unit += WALK_WAVES) {
+        const int slot0 = unit % groups * (32 * R);
+        const int t0 = unit / groups * per_chunk, t1 = min(t0 + per_chunk, m_tiles);
+        Frag ring[P], q[R];
+        float best[R];
+        int best_tile[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) q[r] = query(slot0 + r * 32 + c);
+#pragma unroll
+        for (int p = 0; p < P; ++p) ring[p] = O::load_tile(tgt + (int64_t)min(t0 + p, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            arrived(q[r]);
+            best[r] = ninf;
+            best_tile[r] = 0x7FFFFFFF;
+        }
+        for (int tb = t0; tb < t1; tb += P) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const int t = tb + p;
+                if (__builtin_expect(t < t1, 1)) {  // uniform
+                    const Frag cur = ring[p];
+                    ring[p] = O::load_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+                    f32x16 acc[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
+                    if (__builtin_expect(t * 32 + 32 > m, 0)) {  // only the last tile of the map can be partial
+                        const int bound = m - t * 32 - 4 * h;
+#pragma unroll
+                        for (int r = 0; r < R; ++r)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v)
+                                if (tile_row(v, 0) >= bound) acc[r][v] = ninf;
+                    }
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const float top = fold16(best[r], acc[r]);
+                        if (top > best[r]) best_tile[r] = t;  // strictly: the lowest tile wins among equal scores
+                        best[r] = top;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float ob = __shfl_xor(best[r], 32);
+            const int ot = __shfl_xor(best_tile[r], 32);
+            if (ob > best[r] || (ob == best[r] && ot < best_tile[r])) {
+                best[r] = ob;
+                best_tile[r] = ot;
+            }
+            const int slot = slot0 + r * 32 + c;
+            if (h == 0 && slot < n_act) atomicMax(&keys[slot], pack_key(best[r], best_tile[r]));
+        }
+    }
+    __syncthreads();
+    for (int s0 = wave * Q; s0 < n_act; s0 += WALK_WAVES * Q) {
+        Frag q[Q], cand[Q];
+        int tile[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            tile[i] = min(key_index(keys[min(s0 + i, n_act - 1)]), m_tiles - 1);
+            q[i] = query(s0 + i);
+            cand[i] = O::load(tgt + ((int64_t)tile[i] * 32 + c) * O::ROW_BYTES, h);
+        }
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int j = lowest_at_maximum(O::mma(cand[i], q[i]), tile[i], m, h).idx;
+            if (lane == 0 && s0 + i < n_act) found[s0 + i] = j;
+        }
+    }
+    __syncthreads();
+}
+
+// LDS (dynamic): keys[n_seeds], then u, v, w (U^t, V^t, U^{t+1}) and the seed number per slot, then
+// the bitmap of the matched pixels of image 1 and the rank of each of its words.
+template <int CT, int DP>
+__global__ __launch_bounds__(WALK_THREADS) void recip_walk_kernel(WalkArgs a) {
+    extern __shared__ u64 walk_lds[];
+    __shared__ int wave_sums[17];
+    u64* keys = walk_lds;
+    int32_t* u = reinterpret_cast<int32_t*>(keys + a.n_seeds);
+    int32_t* v = u + a.n_seeds;
+    int32_t* w = v + a.n_seeds;
+    int32_t* sid = w + a.n_seeds;
+    uint32_t* bitmap = reinterpret_cast<uint32_t*>(sid + a.n_seeds);
+    int32_t* word_rank = reinterpret_cast<int32_t*>(bitmap + a.n_words);
+    const int b = blockIdx.x, me = threadIdx.x;
+    const int64_t base = (int64_t)b * a.n_seeds;
+    const char* p1 = a.p1 + (int64_t)b * a.bstride1;
+    const char* p2 = a.p2 + (int64_t)b * a.bstride2;
+
+    int n_act = a.n_seeds;
+    if (me < n_act) {
+        u[me] = a.seeds[base + me];
+        sid[me] = me;
+    }
+    for (int i = me; i < a.n_words; i += WALK_THREADS) bitmap[i] = 0;
+    for (int t = 0; n_act > 0; ++t) {  // n_act is uniform in the workgroup; it is 0 after max_iter trips at the latest
+        walk_search<CT, DP>(p1, a.rows1, u, p2, a.m, n_act, keys, v);       // V^t = NN_2(U^t)
+        if (a.max_iter > 0) walk_search<CT, DP>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
+        const bool last = t + 1 >= a.max_iter;
+        bool survive = false;
+        int32_t u_next = 0, my_sid = 0;
+        if (me < n_act) {
+            my_sid = sid[me];
+            u_next = w[me];
+            const bool converged = a.max_iter > 0 && u_next == u[me];
+            survive = !converged && !last;
+            if (!survive) {
+                a.seed_i[base + my_sid] = u[me];
+                a.seed_j[base + my_sid] = v[me];
+                a.seed_iter[base + my_sid] = converged ? t : -1;
+                if (converged) atomicOr(&bitmap[(uint32_t)u_next >> 5], 1u << (u_next & 31));
+            }
+        }
+        int kept;
+        const int pos = block_scan_flag(survive, wave_sums, kept);  // its barriers also end the reads of u and sid above
+        if (survive) {
+            u[pos] = u_next;
+            sid[pos] = my_sid;
+        }
+        n_act = kept;
+    }
+
+    // step 4: the matches as a set, sorted (see recip_dedup_kernel).  A converged seed's pixels are
+    // read back from the outputs by the thread that handles the seed.
+    __threadfence_block();
+    __syncthreads();
+    const int per_thread = (a.n_words + WALK_THREADS - 1) / WALK_THREADS;
+    const int w0 = min(me * per_thread, a.n_words), w1 = min(w0 + per_thread, a.n_words);
+    int mine = 0;
+    for (int i = w0; i < w1; ++i) mine += __popc(bitmap[i]);
+    int count;
+    int rank = block_scan_int(mine, wave_sums, count);
+    for (int i = w0; i < w1; ++i) {
+        word_rank[i] = rank;
+        rank += __popc(bitmap[i]);
+    }
+    __syncthreads();
+    if (me < a.n_seeds && a.seed_iter[base + me] >= 0) {
+        const uint32_t i = (uint32_t)a.seed_i[base + me];
+        const int pos = word_rank[i >> 5] + __popc(bitmap[i >> 5] & ((1u << (i & 31)) - 1u));
+        a.pairs[(base + pos) * 2 + 0] = (int32_t)i;
+        a.pairs[(base + pos) * 2 + 1] = a.seed_j[base + me];
+    }
+    if (me >= count && me < a.n_seeds) {
+        a.pairs[(base + me) * 2 + 0] = -1;
+        a.pairs[(base + me) * 2 + 1] = -1;
+    }
+    if (me == 0) a.n_pairs[b] = count;
+}
+
+static size_t walk_lds_bytes(int64_t n, int64_t n_seeds) {
+    return (size_t)n_seeds * (sizeof(u64) + 4 * sizeof(int32_t)) + (size_t)((n + 31) / 32) * 2 * sizeof(int32_t);
+}
+
+// Where one workgroup per pair beats the launch sequence.  Measured on the benchmark's maps (three
+// iterations with live seeds), microseconds per call, one pair, fp16, 24 channels: the sequence costs
+// 24 + 13 * max_iter whatever the size up to 160x120; the walk 36 at 192 products of 32x32 scores
+// per search (64x48, 48 seeds), 72 at 576, 81 at 768, 142 at 2304.  At ten allowed iterations the lines
+// would cross near 2000 products; 1000 keeps a walk whose seeds all move to the end (every search at
+// full size) within twice the sequence.  At two allowed iterations 192 products take 36 against 45.  Wide
+// rows and fp32 products cost about five times as much per product (192 products: 80 and 84).
+bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int compute, int dp) {
+    if (n_seeds < 1 || n_seeds > WALK_MAX_SEEDS || n < 1 || m < 1 || walk_lds_bytes(n, n_seeds) > 60 * 1024) return false;
+    const int64_t products = (n_seeds + 31) / 32 * (((n > m ? n : m) + 31) / 32);
+    const int64_t price = compute == FNN_F32 || dp > 32 ? 5 : 1;
+    return products * price <= 100 * (int64_t)(max_iter < 10 ? max_iter : 10);
+}
+
+template <int CT, int DP>
+static hipError_t launch_walk_t(const WalkArgs& a, int batch, hipStream_t s) {
+    return launch(TK_RECIP_WALK, recip_walk_kernel<CT, DP>, dim3(batch), dim3(WALK_THREADS), walk_lds_bytes(a.n, a.n_seeds), s, a);
+}
+
+hipError_t launch_walk(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s) {
+    if (compute == FNN_F16) {
+        if (dp == 16) return launch_walk_t<CT_F16, 16>(a, batch, s);
+        if (dp == 24) return launch_walk_t<CT_F16, 24>(a, batch, s);
+        if (dp == 32) return launch_walk_t<CT_F16, 32>(a, batch, s);
+        if (dp == 48) return launch_walk_t<CT_F16, 48>(a, batch, s);
+        if (dp == 64) return launch_walk_t<CT_F16, 64>(a, batch, s);
+        if (dp == 80) return launch_walk_t<CT_F16, 80>(a, batch, s);
+        if (dp == 96) return launch_walk_t<CT_F16, 96>(a, batch, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 16) return launch_walk_t<CT_BF16, 16>(a, batch, s);
+        if (dp == 24) return launch_walk_t<CT_BF16, 24>(a, batch, s);
+        if (dp == 32) return launch_walk_t<CT_BF16, 32>(a, batch, s);
+    } else {
+        if (dp == 8) return launch_walk_t<CT_F32, 8>(a, batch, s);
+        if (dp == 16) return launch_walk_t<CT_F32, 16>(a, batch, s);
+        if (dp == 24) return launch_walk_t<CT_F32, 24>(a, batch, s);
+        if (dp == 32) return launch_walk_t<CT_F32, 32>(a, batch, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace fnn
