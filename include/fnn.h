@@ -99,7 +99,7 @@ typedef struct {
 /*
  * FNN_FLAG_NORMALIZE: the maps are raw matching-head outputs (section 3.2.4, "Matching Head");
  * every descriptor is divided by its Euclidean norm before the cast to the compute format:
- * norm2 = sum_k x[k]*x[k] in fp32 (k ascending, products and sums rounded separately),
+ * norm2 = sum_k x[k]*x[k] in fp32 (k ascending; a product may be fused with its addition),
  * y[k] = x[k] / sqrt(norm2) with correctly rounded fp32 sqrt and division; an all-zero
  * descriptor stays zero.  The step is fused into the prepare pass.
  */

@@ -64,6 +64,7 @@ struct PrepSide {
     int32_t segment_major;           // 1: rows are stored in the dense kernel's segment-major order
     int64_t row_stride;              // source row stride, elements
     int32_t dtype;                   // source storage format
+    int32_t vector_rows;             // set by the launcher: rows may be copied whole in 16-byte pieces
     int32_t second_image;            // L2 score: 0 = rows [x, 1.., -|x|^2/2..], 1 = rows [x, -|x|^2/2.., 1..]
     void* dst;                       // [batch][n_pad][dp] in the compute format
 };

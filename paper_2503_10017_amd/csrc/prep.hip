@@ -18,15 +18,15 @@ __device__ __forceinline__ float load_as_float(const void* base, int64_t idx, in
     return __uint_as_float((uint32_t)raw << 16);
 }
 
-// Euclidean norm of one source descriptor as FNN_FLAG_NORMALIZE defines it: squares and
-// sums rounded separately (no fused multiply-add), channels in ascending order.
-__device__ __forceinline__ float descriptor_norm(const void* src, int64_t first, int d, int dtype) {
-    float sum = 0.0f;
-    for (int k = 0; k < d; ++k) {
-        const float x = load_as_float(src, first + k, dtype);
-        sum = __fadd_rn(sum, __fmul_rn(x, x));
-    }
-    return __fsqrt_rn(sum);
+// The same for the raw bits of one 16-bit element.
+__device__ __forceinline__ float bits_as_float(uint16_t raw, int dtype) {
+    return dtype == FNN_F16 ? (float)__builtin_bit_cast(_Float16, raw) : __uint_as_float((uint32_t)raw << 16);
+}
+
+typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint4 pack8(const uint16_t* x) {
+    return make_uint4(x[0] | ((uint32_t)x[1] << 16), x[2] | ((uint32_t)x[3] << 16), x[4] | ((uint32_t)x[5] << 16), x[6] | ((uint32_t)x[7] << 16));
 }
 
 // x as the compute format holds it (round to nearest even), back in fp32.
@@ -34,20 +34,6 @@ __device__ __forceinline__ float round_to_compute(float x, int compute) {
     if (compute == FNN_F16) return (float)(_Float16)x;
     if (compute == FNN_BF16) return __uint_as_float((uint32_t)float_to_bf16_rne(x) << 16);
     return x;
-}
-
-// -1/2 * |x|^2 of one descriptor AS PREPARED (normalised if asked, rounded to the compute
-// format): fp32 sum, channels ascending, squares and sums rounded separately.
-__device__ __forceinline__ float minus_half_norm2(const void* src, int64_t first, int d, int dtype, int compute,
-                                                  float divide_by) {
-    float sum = 0.0f;
-    for (int k = 0; k < d; ++k) {
-        float x = load_as_float(src, first + k, dtype);
-        if (divide_by > 0.0f) x = __fdiv_rn(x, divide_by);
-        x = round_to_compute(x, compute);
-        sum = __fadd_rn(sum, __fmul_rn(x, x));
-    }
-    return -0.5f * sum;
 }
 
 // Side jobs spread over all threads of the launch (see PrepExtra).
@@ -67,7 +53,8 @@ __device__ __forceinline__ void prep_side_jobs(const PrepArgs& a) {
     }
 }
 
-// One thread produces 8 consecutive channels of one output row.
+// Plain casts of any storage format, channel count, row stride and alignment: one thread produces 8
+// consecutive channels of one output row, element by element.
 __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
     prep_side_jobs(a);
     const int side_idx = blockIdx.y / a.batch;
@@ -83,54 +70,11 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
         const int64_t row = item / groups;                               // stored row
         const int64_t pix = sd.segment_major ? slot_pixel(row) : row;   // pixel it holds
         const int g = (int)(item % groups);
-        // channels that carry data: the descriptor, or three copies of it (FNN_FLAG_SPLIT)
-        const int data_channels = a.split ? 3 * a.d : a.d;
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int k = g * 8 + e;
-            const int ch = a.split ? k % a.d : k;
-            v[e] = (pix < sd.n && k < data_channels) ? load_as_float(src, pix * sd.row_stride + ch, sd.dtype) : 0.0f;
-        }
-        float norm = 0.0f;
-        if (a.normalize && pix < sd.n) {
-            norm = descriptor_norm(src, pix * sd.row_stride, a.d, sd.dtype);
-            if (norm > 0.0f) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = __fdiv_rn(v[e], norm);
-            }
-        }
-        // Two-term fp16 representation: copy 0 holds hi, and of copies 1 and 2 image 1 holds
-        // (hi, lo), image 2 (lo, hi), so that a row of one times a row of the other sums
-        // hi*hi + hi*lo + lo*hi.
-        if (a.split) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int k = g * 8 + e;
-                if (k < data_channels) {
-                    const int copy = k / a.d;
-                    const float hi = (float)(_Float16)v[e];
-                    const float lo = (float)(_Float16)__fsub_rn(v[e], hi);
-                    v[e] = (copy == 0 || copy == (sd.second_image ? 2 : 1)) ? hi : lo;
-                }
-            }
-        }
-        // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2).  For a
-        // 16-bit format the norm term is split into a rounded value and the rounded remainder.
-        const int extra = a.compute == FNN_F32 ? 1 : 2;
-        if (a.l2 && pix < sd.n && g * 8 + 8 > a.d && g * 8 < a.d + 2 * extra) {
-            const float term = minus_half_norm2(src, pix * sd.row_stride, a.d, sd.dtype, a.compute, norm);
-            const float hi = round_to_compute(term, a.compute);
-            const float lo = round_to_compute(term - hi, a.compute);
-            const int ones0 = a.d + (sd.second_image ? extra : 0);   // first unit channel
-            const int term0 = a.d + (sd.second_image ? 0 : extra);   // first norm channel
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int k = g * 8 + e;
-                if (k >= ones0 && k < ones0 + extra) v[e] = 1.0f;
-                if (k == term0) v[e] = hi;
-                if (extra == 2 && k == term0 + 1) v[e] = lo;
-            }
+            v[e] = (pix < sd.n && k < a.d) ? load_as_float(src, pix * sd.row_stride + k, sd.dtype) : 0.0f;
         }
         if (a.compute == FNN_F32) {
             float4* out = reinterpret_cast<float4*>(dst + (row * a.dp + g * 8) * 4);
@@ -151,10 +95,243 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
     }
 }
 
+// The options that need a whole row at once (FNN_FLAG_NORMALIZE, FNN_FLAG_L2, FNN_FLAG_SPLIT), for any
+// storage format, channel count, row stride and alignment.
+// A workgroup takes STAGE_ROWS stored rows at a time: it copies the rows' bytes into LDS as they lie in
+// memory (16 bytes per lane where the rows are aligned and close together, else one element per
+// lane), every thread then makes one output row in registers, and the finished rows leave LDS as
+// one contiguous run of 16-byte stores.  What bounds it is the memory traffic.  One 512x384 pair, 24
+// channels, before (every thread reading its part of a row element by element, and the whole row
+// again for a norm; with FNN_FLAG_SPLIT one thread per row, lanes 96 bytes in and 160 bytes out
+// apart) and now, microseconds: fp16 maps with FNN_FLAG_L2 39.6 / 16.6, with FNN_FLAG_NORMALIZE
+// 35.2 / 14.4, fp32 maps with FNN_FLAG_SPLIT 32.3 / 19.4; 17-channel fp32 maps with
+// FNN_FLAG_NORMALIZE 34.1 / 17.9 (two pairs with L2 69.6 / 26.0, four with SPLIT 115 / 64); maps of a few thousand pixels between 4 us less and 2 us more.  Plain
+// casts stay with the kernel above (23-channel bf16 14 against 16 us, small maps 4 against 8).
+constexpr int STAGE_ROWS = 256;
+constexpr int STAGE_MAX_ROW_BYTES = 192;  // widest row held in LDS (48 KB per workgroup)
+
+// Pixel that staged row r of the run of stored rows [row0, row0 + STAGE_ROWS) holds, and the place of that
+// pixel's output row in the run.  Segment major: the run is blocks t0..t0+7 of a super-block, staged as
+// 32 runs of 8 consecutive pixels.
+struct StageRun {
+    int64_t first;   // natural order: the first pixel; segment major: the super-block's pixel t0 of lane 0
+    bool segments;
+    __device__ __forceinline__ StageRun(int64_t row0, bool segment_major) : segments(segment_major) {
+        first = segment_major ? slot_pixel(row0) : row0;
+    }
+    __device__ __forceinline__ int64_t pixel(int r) const { return segments ? first + (int64_t)(r >> 3) * DENSE_S + (r & 7) : first + r; }
+    __device__ __forceinline__ int out_row(int r) const { return segments ? (r & 7) * 32 + (r >> 3) : r; }
+};
+static_assert(STAGE_ROWS == 32 * 8 && DENSE_S % 8 == 0, "a run of stored rows is 8 whole blocks of one super-block");
+
+// IN = ceil(d / 8).
+template <int IN, int COMPUTE>
+__global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
+    extern __shared__ uint4 stage[];
+    prep_side_jobs(a);
+    const int side_idx = blockIdx.y / a.batch;
+    const int b = blockIdx.y % a.batch;
+    const PrepSide& sd = a.side[side_idx];
+    constexpr int ESIZE = (COMPUTE == FNN_F32) ? 4 : 2;
+    constexpr int EXTRA = (COMPUTE == FNN_F32) ? 1 : 2;  // channels per L2 term
+    const int tid = threadIdx.x, d = a.d;
+    const int es = sd.dtype == FNN_F32 ? 4 : 2;
+    const int pitch = sd.vector_rows ? (int)sd.row_stride * es : d * es;  // bytes between staged rows
+    const int out_bytes = a.dp * ESIZE;
+    const char* src = reinterpret_cast<const char*>(sd.src[b]);
+    char* dst = reinterpret_cast<char*>(sd.dst) + (int64_t)b * sd.n_pad * out_bytes;
+    char* lds = reinterpret_cast<char*>(stage);
+    const int64_t valid = (sd.n - 1) * sd.row_stride * es + (int64_t)d * es;  // bytes of the map (n > 0 here or no row is read)
+
+    for (int64_t row0 = (int64_t)blockIdx.x * STAGE_ROWS; row0 < sd.n_pad; row0 += (int64_t)gridDim.x * STAGE_ROWS) {
+        const StageRun run(row0, sd.segment_major != 0);
+        if (sd.vector_rows) {
+            const int seg_units = (run.segments ? 8 : STAGE_ROWS) * pitch / 16;
+            const int units = STAGE_ROWS * pitch / 16;
+            auto offset = [&](int u) -> int64_t {
+                const int seg = run.segments ? u / seg_units : 0;
+                return run.pixel(seg * 8) * pitch + (int64_t)(u - seg * seg_units) * 16;
+            };
+            for (int u0 = tid; u0 < units; u0 += 4 * STAGE_ROWS) {  // four loads in flight per lane
+                words4 x[4];
+                bool whole[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int u = u0 + i * STAGE_ROWS;
+                    const int64_t off = offset(u);
+                    whole[i] = u < units && off + 16 <= valid;
+                    x[i] = whole[i] ? *reinterpret_cast<const words4*>(src + off) : (words4)(0u);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int u = u0 + i * STAGE_ROWS;
+                    if (whole[i]) {
+                        reinterpret_cast<words4*>(stage)[u] = x[i];
+                    } else if (u < units) {  // the end of the map: only whole elements inside it
+                        const int64_t off = offset(u);
+                        for (int e = 0; e < 16 && off + e + es <= valid; e += es) {
+                            if (es == 4) *reinterpret_cast<uint32_t*>(lds + u * 16 + e) = *reinterpret_cast<const uint32_t*>(src + off + e);
+                            else *reinterpret_cast<uint16_t*>(lds + u * 16 + e) = *reinterpret_cast<const uint16_t*>(src + off + e);
+                        }
+                    }
+                }
+            }
+        } else {
+            for (int i0 = tid; i0 < STAGE_ROWS * d; i0 += 8 * STAGE_ROWS) {  // eight loads in flight per lane
+                uint32_t x[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int i = i0 + k * STAGE_ROWS, r = i / d, ch = i - r * d;
+                    const int64_t pix = run.pixel(min(r, STAGE_ROWS - 1));
+                    const int64_t at = min(pix, sd.n - 1) * sd.row_stride + ch;  // rows past the map repeat the last one, see `real`
+                    x[k] = es == 4 ? reinterpret_cast<const uint32_t*>(src)[at] : reinterpret_cast<const uint16_t*>(src)[at];
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int i = i0 + k * STAGE_ROWS;
+                    if (i < STAGE_ROWS * d) {
+                        if (es == 4) *reinterpret_cast<uint32_t*>(lds + i * 4) = x[k];
+                        else *reinterpret_cast<uint16_t*>(lds + i * 2) = (uint16_t)x[k];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+
+        float v[IN * 8];
+        const bool real = run.pixel(tid) < sd.n;  // rows past the map are zero
+        const char* row = lds + tid * pitch;
+        if (d == IN * 8 && pitch % 16 == 0) {  // uniform
+            if (es == 4) {
+#pragma unroll
+                for (int q = 0; q < IN * 2; ++q) {
+                    const float4 x = reinterpret_cast<const float4*>(row)[q];
+                    v[4 * q + 0] = x.x;
+                    v[4 * q + 1] = x.y;
+                    v[4 * q + 2] = x.z;
+                    v[4 * q + 3] = x.w;
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < IN; ++q) {
+                    const uint4 x = reinterpret_cast<const uint4*>(row)[q];
+                    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[8 * q + e] = bits_as_float((uint16_t)(w[e / 2] >> (16 * (e & 1))), sd.dtype);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < IN * 8; ++k) v[k] = k < d ? load_as_float(row, k, sd.dtype) : 0.0f;
+        }
+        if (!real) {
+#pragma unroll
+            for (int k = 0; k < IN * 8; ++k) v[k] = 0.0f;
+        }
+        __syncthreads();  // the staged rows are in registers: the finished ones may take their place
+
+        // Channels at and past d are zero, so they change neither sum.  The sums run over fused
+        // multiply-adds in ascending order, which is what the element-by-element loops compiled to.
+        if (a.normalize) {
+            float sum = 0.0f;
+#pragma unroll
+            for (int k = 0; k < IN * 8; ++k) sum = __builtin_fmaf(v[k], v[k], sum);
+            const float norm = __builtin_sqrtf(sum);  // correctly rounded
+            if (norm > 0.0f) {
+#pragma unroll
+                for (int k = 0; k < IN * 8; ++k) v[k] = __fdiv_rn(v[k], norm);
+            }
+        }
+        char* out = lds + run.out_row(tid) * out_bytes;
+        if (COMPUTE == FNN_F16 && a.split) {
+            // copy 0 holds hi, and of copies 1 and 2 image 1 holds (hi, lo), image 2 (lo, hi), so that a row
+            // of one times a row of the other sums hi*hi + hi*lo + lo*hi
+            const int lo_copy = sd.second_image ? 1 : 2;
+            uint16_t hi[IN * 8], lo[IN * 8];
+#pragma unroll
+            for (int k = 0; k < IN * 8; ++k) {
+                const _Float16 x = (_Float16)v[k];
+                hi[k] = __builtin_bit_cast(uint16_t, x);
+                lo[k] = float_to_f16_rne(__fsub_rn(v[k], (float)x));
+            }
+            if (d == IN * 8) {  // uniform: a copy is IN whole 16-byte vectors
+#pragma unroll
+                for (int g = 0; g < IN; ++g) {
+                    const uint4 h4 = pack8(hi + 8 * g), l4 = pack8(lo + 8 * g);
+                    uint4* o = reinterpret_cast<uint4*>(out) + g;
+                    o[0] = h4;
+                    o[lo_copy * IN] = l4;
+                    o[(3 - lo_copy) * IN] = h4;
+                }
+                for (int q = 3 * IN; q < a.dp / 8; ++q) reinterpret_cast<uint4*>(out)[q] = make_uint4(0, 0, 0, 0);
+            } else {
+                uint16_t* o = reinterpret_cast<uint16_t*>(out);
+#pragma unroll
+                for (int k = 0; k < IN * 8; ++k) {
+                    if (k < d) {
+                        o[k] = hi[k];
+                        o[lo_copy * d + k] = lo[k];
+                        o[(3 - lo_copy) * d + k] = hi[k];
+                    }
+                }
+                for (int k = 3 * d; k < a.dp; ++k) o[k] = 0;
+            }
+        } else {
+            // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2).  For a 16-bit
+            // format the norm term is split into a rounded value and the rounded remainder.
+            float hi = 0.0f, lo = 0.0f;
+            if (a.l2) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int k = 0; k < IN * 8; ++k) {
+                    const float x = round_to_compute(v[k], COMPUTE);
+                    sum = __builtin_fmaf(x, x, sum);
+                }
+                const float term = -0.5f * sum;
+                hi = round_to_compute(term, COMPUTE);
+                lo = round_to_compute(term - hi, COMPUTE);
+            }
+            const bool extras = a.l2 && real;
+            const int ones0 = d + (sd.second_image ? EXTRA : 0);   // first unit channel
+            const int term0 = d + (sd.second_image ? 0 : EXTRA);   // first norm channel
+            auto channel = [&](int k) -> float {  // k is known at compile time, d is uniform
+                float x = k < IN * 8 ? v[k < IN * 8 ? k : 0] : 0.0f;
+                if (extras) {
+                    if (k >= ones0 && k < ones0 + EXTRA) x = 1.0f;
+                    if (k == term0) x = hi;
+                    if (EXTRA == 2 && k == term0 + 1) x = lo;
+                }
+                return x;
+            };
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q * 8 < a.dp) {  // uniform
+                    if (COMPUTE == FNN_F32) {
+                        float4* o = reinterpret_cast<float4*>(out) + 2 * q;
+                        o[0] = make_float4(channel(8 * q), channel(8 * q + 1), channel(8 * q + 2), channel(8 * q + 3));
+                        o[1] = make_float4(channel(8 * q + 4), channel(8 * q + 5), channel(8 * q + 6), channel(8 * q + 7));
+                    } else {
+                        uint16_t bits[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            bits[e] = (COMPUTE == FNN_F16) ? float_to_f16_rne(channel(8 * q + e)) : float_to_bf16_rne(channel(8 * q + e));
+                        reinterpret_cast<uint4*>(out)[q] = pack8(bits);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        const int n_out = (int)min((int64_t)STAGE_ROWS, sd.n_pad - row0);
+        uint4* to = reinterpret_cast<uint4*>(dst + row0 * out_bytes);
+        for (int u = tid; u < n_out * out_bytes / 16; u += STAGE_ROWS) to[u] = stage[u];
+        __syncthreads();  // the next run is staged in the same place
+    }
+}
+
 // Fast path for the options that need a whole row at once (FNN_FLAG_NORMALIZE, FNN_FLAG_L2) on
 // fp32 sources with d a multiple of 8: one thread per row.  The row is read once with 16-byte
-// loads; norm and squared length are formed in registers exactly as descriptor_norm and
-// minus_half_norm2 define them (channels ascending, every product and sum rounded on its own).
+// loads; norm and squared length are formed in registers (channels ascending, every product and sum
+// rounded on its own).
 // IN = d / 8, OUT = dp / 8.
 template <int IN, int OUT, int COMPUTE>
 __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
@@ -234,71 +411,6 @@ __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
     }
 }
 
-// FNN_FLAG_SPLIT on fp32 sources with d = 8 * IN whole 16-byte vectors: one thread per row
-// reads the descriptor once and writes its three copies (see prep_kernel for the layout).
-template <int IN>
-__global__ __launch_bounds__(256) void prep_split_rows_kernel(PrepArgs a) {
-    prep_side_jobs(a);
-    const int side_idx = blockIdx.y / a.batch;
-    const int b = blockIdx.y % a.batch;
-    const PrepSide& sd = a.side[side_idx];
-    constexpr int D = IN * 8, DP = padded_d(3 * D, FNN_F16);
-    char* dst = reinterpret_cast<char*>(sd.dst) + (int64_t)b * sd.n_pad * DP * 2;
-    const float* src = reinterpret_cast<const float*>(sd.src[b]);
-    const int lo_copy = sd.second_image ? 1 : 2;  // which of copies 1, 2 holds the lo terms
-    for (uint32_t row = blockIdx.x * blockDim.x + threadIdx.x; row < (uint32_t)sd.n_pad; row += gridDim.x * blockDim.x) {
-        const int64_t pix = sd.segment_major ? slot_pixel(row) : (int64_t)row;
-        uint32_t hi[D], lo[D];
-#pragma unroll
-        for (int e = 0; e < D; ++e) hi[e] = lo[e] = 0;
-        if (pix < sd.n) {
-            float v[D];
-            const float4* p = reinterpret_cast<const float4*>(src + pix * sd.row_stride);
-#pragma unroll
-            for (int q = 0; q < IN * 2; ++q) {
-                const float4 x = p[q];
-                v[4 * q + 0] = x.x;
-                v[4 * q + 1] = x.y;
-                v[4 * q + 2] = x.z;
-                v[4 * q + 3] = x.w;
-            }
-            if (a.normalize) {
-                float sum = 0.0f;
-#pragma unroll
-                for (int e = 0; e < D; ++e) sum = __fadd_rn(sum, __fmul_rn(v[e], v[e]));
-                const float norm = __fsqrt_rn(sum);
-                if (norm > 0.0f) {
-#pragma unroll
-                    for (int e = 0; e < D; ++e) v[e] = __fdiv_rn(v[e], norm);
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < D; ++e) {
-                const _Float16 h = (_Float16)v[e];
-                hi[e] = __builtin_bit_cast(uint16_t, h);
-                lo[e] = float_to_f16_rne(__fsub_rn(v[e], (float)h));
-            }
-        }
-        uint4* out = reinterpret_cast<uint4*>(dst + (int64_t)row * DP * 2);
-#pragma unroll
-        for (int q = 0; q < DP / 8; ++q) {
-            uint32_t w[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                uint32_t half[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int k = 8 * q + 2 * e + t;       // compile-time channel of the output row
-                    const int copy = k / D, ch = k % D;
-                    half[t] = (k >= 3 * D) ? 0u : ((copy == lo_copy) ? lo[ch] : hi[ch]);
-                }
-                w[e] = half[0] | (half[1] << 16);
-            }
-            out[q] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-    }
-}
-
 template <int IN, int OUT>
 static hipError_t launch_prep_rows(const PrepArgs& a, dim3 grid, hipStream_t s) {
     if (a.compute == FNN_F32) return launch(TK_PREP, prep_rows_f32_kernel<IN, OUT, FNN_F32>, grid, dim3(256), 0, s, a);
@@ -356,6 +468,29 @@ static hipError_t launch_prep_fast(const PrepArgs& a, dim3 grid, hipStream_t s) 
     return launch(TK_PREP, prep_f32_kernel<GROUPS, FNN_BF16>, grid, dim3(256), 0, s, a);
 }
 
+template <int IN>
+static hipError_t launch_prep_staged(PrepArgs a, hipStream_t s) {
+    int64_t most = 0;
+    int row_bytes = a.dp * elem_size(a.compute);
+    for (int i = 0; i < a.n_sides; ++i) {
+        PrepSide& sd = a.side[i];
+        const int64_t stride_bytes = sd.row_stride * elem_size(sd.dtype);
+        // rows copied whole, gaps included: 16-byte aligned maps whose rows lie close together
+        sd.vector_rows = sd.row_stride <= STAGE_MAX_ROW_BYTES && stride_bytes <= STAGE_MAX_ROW_BYTES && sd.row_stride <= 2 * (int64_t)a.d;
+        for (int b = 0; b < a.batch && sd.vector_rows; ++b) sd.vector_rows = ((uintptr_t)sd.src[b] % 16) == 0;
+        const int staged = sd.vector_rows ? (int)stride_bytes : a.d * elem_size(sd.dtype);
+        if (staged > row_bytes) row_bytes = staged;
+        if (sd.n_pad > most) most = sd.n_pad;
+    }
+    int64_t blocks = (most + STAGE_ROWS - 1) / STAGE_ROWS;
+    if (blocks > 4096) blocks = 4096;
+    const dim3 grid((unsigned)blocks, (unsigned)(a.n_sides * a.batch));
+    const size_t lds = (size_t)STAGE_ROWS * row_bytes;
+    if (a.compute == FNN_F32) return launch(TK_PREP, prep_staged_kernel<IN, FNN_F32>, grid, dim3(STAGE_ROWS), lds, s, a);
+    if (a.compute == FNN_F16) return launch(TK_PREP, prep_staged_kernel<IN, FNN_F16>, grid, dim3(STAGE_ROWS), lds, s, a);
+    return launch(TK_PREP, prep_staged_kernel<IN, FNN_BF16>, grid, dim3(STAGE_ROWS), lds, s, a);
+}
+
 __global__ __launch_bounds__(256) void fill_none_kernel(int32_t* idx, float* score, int64_t count) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
         idx[i] = -1;
@@ -397,14 +532,6 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
         vector_rows = sd.dtype == FNN_F32 && sd.row_stride % 4 == 0;
         for (int b = 0; b < a.batch && vector_rows; ++b) vector_rows = ((uintptr_t)sd.src[b] % 16) == 0;
     }
-    if (vector_rows && a.split && a.d % 8 == 0 && a.dp == padded_d(3 * a.d, FNN_F16)) {
-        switch (a.d / 8) {
-            case 1: return launch(TK_PREP, prep_split_rows_kernel<1>, grid, dim3(256), 0, s, a);
-            case 2: return launch(TK_PREP, prep_split_rows_kernel<2>, grid, dim3(256), 0, s, a);
-            case 3: return launch(TK_PREP, prep_split_rows_kernel<3>, grid, dim3(256), 0, s, a);
-            case 4: return launch(TK_PREP, prep_split_rows_kernel<4>, grid, dim3(256), 0, s, a);
-        }
-    }
     if (vector_rows && !a.split && (a.normalize || a.l2) && a.d % 8 == 0) {
         const int in = a.d / 8, out = a.dp / 8;
         if (in == 1 && out == 1) return launch_prep_rows<1, 1>(a, grid, s);
@@ -424,7 +551,14 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
             case 4: return launch_prep_fast<4>(a, grid, s);
         }
     }
-    return launch(TK_PREP, prep_kernel, grid, dim3(256), 0, s, a);
+    if (!a.normalize && !a.l2 && !a.split) return launch(TK_PREP, prep_kernel, grid, dim3(256), 0, s, a);
+    switch ((a.d + 7) / 8) {
+        case 1: return launch_prep_staged<1>(a, s);
+        case 2: return launch_prep_staged<2>(a, s);
+        case 3: return launch_prep_staged<3>(a, s);
+        case 4: return launch_prep_staged<4>(a, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace fnn

@@ -1,0 +1,50 @@
+"""The prepare step with options that need a whole row (FNN_FLAG_NORMALIZE, FNN_FLAG_L2, FNN_FLAG_SPLIT): rows are
+staged through LDS in runs of 256, copied whole where the map is 16-byte aligned and its rows lie close
+together, element by element otherwise.  How the caller stores a map must not change a single bit of the
+result: contiguous, strided and misaligned storage of the same values are compared, at the edges of a run
+and -- fnn_mutual_dense, whose image 1 is stored in another order -- of a super-block of 4096 pixels; and
+the exactly representable values of L2 and SPLIT against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2503_10017_amd as fnn
+from gpu_helpers import dev, exact_maps, host
+
+pytestmark = pytest.mark.gpu
+
+
+def stored(x, dtype, stride, offset):
+    """The rows of x, `stride` elements apart, the first one `offset` elements into its allocation."""
+    n, d = x.shape
+    flat = torch.full((offset + n * stride + 8,), 3.0, dtype=dtype, device="cuda:0")   # junk between the rows
+    view = flat[offset:offset + n * stride].view(n, stride)[:, :d]
+    view.copy_(x)
+    return view
+
+
+@pytest.mark.parametrize("option,compute,dtype", [("normalize", "f16", torch.float16), ("normalize", "bf16", torch.bfloat16),
+                                                  ("normalize", "f32", torch.float16), ("l2", "f16", torch.float16),
+                                                  ("l2", "bf16", torch.float32), ("l2", "f32", torch.float32),
+                                                  ("split", "f16", torch.float32)])
+@pytest.mark.parametrize("n,m,d", [(255, 257, 24), (256, 33, 17), (4097, 513, 8), (1, 4095, 5), (300, 290, 28)])
+def test_storage_does_not_change_the_result(option, compute, dtype, n, m, d):
+    a, b = exact_maps(n + m + d, n, m, d)
+    ta, tb = dev(a).to(dtype), dev(b).to(dtype)
+    want = dense = None
+    for stride, offset in ((d, 0), (d + 5, 0), (d, 1), (d + 1, 3), (2 * d, 0), (3 * d + 1, 2)):
+        sa, sb = stored(ta, dtype, stride, offset), stored(tb, dtype, stride, offset)
+        idx, score = (host(x) for x in fnn.fnn_nearest(sa, sb, compute=compute, **{option: True}))
+        out = {k: host(v) for k, v in fnn.fnn_mutual_dense(sa, sb, compute=compute, **{option: True}).items()}
+        if want is None:
+            want, dense = (idx, score), out
+            if option != "normalize":
+                ref = oracle.nearest_l2(a, b) if option == "l2" else oracle.nearest(a, b)
+                assert np.array_equal(idx[0], ref[0])
+                assert np.array_equal(-2.0 * score[0] if option == "l2" else score[0], ref[1])
+        assert np.array_equal(idx, want[0]) and np.array_equal(score, want[1]), (stride, offset)
+        n_pairs = int(dense["n_pairs"][0])
+        for key in ("nn12", "s12", "nn21", "s21", "n_pairs"):
+            assert np.array_equal(out[key], dense[key]), (key, stride, offset)
+        assert np.array_equal(out["pairs"][0, :n_pairs], dense["pairs"][0, :n_pairs])
