@@ -319,6 +319,13 @@ void search_first_kernel(FirstSearchArgs fa) {
     const int n_act = a.nq;
     if (n_act <= 0 || a.m_tiles <= 0) return;
 
+    // On prepared maps the groups of R query blocks are dealt evenly to the waves of all quads: 25 groups
+    // (3185 queries) give the 12 waves of three quads two or three each, where filling one quad after the
+    // other left the third with a single group and three idle waves (four pairs of 517x389 and 433x301
+    // pixels: 105 + 154 us for the two first searches, 99 + 145 dealt evenly).  The waves with one
+    // group more sit at different places of their workgroups, that is on different SIMDs.  The variant for the
+    // caller's fp32 maps fills the quads in turn: its loop is sensitive to how it is laid out, and with
+    // the even deal every pixel of a 512x384 pair as a query took 1750 instead of 1690 us.
     const int row_groups = (n_act + 32 * R * G - 1) / (32 * R * G);
     const int quads = (row_groups + SEARCH_WAVES - 1) / SEARCH_WAVES;
     int chunks = max(1, (int)gridDim.x / quads);
@@ -334,7 +341,14 @@ void search_first_kernel(FirstSearchArgs fa) {
     const int units = quads * chunks;
     for (int unit = wgi; unit < units; unit += gridDim.x) {  // uniform in the workgroup
         const int chunk = unit / quads, quad = unit % quads;
-        const int slot0 = (quad * SEARCH_WAVES + wave) * 32 * R * G;
+        int slot0 = (quad * SEARCH_WAVES + wave) * 32 * R * G, slot_end = n_act;  // this wave's slots
+        if constexpr (!RAWT) {
+            const int groups = (n_act + 32 * R - 1) / (32 * R);
+            const int per_wave = groups / (quads * SEARCH_WAVES), more = groups % (quads * SEARCH_WAVES);
+            const int rank = ((wave + quad) & (SEARCH_WAVES - 1)) * quads + quad;
+            slot0 = (rank * per_wave + min(rank, more)) * 32 * R;
+            slot_end = min(n_act, slot0 + (per_wave + (rank < more ? 1 : 0)) * 32 * R);
+        }
         const int t0 = chunk * tiles_per_chunk;
         const int t1 = min(t0 + tiles_per_chunk, a.m_tiles);
         const int n_turns = (t1 - t0 + FIRST_TURN - 1) / FIRST_TURN;
@@ -354,7 +368,7 @@ void search_first_kernel(FirstSearchArgs fa) {
         int best_tile[G][R];
         bool live[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) live[g] = slot0 + g * 32 * R < n_act;  // uniform in the wave
+        for (int g = 0; g < G; ++g) live[g] = slot0 + g * 32 * R < slot_end;  // uniform in the wave
         {
             int32_t row[G * R];
             query_rows<G * R>(a, qbase, slot0, n_act, c, row);
@@ -453,7 +467,7 @@ void search_first_kernel(FirstSearchArgs fa) {
                     best_tile[g][r] = ot;
                 }
                 const int slot = slot0 + (g * R + r) * 32 + c;
-                if (h == 0 && slot < n_act) atomicMax(&a.out_keys[qbase + slot], pack_key(mine, best_tile[g][r]));
+                if (h == 0 && slot < slot_end) atomicMax(&a.out_keys[qbase + slot], pack_key(mine, best_tile[g][r]));
             }
         __syncthreads();  // the next unit's first turn reuses ring slot 0
     }
