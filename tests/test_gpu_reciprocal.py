@@ -173,11 +173,11 @@ def test_hip_graph_capture_and_replay():
             assert np.array_equal(host(again[k]), want[k]), (rep, k, "eager")
 
 
-@pytest.mark.parametrize("batch,n_seeds", [(1, 1537), (33, 16500)])
+@pytest.mark.parametrize("batch,n_seeds", [(1, 1537), (1, 4096), (2, 4097), (1, 5121), (33, 16500)])
 def test_bookkeeping_over_several_rounds_of_slots(batch, n_seeds):
     """The reciprocity test and compaction hand their survivors on once per round of 1024 slots per
     workgroup: 16 500 seeds in a batch of 33 (16 workgroups per pair) need a second round, 1537 seeds
-    of one pair leave the last workgroup a single slot."""
+    of one pair leave the last workgroup a single slot.  The final sort takes 4096 seeds at a time."""
     a, b = exact_maps(5 + batch, 2100, 1999, 24)
     seeds = np.random.default_rng(batch).integers(0, 2100, size=n_seeds).astype(np.int32)
     ref = oracle.reciprocal(a, b, seeds, 4)
