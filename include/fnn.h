@@ -23,7 +23,9 @@
  *    of Algorithm 1).
  *  - A map is a row-major [n][d] array in DEVICE memory, pixel id = y * W + x, rows
  *    `row_stride` elements apart (row_stride >= d).  1 <= d <= FNN_MAX_D.
- *    n <= 2^31 - 64.  Inputs must be finite; NaN/Inf give unspecified results.
+ *    n <= 2^31 - 64.  Inputs must be finite, also after rounding to the compute format
+ *    (FNN_F16: |x| < 65520), and so must the scores; otherwise the results are unspecified (the
+ *    indices that fnn_nearest and fnn_reciprocal return still lie inside the maps).
  *  - `batch` independent image pairs share shapes; maps are passed as HOST arrays of
  *    `batch` fnn_map structs (1 <= batch <= FNN_MAX_BATCH); every other array is ONE
  *    contiguous DEVICE buffer with the batch index outermost.

@@ -322,6 +322,9 @@ __device__ __forceinline__ void arrived(Frag& f) {
 
 // The largest of a tile's 32 scores against one query that every lane of the wave holds in its column
 // (result registers of lanes 0 and 32 together cover the tile), and the lowest candidate that attains it.
+// A tile whose scores are all NaN has no score that equals the maximum: the index is then kept
+// inside the map, because the callers address memory with it (the rows of the next search, the
+// bitmap and the list of the matched pixels).
 struct Resolved {
     int32_t idx;
     float score;
@@ -340,7 +343,7 @@ __device__ __forceinline__ Resolved lowest_at_maximum(f32x16 acc, int tile, int 
     for (int v = 15; v >= 0; --v)
         if (acc[v] == top) row = tile_row(v, h);
     row = min(row, __shfl_xor(row, 32));
-    return {tile * 32 + row, top};
+    return {min(tile * 32 + row, m - 1), top};
 }
 
 // ---------------------------------------------------------------------------------------
