@@ -124,7 +124,10 @@ typedef struct {
  *   <a, b> - 1/2 ||a||^2 - 1/2 ||b||^2
  * with the two norm terms carried in spare channels of the prepared rows (each split into
  * two 16-bit halves for the 16-bit formats), fp32 accumulation.  ||x||^2 is the fp32 sum
- * (k ascending, squares and sums rounded separately) of the rounded channels.  Needs
+ * (k ascending, squares and sums rounded separately) of the rounded channels.  In FNN_F16 the
+ * two halves hold 1/2 ||x||^2 up to 65504 (||x|| up to 361) to fp32 grade, up to 131008 to within 16,
+ * and longer rows as 131008: scale such maps down first (the ranking does not change) or use
+ * another format.  Needs
  * d <= 28 (16-bit compute formats) or d <= 30 (FNN_F32), else FNN_E_SHAPE; size the
  * workspace with fnn_workspace_bytes_opts.  May be combined with FNN_FLAG_NORMALIZE.
  */

@@ -36,6 +36,16 @@ __device__ __forceinline__ float round_to_compute(float x, int compute) {
     return x;
 }
 
+// The norm term of the L2 score, -1/2 |x|^2, as the norm channels hold it: a rounded value and, in a
+// 16-bit format, the rounded remainder.  fp16 ends at 65504: a longer row's term is held at the ends of
+// the two halves' ranges instead of as -inf and the +inf that remains, whose sum is not a number.
+constexpr float F16_LARGEST = 65504.0f;
+__device__ __forceinline__ void split_norm_term(float term, int compute, float& hi, float& lo) {
+    const float lowest = compute == FNN_F16 ? -F16_LARGEST : -__builtin_inff();
+    hi = round_to_compute(__builtin_fmaxf(term, lowest), compute);
+    lo = round_to_compute(__builtin_fmaxf(term - hi, lowest), compute);
+}
+
 // Side jobs spread over all threads of the launch (see PrepExtra).
 __device__ __forceinline__ void prep_side_jobs(const PrepArgs& a) {
     const PrepExtra& x = a.extra;
@@ -277,8 +287,7 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
                 for (int k = 3 * d; k < a.dp; ++k) o[k] = 0;
             }
         } else {
-            // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2).  For a 16-bit
-            // format the norm term is split into a rounded value and the rounded remainder.
+            // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2)
             float hi = 0.0f, lo = 0.0f;
             if (a.l2) {
                 float sum = 0.0f;
@@ -287,9 +296,7 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
                     const float x = round_to_compute(v[k], COMPUTE);
                     sum = __builtin_fmaf(x, x, sum);
                 }
-                const float term = -0.5f * sum;
-                hi = round_to_compute(term, COMPUTE);
-                lo = round_to_compute(term - hi, COMPUTE);
+                split_norm_term(-0.5f * sum, COMPUTE, hi, lo);
             }
             const bool extras = a.l2 && real;
             const int ones0 = d + (sd.second_image ? EXTRA : 0);   // first unit channel
@@ -375,9 +382,8 @@ __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
                 float sum = 0.0f;
 #pragma unroll
                 for (int e = 0; e < D; ++e) sum = __fadd_rn(sum, __fmul_rn(v[e], v[e]));
-                const float term = -0.5f * sum;
-                const float hi = round_to_compute(term, COMPUTE);
-                const float lo = round_to_compute(term - hi, COMPUTE);
+                float hi, lo;
+                split_norm_term(-0.5f * sum, COMPUTE, hi, lo);
                 const int ones0 = D + (sd.second_image ? EXTRA : 0);
                 const int term0 = D + (sd.second_image ? 0 : EXTRA);
 #pragma unroll

@@ -148,3 +148,31 @@ def test_normalize_then_l2():
     assert clear.mean() > 0.9
     assert np.array_equal(host(gi)[0][clear], ri[clear])
     assert np.abs(-2.0 * host(gs)[0] - rbest).max() <= 1e-5
+
+
+@pytest.mark.parametrize("storage", [torch.float32, torch.float16])
+@pytest.mark.parametrize("n,m", [(60, 77), (2000, 2500)])     # one workgroup per pair, launch sequence
+def test_rows_too_long_for_fp16_norm_terms(storage, n, m):
+    """1/2 |x|^2 past 65504 does not fit one fp16 value: the remainder carries what it can, up to 131008, and longer
+    rows are held there.  Whole numbers of at most 200: every term is exact in fp32, so the scores are known."""
+    rng = np.random.default_rng(n)
+    a, b = (np.rint(rng.uniform(-1, 1, size=(k, 24)) * np.linspace(20, 200, k)[:, None]) for k in (n, m))
+
+    def term(x):
+        t = -0.5 * (x * x).sum(axis=1)
+        hi = np.maximum(t, -65504.0).astype(np.float16).astype(np.float64)
+        return hi + np.maximum(t - hi, -65504.0).astype(np.float16).astype(np.float64)
+
+    lengths = 0.5 * (a * a).sum(axis=1)
+    assert (lengths < 65504).any() and (lengths > 131008).any() and ((lengths > 65504) & (lengths < 131008)).any()
+    score = a @ b.T + term(a)[:, None] + term(b)[None]
+    ta, tb = (dev(x.astype(np.float32)).to(storage) for x in (a, b))
+    idx, best = fnn.fnn_nearest(ta, tb, compute="f16", l2=True)
+    assert np.array_equal(host(idx)[0], score.argmax(axis=1)) and np.array_equal(host(best)[0], score.max(axis=1))
+    seeds = np.arange(0, n, 3, dtype=np.int32)
+    out = fnn.fnn_reciprocal(ta, tb, dev(seeds)[None], max_iter=10, compute="f16", l2=True)
+    out = {k: host(v)[0] for k, v in out.items()}
+    done = out["seed_iter"] >= 0
+    assert done.any()
+    assert np.array_equal(out["seed_j"], score.argmax(axis=1)[out["seed_i"]])
+    assert np.array_equal(out["seed_i"][done], score.argmax(axis=0)[out["seed_j"][done]])
