@@ -101,9 +101,10 @@ typedef struct {
 /*
  * FNN_FLAG_NORMALIZE: the maps are raw matching-head outputs (section 3.2.4, "Matching Head");
  * every descriptor is divided by its Euclidean norm before the cast to the compute format:
- * norm2 = sum_k x[k]*x[k] in fp32 (k ascending; a product may be fused with its addition),
- * y[k] = x[k] / sqrt(norm2) with correctly rounded fp32 sqrt and division; an all-zero
- * descriptor stays zero.  The step is fused into the prepare pass.
+ * norm2 = sum_k x[k]*x[k] in fp32, k ascending, every step one fused multiply-add
+ * (norm2 <- fma(x[k], x[k], norm2), rounded once), y[k] = x[k] / sqrt(norm2) with correctly
+ * rounded fp32 sqrt and division; an all-zero descriptor stays zero.  The result does not depend
+ * on how the map is stored.  The step is fused into the prepare pass.
  */
 #define FNN_FLAG_NORMALIZE 1
 /*

@@ -36,6 +36,29 @@ __device__ __forceinline__ float round_to_compute(float x, int compute) {
     return x;
 }
 
+// |x|^2 of a row's first N channels as FNN_FLAG_NORMALIZE and FNN_FLAG_L2 define it: k ascending, every step one
+// fused multiply-add.  Written out, so that it does not rest on what the compiler chooses to fuse; a
+// channel that is zero changes nothing.
+template <int N, int M>
+__device__ __forceinline__ float squared_length(const float (&x)[M]) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int k = 0; k < N; ++k) sum = __builtin_fmaf(x[k], x[k], sum);
+    return sum;
+}
+// A row's first N channels divided by their norm (FNN_FLAG_NORMALIZE); an all-zero row stays zero.  Both kernels
+// that normalise call this one, so that a row's bits do not depend on how the caller stored it.  The
+// square root is the builtin: it is correctly rounded, where __fsqrt_rn compiled to the bare
+// hardware root (off by one unit in the last place now and then) in the kernel of aligned rows.
+template <int N, int M>
+__device__ __forceinline__ void normalize_row(float (&x)[M]) {
+    const float norm = __builtin_sqrtf(squared_length<N>(x));
+    if (norm > 0.0f) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] = __fdiv_rn(x[k], norm);
+    }
+}
+
 // The norm term of the L2 score, -1/2 |x|^2, as the norm channels hold it: a rounded value and, in a
 // 16-bit format, the rounded remainder.  fp16 ends at 65504: a longer row's term is held at the ends of
 // the two halves' ranges instead of as -inf and the +inf that remains, whose sum is not a number.
@@ -240,18 +263,7 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
         }
         __syncthreads();  // the staged rows are in registers: the finished ones may take their place
 
-        // Channels at and past d are zero, so they change neither sum.  The sums run over fused
-        // multiply-adds in ascending order, which is what the element-by-element loops compiled to.
-        if (a.normalize) {
-            float sum = 0.0f;
-#pragma unroll
-            for (int k = 0; k < IN * 8; ++k) sum = __builtin_fmaf(v[k], v[k], sum);
-            const float norm = __builtin_sqrtf(sum);  // correctly rounded
-            if (norm > 0.0f) {
-#pragma unroll
-                for (int k = 0; k < IN * 8; ++k) v[k] = __fdiv_rn(v[k], norm);
-            }
-        }
+        if (a.normalize) normalize_row<IN * 8>(v);  // channels at and past d are zero
         char* out = lds + run.out_row(tid) * out_bytes;
         if (COMPUTE == FNN_F16 && a.split) {
             // copy 0 holds hi, and of copies 1 and 2 image 1 holds (hi, lo), image 2 (lo, hi), so that a row
@@ -290,13 +302,9 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
             // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2)
             float hi = 0.0f, lo = 0.0f;
             if (a.l2) {
-                float sum = 0.0f;
 #pragma unroll
-                for (int k = 0; k < IN * 8; ++k) {
-                    const float x = round_to_compute(v[k], COMPUTE);
-                    sum = __builtin_fmaf(x, x, sum);
-                }
-                split_norm_term(-0.5f * sum, COMPUTE, hi, lo);
+                for (int k = 0; k < IN * 8; ++k) v[k] = round_to_compute(v[k], COMPUTE);
+                split_norm_term(-0.5f * squared_length<IN * 8>(v), COMPUTE, hi, lo);
             }
             const bool extras = a.l2 && real;
             const int ones0 = d + (sd.second_image ? EXTRA : 0);   // first unit channel
@@ -337,8 +345,7 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
 
 // Fast path for the options that need a whole row at once (FNN_FLAG_NORMALIZE, FNN_FLAG_L2) on
 // fp32 sources with d a multiple of 8: one thread per row.  The row is read once with 16-byte
-// loads; norm and squared length are formed in registers (channels ascending, every product and sum
-// rounded on its own).
+// loads; norm and squared length are formed in registers.
 // IN = d / 8, OUT = dp / 8.
 template <int IN, int OUT, int COMPUTE>
 __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
@@ -366,24 +373,12 @@ __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
                 v[4 * q + 2] = x.z;
                 v[4 * q + 3] = x.w;
             }
-            if (a.normalize) {
-                float sum = 0.0f;
-#pragma unroll
-                for (int e = 0; e < D; ++e) sum = __fadd_rn(sum, __fmul_rn(v[e], v[e]));
-                const float norm = __fsqrt_rn(sum);
-                if (norm > 0.0f) {
-#pragma unroll
-                    for (int e = 0; e < D; ++e) v[e] = __fdiv_rn(v[e], norm);
-                }
-            }
+            if (a.normalize) normalize_row<D>(v);
 #pragma unroll
             for (int e = 0; e < D; ++e) v[e] = round_to_compute(v[e], COMPUTE);
             if (a.l2) {
-                float sum = 0.0f;
-#pragma unroll
-                for (int e = 0; e < D; ++e) sum = __fadd_rn(sum, __fmul_rn(v[e], v[e]));
                 float hi, lo;
-                split_norm_term(-0.5f * sum, COMPUTE, hi, lo);
+                split_norm_term(-0.5f * squared_length<D>(v), COMPUTE, hi, lo);
                 const int ones0 = D + (sd.second_image ? EXTRA : 0);
                 const int term0 = D + (sd.second_image ? 0 : EXTRA);
 #pragma unroll

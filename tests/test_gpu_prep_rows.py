@@ -48,3 +48,30 @@ def test_storage_does_not_change_the_result(option, compute, dtype, n, m, d):
         for key in ("nn12", "s12", "nn21", "s21", "n_pairs"):
             assert np.array_equal(out[key], dense[key]), (key, stride, offset)
         assert np.array_equal(out["pairs"][0, :n_pairs], dense["pairs"][0, :n_pairs])
+
+
+def lengthy_maps(seed, n, d):
+    """Gaussian rows of lengths between 0.05 and 20, one of them zero: sums of squares that round at every step."""
+    rng = np.random.default_rng(seed)
+    x = (rng.standard_normal((n, d)) * rng.uniform(0.05, 20.0, size=(n, 1))).astype(np.float32)
+    x[n // 2] = 0.0
+    return x
+
+
+def prepared(x, compute, **kw):
+    """The channels of every row as the prepare step leaves them: their products with the unit rows, one pair each."""
+    unit = torch.eye(x.shape[1], dtype=x.dtype, device=x.device)
+    score = fnn.fnn_nearest([x] * x.shape[1], [unit[k:k + 1] for k in range(x.shape[1])], compute=compute, **kw)[1]
+    return host(score).T
+
+
+@pytest.mark.parametrize("compute,kw", [("f32", {}), ("f16", {}), ("bf16", {}), ("f16", {"split": True})])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("d", [5, 8, 16, 17, 24, 32])
+def test_normalised_rows_are_the_defined_ones_bit_for_bit(compute, kw, dtype, d):
+    x = dev(lengthy_maps(d, 1030, d)).to(dtype)
+    y = oracle.normalize(host(x.float()))
+    want = {"f32": y, "f16": sum(oracle.split_fp16(y)) if kw else oracle.round_fp16(y), "bf16": oracle.round_bf16(y)}[compute]
+    for stride, offset in ((d, 0), (d, 1), (d + 4, 0), (d + 1, 3), (3 * d + 1, 2)):
+        got = prepared(stored(x, dtype, stride, offset), compute, normalize=True, **kw)
+        assert np.array_equal(got, want), (stride, offset)
