@@ -235,6 +235,15 @@ void search_kernel(SearchArgs a) {
 
     const int64_t units = (int64_t)row_groups * chunks;
     for (int64_t unit = wave; unit < units; unit += n_waves) {
+        // The few-query units below start at slot 0.  Where the query fragments of the ordinary unit leave no
+        // registers to spare, the compiler must not see that as a constant: it prepared the lane addresses
+        // of all three units ahead of the loop and spilled them, and a kernel that uses scratch
+        // memory takes 2 us longer to start (fp16, 24 channels, G = 4, one 1024x768 map: 22.1 us for 48 live
+        // queries with 21 registers spilled, 19.2 us without; 100 live 24.2 and 20.6; eight 512x384 maps in
+        // bf16, 48 live, 18.9 and 16.4).  The narrower variants keep the constant (100 queries of four 512x384
+        // pairs, G = 1: 13.1 us with it, 13.8 us without).
+        int first_slot = 0;
+        if (G * R * Ops<CT, DP>::ROW_BYTES / 8 >= 96) asm volatile("" : "+s"(first_slot));
         const int chunk = (int)(unit / row_groups);
         const int rg = (int)(unit % row_groups);
         const int slot0 = rg * 32 * R * G;
@@ -244,11 +253,11 @@ void search_kernel(SearchArgs a) {
             // few live queries (one row group, so combine is set): only the blocks that hold a
             // live query are multiplied, and the ring is as long as the registers allow
             if (n_act <= 32)
-                search_unit<CT, DP, 1, stream_ring<CT, DP, 1>(), 1, true>(a, src, tgt, qbase, n_act, 0, t0, t1, true, wg_keys, c, h);
+                search_unit<CT, DP, 1, stream_ring<CT, DP, 1>(), 1, true>(a, src, tgt, qbase, n_act, first_slot, t0, t1, true, wg_keys, c, h);
             else if (n_act <= 64)
-                search_unit<CT, DP, 2, stream_ring<CT, DP, 2>(), 1, true>(a, src, tgt, qbase, n_act, 0, t0, t1, true, wg_keys, c, h);
+                search_unit<CT, DP, 2, stream_ring<CT, DP, 2>(), 1, true>(a, src, tgt, qbase, n_act, first_slot, t0, t1, true, wg_keys, c, h);
             else
-                search_unit<CT, DP, R, stream_ring<CT, DP, R>(), 1, true>(a, src, tgt, qbase, n_act, 0, t0, t1, true, wg_keys, c, h);
+                search_unit<CT, DP, R, stream_ring<CT, DP, R>(), 1, true>(a, src, tgt, qbase, n_act, first_slot, t0, t1, true, wg_keys, c, h);
         } else {
             search_unit<CT, DP, R, P, G, false>(a, src, tgt, qbase, n_act, slot0, t0, t1, combine, wg_keys, c, h);
         }

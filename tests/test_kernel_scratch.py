@@ -1,0 +1,43 @@
+"""The search kernels of the paper's row width keep everything in registers: a kernel that spills uses scratch
+memory, and a launch of one takes about 2 us longer to start.  Read from the kernel descriptions in the built library."""
+import re
+import struct
+import subprocess
+
+import pytest
+
+import paper_2503_10017_amd as fnn
+
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+
+
+def scratch_bytes(tmp_path):
+    """Kernel name -> bytes of scratch memory per lane, over every gfx950 code object in the library."""
+    with open(fnn.library_path(), "rb") as f:
+        image = f.read()
+    found = {}
+    for bundle in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", image):
+        at = bundle.end()
+        count, = struct.unpack_from("<Q", image, at)
+        at += 8
+        for _ in range(count):
+            offset, size, name_len = struct.unpack_from("<QQQ", image, at)
+            target = image[at + 24:at + 24 + name_len]
+            at += 24 + name_len
+            if b"gfx950" not in target or size == 0:
+                continue
+            path = tmp_path / "code.o"
+            path.write_bytes(image[bundle.start() + offset:bundle.start() + offset + size])
+            notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+            for name, scratch in re.findall(r"\.name:\s+(_Z\S+)\n\s+\.private_segment_fixed_size: (\d+)", notes):
+                found[name] = int(scratch)
+    return found
+
+
+@pytest.mark.parametrize("kernel", ["search_kernel", "search_first_kernel"])
+def test_no_scratch_memory_at_24_channels_in_16_bits(kernel, tmp_path):
+    scratch = scratch_bytes(tmp_path)
+    half24 = {k: v for k, v in scratch.items()
+              if re.match(rf"_ZN3fnn\d+{kernel}ILi[12]E" + ("Li24E" if kernel == "search_kernel" else ""), k)}
+    assert len(half24) >= 2
+    assert not {k: v for k, v in half24.items() if v}
