@@ -5,9 +5,8 @@
 // of device time and up), of which its arithmetic is 2 us.  Here the searches of a pair follow one
 // another behind workgroup barriers, and the loop really ends when no seed is left.
 //
-// What bounds it: at the smallest sizes the latency of a search (query rows, first tiles, LDS merge:
-// about 2 us), at the largest it takes the vector ALU of the one compute unit a pair occupies, which is
-// why the host stops choosing it where walk_applies() says.
+// What bounds it: the latency of a search (query rows, first tiles, LDS merge, winning tiles: 4 us), then the
+// arithmetic of the one compute unit that a pair occupies; walk_applies() says up to which size the host chooses it.
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
 #include "trace.hpp"
@@ -16,7 +15,8 @@ namespace fnn {
 
 constexpr int WALK_WAVES = 16;
 constexpr int WALK_THREADS = WALK_WAVES * 64;
-constexpr int WALK_MAX_SEEDS = WALK_THREADS;  // the compaction handles one slot per thread
+constexpr int WALK_MAX_SEEDS = 96;  // see walk_applies()
+static_assert(WALK_MAX_SEEDS <= WALK_THREADS, "the compaction handles one slot per thread");
 
 // Query blocks a wave multiplies with each loaded tile and tiles it keeps in flight: 128 registers
 // (four waves per SIMD) hold the query fragments, the results and the ring.
@@ -212,18 +212,29 @@ static size_t walk_lds_bytes(int64_t n, int64_t n_seeds) {
     return (size_t)n_seeds * (sizeof(u64) + 4 * sizeof(int32_t)) + (size_t)((n + 31) / 32) * 2 * sizeof(int32_t);
 }
 
-// Where one workgroup per pair beats the launch sequence.  Measured on the benchmark's maps (three
-// iterations with live seeds), microseconds per call, one pair, fp16, 24 channels: the sequence costs
-// 24 + 13 * max_iter whatever the size up to 160x120; the walk 36 at 192 products of 32x32 scores
-// per search (64x48, 48 seeds), 72 at 576, 81 at 768, 142 at 2304.  At ten allowed iterations the lines
-// would cross near 2000 products; 1000 keeps a walk whose seeds all move to the end (every search at
-// full size) within twice the sequence.  At two allowed iterations 192 products take 36 against 45.  Wide
-// rows and fp32 products cost about five times as much per product (192 products: 80 and 84).
+// Where one workgroup per pair is no slower than the launch sequence, however long the seeds keep
+// moving.  Both sides in microseconds per call, one pair, fp16, 24 channels: a call of the walk takes 10, and
+// every iteration with live seeds 8 + 2.1 per block of 32 seeds + 0.018 per product of 32x32 scores and
+// search (query blocks are multiplied in twos); an iteration without live seeds takes nothing.  The sequence took 13 + 18
+// (one or two blocks) to 21 for every allowed iteration when the walk came, 13 + 16 to 18 now.  With
+// every seed live for all ten allowed iterations, and with all of them settled in the first:
+//     1 block  x 175 tiles  walk 161 / 23, sequence 159 / 151 (before the walk: 186 / 189)
+//     2 blocks x 175 tiles  walk 182 / 26, sequence 176 / 155 (195 / 192)
+//     3 blocks x  87 tiles  walk 196 / 27, sequence 190 / 154 (214 / 193)
+//     8 blocks x  64 tiles  walk 343 / 42, sequence 189 / 154 (222 / 187): past the line
+//    31 blocks x  31 tiles  walk 940 / 103, sequence 195 / 152 (231 / 191): past the line
+// A fragment of 32 channels takes half as much again per product (2 blocks x 120 tiles: 184 against 199 before).
+// Wide rows and fp32 products leave room for one block at a time (96 channels, 24 tiles: 210 against 236;
+// fp32 products of 32 channels: 266 against 286; two blocks x 2 tiles: 303 against 223).
+// The 64x48 pair with 48 seeds (2 blocks x 96 tiles) takes 23 to 154 against 189 to 194.  With a few allowed
+// iterations the sequence is short as well: at most 100 products for each.
 bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int compute, int dp) {
-    if (n_seeds < 1 || n_seeds > WALK_MAX_SEEDS || n < 1 || m < 1 || walk_lds_bytes(n, n_seeds) > 60 * 1024) return false;
-    const int64_t products = (n_seeds + 31) / 32 * (((n > m ? n : m) + 31) / 32);
-    const int64_t price = compute == FNN_F32 || dp > 32 ? 5 : 1;
-    return products * price <= 100 * (int64_t)(max_iter < 10 ? max_iter : 10);
+    if (n_seeds < 1 || n_seeds > WALK_MAX_SEEDS || n < 1 || m < 1) return false;
+    const int64_t blocks = (n_seeds + 31) / 32, tiles = ((n > m ? n : m) + 31) / 32;
+    const bool costly = compute == FNN_F32 || dp > 32;
+    if (blocks * tiles * (costly ? 5 : 1) > 100 * (int64_t)max_iter) return false;
+    if (costly) return blocks == 1 && tiles <= 24;
+    return (blocks + 1) / 2 * 2 * tiles <= (dp > 24 ? 240 : 350);
 }
 
 template <int CT, int DP>
