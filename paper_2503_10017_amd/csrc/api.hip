@@ -10,7 +10,7 @@ using namespace fnn;
 
 namespace {
 
-constexpr int64_t MAX_PIXELS = 2147483647LL - 64;
+constexpr int64_t MAX_PIXELS = MAX_SLOTS;
 constexpr int64_t MAX_DENSE_PIXELS = 1LL << 30;  // keeps the padded bucket lists of the dense mode within int32
 constexpr size_t WS_ALIGN = 256;
 

@@ -52,6 +52,7 @@ inline int l2_extra_channels(int compute) { return compute == FNN_F32 ? 2 : 4; }
 inline int effective_d(int d, int compute, bool l2, bool split = false) {
     return split ? 3 * d : (l2 ? d + l2_extra_channels(compute) : d);
 }
+constexpr int64_t MAX_SLOTS = 2147483647LL - 64;  // most queries or seeds of a pair
 constexpr int MAX_ROW_CHANNELS = 96;  // widest prepared row (16-bit formats; fp32 rows hold at most 32)
 inline int elem_size(int dtype) { return dtype == FNN_F32 ? 4 : 2; }
 inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }

@@ -9,6 +9,7 @@ namespace fnn {
 
 constexpr int DEDUP_THREADS = 1024;
 constexpr int DEDUP_AHEAD = 4;
+static_assert(MAX_SLOTS + 2 * DEDUP_AHEAD * DEDUP_THREADS <= 0xFFFFFFFFLL, "seeds are counted in 32 bits");
 constexpr size_t DEDUP_LDS_BYTES = 60 * 1024;  // dynamic LDS a launch may ask for without raising the kernel's limit (64 KB incl. static)
 
 struct DedupArgs {
@@ -45,6 +46,7 @@ __global__ __launch_bounds__(DEDUP_THREADS) void recip_dedup_kernel(DedupArgs a)
     extern __shared__ uint32_t dedup_tables[];
     const int b = blockIdx.x;
     const int64_t base = (int64_t)b * a.n_seeds;
+    const uint32_t n_seeds = a.n_seeds;  // without a sign: the loops below count past the last seed, near 2^31 too
     uint32_t* bitmap = LOCAL ? dedup_tables : a.bitmap + (int64_t)b * a.n_words;
     RANK* word_rank = LOCAL ? reinterpret_cast<RANK*>(dedup_tables + a.n_words)
                             : reinterpret_cast<RANK*>(a.word_rank + (int64_t)b * a.n_words);
@@ -53,18 +55,18 @@ __global__ __launch_bounds__(DEDUP_THREADS) void recip_dedup_kernel(DedupArgs a)
         __syncthreads();
     }
 
-    for (int s0 = threadIdx.x; s0 < a.n_seeds; s0 += DEDUP_AHEAD * DEDUP_THREADS) {
+    for (uint32_t s0 = threadIdx.x; s0 < n_seeds; s0 += DEDUP_AHEAD * DEDUP_THREADS) {
         int32_t iter[DEDUP_AHEAD], match[DEDUP_AHEAD];
 #pragma unroll
         for (int k = 0; k < DEDUP_AHEAD; ++k) {
-            const int s = min(s0 + k * DEDUP_THREADS, a.n_seeds - 1);
+            const uint32_t s = min(s0 + k * DEDUP_THREADS, n_seeds - 1);
             iter[k] = a.seed_iter[base + s];
             match[k] = a.seed_i[base + s];
         }
 #pragma unroll
         for (int k = 0; k < DEDUP_AHEAD; ++k) {
             const uint32_t i = (uint32_t)match[k];
-            if (s0 + k * DEDUP_THREADS < a.n_seeds && iter[k] >= 0) atomicOr(&bitmap[i >> 5], 1u << (i & 31));
+            if (s0 + k * DEDUP_THREADS < n_seeds && iter[k] >= 0) atomicOr(&bitmap[i >> 5], 1u << (i & 31));
         }
     }
     __syncthreads();
@@ -84,18 +86,18 @@ __global__ __launch_bounds__(DEDUP_THREADS) void recip_dedup_kernel(DedupArgs a)
     }
     __syncthreads();
 
-    for (int s0 = threadIdx.x; s0 < a.n_seeds; s0 += DEDUP_AHEAD * DEDUP_THREADS) {
+    for (uint32_t s0 = threadIdx.x; s0 < n_seeds; s0 += DEDUP_AHEAD * DEDUP_THREADS) {
         int32_t iter[DEDUP_AHEAD], match_i[DEDUP_AHEAD], match_j[DEDUP_AHEAD];
 #pragma unroll
         for (int k = 0; k < DEDUP_AHEAD; ++k) {
-            const int s = min(s0 + k * DEDUP_THREADS, a.n_seeds - 1);
+            const uint32_t s = min(s0 + k * DEDUP_THREADS, n_seeds - 1);
             iter[k] = a.seed_iter[base + s];
             match_i[k] = a.seed_i[base + s];
             match_j[k] = a.seed_j[base + s];
         }
 #pragma unroll
         for (int k = 0; k < DEDUP_AHEAD; ++k) {
-            if (s0 + k * DEDUP_THREADS < a.n_seeds && iter[k] >= 0) {
+            if (s0 + k * DEDUP_THREADS < n_seeds && iter[k] >= 0) {
                 const uint32_t i = (uint32_t)match_i[k];
                 const uint32_t word = __hip_atomic_load(&bitmap[i >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const int pos = (int)__hip_atomic_load(&word_rank[i >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(DEDUP_THREADS) void recip_dedup_kernel(DedupArgs a)
             }
         }
     }
-    for (int i = count + threadIdx.x; i < a.n_seeds; i += DEDUP_THREADS) {
+    for (uint32_t i = count + threadIdx.x; i < n_seeds; i += DEDUP_THREADS) {
         a.pairs[(base + i) * 2 + 0] = -1;
         a.pairs[(base + i) * 2 + 1] = -1;
     }

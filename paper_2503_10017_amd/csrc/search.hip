@@ -510,7 +510,7 @@ __device__ __forceinline__ void resolve_body(const SearchArgs& a, int32_t* out_i
     const char* tgt = a.tgt + (int64_t)b * a.tgt_bstride;
     const int64_t qbase = (int64_t)b * a.nq;
 
-    for (int slot = wave; slot < n_act; slot += n_waves) {
+    for (uint32_t slot = wave; slot < (uint32_t)n_act; slot += n_waves) {  // without a sign, see resolve_step_kernel
         const u64 key = a.out_keys[qbase + slot];
         const int64_t qrow = query_row(a, qbase, slot);  // fetched beside the key, not behind the test of it
         Resolved res = {-1, -__builtin_inff()};
@@ -556,6 +556,8 @@ void resolve_raw_kernel(FirstSearchArgs fa, int32_t* out_idx, float* out_score, 
 // share of a 1024x768 call was 30 us) and 1.6 us (2.5 us of host time) of every other.
 constexpr int STEP_WAVES = 16;
 constexpr int STEP_ROUND = 1024;  // slots a workgroup takes before it hands its survivors on (8 KB of LDS)
+constexpr int STEP_MAX_WGS = 512;  // of all pairs: two workgroups of 16 waves per compute unit are resident
+static_assert(MAX_SLOTS + (int64_t)STEP_MAX_WGS * STEP_ROUND <= 0xFFFFFFFFLL, "a round past the last slot must not wrap around");
 template <int CT, int DP>
 __global__ __launch_bounds__(STEP_WAVES * 64)
 void resolve_step_kernel(SearchArgs a, StepArgs st) {
@@ -570,12 +572,14 @@ void resolve_step_kernel(SearchArgs a, StepArgs st) {
     const char* tgt = a.tgt + (int64_t)b * a.tgt_bstride;
     const int64_t base = (int64_t)b * a.nq;
 
-    for (int round = 0; round < n_act; round += gridDim.x * STEP_ROUND) {  // uniform in the launch's workgroups of this pair
+    // slots are counted in 32 bits without a sign: the round after the last one may lie past 2^31
+    const uint32_t step = gridDim.x * STEP_ROUND;
+    for (uint32_t round = 0; round < (uint32_t)n_act; round += step) {  // uniform in the launch's workgroups of this pair
         if (threadIdx.x == 0) n_moving = 0;
         __syncthreads();
         // the workgroups take the slots of a round 16 at a time in turn, so that few slots spread over all of them
-        const int end = min(n_act, round + (int)gridDim.x * STEP_ROUND);
-        for (int slot = round + blockIdx.x * STEP_WAVES + wave; slot < end; slot += gridDim.x * STEP_WAVES) {  // uniform in the wave
+        const uint32_t end = min((uint32_t)n_act, round + step);
+        for (uint32_t slot = round + blockIdx.x * STEP_WAVES + wave; slot < end; slot += gridDim.x * STEP_WAVES) {  // uniform in the wave
             const u64 kf = st.keys_f[base + slot];
             const u64 kb = a.out_keys[base + slot];
             const int32_t u = st.cur_u[base + slot];
@@ -801,7 +805,7 @@ hipError_t launch_resolve(const SearchArgs& a, int batch, int compute, int dp, i
 template <int CT, int DP>
 static hipError_t launch_resolve_step_t(const SearchArgs& a, const StepArgs& st, int batch, hipStream_t s) {
     int wgs = (a.nq + STEP_WAVES - 1) / STEP_WAVES;
-    const int cap = 512 / batch > 16 ? 512 / batch : 16;  // two workgroups of 16 waves per compute unit are resident
+    const int cap = STEP_MAX_WGS / batch > 16 ? STEP_MAX_WGS / batch : 16;
     if (wgs > cap) wgs = cap;
     return launch(TK_RECIP_STEP, resolve_step_kernel<CT, DP>, dim3(wgs, batch), dim3(STEP_WAVES * 64), 0, s, a, st);
 }
