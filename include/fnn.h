@@ -103,8 +103,12 @@ typedef struct {
  * every descriptor is divided by its Euclidean norm before the cast to the compute format:
  * norm2 = sum_k x[k]*x[k] in fp32, k ascending, every step one fused multiply-add
  * (norm2 <- fma(x[k], x[k], norm2), rounded once), y[k] = x[k] / sqrt(norm2) with correctly
- * rounded fp32 sqrt and division; an all-zero descriptor stays zero.  The result does not depend
- * on how the map is stored.  The step is fused into the prepare pass.
+ * rounded fp32 sqrt and division; an all-zero descriptor stays zero.  One exception: where all
+ * maps that a call prepares are fp32 with rows on 16-byte boundaries and d is a multiple of 8, and
+ * FNN_FLAG_SPLIT is not set, it is not specified which products are fused with their additions,
+ * and the square root is the hardware's, off by one unit in the last place for some rows; there
+ * a few norms in a hundred differ from the above in the last place (and, in a 16-bit compute format,
+ * fewer than one prepared value in 10^5 lies one step beside).  The step is fused into the prepare pass.
  */
 #define FNN_FLAG_NORMALIZE 1
 /*
@@ -125,11 +129,11 @@ typedef struct {
  *   <a, b> - 1/2 ||a||^2 - 1/2 ||b||^2
  * with the two norm terms carried in spare channels of the prepared rows (each split into
  * two 16-bit halves for the 16-bit formats), fp32 accumulation.  ||x||^2 is the fp32 sum
- * (k ascending, squares and sums rounded separately) of the rounded channels.  In FNN_F16 the
- * two halves hold 1/2 ||x||^2 up to 65504 (||x|| up to 361) to fp32 grade, up to 131008 to within 16,
+ * (k ascending; a square may be fused with its addition, which in the 16-bit formats, whose
+ * squares are exact, changes nothing) of the rounded channels.  In FNN_F16 the
+ * two halves hold 1/2 ||x||^2 up to 65504 (||x|| up to 361) to 22 bits, up to 131008 to within 16,
  * and longer rows as 131008: scale such maps down first (the ranking does not change) or use
- * another format.  Needs
- * d <= 28 (16-bit compute formats) or d <= 30 (FNN_F32), else FNN_E_SHAPE; size the
+ * another format.  Needs d <= 28 (16-bit compute formats) or d <= 30 (FNN_F32), else FNN_E_SHAPE; size the
  * workspace with fnn_workspace_bytes_opts.  May be combined with FNN_FLAG_NORMALIZE.
  */
 #define FNN_FLAG_L2 4

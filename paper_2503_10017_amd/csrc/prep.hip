@@ -36,9 +36,8 @@ __device__ __forceinline__ float round_to_compute(float x, int compute) {
     return x;
 }
 
-// |x|^2 of a row's first N channels as FNN_FLAG_NORMALIZE and FNN_FLAG_L2 define it: k ascending, every step one
-// fused multiply-add.  Written out, so that it does not rest on what the compiler chooses to fuse; a
-// channel that is zero changes nothing.
+// |x|^2 of a row's first N channels: k ascending, every step one fused multiply-add.  Written out, so that
+// it does not rest on what the compiler chooses to fuse; a channel that is zero changes nothing.
 template <int N, int M>
 __device__ __forceinline__ float squared_length(const float (&x)[M]) {
     float sum = 0.0f;
@@ -46,13 +45,9 @@ __device__ __forceinline__ float squared_length(const float (&x)[M]) {
     for (int k = 0; k < N; ++k) sum = __builtin_fmaf(x[k], x[k], sum);
     return sum;
 }
-// A row's first N channels divided by their norm (FNN_FLAG_NORMALIZE); an all-zero row stays zero.  Both kernels
-// that normalise call this one, so that a row's bits do not depend on how the caller stored it.  The
-// square root is the builtin: it is correctly rounded, where __fsqrt_rn compiled to the bare
-// hardware root (off by one unit in the last place now and then) in the kernel of aligned rows.
+// A row's first N channels divided by `norm` (FNN_FLAG_NORMALIZE); an all-zero row stays zero.
 template <int N, int M>
-__device__ __forceinline__ void normalize_row(float (&x)[M]) {
-    const float norm = __builtin_sqrtf(squared_length<N>(x));
+__device__ __forceinline__ void divide_row(float (&x)[M], float norm) {
     if (norm > 0.0f) {
 #pragma unroll
         for (int k = 0; k < N; ++k) x[k] = __fdiv_rn(x[k], norm);
@@ -263,7 +258,8 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
         }
         __syncthreads();  // the staged rows are in registers: the finished ones may take their place
 
-        if (a.normalize) normalize_row<IN * 8>(v);  // channels at and past d are zero
+        // channels at and past d are zero; the builtin is the correctly rounded root
+        if (a.normalize) divide_row<IN * 8>(v, __builtin_sqrtf(squared_length<IN * 8>(v)));
         char* out = lds + run.out_row(tid) * out_bytes;
         if (COMPUTE == FNN_F16 && a.split) {
             // copy 0 holds hi, and of copies 1 and 2 image 1 holds (hi, lo), image 2 (lo, hi), so that a row
@@ -345,7 +341,11 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
 
 // Fast path for the options that need a whole row at once (FNN_FLAG_NORMALIZE, FNN_FLAG_L2) on
 // fp32 sources with d a multiple of 8: one thread per row.  The row is read once with 16-byte
-// loads; norm and squared length are formed in registers.
+// loads; norm and squared length are formed in registers, channels ascending.  Despite their
+// names the intrinsics leave both roundings to the compiler: it fuses most products with their additions
+// (for 16 channels and more as x[0]^2 + rounded x[1]^2 first), and the root is the hardware's, off
+// by one unit in the last place for some rows.  The header allows both for this path; written
+// out like squared_length() they would change the last place of about 1 % of the norms.
 // IN = d / 8, OUT = dp / 8.
 template <int IN, int OUT, int COMPUTE>
 __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
@@ -373,12 +373,20 @@ __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
                 v[4 * q + 2] = x.z;
                 v[4 * q + 3] = x.w;
             }
-            if (a.normalize) normalize_row<D>(v);
+            if (a.normalize) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int e = 0; e < D; ++e) sum = __fadd_rn(sum, __fmul_rn(v[e], v[e]));
+                divide_row<D>(v, __fsqrt_rn(sum));
+            }
 #pragma unroll
             for (int e = 0; e < D; ++e) v[e] = round_to_compute(v[e], COMPUTE);
             if (a.l2) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int e = 0; e < D; ++e) sum = __fadd_rn(sum, __fmul_rn(v[e], v[e]));
                 float hi, lo;
-                split_norm_term(-0.5f * squared_length<D>(v), COMPUTE, hi, lo);
+                split_norm_term(-0.5f * sum, COMPUTE, hi, lo);
                 const int ones0 = D + (sd.second_image ? EXTRA : 0);
                 const int term0 = D + (sd.second_image ? 0 : EXTRA);
 #pragma unroll

@@ -3,7 +3,9 @@ staged through LDS in runs of 256, copied whole where the map is 16-byte aligned
 together, element by element otherwise.  How the caller stores a map must not change a single bit of the
 result: contiguous, strided and misaligned storage of the same values are compared, at the edges of a run
 and -- fnn_mutual_dense, whose image 1 is stored in another order -- of a super-block of 4096 pixels; and
-the exactly representable values of L2 and SPLIT against the oracle."""
+the exactly representable values of L2 and SPLIT against the oracle.  Normalised rows are compared channel
+by channel with the oracle's, on Gaussian rows whose sums round at every step (the header's
+exception, the norms of aligned fp32 rows, is held to its bound).  Squared lengths likewise, against 64 bits."""
 import numpy as np
 import pytest
 import torch
@@ -74,4 +76,22 @@ def test_normalised_rows_are_the_defined_ones_bit_for_bit(compute, kw, dtype, d)
     want = {"f32": y, "f16": sum(oracle.split_fp16(y)) if kw else oracle.round_fp16(y), "bf16": oracle.round_bf16(y)}[compute]
     for stride, offset in ((d, 0), (d, 1), (d + 4, 0), (d + 1, 3), (3 * d + 1, 2)):
         got = prepared(stored(x, dtype, stride, offset), compute, normalize=True, **kw)
-        assert np.array_equal(got, want), (stride, offset)
+        if dtype == torch.float32 and d % 8 == 0 and stride % 4 == 0 and offset % 4 == 0 and not kw:
+            # the header's exception.  Both sums of d rounded steps (and one rounded product) lie within (2 d + 1) 2^-24
+            # of each other, their roots within half of that and one last place (2^-23), and both divisions round
+            # (2^-24 each); in a 16-bit format that may carry a value over to its neighbour
+            far = np.abs(got - want) > np.abs(want) * {"f32": (d + 4.5) * 2.0**-24, "f16": 2.0**-10, "bf16": 2.0**-7}[compute]
+            assert not far.any() and (got == want).mean() > (0.5 if compute == "f32" else 0.999), (stride, offset)
+        else:
+            assert np.array_equal(got, want), (stride, offset)
+
+
+@pytest.mark.parametrize("d", [5, 8, 16, 24, 28])
+def test_squared_lengths_in_fp32(d):
+    x = dev(lengthy_maps(d, 1030, d))
+    want = -0.5 * (host(x).astype(np.float64) ** 2).sum(axis=1)
+    zero = torch.zeros((1, d), device=x.device)
+    for stride, offset in ((d, 0), (d, 1), (d + 4, 0), (d + 1, 3)):
+        # against a zero row the score is the length's own term: d squares and d sums, each rounded at most once
+        score = host(fnn.fnn_nearest(stored(x, torch.float32, stride, offset), zero, compute="f32", l2=True)[1])[0]
+        assert (np.abs(score - want) <= np.abs(want) * 2 * d * 2.0**-24).all(), (stride, offset)
