@@ -87,7 +87,7 @@ const char* fnn_trace_kind_name(int32_t kind) {
         case TK_PREP: return "prep_kernel";
         case TK_FILL: return "fill_none_kernel";
         case TK_SEARCH: return "search_kernel";
-        case TK_RECIP_STEP: return "recip_step_kernel";
+        case TK_RECIP_STEP: return "resolve_step_kernel";
         case TK_RECIP_DEDUP: return "recip_dedup_kernel";
         case TK_DENSE: return "dense_kernel";
         case TK_DENSE_FINAL: return "dense_final_kernels";

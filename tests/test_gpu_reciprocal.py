@@ -184,3 +184,15 @@ def test_bookkeeping_over_several_rounds_of_slots(batch, n_seeds):
     got = run_reciprocal([a] * batch, [b] * batch, np.repeat(seeds[None], batch, axis=0), 4, "f16")
     for p in {0, batch - 1}:
         check_reciprocal_exact(got, p, ref)
+
+
+def test_trace_names_the_launches_of_an_iteration():
+    # prepare, search and its resolve pass; per iteration the search back, its resolve pass with the bookkeeping, and
+    # (but for the last) the search forward with its resolve pass; the final sort
+    a, b = exact_maps(9, 2100, 1999, 24)
+    fnn.fnn_trace_begin(64)
+    run_reciprocal([a], [b], np.arange(0, 2100, 7, dtype=np.int32)[None], 3, "f16")
+    names = [name for name, _ in fnn.fnn_trace_end(64)]
+    forward = ["search_kernel", "resolve_kernel"]
+    back = ["search_kernel", "resolve_step_kernel"]
+    assert names == ["prep_kernel"] + (forward + back) * 3 + ["recip_dedup_kernel"]
