@@ -201,7 +201,7 @@ struct WalkArgs {
     int32_t n_words;       // ceil(n / 32)
     const int32_t* seeds;  // [batch][n_seeds]
     int32_t n_seeds;
-    int32_t max_iter;
+    int32_t max_iter;      // at least 1
     int32_t* seed_i;
     int32_t* seed_j;
     int32_t* seed_iter;

@@ -100,8 +100,8 @@ __device__ __forceinline__ void search_unit(const SearchArgs& a, const char* src
             ring[p] = O::load_tile(tgt + (int64_t)(t0 + p) * (32 * O::ROW_BYTES), c, h);
     }
 
-    // blocks past the live queries of the last row group are computed on row 0 and dropped;
-    // a whole group of R blocks past them is skipped
+    // blocks past the live queries of the last row group repeat the last one and are dropped; a
+    // whole group of R blocks past them is skipped
     Frag q[G][R];
     float best[G][R];
     int best_tile[G][R];

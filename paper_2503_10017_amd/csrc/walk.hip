@@ -155,14 +155,14 @@ __global__ __launch_bounds__(WALK_THREADS) void recip_walk_kernel(WalkArgs a) {
     for (int i = me; i < a.n_words; i += WALK_THREADS) bitmap[i] = 0;
     for (int t = 0; n_act > 0; ++t) {  // n_act is uniform in the workgroup; it is 0 after max_iter trips at the latest
         walk_search<CT, DP>(p1, a.rows1, u, p2, a.m, n_act, keys, v);       // V^t = NN_2(U^t)
-        if (a.max_iter > 0) walk_search<CT, DP>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
+        walk_search<CT, DP>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
         const bool last = t + 1 >= a.max_iter;
         bool survive = false;
         int32_t u_next = 0, my_sid = 0;
         if (me < n_act) {
             my_sid = sid[me];
             u_next = w[me];
-            const bool converged = a.max_iter > 0 && u_next == u[me];
+            const bool converged = u_next == u[me];
             survive = !converged && !last;
             if (!survive) {
                 a.seed_i[base + my_sid] = u[me];

@@ -8,7 +8,8 @@ import torch
 
 import oracle
 import paper_2503_10017_amd as fnn
-from gpu_helpers import check_reciprocal_exact, dev, exact_maps, host
+import synth_inputs as synth
+from gpu_helpers import GAP_ROUNDED, check_reciprocal_exact, check_reciprocal_pinned, dev, exact_maps, host
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +78,40 @@ def test_seeds_that_move_to_the_last_iteration(n_seeds):
         assert walked == (n_seeds == 96)
         assert np.array_equal(got["seed_i"][0], np.minimum(seeds[0] + max_iter - 1, d - 1))
         check_reciprocal_exact(got, 0, oracle.reciprocal(a, b, seeds[0], max_iter))
+
+
+@pytest.mark.parametrize("walks,w,h,sub", [(True, 40, 28, 4), (False, 48, 40, 4)])     # 3 and 4 blocks of seeds
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+def test_squared_distance_on_both_routes(walks, w, h, sub, compute):
+    a, b = synth.exact_pair(77, w, h, 24)
+    seeds = synth.grid_seeds(w, h, sub)
+    got, walked = traced([a], [b], seeds[None], 10, compute, l2=True)
+    assert walked == walks
+    check_reciprocal_exact(got, 0, oracle.reciprocal(a, b, seeds, 10, metric="l2"))
+
+
+@pytest.mark.parametrize("walks,n_seeds", [(True, 90), (False, 130)])
+@pytest.mark.parametrize("compute,dtype,d", [("f16", torch.float16, 24), ("bf16", torch.bfloat16, 16), ("f16", torch.float16, 32)])
+def test_maps_used_in_place_on_both_routes(walks, n_seeds, compute, dtype, d):
+    """Whole 32-pixel tiles of packed rows in the compute format, stacked: no prepared copy, and no padding behind the last row."""
+    maps = [exact_maps(60 + k, 1024, 992, d) for k in range(2)]
+    seeds = np.random.default_rng(n_seeds).integers(0, 1024, size=(2, n_seeds)).astype(np.int32)
+    stack = [dev(np.stack([m[side] for m in maps])).to(dtype) for side in range(2)]
+    fnn.fnn_trace_begin(128)
+    out = fnn.fnn_reciprocal(stack[0], stack[1], dev(seeds), max_iter=10, compute=compute)
+    torch.cuda.synchronize()
+    names = [name for name, _ in fnn.fnn_trace_end(128)]
+    assert names[0] == ("recip_walk_kernel" if walks else "prep_kernel") and ("recip_walk_kernel" in names) == walks
+    for p in range(2):
+        check_reciprocal_exact({k: host(v) for k, v in out.items()}, p, oracle.reciprocal(*maps[p], seeds[p], 10))
+
+
+def test_normalised_pair_on_both_routes():
+    a, b, _ = synth.warped_pair(61, 40, 30, 24)
+    rng = np.random.default_rng(5)
+    a, b = (x * rng.uniform(0.1, 9.0, size=(x.shape[0], 1)).astype(np.float32) for x in (a, b))
+    ra, rb = (oracle.round_fp16(oracle.normalize(x)) for x in (a, b))
+    for seeds, walks in ((np.arange(0, 1200, 13, dtype=np.int32), True), (np.arange(0, 1200, 9, dtype=np.int32), False)):
+        got, walked = traced([a], [b], seeds[None], 10, "f16", normalize=True)
+        assert walked == walks
+        check_reciprocal_pinned(got, 0, oracle.reciprocal(ra, rb, seeds, 10), ra, rb, GAP_ROUNDED)
