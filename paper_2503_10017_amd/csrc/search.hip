@@ -406,10 +406,12 @@ void search_first_kernel(FirstSearchArgs fa) {
                 best_tile[g][r] = 0x7FFFFFFF;
             }
 
-        // The quads of a chunk would all read the same tile at the same moment and queue on one channel of
-        // L2: they start up to 2 us apart instead (every pixel of a 512x384 pair as a query, 128
-        // quads per chunk: 1660 against 1715 us).
-        for (int i = 0; i < (quad & 7); ++i) __builtin_amdgcn_s_sleep(8);
+        // The quads of a chunk that read the caller's map would all ask for the same fp32 tile at the same moment
+        // and queue on one channel of L2: they start up to 2 us apart instead (fp16, every pixel of a 512x384
+        // pair as a query, 128 quads per chunk: 1756 us so, 1786 us in step).  Prepared tiles are half the bytes and
+        // do not queue, there the late start only costs (stored bf16 1593 us so, 1545 us in step; fp16 1685 and 1649).
+        if constexpr (RAWT)
+            for (int i = 0; i < (quad & 7); ++i) __builtin_amdgcn_s_sleep(8);
 
         // one turn: stage my tile of the turn, then multiply the four staged tiles
         auto turn = [&](int k, auto slot_tag) {
