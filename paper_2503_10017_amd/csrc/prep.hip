@@ -81,8 +81,31 @@ __device__ __forceinline__ void prep_side_jobs(const PrepArgs& a) {
     }
 }
 
-// Plain casts of any storage format, channel count, row stride and alignment: one thread produces 8
-// consecutive channels of one output row, element by element.
+// The norm of one source descriptor, and -1/2 |x|^2 of one as prepared (divided by `norm` if that is set, then
+// rounded to the compute format), read element by element: squared_length() in a rolled loop.
+__device__ __forceinline__ float descriptor_norm(const void* src, int64_t first, int d, int dtype) {
+    float sum = 0.0f;
+    for (int k = 0; k < d; ++k) {
+        const float x = load_as_float(src, first + k, dtype);
+        sum = __builtin_fmaf(x, x, sum);
+    }
+    return __builtin_sqrtf(sum);
+}
+__device__ __forceinline__ float prepared_norm_term(const void* src, int64_t first, int d, int dtype, int compute, float norm) {
+    float sum = 0.0f;
+    for (int k = 0; k < d; ++k) {
+        float x = load_as_float(src, first + k, dtype);
+        if (norm > 0.0f) x = __fdiv_rn(x, norm);
+        x = round_to_compute(x, compute);
+        sum = __builtin_fmaf(x, x, sum);
+    }
+    return -0.5f * sum;
+}
+
+// Any storage format, channel count, row stride and alignment: one thread produces 8 consecutive channels
+// of one output row, element by element.  OPTIONS: with NORMALIZE, L2 or SPLIT, where every thread reads
+// the whole row for a norm; launch_prep() says which maps take that and which the staged kernel below.
+template <bool OPTIONS>
 __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
     prep_side_jobs(a);
     const int side_idx = blockIdx.y / a.batch;
@@ -93,6 +116,8 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
     const int esize = (a.compute == FNN_F32) ? 4 : 2;
     char* dst = reinterpret_cast<char*>(sd.dst) + (int64_t)b * sd.n_pad * a.dp * esize;
     const void* src = sd.src[b];
+    const bool split = OPTIONS && a.split;
+    const int data_channels = split ? 3 * a.d : a.d;  // channels that carry data: the descriptor, or three copies of it
     for (int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; item < total;
          item += (int64_t)gridDim.x * blockDim.x) {
         const int64_t row = item / groups;                               // stored row
@@ -102,7 +127,45 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int k = g * 8 + e;
-            v[e] = (pix < sd.n && k < a.d) ? load_as_float(src, pix * sd.row_stride + k, sd.dtype) : 0.0f;
+            const int ch = split ? k % a.d : k;
+            v[e] = (pix < sd.n && k < data_channels) ? load_as_float(src, pix * sd.row_stride + ch, sd.dtype) : 0.0f;
+        }
+        if constexpr (OPTIONS) {
+            float norm = 0.0f;
+            if (a.normalize && pix < sd.n) {
+                norm = descriptor_norm(src, pix * sd.row_stride, a.d, sd.dtype);
+                if (norm > 0.0f) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = __fdiv_rn(v[e], norm);
+                }
+            }
+            if (split) {  // the copies' layout: see prep_staged_kernel
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int k = g * 8 + e;
+                    if (k < data_channels) {
+                        const int copy = k / a.d;
+                        const float hi = (float)(_Float16)v[e];
+                        const float lo = __fsub_rn(v[e], hi);
+                        v[e] = (copy == 0 || copy == (sd.second_image ? 2 : 1)) ? hi : lo;
+                    }
+                }
+            }
+            // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2)
+            const int extra = a.compute == FNN_F32 ? 1 : 2;
+            if (a.l2 && pix < sd.n && g * 8 + 8 > a.d && g * 8 < a.d + 2 * extra) {
+                float hi, lo;
+                split_norm_term(prepared_norm_term(src, pix * sd.row_stride, a.d, sd.dtype, a.compute, norm), a.compute, hi, lo);
+                const int ones0 = a.d + (sd.second_image ? extra : 0);   // first unit channel
+                const int term0 = a.d + (sd.second_image ? 0 : extra);   // first norm channel
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int k = g * 8 + e;
+                    if (k >= ones0 && k < ones0 + extra) v[e] = 1.0f;
+                    if (k == term0) v[e] = hi;
+                    if (extra == 2 && k == term0 + 1) v[e] = lo;
+                }
+            }
         }
         if (a.compute == FNN_F32) {
             float4* out = reinterpret_cast<float4*>(dst + (row * a.dp + g * 8) * 4);
@@ -129,11 +192,10 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
 // memory (16 bytes per lane where the rows are aligned and close together, else one element per
 // lane), every thread then makes one output row in registers, and the finished rows leave LDS as
 // one contiguous run of 16-byte stores.  What bounds it is the memory traffic.  One 512x384 pair, 24
-// channels, before (every thread reading its part of a row element by element, and the whole row
-// again for a norm; with FNN_FLAG_SPLIT one thread per row, lanes 96 bytes in and 160 bytes out
-// apart) and now, microseconds: fp16 maps with FNN_FLAG_L2 39.6 / 16.6, with FNN_FLAG_NORMALIZE
-// 35.2 / 14.4, fp32 maps with FNN_FLAG_SPLIT 32.3 / 19.4; 17-channel fp32 maps with
-// FNN_FLAG_NORMALIZE 34.1 / 17.9 (two pairs with L2 69.6 / 26.0, four with SPLIT 115 / 64); maps of a few thousand pixels between 4 us less and 2 us more.  Plain
+// channels, every thread reading its part of a row element by element, and the whole row again for a
+// norm (with FNN_FLAG_SPLIT one thread per row, lanes 96 bytes in and 160 bytes out apart), against this, microseconds:
+// fp16 maps with FNN_FLAG_L2 39.2 / 17.4, with FNN_FLAG_NORMALIZE 36.1 / 14.5, fp32 maps with FNN_FLAG_SPLIT
+// 32.9 / 19.2; 17-channel fp32 maps with FNN_FLAG_NORMALIZE 35.3 / 18.4.  Fewer rows: see staging_pays().  Plain
 // casts stay with the kernel above (23-channel bf16 14 against 16 us, small maps 4 against 8).
 constexpr int STAGE_ROWS = 256;
 constexpr int STAGE_MAX_ROW_BYTES = 192;  // widest row held in LDS (48 KB per workgroup)
@@ -272,28 +334,15 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
                 hi[k] = __builtin_bit_cast(uint16_t, x);
                 lo[k] = float_to_f16_rne(__fsub_rn(v[k], (float)x));
             }
-            if (d == IN * 8) {  // uniform: a copy is IN whole 16-byte vectors
 #pragma unroll
-                for (int g = 0; g < IN; ++g) {
-                    const uint4 h4 = pack8(hi + 8 * g), l4 = pack8(lo + 8 * g);
-                    uint4* o = reinterpret_cast<uint4*>(out) + g;
-                    o[0] = h4;
-                    o[lo_copy * IN] = l4;
-                    o[(3 - lo_copy) * IN] = h4;
-                }
-                for (int q = 3 * IN; q < a.dp / 8; ++q) reinterpret_cast<uint4*>(out)[q] = make_uint4(0, 0, 0, 0);
-            } else {
-                uint16_t* o = reinterpret_cast<uint16_t*>(out);
-#pragma unroll
-                for (int k = 0; k < IN * 8; ++k) {
-                    if (k < d) {
-                        o[k] = hi[k];
-                        o[lo_copy * d + k] = lo[k];
-                        o[(3 - lo_copy) * d + k] = hi[k];
-                    }
-                }
-                for (int k = 3 * d; k < a.dp; ++k) o[k] = 0;
+            for (int g = 0; g < IN; ++g) {  // d == 8 * IN here (see staging_pays), so a copy is IN whole 16-byte vectors
+                const uint4 h4 = pack8(hi + 8 * g), l4 = pack8(lo + 8 * g);
+                uint4* o = reinterpret_cast<uint4*>(out) + g;
+                o[0] = h4;
+                o[lo_copy * IN] = l4;
+                o[(3 - lo_copy) * IN] = h4;
             }
+            for (int q = 3 * IN; q < a.dp / 8; ++q) reinterpret_cast<uint4*>(out)[q] = make_uint4(0, 0, 0, 0);
         } else {
             // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2)
             float hi = 0.0f, lo = 0.0f;
@@ -427,6 +476,50 @@ static hipError_t launch_prep_rows(const PrepArgs& a, dim3 grid, hipStream_t s) 
     return launch(TK_PREP, prep_rows_f32_kernel<IN, OUT, FNN_BF16>, grid, dim3(256), 0, s, a);
 }
 
+// FNN_FLAG_SPLIT on few aligned fp32 rows of D = 8 * IN channels: one thread per row, straight from memory to memory
+// (the copies' layout: see prep_staged_kernel).
+template <int IN>
+__global__ __launch_bounds__(256) void prep_split_rows_kernel(PrepArgs a) {
+    prep_side_jobs(a);
+    const int side_idx = blockIdx.y / a.batch;
+    const int b = blockIdx.y % a.batch;
+    const PrepSide& sd = a.side[side_idx];
+    constexpr int D = IN * 8, OUT = padded_d(3 * D, FNN_F16) / 8;
+    uint4* dst = reinterpret_cast<uint4*>(sd.dst) + (int64_t)b * sd.n_pad * OUT;
+    const float* src = reinterpret_cast<const float*>(sd.src[b]);
+    const int lo_copy = sd.second_image ? 1 : 2;
+    for (uint32_t row = blockIdx.x * blockDim.x + threadIdx.x; row < (uint32_t)sd.n_pad; row += gridDim.x * blockDim.x) {
+        const int64_t pix = sd.segment_major ? slot_pixel(row) : (int64_t)row;
+        float v[D];
+#pragma unroll
+        for (int q = 0; q < IN * 2; ++q) {
+            const float4 x = pix < sd.n ? reinterpret_cast<const float4*>(src + pix * sd.row_stride)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+            v[4 * q + 0] = x.x;
+            v[4 * q + 1] = x.y;
+            v[4 * q + 2] = x.z;
+            v[4 * q + 3] = x.w;
+        }
+        if (a.normalize) divide_row<D>(v, __builtin_sqrtf(squared_length<D>(v)));
+        uint16_t hi[D], lo[D];
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            const _Float16 x = (_Float16)v[k];
+            hi[k] = __builtin_bit_cast(uint16_t, x);
+            lo[k] = float_to_f16_rne(__fsub_rn(v[k], (float)x));
+        }
+        uint4* out = dst + (int64_t)row * OUT;
+#pragma unroll
+        for (int g = 0; g < IN; ++g) {
+            const uint4 h4 = pack8(hi + 8 * g);
+            out[g] = h4;
+            out[lo_copy * IN + g] = pack8(lo + 8 * g);
+            out[(3 - lo_copy) * IN + g] = h4;
+        }
+#pragma unroll
+        for (int q = 3 * IN; q < OUT; ++q) out[q] = make_uint4(0, 0, 0, 0);
+    }
+}
+
 // Fast path: fp32 source whose rows are whole 16-byte vectors and need no channel padding
 // (d == dp).  GROUPS = dp / 8 is a compile-time constant so that the row / group split of the
 // item index costs a multiply, and every thread moves two 16-byte loads into one (16-bit
@@ -477,6 +570,15 @@ static hipError_t launch_prep_fast(const PrepArgs& a, dim3 grid, hipStream_t s) 
     return launch(TK_PREP, prep_f32_kernel<GROUPS, FNN_BF16>, grid, dim3(256), 0, s, a);
 }
 
+// Rows that the staged kernel copies whole, gaps included: 16-byte aligned maps whose rows lie close together.
+static bool rows_copied_whole(const PrepArgs& a, const PrepSide& sd) {
+    if (sd.row_stride > STAGE_MAX_ROW_BYTES || sd.row_stride * elem_size(sd.dtype) > STAGE_MAX_ROW_BYTES || sd.row_stride > 2 * (int64_t)a.d)
+        return false;
+    for (int b = 0; b < a.batch; ++b)
+        if (((uintptr_t)sd.src[b] % 16) != 0) return false;
+    return true;
+}
+
 template <int IN>
 static hipError_t launch_prep_staged(PrepArgs a, hipStream_t s) {
     int64_t most = 0;
@@ -484,9 +586,7 @@ static hipError_t launch_prep_staged(PrepArgs a, hipStream_t s) {
     for (int i = 0; i < a.n_sides; ++i) {
         PrepSide& sd = a.side[i];
         const int64_t stride_bytes = sd.row_stride * elem_size(sd.dtype);
-        // rows copied whole, gaps included: 16-byte aligned maps whose rows lie close together
-        sd.vector_rows = sd.row_stride <= STAGE_MAX_ROW_BYTES && stride_bytes <= STAGE_MAX_ROW_BYTES && sd.row_stride <= 2 * (int64_t)a.d;
-        for (int b = 0; b < a.batch && sd.vector_rows; ++b) sd.vector_rows = ((uintptr_t)sd.src[b] % 16) == 0;
+        sd.vector_rows = rows_copied_whole(a, sd);
         const int staged = sd.vector_rows ? (int)stride_bytes : a.d * elem_size(sd.dtype);
         if (staged > row_bytes) row_bytes = staged;
         if (sd.n_pad > most) most = sd.n_pad;
@@ -516,6 +616,28 @@ hipError_t launch_fill_i32f32(int32_t* idx, float* score, int64_t count, hipStre
 
 // The side jobs alone.
 __global__ __launch_bounds__(256) void init_kernel(PrepArgs a) { prep_side_jobs(a); }
+
+// Whether maps with options go through LDS.  Few rows are all latency, and staging adds three barriers and,
+// where rows are not copied whole or are not whole 8-channel groups, a longer chain per thread.  One pair, fp32 maps
+// of 24 channels off their alignment, element by element against staged, microseconds: NORMALIZE 6.2 / 9.3 at
+// 2 x 3072 rows, 7.7 / 9.6 at 2 x 12288, 16.1 / 11.2 at 2 x 49152; L2 8.9 / 9.6, 9.0 / 9.8, 13.8 / 12.0; SPLIT 5.1 / 9.3,
+// 7.3 / 10.0, 20.1 / 14.4.  Up to 8 channels one thread holds a row anyway (fp16 maps of 5, fp32 products: 4.2 / 4.8 at
+// 2 x 3072, 10.3 / 12.8 at 2 x 196608; 16-bit products cross near 2 x 65536).  The copies of a SPLIT row that is not made
+// of whole groups would be written to LDS two bytes at a time, lanes a row apart (17 channels: 5.0 / 12.0, 43 / 53).  Aligned
+// fp32 maps of 17 channels copied whole: NORMALIZE 5.4 / 6.6 at 2 x 3072, 10.0 / 9.1 at 2 x 49152, L2 7.0 / 6.7 and 10.6 / 8.3.
+static int64_t rows_prepared(const PrepArgs& a) {
+    int64_t rows = 0;
+    for (int i = 0; i < a.n_sides; ++i) rows += a.side[i].n_pad * a.batch;
+    return rows;
+}
+static bool staging_pays(const PrepArgs& a) {
+    const int64_t rows = rows_prepared(a);
+    bool whole = true;
+    for (int i = 0; i < a.n_sides; ++i) whole = whole && rows_copied_whole(a, a.side[i]);
+    if (a.split && a.d % 8 != 0) return false;
+    if (a.d <= 8 && !a.split) return a.compute != FNN_F32 && rows > 131072;
+    return rows > 32768 || (whole && (a.d % 8 == 0 || a.l2));
+}
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
     int64_t most = 0;
@@ -551,6 +673,16 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
         if (in == 3 && out == 4) return launch_prep_rows<3, 4>(a, grid, s);
         if (in == 4 && out == 4) return launch_prep_rows<4, 4>(a, grid, s);
     }
+    // one pair of fp32 maps of 24 channels, a thread per row against staged: 4.2 / 5.3 us at 2 x 3072 rows, 6.2 / 6.0 at
+    // 2 x 12288 (four pairs of 3072: 5.1 / 6.0), 12.1 / 10.4 at 2 x 49152
+    if (vector_rows && a.split && a.d % 8 == 0 && rows_prepared(a) <= 24576) {
+        switch (a.d / 8) {
+            case 1: return launch(TK_PREP, prep_split_rows_kernel<1>, grid, dim3(256), 0, s, a);
+            case 2: return launch(TK_PREP, prep_split_rows_kernel<2>, grid, dim3(256), 0, s, a);
+            case 3: return launch(TK_PREP, prep_split_rows_kernel<3>, grid, dim3(256), 0, s, a);
+            case 4: return launch(TK_PREP, prep_split_rows_kernel<4>, grid, dim3(256), 0, s, a);
+        }
+    }
     const bool fast = vector_rows && a.d == a.dp && !a.l2 && !a.normalize && !a.split;
     if (fast) {
         switch (a.dp / 8) {
@@ -560,7 +692,8 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
             case 4: return launch_prep_fast<4>(a, grid, s);
         }
     }
-    if (!a.normalize && !a.l2 && !a.split) return launch(TK_PREP, prep_kernel, grid, dim3(256), 0, s, a);
+    if (!a.normalize && !a.l2 && !a.split) return launch(TK_PREP, prep_kernel<false>, grid, dim3(256), 0, s, a);
+    if (!staging_pays(a)) return launch(TK_PREP, prep_kernel<true>, grid, dim3(256), 0, s, a);
     switch ((a.d + 7) / 8) {
         case 1: return launch_prep_staged<1>(a, s);
         case 2: return launch_prep_staged<2>(a, s);

@@ -1,6 +1,6 @@
-"""The prepare step with options that need a whole row (FNN_FLAG_NORMALIZE, FNN_FLAG_L2, FNN_FLAG_SPLIT): rows are
+"""The prepare step with options that need a whole row (FNN_FLAG_NORMALIZE, FNN_FLAG_L2, FNN_FLAG_SPLIT).  Many rows are
 staged through LDS in runs of 256, copied whole where the map is 16-byte aligned and its rows lie close
-together, element by element otherwise.  How the caller stores a map must not change a single bit of the
+together, element by element otherwise; few rows are prepared element by element or one per thread.  How the caller stores a map must not change a single bit of the
 result: contiguous, strided and misaligned storage of the same values are compared, at the edges of a run
 and -- fnn_mutual_dense, whose image 1 is stored in another order -- of a super-block of 4096 pixels; and
 the exactly representable values of L2 and SPLIT against the oracle.  Normalised rows are compared channel
@@ -31,25 +31,26 @@ def stored(x, dtype, stride, offset):
                                                   ("l2", "bf16", torch.float32), ("l2", "f32", torch.float32),
                                                   ("split", "f16", torch.float32)])
 @pytest.mark.parametrize("n,m,d", [(255, 257, 24), (256, 33, 17), (4097, 513, 8), (1, 4095, 5), (300, 290, 28)])
-def test_storage_does_not_change_the_result(option, compute, dtype, n, m, d):
+@pytest.mark.parametrize("batch", [1, 64])       # few rows and many: more than 32768 where n + m is 513 or more
+def test_storage_does_not_change_the_result(option, compute, dtype, n, m, d, batch):
     a, b = exact_maps(n + m + d, n, m, d)
     ta, tb = dev(a).to(dtype), dev(b).to(dtype)
     want = dense = None
     for stride, offset in ((d, 0), (d + 5, 0), (d, 1), (d + 1, 3), (2 * d, 0), (3 * d + 1, 2)):
         sa, sb = stored(ta, dtype, stride, offset), stored(tb, dtype, stride, offset)
+        sa, sb = [sa] * batch, [sb] * batch
         idx, score = (host(x) for x in fnn.fnn_nearest(sa, sb, compute=compute, **{option: True}))
         out = {k: host(v) for k, v in fnn.fnn_mutual_dense(sa, sb, compute=compute, **{option: True}).items()}
         if want is None:
-            want, dense = (idx, score), out
+            want, dense = (idx[0], score[0]), {k: v[0] for k, v in out.items()}
             if option != "normalize":
                 ref = oracle.nearest_l2(a, b) if option == "l2" else oracle.nearest(a, b)
                 assert np.array_equal(idx[0], ref[0])
                 assert np.array_equal(-2.0 * score[0] if option == "l2" else score[0], ref[1])
-        assert np.array_equal(idx, want[0]) and np.array_equal(score, want[1]), (stride, offset)
-        n_pairs = int(dense["n_pairs"][0])
-        for key in ("nn12", "s12", "nn21", "s21", "n_pairs"):
-            assert np.array_equal(out[key], dense[key]), (key, stride, offset)
-        assert np.array_equal(out["pairs"][0, :n_pairs], dense["pairs"][0, :n_pairs])
+        for p in range(batch):
+            assert np.array_equal(idx[p], want[0]) and np.array_equal(score[p], want[1]), (stride, offset)
+            for key in ("nn12", "s12", "nn21", "s21", "n_pairs", "pairs"):
+                assert np.array_equal(out[key][p], dense[key]), (key, stride, offset)
 
 
 def lengthy_maps(seed, n, d):
@@ -69,9 +70,10 @@ def prepared(x, compute, **kw):
 
 @pytest.mark.parametrize("compute,kw", [("f32", {}), ("f16", {}), ("bf16", {}), ("f16", {"split": True})])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
-@pytest.mark.parametrize("d", [5, 8, 16, 17, 24, 32])
-def test_normalised_rows_are_the_defined_ones_bit_for_bit(compute, kw, dtype, d):
-    x = dev(lengthy_maps(d, 1030, d)).to(dtype)
+@pytest.mark.parametrize("n,d", [(1030, 5), (30000, 5), (1030, 8), (20000, 8), (500, 16), (2100, 16), (1030, 17), (2000, 17), (200, 24), (1030, 24),
+                                 (1500, 24), (200, 32), (1100, 32)])        # few rows and many (n rows in d pairs)
+def test_normalised_rows_are_the_defined_ones_bit_for_bit(compute, kw, dtype, n, d):
+    x = dev(lengthy_maps(d, n, d)).to(dtype)
     y = oracle.normalize(host(x.float()))
     want = {"f32": y, "f16": sum(oracle.split_fp16(y)) if kw else oracle.round_fp16(y), "bf16": oracle.round_bf16(y)}[compute]
     for stride, offset in ((d, 0), (d, 1), (d + 4, 0), (d + 1, 3), (3 * d + 1, 2)):
@@ -86,9 +88,10 @@ def test_normalised_rows_are_the_defined_ones_bit_for_bit(compute, kw, dtype, d)
             assert np.array_equal(got, want), (stride, offset)
 
 
+@pytest.mark.parametrize("n", [1030, 40000])
 @pytest.mark.parametrize("d", [5, 8, 16, 24, 28])
-def test_squared_lengths_in_fp32(d):
-    x = dev(lengthy_maps(d, 1030, d))
+def test_squared_lengths_in_fp32(n, d):
+    x = dev(lengthy_maps(d, n, d))
     want = -0.5 * (host(x).astype(np.float64) ** 2).sum(axis=1)
     zero = torch.zeros((1, d), device=x.device)
     for stride, offset in ((d, 0), (d, 1), (d + 4, 0), (d + 1, 3)):
