@@ -334,15 +334,28 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
                 hi[k] = __builtin_bit_cast(uint16_t, x);
                 lo[k] = float_to_f16_rne(__fsub_rn(v[k], (float)x));
             }
+            if (d == IN * 8) {  // uniform: a copy is IN whole 16-byte vectors
 #pragma unroll
-            for (int g = 0; g < IN; ++g) {  // d == 8 * IN here (see staging_pays), so a copy is IN whole 16-byte vectors
-                const uint4 h4 = pack8(hi + 8 * g), l4 = pack8(lo + 8 * g);
-                uint4* o = reinterpret_cast<uint4*>(out) + g;
-                o[0] = h4;
-                o[lo_copy * IN] = l4;
-                o[(3 - lo_copy) * IN] = h4;
+                for (int g = 0; g < IN; ++g) {
+                    const uint4 h4 = pack8(hi + 8 * g), l4 = pack8(lo + 8 * g);
+                    uint4* o = reinterpret_cast<uint4*>(out) + g;
+                    o[0] = h4;
+                    o[lo_copy * IN] = l4;
+                    o[(3 - lo_copy) * IN] = h4;
+                }
+                for (int q = 3 * IN; q < a.dp / 8; ++q) reinterpret_cast<uint4*>(out)[q] = make_uint4(0, 0, 0, 0);
+            } else {
+                uint16_t* o = reinterpret_cast<uint16_t*>(out);
+#pragma unroll
+                for (int k = 0; k < IN * 8; ++k) {
+                    if (k < d) {
+                        o[k] = hi[k];
+                        o[lo_copy * d + k] = lo[k];
+                        o[(3 - lo_copy) * d + k] = hi[k];
+                    }
+                }
+                for (int k = 3 * d; k < a.dp; ++k) o[k] = 0;
             }
-            for (int q = 3 * IN; q < a.dp / 8; ++q) reinterpret_cast<uint4*>(out)[q] = make_uint4(0, 0, 0, 0);
         } else {
             // L2 score: channels d.. hold the unit partners and -|x|^2/2 (see FNN_FLAG_L2)
             float hi = 0.0f, lo = 0.0f;
@@ -622,9 +635,13 @@ __global__ __launch_bounds__(256) void init_kernel(PrepArgs a) { prep_side_jobs(
 // of 24 channels off their alignment, element by element against staged, microseconds: NORMALIZE 6.2 / 9.3 at
 // 2 x 3072 rows, 7.7 / 9.6 at 2 x 12288, 16.1 / 11.2 at 2 x 49152; L2 8.9 / 9.6, 9.0 / 9.8, 13.8 / 12.0; SPLIT 5.1 / 9.3,
 // 7.3 / 10.0, 20.1 / 14.4.  Up to 8 channels one thread holds a row anyway (fp16 maps of 5, fp32 products: 4.2 / 4.8 at
-// 2 x 3072, 10.3 / 12.8 at 2 x 196608; 16-bit products cross near 2 x 65536).  The copies of a SPLIT row that is not made
-// of whole groups would be written to LDS two bytes at a time, lanes a row apart (17 channels: 5.0 / 12.0, 43 / 53).  Aligned
-// fp32 maps of 17 channels copied whole: NORMALIZE 5.4 / 6.6 at 2 x 3072, 10.0 / 9.1 at 2 x 49152, L2 7.0 / 6.7 and 10.6 / 8.3.
+// 2 x 3072, 10.3 / 12.8 at 2 x 196608; 16-bit products cross near 2 x 65536).  Aligned fp32 maps of 17 channels copied
+// whole: NORMALIZE 5.4 / 6.6 at 2 x 3072, 10.0 / 9.1 at 2 x 49152, L2 7.0 / 6.7 and 10.6 / 8.3.
+// The copies of a SPLIT row that is not made of whole groups are written to LDS two bytes at a time, lanes a
+// row apart: with 64 prepared channels all of them hit one bank (17 channels: 5.0 / 12.0 at 2 x 3072, 43 / 53 at
+// 2 x 196608), with others it pays for many rows (12 channels: 5.1 / 6.6, 12.3 / 9.2 at 2 x 49152, 35.3 / 21.3; off their
+// alignment 12.2 / 12.3 and 35.5 / 25.6; 31 channels 22.4 / 23.1 and 59.1 / 50.0; off their alignment 22.2 / 28.2 and
+// 59.0 / 61.1).
 static int64_t rows_prepared(const PrepArgs& a) {
     int64_t rows = 0;
     for (int i = 0; i < a.n_sides; ++i) rows += a.side[i].n_pad * a.batch;
@@ -634,7 +651,10 @@ static bool staging_pays(const PrepArgs& a) {
     const int64_t rows = rows_prepared(a);
     bool whole = true;
     for (int i = 0; i < a.n_sides; ++i) whole = whole && rows_copied_whole(a, a.side[i]);
-    if (a.split && a.d % 8 != 0) return false;
+    if (a.split && a.d % 8 != 0) {
+        if (a.d == 1 || a.dp == 64) return false;
+        return a.dp <= 80 ? rows > (whole ? 65536 : 131072) : whole && rows > 131072;
+    }
     if (a.d <= 8 && !a.split) return a.compute != FNN_F32 && rows > 131072;
     return rows > 32768 || (whole && (a.d % 8 == 0 || a.l2));
 }
