@@ -53,8 +53,15 @@ __device__ __forceinline__ void dense_sweep(const DenseArgs& a, const typename O
     using Frag = typename O::Frag;
     constexpr int J = DENSE_J, S = DENSE_S;
     const float ninf = -__builtin_inff();
-    Frag qa = O::load_tile(qbase, c, h);
-    Frag qb = O::load_tile(qbase + 32 * O::ROW_BYTES, c, h);
+    // Which form of the load the masked sweep of the widest fp32 rows takes is the registers' doing: 16 pairs of 4480 and
+    // 129336 pixels 11.05 ms with stream_tile, 12.18 ms with load_tile, one of 10725 398 and 415 us; one of 98304 and
+    // 65000, whose sweeps hardly ever mask, 3.62 and 3.55 ms.  The other rows are slower with it (see stream_tile).
+    const auto load = [&](const char* tile) {
+        if constexpr (TAIL && CT == CT_F32 && DP == 32) return O::stream_tile(tile, c, h);
+        else return O::load_tile(tile, c, h);
+    };
+    Frag qa = load(qbase);
+    Frag qb = load(qbase + 32 * O::ROW_BYTES);
     // Software pipeline: the matrix instructions of the NEXT product pair are issued before
     // the current pair's 32 result registers are folded, so the matrix cores stay busy while
     // the vector ALU works.
@@ -67,8 +74,8 @@ __device__ __forceinline__ void dense_sweep(const DenseArgs& a, const typename O
     for (int t = 0; t < S; t += 2) {
         // prefetch the next two query blocks (the last step reloads its own)
         const int tn = min(t + 2, S - 2);
-        const Frag na = O::load_tile(qbase + (int64_t)tn * 32 * O::ROW_BYTES, c, h);
-        const Frag nb = O::load_tile(qbase + (int64_t)(tn + 1) * 32 * O::ROW_BYTES, c, h);
+        const Frag na = load(qbase + (int64_t)tn * 32 * O::ROW_BYTES);
+        const Frag nb = load(qbase + (int64_t)(tn + 1) * 32 * O::ROW_BYTES);
         float ra = ninf, rb = ninf;
 #pragma unroll
         for (int jt = 0; jt < J; ++jt) {
@@ -687,7 +694,10 @@ void dense_resolve_rows_kernel(DenseArgs a, int32_t* nn12, float* s12) {
         float top = ninf;
 #pragma unroll
         for (int jt = 0; jt < J; ++jt) {
-            const Frag cand = O::load_tile(d2 + (int64_t)min(tbase + jt, a.m_tiles - 1) * (32 * O::ROW_BYTES), c, h);
+            const char* tile = d2 + (int64_t)min(tbase + jt, a.m_tiles - 1) * (32 * O::ROW_BYTES);
+            Frag cand;
+            if constexpr (CT == CT_F32 && DP == 32) cand = O::stream_tile(tile, c, h);  // 399 against 456 us for those 16 pairs
+            else cand = O::load_tile(tile, c, h);
             x[jt] = O::mma(cand, q);
 #pragma unroll
             for (int v = 0; v < 16; ++v)

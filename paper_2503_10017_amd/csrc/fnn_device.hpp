@@ -98,13 +98,22 @@ struct Ops {
 
     // The same for lane c of a 32-pixel tile whose address `tile` is the same in every lane:
     // written as uniform base + 32-bit lane offset so that the load takes its base from scalar
-    // registers and a streaming loop spends no vector instruction on addresses.  (The offset passes
-    // through the empty asm because its widening to 64 bits would otherwise be hoisted out of the
-    // loop, where the load no longer sees that it is a 32-bit offset and adds it to the base itself:
-    // two vector instructions per load and two more registers.)
+    // registers and a streaming loop spends no vector instruction on addresses.
     static __device__ __forceinline__ Frag load_tile(const char* tile, uint32_t c, int h) {
+        return load_at(tile, c * (uint32_t)ROW_BYTES + (uint32_t)h * (uint32_t)LANE_BYTES);
+    }
+    // The same for the loops of the searches.  Their offset passes through the empty asm because its
+    // widening to 64 bits would otherwise be hoisted out of the loop, where the load no longer sees that it is a
+    // 32-bit offset and adds it to the base itself: two vector instructions per load and two more
+    // registers.  (In the dense kernels, whose loads hide behind twice the arithmetic, the asm only gets in the
+    // scheduler's way: fp32 products, 24 channels, two pairs of 248x203 pixels 2702 us with it, 2509 us without; fp16, 24
+    // channels, 16 pairs of 4480 and 129336 pixels 1986 and 1851 us.)
+    static __device__ __forceinline__ Frag stream_tile(const char* tile, uint32_t c, int h) {
         uint32_t off = c * (uint32_t)ROW_BYTES + (uint32_t)h * (uint32_t)LANE_BYTES;
         asm volatile("" : "+v"(off));
+        return load_at(tile, off);
+    }
+    static __device__ __forceinline__ Frag load_at(const char* tile, uint32_t off) {
         Frag f;
 #pragma unroll
         for (int i = 0; i < NV; ++i) f.v[i] = *reinterpret_cast<const uint4*>(tile + (off + 16u * i));
@@ -152,11 +161,17 @@ struct OpsHalf24 {
         return f;
     }
 
-    // uniform tile address + 32-bit lane offsets (see Ops::load_tile)
+    // uniform tile address + 32-bit lane offsets (see Ops::load_tile, Ops::stream_tile)
     static __device__ __forceinline__ Frag load_tile(const char* tile, uint32_t c, int h) {
-        Frag f;
+        return load_at(tile, c * 48u + 16u * (uint32_t)h, c * 48u + 32u + 8u * (uint32_t)h);
+    }
+    static __device__ __forceinline__ Frag stream_tile(const char* tile, uint32_t c, int h) {
         uint32_t lo = c * 48u + 16u * (uint32_t)h, hi = c * 48u + 32u + 8u * (uint32_t)h;
         asm volatile("" : "+v"(lo), "+v"(hi));
+        return load_at(tile, lo, hi);
+    }
+    static __device__ __forceinline__ Frag load_at(const char* tile, uint32_t lo, uint32_t hi) {
+        Frag f;
         f.lo = *reinterpret_cast<const uint4*>(tile + lo);
         f.hi = *reinterpret_cast<const uint2*>(tile + hi);
         return f;

@@ -95,9 +95,9 @@ __device__ __forceinline__ void search_unit(const SearchArgs& a, const char* src
     Frag ring[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        if (!EXACT) ring[p] = O::load_tile(tgt + (int64_t)min(t0 + p, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+        if (!EXACT) ring[p] = O::stream_tile(tgt + (int64_t)min(t0 + p, t1 - 1) * (32 * O::ROW_BYTES), c, h);
         else if (p == 0 || t0 + p < t1)  // uniform; a slot past the end is never used
-            ring[p] = O::load_tile(tgt + (int64_t)(t0 + p) * (32 * O::ROW_BYTES), c, h);
+            ring[p] = O::stream_tile(tgt + (int64_t)(t0 + p) * (32 * O::ROW_BYTES), c, h);
     }
 
     // blocks past the live queries of the last row group repeat the last one and are dropped; a
@@ -129,8 +129,8 @@ __device__ __forceinline__ void search_unit(const SearchArgs& a, const char* src
             const int t = tb + p;
             if (__builtin_expect(t < t1, 1)) {  // uniform
                 const Frag cur = ring[p];
-                if (!EXACT) ring[p] = O::load_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
-                else if (t + P < t1) ring[p] = O::load_tile(tgt + (int64_t)(t + P) * (32 * O::ROW_BYTES), c, h);
+                if (!EXACT) ring[p] = O::stream_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+                else if (t + P < t1) ring[p] = O::stream_tile(tgt + (int64_t)(t + P) * (32 * O::ROW_BYTES), c, h);
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
                     if (__builtin_expect(live[g], 1)) {
@@ -298,7 +298,7 @@ struct FirstTile {
             if (t < t1 && pixel < fa.s.m) return O::load_raw(fa.raw_tgt.map[b] + pixel * fa.raw_tgt.row_stride, h);
             return O::zero_raw();  // padding rows of the prepared map are zero
         } else {
-            return O::load_tile(tgt + (int64_t)min(t, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+            return O::stream_tile(tgt + (int64_t)min(t, t1 - 1) * (32 * O::ROW_BYTES), c, h);
         }
     }
     static __device__ __forceinline__ typename O::Frag fragment(const Pending& p) {

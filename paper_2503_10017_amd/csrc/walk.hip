@@ -64,7 +64,7 @@ __device__ __forceinline__ void walk_search(const char* src, int src_rows, const
 #pragma unroll
         for (int r = 0; r < R; ++r) q[r] = query(slot0 + r * 32 + c);
 #pragma unroll
-        for (int p = 0; p < P; ++p) ring[p] = O::load_tile(tgt + (int64_t)min(t0 + p, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+        for (int p = 0; p < P; ++p) ring[p] = O::stream_tile(tgt + (int64_t)min(t0 + p, t1 - 1) * (32 * O::ROW_BYTES), c, h);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             arrived(q[r]);
@@ -77,7 +77,7 @@ __device__ __forceinline__ void walk_search(const char* src, int src_rows, const
                 const int t = tb + p;
                 if (__builtin_expect(t < t1, 1)) {  // uniform
                     const Frag cur = ring[p];
-                    ring[p] = O::load_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+                    ring[p] = O::stream_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
                     f32x16 acc[R];
 #pragma unroll
                     for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
