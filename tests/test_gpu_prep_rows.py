@@ -1,11 +1,12 @@
 """The prepare step with options that need a whole row (FNN_FLAG_NORMALIZE, FNN_FLAG_L2, FNN_FLAG_SPLIT).  Many rows are
 staged through LDS in runs of 256, copied whole where the map is 16-byte aligned and its rows lie close
-together, element by element otherwise; few rows are prepared element by element or one per thread.  How the caller stores a map must not change a single bit of the
-result: contiguous, strided and misaligned storage of the same values are compared, at the edges of a run
-and -- fnn_mutual_dense, whose image 1 is stored in another order -- of a super-block of 4096 pixels; and
-the exactly representable values of L2 and SPLIT against the oracle.  Normalised rows are compared channel
-by channel with the oracle's, on Gaussian rows whose sums round at every step (the header's
-exception, the norms of aligned fp32 rows, is held to its bound).  Squared lengths likewise, against 64 bits."""
+together, element by element otherwise; few rows are prepared element by element or one per thread.  How
+the caller stores a map must not change a single bit of the result: contiguous, strided and misaligned
+storage of the same values are compared, at the edges of a run and -- fnn_mutual_dense, whose image 1 is
+stored in another order -- of a super-block of 4096 pixels; and the exactly representable values of L2 and
+SPLIT against the oracle.  Normalised rows are compared channel by channel with the oracle's, on Gaussian
+rows whose sums round at every step (the header's exception, the norms of aligned fp32 rows, is held to
+its bound).  Squared lengths likewise, against 64 bits."""
 import numpy as np
 import pytest
 import torch
