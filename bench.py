@@ -49,6 +49,23 @@ def searches_from_iters(seed_iter, n_seeds, max_iter):
     return counts
 
 
+TWO_STEPS = 1000  # added to the trace detail of a search that ran in two steps
+
+
+def join_search_steps(trace):
+    """A large search is two launches (8-bit scores, then the products of what they leave over): one row for both."""
+    rows = []
+    for name, ms, detail in trace:
+        if name == "coarse_kernel":
+            rows.append(("search_kernel", ms, TWO_STEPS + detail))
+        elif name == "refine_kernel":
+            first, first_ms, first_detail = rows[-1]
+            rows[-1] = (first, first_ms + ms, first_detail)
+        else:
+            rows.append((name, ms, detail))
+    return rows
+
+
 def csrc_fingerprint() -> str:
     """Hash of the kernel sources: ties a stored counter measurement to the code it was taken on."""
     import hashlib
@@ -142,6 +159,7 @@ def main() -> int:
         step()
     torch.cuda.synchronize()
     trace_details = fnn.fnn_trace_end(args.steps * 64, details=True)
+    trace_details = join_search_steps(trace_details)
     trace = [(name, ms) for name, ms, _ in trace_details]
     trace_details = [row for row in trace_details if row[0] == "search_kernel"]
     by_kernel = {}
@@ -168,7 +186,10 @@ def main() -> int:
     # fp32 maps with a 16-bit compute format: the first forward and the first backward search read the
     # caller's fp32 map (4 bytes per value) and write the prepared copy (esize bytes per value) instead
     # of reading a prepared map -- the cast that a separate prepare pass would have done
-    fused_first = compute != "f32" and any(d >= 100 for _, _, d in trace_details[:2 * int(round(launches_per_step))])
+    fused_first = compute != "f32" and any(100 <= d < TWO_STEPS for _, _, d in trace_details[:2 * int(round(launches_per_step))])
+    # a search in two steps also reads the candidates' 8-bit rows (32 bytes)
+    two_steps = [d >= TWO_STEPS for _, _, d in trace_details[:int(round(launches_per_step))]]
+    bytes_per_step += sum(two_steps) * BATCH * N_PIX * 32
     if fused_first:
         bytes_per_step += 2 * BATCH * N_PIX * D * 4
     flops_per_launch = flops_per_step / max(launches_per_step, 1)
@@ -191,6 +212,8 @@ def main() -> int:
         by = BATCH * N_PIX * D * esize + k_act * (D * esize + 8)
         if fused_first and i < 2:
             by += BATCH * N_PIX * D * 4   # fp32 map read and prepared copy written instead of a prepared map read
+        if two_steps[i]:
+            by += BATCH * N_PIX * 32
         t_mfma = fl / (peak * 1e12) * 1e6
         t_hbm = by / (PEAK_HBM * 1e9) * 1e6
         per_search_rows.append({
@@ -232,7 +255,8 @@ def main() -> int:
             "launches_per_step": launches_per_step, "avg_launch_ms": round(avg_search_ms, 5),
             "flops_per_launch": flops_per_launch,
             "note": "algorithmic flops = 2*24*M*(active queries), averaged over all search launches of a step "
-                    "(launches after every seed has converged do no work but count)",
+                    "(launches after every seed has converged do no work but count); the two launches of a search in "
+                    "two steps count as one, and their 8-bit products are not counted as flops",
         },
         "roofline_hbm": {
             "kernel": "search_kernel", "bound": "hbm", "achieved": round(achieved_gbs, 1), "peak": PEAK_HBM,

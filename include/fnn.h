@@ -44,8 +44,12 @@
  *    which fills that cache.
  *  - The maps are read by the enqueued work and never written: keep them alive and unchanged
  *    until the stream has passed the call.  The searches work on a prepared copy of each map in
- *    the workspace (cast to the compute format, rows padded to whole 32-pixel tiles).  Two cases
- *    need no separate copy pass, and results do not depend on which way a map took:
+ *    the workspace (cast to the compute format, rows padded to whole 32-pixel tiles).  Large searches
+ *    (from 2048 queries per pair, with FNN_F32 or FNN_FLAG_SPLIT from 256, against maps of at least 16384 pixels) score an
+ *    8-bit copy of the maps first and multiply in the compute format only where a bound on what the 8 bits left out says
+ *    that the best candidate may be: the same results, from a workspace of the size that fnn_workspace_bytes() returns;
+ *    one that has room for the prepared maps and the call's state only is accepted as well and searched in one
+ *    step.  Two cases need no separate copy pass, and results do not depend on which way a map took:
  *    (a) the caller's array already is what the copy would be -- stored in the compute format,
  *    d in {16, 24, 32} (16-bit formats) or a multiple of 8 (FNN_F32), row_stride == d, n a
  *    multiple of 32, 16-byte aligned, the batch's maps equally spaced in memory, no flags --

@@ -84,6 +84,72 @@ RecipLayout carve_recip(Carver& cv, int batch, int64_t n, int64_t m, int d, int6
     return L;
 }
 
+// Room for the two-step search behind the layouts above.  A caller's workspace that ends before it is searched in one step.
+struct CoarseLayout {
+    CoarseMap map[2];      // images 1 and 2 (fnn_nearest: the queries and the candidates)
+    uint16_t* upper;
+    uint32_t* lower;       // [searches][batch][slot_pitch]
+    int64_t lower_count;   // words of one search
+    int64_t slot_pitch;
+    int64_t slab;
+};
+CoarseMap carve_coarse_map(Carver& cv, int batch, int64_t pixels) {
+    CoarseMap M;
+    M.n_segs = (int32_t)((pixels + SEG_PIXELS - 1) / SEG_PIXELS);
+    const size_t rows = (size_t)batch * M.n_segs * SEG_PIXELS;
+    M.rows = (char*)cv.take(rows * COARSE_ROW_BYTES);
+    M.row_bound = (uint32_t*)cv.take(rows * sizeof(uint32_t));
+    M.seg = (SegInfo*)cv.take((size_t)batch * M.n_segs * sizeof(SegInfo));
+    return M;
+}
+// both_searched: image 1 is a map of candidates too
+CoarseLayout carve_coarse(Carver& cv, int batch, int64_t rows1, int64_t rows2, bool both_searched, int64_t nq, int searches) {
+    CoarseLayout L;
+    L.map[0] = carve_coarse_map(cv, batch, rows1);
+    L.map[1] = carve_coarse_map(cv, batch, rows2);
+    const int64_t segs = both_searched && L.map[0].n_segs > L.map[1].n_segs ? L.map[0].n_segs : L.map[1].n_segs;
+    int64_t cells = 0;
+    for (int i = both_searched ? 0 : 1; i < 2; ++i) {
+        const int64_t of_map = (int64_t)L.map[i].n_segs * coarse_cells(nq, L.map[i].n_segs, batch);
+        if (of_map > cells) cells = of_map;
+    }
+    L.slot_pitch = round_up(nq, 64);
+    L.slab = coarse_slab(nq, segs, batch);
+    L.lower_count = batch * L.slot_pitch;
+    L.lower = (uint32_t*)cv.take((size_t)searches * L.lower_count * sizeof(uint32_t));
+    L.upper = (uint16_t*)cv.take((size_t)batch * cells * L.slab * sizeof(uint16_t));
+    return L;
+}
+CoarseArgs coarse_args(const CoarseLayout& L, int src, int search) {
+    CoarseArgs ca;
+    memset(&ca, 0, sizeof(ca));
+    ca.src = L.map[src];
+    ca.tgt = L.map[src ^ 1];
+    ca.upper = L.upper;
+    ca.lower = L.lower + search * L.lower_count;
+    ca.slab = (int32_t)L.slab;
+    ca.slot_pitch = L.slot_pitch;
+    return ca;
+}
+// Queries of fnn_nearest that are few beside their map are taken out of it, in the order of their slots.
+bool list_queries(const int32_t* q_idx, int64_t nq, int64_t n) { return q_idx && nq <= n / 2; }
+constexpr int RECIP_COARSE_SEARCHES = 4;  // out and back, of the first two iterations
+
+// Searches of a call that run in two steps, if its workspace allows: none or the one of fnn_nearest, none, the first two or the
+// first four of the iteration.  About half the seeds live to see the second iteration; if few do, two launches are wasted.
+int nearest_coarse_searches(int batch, int64_t n, int64_t m, int64_t nq, bool listed, int compute, int dp, bool l2) {
+    if (nq < coarse_least_queries(compute, dp)) return 0;
+    const double gain = coarse_gain(nq, m, batch, compute, dp, l2) - coarse_cost(batch * (m + (listed ? nq : n)), compute, dp);
+    return gain > COARSE_LEAST_GAIN ? 1 : 0;
+}
+int recip_coarse_searches(int batch, int64_t n, int64_t m, int64_t n_seeds, int compute, int dp, bool l2) {
+    if (n_seeds < coarse_least_queries(compute, dp)) return 0;
+    const double first = coarse_gain(n_seeds, m, batch, compute, dp, l2) + coarse_gain(n_seeds, n, batch, compute, dp, l2);
+    const double second = coarse_gain(n_seeds / 2, m, batch, compute, dp, l2) + coarse_gain(n_seeds / 2, n, batch, compute, dp, l2);
+    const double gain = first + (second > 0.0 ? second : 0.0) - coarse_cost(batch * (n + m), compute, dp);
+    return gain <= COARSE_LEAST_GAIN ? 0 : (second > 2.0 * COARSE_LEAST_GAIN ? RECIP_COARSE_SEARCHES : 2);
+}
+
 struct DenseLayout {
     MapsLayout maps;
     u64* row_keys;
@@ -255,6 +321,20 @@ hipError_t prep_both(int32_t batch, const fnn_map* a, const fnn_map* b, const Ma
     return launch_prep(pa, s);
 }
 
+// One side of the quantise launch; raw: the caller's fp32 maps are read, else the prepared ones at `prepared`.
+void fill_quantise_side(QuantiseSide& sd, int32_t batch, const fnn_map* maps, bool raw, const char* prepared, int64_t bstride, int64_t n_pad,
+                        int second_image, const CoarseMap& out) {
+    sd.prepared = prepared;
+    sd.bstride = bstride;
+    sd.n = maps[0].n;
+    sd.n_pad = n_pad;
+    if (raw)
+        for (int b = 0; b < batch; ++b) sd.raw[b] = (const float*)maps[b].data;
+    sd.raw_stride = maps[0].row_stride;
+    sd.second_image = second_image;
+    sd.out = out;
+}
+
 #define FNN_TRY(expr)                        \
     do {                                     \
         if ((expr) != hipSuccess) return FNN_E_HIP; \
@@ -314,14 +394,25 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
     if (de < 0) return 0;
     const int32_t compute = opts->compute;
     size_t most = 0;
+    const int dp = padded_d(de, compute);
+    const bool l2 = (opts->flags & FNN_FLAG_L2) != 0;
     {
         Carver cv{nullptr, 0};
         carve_nearest(cv, batch, n, m, de, n_queries, compute);
         most = cv.used;
+        // the queries' own rows, or their whole map, whichever the call may need
+        for (int listed = 0; listed < 2; ++listed) {
+            if (!nearest_coarse_searches(batch, n, m, n_queries, listed != 0, compute, dp, l2)) continue;
+            Carver with = cv;
+            carve_coarse(with, batch, listed ? n_queries : n, m, false, n_queries, 1);
+            if (with.used > most) most = with.used;
+        }
     }
     {
         Carver cv{nullptr, 0};
         carve_recip(cv, batch, n, m, de, n_queries, compute);
+        if (recip_coarse_searches(batch, n, m, n_queries, compute, dp, l2))
+            carve_coarse(cv, batch, n, m, true, n_queries, RECIP_COARSE_SEARCHES);
         if (cv.used > most) most = cv.used;
     }
     {
@@ -380,7 +471,14 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
     const bool staged_shape = !nq_active && first_search_applies(nq, m, batch);
     const bool fused = staged_shape && raw_options(opts) && raw_rows(batch, src) && raw_rows(batch, tgt);
     const bool staged = fused || (staged_shape && L.maps.dp == 24 && opts->compute != FNN_F32);
-    FNN_TRY(prep_both(batch, src, tgt, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
+    // ... or, where that is faster and the workspace has the room, in two steps, the first in 8 bits
+    const bool listed = list_queries(q_idx, nq, n);
+    CoarseLayout C = carve_coarse(cv, batch, listed ? nq : n, m, false, nq, 1);
+    const bool coarse = !nq_active && cv.used <= workspace_bytes &&
+                        nearest_coarse_searches(batch, n, m, nq, listed, opts->compute, L.maps.dp, (opts->flags & FNN_FLAG_L2) != 0);
+    const bool raw = coarse && raw_options(opts) && raw_rows(batch, src) && raw_rows(batch, tgt);
+    const bool prepared = raw || (coarse && direct1 && direct2);  // the quantise launch is the first, and takes the side jobs
+    if (!prepared) FNN_TRY(prep_both(batch, src, tgt, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
     SearchArgs sa;
     memset(&sa, 0, sizeof(sa));
     sa.src = p1;
@@ -394,7 +492,32 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
     sa.m = (int32_t)m;
     sa.m_tiles = (int32_t)(L.maps.m_pad / 32);
     sa.out_keys = L.keys;
-    if (staged) {
+    if (coarse) {
+        QuantiseArgs qa;
+        memset(&qa, 0, sizeof(qa));
+        if (prepared) qa.extra = extra;
+        fill_quantise_side(qa.side[0], batch, src, raw, p1, bs1, L.maps.n_pad, 0, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, tgt, raw, p2, bs2, L.maps.m_pad, 1, C.map[1]);
+        if (listed) {
+            qa.side[0].gather = q_idx;
+            qa.side[0].gather_rows = n;
+            qa.side[0].n = nq;
+            if (raw) {  // the prepared copy of image 1 holds the listed rows only
+                qa.side[0].n_pad = nq;
+                sa.q_idx = nullptr;
+                sa.src_rows = (int32_t)nq;
+            }
+        }
+        qa.batch = batch;
+        qa.raw_rows = raw ? 1 : 0;
+        qa.lower = C.lower;
+        qa.lower_count = C.lower_count;
+        qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
+        FNN_TRY(launch_quantise(qa, opts->compute, L.maps.dp, s));
+        CoarseArgs ca = coarse_args(C, 0, 0);
+        ca.src_listed = listed ? 1 : 0;
+        FNN_TRY(launch_coarse_search(sa, ca, batch, opts->compute, L.maps.dp, s));
+    } else if (staged) {
         FirstSearchArgs first;
         memset(&first, 0, sizeof(first));
         first.s = sa;
@@ -546,7 +669,27 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     // the same LDS-staged kernel serves the first two searches on prepared 24-channel maps
     const bool staged = fused || (L.maps.dp == 24 && opts->compute != FNN_F32 && first_search_applies(n_seeds, n, batch) &&
                                   first_search_applies(n_seeds, m, batch));
-    FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
+    // ... and large ones run in two steps, the first in 8 bits, where the workspace has the room
+    CoarseLayout C = carve_coarse(cv, batch, n, m, true, n_seeds, RECIP_COARSE_SEARCHES);
+    const int coarse_searches = walk || cv.used > workspace_bytes ? 0 : recip_coarse_searches(batch, n, m, n_seeds, compute, L.maps.dp,
+                                                                                              (opts->flags & FNN_FLAG_L2) != 0);
+    const bool coarse = coarse_searches > 0;
+    const bool raw = coarse && raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
+    const bool prepared = raw || (coarse && direct1 && direct2);  // the quantise launch is the first, and takes the side jobs
+    if (!prepared) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
+    if (coarse) {
+        QuantiseArgs qa;
+        memset(&qa, 0, sizeof(qa));
+        if (prepared) qa.extra = extra;
+        fill_quantise_side(qa.side[0], batch, d1, raw, p1, bs1, L.maps.n_pad, 0, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, raw, p2, bs2, L.maps.m_pad, 1, C.map[1]);
+        qa.batch = batch;
+        qa.raw_rows = raw ? 1 : 0;
+        qa.lower = C.lower;
+        qa.lower_count = RECIP_COARSE_SEARCHES * C.lower_count;
+        qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
+        FNN_TRY(launch_quantise(qa, compute, L.maps.dp, s));
+    }
 
     if (walk) {
         WalkArgs wa;
@@ -616,7 +759,15 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         step.next_active = L.st.n_active[w ^ 1];  // emptied by the resolve pass of the search forward
     };
     take_state(0);
-    if (fused) {
+    // search number k of the call (out 0, back 0, out 1, ...): the first few may run in two steps
+    auto search = [&](const SearchArgs& a, int k) -> hipError_t {
+        if (k >= coarse_searches) return launch_search(a, batch, compute, L.maps.dp, s);
+        CoarseArgs ca = coarse_args(C, k & 1, k);
+        ca.min_live = k < 2 ? 0 : coarse_min_live(compute, L.maps.dp);
+        return launch_coarse_search(a, ca, batch, compute, L.maps.dp, s);
+    };
+    const bool fuse_first = fused && !coarse, stage_first = staged && !coarse;
+    if (fuse_first) {
         FirstSearchArgs first;  // V^0 = NN_2(U^0): queries and candidates still raw; writes the prepared image 2
         first.s = fwd;
         first.s.src_rows = (int32_t)n;  // query rows are clamped to the caller's map, which has no padding rows
@@ -625,14 +776,14 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         first.raw_queries = 1;
         FNN_TRY(launch_search_first(first, batch, compute, s));
         FNN_TRY(launch_resolve_raw(first, batch, compute, nullptr, nullptr, step.next_active, s));
-    } else if (staged) {
+    } else if (stage_first) {
         FirstSearchArgs first;
         memset(&first, 0, sizeof(first));
         first.s = fwd;
         FNN_TRY(launch_search_first(first, batch, compute, s));
         FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, step.next_active, s));
     } else {
-        FNN_TRY(launch_search(fwd, batch, compute, L.maps.dp, s));  // V^0 = NN_2(U^0)
+        FNN_TRY(search(fwd, 0));  // V^0 = NN_2(U^0)
         FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, step.next_active, s));
     }
     if (opts->max_iter == 0) {
@@ -641,21 +792,21 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     }
     for (int t = 0; t < opts->max_iter; ++t) {
         const bool last = (t == opts->max_iter - 1);
-        if (staged && t == 0) {
+        if (stage_first && t == 0) {
             FirstSearchArgs first;  // U^1 = NN_1(V^0): queries from the prepared image 2; if raw, writes the prepared image 1
             memset(&first, 0, sizeof(first));
             first.s = bwd;
-            if (fused) fill_raw(first.raw_tgt, batch, d1);
+            if (fuse_first) fill_raw(first.raw_tgt, batch, d1);
             FNN_TRY(launch_search_first(first, batch, compute, s));
         } else {
-            FNN_TRY(launch_search(bwd, batch, compute, L.maps.dp, s));  // U^{t+1} = NN_1(V^t)
+            FNN_TRY(search(bwd, 2 * t + 1));  // U^{t+1} = NN_1(V^t)
         }
         step.t = t;
         step.mode = last ? 1 : 0;
         FNN_TRY(launch_resolve_step(bwd, step, batch, compute, L.maps.dp, s));
         if (last) break;
         take_state(which ^ 1);
-        FNN_TRY(launch_search(fwd, batch, compute, L.maps.dp, s));  // V^{t+1} = NN_2(U^{t+1})
+        FNN_TRY(search(fwd, 2 * t + 2));  // V^{t+1} = NN_2(U^{t+1})
         FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, step.next_active, s));
     }
     FNN_TRY(launch_recip_dedup(L.st, ns, batch, seed_i, seed_j, seed_iter, pairs, n_pairs, s));

@@ -1,0 +1,669 @@
+// Pass 1 of a large search in two steps whose keys are, bit for bit, those of search_kernel.
+//
+// Step 1 (coarse_kernel) scores every query against every candidate in 8-bit integers: one K=32 instruction per
+// 32x32 block, at the rate of a K=16 fp16 one, and eight 3-input maxima, with nothing tracked per
+// tile (25-26 ns per block and SIMD in a bare loop; search_kernel's arithmetic for 24 channels 42-47 ns).  It keeps one
+// number per query and CELL of 512 or 1024 candidates, an upper bound of the cell's scores, and one per query, a
+// lower bound of its best score.  Step 2 (refine_kernel) multiplies each cell again, in the format the call asked
+// for and with the same instructions as search_kernel, but only for the queries whose upper bound there reaches
+// their lower bound; every other cell holds no candidate that could win or tie.  Of the 192 segments of a 512x384 map
+// a query needs 4 on average (unit rows, no structure; 2 where neighbouring pixels resemble each other).
+//
+// The bounds.  With a row a = s q + r, q its 8-bit row, s its segment's scale, r the remainder, a product is
+//     a.b = s_a s_b (q_a.q_b) + (s_a q_a).r_b + r_a.b,     |second| + |third| <= |a| |r_b| + |r_a| (|b| + |r_b|),
+// the integer sum is exact, and |a|, |r_a| are taken from the row, |r_b| and |b| from the segment's worst row.
+// What the matrix instructions round when they sum up to 96 products in fp32, and what is rounded here, is
+// below 4e-5 |a| |b| (ROUNDING, counted on both sides).  Rows whose squares leave fp32's range, or that are not finite, take
+// no part in the 8-bit scores: their bounds are so wide that they are always refined.
+#include <type_traits>
+
+#include "fnn_device.hpp"
+#include "fnn_kernels.hpp"
+#include "query_rows.hpp"
+#include "side_jobs.hpp"
+#include "trace.hpp"
+
+namespace fnn {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+
+// ---- the 8-bit maps ------------------------------------------------------------------------------
+constexpr float ROUNDING = 2e-5f;          // of a row's length, on top of its remainder
+constexpr float UNBOUNDED = 1e18f;         // the "bound" of a row that has none; its square is still a number
+constexpr float LEAST_SQUARE = 1e-30f;     // |x|^2 of a row that the bounds hold for
+constexpr float LARGEST_SQUARE = 1e30f;
+// fp16 values below 2^-14 may count as 0 in the matrix instructions.  Where a step of the scale is wider than twice
+// that they are 0 in the 8-bit row too; elsewhere their length (at most sqrt(96) * 2^-14) joins the remainder.
+constexpr float F16_SMALL = 6.2e-5f;
+constexpr float F16_SMALL_LENGTH = 6.1e-4f;
+
+__device__ __forceinline__ uint32_t bf16_up(float x) { return (__float_as_uint(x) + 0xFFFFu) >> 16; }  // x >= 0
+
+// The channels of a prepared row as fp32 numbers.  SPLIT: the descriptor hi + lo of a two-term row; its score leaves out
+// the products lo * lo, at most 2^-22 of |a| |b|.
+template <int CT, int DP, bool SPLIT>
+struct PreparedRow {
+    static constexpr int CHANNELS = SPLIT ? FNN_MAX_D : DP;
+    static __device__ __forceinline__ void load(const char* row, int d, int lo_copy, float (&x)[CHANNELS]) {
+        if constexpr (SPLIT) {
+            if (d % 8 == 0) {  // uniform
+#pragma unroll
+                for (int g = 0; g < CHANNELS / 8; ++g) {
+                    const bool in = 8 * g < d;
+                    f16x8 hi = {0, 0, 0, 0, 0, 0, 0, 0}, lo = hi;
+                    if (in) {
+                        hi = *reinterpret_cast<const f16x8*>(row + 16 * g);
+                        lo = *reinterpret_cast<const f16x8*>(row + 2 * lo_copy * d + 16 * g);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[8 * g + e] = (float)hi[e] + (float)lo[e];
+                }
+            } else {
+                const _Float16* e = reinterpret_cast<const _Float16*>(row);
+#pragma unroll
+                for (int k = 0; k < CHANNELS; ++k) x[k] = k < d ? (float)e[k] + (float)e[lo_copy * d + k] : 0.0f;
+            }
+        } else if constexpr (CT == CT_F32) {
+#pragma unroll
+            for (int q = 0; q < DP / 4; ++q) {
+                const float4 v = reinterpret_cast<const float4*>(row)[q];
+                x[4 * q] = v.x;
+                x[4 * q + 1] = v.y;
+                x[4 * q + 2] = v.z;
+                x[4 * q + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < DP / 8; ++q) {
+                const uint4 v = reinterpret_cast<const uint4*>(row)[q];
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t bits = (w[e / 2] >> (16 * (e & 1))) & 0xFFFFu;
+                    x[8 * q + e] = CT == CT_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits) : __uint_as_float(bits << 16);
+                }
+            }
+        }
+    }
+};
+
+// The largest of a value over a workgroup (every thread gets it); `word` is LDS that nothing else uses.
+__device__ __forceinline__ float workgroup_max(float x, float* word) {  // x >= 0: its bits order like the value
+    x = half_max(x);
+    x = __builtin_fmaxf(x, __shfl_xor(x, 32));
+    if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<uint32_t*>(word), __float_as_uint(x));
+    __syncthreads();
+    return *word;
+}
+
+// One workgroup turns one segment of prepared rows into 8-bit rows, a thread QUANTISE_ROWS of them, held in registers between
+// the segment's largest value and the rounding.  RAW: the rows are the caller's fp32 rows of 24 channels; they are
+// rounded to the compute format here and the prepared map is written too.  Bound by memory.
+constexpr int QUANTISE_THREADS = 512;
+constexpr int QUANTISE_ROWS = SEG_PIXELS / QUANTISE_THREADS;
+template <int CT, int DP, bool SPLIT, bool RAW>
+__global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs a) {
+    using Row = PreparedRow<CT, DP, SPLIT>;
+    constexpr int K = Row::CHANNELS;
+    __shared__ float top[4];  // largest value, remainder, length, and whether a row has no bound
+    side_jobs(a.extra, a.batch);
+    {
+        const int64_t tid = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * QUANTISE_THREADS + threadIdx.x;
+        const int64_t n_threads = (int64_t)gridDim.x * gridDim.y * QUANTISE_THREADS;
+        for (int64_t i = tid; i < a.lower_count; i += n_threads) a.lower[i] = 0;
+    }
+    const QuantiseSide& sd = a.side[blockIdx.y / a.batch];
+    const int b = blockIdx.y % a.batch, seg = blockIdx.x;
+    if (seg >= sd.out.n_segs) return;  // uniform: the two maps may differ in size
+    if (threadIdx.x < 4) top[threadIdx.x] = 0.0f;
+    __syncthreads();
+
+    const char* prepared = sd.prepared + (int64_t)b * sd.bstride;
+    float x[QUANTISE_ROWS][K];
+    float square[QUANTISE_ROWS], largest = 0.0f;
+    bool bounded[QUANTISE_ROWS];
+#pragma unroll
+    for (int i = 0; i < QUANTISE_ROWS; ++i) {
+        const int64_t pixel = (int64_t)seg * SEG_PIXELS + i * QUANTISE_THREADS + threadIdx.x;
+        int64_t row = min(pixel, sd.n - 1);  // rows past the map repeat its last one, whose scores are real
+        if (sd.gather) row = min(max((int64_t)sd.gather[(int64_t)b * sd.n + row], (int64_t)0), sd.gather_rows - 1);
+        if constexpr (RAW) {
+            using O = Ops<CT, 24>;
+            const float4* p = reinterpret_cast<const float4*>(sd.raw[b] + row * sd.raw_stride);
+            uint32_t w[12];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const float4 v = p[q];
+                w[2 * q] = round_pair<CT>(v.x, v.y);
+                w[2 * q + 1] = round_pair<CT>(v.z, v.w);
+            }
+            if (pixel < sd.n_pad) {
+                uint4* out = reinterpret_cast<uint4*>(const_cast<char*>(prepared) + pixel * O::ROW_BYTES);
+                const bool real = pixel < sd.n;  // padding rows of the prepared map are zero
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    out[q] = real ? make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]) : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int k = 0; k < 24; ++k) {
+                const uint32_t bits = (w[k / 2] >> (16 * (k & 1))) & 0xFFFFu;
+                x[i][k] = CT == CT_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits) : __uint_as_float(bits << 16);
+            }
+        } else {
+            constexpr int ROW_BYTES = DP * (CT == CT_F32 ? 4 : 2);
+            Row::load(prepared + row * ROW_BYTES, a.split_d, sd.second_image ? 1 : 2, x[i]);
+        }
+        float most = 0.0f, sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            most = __builtin_fmaxf(most, __builtin_fabsf(x[i][k]));
+            sum = __builtin_fmaf(x[i][k], x[i][k], sum);
+        }
+        square[i] = sum;
+        // compared as integers, which puts a sum that is not a number past the largest
+        const uint32_t bits = __float_as_uint(sum) & 0x7FFFFFFFu;
+        bounded[i] = (bits == 0 && __float_as_uint(most) == 0) ||
+                     (bits >= __float_as_uint(LEAST_SQUARE) && bits <= __float_as_uint(LARGEST_SQUARE));
+        if (bounded[i]) largest = __builtin_fmaxf(largest, most);
+    }
+    largest = workgroup_max(largest, &top[0]);
+    const float scale = largest * (1.0f / 127.0f);
+    const float inverse = largest > 0.0f ? 127.0f / largest : 0.0f;
+    const float small = CT == CT_F16 && scale < 2.0f * F16_SMALL ? F16_SMALL_LENGTH : 0.0f;
+
+    float residual = 0.0f, length = 0.0f, unbounded = 0.0f;
+    const int64_t first = ((int64_t)b * sd.out.n_segs + seg) * SEG_PIXELS;
+#pragma unroll
+    for (int i = 0; i < QUANTISE_ROWS; ++i) {
+        const int64_t out_row = first + i * QUANTISE_THREADS + threadIdx.x;
+        // x / scale is rounded to the nearest integer by adding 1.5 * 2^23, which leaves it in the low bits; an unbounded row's
+        // integers mean nothing
+        constexpr float INTEGER = 12582912.0f;
+        uint32_t words[COARSE_ROW_BYTES / 4];
+        float left = 0.0f;
+#pragma unroll
+        for (int w = 0; w < COARSE_ROW_BYTES / 4; ++w) {
+            uint32_t q[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = 4 * w + e;
+                if (k < K) {
+                    const float v = x[i][k < K ? k : 0];
+                    const float t = __builtin_fmaf(v, inverse, INTEGER);
+                    const float r = __builtin_fmaf(-scale, t - INTEGER, v);
+                    left = __builtin_fmaf(r, r, left);
+                    q[e] = __float_as_uint(t);
+                }
+            }
+            const uint32_t low = __builtin_amdgcn_perm(q[1], q[0], 0x0C0C0400u);  // bytes (0 0 q1 q0)
+            words[w] = __builtin_amdgcn_perm(q[3], __builtin_amdgcn_perm(q[2], low, 0x0C040100u), 0x04020100u);
+        }
+        const float len = __builtin_sqrtf(square[i]) * (1.0f + 1e-5f);
+        const float rest = __builtin_sqrtf(left) * (1.0f + 1e-5f) + ROUNDING * len + small;
+        uint32_t bound = bf16_up(UNBOUNDED) | (bf16_up(UNBOUNDED) << 16);
+        if (bounded[i]) {
+            residual = __builtin_fmaxf(residual, rest);
+            length = __builtin_fmaxf(length, len);
+            const float per_scale = scale > 0.0f ? 1.0f / scale : 0.0f;  // a segment of zero rows: every score is 0
+            bound = bf16_up(rest * per_scale * (1.0f + 1e-6f)) | (bf16_up(len * per_scale * (1.0f + 1e-6f)) << 16);
+        } else {
+            unbounded = 1.0f;
+        }
+        uint4* out = reinterpret_cast<uint4*>(sd.out.rows + out_row * COARSE_ROW_BYTES);
+        out[0] = make_uint4(words[0], words[1], words[2], words[3]);
+        out[1] = make_uint4(words[4], words[5], words[6], words[7]);
+        sd.out.row_bound[out_row] = bound;
+    }
+    residual = workgroup_max(residual, &top[1]);
+    length = workgroup_max(length, &top[2]);
+    unbounded = workgroup_max(unbounded, &top[3]);
+    if (threadIdx.x == 0) {
+        SegInfo info = {scale, residual, length + residual, 0.0f};
+        if (unbounded > 0.0f) info = {scale, UNBOUNDED, UNBOUNDED, 0.0f};
+        sd.out.seg[(int64_t)b * sd.out.n_segs + seg] = info;
+    }
+}
+
+// Queries that are not listed are the rows of their map in order: those from slot `first` on are the rows of the map from
+// row `first` on.  Returns how far to move the map's start.
+__device__ __forceinline__ int64_t take_slots_from(SearchArgs& a, int first) {
+    if (a.q_idx || a.q_keys) return 0;
+    a.src_rows -= first;
+    return first;
+}
+
+// ---- step 1 ------------------------------------------------------------------------------------
+constexpr int COARSE_WAVES = 4;  // waves per workgroup
+constexpr int COARSE_TURN = 8;   // candidate tiles staged per turn, two per wave
+constexpr int TILE_BYTES = 32 * COARSE_ROW_BYTES;
+
+#define FNN_LDS_PTR(p) ((void __attribute__((address_space(3)))*)(p))
+
+__device__ __forceinline__ int max3i(int a, int b, int c) { return max(max(a, b), c); }
+__device__ __forceinline__ int fold16i(int seed, const i32x16& x) {
+    const int t0 = max3i(x[0], x[1], x[2]);
+    const int t1 = max3i(x[3], x[4], x[5]);
+    const int t2 = max3i(x[6], x[7], x[8]);
+    const int t3 = max3i(x[9], x[10], x[11]);
+    const int t4 = max3i(x[12], x[13], x[14]);
+    return max3i(seed, max3i(t0, t1, t2), max3i(t3, t4, x[15]));
+}
+
+// The four waves of a workgroup hold PAIRS pairs of query blocks each and sweep the same tiles, which reach LDS by direct loads
+// (a tile is 1 KB: one 16-byte load per lane), the next turn's while this turn's are multiplied.
+// Bound by the vector maxima and the matrix instructions, which take about the same time each.
+template <int PAIRS, int CELL_TILES>
+__global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
+void coarse_kernel(SearchArgs a, CoarseArgs ca) {
+    constexpr int TURNS = CELL_TILES / COARSE_TURN, CELLS = SEG_TILES / CELL_TILES;
+    static_assert(TURNS % 2 == 0, "a cell is an even number of turns, so it starts on stage slot 0");
+    __shared__ uint4 stage0[COARSE_TURN][64], stage1[COARSE_TURN][64];  // two variables, see dense_staged_kernel
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // one XCD owns a contiguous run of (pair, unit) work, see search_kernel
+    const int n_wgs = gridDim.x * gridDim.y;
+    int wg = blockIdx.y * gridDim.x + blockIdx.x;
+    if ((n_wgs & 7) == 0) wg = (wg & 7) * (n_wgs >> 3) + (wg >> 3);
+    const int b = wg / gridDim.x;
+    const int wgi = wg % gridDim.x;
+    int n_act = a.nq;
+    if (a.nq_active) n_act = min(max(a.nq_active[b], 0), a.nq);
+    if (n_act < ca.min_live) return;
+    n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
+    if (n_act <= 0) return;
+
+    // pairs of query blocks are dealt evenly to the waves of all quads; those with one more sit at
+    // different places of their workgroups, that is on different SIMDs
+    const int n_cells = ca.tgt.n_segs * CELLS;
+    const int pairs = (n_act + 63) / 64;
+    const int quads = (pairs + PAIRS * COARSE_WAVES - 1) / (PAIRS * COARSE_WAVES);
+    const int chunks = min(max(1, (int)gridDim.x / quads), n_cells);
+    const int per_wave = pairs / (quads * COARSE_WAVES), more = pairs % (quads * COARSE_WAVES);
+
+    if (ca.src_listed) {
+        a.q_idx = nullptr;
+        a.src_rows = a.nq;
+    }
+    const int64_t shift = take_slots_from(a, ca.first_slot);
+    const char* src = ca.src.rows + ((int64_t)b * ca.src.n_segs * SEG_PIXELS + shift) * COARSE_ROW_BYTES;
+    const uint32_t* src_bound = ca.src.row_bound + (int64_t)b * ca.src.n_segs * SEG_PIXELS + shift;
+    const char* tgt = ca.tgt.rows + (int64_t)b * ca.tgt.n_segs * SEG_PIXELS * COARSE_ROW_BYTES;
+    const SegInfo* info = ca.tgt.seg + (int64_t)b * ca.tgt.n_segs;
+    const int64_t qbase = (int64_t)b * a.nq + ca.first_slot;
+
+    const int units = quads * chunks;
+    for (int unit = wgi; unit < units; unit += gridDim.x) {  // uniform in the workgroup
+        const int chunk = unit / quads, quad = unit % quads;
+        const int rank = ((wave + quad) & (COARSE_WAVES - 1)) * quads + quad;
+        const int slot0 = (rank * per_wave + min(rank, more)) * 64;
+        const int slot_end = min(n_act, slot0 + (per_wave + (rank < more ? 1 : 0)) * 64);
+        const int cell0 = (int)((int64_t)chunk * n_cells / chunks), cell1 = (int)((int64_t)(chunk + 1) * n_cells / chunks);
+        const char* first = tgt + (int64_t)cell0 * CELL_TILES * TILE_BYTES;
+        const int total = (cell1 - cell0) * TURNS;
+
+        auto stage_turn = [&](uint4 (&slot)[COARSE_TURN][64], int k) {
+            const char* from = first + (int64_t)min(k, total - 1) * (COARSE_TURN * TILE_BYTES) + c * COARSE_ROW_BYTES + h * 16;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                __builtin_amdgcn_global_load_lds((const void*)(from + (2 * wave + i) * TILE_BYTES), FNN_LDS_PTR(&slot[2 * wave + i][0]), 16, 0, 0);
+        };
+        stage_turn(stage0, 0);
+
+        i32x4 q[PAIRS][2];
+        int best[PAIRS][2];
+        float low[PAIRS];        // lane l of pair p: the slot slot0 + 64 p + l
+        uint32_t bound[PAIRS];
+        bool live[PAIRS];
+        {
+            int32_t row[2 * PAIRS];
+            query_rows<2 * PAIRS>(a, qbase, slot0, n_act, c, row);
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+                live[p] = slot0 + p * 64 < slot_end;  // uniform in the wave
+                const int32_t even = row[2 * p], odd = row[2 * p + 1];
+                q[p][0] = *reinterpret_cast<const i32x4*>(src + (int64_t)even * COARSE_ROW_BYTES + 16 * h);
+                q[p][1] = *reinterpret_cast<const i32x4*>(src + (int64_t)odd * COARSE_ROW_BYTES + 16 * h);
+                bound[p] = src_bound[h ? odd : even];
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            arrived(q[p][0]);
+            arrived(q[p][1]);
+            arrived(bound[p]);
+            best[p][0] = best[p][1] = -0x7FFFFFFF;
+            low[p] = -__builtin_inff();
+        }
+
+        auto turn = [&](int k, auto slot_tag) {
+            constexpr int SLOT = decltype(slot_tag)::value;
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the turn is in LDS
+            __syncthreads();                     // everyone's is, and everyone has left the other slot
+            stage_turn(SLOT ? stage0 : stage1, k + 1);
+#pragma unroll
+            for (int j = 0; j < COARSE_TURN; ++j) {
+                const i32x4 cur = __builtin_bit_cast(i32x4, SLOT ? stage1[j][lane] : stage0[j][lane]);
+#pragma unroll
+                for (int p = 0; p < PAIRS; ++p) {
+                    if (__builtin_expect(live[p], 1)) {
+                        const i32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                        const i32x16 even = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur, q[p][0], zero, 0, 0, 0);
+                        const i32x16 odd = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur, q[p][1], zero, 0, 0, 0);
+                        best[p][0] = fold16i(best[p][0], even);
+                        best[p][1] = fold16i(best[p][1], odd);
+                    }
+                }
+            }
+        };
+        for (int cell = cell0; cell < cell1; ++cell) {
+            const int k = (cell - cell0) * TURNS;
+#pragma unroll 1
+            for (int tt = 0; tt < TURNS; tt += 2) {
+                turn(k + tt, std::integral_constant<int, 0>{});
+                turn(k + tt + 1, std::integral_constant<int, 1>{});
+            }
+            // lanes 0..31 finish the first block of a pair, lanes 32..63 the second
+            const SegInfo si = info[cell / CELLS];
+            uint16_t* upper = ca.upper + ((int64_t)b * n_cells + cell) * ca.slab + slot0 + lane;
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+                if (live[p]) {
+                    const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)best[p][0], (uint32_t)best[p][1], false, false);
+                    const float score = (float)max((int)sw[0], (int)sw[1]) * si.scale;
+                    const float error = __builtin_fmaf(__uint_as_float(bound[p] & 0xFFFF0000u), si.residual,
+                                                       __uint_as_float(bound[p] << 16) * si.length);
+                    low[p] = __builtin_fmaxf(low[p], score - error);
+                    float up = score + error;
+                    up = __builtin_fmaf(__builtin_fabsf(up), 1.0f / 126.0f, up);  // so that cutting it to bf16 leaves a bound
+                    if (slot0 + p * 64 + lane < slot_end) upper[p * 64] = (uint16_t)(__float_as_uint(up) >> 16);
+                    best[p][0] = best[p][1] = -0x7FFFFFFF;
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const int slot = slot0 + p * 64 + lane;
+            if (slot < slot_end) atomicMax(&ca.lower[(int64_t)b * ca.slot_pitch + ca.first_slot + slot], order_bits(low[p]));
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // the turn past the last one has landed too
+        __syncthreads();                     // before the next unit's first turn takes its place
+    }
+}
+
+// ---- step 2 ------------------------------------------------------------------------------------
+// A workgroup owns one segment and a range of the queries: the segment's tiles stay in registers, RT per wave, and the
+// queries that need it are collected in LDS and streamed past them, 32 at a time.
+template <int CT, int DP>
+constexpr int refine_tiles() { return Ops<CT, DP>::ROW_BYTES / 8 <= 8 ? 8 : 4; }  // a tile is ROW_BYTES / 8 registers
+template <int CT, int DP>
+constexpr int refine_waves() { return Ops<CT, DP>::ROW_BYTES <= 48 ? 4 : (Ops<CT, DP>::ROW_BYTES < 160 ? 3 : 2); }  // per SIMD
+constexpr int REFINE_SCAN = 4096;             // queries looked at between two looks at the list's length
+constexpr int REFINE_LIST = REFINE_SCAN + 1024;
+constexpr int REFINE_PART = 512;               // a multiple of 32
+constexpr int REFINE_RANGE = 4 * REFINE_SCAN;  // queries of a workgroup
+
+template <int CT, int DP, int RT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(refine_waves<CT, DP>())))
+void refine_kernel(SearchArgs a, CoarseArgs ca) {
+    using O = Ops<CT, DP>;
+    using Frag = typename O::Frag;
+    constexpr int THREADS = 64 * WAVES, PER = REFINE_SCAN / THREADS;
+    __shared__ int list_row[REFINE_LIST];        // queries that need this segment: their rows,
+    __shared__ uint16_t list_slot[REFINE_LIST];  // and their slots in the workgroup's range
+    __shared__ u64 keys[REFINE_PART];            // what the waves found for REFINE_PART of them
+    __shared__ int n_list;
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cell = blockIdx.x, b = blockIdx.z;
+    int n_act = a.nq;
+    if (a.nq_active) n_act = min(max(a.nq_active[b], 0), a.nq);
+    const bool every = n_act < ca.min_live;       // step 1 left these queries to this kernel
+    n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
+    const int begin = blockIdx.y * REFINE_RANGE;
+    n_act = min(n_act, begin + REFINE_RANGE);
+    const int tile0 = (cell * WAVES + wave) * RT;
+    if (n_act <= begin) return;
+
+    const char* tgt = a.tgt + (int64_t)b * a.tgt_bstride;
+    const char* src = a.src + (int64_t)b * a.src_bstride + take_slots_from(a, ca.first_slot) * O::ROW_BYTES;
+    const int64_t qbase = (int64_t)b * a.nq + ca.first_slot;
+    const float ninf = -__builtin_inff();
+    const uint16_t* upper = ca.upper + ((int64_t)b * gridDim.x + cell) * ca.slab;
+    const uint32_t* lower = ca.lower + (int64_t)b * ca.slot_pitch + ca.first_slot;
+    Frag cand[RT];
+#pragma unroll
+    for (int j = 0; j < RT; ++j) cand[j] = O::load_tile(tgt + (int64_t)min(tile0 + j, a.m_tiles - 1) * (32 * O::ROW_BYTES), c, h);
+    const bool tail = (tile0 + RT) * 32 > a.m;  // uniform: some of this wave's candidates lie past the map
+
+    if (threadIdx.x == 0) n_list = 0;
+    for (int i = threadIdx.x; i < REFINE_PART; i += THREADS) keys[i] = 0;
+    __syncthreads();
+    for (int base = begin; base < n_act; base += REFINE_SCAN) {  // uniform
+        const int slot = base + (int)threadIdx.x * PER;
+        uint32_t need = 0;
+        if (slot < n_act) {
+            if (every) {
+                need = (1u << PER) - 1;
+            } else {
+                // the tables' rows hold whole 64s of slots: all PER are there
+                uint4 u[PER / 8], l[PER / 4];
+#pragma unroll
+                for (int i = 0; i < PER / 8; ++i) u[i] = reinterpret_cast<const uint4*>(upper + slot)[i];
+#pragma unroll
+                for (int i = 0; i < PER / 4; ++i) l[i] = reinterpret_cast<const uint4*>(lower + slot)[i];
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    const uint4 u8 = u[i / 8], l4 = l[i / 4];
+                    const uint32_t uw = (i & 7) < 2 ? u8.x : ((i & 7) < 4 ? u8.y : ((i & 7) < 6 ? u8.z : u8.w));
+                    const uint32_t lw = (i & 3) == 0 ? l4.x : ((i & 3) == 1 ? l4.y : ((i & 3) == 2 ? l4.z : l4.w));
+                    const float up = __uint_as_float(i & 1 ? uw & 0xFFFF0000u : uw << 16);
+                    if (up >= unorder_bits(lw)) need |= 1u << i;
+                }
+            }
+            if (n_act - slot < PER) need &= (1u << (n_act - slot)) - 1;
+        }
+        // a prefix sum over the wave, one LDS atomic for its total
+        const int mine = __popc(need);
+        int upto = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(upto, d);
+            if (lane >= d) upto += y;
+        }
+        const int count = __shfl(upto, 63);
+        int at = 0;
+        if (lane == 0 && count) at = atomicAdd(&n_list, count);
+        at = __shfl(at, 0) + upto - mine;
+        for (; need; need &= need - 1, ++at) {
+            const int found = slot + __builtin_ctz(need);
+            list_slot[at] = (uint16_t)(found - begin);
+            list_row[at] = (int)query_row(a, qbase, found);
+        }
+        __syncthreads();
+        const int n = n_list;
+        __syncthreads();  // read by every wave before the next round adds to it
+        if (n > REFINE_LIST - REFINE_SCAN || base + REFINE_SCAN >= n_act) {  // uniform
+            auto sweep = [&](int part, int part_end, auto tail_tag) {
+                constexpr bool TAIL = decltype(tail_tag)::value;
+                Frag next = O::load(src + (int64_t)list_row[min(part + c, n - 1)] * O::ROW_BYTES, h);
+#pragma unroll 1
+                for (int first = part; first < part_end; first += 32) {
+                    const Frag q = next;
+                    next = O::load(src + (int64_t)list_row[min(first + 32 + c, n - 1)] * O::ROW_BYTES, h);
+                    float best = ninf;
+                    int best_tile = 0x7FFFFFFF;
+                    int bound = a.m - tile0 * 32 - 4 * h;
+                    if (TAIL) asm volatile("" : "+v"(bound));  // else its comparisons are kept from block to block
+#pragma unroll
+                    for (int j = 0; j < RT; ++j) {
+                        f32x16 acc = O::mma(cand[j], q);
+                        if (TAIL) {
+#pragma unroll
+                            for (int v = 0; v < 16; ++v)
+                                if (32 * j + tile_row(v, 0) >= bound) acc[v] = ninf;
+                        }
+                        const float top = fold16(best, acc);
+                        if (top > best) best_tile = tile0 + j;
+                        best = top;
+                        // more than two products in flight cost registers, that is resident waves
+                        if (j & 1) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    const float ob = __shfl_xor(best, 32);
+                    const int ot = __shfl_xor(best_tile, 32);
+                    if (ob > best || (ob == best && ot < best_tile)) {
+                        best = ob;
+                        best_tile = ot;
+                    }
+                    if (h == 0 && first + c < n) atomicMax(&keys[first - part + c], pack_key(best, best_tile));
+                }
+            };
+            for (int part = 0; part < n; part += REFINE_PART) {  // uniform
+                const int part_end = min(n, part + REFINE_PART);
+                if (tail) sweep(part, part_end, std::true_type{});  // uniform in the wave, and there is no barrier inside
+                else sweep(part, part_end, std::false_type{});
+                __syncthreads();
+                for (int i = threadIdx.x; i < part_end - part; i += THREADS) {
+                    atomicMax(&a.out_keys[qbase + begin + list_slot[part + i]], keys[i]);
+                    keys[i] = 0;
+                }
+                __syncthreads();
+            }
+            if (threadIdx.x == 0) n_list = 0;
+            __syncthreads();
+        }
+    }
+}
+
+// ---- launches --------------------------------------------------------------------------------------
+template <int CT, int DP, bool SPLIT, bool RAW>
+static hipError_t launch_quantise_t(const QuantiseArgs& a, hipStream_t s) {
+    const int segs = a.side[0].out.n_segs > a.side[1].out.n_segs ? a.side[0].out.n_segs : a.side[1].out.n_segs;
+    return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW>, dim3(segs, 2 * a.batch), dim3(QUANTISE_THREADS), 0, s, a);
+}
+hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream_t s) {
+    if (a.raw_rows) {
+        if (compute == FNN_F16) return launch_quantise_t<CT_F16, 24, false, true>(a, s);
+        return launch_quantise_t<CT_BF16, 24, false, true>(a, s);
+    }
+    if (a.split_d) {
+        if (dp == 48) return launch_quantise_t<CT_F16, 48, true, false>(a, s);
+        if (dp == 64) return launch_quantise_t<CT_F16, 64, true, false>(a, s);
+        if (dp == 80) return launch_quantise_t<CT_F16, 80, true, false>(a, s);
+        if (dp == 96) return launch_quantise_t<CT_F16, 96, true, false>(a, s);
+    } else if (compute == FNN_F16) {
+        if (dp == 24) return launch_quantise_t<CT_F16, 24, false, false>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_F16, 32, false, false>(a, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 24) return launch_quantise_t<CT_BF16, 24, false, false>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_BF16, 32, false, false>(a, s);
+    } else {
+        if (dp == 8) return launch_quantise_t<CT_F32, 8, false, false>(a, s);
+        if (dp == 16) return launch_quantise_t<CT_F32, 16, false, false>(a, s);
+        if (dp == 24) return launch_quantise_t<CT_F32, 24, false, false>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_F32, 32, false, false>(a, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// The model behind the choice, in nanoseconds, fitted to calls between 16384 and a million pixels; both ways of 45 drawn calls
+// near the line, inputs not in the caches: those it takes gain 4 to 49 %, those it leaves would have gained 8 % at most (one
+// 512x384 pair of fp16 products, 263 us in one step, 274 in two).
+constexpr double BYTES_PER_NS = 4500.0;  // what the passes over the maps reach
+static int coarse_row_bytes(int compute, int dp) { return dp * elem_size(compute); }
+double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, bool l2) {
+    const bool cheap = compute != FNN_F32 && dp <= 32;
+    // rows of 16 channels take one matrix instruction per block as it is
+    if (m < 16 * SEG_PIXELS || nq > 0x7FFFFFFF / 2 || (cheap && dp <= 16)) return -1e30;
+    // what a block of 32x32 scores takes one SIMD in search_kernel, and in coarse_kernel
+    const double exact = compute == FNN_F32 ? 18.75 * dp : (cheap ? 46.0 : 1.64 * dp), coarse = 28.0;
+    const double blocks = (double)batch * ((nq + 31) / 32) * ((m + 31) / 32) / 1024.0;
+    // segments that a query is multiplied with again.  FNN_FLAG_L2 has wide bounds: its norm terms are multiplied by channels of ones.
+    const double again = (l2 ? 32.0 : 5.0) * SEG_PIXELS / m;
+    return blocks * (exact * (1.0 - again) - coarse) - 5000.0 - (double)batch * m * coarse_row_bytes(compute, dp) / BYTES_PER_NS;
+}
+double coarse_cost(int64_t rows, int compute, int dp) {
+    return 4000.0 + (double)rows * (coarse_row_bytes(compute, dp) + COARSE_ROW_BYTES + 4) / BYTES_PER_NS;
+}
+
+// Half segments balance a small search better (its workgroups get two or three cells each) and spread step 2 over more
+// workgroups; a large one saves the second half's epilogue and start-up.  Whole against half segments, all of a call's time: one
+// 512x384 pair with 3072 queries 237 / 227 us, four 517x389 ones 497 / 493, four two-term ones 784 / 736; one 1024x768 pair with 12288
+// queries 1097 / 1128, 16 512x384 ones 1492 / 1529.
+int coarse_cells(int64_t nq, int64_t n_segs, int batch) { return (double)((nq + 63) / 64) * n_segs * batch < 73728.0 ? 2 : 1; }
+
+int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch) {
+    const int64_t most = ((int64_t)128 << 20) / ((n_segs > 0 ? n_segs : 1) * batch) / 1024 * 1024;  // 256 MB of bounds (whole segments)
+    const int64_t all = round_up(nq, 64);
+    if (most < 8192) return all < 8192 ? all : 8192;
+    return all < most ? all : most;
+}
+
+template <int PAIRS, int CELL>
+static int coarse_wgs_per_pair(int batch) {
+    static DeviceCache resident_wgs;  // workgroups the current device holds at once
+    const long long resident = resident_wgs.get([](int dev) -> long long {
+        int per_cu = 0;
+        hipDeviceProp_t prop;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, coarse_kernel<PAIRS, CELL>, COARSE_WAVES * 64, 0) != hipSuccess ||
+            hipGetDeviceProperties(&prop, dev) != hipSuccess)
+            return -1;
+        return (long long)(per_cu > 0 ? per_cu : 1) * prop.multiProcessorCount;
+    });
+    if (resident <= 0) return 0;
+    int wgs = (int)resident / batch;
+    if (wgs >= 8) wgs &= ~7;  // a multiple of 8 per pair keeps the XCD renumbering a bijection
+    return wgs < 1 ? 1 : wgs;
+}
+template <int PAIRS, int CELL>
+static hipError_t launch_coarse_t(const SearchArgs& a, const CoarseArgs& ca, int batch, hipStream_t s) {
+    const int wgs = coarse_wgs_per_pair<PAIRS, CELL>(batch);
+    if (wgs == 0) return hipErrorUnknown;
+    return launch_detail(TK_COARSE, PAIRS * 2, coarse_kernel<PAIRS, CELL>, dim3(wgs, batch), dim3(COARSE_WAVES * 64), 0, s, a, ca);
+}
+template <int CT, int DP, int CELL>
+static hipError_t launch_refine_t(const SearchArgs& a, const CoarseArgs& ca, int batch, hipStream_t s) {
+    constexpr int RT = refine_tiles<CT, DP>() * CELL / SEG_TILES, WAVES = CELL / RT;
+    const int64_t slots = a.nq - ca.first_slot < ca.slab ? a.nq - ca.first_slot : ca.slab;
+    const unsigned ranges = (unsigned)((slots + REFINE_RANGE - 1) / REFINE_RANGE);
+    return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES>, dim3(ca.tgt.n_segs * (SEG_TILES / CELL), ranges, batch), dim3(64 * WAVES), 0, s, a, ca);
+}
+template <int CT, int DP>
+static hipError_t launch_both_t(const SearchArgs& a, CoarseArgs ca, int batch, hipStream_t s) {
+    const int pairs = (a.nq + 63) / 64;
+    const bool half = coarse_cells(a.nq, ca.tgt.n_segs, batch) == 2;
+    // The more query blocks a wave holds, the fewer times a tile is read (every pixel of a 512x384 pair: 12 blocks 1064 us, 16 blocks
+    // 992); three quads of 12 deal 16 pairs' 96 blocks evenly, where three of 16 leave waves idle (279 and 290 us).
+    const bool six = pairs % 32 != 0 && pairs % 24 == 0;
+    for (int64_t first = 0; first < a.nq; first += ca.slab) {
+        ca.first_slot = (int32_t)first;
+        hipError_t e = half ? launch_coarse_t<2, SEG_TILES / 2>(a, ca, batch, s)
+                            : (six ? launch_coarse_t<6, SEG_TILES>(a, ca, batch, s) : launch_coarse_t<8, SEG_TILES>(a, ca, batch, s));
+        if (e == hipSuccess) e = half ? launch_refine_t<CT, DP, SEG_TILES / 2>(a, ca, batch, s) : launch_refine_t<CT, DP, SEG_TILES>(a, ca, batch, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_coarse_search(const SearchArgs& a, const CoarseArgs& ca, int batch, int compute, int dp, hipStream_t s) {
+    if (a.nq <= 0 || batch <= 0) return hipSuccess;
+    if (compute == FNN_F16) {
+        if (dp == 24) return launch_both_t<CT_F16, 24>(a, ca, batch, s);
+        if (dp == 32) return launch_both_t<CT_F16, 32>(a, ca, batch, s);
+        if (dp == 48) return launch_both_t<CT_F16, 48>(a, ca, batch, s);
+        if (dp == 64) return launch_both_t<CT_F16, 64>(a, ca, batch, s);
+        if (dp == 80) return launch_both_t<CT_F16, 80>(a, ca, batch, s);
+        if (dp == 96) return launch_both_t<CT_F16, 96>(a, ca, batch, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 24) return launch_both_t<CT_BF16, 24>(a, ca, batch, s);
+        if (dp == 32) return launch_both_t<CT_BF16, 32>(a, ca, batch, s);
+    } else {
+        if (dp == 8) return launch_both_t<CT_F32, 8>(a, ca, batch, s);
+        if (dp == 16) return launch_both_t<CT_F32, 16>(a, ca, batch, s);
+        if (dp == 24) return launch_both_t<CT_F32, 24>(a, ca, batch, s);
+        if (dp == 32) return launch_both_t<CT_F32, 32>(a, ca, batch, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace fnn

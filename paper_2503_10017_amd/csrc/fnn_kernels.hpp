@@ -135,6 +135,73 @@ hipError_t launch_search_first(const FirstSearchArgs& a, int batch, int compute,
 // launch_resolve with the queries still in the caller's fp32 map
 hipError_t launch_resolve_raw(const FirstSearchArgs& a, int batch, int compute, int32_t* out_idx, float* out_score, int32_t* clear_count,
                               hipStream_t s);
+// ---- pass 1 in 8 bits, for searches large enough (coarse.hip) -------------------------------
+// Pixels of a map are taken SEG_PIXELS at a time: one scale and one set of bounds for each segment.  A query's scores
+// are bounded per CELL, a whole segment or half of one.
+constexpr int SEG_TILES = 32;
+constexpr int SEG_PIXELS = 32 * SEG_TILES;
+constexpr int COARSE_ROW_BYTES = 32;  // one K=32 matrix instruction
+struct SegInfo {
+    float scale;     // a row is about scale * its 8-bit row
+    float residual;  // at most this far from it, in any of the segment's rows
+    float length;    // the longest 8-bit row, scaled
+    float reserved;
+};
+// The 8-bit image of a batch of prepared maps.  Rows past the map repeat its last row.
+struct CoarseMap {
+    char* rows;           // [batch][n_segs * SEG_PIXELS][COARSE_ROW_BYTES]
+    uint32_t* row_bound;  // [batch][n_segs * SEG_PIXELS] length and residual of every row over its segment's scale (two bf16, rounded up)
+    SegInfo* seg;         // [batch][n_segs]
+    int32_t n_segs;
+};
+struct QuantiseSide {
+    const char* prepared;  // [batch] prepared maps, bstride bytes apart: read, or (raw) written on the way
+    int64_t bstride;
+    int64_t n;             // valid pixels (gather: rows listed)
+    int64_t n_pad;         // prepared rows per pair (raw)
+    const float* raw[FNN_MAX_BATCH];  // the caller's fp32 rows of 24 channels, 16-byte aligned (raw_rows)
+    int64_t raw_stride;    // floats
+    const int32_t* gather; // [batch][n] rows of the source to take, in this order (NULL: all of them)
+    int64_t gather_rows;   // rows of that source; the list's entries are clamped to it
+    int32_t second_image;  // which copies of a two-term row hold the low halves
+    CoarseMap out;
+};
+struct QuantiseArgs {
+    PrepExtra extra;       // side jobs that ride along where there is no prepare launch
+    QuantiseSide side[2];
+    int32_t batch;
+    int32_t raw_rows;
+    uint32_t* lower;       // bounds to clear
+    int64_t lower_count;
+    int32_t split_d;       // channels of a two-term row's descriptor (0: rows are not two-term)
+};
+hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream_t s);
+
+struct CoarseArgs {
+    CoarseMap src, tgt;
+    int32_t src_listed;    // src holds the queries themselves, in the order of their slots
+    uint16_t* upper;       // [batch][cells][slab] bf16: no score of the cell lies above it
+    uint32_t* lower;       // [batch][slot_pitch] order_bits: some score lies at or above it (0 on entry)
+    int32_t slab;          // slots that one launch takes (a multiple of 64)
+    int64_t slot_pitch;    // queries of a pair, rounded up to whole 64s
+    int32_t first_slot;    // set by the launcher
+    int32_t min_live;      // fewer live queries of a pair than this: its cells are refined for every query
+};
+// What launch_search does: the queries' list and live count, the prepared maps and the keys are those of `a`.
+hipError_t launch_coarse_search(const SearchArgs& a, const CoarseArgs& ca, int batch, int compute, int dp, hipStream_t s);
+// Nanoseconds of the device that a search of `nq` queries per pair against maps of m pixels gains in two steps (very negative where
+// it has to run in one), and what the 8-bit maps of `rows` pixels cost
+double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, bool l2);
+double coarse_cost(int64_t rows, int compute, int dp);
+constexpr double COARSE_LEAST_GAIN = 3000.0;  // of a call
+// Fewer queries per pair than this spread the second step thin: a call with so few runs in one
+inline int64_t coarse_least_queries(int compute, int dp) { return compute == FNN_F32 || dp > 32 ? 256 : 2048; }
+// Live queries of a pair below which its part of a later search goes straight to the second step
+inline int coarse_min_live(int compute, int dp) { return compute == FNN_F32 || dp > 32 ? 64 : 512; }
+// Slots per launch that keep the table of upper bounds small
+int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch);
+int coarse_cells(int64_t nq, int64_t n_segs, int batch);  // cells of a segment
+
 // Pass 2: out_keys become (best score, lowest candidate index); optionally also stored to
 // out_idx / out_score (either may be NULL).  Queries without any candidate get -1 / -inf.
 // clear_count, if not NULL, is int32[batch] to set to 0.

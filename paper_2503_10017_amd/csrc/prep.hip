@@ -5,6 +5,7 @@
 #include "dense_perm.hpp"
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
+#include "side_jobs.hpp"
 #include "trace.hpp"
 
 namespace fnn {
@@ -64,23 +65,6 @@ __device__ __forceinline__ void split_norm_term(float term, int compute, float& 
     lo = round_to_compute(__builtin_fmaxf(term - hi, lowest), compute);
 }
 
-// Side jobs spread over all threads of the launch (see PrepExtra).
-__device__ __forceinline__ void prep_side_jobs(const PrepArgs& a) {
-    const PrepExtra& x = a.extra;
-    const int64_t tid = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t n_threads = (int64_t)gridDim.x * gridDim.y * blockDim.x;
-    if (x.zero_ptr)
-        for (int64_t i = tid; i < x.zero_count; i += n_threads) x.zero_ptr[i] = 0;
-    if (x.seeds) {
-        const int64_t total = (int64_t)a.batch * x.n_seeds;
-        for (int64_t i = tid; i < total; i += n_threads) {
-            x.cur_u[i] = x.seeds[i];
-            x.seed_id[i] = (int32_t)(i % x.n_seeds);
-        }
-        for (int64_t b = tid; b < a.batch; b += n_threads) x.n_active[b] = x.n_seeds;
-    }
-}
-
 // The norm of one source descriptor, and -1/2 |x|^2 of one as prepared (divided by `norm` if that is set, then
 // rounded to the compute format), read element by element: squared_length() in a rolled loop.
 __device__ __forceinline__ float descriptor_norm(const void* src, int64_t first, int d, int dtype) {
@@ -107,7 +91,7 @@ __device__ __forceinline__ float prepared_norm_term(const void* src, int64_t fir
 // the whole row for a norm; launch_prep() says which maps take that and which the staged kernel below.
 template <bool OPTIONS>
 __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
-    prep_side_jobs(a);
+    side_jobs(a.extra, a.batch);
     const int side_idx = blockIdx.y / a.batch;
     const int b = blockIdx.y % a.batch;
     const PrepSide& sd = a.side[side_idx];
@@ -218,7 +202,7 @@ static_assert(STAGE_ROWS == 32 * 8 && DENSE_S % 8 == 0, "a run of stored rows is
 template <int IN, int COMPUTE>
 __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
     extern __shared__ uint4 stage[];
-    prep_side_jobs(a);
+    side_jobs(a.extra, a.batch);
     const int side_idx = blockIdx.y / a.batch;
     const int b = blockIdx.y % a.batch;
     const PrepSide& sd = a.side[side_idx];
@@ -411,7 +395,7 @@ __global__ __launch_bounds__(STAGE_ROWS) void prep_staged_kernel(PrepArgs a) {
 // IN = d / 8, OUT = dp / 8.
 template <int IN, int OUT, int COMPUTE>
 __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
-    prep_side_jobs(a);
+    side_jobs(a.extra, a.batch);
     const int side_idx = blockIdx.y / a.batch;
     const int b = blockIdx.y % a.batch;
     const PrepSide& sd = a.side[side_idx];
@@ -493,7 +477,7 @@ static hipError_t launch_prep_rows(const PrepArgs& a, dim3 grid, hipStream_t s) 
 // (the copies' layout: see prep_staged_kernel).
 template <int IN>
 __global__ __launch_bounds__(256) void prep_split_rows_kernel(PrepArgs a) {
-    prep_side_jobs(a);
+    side_jobs(a.extra, a.batch);
     const int side_idx = blockIdx.y / a.batch;
     const int b = blockIdx.y % a.batch;
     const PrepSide& sd = a.side[side_idx];
@@ -539,7 +523,7 @@ __global__ __launch_bounds__(256) void prep_split_rows_kernel(PrepArgs a) {
 // formats) or two (fp32) 16-byte stores.
 template <int GROUPS, int COMPUTE>
 __global__ __launch_bounds__(256) void prep_f32_kernel(PrepArgs a) {
-    prep_side_jobs(a);
+    side_jobs(a.extra, a.batch);
     const int side_idx = blockIdx.y / a.batch;
     const int b = blockIdx.y % a.batch;
     const PrepSide& sd = a.side[side_idx];
@@ -628,7 +612,7 @@ hipError_t launch_fill_i32f32(int32_t* idx, float* score, int64_t count, hipStre
 }
 
 // The side jobs alone.
-__global__ __launch_bounds__(256) void init_kernel(PrepArgs a) { prep_side_jobs(a); }
+__global__ __launch_bounds__(256) void init_kernel(PrepArgs a) { side_jobs(a.extra, a.batch); }
 
 // Whether maps with options go through LDS.  Few rows are all latency, and staging adds three barriers and,
 // where rows are not copied whole or are not whole 8-channel groups, a longer chain per thread.  One pair, fp32 maps

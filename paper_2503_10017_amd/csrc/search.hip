@@ -18,6 +18,7 @@
 
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
+#include "query_rows.hpp"
 #include "trace.hpp"
 
 namespace fnn {
@@ -34,45 +35,6 @@ constexpr int SEARCH_WIDE_MIN_TILES = 128;  // a wave takes more groups only whi
 constexpr int SEARCH_MIN_TILES = 8;
 constexpr int SEARCH_WAVES = 4;       // waves per workgroup
 constexpr int SEARCH_P = 4;           // candidate tiles in flight per wave
-
-__device__ __forceinline__ int64_t query_row(const SearchArgs& a, int64_t qbase, int slot) {
-    int64_t row;
-    if (a.q_keys) row = (int64_t)(0xFFFFFFFFu - (uint32_t)(a.q_keys[qbase + slot] & 0xFFFFFFFFull));
-    else if (a.q_idx) row = a.q_idx[qbase + slot];
-    else row = slot;
-    return min(max(row, (int64_t)0), (int64_t)a.src_rows - 1);  // never read outside the map
-}
-
-// The rows of this lane's query in N consecutive 32-query blocks from slot0 on.  All N index loads
-// are in flight together: taken one by one behind the tests above, each waited for the one
-// before it and for that block's row, two memory latencies per block before a wave could start (one
-// 512x384 pair: first search 37.6 -> 33.4 us, 16 pairs with 1450 queries each 241 -> 228 us, with the
-// waits moved out of the candidate loop, see arrived()).  Slots past the live queries repeat the
-// last one; their results are dropped.
-template <int N>
-__device__ __forceinline__ void query_rows(const SearchArgs& a, int64_t qbase, int slot0, int n_act, int c, int32_t (&row)[N]) {
-    int slot[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) slot[i] = min(slot0 + i * 32 + c, n_act - 1);
-    if (a.q_keys) {
-        uint32_t low[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) low[i] = reinterpret_cast<const uint32_t*>(a.q_keys + qbase + slot[i])[0];
-#pragma unroll
-        for (int i = 0; i < N; ++i) row[i] = (int32_t)min(0xFFFFFFFFu - low[i], (uint32_t)a.src_rows - 1u);
-    } else if (a.q_idx) {
-        int32_t idx[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) idx[i] = a.q_idx[qbase + slot[i]];
-#pragma unroll
-        for (int i = 0; i < N; ++i) row[i] = idx[i];
-    } else {
-#pragma unroll
-        for (int i = 0; i < N; ++i) row[i] = slot[i];
-    }
-#pragma unroll
-    for (int i = 0; i < N; ++i) row[i] = min(max(row[i], 0), a.src_rows - 1);  // never read outside the map
-}
 
 // One unit of pass 1: the query blocks of slots [slot0, slot0 + 32*R*G) against the candidate
 // tiles [t0, t1).  Per query the best score and the 32-candidate TILE that holds it: a lane only

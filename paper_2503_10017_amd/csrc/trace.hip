@@ -96,6 +96,9 @@ const char* fnn_trace_kind_name(int32_t kind) {
         case TK_BLOCKED: return "blocked_kernels";
         case TK_PIXELS: return "pairs_to_pixels_kernel";
         case TK_RECIP_WALK: return "recip_walk_kernel";
+        case TK_QUANTISE: return "quantise_kernel";
+        case TK_COARSE: return "coarse_kernel";
+        case TK_REFINE: return "refine_kernel";
         default: return "unknown";
     }
 }

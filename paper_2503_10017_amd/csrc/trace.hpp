@@ -22,7 +22,10 @@ enum TraceKind : int {
     TK_BLOCKED = 11,
     TK_PIXELS = 12,
     TK_RECIP_WALK = 13,
-    TK_COUNT = 14
+    TK_QUANTISE = 14,
+    TK_COARSE = 15,
+    TK_REFINE = 16,
+    TK_COUNT = 17
 };
 
 // Returns false when no trace is open or it is full; otherwise hands out the next event pair.

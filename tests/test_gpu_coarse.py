@@ -1,0 +1,223 @@
+"""Large searches score everything in 8 bits first and multiply again, in the call's own format, only where a bound
+says that the best candidate may be.  The same call with a workspace that ends where the 8-bit maps would begin runs in
+one step: both must give the same bits, whatever the maps hold, and the trace says which way a call took."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2503_10017_amd as fnn
+from gpu_helpers import check_nearest_against, check_reciprocal_exact, dev, exact_maps, host, unit_maps, GAP_ROUNDED, ROUNDERS, SCORE_TOL_ROUNDED
+
+pytestmark = pytest.mark.gpu
+
+ELEMENT = {"f32": 4, "f16": 2, "bf16": 2}
+
+
+def up(x, to):
+    return -(-x // to) * to
+
+
+def channels(d, compute, l2=False, split=False):
+    d = 3 * d if split else d + (0 if not l2 else 2 if compute == "f32" else 4)
+    if compute == "f32":
+        return up(d, 8)
+    return 16 if d <= 16 else 24 if d <= 24 else up(d, 16)
+
+
+def enough_pairs(nq, n, m, compute, d, **kw):
+    """Pairs that make a call worth two steps, by the library's own estimate of both (nanoseconds)."""
+    dp = channels(d, compute, kw.get("l2", False), kw.get("split", False))
+    row, block = dp * ELEMENT[compute], 18.75 * dp if compute == "f32" else 46.0 if dp <= 32 else 1.64 * dp
+    again = 1024 * (32.0 if kw.get("l2") else 5.0)
+
+    def gain(pixels):
+        return -(-nq // 32) * -(-pixels // 32) / 1024.0 * (block * (1.0 - again / pixels) - 28.0) - pixels * row / 4500.0
+
+    maps = (n + m) * (row + 36) / 4500.0
+    for batch in range(1, 65):
+        if batch * gain(m) - 5000.0 - 4000.0 - batch * maps > 3000.0 and batch * (gain(m) + gain(n) - maps) - 14000.0 > 3000.0:
+            return batch
+    raise AssertionError("no batch is worth it")
+
+
+def one_step_bytes(op, batch, n, m, d, nq, compute, **kw):
+    """The workspace of a search in one step: prepared maps and keys, for the iteration its state too."""
+    row = channels(d, compute, kw.get("l2", False), kw.get("split", False)) * ELEMENT[compute]
+    maps = up(batch * up(n, 32) * row, 256) + up(batch * up(m, 32) * row, 256)
+    if op == "nearest":
+        return maps + up(batch * nq * 8, 256)
+    words = up(batch * up(n, 32) // 32 * 4, 256)
+    return maps + 2 * up(batch * nq * 8, 256) + 2 * words + 4 * up(batch * nq * 4, 256) + up(batch * 4, 256)
+
+
+def run(op, a, b, queries, compute, two_steps, max_iter=6, **kw):
+    batch, n, d = a.shape
+    m = b.shape[1]
+    nq = n if queries is None else queries.shape[1]
+    small = one_step_bytes(op, batch, n, m, d, nq, compute, **kw)
+    full = fnn.fnn_workspace_bytes_opts(batch, n, m, d, nq, compute, max_iter, **{k: v for k, v in kw.items()})
+    assert full > small
+    ws = torch.full((full if two_steps else small,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    fnn.fnn_trace_begin(128)
+    try:
+        if op == "nearest":
+            idx, score = fnn.fnn_nearest(a, b, q_idx=queries, compute=compute, workspace=ws, **kw)
+            out = {"idx": idx, "score": score}
+        else:
+            out = fnn.fnn_reciprocal(a, b, queries, max_iter, compute, workspace=ws, **kw)
+        torch.cuda.synchronize()
+    finally:
+        names = [name for name, _ in fnn.fnn_trace_end(128)]
+    assert ("coarse_kernel" in names) == two_steps and ("refine_kernel" in names) == two_steps
+    return {k: host(v) for k, v in out.items()}
+
+
+def same(op, a, b, queries, compute, **kw):
+    two, one = (run(op, a, b, queries, compute, x, **kw) for x in (True, False))
+    for k in one:
+        assert np.array_equal(two[k], one[k]), (k, int(np.sum(two[k] != one[k])))
+    return two
+
+
+@pytest.mark.parametrize("n,m,nq,compute,stored,d,kw", [
+    (65536, 65536, 4096, "f16", "f32", 24, {}),                      # whole segments, raw rows
+    (70011, 65537, 4097, "bf16", "f32", 24, {}),                     # one candidate in the last segment
+    (66000, 70001, 5001, "f16", "f32", 21, {}),                      # channels padded: prepared first
+    (66000, 68001, 4500, "bf16", "f16", 30, {}),                     # 32-channel rows
+    (65551, 70017, 4200, "f16", "f16", 24, {}),                      # rows of the caller, not whole tiles
+    (65568, 70016, 4200, "f16", "f16", 24, {}),                      # ... and where they are
+    (33000, 36001, 1000, "f32", "f32", 24, {}),
+    (33000, 36001, 1500, "f32", "f32", 5, {}),
+    (33000, 35001, 700, "f32", "f32", 31, {}),
+    (132000, 131100, 600, "f32", "bf16", 13, {"l2": True}),
+    (66000, 70000, 3000, "f16", "f32", 24, {"split": True}),
+    (66000, 70000, 2600, "f16", "f32", 13, {"split": True}),
+    (66000, 70000, 2800, "f16", "f32", 32, {"split": True, "normalize": True}),
+    (67000, 68000, 4500, "bf16", "f32", 24, {"normalize": True}),
+])
+@pytest.mark.parametrize("op", ["nearest", "reciprocal"])
+def test_same_bits_in_two_steps_as_in_one(op, n, m, nq, compute, stored, d, kw):
+    batch = enough_pairs(nq, n, m, compute, d, **kw)
+    gen = torch.Generator(device="cuda:0").manual_seed(n + m + nq)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda:0")
+
+    a = torch.nn.functional.normalize(normal(batch, n, d), dim=2)
+    b = torch.nn.functional.normalize(normal(batch, m, d), dim=2)
+    b[:, :n // 2] = torch.nn.functional.normalize(a[:, :n // 2] + 0.3 * b[:, :n // 2], dim=2)  # half the pixels have a partner
+    if kw:  # raw rows
+        a, b = a * torch.exp(0.3 * normal(batch, n, 1)), b * torch.exp(0.3 * normal(batch, m, 1))
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[stored]
+    a, b = a.to(kind), b.to(kind)
+    q = torch.randint(0, n, (batch, nq), generator=gen, device="cuda:0", dtype=torch.int32)
+    got = same(op, a, b, q, compute, **kw)
+    if op == "nearest" and not kw and stored == "f32" and compute != "f32":
+        ra, rb = ROUNDERS[compute](host(a[0])), ROUNDERS[compute](host(b[0]))
+        ri, rbest, rsecond = oracle.nearest(ra[host(q[0])], rb)
+        check_nearest_against(got["idx"][0], got["score"][0], ri, rbest, rsecond, GAP_ROUNDED, SCORE_TOL_ROUNDED)
+    if op == "nearest" and n in (65536, 65568):
+        same(op, a, b, None, compute, **kw)  # every pixel a query
+
+
+@pytest.mark.parametrize("compute", ["f16", "f32"])
+def test_exact_maps_with_ties_match_the_oracle(compute):
+    a, b = exact_maps(5, 65600, 66001, 24)
+    b[7000:7400] = b[100:500]      # equal candidates in different segments: the lowest index wins
+    q = np.arange(0, 65600, 15).astype(np.int32)
+    batch = enough_pairs(len(q), len(a), len(b), compute, 24)
+    ta, tb, tq = dev(a)[None].repeat(batch, 1, 1), dev(b)[None].repeat(batch, 1, 1), dev(np.tile(q, (batch, 1)))
+    got = same("nearest", ta, tb, tq, compute)
+    ri, rbest, _ = oracle.nearest(a[q], b)
+    assert np.array_equal(got["idx"][-1], ri) and np.array_equal(got["score"][-1], rbest)
+    got = same("reciprocal", ta, tb, tq, compute)
+    check_reciprocal_exact(got, batch - 1, oracle.reciprocal(a, b, q, 6))
+
+
+def _special(kind, rng, n, m):
+    a, b = unit_maps(int(rng.integers(1 << 30)), n, m, 24)
+    if kind == "all equal":
+        a[:], b[:] = a[0], a[0]
+    elif kind == "negative":                       # every score is below zero: padding must not win
+        a, b = np.abs(a) + 0.1, -np.abs(b) - 0.1
+    elif kind == "outlier":                        # one row far longer than the rest flattens its segment's 8-bit rows
+        a[3], b[5000] = 3000.0 * a[3], 3000.0 * b[5000]
+    elif kind == "zero rows":
+        a[::3], b[:2048], b[-5:] = 0.0, 0.0, 0.0
+    elif kind == "tiny":                           # below what fp16 calls normal
+        a, b = a * np.float32(1e-4), b * np.float32(3e-5)
+    elif kind == "lengths":
+        a = a * np.exp(2.0 * rng.standard_normal((n, 1))).astype(np.float32)
+        b = b * np.exp(2.0 * rng.standard_normal((m, 1))).astype(np.float32)
+    elif kind == "beyond bounds":                  # squares that leave fp32's comfortable range
+        a[:1000] *= np.float32(1e-17)
+        b[:1000] *= np.float32(1e-18)
+        a[1000:1200] *= np.float32(1e16)
+        b[3000:3200] *= np.float32(1e17)
+    elif kind == "not finite":
+        a[::7, 3], a[5::7, 4], b[1::5, 7], b[2::50] = np.nan, np.inf, np.nan, -np.inf
+    return a, b
+
+
+SPECIAL = ["all equal", "negative", "outlier", "zero rows", "tiny", "lengths", "beyond bounds", "not finite"]
+
+
+@pytest.mark.parametrize("kind,compute", [(k, c) for k in SPECIAL for c in ("f16", "bf16", "f32") if (k, c) != ("beyond bounds", "f16")])
+def test_maps_that_strain_the_bounds(kind, compute):
+    rng = np.random.default_rng(11)
+    n, m = 65601, 66011
+    batch = enough_pairs(4500, n, m, compute, 24)
+    maps = [_special(kind, rng, n, m) for _ in range(min(batch, 3))]
+    maps = [maps[p % len(maps)] for p in range(batch)]
+    a, b = (dev(np.stack([x[i] for x in maps])) for i in (0, 1))
+    q = dev(rng.integers(0, n, size=(batch, 4500)).astype(np.int32))
+    q[:, :8] = 3
+    if kind == "not finite":  # unspecified results, but indices inside the maps
+        got = run("nearest", a, b, q, compute, True)
+        assert got["idx"].min() >= 0 and got["idx"].max() < m
+        got = run("reciprocal", a, b, q, compute, True)
+        assert min(got["seed_i"].min(), got["seed_j"].min()) >= 0 and got["seed_i"].max() < n and got["seed_j"].max() < m
+        return
+    same("nearest", a, b, q, compute)
+    same("reciprocal", a, b, q, compute)
+
+
+def test_queries_in_more_than_one_launch():
+    """The table of bounds covers as many queries at a time as 256 MB hold."""
+    n, m, batch = 16400, 200000, 64
+    a, b = unit_maps(77, n, m, 24)
+    ta, tb = [dev(a).half()] * batch, [dev(b).half()] * batch
+    nq = n
+    full = fnn.fnn_workspace_bytes(batch, n, m, 24, nq, "f16")
+    fnn.fnn_trace_begin(32)
+    ws = torch.full((full,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    idx, score = fnn.fnn_nearest(ta, tb, compute="f16", workspace=ws)
+    torch.cuda.synchronize()
+    names = [name for name, _ in fnn.fnn_trace_end(32)]
+    assert names.count("coarse_kernel") == 1 + (nq - 1) // max(8192, (128 << 20) // (196 * batch) // 1024 * 1024) > 1
+    small = one_step_bytes("nearest", batch, n, m, 24, nq, "f16")
+    want, wscore = fnn.fnn_nearest(ta, tb, compute="f16", workspace=ws[:small])
+    assert torch.equal(idx, want) and torch.equal(score, wscore)
+
+
+def test_small_and_narrow_calls_keep_one_step():
+    a, b = unit_maps(3, 66000, 66000, 24)
+    ta, tb = dev(a), dev(b)
+    q = dev(np.arange(8192, dtype=np.int32))[None].repeat(32, 1)
+
+    def two_steps(x, y, queries, compute, **kw):
+        fnn.fnn_trace_begin(16)
+        fnn.fnn_nearest([x] * len(queries), [y] * len(queries), q_idx=queries, compute=compute, **kw)
+        torch.cuda.synchronize()
+        return "coarse_kernel" in [name for name, _ in fnn.fnn_trace_end(16)]
+
+    assert two_steps(ta, tb, q, "f16") and not two_steps(ta, tb, q[:, :2047].contiguous(), "f16")
+    assert two_steps(ta, tb, q[:, :2047].contiguous(), "f32") and two_steps(ta, tb, q[:, :2047].contiguous(), "f16", split=True)
+    assert not two_steps(ta, tb, q[:, :255].contiguous(), "f32")
+    assert not two_steps(ta, tb[:16383], q, "f32") and two_steps(ta, tb[:16384], q, "f32")
+    assert not two_steps(ta, tb, q[:1], "f16")                             # one pair of this size
+    assert not two_steps(ta[:, :16], tb[:, :16], q, "f16")                # one matrix instruction as it is
+    assert not two_steps(ta, tb, q, "f16", l2=True)                       # bounds too wide on a map of this size
+    count = torch.full((32,), 8192, dtype=torch.int32, device="cuda:0")
+    assert not two_steps(ta, tb, q, "f16", nq_active=count)               # live counts on the device
