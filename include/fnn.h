@@ -47,7 +47,7 @@
  *    the workspace (cast to the compute format, rows padded to whole 32-pixel tiles).  Large searches
  *    (from 2048 queries per pair, with FNN_F32 or FNN_FLAG_SPLIT from 256, against maps of at least 16384 pixels) score an
  *    8-bit copy of the maps first and multiply in the compute format only where a bound on what the 8 bits left out says
- *    that the best candidate may be: the same results, from a workspace of the size that fnn_workspace_bytes() returns;
+ *    that the best candidate may be, and so does fnn_mutual_dense on large maps: the same results, from a workspace of the size that fnn_workspace_bytes() returns;
  *    one that has room for the prepared maps and the call's state only is accepted as well and searched in one
  *    step.  Two cases need no separate copy pass, and results do not depend on which way a map took:
  *    (a) the caller's array already is what the copy would be -- stored in the compute format,
@@ -245,7 +245,7 @@ int32_t fnn_reciprocal_static(int32_t batch, const fnn_map* d1, const fnn_map* d
  *   nn21[b][j] = lowest i maximising S[i][j],  s21 = that score      (int32/float [batch][m])
  *   pairs[b]   = the (i, nn12[i]) with nn21[nn12[i]] == i, ascending in i
  *                (int32[batch][min(n,m)][2], entries past n_pairs[b] are -1)
- * Every S[i][j] is computed once and feeds both directions, so nn12 and nn21 are consistent
+ * Both directions take the same products, bit for bit, so nn12 and nn21 are consistent
  * with each other.  s12, s21 may be NULL.
  * n and m may not exceed 2^30 here (FNN_E_SHAPE).
  */

@@ -93,10 +93,10 @@ struct CoarseLayout {
     int64_t slot_pitch;
     int64_t slab;
 };
-CoarseMap carve_coarse_map(Carver& cv, int batch, int64_t pixels) {
+CoarseMap carve_coarse_map(Carver& cv, int batch, int64_t pixels, int segment = SEG_PIXELS) {
     CoarseMap M;
-    M.n_segs = (int32_t)((pixels + SEG_PIXELS - 1) / SEG_PIXELS);
-    const size_t rows = (size_t)batch * M.n_segs * SEG_PIXELS;
+    M.n_segs = (int32_t)((pixels + segment - 1) / segment);
+    const size_t rows = (size_t)batch * M.n_segs * segment;
     M.rows = (char*)cv.take(rows * COARSE_ROW_BYTES);
     M.row_bound = (uint32_t*)cv.take(rows * sizeof(uint32_t));
     M.seg = (SegInfo*)cv.take((size_t)batch * M.n_segs * sizeof(SegInfo));
@@ -137,15 +137,15 @@ constexpr int RECIP_COARSE_SEARCHES = 4;  // out and back, of the first two iter
 
 // Searches of a call that run in two steps, if its workspace allows: none or the one of fnn_nearest, none, the first two or the
 // first four of the iteration.  About half the seeds live to see the second iteration; if few do, two launches are wasted.
-int nearest_coarse_searches(int batch, int64_t n, int64_t m, int64_t nq, bool listed, int compute, int dp, bool l2) {
+int nearest_coarse_searches(int batch, int64_t n, int64_t m, int64_t nq, bool listed, int compute, int dp, int d, bool l2) {
     if (nq < coarse_least_queries(compute, dp)) return 0;
-    const double gain = coarse_gain(nq, m, batch, compute, dp, l2) - coarse_cost(batch * (m + (listed ? nq : n)), compute, dp);
+    const double gain = coarse_gain(nq, m, batch, compute, dp, d, l2) - coarse_cost(batch * (m + (listed ? nq : n)), compute, dp);
     return gain > COARSE_LEAST_GAIN ? 1 : 0;
 }
-int recip_coarse_searches(int batch, int64_t n, int64_t m, int64_t n_seeds, int compute, int dp, bool l2) {
+int recip_coarse_searches(int batch, int64_t n, int64_t m, int64_t n_seeds, int compute, int dp, int d, bool l2) {
     if (n_seeds < coarse_least_queries(compute, dp)) return 0;
-    const double first = coarse_gain(n_seeds, m, batch, compute, dp, l2) + coarse_gain(n_seeds, n, batch, compute, dp, l2);
-    const double second = coarse_gain(n_seeds / 2, m, batch, compute, dp, l2) + coarse_gain(n_seeds / 2, n, batch, compute, dp, l2);
+    const double first = coarse_gain(n_seeds, m, batch, compute, dp, d, l2) + coarse_gain(n_seeds, n, batch, compute, dp, d, l2);
+    const double second = coarse_gain(n_seeds / 2, m, batch, compute, dp, d, l2) + coarse_gain(n_seeds / 2, n, batch, compute, dp, d, l2);
     const double gain = first + (second > 0.0 ? second : 0.0) - coarse_cost(batch * (n + m), compute, dp);
     return gain <= COARSE_LEAST_GAIN ? 0 : (second > 2.0 * COARSE_LEAST_GAIN ? RECIP_COARSE_SEARCHES : 2);
 }
@@ -186,6 +186,38 @@ DenseLayout carve_dense(Carver& cv, int batch, int64_t n, int64_t m, int d, int 
     const int64_t most = n > m ? n : m;
     L.blocks_per_pair = (most + 1023) / 1024;
     L.block_counts = (int32_t*)cv.take((size_t)batch * (L.blocks_per_pair + 1) * sizeof(int32_t));
+    return L;
+}
+
+// Room for the dense mode's 8-bit pass behind its own layout.
+struct DenseCoarseLayout {
+    DenseCoarseArgs args;
+    int32_t n_sb;  // runs of DENSE_SB_PIXELS of image 1
+    int32_t slab;  // ... per launch
+};
+DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m) {
+    DenseCoarseLayout L;
+    memset(&L, 0, sizeof(L));
+    DenseCoarseArgs& a = L.args;
+    a.seg_pixels = dense_seg_pixels(n);
+    a.map[0] = carve_coarse_map(cv, batch, round_up(n, DENSE_SB_PIXELS), a.seg_pixels);
+    a.map[1] = carve_coarse_map(cv, batch, round_up(m, DENSE_SB_PIXELS), a.seg_pixels);
+    a.n_tiles[0] = (int32_t)((n + 31) / 32);
+    a.n_tiles[1] = (int32_t)((m + 31) / 32);
+    a.cell_groups = dense_cell_groups(n, m);
+    a.n_cells = (int32_t)((m + 512 * a.cell_groups - 1) / (512 * a.cell_groups));
+    // 128 MB of scores for the queries of a launch
+    const int64_t per_sb = (int64_t)batch * a.n_cells * DENSE_SB_PIXELS * (int64_t)sizeof(uint16_t);
+    int64_t slab = ((int64_t)128 << 20) / (per_sb > 0 ? per_sb : 1);
+    if (slab < 1) slab = 1;
+    L.n_sb = (int32_t)((n + DENSE_SB_PIXELS - 1) / DENSE_SB_PIXELS);
+    const int64_t launches = (L.n_sb + slab - 1) / slab;
+    L.slab = launches > 0 ? (int32_t)((L.n_sb + launches - 1) / launches) : 1;
+    const size_t pixels2 = (size_t)a.map[1].n_segs * a.seg_pixels;
+    a.best[0] = (uint16_t*)cv.take((size_t)per_sb * L.slab);
+    a.best[1] = (uint16_t*)cv.take((size_t)batch * a.map[0].n_segs * pixels2 * sizeof(uint16_t));
+    a.mask[0] = (uint64_t*)cv.take((size_t)per_sb * L.slab / 16);
+    a.mask[1] = (uint64_t*)cv.take((size_t)batch * a.map[0].n_segs * pixels2 / 8);
     return L;
 }
 
@@ -323,7 +355,7 @@ hipError_t prep_both(int32_t batch, const fnn_map* a, const fnn_map* b, const Ma
 
 // One side of the quantise launch; raw: the caller's fp32 maps are read, else the prepared ones at `prepared`.
 void fill_quantise_side(QuantiseSide& sd, int32_t batch, const fnn_map* maps, bool raw, const char* prepared, int64_t bstride, int64_t n_pad,
-                        int second_image, const CoarseMap& out) {
+                        const CoarseMap& out) {
     sd.prepared = prepared;
     sd.bstride = bstride;
     sd.n = maps[0].n;
@@ -331,8 +363,58 @@ void fill_quantise_side(QuantiseSide& sd, int32_t batch, const fnn_map* maps, bo
     if (raw)
         for (int b = 0; b < batch; ++b) sd.raw[b] = (const float*)maps[b].data;
     sd.raw_stride = maps[0].row_stride;
-    sd.second_image = second_image;
     sd.out = out;
+}
+
+// Both directions of the dense mode from its 8-bit maps to the keys: pass 1 range by range of image 1, the second step for the queries
+// of a range at once, for the candidates when every range is done.
+hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int batch, int64_t n, int64_t m, int compute, hipStream_t s) {
+    SearchArgs rows;
+    memset(&rows, 0, sizeof(rows));
+    rows.src = (const char*)L.maps.p1;
+    rows.src_bstride = L.maps.bstride1;
+    rows.src_rows = (int32_t)L.maps.n_pad;
+    rows.nq = (int32_t)n;
+    rows.tgt = (const char*)L.maps.p2;
+    rows.tgt_bstride = L.maps.bstride2;
+    rows.m = (int32_t)m;
+    rows.m_tiles = (int32_t)(L.maps.m_pad / 32);
+    rows.out_keys = L.row_keys;
+    SearchArgs cols = rows;
+    cols.src = rows.tgt;
+    cols.src_bstride = rows.tgt_bstride;
+    cols.src_rows = (int32_t)L.maps.m_pad;
+    cols.nq = (int32_t)m;
+    cols.tgt = rows.src;
+    cols.tgt_bstride = rows.src_bstride;
+    cols.m = (int32_t)n;
+    cols.m_tiles = (int32_t)((n + 31) / 32);
+    cols.out_keys = L.col_keys;
+
+    CoarseArgs ca;
+    memset(&ca, 0, sizeof(ca));
+    DenseCoarseArgs da = C.args;
+    for (int sb = 0; sb < C.n_sb; sb += C.slab) {
+        da.first_sb = sb;
+        da.n_sb = C.n_sb - sb < C.slab ? C.n_sb - sb : C.slab;
+        hipError_t e = launch_dense_coarse(da, batch, s);
+        if (e == hipSuccess) e = launch_dense_select(da, 0, batch, s);
+        ca.mask = da.mask[0];
+        ca.slab = da.n_sb * DENSE_SB_PIXELS;
+        ca.n_cells = da.n_cells;
+        ca.cell_shift = da.cell_groups == 8 ? 2 : (da.cell_groups == 4 ? 1 : 0);
+        ca.first_slot = sb * DENSE_SB_PIXELS;
+        if (e == hipSuccess) e = launch_refine(rows, ca, batch, compute, L.maps.dp, s);
+        if (e != hipSuccess) return e;
+    }
+    hipError_t e = launch_dense_select(da, 1, batch, s);
+    ca.mask = da.mask[1];
+    ca.slab = da.map[1].n_segs * da.seg_pixels;
+    ca.n_cells = da.map[0].n_segs;
+    ca.cell_shift = da.seg_pixels == 4096 ? 2 : 1;
+    ca.first_slot = 0;
+    if (e == hipSuccess) e = launch_refine(cols, ca, batch, compute, L.maps.dp, s);
+    return e;
 }
 
 #define FNN_TRY(expr)                        \
@@ -402,7 +484,7 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
         most = cv.used;
         // the queries' own rows, or their whole map, whichever the call may need
         for (int listed = 0; listed < 2; ++listed) {
-            if (!nearest_coarse_searches(batch, n, m, n_queries, listed != 0, compute, dp, l2)) continue;
+            if (!nearest_coarse_searches(batch, n, m, n_queries, listed != 0, compute, dp, d, l2)) continue;
             Carver with = cv;
             carve_coarse(with, batch, listed ? n_queries : n, m, false, n_queries, 1);
             if (with.used > most) most = with.used;
@@ -411,13 +493,15 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
     {
         Carver cv{nullptr, 0};
         carve_recip(cv, batch, n, m, de, n_queries, compute);
-        if (recip_coarse_searches(batch, n, m, n_queries, compute, dp, l2))
+        if (recip_coarse_searches(batch, n, m, n_queries, compute, dp, d, l2))
             carve_coarse(cv, batch, n, m, true, n_queries, RECIP_COARSE_SEARCHES);
         if (cv.used > most) most = cv.used;
     }
     {
         Carver cv{nullptr, 0};
         carve_dense(cv, batch, n, m, de, compute);
+        if (n <= MAX_DENSE_PIXELS && m <= MAX_DENSE_PIXELS && dense_coarse_gain(n, m, batch, compute, dp, d, l2) > 0.0)
+            carve_dense_coarse(cv, batch, n, m);
         if (cv.used > most) most = cv.used;
     }
     return most + WS_ALIGN;
@@ -475,7 +559,7 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
     const bool listed = list_queries(q_idx, nq, n);
     CoarseLayout C = carve_coarse(cv, batch, listed ? nq : n, m, false, nq, 1);
     const bool coarse = !nq_active && cv.used <= workspace_bytes &&
-                        nearest_coarse_searches(batch, n, m, nq, listed, opts->compute, L.maps.dp, (opts->flags & FNN_FLAG_L2) != 0);
+                        nearest_coarse_searches(batch, n, m, nq, listed, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0);
     const bool raw = coarse && raw_options(opts) && raw_rows(batch, src) && raw_rows(batch, tgt);
     const bool prepared = raw || (coarse && direct1 && direct2);  // the quantise launch is the first, and takes the side jobs
     if (!prepared) FNN_TRY(prep_both(batch, src, tgt, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
@@ -496,8 +580,8 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (prepared) qa.extra = extra;
-        fill_quantise_side(qa.side[0], batch, src, raw, p1, bs1, L.maps.n_pad, 0, C.map[0]);
-        fill_quantise_side(qa.side[1], batch, tgt, raw, p2, bs2, L.maps.m_pad, 1, C.map[1]);
+        fill_quantise_side(qa.side[0], batch, src, raw, p1, bs1, L.maps.n_pad, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, tgt, raw, p2, bs2, L.maps.m_pad, C.map[1]);
         if (listed) {
             qa.side[0].gather = q_idx;
             qa.side[0].gather_rows = n;
@@ -510,6 +594,7 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
         }
         qa.batch = batch;
         qa.raw_rows = raw ? 1 : 0;
+        qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = C.lower_count;
         qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
@@ -671,7 +756,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
                                   first_search_applies(n_seeds, m, batch));
     // ... and large ones run in two steps, the first in 8 bits, where the workspace has the room
     CoarseLayout C = carve_coarse(cv, batch, n, m, true, n_seeds, RECIP_COARSE_SEARCHES);
-    const int coarse_searches = walk || cv.used > workspace_bytes ? 0 : recip_coarse_searches(batch, n, m, n_seeds, compute, L.maps.dp,
+    const int coarse_searches = walk || cv.used > workspace_bytes ? 0 : recip_coarse_searches(batch, n, m, n_seeds, compute, L.maps.dp, d,
                                                                                               (opts->flags & FNN_FLAG_L2) != 0);
     const bool coarse = coarse_searches > 0;
     const bool raw = coarse && raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
@@ -681,10 +766,11 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (prepared) qa.extra = extra;
-        fill_quantise_side(qa.side[0], batch, d1, raw, p1, bs1, L.maps.n_pad, 0, C.map[0]);
-        fill_quantise_side(qa.side[1], batch, d2, raw, p2, bs2, L.maps.m_pad, 1, C.map[1]);
+        fill_quantise_side(qa.side[0], batch, d1, raw, p1, bs1, L.maps.n_pad, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, raw, p2, bs2, L.maps.m_pad, C.map[1]);
         qa.batch = batch;
         qa.raw_rows = raw ? 1 : 0;
+        qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = RECIP_COARSE_SEARCHES * C.lower_count;
         qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
@@ -858,7 +944,14 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
     memset(&extra, 0, sizeof(extra));
     extra.zero_ptr = L.row_keys;  // both key tables and the bucket counters start empty
     extra.zero_count = L.zero_words;
-    if (n > 0 && m > 0) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, true));
+    DenseFinalArgs fa;
+    fa.n = (int32_t)n;
+    fa.m = (int32_t)m;
+    fa.nn12 = nn12;
+    fa.nn21 = nn21;
+    fa.pairs = pairs;
+    fa.n_pairs = n_pairs;
+    fa.block_counts = L.block_counts;
 
     DenseArgs da;
     memset(&da, 0, sizeof(da));
@@ -881,6 +974,28 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
     da.lists = L.lists;
     da.chunk_unit = L.chunk_unit;
     da.chunk_totals = L.chunk_totals;
+
+    // Large maps: 8-bit scores first, then, where the workspace has the room, the second step of the searches in both directions
+    DenseCoarseLayout C = carve_dense_coarse(cv, batch, n, m);
+    if (cv.used <= workspace_bytes && dense_coarse_gain(n, m, batch, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0) > 0.0) {
+        const bool raw = raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
+        if (!raw) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra));
+        QuantiseArgs qa;
+        memset(&qa, 0, sizeof(qa));
+        if (raw) qa.extra = extra;
+        fill_quantise_side(qa.side[0], batch, d1, raw, (const char*)L.maps.p1, L.maps.bstride1, L.maps.n_pad, C.args.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
+        qa.batch = batch;
+        qa.raw_rows = raw ? 1 : 0;
+        qa.seg_pixels = C.args.seg_pixels;
+        qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
+        FNN_TRY(launch_quantise(qa, opts->compute, L.maps.dp, s));
+        FNN_TRY(dense_two_steps(C, L, batch, n, m, opts->compute, s));
+        FNN_TRY(launch_dense_resolve(da, batch, opts->compute, L.maps.dp, nn12, s12, nn21, s21, s));
+        FNN_TRY(launch_dense_final(fa, batch, s));
+        return FNN_OK;
+    }
+    if (n > 0 && m > 0) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, true));
     // Workgroup tile: one query super-block (32 KB of LDS keys) x up to 8 candidate groups (of
     // DENSE_WAVES x DENSE_J tiles).  Larger tiles mean fewer merges into the global key
     // tables; small problems shrink the tile until the grid covers the chip a few times.
@@ -897,14 +1012,6 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
     else if (n > 0) FNN_TRY(launch_fill_i32f32(nn12, s12, (int64_t)batch * n, s));
     else if (m > 0) FNN_TRY(launch_fill_i32f32(nn21, s21, (int64_t)batch * m, s));
 
-    DenseFinalArgs fa;
-    fa.n = (int32_t)n;
-    fa.m = (int32_t)m;
-    fa.nn12 = nn12;
-    fa.nn21 = nn21;
-    fa.pairs = pairs;
-    fa.n_pairs = n_pairs;
-    fa.block_counts = L.block_counts;
     FNN_TRY(launch_dense_final(fa, batch, s));
     if (n == 0 && m == 0) {
         // no kernel ran: n_pairs still has to be defined

@@ -17,6 +17,7 @@
 // no part in the 8-bit scores: their bounds are so wide that they are always refined.
 #include <type_traits>
 
+#include "coarse_device.hpp"
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
 #include "query_rows.hpp"
@@ -24,9 +25,6 @@
 #include "trace.hpp"
 
 namespace fnn {
-
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x16 __attribute__((ext_vector_type(16)));
 
 // ---- the 8-bit maps ------------------------------------------------------------------------------
 constexpr float ROUNDING = 2e-5f;          // of a row's length, on top of its remainder
@@ -40,29 +38,21 @@ constexpr float F16_SMALL_LENGTH = 6.1e-4f;
 
 __device__ __forceinline__ uint32_t bf16_up(float x) { return (__float_as_uint(x) + 0xFFFFu) >> 16; }  // x >= 0
 
-// The channels of a prepared row as fp32 numbers.  SPLIT: the descriptor hi + lo of a two-term row; its score leaves out
-// the products lo * lo, at most 2^-22 of |a| |b|.
+// The channels of a prepared row as fp32 numbers.  SPLIT: the high halves of a two-term row's descriptor, which stand in for
+// it: what the low halves add, at most 2^-11 of it, joins the remainder (LOW_HALVES), and so does the product of two
+// low halves that the score leaves out.
+constexpr float LOW_HALVES = 5.2e-4f;
 template <int CT, int DP, bool SPLIT>
 struct PreparedRow {
     static constexpr int CHANNELS = SPLIT ? FNN_MAX_D : DP;
-    static __device__ __forceinline__ void load(const char* row, int d, int lo_copy, float (&x)[CHANNELS]) {
+    static __device__ __forceinline__ void load(const char* row, int d, float (&x)[CHANNELS]) {
         if constexpr (SPLIT) {
-            if (d % 8 == 0) {  // uniform
 #pragma unroll
-                for (int g = 0; g < CHANNELS / 8; ++g) {
-                    const bool in = 8 * g < d;
-                    f16x8 hi = {0, 0, 0, 0, 0, 0, 0, 0}, lo = hi;
-                    if (in) {
-                        hi = *reinterpret_cast<const f16x8*>(row + 16 * g);
-                        lo = *reinterpret_cast<const f16x8*>(row + 2 * lo_copy * d + 16 * g);
-                    }
+            for (int g = 0; g < CHANNELS / 8; ++g) {
+                f16x8 hi = {0, 0, 0, 0, 0, 0, 0, 0};
+                if (8 * g < d) hi = *reinterpret_cast<const f16x8*>(row + 16 * g);  // uniform; rows hold 3 d channels
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[8 * g + e] = (float)hi[e] + (float)lo[e];
-                }
-            } else {
-                const _Float16* e = reinterpret_cast<const _Float16*>(row);
-#pragma unroll
-                for (int k = 0; k < CHANNELS; ++k) x[k] = k < d ? (float)e[k] + (float)e[lo_copy * d + k] : 0.0f;
+                for (int e = 0; e < 8; ++e) x[8 * g + e] = 8 * g + e < d ? (float)hi[e] : 0.0f;
             }
         } else if constexpr (CT == CT_F32) {
 #pragma unroll
@@ -97,20 +87,19 @@ __device__ __forceinline__ float workgroup_max(float x, float* word) {  // x >= 
     return *word;
 }
 
-// One workgroup turns one segment of prepared rows into 8-bit rows, a thread QUANTISE_ROWS of them, held in registers between
-// the segment's largest value and the rounding.  RAW: the rows are the caller's fp32 rows of 24 channels; they are
-// rounded to the compute format here and the prepared map is written too.  Bound by memory.
-constexpr int QUANTISE_THREADS = 512;
-constexpr int QUANTISE_ROWS = SEG_PIXELS / QUANTISE_THREADS;
-template <int CT, int DP, bool SPLIT, bool RAW>
-__global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs a) {
+// One workgroup turns one segment of prepared rows into 8-bit rows, a thread ROWS of them.  Between the segment's largest value
+// and the rounding the rows stay in registers, or, where they are too many (RELOAD), are read a second time.
+// RAW: the rows are the caller's fp32 rows of 24 channels; they are rounded to the compute format here and the
+// prepared map is written too.  Bound by memory.
+template <int CT, int DP, bool SPLIT, bool RAW, int THREADS, int ROWS, bool RELOAD>
+__global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
     using Row = PreparedRow<CT, DP, SPLIT>;
-    constexpr int K = Row::CHANNELS;
+    constexpr int K = Row::CHANNELS, SEGMENT = THREADS * ROWS, KEPT = RELOAD ? 1 : ROWS;
     __shared__ float top[4];  // largest value, remainder, length, and whether a row has no bound
     side_jobs(a.extra, a.batch);
     {
-        const int64_t tid = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * QUANTISE_THREADS + threadIdx.x;
-        const int64_t n_threads = (int64_t)gridDim.x * gridDim.y * QUANTISE_THREADS;
+        const int64_t tid = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * THREADS + threadIdx.x;
+        const int64_t n_threads = (int64_t)gridDim.x * gridDim.y * THREADS;
         for (int64_t i = tid; i < a.lower_count; i += n_threads) a.lower[i] = 0;
     }
     const QuantiseSide& sd = a.side[blockIdx.y / a.batch];
@@ -120,12 +109,11 @@ __global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs
     __syncthreads();
 
     const char* prepared = sd.prepared + (int64_t)b * sd.bstride;
-    float x[QUANTISE_ROWS][K];
-    float square[QUANTISE_ROWS], largest = 0.0f;
-    bool bounded[QUANTISE_ROWS];
-#pragma unroll
-    for (int i = 0; i < QUANTISE_ROWS; ++i) {
-        const int64_t pixel = (int64_t)seg * SEG_PIXELS + i * QUANTISE_THREADS + threadIdx.x;
+    float x[KEPT][K], square[KEPT];
+    bool bounded[KEPT];
+    // row i of this thread into x[at]: its values, their squares' sum, and whether the bounds hold for it; returns its largest value
+    auto read = [&](int i, int at, bool write) -> float {
+        const int64_t pixel = (int64_t)seg * SEGMENT + i * THREADS + threadIdx.x;
         int64_t row = min(pixel, sd.n - 1);  // rows past the map repeat its last one, whose scores are real
         if (sd.gather) row = min(max((int64_t)sd.gather[(int64_t)b * sd.n + row], (int64_t)0), sd.gather_rows - 1);
         if constexpr (RAW) {
@@ -138,7 +126,7 @@ __global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs
                 w[2 * q] = round_pair<CT>(v.x, v.y);
                 w[2 * q + 1] = round_pair<CT>(v.z, v.w);
             }
-            if (pixel < sd.n_pad) {
+            if (write && pixel < sd.n_pad) {
                 uint4* out = reinterpret_cast<uint4*>(const_cast<char*>(prepared) + pixel * O::ROW_BYTES);
                 const bool real = pixel < sd.n;  // padding rows of the prepared map are zero
 #pragma unroll
@@ -148,24 +136,32 @@ __global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs
 #pragma unroll
             for (int k = 0; k < 24; ++k) {
                 const uint32_t bits = (w[k / 2] >> (16 * (k & 1))) & 0xFFFFu;
-                x[i][k] = CT == CT_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits) : __uint_as_float(bits << 16);
+                x[at][k] = CT == CT_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits) : __uint_as_float(bits << 16);
             }
         } else {
             constexpr int ROW_BYTES = DP * (CT == CT_F32 ? 4 : 2);
-            Row::load(prepared + row * ROW_BYTES, a.split_d, sd.second_image ? 1 : 2, x[i]);
+            Row::load(prepared + row * ROW_BYTES, a.split_d, x[at]);
         }
         float most = 0.0f, sum = 0.0f;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            most = __builtin_fmaxf(most, __builtin_fabsf(x[i][k]));
-            sum = __builtin_fmaf(x[i][k], x[i][k], sum);
+            most = __builtin_fmaxf(most, __builtin_fabsf(x[at][k]));
+            sum = __builtin_fmaf(x[at][k], x[at][k], sum);
         }
-        square[i] = sum;
+        square[at] = sum;
         // compared as integers, which puts a sum that is not a number past the largest
         const uint32_t bits = __float_as_uint(sum) & 0x7FFFFFFFu;
-        bounded[i] = (bits == 0 && __float_as_uint(most) == 0) ||
-                     (bits >= __float_as_uint(LEAST_SQUARE) && bits <= __float_as_uint(LARGEST_SQUARE));
-        if (bounded[i]) largest = __builtin_fmaxf(largest, most);
+        bounded[at] = (bits == 0 && __float_as_uint(most) == 0) ||
+                      (bits >= __float_as_uint(LEAST_SQUARE) && bits <= __float_as_uint(LARGEST_SQUARE));
+        return bounded[at] ? most : 0.0f;
+    };
+    float largest = 0.0f;
+    if constexpr (RELOAD) {
+#pragma unroll 1
+        for (int i = 0; i < ROWS; ++i) largest = __builtin_fmaxf(largest, read(i, 0, true));
+    } else {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) largest = __builtin_fmaxf(largest, read(i, i, true));
     }
     largest = workgroup_max(largest, &top[0]);
     const float scale = largest * (1.0f / 127.0f);
@@ -173,10 +169,9 @@ __global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs
     const float small = CT == CT_F16 && scale < 2.0f * F16_SMALL ? F16_SMALL_LENGTH : 0.0f;
 
     float residual = 0.0f, length = 0.0f, unbounded = 0.0f;
-    const int64_t first = ((int64_t)b * sd.out.n_segs + seg) * SEG_PIXELS;
-#pragma unroll
-    for (int i = 0; i < QUANTISE_ROWS; ++i) {
-        const int64_t out_row = first + i * QUANTISE_THREADS + threadIdx.x;
+    const int64_t first = ((int64_t)b * sd.out.n_segs + seg) * SEGMENT;
+    auto write = [&](int i, int at) {
+        const int64_t out_row = first + i * THREADS + threadIdx.x;
         // x / scale is rounded to the nearest integer by adding 1.5 * 2^23, which leaves it in the low bits; an unbounded row's
         // integers mean nothing
         constexpr float INTEGER = 12582912.0f;
@@ -189,7 +184,7 @@ __global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs
             for (int e = 0; e < 4; ++e) {
                 const int k = 4 * w + e;
                 if (k < K) {
-                    const float v = x[i][k < K ? k : 0];
+                    const float v = x[at][k < K ? k : 0];
                     const float t = __builtin_fmaf(v, inverse, INTEGER);
                     const float r = __builtin_fmaf(-scale, t - INTEGER, v);
                     left = __builtin_fmaf(r, r, left);
@@ -199,10 +194,11 @@ __global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs
             const uint32_t low = __builtin_amdgcn_perm(q[1], q[0], 0x0C0C0400u);  // bytes (0 0 q1 q0)
             words[w] = __builtin_amdgcn_perm(q[3], __builtin_amdgcn_perm(q[2], low, 0x0C040100u), 0x04020100u);
         }
-        const float len = __builtin_sqrtf(square[i]) * (1.0f + 1e-5f);
-        const float rest = __builtin_sqrtf(left) * (1.0f + 1e-5f) + ROUNDING * len + small;
+        constexpr float LOW = SPLIT ? LOW_HALVES : 0.0f;
+        const float len = __builtin_sqrtf(square[at]) * (1.0f + 1e-5f + LOW);
+        const float rest = __builtin_sqrtf(left) * (1.0f + 1e-5f) + (ROUNDING + LOW) * len + small;
         uint32_t bound = bf16_up(UNBOUNDED) | (bf16_up(UNBOUNDED) << 16);
-        if (bounded[i]) {
+        if (bounded[at]) {
             residual = __builtin_fmaxf(residual, rest);
             length = __builtin_fmaxf(length, len);
             const float per_scale = scale > 0.0f ? 1.0f / scale : 0.0f;  // a segment of zero rows: every score is 0
@@ -214,6 +210,16 @@ __global__ __launch_bounds__(QUANTISE_THREADS) void quantise_kernel(QuantiseArgs
         out[0] = make_uint4(words[0], words[1], words[2], words[3]);
         out[1] = make_uint4(words[4], words[5], words[6], words[7]);
         sd.out.row_bound[out_row] = bound;
+    };
+    if constexpr (RELOAD) {
+#pragma unroll 1
+        for (int i = 0; i < ROWS; ++i) {
+            (void)read(i, 0, false);
+            write(i, 0);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) write(i, i);
     }
     residual = workgroup_max(residual, &top[1]);
     length = workgroup_max(length, &top[2]);
@@ -234,22 +240,6 @@ __device__ __forceinline__ int64_t take_slots_from(SearchArgs& a, int first) {
 }
 
 // ---- step 1 ------------------------------------------------------------------------------------
-constexpr int COARSE_WAVES = 4;  // waves per workgroup
-constexpr int COARSE_TURN = 8;   // candidate tiles staged per turn, two per wave
-constexpr int TILE_BYTES = 32 * COARSE_ROW_BYTES;
-
-#define FNN_LDS_PTR(p) ((void __attribute__((address_space(3)))*)(p))
-
-__device__ __forceinline__ int max3i(int a, int b, int c) { return max(max(a, b), c); }
-__device__ __forceinline__ int fold16i(int seed, const i32x16& x) {
-    const int t0 = max3i(x[0], x[1], x[2]);
-    const int t1 = max3i(x[3], x[4], x[5]);
-    const int t2 = max3i(x[6], x[7], x[8]);
-    const int t3 = max3i(x[9], x[10], x[11]);
-    const int t4 = max3i(x[12], x[13], x[14]);
-    return max3i(seed, max3i(t0, t1, t2), max3i(t3, t4, x[15]));
-}
-
 // The four waves of a workgroup hold PAIRS pairs of query blocks each and sweep the same tiles, which reach LDS by direct loads
 // (a tile is 1 KB: one 16-byte load per lane), the next turn's while this turn's are multiplied.
 // Bound by the vector maxima and the matrix instructions, which take about the same time each.
@@ -347,9 +337,7 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
 #pragma unroll
                 for (int p = 0; p < PAIRS; ++p) {
                     if (__builtin_expect(live[p], 1)) {
-                        const i32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                        const i32x16 even = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur, q[p][0], zero, 0, 0, 0);
-                        const i32x16 odd = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur, q[p][1], zero, 0, 0, 0);
+                        const i32x16 even = product8(cur, q[p][0]), odd = product8(cur, q[p][1]);
                         best[p][0] = fold16i(best[p][0], even);
                         best[p][1] = fold16i(best[p][1], odd);
                     }
@@ -392,7 +380,7 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
 }
 
 // ---- step 2 ------------------------------------------------------------------------------------
-// A workgroup owns one segment and a range of the queries: the segment's tiles stay in registers, RT per wave, and the
+// A workgroup owns one cell (or a part of one) and a range of the queries: its tiles stay in registers, RT per wave, and the
 // queries that need it are collected in LDS and streamed past them, 32 at a time.
 template <int CT, int DP>
 constexpr int refine_tiles() { return Ops<CT, DP>::ROW_BYTES / 8 <= 8 ? 8 : 4; }  // a tile is ROW_BYTES / 8 registers
@@ -403,12 +391,14 @@ constexpr int REFINE_LIST = REFINE_SCAN + 1024;
 constexpr int REFINE_PART = 512;               // a multiple of 32
 constexpr int REFINE_RANGE = 4 * REFINE_SCAN;  // queries of a workgroup
 
-template <int CT, int DP, int RT, int WAVES>
+// MASK: which queries need a cell is read from a table of bits; the keys name units of DENSE_J tiles instead of tiles.
+template <int CT, int DP, int RT, int WAVES, bool MASK>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(refine_waves<CT, DP>())))
 void refine_kernel(SearchArgs a, CoarseArgs ca) {
     using O = Ops<CT, DP>;
     using Frag = typename O::Frag;
-    constexpr int THREADS = 64 * WAVES, PER = REFINE_SCAN / THREADS;
+    constexpr int THREADS = 64 * WAVES, PER = REFINE_SCAN / THREADS, UNIT = MASK ? DENSE_J : 1;
+    static_assert(RT % UNIT == 0, "a wave holds whole units");
     __shared__ int list_row[REFINE_LIST];        // queries that need this segment: their rows,
     __shared__ uint16_t list_slot[REFINE_LIST];  // and their slots in the workgroup's range
     __shared__ u64 keys[REFINE_PART];            // what the waves found for REFINE_PART of them
@@ -429,7 +419,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     const char* src = a.src + (int64_t)b * a.src_bstride + take_slots_from(a, ca.first_slot) * O::ROW_BYTES;
     const int64_t qbase = (int64_t)b * a.nq + ca.first_slot;
     const float ninf = -__builtin_inff();
-    const uint16_t* upper = ca.upper + ((int64_t)b * gridDim.x + cell) * ca.slab;
+    const uint16_t* upper = ca.upper + ((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab;
     const uint32_t* lower = ca.lower + (int64_t)b * ca.slot_pitch + ca.first_slot;
     Frag cand[RT];
 #pragma unroll
@@ -443,7 +433,11 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
         const int slot = base + (int)threadIdx.x * PER;
         uint32_t need = 0;
         if (slot < n_act) {
-            if (every) {
+            if constexpr (MASK) {
+                static_assert(PER <= 16, "a thread's bits lie in one 16-bit word");
+                const int64_t word = (((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab + slot) / 16;
+                need = (uint32_t)reinterpret_cast<const uint16_t*>(ca.mask)[word] >> (slot & 15) & ((1u << PER) - 1);
+            } else if (every) {
                 need = (1u << PER) - 1;
             } else {
                 // the tables' rows hold whole 64s of slots: all PER are there
@@ -492,30 +486,36 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
                     const Frag q = next;
                     next = O::load(src + (int64_t)list_row[min(first + 32 + c, n - 1)] * O::ROW_BYTES, h);
                     float best = ninf;
-                    int best_tile = 0x7FFFFFFF;
+                    int best_unit = 0x7FFFFFFF;
                     int bound = a.m - tile0 * 32 - 4 * h;
                     if (TAIL) asm volatile("" : "+v"(bound));  // else its comparisons are kept from block to block
 #pragma unroll
-                    for (int j = 0; j < RT; ++j) {
-                        f32x16 acc = O::mma(cand[j], q);
-                        if (TAIL) {
+                    for (int u = 0; u < RT; u += UNIT) {
+                        float top = best;
 #pragma unroll
-                            for (int v = 0; v < 16; ++v)
-                                if (32 * j + tile_row(v, 0) >= bound) acc[v] = ninf;
+                        for (int j = u; j < u + UNIT; ++j) {
+                            f32x16 acc = O::mma(cand[j], q);
+                            if (TAIL) {
+#pragma unroll
+                                for (int v = 0; v < 16; ++v)
+                                    if (32 * j + tile_row(v, 0) >= bound) acc[v] = ninf;
+                            }
+                            top = fold16(top, acc);
+                            // more than two products in flight cost registers, that is resident waves
+                            if (UNIT > 1 && (j & 1)) {
+                                asm volatile("" : "+v"(top));
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
                         }
-                        const float top = fold16(best, acc);
-                        if (top > best) best_tile = tile0 + j;
+                        if (top > best) best_unit = (tile0 + u) / UNIT;
                         best = top;
-                        // more than two products in flight cost registers, that is resident waves
-                        if (j & 1) __builtin_amdgcn_sched_barrier(0);
+                        if (UNIT == 1 && (u & 1)) {
+                            asm volatile("" : "+v"(best));
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
-                    const float ob = __shfl_xor(best, 32);
-                    const int ot = __shfl_xor(best_tile, 32);
-                    if (ob > best || (ob == best && ot < best_tile)) {
-                        best = ob;
-                        best_tile = ot;
-                    }
-                    if (h == 0 && first + c < n) atomicMax(&keys[first - part + c], pack_key(best, best_tile));
+                    // both halves of the wave file what they found
+                    if (first + c < n) atomicMax(&keys[first - part + c], pack_key(best, best_unit));
                 }
             };
             for (int part = 0; part < n; part += REFINE_PART) {  // uniform
@@ -539,7 +539,11 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
 template <int CT, int DP, bool SPLIT, bool RAW>
 static hipError_t launch_quantise_t(const QuantiseArgs& a, hipStream_t s) {
     const int segs = a.side[0].out.n_segs > a.side[1].out.n_segs ? a.side[0].out.n_segs : a.side[1].out.n_segs;
-    return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW>, dim3(segs, 2 * a.batch), dim3(QUANTISE_THREADS), 0, s, a);
+    const dim3 grid(segs, 2 * a.batch);
+    if (a.seg_pixels == 4096) return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW, 1024, 4, true>, grid, dim3(1024), 0, s, a);
+    if (a.seg_pixels == 2048) return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW, 1024, 2, false>, grid, dim3(1024), 0, s, a);
+    if (a.seg_pixels != SEG_PIXELS) return hipErrorInvalidValue;
+    return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW, 512, SEG_PIXELS / 512, false>, grid, dim3(512), 0, s, a);
 }
 hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream_t s) {
     if (a.raw_rows) {
@@ -547,6 +551,8 @@ hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream
         return launch_quantise_t<CT_BF16, 24, false, true>(a, s);
     }
     if (a.split_d) {
+        if (dp == 24) return launch_quantise_t<CT_F16, 24, true, false>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_F16, 32, true, false>(a, s);
         if (dp == 48) return launch_quantise_t<CT_F16, 48, true, false>(a, s);
         if (dp == 64) return launch_quantise_t<CT_F16, 64, true, false>(a, s);
         if (dp == 80) return launch_quantise_t<CT_F16, 80, true, false>(a, s);
@@ -571,15 +577,24 @@ hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream
 // 512x384 pair of fp16 products, 263 us in one step, 274 in two).
 constexpr double BYTES_PER_NS = 4500.0;  // what the passes over the maps reach
 static int coarse_row_bytes(int compute, int dp) { return dp * elem_size(compute); }
-double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, bool l2) {
+// Cells that a slot is multiplied with again: 4 of 1024 pixels for unit rows of 16 channels and more, however large the map; with few
+// channels, a share of the map (of 96 segments 5.3, 6.6, 10, 28 and 89 at 12, 10, 8, 6 and 4 channels).  FNN_FLAG_L2 has
+// wider bounds, because its norm terms are multiplied by channels of ones (20 of 96, 29 of 192; 47 and 77 of 96 at 8 and 6).
+double coarse_cells_again(double cells, int d, bool l2) {
+    const double few = (l2 ? 8.0 : 6.0) / d;
+    const double again = (l2 ? 32.0 : 5.0) + 0.26 * few * few * few * few * cells;
+    return again < cells ? again : cells;
+}
+double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, int d, bool l2) {
     const bool cheap = compute != FNN_F32 && dp <= 32;
     // rows of 16 channels take one matrix instruction per block as it is
     if (m < 16 * SEG_PIXELS || nq > 0x7FFFFFFF / 2 || (cheap && dp <= 16)) return -1e30;
+    if (batch * m > (int64_t)1 << 26) return -1e30;  // the tables of bounds would pass 1 GB
     // what a block of 32x32 scores takes one SIMD in search_kernel, and in coarse_kernel
     const double exact = compute == FNN_F32 ? 18.75 * dp : (cheap ? 46.0 : 1.64 * dp), coarse = 28.0;
     const double blocks = (double)batch * ((nq + 31) / 32) * ((m + 31) / 32) / 1024.0;
-    // segments that a query is multiplied with again.  FNN_FLAG_L2 has wide bounds: its norm terms are multiplied by channels of ones.
-    const double again = (l2 ? 32.0 : 5.0) * SEG_PIXELS / m;
+    // (the second step runs at two thirds of search_kernel's rate)
+    const double segments = (double)m / SEG_PIXELS, again = 1.5 * coarse_cells_again(segments, d, l2) / segments;
     return blocks * (exact * (1.0 - again) - coarse) - 5000.0 - (double)batch * m * coarse_row_bytes(compute, dp) / BYTES_PER_NS;
 }
 double coarse_cost(int64_t rows, int compute, int dp) {
@@ -621,17 +636,20 @@ static hipError_t launch_coarse_t(const SearchArgs& a, const CoarseArgs& ca, int
     if (wgs == 0) return hipErrorUnknown;
     return launch_detail(TK_COARSE, PAIRS * 2, coarse_kernel<PAIRS, CELL>, dim3(wgs, batch), dim3(COARSE_WAVES * 64), 0, s, a, ca);
 }
-template <int CT, int DP, int CELL>
+// CELL: tiles of a workgroup.
+template <int CT, int DP, int CELL, bool MASK = false>
 static hipError_t launch_refine_t(const SearchArgs& a, const CoarseArgs& ca, int batch, hipStream_t s) {
     constexpr int RT = refine_tiles<CT, DP>() * CELL / SEG_TILES, WAVES = CELL / RT;
     const int64_t slots = a.nq - ca.first_slot < ca.slab ? a.nq - ca.first_slot : ca.slab;
     const unsigned ranges = (unsigned)((slots + REFINE_RANGE - 1) / REFINE_RANGE);
-    return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES>, dim3(ca.tgt.n_segs * (SEG_TILES / CELL), ranges, batch), dim3(64 * WAVES), 0, s, a, ca);
+    return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES, MASK>, dim3((a.m_tiles + CELL - 1) / CELL, ranges, batch), dim3(64 * WAVES), 0, s, a, ca);
 }
 template <int CT, int DP>
 static hipError_t launch_both_t(const SearchArgs& a, CoarseArgs ca, int batch, hipStream_t s) {
     const int pairs = (a.nq + 63) / 64;
     const bool half = coarse_cells(a.nq, ca.tgt.n_segs, batch) == 2;
+    ca.n_cells = ca.tgt.n_segs * (half ? 2 : 1);
+    ca.cell_shift = 0;
     // The more query blocks a wave holds, the fewer times a tile is read (every pixel of a 512x384 pair: 12 blocks 1064 us, 16 blocks
     // 992); three quads of 12 deal 16 pairs' 96 blocks evenly, where three of 16 leave waves idle (279 and 290 us).
     const bool six = pairs % 32 != 0 && pairs % 24 == 0;
@@ -662,6 +680,27 @@ hipError_t launch_coarse_search(const SearchArgs& a, const CoarseArgs& ca, int b
         if (dp == 16) return launch_both_t<CT_F32, 16>(a, ca, batch, s);
         if (dp == 24) return launch_both_t<CT_F32, 24>(a, ca, batch, s);
         if (dp == 32) return launch_both_t<CT_F32, 32>(a, ca, batch, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_refine(const SearchArgs& a, const CoarseArgs& ca, int batch, int compute, int dp, hipStream_t s) {
+    if (a.nq <= 0 || batch <= 0) return hipSuccess;
+    if (compute == FNN_F16) {
+        if (dp == 24) return launch_refine_t<CT_F16, 24, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 32) return launch_refine_t<CT_F16, 32, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 48) return launch_refine_t<CT_F16, 48, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 64) return launch_refine_t<CT_F16, 64, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 80) return launch_refine_t<CT_F16, 80, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 96) return launch_refine_t<CT_F16, 96, SEG_TILES, true>(a, ca, batch, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 24) return launch_refine_t<CT_BF16, 24, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 32) return launch_refine_t<CT_BF16, 32, SEG_TILES, true>(a, ca, batch, s);
+    } else {
+        if (dp == 8) return launch_refine_t<CT_F32, 8, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 16) return launch_refine_t<CT_F32, 16, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 24) return launch_refine_t<CT_F32, 24, SEG_TILES, true>(a, ca, batch, s);
+        if (dp == 32) return launch_refine_t<CT_F32, 32, SEG_TILES, true>(a, ca, batch, s);
     }
     return hipErrorInvalidValue;
 }

@@ -667,10 +667,27 @@ __global__ __launch_bounds__(BUCKET_THREADS) void dense_bucket_fill_kernel(Dense
 // Lane c holds query list[c]; result register v of lane (c, h) for tile jt is that query's
 // score against candidate (tbase + jt)*32 + tile_row(v, h), so the lowest index at the
 // maximum is found inside the lane (registers ascend with the candidate) and across its
-// two halves.
-template <int CT, int DP>
+// two halves.  NATURAL: the queries' map is stored in natural order.
+struct ResolveSide {
+    const char* queries;
+    int64_t q_bstride;
+    int32_t n;
+    const char* candidates;
+    int64_t c_bstride;
+    int32_t m, m_tiles;
+    const int32_t* list;        // the side's part of pair 0, and the strides from pair to pair
+    const int32_t* chunk_unit;
+    const int32_t* cursor;
+    int64_t list_stride, chunk_stride, cursor_stride;
+    const int32_t* total;       // chunks of pair 0; two words per pair
+    int64_t cap;
+    int32_t units;
+    int32_t* idx;               // [batch][n]
+    float* score;               // [batch][n] or NULL
+};
+template <int CT, int DP, bool NATURAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-void dense_resolve_rows_kernel(DenseArgs a, int32_t* nn12, float* s12) {
+void dense_resolve_rows_kernel(ResolveSide a) {
     using O = Ops<CT, DP>;
     using Frag = typename O::Frag;
     constexpr int J = DENSE_J;
@@ -678,18 +695,19 @@ void dense_resolve_rows_kernel(DenseArgs a, int32_t* nn12, float* s12) {
     const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_waves = gridDim.x * 4;
     const int b = blockIdx.y;
-    const char* d1 = a.d1 + (int64_t)b * a.d1_bstride;
-    const char* d2 = a.d2 + (int64_t)b * a.d2_bstride;
-    const int32_t* list = a.lists + (int64_t)b * (a.rows_cap + a.cols_cap);
-    const int32_t* chunk_unit = a.chunk_unit + ((int64_t)b * (a.rows_cap + a.cols_cap)) / 32;
-    const int32_t* cursor = a.unit_cursor + (int64_t)b * (a.row_units + a.col_units);  // after the fill: end of bucket
-    const int total = min(a.chunk_totals[b * 2 + 0], (int)(a.rows_cap / 32));
+    const char* d1 = a.queries + (int64_t)b * a.q_bstride;
+    const char* d2 = a.candidates + (int64_t)b * a.c_bstride;
+    const int32_t* list = a.list + b * a.list_stride;
+    const int32_t* chunk_unit = a.chunk_unit + b * a.chunk_stride;
+    const int32_t* cursor = a.cursor + b * a.cursor_stride;  // after the fill: end of bucket
+    const int total = min(a.total[b * 2], (int)(a.cap / 32));
     const float ninf = -__builtin_inff();
     for (int w = wave; w < total; w += n_waves) {
-        const int unit = max(0, min(chunk_unit[w], a.row_units - 1));
+        const int unit = max(0, min(chunk_unit[w], a.units - 1));
         const int tbase = unit * J;
         const int i = w * 32 + c < cursor[unit] ? list[(int64_t)w * 32 + c] : -1;  // past the bucket's fill level
-        const Frag q = O::load(d1 + segment_slot(max(0, min(i, a.n - 1))) * O::ROW_BYTES, h);
+        const int64_t pixel = max(0, min(i, a.n - 1));
+        const Frag q = O::load(d1 + (NATURAL ? pixel : segment_slot(pixel)) * O::ROW_BYTES, h);
         f32x16 x[J];
         float top = ninf;
 #pragma unroll
@@ -713,8 +731,8 @@ void dense_resolve_rows_kernel(DenseArgs a, int32_t* nn12, float* s12) {
                 if (x[jt][v] == top) row = jt * 32 + tile_row(v, h);
         row = min(row, __shfl_xor(row, 32));
         if (h == 0 && i >= 0 && i < a.n) {
-            nn12[(int64_t)b * a.n + i] = row < J * 32 ? tbase * 32 + row : -1;
-            if (s12) s12[(int64_t)b * a.n + i] = top;
+            a.idx[(int64_t)b * a.n + i] = row < J * 32 ? tbase * 32 + row : -1;
+            if (a.score) a.score[(int64_t)b * a.n + i] = top;
         }
     }
 }
@@ -858,21 +876,9 @@ __global__ __launch_bounds__(FINAL_THREADS) void dense_scatter_kernel(DenseFinal
     }
 }
 
-template <int CT, int DP>
-static hipError_t launch_dense_t(const DenseArgs& a, int batch, int32_t* nn12, float* s12, int32_t* nn21, float* s21,
-                                 hipStream_t s) {
-    const int groups = (a.m_tiles + DENSE_TILES_PER_GROUP - 1) / DENSE_TILES_PER_GROUP;
-    dim3 grid((groups + a.groups_per_wg - 1) / a.groups_per_wg, (a.n_sb + a.sb_per_wg - 1) / a.sb_per_wg, batch);
-    const size_t lds_bytes = ((size_t)a.sb_per_wg * DENSE_S * 32 + DENSE_WAVES * DENSE_J * 32) * sizeof(u64) +
-                             DENSE_WAVES * 32 * sizeof(float);  // row keys, column keys, 32 maxima per wave
+// The pixels of both images grouped by their winning unit.
+static hipError_t launch_dense_buckets(const DenseArgs& a, int batch, int32_t* nn12, float* s12, int32_t* nn21, float* s21, hipStream_t s) {
     hipError_t e;
-    if constexpr (DENSE_STAGED && CT != CT_F32 && DP == 24) {
-        if (a.sb_per_wg != 1) return hipErrorInvalidValue;  // the staged kernel's key table holds one super-block
-        e = launch_detail(TK_DENSE, 1, dense_staged_kernel<CT>, grid, dim3(DENSE_WAVES * 64), 0, s, a);
-    } else {
-        e = launch(TK_DENSE, dense_kernel<CT, DP>, grid, dim3(DENSE_WAVES * 64), lds_bytes, s, a);
-    }
-    if (e != hipSuccess) return e;
     const int most = a.n > a.m ? a.n : a.m;
     const size_t hist_bytes = ((size_t)a.row_units + a.col_units) * sizeof(int);
     const bool local = hist_bytes <= 64 * 1024;  // the bucket histogram fits in LDS
@@ -891,15 +897,87 @@ static hipError_t launch_dense_t(const DenseArgs& a, int batch, int32_t* nn12, f
     else
         e = launch(TK_DENSE_RESOLVE, dense_bucket_fill_kernel<false>, bucket_grid, dim3(BUCKET_THREADS), 0, s, a, nn12,
                    s12, nn21, s21);
-    if (e != hipSuccess) return e;
+    return e;
+}
+
+static unsigned resolve_wgs(int64_t cap_positions, int batch) {
     const int cap = 4096 / batch > 64 ? 4096 / batch : 64;
-    int wgs = (int)((a.rows_cap / 32 + 3) / 4);
-    if (wgs > cap) wgs = cap;
-    e = launch(TK_DENSE_RESOLVE, dense_resolve_rows_kernel<CT, DP>, dim3(wgs, batch), dim3(256), 0, s, a, nn12, s12);
+    const int wgs = (int)((cap_positions / 32 + 3) / 4);
+    return (unsigned)(wgs > cap ? cap : wgs);
+}
+static ResolveSide row_side(const DenseArgs& a, int32_t* nn12, float* s12) {
+    ResolveSide r;
+    r.queries = a.d1;
+    r.q_bstride = a.d1_bstride;
+    r.n = a.n;
+    r.candidates = a.d2;
+    r.c_bstride = a.d2_bstride;
+    r.m = a.m;
+    r.m_tiles = a.m_tiles;
+    r.list = a.lists;
+    r.chunk_unit = a.chunk_unit;
+    r.cursor = a.unit_cursor;
+    r.list_stride = a.rows_cap + a.cols_cap;
+    r.chunk_stride = r.list_stride / 32;
+    r.cursor_stride = a.row_units + a.col_units;
+    r.total = a.chunk_totals;
+    r.cap = a.rows_cap;
+    r.units = a.row_units;
+    r.idx = nn12;
+    r.score = s12;
+    return r;
+}
+// The candidates of natural maps: the same with the images' places changed.
+static ResolveSide col_side(const DenseArgs& a, int32_t* nn21, float* s21) {
+    ResolveSide r = row_side(a, nn21, s21);
+    r.queries = a.d2;
+    r.q_bstride = a.d2_bstride;
+    r.n = a.m;
+    r.candidates = a.d1;
+    r.c_bstride = a.d1_bstride;
+    r.m = a.n;
+    r.m_tiles = (a.n + 31) / 32;
+    r.list += a.rows_cap;
+    r.chunk_unit += a.rows_cap / 32;
+    r.cursor += a.row_units;
+    r.total += 1;
+    r.cap = a.cols_cap;
+    r.units = a.col_units;
+    return r;
+}
+
+template <int CT, int DP>
+static hipError_t launch_dense_t(const DenseArgs& a, int batch, int32_t* nn12, float* s12, int32_t* nn21, float* s21,
+                                 hipStream_t s) {
+    const int groups = (a.m_tiles + DENSE_TILES_PER_GROUP - 1) / DENSE_TILES_PER_GROUP;
+    dim3 grid((groups + a.groups_per_wg - 1) / a.groups_per_wg, (a.n_sb + a.sb_per_wg - 1) / a.sb_per_wg, batch);
+    const size_t lds_bytes = ((size_t)a.sb_per_wg * DENSE_S * 32 + DENSE_WAVES * DENSE_J * 32) * sizeof(u64) +
+                             DENSE_WAVES * 32 * sizeof(float);  // row keys, column keys, 32 maxima per wave
+    hipError_t e;
+    if constexpr (DENSE_STAGED && CT != CT_F32 && DP == 24) {
+        if (a.sb_per_wg != 1) return hipErrorInvalidValue;  // the staged kernel's key table holds one super-block
+        e = launch_detail(TK_DENSE, 1, dense_staged_kernel<CT>, grid, dim3(DENSE_WAVES * 64), 0, s, a);
+    } else {
+        e = launch(TK_DENSE, dense_kernel<CT, DP>, grid, dim3(DENSE_WAVES * 64), lds_bytes, s, a);
+    }
     if (e != hipSuccess) return e;
-    wgs = (int)((a.cols_cap / 32 + 3) / 4);
-    if (wgs > cap) wgs = cap;
-    return launch(TK_DENSE_RESOLVE, dense_resolve_cols_kernel<CT, DP>, dim3(wgs, batch), dim3(256), 0, s, a, nn21, s21);
+    e = launch_dense_buckets(a, batch, nn12, s12, nn21, s21, s);
+    if (e != hipSuccess) return e;
+    e = launch(TK_DENSE_RESOLVE, dense_resolve_rows_kernel<CT, DP, false>, dim3(resolve_wgs(a.rows_cap, batch), batch), dim3(256), 0, s,
+               row_side(a, nn12, s12));
+    if (e != hipSuccess) return e;
+    return launch(TK_DENSE_RESOLVE, dense_resolve_cols_kernel<CT, DP>, dim3(resolve_wgs(a.cols_cap, batch), batch), dim3(256), 0, s, a, nn21, s21);
+}
+
+template <int CT, int DP>
+static hipError_t launch_dense_resolve_t(const DenseArgs& a, int batch, int32_t* nn12, float* s12, int32_t* nn21, float* s21, hipStream_t s) {
+    hipError_t e = launch_dense_buckets(a, batch, nn12, s12, nn21, s21, s);
+    if (e != hipSuccess) return e;
+    e = launch(TK_DENSE_RESOLVE, dense_resolve_rows_kernel<CT, DP, true>, dim3(resolve_wgs(a.rows_cap, batch), batch), dim3(256), 0, s,
+               row_side(a, nn12, s12));
+    if (e != hipSuccess) return e;
+    return launch(TK_DENSE_RESOLVE, dense_resolve_rows_kernel<CT, DP, true>, dim3(resolve_wgs(a.cols_cap, batch), batch), dim3(256), 0, s,
+                  col_side(a, nn21, s21));
 }
 
 hipError_t launch_dense(const DenseArgs& a, int batch, int compute, int dp, int32_t* nn12, float* s12, int32_t* nn21,
@@ -922,6 +1000,28 @@ hipError_t launch_dense(const DenseArgs& a, int batch, int compute, int dp, int3
         if (dp == 16) return launch_dense_t<CT_F32, 16>(a, batch, nn12, s12, nn21, s21, s);
         if (dp == 24) return launch_dense_t<CT_F32, 24>(a, batch, nn12, s12, nn21, s21, s);
         if (dp == 32) return launch_dense_t<CT_F32, 32>(a, batch, nn12, s12, nn21, s21, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_dense_resolve(const DenseArgs& a, int batch, int compute, int dp, int32_t* nn12, float* s12, int32_t* nn21,
+                        float* s21, hipStream_t s) {
+    if (a.n <= 0 || a.m <= 0 || batch <= 0) return hipSuccess;
+    if (compute == FNN_F16) {
+        if (dp == 24) return launch_dense_resolve_t<CT_F16, 24>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 32) return launch_dense_resolve_t<CT_F16, 32>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 48) return launch_dense_resolve_t<CT_F16, 48>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 64) return launch_dense_resolve_t<CT_F16, 64>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 80) return launch_dense_resolve_t<CT_F16, 80>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 96) return launch_dense_resolve_t<CT_F16, 96>(a, batch, nn12, s12, nn21, s21, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 24) return launch_dense_resolve_t<CT_BF16, 24>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 32) return launch_dense_resolve_t<CT_BF16, 32>(a, batch, nn12, s12, nn21, s21, s);
+    } else {
+        if (dp == 8) return launch_dense_resolve_t<CT_F32, 8>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 16) return launch_dense_resolve_t<CT_F32, 16>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 24) return launch_dense_resolve_t<CT_F32, 24>(a, batch, nn12, s12, nn21, s21, s);
+        if (dp == 32) return launch_dense_resolve_t<CT_F32, 32>(a, batch, nn12, s12, nn21, s21, s);
     }
     return hipErrorInvalidValue;
 }

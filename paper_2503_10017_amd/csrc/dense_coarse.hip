@@ -1,0 +1,274 @@
+// Pass 1 of the dense mode in 8-bit integers: the same sweep as dense_kernel -- every 32x32 block of scores formed once and
+// folded into the best candidate of its queries and the best query of its candidates -- with one matrix
+// instruction per block, nothing located and nothing masked (rows past a map repeat its last one).  What is kept are the
+// maxima per query and cell of candidates and per candidate and segment of queries; bounds on what the 8 bits left out say
+// which cells the second step of the searches (coarse.hip) has to multiply again, in both directions.
+#include <type_traits>
+
+#include "coarse_device.hpp"
+#include "fnn_kernels.hpp"
+#include "trace.hpp"
+
+namespace fnn {
+
+constexpr int DC_J = 4;                                  // candidate tiles resident per wave
+constexpr int DC_GROUP = COARSE_WAVES * DC_J;            // tiles of a workgroup: 512 candidates
+constexpr int DC_TURNS = DENSE_SB_PIXELS / 32 / COARSE_TURN;  // turns of a sweep
+constexpr int DC_STEPS = COARSE_TURN / 2;                // steps of a turn, two query blocks each
+static_assert(DC_TURNS % 2 == 0, "a sweep is an even number of turns, so it starts on stage slot 0");
+constexpr int LOWEST = -0x7FFFFFFF;
+// Maxima are kept as multiples of 16, in 16 bits: at most 128 * 128 * 32 / 16 (a row without bounds may reach one more, whose bound does not care)
+constexpr int KEPT_SHIFT = 4;
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_max_int(int x) { return max(x, __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true)); }
+// transpose_max16 for integers
+__device__ __forceinline__ int transpose_max16_int(const int (&x)[16], int lane) {
+    const int held = held_register(lane);
+    const bool e0 = held & 1, e1 = held & 2, e2 = held & 4, e3 = held & 8;
+    int y8[8], y4[4], y2[2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int even = dpp_max_int<0xB1>(x[2 * k]), odd = dpp_max_int<0xB1>(x[2 * k + 1]);
+        y8[k] = e0 ? odd : even;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int even = dpp_max_int<0x4E>(y8[2 * k]), odd = dpp_max_int<0x4E>(y8[2 * k + 1]);
+        y4[k] = e1 ? odd : even;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int even = dpp_max_int<0x141>(y4[2 * k]), odd = dpp_max_int<0x141>(y4[2 * k + 1]);
+        y2[k] = e2 ? odd : even;
+    }
+    const int even = dpp_max_int<0x140>(y2[0]), odd = dpp_max_int<0x140>(y2[1]);
+    const int y1 = e3 ? odd : even;
+    const auto sw = __builtin_amdgcn_permlane16_swap((uint32_t)y1, (uint32_t)y1, false, false);
+    return max((int)sw[0], (int)sw[1]);
+}
+
+// A workgroup sweeps one run of queries past a few cells of candidates, a group of 16 tiles after the other.  At the end of every
+// SEGMENT of queries the candidates' maxima are reduced over the lanes and kept.
+// Bound by the vector unit: 16 three-input maxima per block, 16.8 instructions in all, that is 67 cycles beside 32 of the
+// matrix instruction.  A bare loop of them takes 35.7 ns per block and SIMD, the kernel 38 to 40 (dense_staged_kernel 56).
+template <int SEGMENT>
+__global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(3)))
+void dense_coarse_kernel(DenseCoarseArgs a) {
+    __shared__ uint4 stage0[COARSE_TURN][64], stage1[COARSE_TURN][64];  // two variables, see dense_staged_kernel
+    __shared__ int row_best[DENSE_SB_PIXELS];                           // best score of every query in the cell
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int held = held_register(lane);
+    const int cell0 = blockIdx.x * a.cells_per_wg, sb = blockIdx.y, b = blockIdx.z;
+    constexpr int SEGS = DENSE_SB_PIXELS / SEGMENT, SEG_TURNS = DC_TURNS / SEGS;
+    const int64_t pixels1 = (int64_t)a.map[0].n_segs * SEGMENT, pixels2 = (int64_t)a.map[1].n_segs * SEGMENT;
+    const char* blocks = a.map[0].rows + ((int64_t)b * pixels1 + (int64_t)(a.first_sb + sb) * DENSE_SB_PIXELS) * COARSE_ROW_BYTES;
+    const char* tiles = a.map[1].rows + (int64_t)b * pixels2 * COARSE_ROW_BYTES;
+    uint16_t* rows = a.best[0] + ((int64_t)b * a.n_cells + cell0) * ((int64_t)a.n_sb * DENSE_SB_PIXELS) + (int64_t)sb * DENSE_SB_PIXELS;
+    uint16_t* cols = a.best[1] + ((int64_t)b * a.map[0].n_segs + (int64_t)(a.first_sb + sb) * SEGS) * pixels2;
+    // groups of this workgroup's cells that hold a pixel of image 2 (uniform)
+    const int group0 = cell0 * a.cell_groups;
+    const int n_groups = min(a.cells_per_wg * a.cell_groups, (a.n_tiles[1] + DC_GROUP - 1) / DC_GROUP - group0);
+    if (n_groups <= 0) return;
+    const int total = n_groups * DC_TURNS;
+
+    auto stage_turn = [&](uint4 (&slot)[COARSE_TURN][64], int k) {
+        uint32_t l;  // read afresh: see dense_stage_turn
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+        const char* from = blocks + (int64_t)(min(k, total - 1) % DC_TURNS) * (COARSE_TURN * TILE_BYTES);
+        const uint32_t off = (l & 31) * COARSE_ROW_BYTES + (l >> 5) * 16;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            __builtin_amdgcn_global_load_lds((const void*)(from + (2 * wave + i) * TILE_BYTES + off), FNN_LDS_PTR(&slot[2 * wave + i][0]), 16, 0, 0);
+    };
+    stage_turn(stage0, 0);
+    for (int i = threadIdx.x; i < DENSE_SB_PIXELS; i += COARSE_WAVES * 64) row_best[i] = LOWEST;
+
+    int k = 0;
+    for (int g = 0; g < n_groups; ++g) {
+        const int tile0 = (group0 + g) * DC_GROUP + wave * DC_J;
+        i32x4 cand[DC_J];
+        int best[DC_J][16];
+#pragma unroll
+        for (int j = 0; j < DC_J; ++j) {
+            cand[j] = *reinterpret_cast<const i32x4*>(tiles + (int64_t)(tile0 + j) * TILE_BYTES + c * COARSE_ROW_BYTES + 16 * h);
+            arrived(cand[j]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) best[j][v] = LOWEST;
+        }
+        auto turn = [&](int tt, auto slot_tag) {
+            constexpr int SLOT = decltype(slot_tag)::value;
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the turn is in LDS
+            __syncthreads();                     // everyone's is, and everyone has left the other slot
+            stage_turn(SLOT ? stage0 : stage1, k + tt + 1);
+            int found[DC_STEPS];  // best score of a step's queries (lanes 0..31 its first block, 32..63 its second)
+#pragma unroll
+            for (int s = 0; s < DC_STEPS; ++s) {
+                const i32x4 qa = __builtin_bit_cast(i32x4, SLOT ? stage1[2 * s][lane] : stage0[2 * s][lane]);
+                const i32x4 qb = __builtin_bit_cast(i32x4, SLOT ? stage1[2 * s + 1][lane] : stage0[2 * s + 1][lane]);
+                int ra = LOWEST, rb = LOWEST;
+#pragma unroll
+                for (int j = 0; j < DC_J; ++j) {
+                    const i32x16 pa = product8(cand[j], qa), pb = product8(cand[j], qb);
+                    ra = fold16i(ra, pa);
+                    rb = fold16i(rb, pb);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) best[j][v] = max3i(best[j][v], pa[v], pb[v]);
+                }
+                const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)ra, (uint32_t)rb, false, false);
+                found[s] = max((int)sw[0], (int)sw[1]);
+                __builtin_amdgcn_sched_barrier(0);  // steps are scheduled one by one: more products in flight would spill
+            }
+#pragma unroll
+            for (int s = 0; s < DC_STEPS; ++s) atomicMax(&row_best[(tt * COARSE_TURN + 2 * s) * 32 + lane], found[s]);
+        };
+#pragma unroll 1
+        for (int seg = 0; seg < SEGS; ++seg) {
+#pragma unroll 1
+            for (int tt = seg * SEG_TURNS; tt < (seg + 1) * SEG_TURNS; tt += 2) {
+                turn(tt, std::integral_constant<int, 0>{});
+                turn(tt + 1, std::integral_constant<int, 1>{});
+            }
+#pragma unroll
+            for (int j = 0; j < DC_J; ++j) {
+                const int top = transpose_max16_int(best[j], lane);
+                if ((lane & 16) == 0)
+                    cols[seg * pixels2 + (int64_t)(tile0 + j) * 32 + tile_row(held, h)] = (uint16_t)(top >> KEPT_SHIFT);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) best[j][v] = LOWEST;
+            }
+        }
+        k += DC_TURNS;
+        if ((g + 1) % a.cell_groups == 0 || g + 1 == n_groups) {  // the end of a cell (uniform)
+            __syncthreads();
+            for (int i = threadIdx.x * 2; i < DENSE_SB_PIXELS; i += COARSE_WAVES * 128) {
+                const int2 two = *reinterpret_cast<const int2*>(&row_best[i]);
+                *reinterpret_cast<uint32_t*>(rows + i) = ((uint32_t)(two.x >> KEPT_SHIFT) & 0xFFFFu) | ((uint32_t)(two.y >> KEPT_SHIFT) << 16);
+                *reinterpret_cast<int2*>(&row_best[i]) = make_int2(LOWEST, LOWEST);
+            }
+            rows += (int64_t)a.n_sb * DENSE_SB_PIXELS;
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // the turn past the last one has landed too
+}
+
+// Which cells may hold the best partner of a slot: the bounds that turn 8-bit scores into products (coarse.hip) give every slot a
+// lower bound of its best score, and a cell whose upper bound reaches it is marked.  A lane takes SELECT_SLOTS slots,
+// 64 apart; the waves of a workgroup share the cells.  Bound by memory; the table is read twice, the second time mostly
+// from cache.
+constexpr int SELECT_WAVES = 4;
+constexpr int SELECT_SLOTS = 4;
+constexpr int SELECT_DEEP = 6;  // cells in flight per wave
+struct SelectArgs {
+    const uint16_t* best;       // [batch][n_cells][pitch]
+    uint64_t* mask;             // [batch][n_cells][pitch / 64]
+    int32_t n_cells;
+    int64_t pitch;              // a multiple of 64
+    int32_t cells_per_seg;      // of the other map
+    const uint32_t* row_bound;  // of the slots, [batch][bound_pitch]
+    int64_t bound_pitch;
+    const SegInfo* seg;         // of the other map, [batch][n_segs]
+    int32_t n_segs;
+};
+__global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectArgs a) {
+    __shared__ float low[SELECT_WAVES][SELECT_SLOTS][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.y;
+    const int64_t slot0 = (int64_t)blockIdx.x * (64 * SELECT_SLOTS);  // whole 64s past the pitch do not exist
+    const uint16_t* column = a.best + (int64_t)b * a.n_cells * a.pitch + slot0 + lane;
+    uint64_t* mask = a.mask + ((int64_t)b * a.n_cells * a.pitch + slot0) / 64;
+    const SegInfo* seg = a.seg + (int64_t)b * a.n_segs;
+    bool here[SELECT_SLOTS];
+    float length[SELECT_SLOTS], residual[SELECT_SLOTS], best[SELECT_SLOTS];
+#pragma unroll
+    for (int e = 0; e < SELECT_SLOTS; ++e) {
+        here[e] = slot0 + 64 * e < a.pitch;  // uniform
+        const uint32_t bound = here[e] ? a.row_bound[(int64_t)b * a.bound_pitch + slot0 + 64 * e + lane] : 0;
+        length[e] = __uint_as_float(bound & 0xFFFF0000u);
+        residual[e] = __uint_as_float(bound << 16);
+        best[e] = -__builtin_inff();
+    }
+    // visit(cell, slot, 8-bit score, its segment) for this wave's cells
+    auto sweep = [&](auto visit) {
+        for (int cell0 = wave; cell0 < a.n_cells; cell0 += SELECT_WAVES * SELECT_DEEP) {
+            int kept[SELECT_DEEP][SELECT_SLOTS];
+#pragma unroll
+            for (int i = 0; i < SELECT_DEEP; ++i)
+#pragma unroll
+                for (int e = 0; e < SELECT_SLOTS; ++e)
+                    kept[i][e] = (int16_t)column[(int64_t)min(cell0 + i * SELECT_WAVES, a.n_cells - 1) * a.pitch + (here[e] ? 64 * e : 0)];
+#pragma unroll
+            for (int i = 0; i < SELECT_DEEP; ++i) {
+                const int cell = cell0 + i * SELECT_WAVES;
+                if (cell < a.n_cells) {  // uniform
+                    const SegInfo si = seg[cell / a.cells_per_seg];
+#pragma unroll
+                    for (int e = 0; e < SELECT_SLOTS; ++e) visit(cell, e, kept[i][e], si);
+                }
+            }
+        }
+    };
+    auto error = [&](int e, const SegInfo& si) { return __builtin_fmaf(length[e], si.residual, residual[e] * si.length); };
+    sweep([&](int, int e, int v, const SegInfo& si) {
+        best[e] = __builtin_fmaxf(best[e], (float)(v * (1 << KEPT_SHIFT)) * si.scale - error(e, si));
+    });
+#pragma unroll
+    for (int e = 0; e < SELECT_SLOTS; ++e) low[wave][e][lane] = best[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < SELECT_SLOTS; ++e)
+#pragma unroll
+        for (int w = 0; w < SELECT_WAVES; ++w) best[e] = __builtin_fmaxf(best[e], low[w][e][lane]);
+    sweep([&](int cell, int e, int v, const SegInfo& si) {
+        const uint64_t need = __ballot((float)((v + 1) * (1 << KEPT_SHIFT)) * si.scale + error(e, si) >= best[e]);
+        if (lane == 0 && here[e]) mask[(int64_t)cell * (a.pitch / 64) + e] = need;
+    });
+}
+
+// Wider cells keep the table of a large map small, narrower ones leave less to multiply again.
+int dense_seg_pixels(int64_t n) { return n > 400000 ? 4096 : 2048; }
+int dense_cell_groups(int64_t n, int64_t m) { return m > 400000 ? dense_seg_pixels(n) / 512 : 2; }  // a cell lies in one segment
+double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2) {
+    if (n < 16384 || m < 16384 || (compute != FNN_F32 && dp <= 16)) return -1e30;
+    if ((double)batch * m * (n / dense_seg_pixels(n)) * 2.0 > 4e9) return -1e30;  // the candidates' table of bounds would be too large
+    // what a block of 32x32 scores takes one SIMD in the dense kernels, in dense_coarse_kernel, and in the second step
+    const double exact = compute == FNN_F32 ? 15.8 * dp : (dp <= 32 ? 2.33 * dp : 1.83 * dp), coarse = 38.0;
+    const double second = compute == FNN_F32 ? 18.75 * dp : (dp <= 32 ? 46.0 : 1.64 * dp);
+    const double cell = 512.0 * dense_cell_groups(n, m), row_bytes = dp * elem_size(compute);
+    const double cells[2] = {m / cell, (double)n / dense_seg_pixels(n)};
+    const double again = coarse_cells_again(cells[0], d, l2) / cells[0] + coarse_cells_again(cells[1], d, l2) / cells[1];
+    const double blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
+    const double bytes = batch * ((double)(n + m) * (2.0 * row_bytes + 40.0) + 8.0 * n * (m / cell) + 8.0 * m * ((double)n / dense_seg_pixels(n)));
+    return blocks * (exact - coarse - second * again) - 30000.0 - bytes / 4500.0 - batch * (double)(n + m) * 0.1;
+}
+
+hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s) {
+    // six workgroups for every resident one (three per compute unit), so that the last ones leave little of the chip idle
+    a.cells_per_wg = 1;
+    const int64_t cells = (int64_t)a.n_cells * a.n_sb * batch;
+    while (a.cells_per_wg < 4 && cells / (a.cells_per_wg * 2) >= 4608) a.cells_per_wg *= 2;
+    const dim3 grid((a.n_cells + a.cells_per_wg - 1) / a.cells_per_wg, a.n_sb, batch);
+    if (a.seg_pixels == 2048) return launch_detail(TK_DENSE, 2, dense_coarse_kernel<2048>, grid, dim3(COARSE_WAVES * 64), 0, s, a);
+    return launch_detail(TK_DENSE, 2, dense_coarse_kernel<4096>, grid, dim3(COARSE_WAVES * 64), 0, s, a);
+}
+
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int side, int batch, hipStream_t s) {
+    SelectArgs sa;
+    const CoarseMap& own = a.map[side];
+    const CoarseMap& other = a.map[side ^ 1];
+    sa.best = a.best[side];
+    sa.mask = a.mask[side];
+    sa.n_cells = side == 0 ? a.n_cells : a.map[0].n_segs;
+    sa.pitch = side == 0 ? (int64_t)a.n_sb * DENSE_SB_PIXELS : (int64_t)own.n_segs * a.seg_pixels;
+    sa.cells_per_seg = side == 0 ? a.seg_pixels / (512 * a.cell_groups) : 1;
+    sa.row_bound = own.row_bound + (side == 0 ? (int64_t)a.first_sb * DENSE_SB_PIXELS : 0);
+    sa.bound_pitch = (int64_t)own.n_segs * a.seg_pixels;
+    sa.seg = other.seg;
+    sa.n_segs = other.n_segs;
+    const int64_t per_wg = 64 * SELECT_SLOTS;
+    return launch(TK_DENSE_SELECT, dense_select_kernel, dim3((unsigned)((sa.pitch + per_wg - 1) / per_wg), batch), dim3(SELECT_WAVES * 64), 0, s, sa);
+}
+
+}  // namespace fnn

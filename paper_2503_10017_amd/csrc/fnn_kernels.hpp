@@ -135,11 +135,17 @@ hipError_t launch_search_first(const FirstSearchArgs& a, int batch, int compute,
 // launch_resolve with the queries still in the caller's fp32 map
 hipError_t launch_resolve_raw(const FirstSearchArgs& a, int batch, int compute, int32_t* out_idx, float* out_score, int32_t* clear_count,
                               hipStream_t s);
+// ---- tiles of the dense mode ------------------------------------------------------------------
+constexpr int DENSE_J = 4;      // candidate tiles resident per wave
+constexpr int DENSE_WAVES = 4;  // waves per workgroup
+constexpr int DENSE_TILES_PER_GROUP = DENSE_J * DENSE_WAVES;
+
 // ---- pass 1 in 8 bits, for searches large enough (coarse.hip) -------------------------------
 // Pixels of a map are taken SEG_PIXELS at a time: one scale and one set of bounds for each segment.  A query's scores
 // are bounded per CELL, a whole segment or half of one.
 constexpr int SEG_TILES = 32;
 constexpr int SEG_PIXELS = 32 * SEG_TILES;
+constexpr int DENSE_SB_PIXELS = 4096;  // the dense mode sweeps so many queries at a time: one or two segments of its maps
 constexpr int COARSE_ROW_BYTES = 32;  // one K=32 matrix instruction
 struct SegInfo {
     float scale;     // a row is about scale * its 8-bit row
@@ -163,7 +169,6 @@ struct QuantiseSide {
     int64_t raw_stride;    // floats
     const int32_t* gather; // [batch][n] rows of the source to take, in this order (NULL: all of them)
     int64_t gather_rows;   // rows of that source; the list's entries are clamped to it
-    int32_t second_image;  // which copies of a two-term row hold the low halves
     CoarseMap out;
 };
 struct QuantiseArgs {
@@ -171,6 +176,7 @@ struct QuantiseArgs {
     QuantiseSide side[2];
     int32_t batch;
     int32_t raw_rows;
+    int32_t seg_pixels;    // SEG_PIXELS, 2048 or 4096
     uint32_t* lower;       // bounds to clear
     int64_t lower_count;
     int32_t split_d;       // channels of a two-term row's descriptor (0: rows are not two-term)
@@ -184,14 +190,21 @@ struct CoarseArgs {
     uint32_t* lower;       // [batch][slot_pitch] order_bits: some score lies at or above it (0 on entry)
     int32_t slab;          // slots that one launch takes (a multiple of 64)
     int64_t slot_pitch;    // queries of a pair, rounded up to whole 64s
-    int32_t first_slot;    // set by the launcher
+    int32_t n_cells;       // of a pair
+    int32_t cell_shift;    // a cell is 2^cell_shift workgroups of the second step
+    const uint64_t* mask;  // launch_refine: [batch][n_cells][slab / 64] the slots that need a cell, instead of the bounds
+    int32_t first_slot;    // (launch_coarse_search sets these)
     int32_t min_live;      // fewer live queries of a pair than this: its cells are refined for every query
 };
 // What launch_search does: the queries' list and live count, the prepared maps and the keys are those of `a`.
 hipError_t launch_coarse_search(const SearchArgs& a, const CoarseArgs& ca, int batch, int compute, int dp, hipStream_t s);
+// The second step alone, for the slots [first_slot, first_slot + slab) and cells of SEG_TILES << cell_shift tiles, from the table
+// `mask`; its keys name units of DENSE_J tiles.
+hipError_t launch_refine(const SearchArgs& a, const CoarseArgs& ca, int batch, int compute, int dp, hipStream_t s);
 // Nanoseconds of the device that a search of `nq` queries per pair against maps of m pixels gains in two steps (very negative where
 // it has to run in one), and what the 8-bit maps of `rows` pixels cost
-double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, bool l2);
+double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, int d, bool l2);
+double coarse_cells_again(double cells, int d, bool l2);
 double coarse_cost(int64_t rows, int compute, int dp);
 constexpr double COARSE_LEAST_GAIN = 3000.0;  // of a call
 // Fewer queries per pair than this spread the second step thin: a call with so few runs in one
@@ -280,9 +293,6 @@ bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int c
 hipError_t launch_walk(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s);
 
 // ---- dense mutual nearest neighbours -----------------------------------------------------
-constexpr int DENSE_J = 4;      // candidate tiles resident per wave
-constexpr int DENSE_WAVES = 4;  // waves per workgroup
-constexpr int DENSE_TILES_PER_GROUP = DENSE_J * DENSE_WAVES;
 struct DenseArgs {
     const char* d1;        // prepared queries, segment-major, [batch][n_sb*32*DENSE_S][dp]
     int64_t d1_bstride;
@@ -310,6 +320,32 @@ struct DenseArgs {
 // nn12/s12/nn21/s21; s12, s21 may be NULL).
 hipError_t launch_dense(const DenseArgs& a, int batch, int compute, int dp, int32_t* nn12, float* s12, int32_t* nn21,
                         float* s21, hipStream_t s);
+
+// Pass 1 in 8 bits (dense_coarse.hip), on maps quantised in segments of seg_pixels: the largest 8-bit score of every query in
+// every cell of candidates, and of every candidate in every segment of queries.
+struct DenseCoarseArgs {
+    CoarseMap map[2];      // images 1 and 2
+    int32_t n_tiles[2];    // tiles of each that hold a pixel
+    int32_t seg_pixels;    // 2048 or 4096
+    int32_t first_sb;      // the runs of DENSE_SB_PIXELS of image 1 that this launch takes
+    int32_t n_sb;
+    int32_t cell_groups;   // groups of 512 candidates in a cell: 2, 4 or 8
+    int32_t n_cells;       // of image 2
+    int32_t cells_per_wg;  // (set by the launcher)
+    uint16_t* best[2];     // [batch][n_cells][n_sb * 4096] of the queries; [batch][map[0].n_segs][pixels of map[1]] of the candidates
+    uint64_t* mask[2];     // the same, a bit per score: cells that may hold the slot's best partner
+};
+hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s);
+// From best[side] to mask[side].  side 0: the queries of this launch's runs; 1: the candidates, once every run is done
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int side, int batch, hipStream_t s);
+int dense_cell_groups(int64_t n, int64_t m);
+int dense_seg_pixels(int64_t n);
+// Nanoseconds that a call gains this way
+double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2);
+
+// Pass 2 for keys that launch_refine left in row_keys and col_keys (units of DENSE_J tiles of the other map), both maps in natural order.
+hipError_t launch_dense_resolve(const DenseArgs& a, int batch, int compute, int dp, int32_t* nn12, float* s12, int32_t* nn21, float* s21,
+                                hipStream_t s);
 
 struct DenseFinalArgs {
     int32_t n, m;

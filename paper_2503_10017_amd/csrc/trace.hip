@@ -99,6 +99,7 @@ const char* fnn_trace_kind_name(int32_t kind) {
         case TK_QUANTISE: return "quantise_kernel";
         case TK_COARSE: return "coarse_kernel";
         case TK_REFINE: return "refine_kernel";
+        case TK_DENSE_SELECT: return "dense_select_kernel";
         default: return "unknown";
     }
 }

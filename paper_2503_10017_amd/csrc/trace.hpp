@@ -25,7 +25,8 @@ enum TraceKind : int {
     TK_QUANTISE = 14,
     TK_COARSE = 15,
     TK_REFINE = 16,
-    TK_COUNT = 17
+    TK_DENSE_SELECT = 17,
+    TK_COUNT = 18
 };
 
 // Returns false when no trace is open or it is full; otherwise hands out the next event pair.

@@ -29,10 +29,11 @@ def enough_pairs(nq, n, m, compute, d, **kw):
     """Pairs that make a call worth two steps, by the library's own estimate of both (nanoseconds)."""
     dp = channels(d, compute, kw.get("l2", False), kw.get("split", False))
     row, block = dp * ELEMENT[compute], 18.75 * dp if compute == "f32" else 46.0 if dp <= 32 else 1.64 * dp
-    again = 1024 * (32.0 if kw.get("l2") else 5.0)
 
     def gain(pixels):
-        return -(-nq // 32) * -(-pixels // 32) / 1024.0 * (block * (1.0 - again / pixels) - 28.0) - pixels * row / 4500.0
+        cells = pixels / 1024
+        again = min(cells, 32.0 + 0.26 * (8.0 / d) ** 4 * cells if kw.get("l2") else 5.0 + 0.26 * (6.0 / d) ** 4 * cells)
+        return -(-nq // 32) * -(-pixels // 32) / 1024.0 * (block * (1.0 - 1.5 * again / cells) - 28.0) - pixels * row / 4500.0
 
     maps = (n + m) * (row + 36) / 4500.0
     for batch in range(1, 65):
@@ -81,20 +82,22 @@ def same(op, a, b, queries, compute, **kw):
 
 
 @pytest.mark.parametrize("n,m,nq,compute,stored,d,kw", [
-    (65536, 65536, 4096, "f16", "f32", 24, {}),                      # whole segments, raw rows
-    (70011, 65537, 4097, "bf16", "f32", 24, {}),                     # one candidate in the last segment
+    (65536, 65536, 8192, "f16", "f32", 24, {}),                      # whole segments, raw rows
+    (70011, 65537, 8193, "bf16", "f32", 24, {}),                     # one candidate in the last segment
     (66000, 70001, 5001, "f16", "f32", 21, {}),                      # channels padded: prepared first
-    (66000, 68001, 4500, "bf16", "f16", 30, {}),                     # 32-channel rows
-    (65551, 70017, 4200, "f16", "f16", 24, {}),                      # rows of the caller, not whole tiles
-    (65568, 70016, 4200, "f16", "f16", 24, {}),                      # ... and where they are
+    (66000, 68001, 9000, "bf16", "f16", 30, {}),                     # 32-channel rows
+    (65551, 70017, 7000, "f16", "f16", 24, {}),                      # rows of the caller, not whole tiles
+    (65568, 70016, 7000, "f16", "f16", 24, {}),                      # ... and where they are
     (33000, 36001, 1000, "f32", "f32", 24, {}),
-    (33000, 36001, 1500, "f32", "f32", 5, {}),
+    (33000, 36001, 1500, "f32", "f32", 8, {}),
     (33000, 35001, 700, "f32", "f32", 31, {}),
     (132000, 131100, 600, "f32", "bf16", 13, {"l2": True}),
     (66000, 70000, 3000, "f16", "f32", 24, {"split": True}),
     (66000, 70000, 2600, "f16", "f32", 13, {"split": True}),
+    (130000, 140000, 9000, "f16", "f32", 8, {"split": True}),
+    (130000, 140000, 9000, "f16", "f32", 10, {"split": True}),
     (66000, 70000, 2800, "f16", "f32", 32, {"split": True, "normalize": True}),
-    (67000, 68000, 4500, "bf16", "f32", 24, {"normalize": True}),
+    (67000, 68000, 7000, "bf16", "f32", 24, {"normalize": True}),
 ])
 @pytest.mark.parametrize("op", ["nearest", "reciprocal"])
 def test_same_bits_in_two_steps_as_in_one(op, n, m, nq, compute, stored, d, kw):
@@ -125,7 +128,7 @@ def test_same_bits_in_two_steps_as_in_one(op, n, m, nq, compute, stored, d, kw):
 def test_exact_maps_with_ties_match_the_oracle(compute):
     a, b = exact_maps(5, 65600, 66001, 24)
     b[7000:7400] = b[100:500]      # equal candidates in different segments: the lowest index wins
-    q = np.arange(0, 65600, 15).astype(np.int32)
+    q = np.arange(0, 65600, 9).astype(np.int32)
     batch = enough_pairs(len(q), len(a), len(b), compute, 24)
     ta, tb, tq = dev(a)[None].repeat(batch, 1, 1), dev(b)[None].repeat(batch, 1, 1), dev(np.tile(q, (batch, 1)))
     got = same("nearest", ta, tb, tq, compute)
@@ -167,11 +170,11 @@ SPECIAL = ["all equal", "negative", "outlier", "zero rows", "tiny", "lengths", "
 def test_maps_that_strain_the_bounds(kind, compute):
     rng = np.random.default_rng(11)
     n, m = 65601, 66011
-    batch = enough_pairs(4500, n, m, compute, 24)
+    batch = enough_pairs(7500, n, m, compute, 24)
     maps = [_special(kind, rng, n, m) for _ in range(min(batch, 3))]
     maps = [maps[p % len(maps)] for p in range(batch)]
     a, b = (dev(np.stack([x[i] for x in maps])) for i in (0, 1))
-    q = dev(rng.integers(0, n, size=(batch, 4500)).astype(np.int32))
+    q = dev(rng.integers(0, n, size=(batch, 7500)).astype(np.int32))
     q[:, :8] = 3
     if kind == "not finite":  # unspecified results, but indices inside the maps
         got = run("nearest", a, b, q, compute, True)

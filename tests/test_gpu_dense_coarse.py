@@ -1,0 +1,107 @@
+"""The dense mode on large maps: 8-bit scores with bounds first, then the second step of the searches in both directions.  With a
+workspace that ends where the 8-bit maps would begin the same call forms every product in its own format: both must give the
+same bits."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2503_10017_amd as fnn
+from gpu_helpers import dev, exact_maps, host
+from test_gpu_coarse import ELEMENT, SPECIAL, _special, channels, up
+
+pytestmark = pytest.mark.gpu
+
+
+def one_step_bytes(batch, n, m, d, compute, **kw):
+    row = channels(d, compute, kw.get("l2", False), kw.get("split", False)) * ELEMENT[compute]
+    n_pad, m_pad = up(n, 4096), up(m, 32)
+    row_units, col_units = -(-m_pad // 128), n_pad // 128
+    lists = up(n, 32) + 32 * row_units + m_pad + 32 * col_units
+    units = 4 * batch * (row_units + col_units)
+    sizes = [batch * n_pad * row, batch * m_pad * row, 8 * batch * (n + m), units, units, 4 * batch * lists, batch * lists // 8, 8 * batch,
+             4 * batch * (-(-max(n, m) // 1024) + 1)]
+    return sum(up(x, 256) for x in sizes)
+
+
+def run(a, b, compute, two_steps, **kw):
+    batch, n, d = a.shape
+    m = b.shape[1]
+    small = one_step_bytes(batch, n, m, d, compute, **kw)
+    full = fnn.fnn_workspace_bytes_opts(batch, n, m, d, 0, compute, **kw)
+    assert full > small + 1024
+    ws = torch.full((full if two_steps else small,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    fnn.fnn_trace_begin(256)
+    try:
+        out = fnn.fnn_mutual_dense(a, b, compute, workspace=ws, **kw)
+        torch.cuda.synchronize()
+    finally:
+        names = [name for name, _ in fnn.fnn_trace_end(256)]
+    assert ("dense_select_kernel" in names) == two_steps
+    return {k: host(v) for k, v in out.items()}, names
+
+
+def same(a, b, compute, **kw):
+    (two, names), (one, _) = (run(a, b, compute, x, **kw) for x in (True, False))
+    for k in one:
+        assert np.array_equal(two[k], one[k]), (k, int(np.sum(two[k] != one[k])))
+    return two, names
+
+
+@pytest.mark.parametrize("n,m,batch,compute,stored,d,kw", [
+    (131072, 131072, 2, "f16", "f32", 24, {}),                  # whole segments, rows where they are
+    (131073, 135169, 2, "bf16", "f32", 24, {}),                 # one pixel in the last segments
+    (150000, 131071, 3, "f16", "f16", 21, {}),
+    (131500, 141000, 4, "bf16", "f32", 29, {}),                 # 32-channel rows
+    (65536, 40000, 1, "f32", "f32", 24, {}),
+    (130001, 70000, 2, "f32", "bf16", 7, {}),
+    (50000, 60001, 1, "f32", "f32", 32, {"normalize": True}),
+    (400001, 390000, 1, "f32", "f32", 16, {"l2": True}),
+    (66000, 65600, 1, "f16", "f32", 24, {"split": True}),
+    (66000, 71000, 1, "f16", "f32", 11, {"split": True}),
+    (200000, 200001, 2, "f16", "f32", 9, {"split": True}),
+    (90000, 404000, 1, "f16", "f32", 24, {"normalize": True}),  # wide cells
+    (404123, 17000, 2, "f32", "f32", 24, {}),
+])
+def test_same_bits_in_two_steps_as_in_one(n, m, batch, compute, stored, d, kw):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + m)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device="cuda:0")
+
+    a = torch.nn.functional.normalize(normal(batch, n, d), dim=2)
+    b = torch.nn.functional.normalize(normal(batch, m, d), dim=2)
+    k = min(n, m) // 2
+    b[:, :k] = torch.nn.functional.normalize(a[:, :k] + 0.3 * b[:, :k], dim=2)  # half the pixels have a partner
+    if kw:
+        a, b = a * torch.exp(0.2 * normal(batch, n, 1)), b * torch.exp(0.2 * normal(batch, m, 1))
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[stored]
+    same(a.to(kind), b.to(kind), compute, **kw)
+
+
+def test_ranges_of_segments_in_launches_of_their_own():
+    """The table of bounds covers as many segments of image 1 as 128 MB hold."""
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    a = torch.nn.functional.normalize(torch.randn((5, 130000, 24), generator=gen, device="cuda:0"), dim=2)
+    b = torch.nn.functional.normalize(a[:, torch.randperm(130000, generator=gen, device="cuda:0")] + 0.1 * torch.randn(a.shape, generator=gen, device="cuda:0"), dim=2)
+    _, names = same(a, b, "bf16")
+    assert names.count("dense_kernel") == 2    # 127 cells x 4096 x 2 bytes x 5 pairs: 25 of the 32 segments fit
+
+
+def test_exact_maps_with_ties_match_the_oracle():
+    a, b = exact_maps(8, 45000, 36000, 24)
+    b[17000:17400] = b[100:500]
+    a[20000:20100] = a[50:150]
+    (got, _), ref = same(dev(a)[None], dev(b)[None], "f32"), oracle.mutual_dense(a, b)
+    for k in ("nn12", "s12", "nn21", "s21"):
+        assert np.array_equal(got[k][0], ref[k]), k
+    assert np.array_equal(got["pairs"][0, :int(got["n_pairs"][0])], ref["pairs"])
+
+
+@pytest.mark.parametrize("kind,compute", [(k, c) for k in SPECIAL for c in ("f16", "f32") if (k, c) != ("beyond bounds", "f16") and k != "not finite"])
+def test_maps_that_strain_the_bounds(kind, compute):
+    rng = np.random.default_rng(12)
+    n, m, batch = (131100, 133000, 2) if compute == "f16" else (40001, 40100, 1)
+    maps = [_special(kind, rng, n, m) for _ in range(batch)]
+    a, b = (dev(np.stack([x[i] for x in maps])) for i in (0, 1))
+    same(a, b, compute)
