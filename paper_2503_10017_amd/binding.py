@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Sequence, Union
 
 import torch
@@ -96,31 +97,56 @@ MapsLike = Union[torch.Tensor, Sequence[torch.Tensor]]
 
 
 def _as_pairs(maps: MapsLike):
-    """[n][d] tensor, [batch][n][d] tensor or a sequence of [n][d] tensors -> list of 2-D views."""
+    """[n][d] tensor, [batch][n][d] tensor or a sequence of [n][d] tensors -> list of 2-D views; a stack with pixels
+    in it stays one tensor."""
     if isinstance(maps, torch.Tensor):
         if maps.dim() == 2:
             return [maps]
         if maps.dim() == 3:
-            return [maps[b] for b in range(maps.shape[0])]
+            return maps if maps.numel() else [maps[b] for b in range(maps.shape[0])]
         raise ValueError("a map is [n][d] or [batch][n][d]")
     return list(maps)
 
 
-def _map_array(views):
-    arr = (_Map * len(views))()
-    for b, t in enumerate(views):
-        if t.dim() != 2 or not t.is_cuda:
+def _dims(pairs):
+    """Pairs, pixels and channels of the first one, and the device."""
+    if isinstance(pairs, torch.Tensor):
+        batch, n, d = pairs.shape
+        return batch, n, d, pairs.device
+    shape = pairs[0].shape
+    return len(pairs), shape[0], shape[1], pairs[0].device
+
+
+# A struct fnn_map.  The call is host work before its first launch: a view, a ctypes structure and five field
+# assignments per pair took 2.2 us, which a call of 16 small pairs waited for 32 times.
+_pack_map = struct.Struct("=QqiiQ").pack
+
+
+def _row_format(t, n, d, row_stride, channel_stride):
+    if not t.is_cuda:
+        raise ValueError("maps must be 2-D device tensors")
+    if t.dtype not in _DTYPES:
+        raise ValueError(f"unsupported map dtype {t.dtype}")
+    if d > 1 and channel_stride != 1:
+        raise ValueError("channels of a map must be contiguous")
+    return n, d, _DTYPES[t.dtype], row_stride if n > 1 else max(d, row_stride)
+
+
+def _map_array(pairs) -> bytes:
+    """The array of fnn_map that the library reads; keep it alive over the call."""
+    if isinstance(pairs, torch.Tensor):
+        batch, n, d = pairs.shape
+        step, row_stride, channel_stride = pairs.stride()
+        rest = _row_format(pairs, n, d, row_stride, channel_stride)
+        step *= pairs.element_size()
+        base = pairs.data_ptr()
+        return b"".join([_pack_map(base + b * step, *rest) for b in range(batch)])
+    out = []
+    for t in pairs:
+        if t.dim() != 2:
             raise ValueError("maps must be 2-D device tensors")
-        if t.dtype not in _DTYPES:
-            raise ValueError(f"unsupported map dtype {t.dtype}")
-        if t.shape[1] > 1 and t.stride(1) != 1:
-            raise ValueError("channels of a map must be contiguous")
-        arr[b].data = t.data_ptr()
-        arr[b].n = t.shape[0]
-        arr[b].d = t.shape[1]
-        arr[b].dtype = _DTYPES[t.dtype]
-        arr[b].row_stride = t.stride(0) if t.shape[0] > 1 else max(t.shape[1], t.stride(0))
-    return arr
+        out.append(_pack_map(t.data_ptr(), *_row_format(t, *t.shape, *t.stride())))
+    return b"".join(out)
 
 
 FNN_FLAG_NORMALIZE = 1
@@ -139,13 +165,13 @@ def _opts(compute, max_iter=0, normalize=False, half_accumulate=False, l2=False,
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream_ptr(stream, device):
     if stream is None:
         stream = torch.cuda.current_stream(device)
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def fnn_workspace_bytes(batch: int, n: int, m: int, d: int, n_queries: int, compute) -> int:
@@ -159,10 +185,8 @@ def fnn_workspace_bytes_opts(batch: int, n: int, m: int, d: int, n_queries: int,
     return int(load_library().fnn_workspace_bytes_opts(batch, n, m, d, n_queries, ctypes.byref(o)))
 
 
-def _workspace(workspace, need, device):
-    if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
-    return workspace
+def _workspace(need, device):
+    return torch.empty(max(need, 256), dtype=torch.uint8, device=device)
 
 
 def fnn_nearest(src: MapsLike, tgt: MapsLike, q_idx: Optional[torch.Tensor] = None,
@@ -175,20 +199,20 @@ def fnn_nearest(src: MapsLike, tgt: MapsLike, q_idx: Optional[torch.Tensor] = No
     (two-term fp16 representation of fp32 descriptors, compute "f16" only)."""
     lib = load_library()
     sv, tv = _as_pairs(src), _as_pairs(tgt)
-    batch = len(sv)
-    device = sv[0].device
+    batch, n, d, device = _dims(sv)
+    m = _dims(tv)[1]
     if nq is None:
-        nq = q_idx.shape[-1] if q_idx is not None else sv[0].shape[0]
+        nq = q_idx.shape[-1] if q_idx is not None else n
     if out_idx is None:
         out_idx = torch.empty((batch, nq), dtype=torch.int32, device=device)
     if out_score is None and want_score:
         out_score = torch.empty((batch, nq), dtype=torch.float32, device=device)
     o = _opts(compute, normalize=normalize, l2=l2, split=split)
-    need = fnn_workspace_bytes_opts(batch, sv[0].shape[0], tv[0].shape[0], sv[0].shape[1], nq, compute, l2=l2, split=split)
-    workspace = _workspace(workspace, need, device)
+    if workspace is None:
+        workspace = _workspace(fnn_workspace_bytes_opts(batch, n, m, d, nq, compute, l2=l2, split=split), device)
     sa, ta = _map_array(sv), _map_array(tv)
-    st = lib.fnn_nearest(batch, ctypes.cast(sa, ctypes.c_void_p), _ptr(q_idx), nq, _ptr(nq_active),
-                         ctypes.cast(ta, ctypes.c_void_p), ctypes.byref(o), _ptr(out_idx), _ptr(out_score),
+    st = lib.fnn_nearest(batch, sa, _ptr(q_idx), nq, _ptr(nq_active),
+                         ta, ctypes.byref(o), _ptr(out_idx), _ptr(out_score),
                          _ptr(workspace), workspace.numel(), _stream_ptr(stream, device))
     if st != 0:
         raise FnnError(st, "fnn_nearest")
@@ -202,8 +226,8 @@ def fnn_reciprocal(d1: MapsLike, d2: MapsLike, seeds: torch.Tensor, max_iter: in
     seed_i, seed_j, seed_iter [batch][n_seeds], pairs [batch][n_seeds][2], n_pairs [batch]."""
     lib = load_library()
     v1, v2 = _as_pairs(d1), _as_pairs(d2)
-    batch = len(v1)
-    device = v1[0].device
+    batch, n, d, device = _dims(v1)
+    m = _dims(v2)[1]
     n_seeds = seeds.shape[-1]
     if out is None:
         out = {
@@ -214,11 +238,10 @@ def fnn_reciprocal(d1: MapsLike, d2: MapsLike, seeds: torch.Tensor, max_iter: in
             "n_pairs": torch.empty((batch,), dtype=torch.int32, device=device),
         }
     o = _opts(compute, max_iter, normalize, l2=l2, split=split)
-    need = fnn_workspace_bytes_opts(batch, v1[0].shape[0], v2[0].shape[0], v1[0].shape[1], n_seeds, compute, l2=l2, split=split)
-    workspace = _workspace(workspace, need, device)
+    if workspace is None:
+        workspace = _workspace(fnn_workspace_bytes_opts(batch, n, m, d, n_seeds, compute, l2=l2, split=split), device)
     a1, a2 = _map_array(v1), _map_array(v2)
-    st = lib.fnn_reciprocal(batch, ctypes.cast(a1, ctypes.c_void_p), ctypes.cast(a2, ctypes.c_void_p),
-                            _ptr(seeds), n_seeds, ctypes.byref(o),
+    st = lib.fnn_reciprocal(batch, a1, a2, _ptr(seeds), n_seeds, ctypes.byref(o),
                             _ptr(out["seed_i"]), _ptr(out["seed_j"]), _ptr(out["seed_iter"]),
                             _ptr(out["pairs"]), _ptr(out["n_pairs"]),
                             _ptr(workspace), workspace.numel(), _stream_ptr(stream, device))
@@ -239,10 +262,9 @@ def fnn_reciprocal_static(d1: MapsLike, d2: MapsLike, seeds: torch.Tensor, out: 
     batch = len(v1)
     o = _opts(compute, max_iter, normalize, l2=l2, split=split)
     a1, a2 = _map_array(v1), _map_array(v2)
-    st = lib.fnn_reciprocal_static(batch, ctypes.cast(a1, ctypes.c_void_p), ctypes.cast(a2, ctypes.c_void_p),
-                                   _ptr(seeds), seeds.shape[-1], ctypes.byref(o),
+    st = lib.fnn_reciprocal_static(batch, a1, a2, _ptr(seeds), seeds.shape[-1], ctypes.byref(o),
                                    _ptr(out["seed_i"]), _ptr(out["seed_j"]), _ptr(out["seed_iter"]),
-                                   _ptr(out["pairs"]), _ptr(out["n_pairs"]), _stream_ptr(stream, v1[0].device))
+                                   _ptr(out["pairs"]), _ptr(out["n_pairs"]), _stream_ptr(stream, _dims(v1)[3]))
     if st != 0:
         raise FnnError(st, "fnn_reciprocal_static")
     return out
@@ -255,9 +277,8 @@ def fnn_mutual_dense(d1: MapsLike, d2: MapsLike, compute="f16", out: Optional[di
     nn12, s12 [batch][n], nn21, s21 [batch][m], pairs [batch][min(n,m)][2], n_pairs [batch]."""
     lib = load_library()
     v1, v2 = _as_pairs(d1), _as_pairs(d2)
-    batch = len(v1)
-    device = v1[0].device
-    n, m = v1[0].shape[0], v2[0].shape[0]
+    batch, n, d, device = _dims(v1)
+    m = _dims(v2)[1]
     if out is None:
         out = {
             "nn12": torch.empty((batch, n), dtype=torch.int32, device=device),
@@ -268,11 +289,10 @@ def fnn_mutual_dense(d1: MapsLike, d2: MapsLike, compute="f16", out: Optional[di
             "n_pairs": torch.empty((batch,), dtype=torch.int32, device=device),
         }
     o = _opts(compute, normalize=normalize, l2=l2, split=split)
-    need = fnn_workspace_bytes_opts(batch, n, m, v1[0].shape[1], 0, compute, l2=l2, split=split)
-    workspace = _workspace(workspace, need, device)
+    if workspace is None:
+        workspace = _workspace(fnn_workspace_bytes_opts(batch, n, m, d, 0, compute, l2=l2, split=split), device)
     a1, a2 = _map_array(v1), _map_array(v2)
-    st = lib.fnn_mutual_dense(batch, ctypes.cast(a1, ctypes.c_void_p), ctypes.cast(a2, ctypes.c_void_p),
-                              ctypes.byref(o), _ptr(out["nn12"]), _ptr(out.get("s12")), _ptr(out["nn21"]),
+    st = lib.fnn_mutual_dense(batch, a1, a2, ctypes.byref(o), _ptr(out["nn12"]), _ptr(out.get("s12")), _ptr(out["nn21"]),
                               _ptr(out.get("s21")), _ptr(out["pairs"]), _ptr(out["n_pairs"]),
                               _ptr(workspace), workspace.numel(), _stream_ptr(stream, device))
     if st != 0:
@@ -292,11 +312,11 @@ def fnn_nearest_blocked(src: torch.Tensor, tgt: torch.Tensor, block_rows: int, b
     out_score = torch.empty((nq,), dtype=torch.float32, device=device)
     need = int(lib.fnn_blocked_workspace_bytes(src.shape[0], tgt.shape[0], src.shape[1], block_rows, block_cols,
                                                _COMPUTE[compute]))
-    workspace = _workspace(workspace, need, device)
+    if workspace is None:
+        workspace = _workspace(need, device)
     o = _opts(compute, normalize=normalize, half_accumulate=half_accumulate)
     sa, ta = _map_array([src]), _map_array([tgt])
-    st = lib.fnn_nearest_blocked(ctypes.cast(sa, ctypes.c_void_p), _ptr(q_idx), nq, ctypes.cast(ta, ctypes.c_void_p),
-                                 ctypes.byref(o), block_rows, block_cols, _ptr(out_idx), _ptr(out_score),
+    st = lib.fnn_nearest_blocked(sa, _ptr(q_idx), nq, ta, ctypes.byref(o), block_rows, block_cols, _ptr(out_idx), _ptr(out_score),
                                  _ptr(workspace), workspace.numel(), _stream_ptr(stream, device))
     if st != 0:
         raise FnnError(st, "fnn_nearest_blocked")
