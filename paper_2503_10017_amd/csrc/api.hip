@@ -732,7 +732,12 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
 
     // the prepare launch also clears the key tables and the sort bitmap and sets U^0 = seeds (a small
     // pair's own workgroup keeps all of that in LDS)
-    const bool walk = walk_applies(n, m, n_seeds, opts->max_iter, compute, L.maps.dp);
+    const char *p1 = (const char*)L.maps.p1, *p2 = (const char*)L.maps.p2;
+    int64_t bs1 = L.maps.bstride1, bs2 = L.maps.bstride2;
+    const bool direct1 = direct_layout(batch, d1, opts, L.maps.dp, &p1, &bs1);
+    const bool direct2 = direct_layout(batch, d2, opts, L.maps.dp, &p2, &bs2);
+    const bool one_group = walk_applies(n, m, n_seeds, opts->max_iter, compute, L.maps.dp);
+    const bool walk = one_group || (!(direct1 && direct2) && groups_apply(n, m, n_seeds, batch, opts->max_iter, compute, L.maps.dp));
     PrepExtra extra;
     memset(&extra, 0, sizeof(extra));
     if (!walk) {
@@ -744,10 +749,6 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         extra.n_active = L.st.n_active[0];
         extra.n_seeds = ns;
     }
-    const char *p1 = (const char*)L.maps.p1, *p2 = (const char*)L.maps.p2;
-    int64_t bs1 = L.maps.bstride1, bs2 = L.maps.bstride2;
-    const bool direct1 = direct_layout(batch, d1, opts, L.maps.dp, &p1, &bs1);
-    const bool direct2 = direct_layout(batch, d2, opts, L.maps.dp, &p2, &bs2);
     // fp32 maps of the paper's shape: no prepare pass; the first forward and the first backward
     // search read the caller's maps and leave the prepared copies behind for the later searches
     const bool fused = !walk && raw_first_search(batch, d1, d2, opts, n_seeds);
@@ -797,7 +798,12 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         wa.seed_iter = seed_iter;
         wa.pairs = pairs;
         wa.n_pairs = n_pairs;
-        FNN_TRY(launch_walk(wa, batch, compute, L.maps.dp, s));
+        if (one_group) {
+            FNN_TRY(launch_walk(wa, batch, compute, L.maps.dp, s));
+        } else {
+            FNN_TRY(launch_groups(wa, batch, compute, L.maps.dp, s));
+            FNN_TRY(launch_recip_dedup(L.st, ns, batch, seed_i, seed_j, seed_iter, pairs, n_pairs, s));
+        }
         return FNN_OK;
     }
 

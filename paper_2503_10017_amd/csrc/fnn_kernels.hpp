@@ -291,6 +291,9 @@ struct WalkArgs {
 // true if a pair is small enough that one workgroup beats the launch sequence
 bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int compute, int dp);
 hipError_t launch_walk(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s);
+// true if one workgroup per 32 seeds beats the launch sequence; the outputs of the sort (pairs, n_pairs) are launch_recip_dedup's
+bool groups_apply(int64_t n, int64_t m, int64_t n_seeds, int batch, int32_t max_iter, int compute, int dp);
+hipError_t launch_groups(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s);
 
 // ---- dense mutual nearest neighbours -----------------------------------------------------
 struct DenseArgs {

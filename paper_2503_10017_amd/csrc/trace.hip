@@ -100,6 +100,7 @@ const char* fnn_trace_kind_name(int32_t kind) {
         case TK_COARSE: return "coarse_kernel";
         case TK_REFINE: return "refine_kernel";
         case TK_DENSE_SELECT: return "dense_select_kernel";
+        case TK_RECIP_GROUPS: return "recip_groups_kernel";
         default: return "unknown";
     }
 }

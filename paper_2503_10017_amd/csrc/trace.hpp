@@ -26,7 +26,8 @@ enum TraceKind : int {
     TK_COARSE = 15,
     TK_REFINE = 16,
     TK_DENSE_SELECT = 17,
-    TK_COUNT = 18
+    TK_RECIP_GROUPS = 18,
+    TK_COUNT = 19
 };
 
 // Returns false when no trace is open or it is full; otherwise hands out the next event pair.

@@ -18,15 +18,18 @@ constexpr int WALK_THREADS = WALK_WAVES * 64;
 constexpr int WALK_MAX_SEEDS = 96;  // see walk_applies()
 static_assert(WALK_MAX_SEEDS <= WALK_THREADS, "the compaction handles one slot per thread");
 
-// Query blocks a wave multiplies with each loaded tile and tiles it keeps in flight: 128 registers
-// (four waves per SIMD) hold the query fragments, the results and the ring.
-template <int CT, int DP>
+// Query blocks R that a wave multiplies with each loaded tile, tiles it keeps in flight and queries that it resolves at a
+// time: 128 registers (four waves per SIMD) hold the query fragments, the results and the ring.  Two blocks share
+// a tile's load; one block alone (at most 32 live seeds) is half the products, leaves room for a longer ring, and
+// its 32 queries are two for each wave.
+template <int CT, int DP, int R>
 struct WalkShape {
     static constexpr int FRAG_REGS = Ops<CT, DP>::ROW_BYTES / 8;
-    static constexpr int R = FRAG_REGS <= 8 ? 2 : 1;
-    static constexpr int P = FRAG_REGS <= 6 ? 4 : 2;
-    static constexpr int Q = FRAG_REGS <= 6 ? 4 : (FRAG_REGS <= 8 ? 2 : 1);  // queries a wave resolves at a time
+    static constexpr int P = FRAG_REGS <= 6 ? (R == 1 ? 6 : 4) : 2;
+    static constexpr int Q = FRAG_REGS <= 8 ? (R == 1 || FRAG_REGS > 6 ? 2 : 4) : 1;
 };
+template <int CT, int DP>
+constexpr int walk_blocks() { return Ops<CT, DP>::ROW_BYTES / 8 <= 8 ? 2 : 1; }
 
 // Nearest candidate of every live slot: queries are rows[slot] of src, the answers go to found[slot].
 // Two passes as in the search of its own (search.hip): a unit of pass 1 is R query blocks against one
@@ -34,12 +37,12 @@ struct WalkShape {
 // winning tile, Q queries of a wave at a time so that their loads overlap.  (Tracking the candidate
 // itself in pass 1 needs no second pass but 40 more vector instructions per product: 229 us instead
 // of 142 us per call for a 128x96 pair with 192 seeds.)
-template <int CT, int DP>
+template <int CT, int DP, int R>
 __device__ __forceinline__ void walk_search(const char* src, int src_rows, const int32_t* rows, const char* tgt, int m, int n_act,
                                             u64* keys, int32_t* found) {
     using O = Ops<CT, DP>;
     using Frag = typename O::Frag;
-    constexpr int R = WalkShape<CT, DP>::R, P = WalkShape<CT, DP>::P, Q = WalkShape<CT, DP>::Q;
+    constexpr int P = WalkShape<CT, DP, R>::P, Q = WalkShape<CT, DP, R>::Q;
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float ninf = -__builtin_inff();
@@ -154,8 +157,14 @@ __global__ __launch_bounds__(WALK_THREADS) void recip_walk_kernel(WalkArgs a) {
     }
     for (int i = me; i < a.n_words; i += WALK_THREADS) bitmap[i] = 0;
     for (int t = 0; n_act > 0; ++t) {  // n_act is uniform in the workgroup; it is 0 after max_iter trips at the latest
-        walk_search<CT, DP>(p1, a.rows1, u, p2, a.m, n_act, keys, v);       // V^t = NN_2(U^t)
-        walk_search<CT, DP>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
+        constexpr int R = walk_blocks<CT, DP>();
+        if (R == 1 || n_act <= 32) {
+            walk_search<CT, DP, 1>(p1, a.rows1, u, p2, a.m, n_act, keys, v);  // V^t = NN_2(U^t)
+            walk_search<CT, DP, 1>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
+        } else {
+            walk_search<CT, DP, R>(p1, a.rows1, u, p2, a.m, n_act, keys, v);
+            walk_search<CT, DP, R>(p2, a.rows2, v, p1, a.n, n_act, keys, w);
+        }
         const bool last = t + 1 >= a.max_iter;
         bool survive = false;
         int32_t u_next = 0, my_sid = 0;
@@ -208,6 +217,56 @@ __global__ __launch_bounds__(WALK_THREADS) void recip_walk_kernel(WalkArgs a) {
     if (me == 0) a.n_pairs[b] = count;
 }
 
+// The same walk with a workgroup for every 32 seeds of a pair: seeds do not meet before the final sort, which is
+// recip_dedup_kernel's here.  A group sweeps the whole map on its own compute unit, so this is for small maps
+// (groups_apply()), where the searches of the ordinary sequence are launches and latency too.
+constexpr int GROUP_SEEDS = 32;
+template <int CT, int DP>
+__global__ __launch_bounds__(WALK_THREADS) void recip_groups_kernel(WalkArgs a) {
+    __shared__ u64 keys[GROUP_SEEDS];
+    __shared__ int32_t u[GROUP_SEEDS], v[GROUP_SEEDS], w[GROUP_SEEDS], sid[GROUP_SEEDS];  // as in recip_walk_kernel
+    __shared__ int live;
+    const int b = blockIdx.y, first = blockIdx.x * GROUP_SEEDS, me = threadIdx.x;
+    const int64_t base = (int64_t)b * a.n_seeds;
+    const char* p1 = a.p1 + (int64_t)b * a.bstride1;
+    const char* p2 = a.p2 + (int64_t)b * a.bstride2;
+
+    int n_act = min(GROUP_SEEDS, a.n_seeds - first);
+    if (me < n_act) {
+        u[me] = a.seeds[base + first + me];
+        sid[me] = first + me;
+    }
+    for (int t = 0; n_act > 0; ++t) {  // uniform; 0 after max_iter trips at the latest
+        walk_search<CT, DP, 1>(p1, a.rows1, u, p2, a.m, n_act, keys, v);  // V^t = NN_2(U^t)
+        walk_search<CT, DP, 1>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
+        if (me < 64) {  // the first wave; all of its reads come before its writes
+            const bool last = t + 1 >= a.max_iter;
+            bool survive = false;
+            int32_t u_next = 0, my_sid = 0;
+            if (me < n_act) {
+                my_sid = sid[me];
+                u_next = w[me];
+                const bool converged = u_next == u[me];
+                survive = !converged && !last;
+                if (!survive) {
+                    a.seed_i[base + my_sid] = u[me];
+                    a.seed_j[base + my_sid] = v[me];
+                    a.seed_iter[base + my_sid] = converged ? t : -1;
+                }
+            }
+            const u64 stay = __ballot(survive);
+            if (survive) {
+                const int pos = __popcll(stay & ((1ull << me) - 1ull));
+                u[pos] = u_next;
+                sid[pos] = my_sid;
+            }
+            if (me == 0) live = __popcll(stay);
+        }
+        __syncthreads();
+        n_act = live;  // written again behind the barriers of the next searches
+    }
+}
+
 static size_t walk_lds_bytes(int64_t n, int64_t n_seeds) {
     return (size_t)n_seeds * (sizeof(u64) + 4 * sizeof(int32_t)) + (size_t)((n + 31) / 32) * 2 * sizeof(int32_t);
 }
@@ -235,6 +294,40 @@ bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int c
     if (blocks * tiles * (costly ? 5 : 1) > 100 * (int64_t)max_iter) return false;
     if (costly) return blocks == 1 && tiles <= 24;
     return (blocks + 1) / 2 * 2 * tiles <= (dp > 24 ? 240 : 350);
+}
+
+// Where a workgroup per 32 seeds is no slower than the launch sequence, however long the seeds keep moving.  Microseconds per
+// call (replayed from a graph, fp16, 24 channels), groups / sequence, with every seed live for all ten allowed iterations and with
+// all of them settled in the first:
+//     200 seeds, 1 pair     60 tiles 112 / 187 and 26 / 87,   240 tiles 172 / 190 and 34 / 87,   400 tiles 220 / 197 and 59 / 95
+//     60 seeds, 4 pairs     (200 tiles and on: fewer walk in one workgroup per pair) 200 tiles 159 / 173 and 32 / 85, 300 189 / 174 and 36 / 86
+//     256 seeds, 32 pairs   60 tiles 132 / 249 and 33 / 96,   150 tiles 225 / 285 and 46 / 105,  250 tiles 317 / 303 and 59 / 111
+// With two allowed iterations the lines cross at 240 and 150 tiles too.  A full chip sweeps each tile at two thirds of the speed.
+// More than one workgroup per compute unit would walk in turns.  Rows of 32 channels are a third wider, fp32 products and
+// two-term rows several times as long per tile.  Past 256 seeds, and on maps that need no prepared copy, the sequence runs as before.
+bool groups_apply(int64_t n, int64_t m, int64_t n_seeds, int batch, int32_t max_iter, int compute, int dp) {
+    if (n_seeds < 1 || n_seeds > 256 || n < 1 || m < 1 || max_iter < 1 || compute == FNN_F32 || dp > 32) return false;
+    const int64_t groups = (n_seeds + GROUP_SEEDS - 1) / GROUP_SEEDS * batch, tiles = ((n > m ? n : m) + 31) / 32;
+    if (groups > 256) return false;
+    if (groups > 64) return tiles <= (dp > 24 ? 100 : 150);
+    return tiles <= (dp > 24 ? 160 : 240);
+}
+template <int CT, int DP>
+static hipError_t launch_groups_t(const WalkArgs& a, int batch, hipStream_t s) {
+    const unsigned groups = (a.n_seeds + GROUP_SEEDS - 1) / GROUP_SEEDS;
+    return launch(TK_RECIP_GROUPS, recip_groups_kernel<CT, DP>, dim3(groups, batch), dim3(WALK_THREADS), 0, s, a);
+}
+hipError_t launch_groups(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s) {
+    if (compute == FNN_F16) {
+        if (dp == 16) return launch_groups_t<CT_F16, 16>(a, batch, s);
+        if (dp == 24) return launch_groups_t<CT_F16, 24>(a, batch, s);
+        if (dp == 32) return launch_groups_t<CT_F16, 32>(a, batch, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 16) return launch_groups_t<CT_BF16, 16>(a, batch, s);
+        if (dp == 24) return launch_groups_t<CT_BF16, 24>(a, batch, s);
+        if (dp == 32) return launch_groups_t<CT_BF16, 32>(a, batch, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int CT, int DP>
