@@ -5,8 +5,10 @@
 // of device time and up), of which its arithmetic is 2 us.  Here the searches of a pair follow one
 // another behind workgroup barriers, and the loop really ends when no seed is left.
 //
-// What bounds it: the latency of a search (query rows, first tiles, LDS merge, winning tiles: 4 us), then the
+// What bounds it: the latency of a search (first tiles, LDS merge, winning tiles), then the
 // arithmetic of the one compute unit that a pair occupies; walk_applies() says up to which size the host chooses it.
+// The rows that a search finds stay in LDS as the next one's queries, and that one's first tiles are loaded meanwhile:
+// 64x48 with 48 seeds 37.0 -> 32.1 us a call, and 46.7 -> 43.7 before that (another, slower machine) when one block of queries is multiplied alone.
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
 #include "trace.hpp"
@@ -26,51 +28,87 @@ template <int CT, int DP, int R>
 struct WalkShape {
     static constexpr int FRAG_REGS = Ops<CT, DP>::ROW_BYTES / 8;
     static constexpr int P = FRAG_REGS <= 6 ? (R == 1 ? 6 : 4) : 2;
-    static constexpr int Q = FRAG_REGS <= 8 ? (R == 1 || FRAG_REGS > 6 ? 2 : 4) : 1;
+    static constexpr bool AHEAD = FRAG_REGS <= 12;  // a search's first tiles are loaded while the one before it ends
+    static constexpr int Q = FRAG_REGS <= 8 ? 2 : 1;  // (four at a time spill beside the ring)
 };
 template <int CT, int DP>
 constexpr int walk_blocks() { return Ops<CT, DP>::ROW_BYTES / 8 <= 8 ? 2 : 1; }
 
-// Nearest candidate of every live slot: queries are rows[slot] of src, the answers go to found[slot].
+// Row j of a prepared map as its fragments hold it, lane half h's half of it, into a row in LDS.
+template <int CT, int DP>
+__device__ __forceinline__ void store_row(char* row, int h, const typename Ops<CT, DP>::Frag& f) {
+    using O = Ops<CT, DP>;
+    if constexpr (O::ROW_BYTES == 48) {
+        O::store_tile(row, 0, h, f);
+    } else {
+#pragma unroll
+        for (int i = 0; i < O::NV; ++i) reinterpret_cast<uint4*>(row + h * O::LANE_BYTES)[i] = f.v[i];
+    }
+}
+
+// How the 16 waves share a search: R query blocks against one chunk of the tiles each (never more units than waves).
+template <int R>
+struct WalkSplit {
+    int m_tiles, groups, per_chunk, chunks;
+    __device__ __forceinline__ WalkSplit(int m, int n_act) {
+        m_tiles = (m + 31) / 32;
+        groups = (n_act + 32 * R - 1) / (32 * R);
+        chunks = max(1, WALK_WAVES / groups);
+        per_chunk = (m_tiles + chunks - 1) / chunks;
+        chunks = (m_tiles + per_chunk - 1) / per_chunk;
+    }
+};
+
+// The first tiles of this wave's chunk.
+template <int CT, int DP, int R>
+struct WalkRing {
+    static constexpr int P = WalkShape<CT, DP, R>::P;
+    typename Ops<CT, DP>::Frag tile[P];
+    __device__ __forceinline__ void fill(const char* tgt, int m, int n_act, int wave, int c, int h) {
+        const WalkSplit<R> split(m, n_act);
+        const int t0 = wave / split.groups * split.per_chunk, t1 = min(t0 + split.per_chunk, split.m_tiles);
+#pragma unroll
+        for (int p = 0; p < P; ++p)  // a wave without a chunk reads the last tile and drops it
+            tile[p] = Ops<CT, DP>::stream_tile(tgt + (int64_t)max(min(t0 + p, t1 - 1), 0) * (32 * Ops<CT, DP>::ROW_BYTES), c, h);
+    }
+};
+
+// Nearest candidate of every live slot: the query of a slot is row at[slot] (at: NULL, row `slot`) of `rows` in LDS, the answers
+// go to found[slot], the candidates' rows to found_rows, also in LDS, where the next search finds its queries.
 // Two passes as in the search of its own (search.hip): a unit of pass 1 is R query blocks against one
 // chunk of the tiles, shared among the 16 waves and merged in LDS; pass 2 recomputes each query's
 // winning tile, Q queries of a wave at a time so that their loads overlap.  (Tracking the candidate
 // itself in pass 1 needs no second pass but 40 more vector instructions per product: 229 us instead
 // of 142 us per call for a 128x96 pair with 192 seeds.)
+// A search waits for two things from memory only, its first tiles and the winning ones, and the first tiles are asked for
+// while the search before it names its winners (`next`, or NULL).  `keys` are empty on entry; next_keys are emptied.
 template <int CT, int DP, int R>
-__device__ __forceinline__ void walk_search(const char* src, int src_rows, const int32_t* rows, const char* tgt, int m, int n_act,
-                                            u64* keys, int32_t* found) {
+__device__ __forceinline__ void walk_search(const char* rows, const int32_t* at, const char* tgt, int m, int n_act, u64* keys, int32_t* found,
+                                            char* found_rows, WalkRing<CT, DP, R>& ring, u64* next_keys, const char* next, int next_m) {
     using O = Ops<CT, DP>;
     using Frag = typename O::Frag;
     constexpr int P = WalkShape<CT, DP, R>::P, Q = WalkShape<CT, DP, R>::Q;
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float ninf = -__builtin_inff();
-    for (int s = threadIdx.x; s < n_act; s += WALK_THREADS) keys[s] = 0;
-    __syncthreads();  // rows (written by the caller) and the empty keys are visible
+    for (int s = threadIdx.x; s < n_act; s += WALK_THREADS) next_keys[s] = 0;
 
     auto query = [&](int slot) {  // slots past the last live one repeat it; their results are dropped
-        const int32_t row = rows[min(slot, n_act - 1)];
-        return O::load(src + (int64_t)min(max(row, 0), src_rows - 1) * O::ROW_BYTES, h);
+        const int s = min(slot, n_act - 1);
+        return O::load(rows + (at ? at[s] : s) * O::ROW_BYTES, h);
     };
-    const int m_tiles = (m + 31) / 32;
-    const int groups = (n_act + 32 * R - 1) / (32 * R);
-    int chunks = max(1, WALK_WAVES / groups);
-    const int per_chunk = (m_tiles + chunks - 1) / chunks;
-    chunks = (m_tiles + per_chunk - 1) / per_chunk;
-    for (int unit = wave; unit < groups * chunks; unit += WALK_WAVES) {
-        const int slot0 = unit % groups * (32 * R);
-        const int t0 = unit / groups * per_chunk, t1 = min(t0 + per_chunk, m_tiles);
-        Frag ring[P], q[R];
+    const WalkSplit<R> split(m, n_act);
+    const int m_tiles = split.m_tiles;
+    if constexpr (!WalkShape<CT, DP, R>::AHEAD) ring.fill(tgt, m, n_act, wave, c, h);
+    if (wave < split.groups * split.chunks) {
+        const int slot0 = wave % split.groups * (32 * R);
+        const int t0 = wave / split.groups * split.per_chunk, t1 = min(t0 + split.per_chunk, m_tiles);
+        Frag q[R];
         float best[R];
         int best_tile[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) q[r] = query(slot0 + r * 32 + c);
-#pragma unroll
-        for (int p = 0; p < P; ++p) ring[p] = O::stream_tile(tgt + (int64_t)min(t0 + p, t1 - 1) * (32 * O::ROW_BYTES), c, h);
-#pragma unroll
         for (int r = 0; r < R; ++r) {
-            arrived(q[r]);
+            q[r] = query(slot0 + r * 32 + c);
             best[r] = ninf;
             best_tile[r] = 0x7FFFFFFF;
         }
@@ -79,8 +117,8 @@ __device__ __forceinline__ void walk_search(const char* src, int src_rows, const
             for (int p = 0; p < P; ++p) {
                 const int t = tb + p;
                 if (__builtin_expect(t < t1, 1)) {  // uniform
-                    const Frag cur = ring[p];
-                    ring[p] = O::stream_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+                    const Frag cur = ring.tile[p];
+                    ring.tile[p] = O::stream_tile(tgt + (int64_t)min(t + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
                     f32x16 acc[R];
 #pragma unroll
                     for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
@@ -113,6 +151,7 @@ __device__ __forceinline__ void walk_search(const char* src, int src_rows, const
             if (h == 0 && slot < n_act) atomicMax(&keys[slot], pack_key(best[r], best_tile[r]));
         }
     }
+    if (WalkShape<CT, DP, R>::AHEAD && next) ring.fill(next, next_m, n_act, wave, c, h);
     __syncthreads();
     for (int s0 = wave * Q; s0 < n_act; s0 += WALK_WAVES * Q) {
         Frag q[Q], cand[Q];
@@ -126,45 +165,64 @@ __device__ __forceinline__ void walk_search(const char* src, int src_rows, const
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             const int j = lowest_at_maximum(O::mma(cand[i], q[i]), tile[i], m, h).idx;
-            if (lane == 0 && s0 + i < n_act) found[s0 + i] = j;
+            if (s0 + i < n_act) {
+                if (lane == 0) found[s0 + i] = j;
+                if (c == (j & 31)) store_row<CT, DP>(found_rows + (s0 + i) * O::ROW_BYTES, h, cand[i]);
+            }
         }
     }
     __syncthreads();
 }
 
-// LDS (dynamic): keys[n_seeds], then u, v, w (U^t, V^t, U^{t+1}) and the seed number per slot, then
-// the bitmap of the matched pixels of image 1 and the rank of each of its words.
+// The seeds' rows of image 1, one thread per 8 bytes, and their indices.
+template <int CT, int DP>
+__device__ __forceinline__ void walk_start(const WalkArgs& a, const int32_t* seeds, const char* p1, int n_act, int32_t* u, int32_t* at, u64* keys, char* rows) {
+    constexpr int ROW_BYTES = Ops<CT, DP>::ROW_BYTES, WORDS = ROW_BYTES / 8;
+    for (int i = threadIdx.x; i < n_act * WORDS; i += WALK_THREADS) {
+        const int slot = i / WORDS, word = i % WORDS;
+        const int32_t seed = seeds[slot];
+        const int64_t row = min(max(seed, 0), a.rows1 - 1);
+        reinterpret_cast<uint2*>(rows + slot * ROW_BYTES)[word] = reinterpret_cast<const uint2*>(p1 + row * ROW_BYTES)[word];
+        if (word == 0) {
+            u[slot] = seed;
+            at[slot] = slot;
+            keys[slot] = 0;
+        }
+    }
+}
+
+// LDS (dynamic): two key tables [n_seeds], then u, v, w (U^t, V^t, U^{t+1}), the seed number and the place of its row per slot,
+// the bitmap of the matched pixels of image 1 and the rank of each of its words, and the rows of V^t and U^{t+1}.
 template <int CT, int DP>
 __global__ __launch_bounds__(WALK_THREADS) void recip_walk_kernel(WalkArgs a) {
-    extern __shared__ u64 walk_lds[];
+    using O = Ops<CT, DP>;
+    extern __shared__ uint4 walk_lds[];
     __shared__ int wave_sums[17];
-    u64* keys = walk_lds;
-    int32_t* u = reinterpret_cast<int32_t*>(keys + a.n_seeds);
+    char* w_rows = reinterpret_cast<char*>(walk_lds);  // whole rows of 16 bytes and more first
+    char* v_rows = w_rows + a.n_seeds * O::ROW_BYTES;
+    u64* keys_f = reinterpret_cast<u64*>(v_rows + a.n_seeds * O::ROW_BYTES);
+    u64* keys_b = keys_f + a.n_seeds;
+    int32_t* u = reinterpret_cast<int32_t*>(keys_b + a.n_seeds);
     int32_t* v = u + a.n_seeds;
     int32_t* w = v + a.n_seeds;
     int32_t* sid = w + a.n_seeds;
-    uint32_t* bitmap = reinterpret_cast<uint32_t*>(sid + a.n_seeds);
+    int32_t* at = sid + a.n_seeds;
+    uint32_t* bitmap = reinterpret_cast<uint32_t*>(at + a.n_seeds);
     int32_t* word_rank = reinterpret_cast<int32_t*>(bitmap + a.n_words);
     const int b = blockIdx.x, me = threadIdx.x;
+    const int lane = me & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(me >> 6);
     const int64_t base = (int64_t)b * a.n_seeds;
     const char* p1 = a.p1 + (int64_t)b * a.bstride1;
     const char* p2 = a.p2 + (int64_t)b * a.bstride2;
 
     int n_act = a.n_seeds;
-    if (me < n_act) {
-        u[me] = a.seeds[base + me];
-        sid[me] = me;
-    }
+    walk_start<CT, DP>(a, a.seeds + base, p1, n_act, u, at, keys_f, w_rows);
+    if (me < n_act) sid[me] = me;
     for (int i = me; i < a.n_words; i += WALK_THREADS) bitmap[i] = 0;
-    for (int t = 0; n_act > 0; ++t) {  // n_act is uniform in the workgroup; it is 0 after max_iter trips at the latest
-        constexpr int R = walk_blocks<CT, DP>();
-        if (R == 1 || n_act <= 32) {
-            walk_search<CT, DP, 1>(p1, a.rows1, u, p2, a.m, n_act, keys, v);  // V^t = NN_2(U^t)
-            walk_search<CT, DP, 1>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
-        } else {
-            walk_search<CT, DP, R>(p1, a.rows1, u, p2, a.m, n_act, keys, v);
-            walk_search<CT, DP, R>(p2, a.rows2, v, p1, a.n, n_act, keys, w);
-        }
+    __syncthreads();
+
+    auto step = [&](int t) {
         const bool last = t + 1 >= a.max_iter;
         bool survive = false;
         int32_t u_next = 0, my_sid = 0;
@@ -185,8 +243,30 @@ __global__ __launch_bounds__(WALK_THREADS) void recip_walk_kernel(WalkArgs a) {
         if (survive) {
             u[pos] = u_next;
             sid[pos] = my_sid;
+            at[pos] = me;
         }
-        n_act = kept;
+        n_act = kept;  // 0 after max_iter trips at the latest
+        __syncthreads();
+    };
+    constexpr int R = walk_blocks<CT, DP>();
+    int t = 0;
+    if constexpr (R > 1) {
+        for (; n_act > 32; ++t) {
+            WalkRing<CT, DP, R> ring;
+            ring.fill(p2, a.m, n_act, wave, c, h);
+            walk_search<CT, DP, R>(w_rows, at, p2, a.m, n_act, keys_f, v, v_rows, ring, keys_b, p1, a.n);     // V^t = NN_2(U^t)
+            walk_search<CT, DP, R>(v_rows, nullptr, p1, a.n, n_act, keys_b, w, w_rows, ring, keys_f, nullptr, 0);  // U^{t+1} = NN_1(V^t)
+            step(t);
+        }
+    }
+    if (n_act > 0) {
+        WalkRing<CT, DP, 1> ring;
+        ring.fill(p2, a.m, n_act, wave, c, h);
+        for (; n_act > 0; ++t) {
+            walk_search<CT, DP, 1>(w_rows, at, p2, a.m, n_act, keys_f, v, v_rows, ring, keys_b, p1, a.n);
+            walk_search<CT, DP, 1>(v_rows, nullptr, p1, a.n, n_act, keys_b, w, w_rows, ring, keys_f, p2, a.m);
+            step(t);
+        }
     }
 
     // step 4: the matches as a set, sorted (see recip_dedup_kernel).  A converged seed's pixels are
@@ -223,22 +303,27 @@ __global__ __launch_bounds__(WALK_THREADS) void recip_walk_kernel(WalkArgs a) {
 constexpr int GROUP_SEEDS = 32;
 template <int CT, int DP>
 __global__ __launch_bounds__(WALK_THREADS) void recip_groups_kernel(WalkArgs a) {
-    __shared__ u64 keys[GROUP_SEEDS];
-    __shared__ int32_t u[GROUP_SEEDS], v[GROUP_SEEDS], w[GROUP_SEEDS], sid[GROUP_SEEDS];  // as in recip_walk_kernel
+    using O = Ops<CT, DP>;
+    __shared__ __attribute__((aligned(16))) char v_rows[GROUP_SEEDS * O::ROW_BYTES], w_rows[GROUP_SEEDS * O::ROW_BYTES];
+    __shared__ u64 keys_f[GROUP_SEEDS], keys_b[GROUP_SEEDS];
+    __shared__ int32_t u[GROUP_SEEDS], v[GROUP_SEEDS], w[GROUP_SEEDS], sid[GROUP_SEEDS], at[GROUP_SEEDS];  // as in recip_walk_kernel
     __shared__ int live;
     const int b = blockIdx.y, first = blockIdx.x * GROUP_SEEDS, me = threadIdx.x;
+    const int lane = me & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(me >> 6);
     const int64_t base = (int64_t)b * a.n_seeds;
     const char* p1 = a.p1 + (int64_t)b * a.bstride1;
     const char* p2 = a.p2 + (int64_t)b * a.bstride2;
 
     int n_act = min(GROUP_SEEDS, a.n_seeds - first);
-    if (me < n_act) {
-        u[me] = a.seeds[base + first + me];
-        sid[me] = first + me;
-    }
+    WalkRing<CT, DP, 1> ring;
+    ring.fill(p2, a.m, n_act, wave, c, h);
+    walk_start<CT, DP>(a, a.seeds + base + first, p1, n_act, u, at, keys_f, w_rows);
+    if (me < n_act) sid[me] = first + me;
+    __syncthreads();
     for (int t = 0; n_act > 0; ++t) {  // uniform; 0 after max_iter trips at the latest
-        walk_search<CT, DP, 1>(p1, a.rows1, u, p2, a.m, n_act, keys, v);  // V^t = NN_2(U^t)
-        walk_search<CT, DP, 1>(p2, a.rows2, v, p1, a.n, n_act, keys, w);  // U^{t+1} = NN_1(V^t)
+        walk_search<CT, DP, 1>(w_rows, at, p2, a.m, n_act, keys_f, v, v_rows, ring, keys_b, p1, a.n);     // V^t = NN_2(U^t)
+        walk_search<CT, DP, 1>(v_rows, nullptr, p1, a.n, n_act, keys_b, w, w_rows, ring, keys_f, p2, a.m);  // U^{t+1} = NN_1(V^t)
         if (me < 64) {  // the first wave; all of its reads come before its writes
             const bool last = t + 1 >= a.max_iter;
             bool survive = false;
@@ -259,6 +344,7 @@ __global__ __launch_bounds__(WALK_THREADS) void recip_groups_kernel(WalkArgs a) 
                 const int pos = __popcll(stay & ((1ull << me) - 1ull));
                 u[pos] = u_next;
                 sid[pos] = my_sid;
+                at[pos] = me;
             }
             if (me == 0) live = __popcll(stay);
         }
@@ -267,8 +353,8 @@ __global__ __launch_bounds__(WALK_THREADS) void recip_groups_kernel(WalkArgs a) 
     }
 }
 
-static size_t walk_lds_bytes(int64_t n, int64_t n_seeds) {
-    return (size_t)n_seeds * (sizeof(u64) + 4 * sizeof(int32_t)) + (size_t)((n + 31) / 32) * 2 * sizeof(int32_t);
+static size_t walk_lds_bytes(int64_t n, int64_t n_seeds, int row_bytes) {
+    return (size_t)n_seeds * (2 * row_bytes + 2 * sizeof(u64) + 5 * sizeof(int32_t)) + (size_t)((n + 31) / 32) * 2 * sizeof(int32_t);
 }
 
 // Where one workgroup per pair is no slower than the launch sequence, however long the seeds keep
@@ -297,20 +383,23 @@ bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int c
 }
 
 // Where a workgroup per 32 seeds is no slower than the launch sequence, however long the seeds keep moving.  Microseconds per
-// call (replayed from a graph, fp16, 24 channels), groups / sequence, with every seed live for all ten allowed iterations and with
-// all of them settled in the first:
-//     200 seeds, 1 pair     60 tiles 112 / 187 and 26 / 87,   240 tiles 172 / 190 and 34 / 87,   400 tiles 220 / 197 and 59 / 95
-//     60 seeds, 4 pairs     (200 tiles and on: fewer walk in one workgroup per pair) 200 tiles 159 / 173 and 32 / 85, 300 189 / 174 and 36 / 86
-//     256 seeds, 32 pairs   60 tiles 132 / 249 and 33 / 96,   150 tiles 225 / 285 and 46 / 105,  250 tiles 317 / 303 and 59 / 111
-// With two allowed iterations the lines cross at 240 and 150 tiles too.  A full chip sweeps each tile at two thirds of the speed.
-// More than one workgroup per compute unit would walk in turns.  Rows of 32 channels are a third wider, fp32 products and
-// two-term rows several times as long per tile.  Past 256 seeds, and on maps that need no prepared copy, the sequence runs as before.
+// call (replayed from a graph, fp16, 24 channels), groups / sequence, with every seed live for all ten allowed iterations, for
+// two, and with all of them settled in the first:
+//     200 seeds, 1 pair     145 tiles  129 / 184,  40 / 48,  29 / 86    220 tiles  150 / 187,  44 / 48,  32 / 86    320 tiles  180 / 195,  51 / 49,  36 / 87
+//     60 seeds, 4 pairs     210 tiles  147 / 171,  45 / 45,  32 / 85    320 tiles  179 / 174,  52 / 46,  36 / 85
+//     256 seeds, 32 pairs   145 tiles  191 / 284,  62 / 69,  46 / 104   220 tiles  251 / 293,  75 / 74,  55 / 109
+// and with 32 channels
+//     200 seeds, 1 pair     145 tiles  151 / 190,  43 / 49,  30 / 87    210 tiles  186 / 193,  51 / 49,  34 / 88
+//     256 seeds, 32 pairs   145 tiles  227 / 305,  68 / 75,  50 / 108
+// A full chip sweeps a tile at two thirds of the speed of a quarter of it, and more than one workgroup per compute unit would walk
+// in turns.  fp32 products and two-term rows take several times as long per tile.  Past 256 seeds, and on maps that need no prepared
+// copy, the sequence runs as before.
 bool groups_apply(int64_t n, int64_t m, int64_t n_seeds, int batch, int32_t max_iter, int compute, int dp) {
     if (n_seeds < 1 || n_seeds > 256 || n < 1 || m < 1 || max_iter < 1 || compute == FNN_F32 || dp > 32) return false;
     const int64_t groups = (n_seeds + GROUP_SEEDS - 1) / GROUP_SEEDS * batch, tiles = ((n > m ? n : m) + 31) / 32;
     if (groups > 256) return false;
-    if (groups > 64) return tiles <= (dp > 24 ? 100 : 150);
-    return tiles <= (dp > 24 ? 160 : 240);
+    if (groups > 64) return tiles <= (dp > 24 ? 145 : 210);
+    return tiles <= (dp > 24 ? 180 : 280);
 }
 template <int CT, int DP>
 static hipError_t launch_groups_t(const WalkArgs& a, int batch, hipStream_t s) {
@@ -332,7 +421,7 @@ hipError_t launch_groups(const WalkArgs& a, int batch, int compute, int dp, hipS
 
 template <int CT, int DP>
 static hipError_t launch_walk_t(const WalkArgs& a, int batch, hipStream_t s) {
-    return launch(TK_RECIP_WALK, recip_walk_kernel<CT, DP>, dim3(batch), dim3(WALK_THREADS), walk_lds_bytes(a.n, a.n_seeds), s, a);
+    return launch(TK_RECIP_WALK, recip_walk_kernel<CT, DP>, dim3(batch), dim3(WALK_THREADS), walk_lds_bytes(a.n, a.n_seeds, Ops<CT, DP>::ROW_BYTES), s, a);
 }
 
 hipError_t launch_walk(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s) {

@@ -11,7 +11,7 @@ from gpu_helpers import check_reciprocal_exact, dev, exact_maps, host
 
 pytestmark = pytest.mark.gpu
 
-FEW, MANY = {24: 240, 32: 160}, {24: 150, 32: 100}   # tiles, up to 64 workgroups and up to 256
+FEW, MANY = {24: 280, 32: 180}, {24: 210, 32: 145}   # tiles, up to 64 workgroups and up to 256
 
 
 def traced(a, b, seeds, max_iter, compute, **kw):
