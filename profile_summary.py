@@ -35,7 +35,7 @@ COMMANDS = {line.split()[0]: line.split(None, 1)[1] for line in __doc__.splitlin
 
 def is_dense_pass1(name):
     """The pass-1 kernel of the dense mode, whichever variant ran."""
-    return "dense_staged_kernel<" in name or "dense_kernel<" in name
+    return "dense_coarse_kernel<" in name or "dense_staged_kernel<" in name or "dense_kernel<" in name
 
 
 def short(name: str) -> str:
@@ -85,12 +85,12 @@ def kernel_stats() -> None:
     def avg_us(pred):
         d = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in trace if pred(r)]
         return (sum(d) / len(d), len(d)) if d else (float("nan"), 0)
-    sk_us, sk_n = avg_us(lambda r: ("search_kernel" in r["Kernel_Name"] or "search_first_kernel" in r["Kernel_Name"])
+    sk_us, sk_n = avg_us(lambda r: any(k in r["Kernel_Name"] for k in ("search_kernel", "search_first_kernel", "::coarse_kernel"))
                          and int(r.get("Grid_Size_Y") or 0) == 16)
     dk = [r for r in stats if is_dense_pass1(r["Name"])]
     lines += ["", "## Agreement with bench.py (same run, its own HIP-event timing)", ""]
     if sk_n:
-        lines.append(f"* search launches of the 16-pair batch (search_kernel and search_first_kernel together, as in bench.py's `roofline`): "
+        lines.append(f"* search launches of the 16-pair batch (coarse_kernel and search_kernel; the refine_kernel launches that bench.py's `roofline` counts with the former are left out here): "
                      f"kernel-trace average {sk_us:.2f} us over {sk_n} launches; bench.py "
                      f"`roofline.avg_launch_ms` = {bench['roofline']['avg_launch_ms']*1e3:.2f} us over its traced launches (the profiler's "
                      "average also covers the warm-up and untraced timed steps, whose launches are the same mix; the HIP events of bench.py bracket "
@@ -138,60 +138,37 @@ def hbm_traffic() -> None:
         f, w = per["fetch"].get(k, [0]), per["write"].get(k, [0])
         lines.append(f"| {k} | {len(f)} | {sum(f)/len(f)*cal['fetch']/1024:.3f} | {sum(w)/len(w)*cal['write']/1024:.3f} |")
 
-    def kernel_bytes(prefix):
-        f = [v for k, v in per["fetch"].items() if k.startswith(prefix)]
-        w = [v for k, v in per["write"].items() if k.startswith(prefix)]
-        if not f or not w:
-            return None, None, None
-        rd = sum(f[0]) / len(f[0]) * cal["fetch"] * 1024
-        wr = sum(w[0]) / len(w[0]) * cal["write"] * 1024
-        return rd, wr, f[0]
-    s_rd, s_wr, s_list = kernel_bytes("search_kernel")
-    d_rd, d_wr, _ = kernel_bytes("dense_staged_kernel")
-    if d_rd is None:
-        d_rd, d_wr, _ = kernel_bytes("dense_kernel")
     result = {"source": f"profiles/hbm_traffic_{SUFFIX}.md (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a 256 MiB copy)"}
-    if s_rd is not None and bench:
-        # bench.py runs its batched reciprocal steps first: one call that builds the outputs, the
-        # warm-up, the timed steps and the traced steps, 2 * max_iter search launches each.  The first
-        # two of a step are launches of search_first_kernel (the staged kernel that also reads the
-        # caller's fp32 maps and writes the prepared copies), the rest of search_kernel.
+
+    def mib(run, prefix, count=None):
+        rows = [x for k, v in per[run].items() if k.startswith(prefix) for x in v][:count]
+        return [x * cal[run] / 1024 for x in rows]
+    if bench and mib("fetch", "coarse_kernel"):
+        # bench.py runs its batched reciprocal steps first: one call that builds the outputs, the warm-up, the timed steps and
+        # the traced steps, 2 * max_iter searches each, of which the first four are a coarse_kernel and a refine_kernel launch.
         per_step = int(round(bench["roofline"]["launches_per_step"]))
         n_steps = 1 + bench["warmup"] + 2 * bench["steps"]
-        def mib(run, prefix, count):
-            rows = [v for k, v in per[run].items() if k.startswith(prefix)]
-            return [x * cal[run] / 1024 for x in rows[0][:count]] if rows else []
-        first_rd, first_wr = mib("fetch", "search_first_kernel", 2 * n_steps), mib("write", "search_first_kernel", 2 * n_steps)
-        n_first = len(first_rd)
-        n_rest = n_steps * per_step - n_first
-        rest_rd, rest_wr = mib("fetch", "search_kernel", n_rest), mib("write", "search_kernel", n_rest)
-        total = sum(first_rd) + sum(first_wr) + sum(rest_rd) + sum(rest_wr)
+        counts = {"coarse_kernel": 4 * n_steps, "refine_kernel<1, 24, 8, 4, false>": 4 * n_steps, "search_kernel": (per_step - 4) * n_steps}
+        total = sum(sum(mib(run, k, c)) for run in ("fetch", "write") for k, c in counts.items())
         result["search_kernel_bytes_per_launch"] = round(total / (n_steps * per_step) * 1048576)
-        live = [x for x in rest_rd if x > 1.0]
         alg = bench["roofline_hbm"]["bytes_per_launch"]
-        lines += ["", "## the search launches of the 16-pair reciprocal steps", "",
-                  f"search_first_kernel (first forward and first backward search of a step; fp32 maps in, prepared fp16 copy out), last two launches: "
-                  + ", ".join(f"{r:.1f} MiB read / {w:.1f} MiB written" for r, w in zip(first_rd[-2:], first_wr[-2:]))
-                  + ".  The fp32 maps of 16 pairs are 288 MiB, their fp16 copy 144 MiB.", "",
-                  f"search_kernel, read MiB per launch, the {per_step - 2} launches of the last step, in launch order: "
-                  + ", ".join(f"{x:.1f}" for x in rest_rd[-(per_step - 2):]), "",
-                  f"Average HBM bytes per search launch over these {n_steps * per_step} launches (read + written): "
-                  f"{result['search_kernel_bytes_per_launch']/1e6:.1f} MB; algorithmic bytes per launch (bench.py `roofline_hbm.bytes_per_launch`): "
-                  f"{alg/1e6:.1f} MB.  A live search of 16 prepared maps must read 16 x 196608 x 48 B = 151 MB = 144 MiB once; the live launches of "
-                  f"search_kernel read {sum(live)/max(len(live),1):.1f} MiB on average (the last-level cache keeps part of a map between the searches "
-                  "of a step), the launches after the last seed has converged read nothing.", ""]
-    if d_rd is not None:
-        d_names = [k for k in times if k.startswith("dense_staged_kernel")] or [k for k in times if k.startswith("dense_kernel")]
-        d_us = times.get(d_names[0]) if d_names else None
-        rate = ""
-        if d_us:
-            t = sum(d_us) / len(d_us)
-            rate = f"  At {t/1e3:.2f} ms per launch (duration under the counter run) that is {(d_rd + d_wr)/t/1e6:.2f} TB/s and does not bound the kernel."
-        result["dense_kernel_bytes_per_launch"] = round(d_rd + d_wr)
-        lines += ["## dense_kernel (cfg 3)", "",
-                  f"Reads {d_rd/1048576:.0f} MiB and writes {d_wr/1048576:.0f} MiB per launch against 19 MB of algorithmic input and 3 MB of keys: the reads are "
-                  "query blocks re-fetched by the workgroups through L2 misses, the writes are the 64-bit atomic key merges (each counted as a partial "
-                  "cache-line write)." + rate, ""]
+        lines += ["", "## the searches of the 16-pair reciprocal steps", ""]
+        for k, c in counts.items():
+            n_last = c // n_steps
+            lines.append(f"{k}, MiB read / written per launch, the {n_last} launches of the last step: "
+                         + ", ".join(f"{r:.1f} / {w:.1f}" for r, w in zip(mib("fetch", k, c)[-n_last:], mib("write", k, c)[-n_last:])))
+            lines.append("")
+        lines += [f"Average HBM bytes per search over these {n_steps * per_step} searches (read + written): "
+                  f"{result['search_kernel_bytes_per_launch']/1e6:.1f} MB; algorithmic bytes per search (bench.py `roofline_hbm.bytes_per_launch`): "
+                  f"{alg/1e6:.1f} MB.  16 prepared maps are 144 MiB, their 8-bit copies 96 MiB.", ""]
+    calls = len(per["fetch"].get(next((k for k in per["fetch"] if k.startswith("dense_coarse_kernel")), ""), []))
+    if calls:
+        parts = ("dense_coarse_kernel", "dense_select_kernel", "refine_kernel<1, 24, 8, 4, true>")
+        sums = {k: (sum(mib("fetch", k)) / calls, sum(mib("write", k)) / calls) for k in parts}
+        result["dense_kernel_bytes_per_launch"] = round(sum(r + w for r, w in sums.values()) * 1048576)
+        lines += ["## pass 1 of the dense mode (cfg 3), MiB read / written per call", "",
+                  "; ".join(f"{k} {r:.0f} / {w:.0f}" for k, (r, w) in sums.items()) + ".  The prepared maps are 18 MiB, their 8-bit copies 12, the tables of "
+                  "8-bit maxima 72 and 36.", ""]
     sys.path.insert(0, ROOT)
     from bench import csrc_fingerprint
     result["csrc_fingerprint"] = csrc_fingerprint()
@@ -210,8 +187,8 @@ def mfma_utilisation() -> None:
     for r in rows:
         disp[(r["Dispatch_Id"], r["Kernel_Name"])][r["Counter_Name"]] = float(r["Counter_Value"])
     trace = {r["Dispatch_Id"]: (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) for r in trace_rows}
-    searches = sorted([(k, v) for k, v in disp.items() if "search_first_kernel" in k[1]], key=lambda kv: -kv[1].get("SQ_INSTS_MFMA", 0))
-    first_name = "search_first_kernel"
+    searches = sorted([(k, v) for k, v in disp.items() if "::coarse_kernel" in k[1]], key=lambda kv: -kv[1].get("SQ_INSTS_MFMA", 0))
+    first_name = "coarse_kernel"
     if not searches:
         searches = sorted([(k, v) for k, v in disp.items() if "search_kernel" in k[1]], key=lambda kv: -kv[1].get("SQ_INSTS_MFMA", 0))
         first_name = "search_kernel"
@@ -235,14 +212,14 @@ def mfma_utilisation() -> None:
     names = ["duration (kernel trace)", "GPU cycles (per XCD)", "matrix instructions", "other vector instructions", "matrix cores busy",
              "vector instruction issue (4 cycles each)", "matrix busy cycles with a vector instruction co-executing",
              "wave cycles waiting on an instruction (SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES)"]
-    lines = ["# Matrix-core and vector-ALU utilisation (rocprofv3 SQ counters): search_kernel and dense_kernel", "", "Command (one counter run):", "",
+    lines = ["# Matrix-core and vector-ALU utilisation (rocprofv3 SQ counters): the 8-bit kernels", "", "Command (one counter run):", "",
              "    " + COMMANDS["mfma"], "",
              "Per dispatch.  GRBM_GUI_ACTIVE is summed over the 8 XCDs, SQ_VALU_MFMA_BUSY_CYCLES over the 1024 SIMDs; SQ_INSTS_* count wave instructions",
-             "(SQ_INSTS_VALU includes the matrix instructions).  A 32x32 product = one K=16 plus one K=8 matrix instruction.", "",
-             f"| quantity | {first_name}, first search of a step (16 x 3072 queries) | dense_kernel (cfg 3) |", "|---|---|---|"]
+             "(SQ_INSTS_VALU includes the matrix instructions).  A 32x32 product = one K=32 integer matrix instruction.", "",
+             f"| quantity | {first_name}, first search of a step (16 x 3072 queries) | dense_coarse_kernel (cfg 3) |", "|---|---|---|"]
     lines += [f"| {n} | {x} | {y} |" for n, x, y in zip(names, a, b)]
-    lines += ["", "Of the vector instructions per product, 8 (search) and 16 (dense) are the three-input maxima that fold the scores; the rest is location",
-              "tracking, address arithmetic, register copies and (dense) the per-super-block column flush."]
+    lines += ["", "Of the vector instructions per product, 8 (search) and 16 (dense) are the three-input maxima that fold the scores; the rest is cell",
+              "bounds, address arithmetic and (dense) the reduction of the column maxima at the end of a segment."]
     write(f"mfma_utilisation_{SUFFIX}.md", lines)
 
 
@@ -264,10 +241,10 @@ def lds_l2() -> None:
             if k.startswith(prefix) and counter in v:
                 return max(v[counter]) if how == "max" else sum(v[counter]) / len(v[counter])
         return float("nan")
-    kernels = [("search_first_kernel", "max", "search_first_kernel, first search of a step (fp32 maps in, LDS-staged)"),
-               ("search_kernel", "max", "search_kernel, largest launch (third search of a step: 16 x ~1450 queries)"),
+    kernels = [("coarse_kernel", "max", "coarse_kernel, first search of a step"), ("refine_kernel<1, 24, 8, 4, false>", "max", "refine_kernel, first search of a step"),
+               ("search_kernel", "max", "search_kernel, largest launch (fifth search of a step: 16 x ~106 queries)"),
                ("resolve_kernel", "max", "resolve_kernel, first resolve of a step"),
-               ("dense_staged_kernel<", "mean", "dense_staged_kernel (cfg 3; query blocks staged through LDS)"), ("prep_f32_kernel", "max", "prepare pass, largest launch (the dense legs: both maps of a pair)")]
+               ("dense_coarse_kernel<", "mean", "dense_coarse_kernel (cfg 3)"), ("quantise_kernel", "max", "quantise_kernel, largest launch (both maps of 16 pairs)")]
     lines = ["# LDS and cache counters (rocprofv3 SQ / TCP / TCC counters): bench.py workloads", "", "Commands (two counter runs):", "",
              "    " + COMMANDS["lds"], "    " + COMMANDS["l2"], "",
              "Per dispatch; SQ_BUSY_CYCLES is summed over the shader engines, the cache counters over all channels.", "",
