@@ -314,6 +314,10 @@ bool raw_rows(int32_t batch, const fnn_map* maps) {
 bool raw_options(const fnn_opts* opts) {
     return opts->flags == 0 && (opts->compute == FNN_F16 || opts->compute == FNN_BF16);
 }
+// The quantise launch of two-term rows reads the caller's rows where it can: 96 bytes instead of 160.
+bool raw_halves(int32_t batch, const fnn_map* a, const fnn_map* b, const fnn_opts* opts) {
+    return opts->flags == FNN_FLAG_SPLIT && raw_rows(batch, a) && raw_rows(batch, b);
+}
 bool raw_first_search(int32_t batch, const fnn_map* a, const fnn_map* b, const fnn_opts* opts, int64_t n_queries) {
     return raw_options(opts) && first_search_applies(n_queries, a[0].n, batch) && first_search_applies(n_queries, b[0].n, batch) &&
            raw_rows(batch, a) && raw_rows(batch, b);
@@ -580,8 +584,9 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (prepared) qa.extra = extra;
-        fill_quantise_side(qa.side[0], batch, src, raw, p1, bs1, L.maps.n_pad, C.map[0]);
-        fill_quantise_side(qa.side[1], batch, tgt, raw, p2, bs2, L.maps.m_pad, C.map[1]);
+        const bool read_raw = raw || raw_halves(batch, src, tgt, opts);
+        fill_quantise_side(qa.side[0], batch, src, read_raw, p1, bs1, L.maps.n_pad, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, tgt, read_raw, p2, bs2, L.maps.m_pad, C.map[1]);
         if (listed) {
             qa.side[0].gather = q_idx;
             qa.side[0].gather_rows = n;
@@ -593,7 +598,7 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
             }
         }
         qa.batch = batch;
-        qa.raw_rows = raw ? 1 : 0;
+        qa.raw_rows = read_raw ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = C.lower_count;
@@ -767,10 +772,11 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (prepared) qa.extra = extra;
-        fill_quantise_side(qa.side[0], batch, d1, raw, p1, bs1, L.maps.n_pad, C.map[0]);
-        fill_quantise_side(qa.side[1], batch, d2, raw, p2, bs2, L.maps.m_pad, C.map[1]);
+        const bool read_raw = raw || raw_halves(batch, d1, d2, opts);
+        fill_quantise_side(qa.side[0], batch, d1, read_raw, p1, bs1, L.maps.n_pad, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, read_raw, p2, bs2, L.maps.m_pad, C.map[1]);
         qa.batch = batch;
-        qa.raw_rows = raw ? 1 : 0;
+        qa.raw_rows = read_raw ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = RECIP_COARSE_SEARCHES * C.lower_count;
@@ -989,10 +995,11 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (raw) qa.extra = extra;
-        fill_quantise_side(qa.side[0], batch, d1, raw, (const char*)L.maps.p1, L.maps.bstride1, L.maps.n_pad, C.args.map[0]);
-        fill_quantise_side(qa.side[1], batch, d2, raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
+        const bool read_raw = raw || raw_halves(batch, d1, d2, opts);
+        fill_quantise_side(qa.side[0], batch, d1, read_raw, (const char*)L.maps.p1, L.maps.bstride1, L.maps.n_pad, C.args.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, read_raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
         qa.batch = batch;
-        qa.raw_rows = raw ? 1 : 0;
+        qa.raw_rows = read_raw ? 1 : 0;
         qa.seg_pixels = C.args.seg_pixels;
         qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
         FNN_TRY(launch_quantise(qa, opts->compute, L.maps.dp, s));

@@ -90,7 +90,8 @@ __device__ __forceinline__ float workgroup_max(float x, float* word) {  // x >= 
 // One workgroup turns one segment of prepared rows into 8-bit rows, a thread ROWS of them.  Between the segment's largest value
 // and the rounding the rows stay in registers, or, where they are too many (RELOAD), are read a second time.
 // RAW: the rows are the caller's fp32 rows of 24 channels; they are rounded to the compute format here and the
-// prepared map is written too.  Bound by memory.
+// prepared map is written too, or, with SPLIT, only the high halves are formed: the prepared rows exist, but are 160
+// bytes where the caller's are 96 (four pairs of 512x384, the whole call 737 -> 721 us).  Bound by memory.
 template <int CT, int DP, bool SPLIT, bool RAW, int THREADS, int ROWS, bool RELOAD>
 __global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
     using Row = PreparedRow<CT, DP, SPLIT>;
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
                 w[2 * q] = round_pair<CT>(v.x, v.y);
                 w[2 * q + 1] = round_pair<CT>(v.z, v.w);
             }
-            if (write && pixel < sd.n_pad) {
+            if (!SPLIT && write && pixel < sd.n_pad) {
                 uint4* out = reinterpret_cast<uint4*>(const_cast<char*>(prepared) + pixel * O::ROW_BYTES);
                 const bool real = pixel < sd.n;  // padding rows of the prepared map are zero
 #pragma unroll
@@ -134,8 +135,8 @@ __global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
                     out[q] = real ? make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]) : make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
-            for (int k = 0; k < 24; ++k) {
-                const uint32_t bits = (w[k / 2] >> (16 * (k & 1))) & 0xFFFFu;
+            for (int k = 0; k < K; ++k) {
+                const uint32_t bits = k < 24 ? (w[k < 24 ? k / 2 : 0] >> (16 * (k & 1))) & 0xFFFFu : 0;
                 x[at][k] = CT == CT_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits) : __uint_as_float(bits << 16);
             }
         } else {
@@ -546,6 +547,7 @@ static hipError_t launch_quantise_t(const QuantiseArgs& a, hipStream_t s) {
     return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW, 512, SEG_PIXELS / 512, false>, grid, dim3(512), 0, s, a);
 }
 hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream_t s) {
+    if (a.raw_rows && a.split_d) return launch_quantise_t<CT_F16, 80, true, true>(a, s);
     if (a.raw_rows) {
         if (compute == FNN_F16) return launch_quantise_t<CT_F16, 24, false, true>(a, s);
         return launch_quantise_t<CT_BF16, 24, false, true>(a, s);
