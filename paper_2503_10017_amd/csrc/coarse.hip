@@ -616,9 +616,10 @@ int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch) {
     return all < most ? all : most;
 }
 
+// Workgroups that the current device holds at once (0: unknown), and those of a launch for each pair.
 template <int PAIRS, int CELL>
-static int coarse_wgs_per_pair(int batch) {
-    static DeviceCache resident_wgs;  // workgroups the current device holds at once
+static int coarse_resident() {
+    static DeviceCache resident_wgs;
     const long long resident = resident_wgs.get([](int dev) -> long long {
         int per_cu = 0;
         hipDeviceProp_t prop;
@@ -627,16 +628,28 @@ static int coarse_wgs_per_pair(int batch) {
             return -1;
         return (long long)(per_cu > 0 ? per_cu : 1) * prop.multiProcessorCount;
     });
-    if (resident <= 0) return 0;
-    int wgs = (int)resident / batch;
+    return resident > 0 ? (int)resident : 0;
+}
+static int coarse_wgs_per_pair(int resident, int batch) {
+    int wgs = resident / batch;
     if (wgs >= 8) wgs &= ~7;  // a multiple of 8 per pair keeps the XCD renumbering a bijection
     return wgs < 1 ? 1 : wgs;
 }
+// What coarse_kernel's split of a search leaves to the busiest wave, times the waves that share a SIMD with it: the time of a
+// launch whose workgroups are all resident, in products of one pair of query blocks and one cell.
+static int64_t coarse_longest(int wide, int resident, int batch, int pairs, int n_cells) {
+    const int wgs = coarse_wgs_per_pair(resident, batch), quads = (pairs + wide * COARSE_WAVES - 1) / (wide * COARSE_WAVES);
+    int chunks = wgs / quads < n_cells ? wgs / quads : n_cells;
+    if (chunks < 1) chunks = 1;
+    const int64_t rounds = ((int64_t)quads * chunks + wgs - 1) / wgs;
+    const int per_wave = (pairs + quads * COARSE_WAVES - 1) / (quads * COARSE_WAVES), cells = (n_cells + chunks - 1) / chunks;
+    return (int64_t)resident * rounds * per_wave * cells;
+}
 template <int PAIRS, int CELL>
 static hipError_t launch_coarse_t(const SearchArgs& a, const CoarseArgs& ca, int batch, hipStream_t s) {
-    const int wgs = coarse_wgs_per_pair<PAIRS, CELL>(batch);
-    if (wgs == 0) return hipErrorUnknown;
-    return launch_detail(TK_COARSE, PAIRS * 2, coarse_kernel<PAIRS, CELL>, dim3(wgs, batch), dim3(COARSE_WAVES * 64), 0, s, a, ca);
+    const int resident = coarse_resident<PAIRS, CELL>();
+    if (resident == 0) return hipErrorUnknown;
+    return launch_detail(TK_COARSE, PAIRS * 2, coarse_kernel<PAIRS, CELL>, dim3(coarse_wgs_per_pair(resident, batch), batch), dim3(COARSE_WAVES * 64), 0, s, a, ca);
 }
 // CELL: tiles of a workgroup.
 template <int CT, int DP, int CELL, bool MASK = false>
@@ -648,13 +661,21 @@ static hipError_t launch_refine_t(const SearchArgs& a, const CoarseArgs& ca, int
 }
 template <int CT, int DP>
 static hipError_t launch_both_t(const SearchArgs& a, CoarseArgs ca, int batch, hipStream_t s) {
-    const int pairs = (a.nq + 63) / 64;
     const bool half = coarse_cells(a.nq, ca.tgt.n_segs, batch) == 2;
     ca.n_cells = ca.tgt.n_segs * (half ? 2 : 1);
     ca.cell_shift = 0;
-    // The more query blocks a wave holds, the fewer times a tile is read (every pixel of a 512x384 pair: 12 blocks 1064 us, 16 blocks
-    // 992); three quads of 12 deal 16 pairs' 96 blocks evenly, where three of 16 leave waves idle (279 and 290 us).
-    const bool six = pairs % 32 != 0 && pairs % 24 == 0;
+    // Waves of up to 16 query blocks read a tile the fewest times; with up to 12 a fourth wave fits on every SIMD.  Whichever leaves less to the
+    // busiest wave is the faster, and where both leave the same to the same quads, the fourth wave is (16 / 12 blocks, fp16, 24 channels, the
+    // whole call: 16 512x384 pairs of 2300 queries 380 / 373 us, 3072 427 / 426, 3500 467 / 495, 4608 563 / 582, 7000 768 / 804; 12 pairs of 3072
+    // 322 / 335; 30 320x240 pairs of 3072 348 / 338, 4608 452 / 459; six 640x480 pairs of 4800 358 / 349; every pixel of one 512x384 pair 1102 / 1108).
+    bool six = false;
+    if (!half) {
+        const int wide = coarse_resident<8, SEG_TILES>(), narrow = coarse_resident<6, SEG_TILES>();
+        if (wide == 0 || narrow == 0) return hipErrorUnknown;
+        const int slab_pairs = (int)((a.nq < ca.slab ? a.nq : ca.slab) + 63) / 64;
+        const int64_t of8 = coarse_longest(8, wide, batch, slab_pairs, ca.n_cells), of6 = coarse_longest(6, narrow, batch, slab_pairs, ca.n_cells);
+        six = of6 < of8 || (of6 == of8 && (slab_pairs + 31) / 32 == (slab_pairs + 23) / 24);
+    }
     for (int64_t first = 0; first < a.nq; first += ca.slab) {
         ca.first_slot = (int32_t)first;
         hipError_t e = half ? launch_coarse_t<2, SEG_TILES / 2>(a, ca, batch, s)

@@ -224,3 +224,21 @@ def test_small_and_narrow_calls_keep_one_step():
     assert not two_steps(ta, tb, q, "f16", l2=True)                       # bounds too wide on a map of this size
     count = torch.full((32,), 8192, dtype=torch.int32, device="cuda:0")
     assert not two_steps(ta, tb, q, "f16", nq_active=count)               # live counts on the device
+
+
+@pytest.mark.parametrize("fewer,more", [(3008, 3072), (4550, 4608), (2900, 3060)])
+def test_kernel_width_follows_the_split_not_the_count(fewer, more):
+    """Query counts whose blocks are dealt alike (the same blocks for the busiest wave of as many quads) take the same kernel."""
+    gen = torch.Generator(device="cuda:0").manual_seed(fewer)
+    a, b = (torch.randn((16, 131072, 24), generator=gen, device="cuda:0").half() for _ in range(2))
+    width = []
+    for nq in (fewer, more):
+        q = torch.randint(0, 131072, (16, nq), generator=gen, device="cuda:0", dtype=torch.int32)
+        fnn.fnn_trace_begin(16)
+        idx, score = fnn.fnn_nearest(a, b, q_idx=q, compute="f16")
+        torch.cuda.synchronize()
+        width.append([detail for name, _, detail in fnn.fnn_trace_end(16, details=True) if name == "coarse_kernel"])
+        ws = torch.empty(one_step_bytes("nearest", 16, 131072, 131072, 24, nq, "f16"), dtype=torch.uint8, device="cuda:0")
+        want, wscore = fnn.fnn_nearest(a, b, q_idx=q, compute="f16", workspace=ws)
+        assert torch.equal(idx, want) and torch.equal(score, wscore)
+    assert width[0] == width[1] and len(width[0]) == 1
