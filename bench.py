@@ -49,7 +49,8 @@ def searches_from_iters(seed_iter, n_seeds, max_iter):
     return counts
 
 
-DENSE_PASS1 = ("dense_kernel", "dense_select_kernel", "refine_kernel")  # the first alone, or all three on large maps
+# the first alone, or all of them on large maps
+DENSE_PASS1 = ("dense_kernel", "dense_sample_kernel", "dense_select_kernel", "refine_kernel", "dense_alike_kernel")
 TWO_STEPS = 1000  # added to the trace detail of a search that ran in two steps
 
 

@@ -194,8 +194,10 @@ struct DenseCoarseLayout {
     DenseCoarseArgs args;
     int32_t n_sb;  // runs of DENSE_SB_PIXELS of image 1
     int32_t slab;  // ... per launch
+    int64_t sample_words;  // 32-bit words that start at 0, from args.sample_lower on
+    char* swept;   // image 1 as the dense kernels read it
 };
-DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m) {
+DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m, const MapsLayout& maps) {
     DenseCoarseLayout L;
     memset(&L, 0, sizeof(L));
     DenseCoarseArgs& a = L.args;
@@ -218,6 +220,15 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     a.best[1] = (uint16_t*)cv.take((size_t)batch * a.map[0].n_segs * pixels2 * sizeof(uint16_t));
     a.mask[0] = (uint64_t*)cv.take((size_t)per_sb * L.slab / 16);
     a.mask[1] = (uint64_t*)cv.take((size_t)batch * a.map[0].n_segs * pixels2 / 8);
+    L.swept = (char*)cv.take((size_t)batch * maps.bstride1);
+    a.pixels[0] = n;
+    a.pixels[1] = m;
+    a.sample_upper[0] = (float*)cv.take((size_t)batch * a.n_cells * DENSE_SAMPLES * sizeof(float));
+    a.sample_upper[1] = (float*)cv.take((size_t)batch * a.map[0].n_segs * DENSE_SAMPLES * sizeof(float));
+    const size_t zeros = cv.used;
+    a.sample_lower = (uint32_t*)cv.take((size_t)batch * 2 * DENSE_SAMPLES * sizeof(uint32_t));
+    a.marked = (int32_t*)cv.take((size_t)batch * 2 * sizeof(int32_t));
+    L.sample_words = (int64_t)((cv.used - zeros) / sizeof(uint32_t));
     return L;
 }
 
@@ -371,8 +382,9 @@ void fill_quantise_side(QuantiseSide& sd, int32_t batch, const fnn_map* maps, bo
 }
 
 // Both directions of the dense mode from its 8-bit maps to the keys: pass 1 range by range of image 1, the second step for the queries
-// of a range at once, for the candidates when every range is done.
-hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int batch, int64_t n, int64_t m, int compute, hipStream_t s) {
+// of a range at once, for the candidates when every range is done.  Pairs whose samples say that this would be the slower way are swept
+// by the dense kernels of `sweep` instead.
+hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int batch, int64_t n, int64_t m, int compute, DenseArgs sweep, hipStream_t s) {
     SearchArgs rows;
     memset(&rows, 0, sizeof(rows));
     rows.src = (const char*)L.maps.p1;
@@ -398,11 +410,20 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
     CoarseArgs ca;
     memset(&ca, 0, sizeof(ca));
     DenseCoarseArgs da = C.args;
+    hipError_t e = launch_dense_sample(da, batch, s);
+    if (e != hipSuccess) return e;
+    const double limit = dense_coarse_limit(compute, L.maps.dp) * DENSE_SAMPLES;
+    da.judge.marked = da.marked;
+    da.judge.weight[0] = (float)(1.0 / (limit * da.n_cells));
+    da.judge.weight[1] = (float)(1.0 / (limit * da.map[0].n_segs));
+    ca.judge = sweep.judge = da.judge;
+    const DenseSwept none = {}, swept = {rows.src, rows.src_bstride, C.swept, L.maps.n_pad, (int32_t)(L.maps.bstride1 / L.maps.n_pad)};
+    const bool at_once = C.slab >= C.n_sb;  // both sides' marks in one launch
     for (int sb = 0; sb < C.n_sb; sb += C.slab) {
         da.first_sb = sb;
         da.n_sb = C.n_sb - sb < C.slab ? C.n_sb - sb : C.slab;
-        hipError_t e = launch_dense_coarse(da, batch, s);
-        if (e == hipSuccess) e = launch_dense_select(da, 0, batch, s);
+        e = launch_dense_coarse(da, batch, s);
+        if (e == hipSuccess) e = launch_dense_select(da, 0, at_once ? 2 : 1, at_once ? swept : none, batch, s);
         ca.mask = da.mask[0];
         ca.slab = da.n_sb * DENSE_SB_PIXELS;
         ca.n_cells = da.n_cells;
@@ -411,13 +432,19 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
         if (e == hipSuccess) e = launch_refine(rows, ca, batch, compute, L.maps.dp, s);
         if (e != hipSuccess) return e;
     }
-    hipError_t e = launch_dense_select(da, 1, batch, s);
+    if (!at_once) e = launch_dense_select(da, 1, 1, swept, batch, s);
     ca.mask = da.mask[1];
     ca.slab = da.map[1].n_segs * da.seg_pixels;
     ca.n_cells = da.map[0].n_segs;
     ca.cell_shift = da.seg_pixels == 4096 ? 2 : 1;
     ca.first_slot = 0;
     if (e == hipSuccess) e = launch_refine(cols, ca, batch, compute, L.maps.dp, s);
+
+    sweep.d1 = C.swept;
+    // a launch that leaves every pair alone costs its workgroups' start: no more of them than fill the chip a few times
+    auto wgs = [&]() { return (int64_t)sweep.n_sb * ((sweep.m_tiles + DENSE_TILES_PER_GROUP * sweep.groups_per_wg - 1) / (DENSE_TILES_PER_GROUP * sweep.groups_per_wg)); };
+    while (wgs() > 8192) sweep.groups_per_wg *= 2;
+    if (e == hipSuccess) e = launch_dense_pass1(sweep, batch, compute, L.maps.dp, s);
     return e;
 }
 
@@ -503,9 +530,9 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
     }
     {
         Carver cv{nullptr, 0};
-        carve_dense(cv, batch, n, m, de, compute);
+        const DenseLayout D = carve_dense(cv, batch, n, m, de, compute);
         if (n <= MAX_DENSE_PIXELS && m <= MAX_DENSE_PIXELS && dense_coarse_gain(n, m, batch, compute, dp, d, l2) > 0.0)
-            carve_dense_coarse(cv, batch, n, m);
+            carve_dense_coarse(cv, batch, n, m, D.maps);
         if (cv.used > most) most = cv.used;
     }
     return most + WS_ALIGN;
@@ -987,28 +1014,6 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
     da.chunk_unit = L.chunk_unit;
     da.chunk_totals = L.chunk_totals;
 
-    // Large maps: 8-bit scores first, then, where the workspace has the room, the second step of the searches in both directions
-    DenseCoarseLayout C = carve_dense_coarse(cv, batch, n, m);
-    if (cv.used <= workspace_bytes && dense_coarse_gain(n, m, batch, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0) > 0.0) {
-        const bool raw = raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
-        if (!raw) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra));
-        QuantiseArgs qa;
-        memset(&qa, 0, sizeof(qa));
-        if (raw) qa.extra = extra;
-        const bool read_raw = raw || raw_halves(batch, d1, d2, opts);
-        fill_quantise_side(qa.side[0], batch, d1, read_raw, (const char*)L.maps.p1, L.maps.bstride1, L.maps.n_pad, C.args.map[0]);
-        fill_quantise_side(qa.side[1], batch, d2, read_raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
-        qa.batch = batch;
-        qa.raw_rows = read_raw ? 1 : 0;
-        qa.seg_pixels = C.args.seg_pixels;
-        qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
-        FNN_TRY(launch_quantise(qa, opts->compute, L.maps.dp, s));
-        FNN_TRY(dense_two_steps(C, L, batch, n, m, opts->compute, s));
-        FNN_TRY(launch_dense_resolve(da, batch, opts->compute, L.maps.dp, nn12, s12, nn21, s21, s));
-        FNN_TRY(launch_dense_final(fa, batch, s));
-        return FNN_OK;
-    }
-    if (n > 0 && m > 0) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, true));
     // Workgroup tile: one query super-block (32 KB of LDS keys) x up to 8 candidate groups (of
     // DENSE_WAVES x DENSE_J tiles).  Larger tiles mean fewer merges into the global key
     // tables; small problems shrink the tile until the grid covers the chip a few times.
@@ -1021,6 +1026,31 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
     while (groups_per_wg > 1 && wg_count() < 1024) groups_per_wg >>= 1;
     da.sb_per_wg = (int32_t)sb_per_wg;
     da.groups_per_wg = (int32_t)groups_per_wg;
+
+    // Large maps: 8-bit scores first, then, where the workspace has the room, the second step of the searches in both directions
+    DenseCoarseLayout C = carve_dense_coarse(cv, batch, n, m, L.maps);
+    if (cv.used <= workspace_bytes && dense_coarse_gain(n, m, batch, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0) > 0.0) {
+        const bool raw = raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
+        if (!raw) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra));
+        QuantiseArgs qa;
+        memset(&qa, 0, sizeof(qa));
+        if (raw) qa.extra = extra;
+        const bool read_raw = raw || raw_halves(batch, d1, d2, opts);
+        fill_quantise_side(qa.side[0], batch, d1, read_raw, (const char*)L.maps.p1, L.maps.bstride1, L.maps.n_pad, C.args.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, read_raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
+        qa.batch = batch;
+        qa.raw_rows = read_raw ? 1 : 0;
+        qa.seg_pixels = C.args.seg_pixels;
+        qa.lower = C.args.sample_lower;
+        qa.lower_count = C.sample_words;
+        qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
+        FNN_TRY(launch_quantise(qa, opts->compute, L.maps.dp, s));
+        FNN_TRY(dense_two_steps(C, L, batch, n, m, opts->compute, da, s));
+        FNN_TRY(launch_dense_resolve(da, batch, opts->compute, L.maps.dp, nn12, s12, nn21, s21, s));
+        FNN_TRY(launch_dense_final(fa, batch, s));
+        return FNN_OK;
+    }
+    if (n > 0 && m > 0) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, true));
     if (n > 0 && m > 0) FNN_TRY(launch_dense(da, batch, opts->compute, L.maps.dp, nn12, s12, nn21, s21, s));
     else if (n > 0) FNN_TRY(launch_fill_i32f32(nn12, s12, (int64_t)batch * n, s));
     else if (m > 0) FNN_TRY(launch_fill_i32f32(nn21, s21, (int64_t)batch * m, s));

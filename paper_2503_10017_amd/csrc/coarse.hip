@@ -390,7 +390,7 @@ constexpr int refine_waves() { return Ops<CT, DP>::ROW_BYTES <= 48 ? 4 : (Ops<CT
 constexpr int REFINE_SCAN = 4096;             // queries looked at between two looks at the list's length
 constexpr int REFINE_LIST = REFINE_SCAN + 1024;
 constexpr int REFINE_PART = 512;               // a multiple of 32
-constexpr int REFINE_RANGE = 4 * REFINE_SCAN;  // queries of a workgroup
+constexpr int REFINE_MOST = 4 * REFINE_SCAN;   // queries of a workgroup (ca.range: a multiple of REFINE_SCAN)
 
 // MASK: which queries need a cell is read from a table of bits; the keys name units of DENSE_J tiles instead of tiles.
 template <int CT, int DP, int RT, int WAVES, bool MASK>
@@ -407,12 +407,13 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cell = blockIdx.x, b = blockIdx.z;
+    if (MASK && ca.judge.alike(b)) return;
     int n_act = a.nq;
     if (a.nq_active) n_act = min(max(a.nq_active[b], 0), a.nq);
     const bool every = n_act < ca.min_live;       // step 1 left these queries to this kernel
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
-    const int begin = blockIdx.y * REFINE_RANGE;
-    n_act = min(n_act, begin + REFINE_RANGE);
+    const int begin = blockIdx.y * ca.range;
+    n_act = min(n_act, begin + ca.range);
     const int tile0 = (cell * WAVES + wave) * RT;
     if (n_act <= begin) return;
 
@@ -653,11 +654,20 @@ static hipError_t launch_coarse_t(const SearchArgs& a, const CoarseArgs& ca, int
 }
 // CELL: tiles of a workgroup.
 template <int CT, int DP, int CELL, bool MASK = false>
-static hipError_t launch_refine_t(const SearchArgs& a, const CoarseArgs& ca, int batch, hipStream_t s) {
+static hipError_t launch_refine_t(const SearchArgs& a, CoarseArgs ca, int batch, hipStream_t s) {
     constexpr int RT = refine_tiles<CT, DP>() * CELL / SEG_TILES, WAVES = CELL / RT;
     const int64_t slots = a.nq - ca.first_slot < ca.slab ? a.nq - ca.first_slot : ca.slab;
-    const unsigned ranges = (unsigned)((slots + REFINE_RANGE - 1) / REFINE_RANGE);
-    return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES, MASK>, dim3((a.m_tiles + CELL - 1) / CELL, ranges, batch), dim3(64 * WAVES), 0, s, a, ca);
+    const unsigned cells = (unsigned)((a.m_tiles + CELL - 1) / CELL);
+    // Where neighbouring pixels resemble each other, what a cell is marked by lies together: a workgroup with many queries may need the
+    // cell for all of them and be what the launch waits for.  Short ranges even that out while the workgroups are few; each reads
+    // its tiles again (dense mode, fp16, 24 channels, both launches with ranges of 16384 / 4096: 512x384, features of 128 pixels
+    // 1104 / 548 us, of one 137 / 132; 1024x768 4302 / 3815 and 1085 / 1662).  Rows that cost more per product lose more to the last block of a
+    // list than they gain (fp32, 384x288, features of one pixel 356 / 794).
+    ca.range = REFINE_MOST;
+    if (MASK && CT != CT_F32 && DP <= 32)
+        for (ca.range = REFINE_SCAN; ca.range < REFINE_MOST && cells * ((slots + ca.range - 1) / ca.range) * batch > 16384;) ca.range *= 2;
+    const unsigned ranges = (unsigned)((slots + ca.range - 1) / ca.range);
+    return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES, MASK>, dim3(cells, ranges, batch), dim3(64 * WAVES), 0, s, a, ca);
 }
 template <int CT, int DP>
 static hipError_t launch_both_t(const SearchArgs& a, CoarseArgs ca, int batch, hipStream_t s) {

@@ -243,6 +243,7 @@ template <int CT, int DP>
 __global__ __launch_bounds__(DENSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<CT, DP>())))
 void dense_kernel(DenseArgs a) {
     extern __shared__ u64 lds[];
+    if (a.judge.marked && !a.judge.alike(blockIdx.z)) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     u64* col_keys = lds + (size_t)a.sb_per_wg * DENSE_S * 32;
     dense_workgroup<CT, DP>(a, lds, col_keys + wave * (DENSE_J * 32),
@@ -415,6 +416,7 @@ __device__ __forceinline__ void dense_sweep_staged(const DenseArgs& a, const typ
 template <int CT>
 __global__ __launch_bounds__(DENSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void dense_staged_kernel(DenseArgs a) {
+    if (a.judge.marked && !a.judge.alike(blockIdx.z)) return;
     using O = Ops<CT, 24>;
     using Frag = typename O::Frag;
     constexpr int J = DENSE_J, S = DENSE_S;
@@ -947,19 +949,24 @@ static ResolveSide col_side(const DenseArgs& a, int32_t* nn21, float* s21) {
 }
 
 template <int CT, int DP>
-static hipError_t launch_dense_t(const DenseArgs& a, int batch, int32_t* nn12, float* s12, int32_t* nn21, float* s21,
-                                 hipStream_t s) {
+static hipError_t launch_dense_pass1_t(const DenseArgs& a, int batch, hipStream_t s) {
     const int groups = (a.m_tiles + DENSE_TILES_PER_GROUP - 1) / DENSE_TILES_PER_GROUP;
     dim3 grid((groups + a.groups_per_wg - 1) / a.groups_per_wg, (a.n_sb + a.sb_per_wg - 1) / a.sb_per_wg, batch);
     const size_t lds_bytes = ((size_t)a.sb_per_wg * DENSE_S * 32 + DENSE_WAVES * DENSE_J * 32) * sizeof(u64) +
                              DENSE_WAVES * 32 * sizeof(float);  // row keys, column keys, 32 maxima per wave
-    hipError_t e;
+    const TraceKind kind = a.judge.marked ? TK_DENSE_ALIKE : TK_DENSE;
     if constexpr (DENSE_STAGED && CT != CT_F32 && DP == 24) {
         if (a.sb_per_wg != 1) return hipErrorInvalidValue;  // the staged kernel's key table holds one super-block
-        e = launch_detail(TK_DENSE, 1, dense_staged_kernel<CT>, grid, dim3(DENSE_WAVES * 64), 0, s, a);
+        return launch_detail(kind, 1, dense_staged_kernel<CT>, grid, dim3(DENSE_WAVES * 64), 0, s, a);
     } else {
-        e = launch(TK_DENSE, dense_kernel<CT, DP>, grid, dim3(DENSE_WAVES * 64), lds_bytes, s, a);
+        return launch(kind, dense_kernel<CT, DP>, grid, dim3(DENSE_WAVES * 64), lds_bytes, s, a);
     }
+}
+
+template <int CT, int DP>
+static hipError_t launch_dense_t(const DenseArgs& a, int batch, int32_t* nn12, float* s12, int32_t* nn21, float* s21,
+                                 hipStream_t s) {
+    hipError_t e = launch_dense_pass1_t<CT, DP>(a, batch, s);
     if (e != hipSuccess) return e;
     e = launch_dense_buckets(a, batch, nn12, s12, nn21, s21, s);
     if (e != hipSuccess) return e;
@@ -1000,6 +1007,27 @@ hipError_t launch_dense(const DenseArgs& a, int batch, int compute, int dp, int3
         if (dp == 16) return launch_dense_t<CT_F32, 16>(a, batch, nn12, s12, nn21, s21, s);
         if (dp == 24) return launch_dense_t<CT_F32, 24>(a, batch, nn12, s12, nn21, s21, s);
         if (dp == 32) return launch_dense_t<CT_F32, 32>(a, batch, nn12, s12, nn21, s21, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_dense_pass1(const DenseArgs& a, int batch, int compute, int dp, hipStream_t s) {
+    if (a.n <= 0 || a.m <= 0 || batch <= 0) return hipSuccess;
+    if (compute == FNN_F16) {
+        if (dp == 24) return launch_dense_pass1_t<CT_F16, 24>(a, batch, s);
+        if (dp == 32) return launch_dense_pass1_t<CT_F16, 32>(a, batch, s);
+        if (dp == 48) return launch_dense_pass1_t<CT_F16, 48>(a, batch, s);
+        if (dp == 64) return launch_dense_pass1_t<CT_F16, 64>(a, batch, s);
+        if (dp == 80) return launch_dense_pass1_t<CT_F16, 80>(a, batch, s);
+        if (dp == 96) return launch_dense_pass1_t<CT_F16, 96>(a, batch, s);
+    } else if (compute == FNN_BF16) {
+        if (dp == 24) return launch_dense_pass1_t<CT_BF16, 24>(a, batch, s);
+        if (dp == 32) return launch_dense_pass1_t<CT_BF16, 32>(a, batch, s);
+    } else {
+        if (dp == 8) return launch_dense_pass1_t<CT_F32, 8>(a, batch, s);
+        if (dp == 16) return launch_dense_pass1_t<CT_F32, 16>(a, batch, s);
+        if (dp == 24) return launch_dense_pass1_t<CT_F32, 24>(a, batch, s);
+        if (dp == 32) return launch_dense_pass1_t<CT_F32, 32>(a, batch, s);
     }
     return hipErrorInvalidValue;
 }

@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "coarse_device.hpp"
+#include "dense_perm.hpp"
 #include "fnn_kernels.hpp"
 #include "trace.hpp"
 
@@ -61,6 +62,7 @@ void dense_coarse_kernel(DenseCoarseArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int held = held_register(lane);
     const int cell0 = blockIdx.x * a.cells_per_wg, sb = blockIdx.y, b = blockIdx.z;
+    if (a.judge.alike(b)) return;
     constexpr int SEGS = DENSE_SB_PIXELS / SEGMENT, SEG_TURNS = DC_TURNS / SEGS;
     const int64_t pixels1 = (int64_t)a.map[0].n_segs * SEGMENT, pixels2 = (int64_t)a.map[1].n_segs * SEGMENT;
     const char* blocks = a.map[0].rows + ((int64_t)b * pixels1 + (int64_t)(a.first_sb + sb) * DENSE_SB_PIXELS) * COARSE_ROW_BYTES;
@@ -160,7 +162,9 @@ void dense_coarse_kernel(DenseCoarseArgs a) {
 constexpr int SELECT_WAVES = 4;
 constexpr int SELECT_SLOTS = 4;
 constexpr int SELECT_DEEP = 6;  // cells in flight per wave
-struct SelectArgs {
+// Of a pair that the samples found alike, the workgroups put the prepared rows of image 1 into the order that the dense kernels sweep (swept.to is NULL in
+// a launch that does not): a thread copies 16 bytes at a time.
+struct SelectSide {
     const uint16_t* best;       // [batch][n_cells][pitch]
     uint64_t* mask;             // [batch][n_cells][pitch / 64]
     int32_t n_cells;
@@ -171,7 +175,25 @@ struct SelectArgs {
     const SegInfo* seg;         // of the other map, [batch][n_segs]
     int32_t n_segs;
 };
-__global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectArgs a) {
+struct SelectArgs {
+    SelectSide side[2];     // blockIdx.z
+    DenseJudge judge;
+    DenseSwept swept;
+};
+__global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectArgs args) {
+    const SelectSide& a = args.side[blockIdx.z];
+    if (args.judge.alike(blockIdx.y)) {
+        const DenseSwept& w = args.swept;
+        if (!w.to) return;
+        const uint4* from = reinterpret_cast<const uint4*>(w.from + (int64_t)blockIdx.y * w.from_bstride);
+        uint4* to = reinterpret_cast<uint4*>(w.to + (int64_t)blockIdx.y * w.n_pad * w.row_bytes);
+        const int words = w.row_bytes / 16;
+        const int64_t n_threads = (int64_t)gridDim.x * gridDim.z * (SELECT_WAVES * 64);
+        for (int64_t i = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * (SELECT_WAVES * 64) + threadIdx.x; i < w.n_pad * words; i += n_threads)
+            to[i] = from[slot_pixel(i / words) * words + i % words];
+        return;
+    }
+    if ((int64_t)blockIdx.x * (64 * SELECT_SLOTS) >= a.pitch) return;  // uniform: the sides differ in size
     __shared__ float low[SELECT_WAVES][SELECT_SLOTS][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -227,23 +249,108 @@ __global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectA
     });
 }
 
+// Whether the 8-bit scores of a pair tell enough apart.  How many cells the bounds leave over is a matter of what the maps hold (a
+// textureless wall, descriptors of few dimensions or of very different lengths leave most of them), so DENSE_SAMPLES pixels of
+// either image, spread over it, are scored against every cell of the other first: what they need is counted, and the launches of
+// the two steps, or else those of the one-step sweep, leave the pair alone.  One 512x384 pair, fp16, 24 channels, the whole call in one
+// step / in two without this / with it (17 us for pairs that keep two steps): features of 1 pixel 2.16 / 1.69 / 1.71 ms, of 64 2.05 / 2.26 / 1.89
+// (short ranges, see launch_refine_t), rank 6 2.13 / 2.82 / 2.17, rank 4 2.12 / 4.60 / 2.15, lengths spread by exp(N(0, 1)) 2.20 / 3.58 / 2.23,
+// one descriptor throughout 1.93 / 4.32 / 1.95.
+constexpr int SAMPLE_BLOCKS = DENSE_SAMPLES / 32;
+constexpr int SAMPLE_WAVES = 8;
+constexpr int SAMPLE_TILES = 8;  // in flight per wave
+__device__ __forceinline__ int64_t sample_pixel(int k, int64_t n) { return (int64_t)(((uint64_t)((uint32_t)k * 0x9E3779B1u) * (uint64_t)n) >> 32); }
+__device__ __forceinline__ int sample_cells(const DenseCoarseArgs& a, int side) { return side == 0 ? a.n_cells : a.map[0].n_segs; }
+// A workgroup scores the samples of one image against one cell of the other.  Bound by the latency of its loads.
+__global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCoarseArgs a) {
+    __shared__ int best[DENSE_SAMPLES];
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cell = blockIdx.x, side = blockIdx.y, b = blockIdx.z;
+    if (cell >= sample_cells(a, side)) return;
+    const CoarseMap& own = a.map[side];
+    const CoarseMap& other = a.map[side ^ 1];
+    const int64_t own_row0 = (int64_t)b * own.n_segs * a.seg_pixels;
+    const int cell_pixels = side == 0 ? 512 * a.cell_groups : a.seg_pixels;  // 1024 to 4096
+    const char* tiles = other.rows + ((int64_t)b * other.n_segs * a.seg_pixels + (int64_t)cell * cell_pixels) * COARSE_ROW_BYTES;
+    const int64_t mine = sample_pixel(threadIdx.x & (DENSE_SAMPLES - 1), a.pixels[side]);
+    const uint32_t bound = own.row_bound[own_row0 + mine];
+    const SegInfo si = other.seg[(int64_t)b * other.n_segs + (int64_t)cell * cell_pixels / a.seg_pixels];
+    if (threadIdx.x < DENSE_SAMPLES) best[threadIdx.x] = LOWEST;
+    i32x4 q[SAMPLE_BLOCKS];
+#pragma unroll
+    for (int k = 0; k < SAMPLE_BLOCKS; ++k)
+        q[k] = *reinterpret_cast<const i32x4*>(own.rows + (own_row0 + sample_pixel(k * 32 + c, a.pixels[side])) * COARSE_ROW_BYTES + 16 * h);
+    int top[SAMPLE_BLOCKS];
+#pragma unroll
+    for (int k = 0; k < SAMPLE_BLOCKS; ++k) top[k] = LOWEST;
+#pragma unroll 1
+    for (int t = wave * SAMPLE_TILES; t < cell_pixels / 32; t += SAMPLE_WAVES * SAMPLE_TILES) {
+        i32x4 tile[SAMPLE_TILES];
+#pragma unroll
+        for (int i = 0; i < SAMPLE_TILES; ++i) tile[i] = *reinterpret_cast<const i32x4*>(tiles + (int64_t)(t + i) * TILE_BYTES + c * COARSE_ROW_BYTES + 16 * h);
+#pragma unroll
+        for (int i = 0; i < SAMPLE_TILES; ++i)
+#pragma unroll
+            for (int k = 0; k < SAMPLE_BLOCKS; ++k) top[k] = fold16i(top[k], product8(tile[i], q[k]));
+    }
+    __syncthreads();
+    if (wave * SAMPLE_TILES < cell_pixels / 32) {
+#pragma unroll
+        for (int k = 0; k < SAMPLE_BLOCKS; ++k) atomicMax(&best[k * 32 + c], top[k]);
+    }
+    __syncthreads();
+    if (threadIdx.x < DENSE_SAMPLES) {
+        const int k = threadIdx.x, kept = best[k] >> KEPT_SHIFT;
+        const float error = __builtin_fmaf(__uint_as_float(bound & 0xFFFF0000u), si.residual, __uint_as_float(bound << 16) * si.length);
+        a.sample_upper[side][((int64_t)b * sample_cells(a, side) + cell) * DENSE_SAMPLES + k] = (float)((kept + 1) * (1 << KEPT_SHIFT)) * si.scale + error;
+        atomicMax(&a.sample_lower[(b * 2 + side) * DENSE_SAMPLES + k], order_bits((float)(kept * (1 << KEPT_SHIFT)) * si.scale - error));
+    }
+}
+constexpr int JUDGE_CELLS = 16;  // of a workgroup
+__global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseArgs a) {
+    const int k = threadIdx.x, side = blockIdx.y, b = blockIdx.z, cells = sample_cells(a, side), first = blockIdx.x * JUDGE_CELLS;
+    const float* upper = a.sample_upper[side] + (int64_t)b * cells * DENSE_SAMPLES + k;
+    const float lower = unorder_bits(a.sample_lower[(b * 2 + side) * DENSE_SAMPLES + k]);
+    float up[JUDGE_CELLS];
+#pragma unroll
+    for (int i = 0; i < JUDGE_CELLS; ++i) up[i] = upper[(int64_t)min(first + i, cells - 1) * DENSE_SAMPLES];
+    int marks = 0;
+#pragma unroll
+    for (int i = 0; i < JUDGE_CELLS; ++i)
+        if (first + i < cells) marks += __popcll(__ballot(up[i] >= lower));  // uniform
+    if ((threadIdx.x & 63) == 0 && marks) atomicAdd(&a.marked[b * 2 + side], marks);
+}
+
 // Wider cells keep the table of a large map small, narrower ones leave less to multiply again.
 int dense_seg_pixels(int64_t n) { return n > 400000 ? 4096 : 2048; }
 int dense_cell_groups(int64_t n, int64_t m) { return m > 400000 ? dense_seg_pixels(n) / 512 : 2; }  // a cell lies in one segment
+// What a block of 32x32 scores takes one SIMD in the dense kernels, in dense_coarse_kernel, and in the second step
+static double dense_exact(int compute, int dp) { return compute == FNN_F32 ? 15.8 * dp : (dp <= 32 ? 2.33 * dp : 1.83 * dp); }
+constexpr double DENSE_COARSE = 38.0;
+static double dense_second(int compute, int dp) { return compute == FNN_F32 ? 18.75 * dp : (dp <= 32 ? 46.0 : 1.64 * dp); }
+// ... there with its lists and what their uneven lengths leave idle: one 512x384 pair of 16-bit rows loses from a share of about 0.26 on
+// (0.24 0.97 of the one step's time, 0.25 0.99), 384x288 in fp32 is at 0.87 with 0.61
+double dense_coarse_limit(int compute, int dp) {
+    return 0.85 * (dense_exact(compute, dp) - DENSE_COARSE) / (compute != FNN_F32 && dp <= 32 ? 58.0 : dense_second(compute, dp));
+}
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2) {
     if (n < 16384 || m < 16384 || (compute != FNN_F32 && dp <= 16)) return -1e30;
     if ((double)batch * m * (n / dense_seg_pixels(n)) * 2.0 > 4e9) return -1e30;  // the candidates' table of bounds would be too large
-    // what a block of 32x32 scores takes one SIMD in the dense kernels, in dense_coarse_kernel, and in the second step
-    const double exact = compute == FNN_F32 ? 15.8 * dp : (dp <= 32 ? 2.33 * dp : 1.83 * dp), coarse = 38.0;
-    const double second = compute == FNN_F32 ? 18.75 * dp : (dp <= 32 ? 46.0 : 1.64 * dp);
     const double cell = 512.0 * dense_cell_groups(n, m), row_bytes = dp * elem_size(compute);
     const double cells[2] = {m / cell, (double)n / dense_seg_pixels(n)};
     const double again = coarse_cells_again(cells[0], d, l2) / cells[0] + coarse_cells_again(cells[1], d, l2) / cells[1];
     const double blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
     const double bytes = batch * ((double)(n + m) * (2.0 * row_bytes + 40.0) + 8.0 * n * (m / cell) + 8.0 * m * ((double)n / dense_seg_pixels(n)));
-    return blocks * (exact - coarse - second * again) - 30000.0 - bytes / 4500.0 - batch * (double)(n + m) * 0.1;
+    return blocks * (dense_exact(compute, dp) - DENSE_COARSE - dense_second(compute, dp) * again) - 45000.0 - bytes / 4500.0 - batch * (double)(n + m) * 0.1;
 }
 
+hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s) {
+    const int cells = a.n_cells > a.map[0].n_segs ? a.n_cells : a.map[0].n_segs;
+    const hipError_t e = launch(TK_DENSE_SAMPLE, dense_sample_kernel, dim3(cells, 2, batch), dim3(SAMPLE_WAVES * 64), 0, s, a);
+    if (e != hipSuccess) return e;
+    return launch(TK_DENSE_SAMPLE, dense_judge_kernel, dim3((cells + JUDGE_CELLS - 1) / JUDGE_CELLS, 2, batch), dim3(DENSE_SAMPLES), 0, s, a);
+}
 hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s) {
     // six workgroups for every resident one (three per compute unit), so that the last ones leave little of the chip idle
     a.cells_per_wg = 1;
@@ -254,8 +361,8 @@ hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s) {
     return launch_detail(TK_DENSE, 2, dense_coarse_kernel<4096>, grid, dim3(COARSE_WAVES * 64), 0, s, a);
 }
 
-hipError_t launch_dense_select(const DenseCoarseArgs& a, int side, int batch, hipStream_t s) {
-    SelectArgs sa;
+static SelectSide select_side(const DenseCoarseArgs& a, int side) {
+    SelectSide sa;
     const CoarseMap& own = a.map[side];
     const CoarseMap& other = a.map[side ^ 1];
     sa.best = a.best[side];
@@ -267,8 +374,20 @@ hipError_t launch_dense_select(const DenseCoarseArgs& a, int side, int batch, hi
     sa.bound_pitch = (int64_t)own.n_segs * a.seg_pixels;
     sa.seg = other.seg;
     sa.n_segs = other.n_segs;
+    return sa;
+}
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, const DenseSwept& swept, int batch, hipStream_t s) {
+    SelectArgs args;
+    args.judge = a.judge;
+    args.swept = swept;
+    int64_t pitch = 0;
+    for (int i = 0; i < sides; ++i) {
+        args.side[i] = select_side(a, first_side + i);
+        if (args.side[i].pitch > pitch) pitch = args.side[i].pitch;
+    }
+    if (sides == 1) args.side[1] = args.side[0];
     const int64_t per_wg = 64 * SELECT_SLOTS;
-    return launch(TK_DENSE_SELECT, dense_select_kernel, dim3((unsigned)((sa.pitch + per_wg - 1) / per_wg), batch), dim3(SELECT_WAVES * 64), 0, s, sa);
+    return launch(TK_DENSE_SELECT, dense_select_kernel, dim3((unsigned)((pitch + per_wg - 1) / per_wg), batch, sides), dim3(SELECT_WAVES * 64), 0, s, args);
 }
 
 }  // namespace fnn

@@ -140,6 +140,16 @@ constexpr int DENSE_J = 4;      // candidate tiles resident per wave
 constexpr int DENSE_WAVES = 4;  // waves per workgroup
 constexpr int DENSE_TILES_PER_GROUP = DENSE_J * DENSE_WAVES;
 
+// What a sample of a pair's pixels says of the dense mode's 8-bit scores: the cells that may hold a sample's best partner, both ways.
+// Where they are too many, the pair is swept in its own format instead.
+struct DenseJudge {
+    const int32_t* marked;  // [batch][2] (NULL: every pair takes the 8-bit scores)
+    float weight[2];        // one over the marks of a side that make the two ways equally fast
+    __device__ __forceinline__ bool alike(int b) const {
+        return marked && (float)marked[2 * b] * weight[0] + (float)marked[2 * b + 1] * weight[1] > 1.0f;
+    }
+};
+
 // ---- pass 1 in 8 bits, for searches large enough (coarse.hip) -------------------------------
 // Pixels of a map are taken SEG_PIXELS at a time: one scale and one set of bounds for each segment.  A query's scores
 // are bounded per CELL, a whole segment or half of one.
@@ -193,7 +203,9 @@ struct CoarseArgs {
     int32_t n_cells;       // of a pair
     int32_t cell_shift;    // a cell is 2^cell_shift workgroups of the second step
     const uint64_t* mask;  // launch_refine: [batch][n_cells][slab / 64] the slots that need a cell, instead of the bounds
-    int32_t first_slot;    // (launch_coarse_search sets these)
+    DenseJudge judge;      // launch_refine: pairs to leave alone
+    int32_t range;         // (the launchers set these) queries that a workgroup of the second step looks at
+    int32_t first_slot;
     int32_t min_live;      // fewer live queries of a pair than this: its cells are refined for every query
 };
 // What launch_search does: the queries' list and live count, the prepared maps and the keys are those of `a`.
@@ -318,11 +330,15 @@ struct DenseArgs {
     int32_t* lists;        // [batch][rows_cap + cols_cap] pixels grouped by unit, buckets start on multiples of 32
     int32_t* chunk_unit;   // [batch][(rows_cap + cols_cap) / 32] unit of every chunk of 32 list positions
     int32_t* chunk_totals; // [batch][2] chunks in use per side
+    DenseJudge judge;      // launch_dense_pass1: the pairs to take (no marks: all)
 };
 // Pass 1 (both maxima with coarse locations) and pass 2 (exact indices and scores into
 // nn12/s12/nn21/s21; s12, s21 may be NULL).
 hipError_t launch_dense(const DenseArgs& a, int batch, int compute, int dp, int32_t* nn12, float* s12, int32_t* nn21,
                         float* s21, hipStream_t s);
+
+// Pass 1 alone.
+hipError_t launch_dense_pass1(const DenseArgs& a, int batch, int compute, int dp, hipStream_t s);
 
 // Pass 1 in 8 bits (dense_coarse.hip), on maps quantised in segments of seg_pixels: the largest 8-bit score of every query in
 // every cell of candidates, and of every candidate in every segment of queries.
@@ -337,12 +353,30 @@ struct DenseCoarseArgs {
     int32_t cells_per_wg;  // (set by the launcher)
     uint16_t* best[2];     // [batch][n_cells][n_sb * 4096] of the queries; [batch][map[0].n_segs][pixels of map[1]] of the candidates
     uint64_t* mask[2];     // the same, a bit per score: cells that may hold the slot's best partner
+    int64_t pixels[2];
+    float* sample_upper[2];  // [batch][cells of the other image][DENSE_SAMPLES]
+    uint32_t* sample_lower;  // [batch][2][DENSE_SAMPLES] order_bits (0 on entry)
+    int32_t* marked;         // [batch][2] (0 on entry): see DenseJudge
+    DenseJudge judge;
+};
+constexpr int DENSE_SAMPLES = 128;  // pixels of either image
+// Counts the marks of the samples.
+hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s);
+// Of pairs that turn out alike: the prepared rows of image 1 in the order that the dense kernels sweep.
+struct DenseSwept {
+    const char* from;  // [batch] prepared maps in natural order
+    int64_t from_bstride;
+    char* to;          // [batch][n_pad][row_bytes], or NULL
+    int64_t n_pad;     // a multiple of DENSE_SB_PIXELS
+    int32_t row_bytes; // a multiple of 16
 };
 hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s);
-// From best[side] to mask[side].  side 0: the queries of this launch's runs; 1: the candidates, once every run is done
-hipError_t launch_dense_select(const DenseCoarseArgs& a, int side, int batch, hipStream_t s);
+// From best[side] to mask[side] for one or both sides.  0: the queries of this launch's runs; 1: the candidates, once every run is done.
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, const DenseSwept& swept, int batch, hipStream_t s);
 int dense_cell_groups(int64_t n, int64_t m);
 int dense_seg_pixels(int64_t n);
+// Share of the cells, of both directions together, that may be multiplied again before the dense kernels are faster
+double dense_coarse_limit(int compute, int dp);
 // Nanoseconds that a call gains this way
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2);
 

@@ -101,6 +101,8 @@ const char* fnn_trace_kind_name(int32_t kind) {
         case TK_REFINE: return "refine_kernel";
         case TK_DENSE_SELECT: return "dense_select_kernel";
         case TK_RECIP_GROUPS: return "recip_groups_kernel";
+        case TK_DENSE_SAMPLE: return "dense_sample_kernel";
+        case TK_DENSE_ALIKE: return "dense_alike_kernel";
         default: return "unknown";
     }
 }

@@ -27,7 +27,9 @@ enum TraceKind : int {
     TK_REFINE = 16,
     TK_DENSE_SELECT = 17,
     TK_RECIP_GROUPS = 18,
-    TK_COUNT = 19
+    TK_DENSE_SAMPLE = 19,
+    TK_DENSE_ALIKE = 20,
+    TK_COUNT = 21
 };
 
 // Returns false when no trace is open or it is full; otherwise hands out the next event pair.

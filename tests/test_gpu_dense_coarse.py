@@ -105,3 +105,56 @@ def test_maps_that_strain_the_bounds(kind, compute):
     maps = [_special(kind, rng, n, m) for _ in range(batch)]
     a, b = (dev(np.stack([x[i] for x in maps])) for i in (0, 1))
     same(a, b, compute)
+
+
+def _alike(kind, n, gen):
+    """Maps of which the 8-bit scores rule out little: one descriptor throughout, or descriptors of three dimensions."""
+    if kind == "equal":
+        return torch.nn.functional.normalize(torch.randn((1, 24), generator=gen, device="cuda:0"), dim=1).repeat(n, 1)
+    few = torch.randn((n, 3), generator=gen, device="cuda:0") @ torch.randn((3, 24), generator=gen, device="cuda:0")
+    return torch.nn.functional.normalize(few, dim=1)
+
+
+@pytest.mark.parametrize("n,m,compute,stored,d,kw", [
+    (131072, 131072, "f16", "f32", 24, {}),
+    (131073, 135169, "bf16", "f16", 24, {}),
+    (131500, 141000, "bf16", "f32", 29, {}),
+    (65537, 40000, "f32", "f32", 21, {}),
+    (66000, 65600, "f16", "f32", 24, {"split": True}),
+])
+def test_pairs_that_look_alike_beside_pairs_that_do_not(n, m, compute, stored, d, kw):
+    """Every pair of a batch goes its own way; the keys of both ways are resolved together."""
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    a = torch.nn.functional.normalize(torch.randn((5, n, 24), generator=gen, device="cuda:0"), dim=2)
+    b = torch.nn.functional.normalize(torch.randn((5, m, 24), generator=gen, device="cuda:0"), dim=2)
+    for p, kind in ((0, "rank 3"), (2, "equal"), (4, "rank 3")):
+        a[p] = _alike(kind, n, gen)
+        b[p] = a[p, torch.randint(0, n, (m,), generator=gen, device="cuda:0")]
+    a, b = (x.repeat(1, 1, 2)[:, :, :d].to({"f32": torch.float32, "f16": torch.float16}[stored]).contiguous() for x in (a, b))
+    same(a, b, compute, **kw)
+
+
+@pytest.mark.parametrize("kind", ["equal", "rank 3"])
+def test_maps_without_contrast_take_no_longer_than_one_step(kind):
+    """Every cell of such maps would be multiplied again: 2.2 times the one step's time.  (The sample, the 8-bit maps and the launches that
+    leave the pair alone are 5 to 10 %.)"""
+    n = 196608
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    a = _alike(kind, n, gen)
+    b = a[torch.randperm(n, generator=gen, device="cuda:0")]
+    ws = torch.empty(fnn.fnn_workspace_bytes(1, n, n, 24, 0, "f16"), dtype=torch.uint8, device="cuda:0")
+    small = ws[:one_step_bytes(1, n, n, 24, "f16")]
+    out = fnn.fnn_mutual_dense(a, b, "f16", workspace=ws)
+
+    def least(workspace):
+        times = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            fnn.fnn_mutual_dense(a, b, "f16", out=out, workspace=workspace)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+
+    assert least(ws) < 1.4 * least(small)
