@@ -90,6 +90,8 @@ struct CoarseLayout {
     uint16_t* upper;
     uint32_t* lower;       // [searches][batch][slot_pitch]
     int64_t lower_count;   // words of one search
+    SearchVote* votes;     // [searches][batch], behind them
+    int64_t zero_words;    // 32-bit words that start at 0, from `lower` on
     int64_t slot_pitch;
     int64_t slab;
 };
@@ -116,11 +118,14 @@ CoarseLayout carve_coarse(Carver& cv, int batch, int64_t rows1, int64_t rows2, b
     L.slot_pitch = round_up(nq, 64);
     L.slab = coarse_slab(nq, segs, batch);
     L.lower_count = batch * L.slot_pitch;
-    L.lower = (uint32_t*)cv.take((size_t)searches * L.lower_count * sizeof(uint32_t));
+    L.zero_words = searches * (L.lower_count + batch * (int64_t)(sizeof(SearchVote) / sizeof(uint32_t)));
+    L.lower = (uint32_t*)cv.take((size_t)L.zero_words * sizeof(uint32_t));
+    L.votes = reinterpret_cast<SearchVote*>(L.lower ? L.lower + searches * L.lower_count : nullptr);
     L.upper = (uint16_t*)cv.take((size_t)batch * cells * L.slab * sizeof(uint16_t));
     return L;
 }
-CoarseArgs coarse_args(const CoarseLayout& L, int src, int search) {
+// vote: whether the pairs of this search may be given up
+CoarseArgs coarse_args(const CoarseLayout& L, int batch, int src, int search, bool vote) {
     CoarseArgs ca;
     memset(&ca, 0, sizeof(ca));
     ca.src = L.map[src];
@@ -129,6 +134,8 @@ CoarseArgs coarse_args(const CoarseLayout& L, int src, int search) {
     ca.lower = L.lower + search * L.lower_count;
     ca.slab = (int32_t)L.slab;
     ca.slot_pitch = L.slot_pitch;
+    if (vote) ca.vote = L.votes + (int64_t)search * batch;
+    ca.even = COARSE_EVEN;
     return ca;
 }
 // Queries of fnn_nearest that are few beside their map are taken out of it, in the order of their slots.
@@ -628,10 +635,10 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
         qa.raw_rows = read_raw ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
-        qa.lower_count = C.lower_count;
+        qa.lower_count = C.zero_words;
         qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
         FNN_TRY(launch_quantise(qa, opts->compute, L.maps.dp, s));
-        CoarseArgs ca = coarse_args(C, 0, 0);
+        CoarseArgs ca = coarse_args(C, batch, 0, 0, coarse_votes(opts->compute, L.maps.dp));
         ca.src_listed = listed ? 1 : 0;
         FNN_TRY(launch_coarse_search(sa, ca, batch, opts->compute, L.maps.dp, s));
     } else if (staged) {
@@ -806,7 +813,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         qa.raw_rows = read_raw ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
-        qa.lower_count = RECIP_COARSE_SEARCHES * C.lower_count;
+        qa.lower_count = C.zero_words;
         qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
         FNN_TRY(launch_quantise(qa, compute, L.maps.dp, s));
     }
@@ -887,7 +894,9 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     // search number k of the call (out 0, back 0, out 1, ...): the first few may run in two steps
     auto search = [&](const SearchArgs& a, int k) -> hipError_t {
         if (k >= coarse_searches) return launch_search(a, batch, compute, L.maps.dp, s);
-        CoarseArgs ca = coarse_args(C, k & 1, k);
+        const bool votes = coarse_votes(compute, L.maps.dp);
+        CoarseArgs ca = coarse_args(C, batch, k & 1, k, votes && k < 2);
+        if (votes && k >= 1) ca.earlier = C.votes + (int64_t)(k >= 2 ? k - 2 : 0) * batch;
         ca.min_live = k < 2 ? 0 : coarse_min_live(compute, L.maps.dp);
         return launch_coarse_search(a, ca, batch, compute, L.maps.dp, s);
     };

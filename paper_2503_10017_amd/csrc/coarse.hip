@@ -240,16 +240,31 @@ __device__ __forceinline__ int64_t take_slots_from(SearchArgs& a, int first) {
     return first;
 }
 
+// Whether a search's findings say that 8-bit scores do not pay.
+__device__ __forceinline__ bool gives_up(const SearchVote& v, float even) { return v.given_up || (float)v.again * (1.0f + even) > (float)v.of * even; }
+
 // ---- step 1 ------------------------------------------------------------------------------------
+// A pair whose bounds rule too little out (see dense_coarse.hip) is given up.  Long searches (VOTE) find out on the way: behind the first cell of a chunk the
+// waves share the lower bounds of 64 queries each, behind the second some of them count the queries that the cell leaves in doubt against what all
+// workgroups know by then, and behind the third and fourth they look whether the votes were too many.  Short ones would lose 10 % to that;
+// there step 2 counts the cells that it had to take.  Step 2 then takes every cell for every query, and the later searches of the call begin
+// there.  Every result comes out of the same products either way.  Microseconds in one step /
+// in two without this / with it, fp16, 24 channels, 512x384: 16 pairs of 3072 seeds, rank 4 1663 / 2651 / 2059, one descriptor throughout 1466 / 2641 /
+// 1872, features of 4 pixels 1615 / 1474 / 1420; the seeds' one search, rank 4 461 / 802 / 723, features of 4 pixels 468 / 445 / 433; every
+// pixel of one pair, rank 4 1654 / 2670 / 1973.
+constexpr int VOTE_CELLS = 4;  // shortest chunk that is worth it
+constexpr int VOTERS = 64;     // of a pair, about; a quarter of them may decide
+
 // The four waves of a workgroup hold PAIRS pairs of query blocks each and sweep the same tiles, which reach LDS by direct loads
 // (a tile is 1 KB: one 16-byte load per lane), the next turn's while this turn's are multiplied.
 // Bound by the vector maxima and the matrix instructions, which take about the same time each.
-template <int PAIRS, int CELL_TILES>
+template <int PAIRS, int CELL_TILES, bool VOTE>
 __global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void coarse_kernel(SearchArgs a, CoarseArgs ca) {
     constexpr int TURNS = CELL_TILES / COARSE_TURN, CELLS = SEG_TILES / CELL_TILES;
     static_assert(TURNS % 2 == 0, "a cell is an even number of turns, so it starts on stage slot 0");
     __shared__ uint4 stage0[COARSE_TURN][64], stage1[COARSE_TURN][64];  // two variables, see dense_staged_kernel
+    __shared__ uint32_t leave;
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // one XCD owns a contiguous run of (pair, unit) work, see search_kernel
@@ -261,6 +276,11 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
     int n_act = a.nq;
     if (a.nq_active) n_act = min(max(a.nq_active[b], 0), a.nq);
     if (n_act < ca.min_live) return;
+    if (ca.earlier && gives_up(ca.earlier[b], ca.even)) {
+        if (ca.vote && wgi == 0 && threadIdx.x == 0) ca.vote[b].given_up = 1;  // for the searches that follow
+        return;
+    }
+    if (VOTE && ca.first_slot > 0 && ca.vote[b].given_up) return;  // an earlier launch of this search found out
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
     if (n_act <= 0) return;
 
@@ -345,6 +365,7 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
                 }
             }
         };
+        bool given_up = false;
         for (int cell = cell0; cell < cell1; ++cell) {
             const int k = (cell - cell0) * TURNS;
 #pragma unroll 1
@@ -355,6 +376,7 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
             // lanes 0..31 finish the first block of a pair, lanes 32..63 the second
             const SegInfo si = info[cell / CELLS];
             uint16_t* upper = ca.upper + ((int64_t)b * n_cells + cell) * ca.slab + slot0 + lane;
+            float first_up = 0.0f;
 #pragma unroll
             for (int p = 0; p < PAIRS; ++p) {
                 if (live[p]) {
@@ -365,8 +387,38 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
                     low[p] = __builtin_fmaxf(low[p], score - error);
                     float up = score + error;
                     up = __builtin_fmaf(__builtin_fabsf(up), 1.0f / 126.0f, up);  // so that cutting it to bf16 leaves a bound
+                    if (p == 0) first_up = up;
                     if (slot0 + p * 64 + lane < slot_end) upper[p * 64] = (uint16_t)(__float_as_uint(up) >> 16);
                     best[p][0] = best[p][1] = -0x7FFFFFFF;
+                }
+            }
+            const int done = cell - cell0;
+            if (VOTE && done < VOTE_CELLS && cell0 + VOTE_CELLS <= cell1) {  // uniform in the workgroup
+                const bool here = slot0 + lane < slot_end;
+                uint32_t* lower = &ca.lower[(int64_t)b * ca.slot_pitch + ca.first_slot + slot0 + lane];
+                // a wave each of a few workgroups votes (see the end of refine_kernel)
+                const int apart = (units + VOTERS - 1) / VOTERS;
+                if (done == 0) {
+                    if (here) atomicMax(lower, order_bits(low[0]));
+                } else if (done == 1) {
+                    if (chunk % apart == 0 && (chunk / apart & (COARSE_WAVES - 1)) == wave) {
+                        const uint32_t known = here ? atomicMax(lower, order_bits(low[0])) : 0;
+                        const uint32_t doubt = __popcll(__ballot(here && first_up >= __builtin_fmaxf(low[0], unorder_bits(known))));
+                        if (lane == 0 && here) {
+                            u64 tally = 1ull << 48 | (u64)min(64, slot_end - slot0) << 24 | doubt;
+                            tally += atomicAdd(&ca.vote[b].tally, tally);
+                            // a query is in doubt about one more of s cells with the odds even : s - 1, where `even` cells of all leave it in doubt
+                            const float even = ca.even * n_cells, others = 2.0f * chunks - 1.0f;
+                            const float all = (float)((uint32_t)(tally >> 24) & 0xFFFFFFu), doubtful = (float)((uint32_t)tally & 0xFFFFFFu);
+                            if (tally >> 48 >= VOTERS / 4 && doubtful * (even + others) > all * even)
+                                __hip_atomic_store(&ca.vote[b].given_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                    }
+                } else {
+                    if (threadIdx.x == 0) leave = __hip_atomic_load(&ca.vote[b].given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __syncthreads();  // (the next write lies behind the barriers of the next turns)
+                    given_up = leave;
+                    if (given_up) break;
                 }
             }
         }
@@ -377,6 +429,7 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);  // the turn past the last one has landed too
         __syncthreads();                     // before the next unit's first turn takes its place
+        if (given_up) return;
     }
 }
 
@@ -410,7 +463,10 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     if (MASK && ca.judge.alike(b)) return;
     int n_act = a.nq;
     if (a.nq_active) n_act = min(max(a.nq_active[b], 0), a.nq);
-    const bool every = n_act < ca.min_live;       // step 1 left these queries to this kernel
+    bool every = n_act < ca.min_live;             // step 1 left these queries to this kernel
+    constexpr bool VOTES = !MASK && CT != CT_F32 && DP <= 32;  // as coarse_votes() says (more arguments cost the widest rows a resident workgroup)
+    if (VOTES) every = every || (ca.vote && ca.vote[b].given_up) || (ca.earlier && gives_up(ca.earlier[b], ca.even));
+    uint32_t again = 0;
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
     const int begin = blockIdx.y * ca.range;
     n_act = min(n_act, begin + ca.range);
@@ -432,54 +488,64 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     for (int i = threadIdx.x; i < REFINE_PART; i += THREADS) keys[i] = 0;
     __syncthreads();
     for (int base = begin; base < n_act; base += REFINE_SCAN) {  // uniform
-        const int slot = base + (int)threadIdx.x * PER;
-        uint32_t need = 0;
-        if (slot < n_act) {
-            if constexpr (MASK) {
-                static_assert(PER <= 16, "a thread's bits lie in one 16-bit word");
-                const int64_t word = (((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab + slot) / 16;
-                need = (uint32_t)reinterpret_cast<const uint16_t*>(ca.mask)[word] >> (slot & 15) & ((1u << PER) - 1);
-            } else if (every) {
-                need = (1u << PER) - 1;
-            } else {
-                // the tables' rows hold whole 64s of slots: all PER are there
-                uint4 u[PER / 8], l[PER / 4];
-#pragma unroll
-                for (int i = 0; i < PER / 8; ++i) u[i] = reinterpret_cast<const uint4*>(upper + slot)[i];
-#pragma unroll
-                for (int i = 0; i < PER / 4; ++i) l[i] = reinterpret_cast<const uint4*>(lower + slot)[i];
-#pragma unroll
-                for (int i = 0; i < PER; ++i) {
-                    const uint4 u8 = u[i / 8], l4 = l[i / 4];
-                    const uint32_t uw = (i & 7) < 2 ? u8.x : ((i & 7) < 4 ? u8.y : ((i & 7) < 6 ? u8.z : u8.w));
-                    const uint32_t lw = (i & 3) == 0 ? l4.x : ((i & 3) == 1 ? l4.y : ((i & 3) == 2 ? l4.z : l4.w));
-                    const float up = __uint_as_float(i & 1 ? uw & 0xFFFF0000u : uw << 16);
-                    if (up >= unorder_bits(lw)) need |= 1u << i;
-                }
+        if (!MASK && every) {
+            // listed side by side: one after the other, PER to a thread, the loads of their rows were a memory latency each (16 512x384 pairs
+            // of seeds, about a hundred of each still live in the second iteration: the call 1027 -> 1005 us)
+            const int count = min(REFINE_SCAN, n_act - base);
+            for (int i = threadIdx.x; i < count; i += THREADS) {
+                list_slot[i] = (uint16_t)(base - begin + i);
+                list_row[i] = (int)query_row(a, qbase, base + i);
             }
-            if (n_act - slot < PER) need &= (1u << (n_act - slot)) - 1;
-        }
-        // a prefix sum over the wave, one LDS atomic for its total
-        const int mine = __popc(need);
-        int upto = mine;
+            if (threadIdx.x == 0) n_list = count;
+        } else {
+            const int slot = base + (int)threadIdx.x * PER;
+            uint32_t need = 0;
+            if (slot < n_act) {
+                if constexpr (MASK) {
+                    static_assert(PER <= 16, "a thread's bits lie in one 16-bit word");
+                    const int64_t word = (((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab + slot) / 16;
+                    need = (uint32_t)reinterpret_cast<const uint16_t*>(ca.mask)[word] >> (slot & 15) & ((1u << PER) - 1);
+                } else {
+                    // the tables' rows hold whole 64s of slots: all PER are there
+                    uint4 u[PER / 8], l[PER / 4];
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int y = __shfl_up(upto, d);
-            if (lane >= d) upto += y;
-        }
-        const int count = __shfl(upto, 63);
-        int at = 0;
-        if (lane == 0 && count) at = atomicAdd(&n_list, count);
-        at = __shfl(at, 0) + upto - mine;
-        for (; need; need &= need - 1, ++at) {
-            const int found = slot + __builtin_ctz(need);
-            list_slot[at] = (uint16_t)(found - begin);
-            list_row[at] = (int)query_row(a, qbase, found);
+                    for (int i = 0; i < PER / 8; ++i) u[i] = reinterpret_cast<const uint4*>(upper + slot)[i];
+#pragma unroll
+                    for (int i = 0; i < PER / 4; ++i) l[i] = reinterpret_cast<const uint4*>(lower + slot)[i];
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) {
+                        const uint4 u8 = u[i / 8], l4 = l[i / 4];
+                        const uint32_t uw = (i & 7) < 2 ? u8.x : ((i & 7) < 4 ? u8.y : ((i & 7) < 6 ? u8.z : u8.w));
+                        const uint32_t lw = (i & 3) == 0 ? l4.x : ((i & 3) == 1 ? l4.y : ((i & 3) == 2 ? l4.z : l4.w));
+                        const float up = __uint_as_float(i & 1 ? uw & 0xFFFF0000u : uw << 16);
+                        if (up >= unorder_bits(lw)) need |= 1u << i;
+                    }
+                }
+                if (n_act - slot < PER) need &= (1u << (n_act - slot)) - 1;
+            }
+            // a prefix sum over the wave, one LDS atomic for its total
+            const int mine = __popc(need);
+            int upto = mine;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int y = __shfl_up(upto, d);
+                if (lane >= d) upto += y;
+            }
+            const int count = __shfl(upto, 63);
+            int at = 0;
+            if (lane == 0 && count) at = atomicAdd(&n_list, count);
+            at = __shfl(at, 0) + upto - mine;
+            for (; need; need &= need - 1, ++at) {
+                const int found = slot + __builtin_ctz(need);
+                list_slot[at] = (uint16_t)(found - begin);
+                list_row[at] = (int)query_row(a, qbase, found);
+            }
         }
         __syncthreads();
         const int n = n_list;
         __syncthreads();  // read by every wave before the next round adds to it
         if (n > REFINE_LIST - REFINE_SCAN || base + REFINE_SCAN >= n_act) {  // uniform
+            again += n;
             auto sweep = [&](int part, int part_end, auto tail_tag) {
                 constexpr bool TAIL = decltype(tail_tag)::value;
                 Frag next = O::load(src + (int64_t)list_row[min(part + c, n - 1)] * O::ROW_BYTES, h);
@@ -534,6 +600,11 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
             if (threadIdx.x == 0) n_list = 0;
             __syncthreads();
         }
+    }
+    // additions to one word are served one after the other: the workgroups of every 16th cell speak for the rest
+    if (VOTES && ca.vote && !every && threadIdx.x == 0 && cell % 16 == 0) {
+        atomicAdd(&ca.vote[b].again, (u64)again);
+        atomicAdd(&ca.vote[b].of, (u64)(n_act - begin));
     }
 }
 
@@ -600,6 +671,9 @@ double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, int d,
     const double segments = (double)m / SEG_PIXELS, again = 1.5 * coarse_cells_again(segments, d, l2) / segments;
     return blocks * (exact * (1.0 - again) - coarse) - 5000.0 - (double)batch * m * coarse_row_bytes(compute, dp) / BYTES_PER_NS;
 }
+// Wider rows and fp32 products cost so much more than an 8-bit score that two steps lose little at worst (one descriptor throughout, two
+// 512x384 pairs in fp32: a quarter).
+bool coarse_votes(int compute, int dp) { return compute != FNN_F32 && dp <= 32; }
 double coarse_cost(int64_t rows, int compute, int dp) {
     return 4000.0 + (double)rows * (coarse_row_bytes(compute, dp) + COARSE_ROW_BYTES + 4) / BYTES_PER_NS;
 }
@@ -619,12 +693,12 @@ int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch) {
 
 // Workgroups that the current device holds at once (0: unknown), and those of a launch for each pair.
 template <int PAIRS, int CELL>
-static int coarse_resident() {
+static int coarse_resident() {  // (voting costs registers, not resident workgroups)
     static DeviceCache resident_wgs;
     const long long resident = resident_wgs.get([](int dev) -> long long {
         int per_cu = 0;
         hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, coarse_kernel<PAIRS, CELL>, COARSE_WAVES * 64, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, coarse_kernel<PAIRS, CELL, false>, COARSE_WAVES * 64, 0) != hipSuccess ||
             hipGetDeviceProperties(&prop, dev) != hipSuccess)
             return -1;
         return (long long)(per_cu > 0 ? per_cu : 1) * prop.multiProcessorCount;
@@ -650,7 +724,9 @@ template <int PAIRS, int CELL>
 static hipError_t launch_coarse_t(const SearchArgs& a, const CoarseArgs& ca, int batch, hipStream_t s) {
     const int resident = coarse_resident<PAIRS, CELL>();
     if (resident == 0) return hipErrorUnknown;
-    return launch_detail(TK_COARSE, PAIRS * 2, coarse_kernel<PAIRS, CELL>, dim3(coarse_wgs_per_pair(resident, batch), batch), dim3(COARSE_WAVES * 64), 0, s, a, ca);
+    if (CELL == SEG_TILES && ca.vote)
+        return launch_detail(TK_COARSE, PAIRS * 2, coarse_kernel<PAIRS, CELL, CELL == SEG_TILES>, dim3(coarse_wgs_per_pair(resident, batch), batch), dim3(COARSE_WAVES * 64), 0, s, a, ca);
+    return launch_detail(TK_COARSE, PAIRS * 2, coarse_kernel<PAIRS, CELL, false>, dim3(coarse_wgs_per_pair(resident, batch), batch), dim3(COARSE_WAVES * 64), 0, s, a, ca);
 }
 // CELL: tiles of a workgroup.
 template <int CT, int DP, int CELL, bool MASK = false>

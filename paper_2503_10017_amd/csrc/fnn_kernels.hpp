@@ -97,6 +97,14 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 hipError_t launch_fill_i32f32(int32_t* idx, float* score, int64_t count, hipStream_t s);
 
 // ---- one-directional search ------------------------------------------------------------
+// What a search in two steps (coarse.hip) found out about the contrast of a pair.  A pair is given up where its queries need so many cells again
+// that 8-bit scores do not pay.
+struct SearchVote {
+    u64 tally;          // of some waves of step 1, while it ran: queries that a cell leaves in doubt (24 bits), of how many (24), by how many waves (16)
+    u64 again, of;      // of step 2: cells that queries had to be multiplied with, of how many
+    uint32_t given_up;  // in step 1
+    uint32_t reserved;
+};
 struct SearchArgs {
     const char* src;        // prepared map the queries are rows of, [batch][*][dp]
     int64_t src_bstride;    // bytes per pair
@@ -207,6 +215,9 @@ struct CoarseArgs {
     int32_t range;         // (the launchers set these) queries that a workgroup of the second step looks at
     int32_t first_slot;
     int32_t min_live;      // fewer live queries of a pair than this: its cells are refined for every query
+    SearchVote* vote;      // [batch] (0 on entry), or NULL: scores in 8 bits whatever the maps hold
+    const SearchVote* earlier;  // [batch] of a search of the same maps, or NULL: pairs that it gives up begin with step 2, for every query
+    float even;            // (vote) cells that a query may have to be multiplied with before one step is faster, over those that it need not
 };
 // What launch_search does: the queries' list and live count, the prepared maps and the keys are those of `a`.
 hipError_t launch_coarse_search(const SearchArgs& a, const CoarseArgs& ca, int batch, int compute, int dp, hipStream_t s);
@@ -217,8 +228,12 @@ hipError_t launch_refine(const SearchArgs& a, const CoarseArgs& ca, int batch, i
 // it has to run in one), and what the 8-bit maps of `rows` pixels cost
 double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, int d, bool l2);
 double coarse_cells_again(double cells, int d, bool l2);
+bool coarse_votes(int compute, int dp);  // whether the searches of such rows should
 double coarse_cost(int64_t rows, int compute, int dp);
 constexpr double COARSE_LEAST_GAIN = 3000.0;  // of a call
+// See CoarseArgs.even: three cells in seven.  (Of a search of 16-bit rows, 46 ns a block in one step, some 17 of 28 are still to do in 8 bits when the
+// votes are in, and the second step takes 58 for every block it is left with.)
+constexpr float COARSE_EVEN = 0.75f;
 // Fewer queries per pair than this spread the second step thin: a call with so few runs in one
 inline int64_t coarse_least_queries(int compute, int dp) { return compute == FNN_F32 || dp > 32 ? 256 : 2048; }
 // Live queries of a pair below which its part of a later search goes straight to the second step
