@@ -429,8 +429,9 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
     for (int sb = 0; sb < C.n_sb; sb += C.slab) {
         da.first_sb = sb;
         da.n_sb = C.n_sb - sb < C.slab ? C.n_sb - sb : C.slab;
+        da.swept = sb == 0 ? swept : none;
         e = launch_dense_coarse(da, batch, s);
-        if (e == hipSuccess) e = launch_dense_select(da, 0, at_once ? 2 : 1, at_once ? swept : none, batch, s);
+        if (e == hipSuccess) e = launch_dense_select(da, 0, at_once ? 2 : 1, batch, s);
         ca.mask = da.mask[0];
         ca.slab = da.n_sb * DENSE_SB_PIXELS;
         ca.n_cells = da.n_cells;
@@ -439,7 +440,7 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
         if (e == hipSuccess) e = launch_refine(rows, ca, batch, compute, L.maps.dp, s);
         if (e != hipSuccess) return e;
     }
-    if (!at_once) e = launch_dense_select(da, 1, 1, swept, batch, s);
+    if (!at_once) e = launch_dense_select(da, 1, 1, batch, s);
     ca.mask = da.mask[1];
     ca.slab = da.map[1].n_segs * da.seg_pixels;
     ca.n_cells = da.map[0].n_segs;

@@ -49,6 +49,16 @@ __device__ __forceinline__ int transpose_max16_int(const int (&x)[16], int lane)
     return max((int)sw[0], (int)sw[1]);
 }
 
+// The prepared rows of image 1 of a pair, in the order that the dense kernels sweep: a thread of a two-dimensional grid copies 16 bytes at a time.
+__device__ __forceinline__ void dense_permute(const DenseSwept& w, int b) {
+    const uint4* from = reinterpret_cast<const uint4*>(w.from + (int64_t)b * w.from_bstride);
+    uint4* to = reinterpret_cast<uint4*>(w.to + (int64_t)b * w.n_pad * w.row_bytes);
+    const int words = w.row_bytes / 16;
+    const int64_t n_threads = (int64_t)gridDim.x * gridDim.y * blockDim.x;
+    for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < w.n_pad * words; i += n_threads)
+        to[i] = from[slot_pixel(i / words) * words + i % words];
+}
+
 // A workgroup sweeps one run of queries past a few cells of candidates, a group of 16 tiles after the other.  At the end of every
 // SEGMENT of queries the candidates' maxima are reduced over the lanes and kept.
 // Bound by the vector unit: 16 three-input maxima per block, 16.8 instructions in all, that is 67 cycles beside 32 of the
@@ -62,7 +72,10 @@ void dense_coarse_kernel(DenseCoarseArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int held = held_register(lane);
     const int cell0 = blockIdx.x * a.cells_per_wg, sb = blockIdx.y, b = blockIdx.z;
-    if (a.judge.alike(b)) return;
+    if (a.judge.alike(b)) {
+        if (a.swept.to) dense_permute(a.swept, b);
+        return;
+    }
     constexpr int SEGS = DENSE_SB_PIXELS / SEGMENT, SEG_TURNS = DC_TURNS / SEGS;
     const int64_t pixels1 = (int64_t)a.map[0].n_segs * SEGMENT, pixels2 = (int64_t)a.map[1].n_segs * SEGMENT;
     const char* blocks = a.map[0].rows + ((int64_t)b * pixels1 + (int64_t)(a.first_sb + sb) * DENSE_SB_PIXELS) * COARSE_ROW_BYTES;
@@ -162,8 +175,6 @@ void dense_coarse_kernel(DenseCoarseArgs a) {
 constexpr int SELECT_WAVES = 4;
 constexpr int SELECT_SLOTS = 4;
 constexpr int SELECT_DEEP = 6;  // cells in flight per wave
-// Of a pair that the samples found alike, the workgroups put the prepared rows of image 1 into the order that the dense kernels sweep (swept.to is NULL in
-// a launch that does not): a thread copies 16 bytes at a time.
 struct SelectSide {
     const uint16_t* best;       // [batch][n_cells][pitch]
     uint64_t* mask;             // [batch][n_cells][pitch / 64]
@@ -178,21 +189,10 @@ struct SelectSide {
 struct SelectArgs {
     SelectSide side[2];     // blockIdx.z
     DenseJudge judge;
-    DenseSwept swept;
 };
 __global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectArgs args) {
-    const SelectSide& a = args.side[blockIdx.z];
-    if (args.judge.alike(blockIdx.y)) {
-        const DenseSwept& w = args.swept;
-        if (!w.to) return;
-        const uint4* from = reinterpret_cast<const uint4*>(w.from + (int64_t)blockIdx.y * w.from_bstride);
-        uint4* to = reinterpret_cast<uint4*>(w.to + (int64_t)blockIdx.y * w.n_pad * w.row_bytes);
-        const int words = w.row_bytes / 16;
-        const int64_t n_threads = (int64_t)gridDim.x * gridDim.z * (SELECT_WAVES * 64);
-        for (int64_t i = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * (SELECT_WAVES * 64) + threadIdx.x; i < w.n_pad * words; i += n_threads)
-            to[i] = from[slot_pixel(i / words) * words + i % words];
-        return;
-    }
+    const SelectSide a = blockIdx.z ? args.side[1] : args.side[0];  // (an index would hide from the compiler that the pointers are global)
+    if (args.judge.alike(blockIdx.y)) return;
     if ((int64_t)blockIdx.x * (64 * SELECT_SLOTS) >= a.pitch) return;  // uniform: the sides differ in size
     __shared__ float low[SELECT_WAVES][SELECT_SLOTS][64];
     const int lane = threadIdx.x & 63;
@@ -376,10 +376,9 @@ static SelectSide select_side(const DenseCoarseArgs& a, int side) {
     sa.n_segs = other.n_segs;
     return sa;
 }
-hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, const DenseSwept& swept, int batch, hipStream_t s) {
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, int batch, hipStream_t s) {
     SelectArgs args;
     args.judge = a.judge;
-    args.swept = swept;
     int64_t pitch = 0;
     for (int i = 0; i < sides; ++i) {
         args.side[i] = select_side(a, first_side + i);

@@ -355,6 +355,14 @@ hipError_t launch_dense(const DenseArgs& a, int batch, int compute, int dp, int3
 // Pass 1 alone.
 hipError_t launch_dense_pass1(const DenseArgs& a, int batch, int compute, int dp, hipStream_t s);
 
+// Of pairs that turn out alike: the prepared rows of image 1 in the order that the dense kernels sweep.
+struct DenseSwept {
+    const char* from;  // [batch] prepared maps in natural order
+    int64_t from_bstride;
+    char* to;          // [batch][n_pad][row_bytes], or NULL: not in this launch
+    int64_t n_pad;     // a multiple of DENSE_SB_PIXELS
+    int32_t row_bytes; // a multiple of 16
+};
 // Pass 1 in 8 bits (dense_coarse.hip), on maps quantised in segments of seg_pixels: the largest 8-bit score of every query in
 // every cell of candidates, and of every candidate in every segment of queries.
 struct DenseCoarseArgs {
@@ -373,21 +381,14 @@ struct DenseCoarseArgs {
     uint32_t* sample_lower;  // [batch][2][DENSE_SAMPLES] order_bits (0 on entry)
     int32_t* marked;         // [batch][2] (0 on entry): see DenseJudge
     DenseJudge judge;
+    DenseSwept swept;
 };
 constexpr int DENSE_SAMPLES = 128;  // pixels of either image
 // Counts the marks of the samples.
 hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s);
-// Of pairs that turn out alike: the prepared rows of image 1 in the order that the dense kernels sweep.
-struct DenseSwept {
-    const char* from;  // [batch] prepared maps in natural order
-    int64_t from_bstride;
-    char* to;          // [batch][n_pad][row_bytes], or NULL
-    int64_t n_pad;     // a multiple of DENSE_SB_PIXELS
-    int32_t row_bytes; // a multiple of 16
-};
 hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s);
 // From best[side] to mask[side] for one or both sides.  0: the queries of this launch's runs; 1: the candidates, once every run is done.
-hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, const DenseSwept& swept, int batch, hipStream_t s);
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, int batch, hipStream_t s);
 int dense_cell_groups(int64_t n, int64_t m);
 int dense_seg_pixels(int64_t n);
 // Share of the cells, of both directions together, that may be multiplied again before the dense kernels are faster
