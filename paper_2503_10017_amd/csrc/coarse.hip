@@ -679,9 +679,10 @@ double coarse_cost(int64_t rows, int compute, int dp) {
 }
 
 // Half segments balance a small search better (its workgroups get two or three cells each) and spread step 2 over more
-// workgroups; a large one saves the second half's epilogue and start-up.  Whole against half segments, all of a call's time: one
-// 512x384 pair with 3072 queries 237 / 227 us, four 517x389 ones 497 / 493, four two-term ones 784 / 736; one 1024x768 pair with 12288
-// queries 1097 / 1128, 16 512x384 ones 1492 / 1529.
+// workgroups; a large one saves the second half's epilogue and start-up.  The line is drawn in pairs of query blocks times segments.  Whole / half
+// segments, all of a call's time in us: 512x384, 3072 queries, 4 pairs (36864) 135 / 130, 6 178 / 172, 7 (64512) 207 / 211, 8 (73728) 225 / 238, 10 282 / 289,
+// 12 342 / 344, 16 437 / 458, seeds that walk, 6 pairs 510 / 507, 8 593 / 629; 640x480, 4800 queries, 3 pairs (67500) 193 / 186, 4 243 / 245, walking 538 / 547 and
+// 665 / 687; one 768x576 pair, 6912 queries (46656) 141 / 125; one 896x672 pair, 9408 (86436) 206 / 209, walking 566 / 596.
 int coarse_cells(int64_t nq, int64_t n_segs, int batch) { return (double)((nq + 63) / 64) * n_segs * batch < 73728.0 ? 2 : 1; }
 
 int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch) {

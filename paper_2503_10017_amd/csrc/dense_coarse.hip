@@ -322,9 +322,12 @@ __global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseA
     if ((threadIdx.x & 63) == 0 && marks) atomicAdd(&a.marked[b * 2 + side], marks);
 }
 
-// Wider cells keep the table of a large map small, narrower ones leave less to multiply again.
-int dense_seg_pixels(int64_t n) { return n > 400000 ? 4096 : 2048; }
-int dense_cell_groups(int64_t n, int64_t m) { return m > 400000 ? dense_seg_pixels(n) / 512 : 2; }  // a cell lies in one segment
+// Wider cells keep the table of a large map small, narrower ones leave less to multiply again.  Segments of 2048 pixels and cells of 1024 against 4096 and
+// 4096, one pair of such maps, the whole call in ms: 196608 pixels 1.75 / 1.91, 262144 2.86 / 2.91, 294912 3.71 / 3.76, 307200 4.16 / 4.06,
+// 371712 6.10 / 5.88, 442368 8.43 / 8.16, 786432 26.4 / 24.9.
+constexpr int64_t DENSE_WIDE_PIXELS = 300000;
+int dense_seg_pixels(int64_t n) { return n > DENSE_WIDE_PIXELS ? 4096 : 2048; }
+int dense_cell_groups(int64_t n, int64_t m) { return m > DENSE_WIDE_PIXELS ? dense_seg_pixels(n) / 512 : 2; }  // a cell lies in one segment
 // What a block of 32x32 scores takes one SIMD in the dense kernels, in dense_coarse_kernel, and in the second step
 static double dense_exact(int compute, int dp) { return compute == FNN_F32 ? 15.8 * dp : (dp <= 32 ? 2.33 * dp : 1.83 * dp); }
 constexpr double DENSE_COARSE = 38.0;
