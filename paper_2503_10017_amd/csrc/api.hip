@@ -198,11 +198,12 @@ DenseLayout carve_dense(Carver& cv, int batch, int64_t n, int64_t m, int d, int 
 
 // Room for the dense mode's 8-bit pass behind its own layout.
 struct DenseCoarseLayout {
-    DenseCoarseArgs args;
+    DenseCoarseArgs args;  // of the first group of pairs
+    int32_t group;         // pairs that share the tables of scores, one group after the other
     int32_t n_sb;  // runs of DENSE_SB_PIXELS of image 1
     int32_t slab;  // ... per launch
     int64_t sample_words;  // 32-bit words that start at 0, from args.sample_lower on
-    char* swept;   // image 1 as the dense kernels read it
+    char* swept;   // image 1 of a group as the dense kernels read it
 };
 DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m, const MapsLayout& maps) {
     DenseCoarseLayout L;
@@ -215,19 +216,23 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     a.n_tiles[1] = (int32_t)((m + 31) / 32);
     a.cell_groups = dense_cell_groups(n, m);
     a.n_cells = (int32_t)((m + 512 * a.cell_groups - 1) / (512 * a.cell_groups));
-    // 128 MB of scores for the queries of a launch
-    const int64_t per_sb = (int64_t)batch * a.n_cells * DENSE_SB_PIXELS * (int64_t)sizeof(uint16_t);
+    // Tables of scores: the candidates' of as many pairs at a time as 512 MB hold (all of a pair's), their queries' a run of 128 MB at a time.  (Groups
+    // of four 512x384 pairs instead of eight cost 1 %.)
+    const size_t pixels2 = (size_t)a.map[1].n_segs * a.seg_pixels, cols = a.map[0].n_segs * pixels2 * sizeof(uint16_t);
+    const int64_t together = cols > 0 && cols < ((size_t)512 << 20) ? (int64_t)(((size_t)512 << 20) / cols) : 1;
+    const int64_t groups = (batch + together - 1) / together;
+    L.group = (int32_t)((batch + groups - 1) / groups);
+    const int64_t per_sb = L.group * a.n_cells * (int64_t)DENSE_SB_PIXELS * (int64_t)sizeof(uint16_t);
     int64_t slab = ((int64_t)128 << 20) / (per_sb > 0 ? per_sb : 1);
     if (slab < 1) slab = 1;
     L.n_sb = (int32_t)((n + DENSE_SB_PIXELS - 1) / DENSE_SB_PIXELS);
     const int64_t launches = (L.n_sb + slab - 1) / slab;
     L.slab = launches > 0 ? (int32_t)((L.n_sb + launches - 1) / launches) : 1;
-    const size_t pixels2 = (size_t)a.map[1].n_segs * a.seg_pixels;
     a.best[0] = (uint16_t*)cv.take((size_t)per_sb * L.slab);
-    a.best[1] = (uint16_t*)cv.take((size_t)batch * a.map[0].n_segs * pixels2 * sizeof(uint16_t));
+    a.best[1] = (uint16_t*)cv.take((size_t)L.group * cols);
     a.mask[0] = (uint64_t*)cv.take((size_t)per_sb * L.slab / 16);
-    a.mask[1] = (uint64_t*)cv.take((size_t)batch * a.map[0].n_segs * pixels2 / 8);
-    L.swept = (char*)cv.take((size_t)batch * maps.bstride1);
+    a.mask[1] = (uint64_t*)cv.take((size_t)L.group * cols / 16);
+    L.swept = (char*)cv.take((size_t)L.group * maps.bstride1);
     a.pixels[0] = n;
     a.pixels[1] = m;
     a.sample_upper[0] = (float*)cv.take((size_t)batch * a.n_cells * DENSE_SAMPLES * sizeof(float));
@@ -388,8 +393,44 @@ void fill_quantise_side(QuantiseSide& sd, int32_t batch, const fnn_map* maps, bo
     sd.out = out;
 }
 
+// The pairs of a group: see dense_two_steps.
+hipError_t dense_group(const DenseCoarseLayout& C, const DenseLayout& L, const SearchArgs& rows, const SearchArgs& cols, DenseCoarseArgs da, DenseArgs sweep,
+                       bool at_once, int pairs, int compute, hipStream_t s) {
+    CoarseArgs ca;
+    memset(&ca, 0, sizeof(ca));
+    ca.judge = sweep.judge = da.judge;
+    hipError_t e = hipSuccess;
+    const DenseSwept none = {}, swept = {rows.src, rows.src_bstride, C.swept, L.maps.n_pad, (int32_t)(L.maps.bstride1 / L.maps.n_pad)};
+    for (int sb = 0; sb < C.n_sb; sb += C.slab) {
+        da.first_sb = sb;
+        da.n_sb = C.n_sb - sb < C.slab ? C.n_sb - sb : C.slab;
+        da.swept = sb == 0 ? swept : none;
+        e = launch_dense_coarse(da, pairs, s);
+        if (e == hipSuccess) e = launch_dense_select(da, 0, at_once ? 2 : 1, pairs, s);
+        ca.mask = da.mask[0];
+        ca.slab = da.n_sb * DENSE_SB_PIXELS;
+        ca.n_cells = da.n_cells;
+        ca.cell_shift = da.cell_groups == 8 ? 2 : (da.cell_groups == 4 ? 1 : 0);
+        ca.first_slot = sb * DENSE_SB_PIXELS;
+        ca.side = 0;
+        if (e == hipSuccess) e = launch_refine(rows, ca, pairs, compute, L.maps.dp, s);
+        if (e != hipSuccess) return e;
+    }
+    if (!at_once) e = launch_dense_select(da, 1, 1, pairs, s);
+    ca.mask = da.mask[1];
+    ca.slab = da.map[1].n_segs * da.seg_pixels;
+    ca.n_cells = da.map[0].n_segs;
+    ca.cell_shift = da.seg_pixels == 4096 ? 2 : 1;
+    ca.first_slot = 0;
+    ca.side = 1;
+    if (e == hipSuccess) e = launch_refine(cols, ca, pairs, compute, L.maps.dp, s);
+    sweep.d1 = C.swept;
+    if (e == hipSuccess) e = launch_dense_pass1(sweep, pairs, compute, L.maps.dp, s);
+    return e;
+}
+
 // Both directions of the dense mode from its 8-bit maps to the keys: pass 1 range by range of image 1, the second step for the queries
-// of a range at once, for the candidates when every range is done.  Pairs whose samples say that this would be the slower way are swept
+// of a range at once, for the candidates when every range is done; a group of pairs after the other.  Pairs whose samples say that this would be the slower way are swept
 // by the dense kernels of `sweep` instead.
 hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int batch, int64_t n, int64_t m, int compute, DenseArgs sweep, hipStream_t s) {
     SearchArgs rows;
@@ -414,45 +455,36 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
     cols.m_tiles = (int32_t)((n + 31) / 32);
     cols.out_keys = L.col_keys;
 
-    CoarseArgs ca;
-    memset(&ca, 0, sizeof(ca));
     DenseCoarseArgs da = C.args;
     hipError_t e = launch_dense_sample(da, batch, s);
-    if (e != hipSuccess) return e;
     const double limit = dense_coarse_limit(compute, L.maps.dp) * DENSE_SAMPLES;
     da.judge.marked = da.marked;
     da.judge.weight[0] = (float)(1.0 / (limit * da.n_cells));
     da.judge.weight[1] = (float)(1.0 / (limit * da.map[0].n_segs));
-    ca.judge = sweep.judge = da.judge;
-    const DenseSwept none = {}, swept = {rows.src, rows.src_bstride, C.swept, L.maps.n_pad, (int32_t)(L.maps.bstride1 / L.maps.n_pad)};
-    const bool at_once = C.slab >= C.n_sb;  // both sides' marks in one launch
-    for (int sb = 0; sb < C.n_sb; sb += C.slab) {
-        da.first_sb = sb;
-        da.n_sb = C.n_sb - sb < C.slab ? C.n_sb - sb : C.slab;
-        da.swept = sb == 0 ? swept : none;
-        e = launch_dense_coarse(da, batch, s);
-        if (e == hipSuccess) e = launch_dense_select(da, 0, at_once ? 2 : 1, batch, s);
-        ca.mask = da.mask[0];
-        ca.slab = da.n_sb * DENSE_SB_PIXELS;
-        ca.n_cells = da.n_cells;
-        ca.cell_shift = da.cell_groups == 8 ? 2 : (da.cell_groups == 4 ? 1 : 0);
-        ca.first_slot = sb * DENSE_SB_PIXELS;
-        if (e == hipSuccess) e = launch_refine(rows, ca, batch, compute, L.maps.dp, s);
-        if (e != hipSuccess) return e;
-    }
-    if (!at_once) e = launch_dense_select(da, 1, 1, batch, s);
-    ca.mask = da.mask[1];
-    ca.slab = da.map[1].n_segs * da.seg_pixels;
-    ca.n_cells = da.map[0].n_segs;
-    ca.cell_shift = da.seg_pixels == 4096 ? 2 : 1;
-    ca.first_slot = 0;
-    if (e == hipSuccess) e = launch_refine(cols, ca, batch, compute, L.maps.dp, s);
-
-    sweep.d1 = C.swept;
     // a launch that leaves every pair alone costs its workgroups' start: no more of them than fill the chip a few times
-    auto wgs = [&]() { return (int64_t)sweep.n_sb * ((sweep.m_tiles + DENSE_TILES_PER_GROUP * sweep.groups_per_wg - 1) / (DENSE_TILES_PER_GROUP * sweep.groups_per_wg)); };
-    while (wgs() > 8192) sweep.groups_per_wg *= 2;
-    if (e == hipSuccess) e = launch_dense_pass1(sweep, batch, compute, L.maps.dp, s);
+    auto wgs = [&]() { return (int64_t)C.group * sweep.n_sb * ((sweep.m_tiles + DENSE_TILES_PER_GROUP * sweep.groups_per_wg - 1) / (DENSE_TILES_PER_GROUP * sweep.groups_per_wg)); };
+    while (wgs() > 4096) sweep.groups_per_wg *= 2;
+    const bool at_once = C.slab >= C.n_sb;  // both sides' marks in one launch
+    for (int b0 = 0; b0 < batch && e == hipSuccess; b0 += C.group) {
+        const int pairs = batch - b0 < C.group ? batch - b0 : C.group;
+        e = dense_group(C, L, rows, cols, da, sweep, at_once, pairs, compute, s);
+        const int step = C.group;
+        rows.src += step * rows.src_bstride;
+        rows.tgt += step * rows.tgt_bstride;
+        rows.out_keys += step * n;
+        cols.src += step * cols.src_bstride;
+        cols.tgt += step * cols.tgt_bstride;
+        cols.out_keys += step * m;
+        for (CoarseMap& map : da.map) {
+            map.rows += (int64_t)step * map.n_segs * da.seg_pixels * COARSE_ROW_BYTES;
+            map.row_bound += (int64_t)step * map.n_segs * da.seg_pixels;
+            map.seg += (int64_t)step * map.n_segs;
+        }
+        da.judge.marked += 2 * step;
+        sweep.d2 += step * sweep.d2_bstride;
+        sweep.row_keys += step * n;
+        sweep.col_keys += step * m;
+    }
     return e;
 }
 

@@ -444,6 +444,7 @@ constexpr int REFINE_SCAN = 4096;             // queries looked at between two l
 constexpr int REFINE_LIST = REFINE_SCAN + 1024;
 constexpr int REFINE_PART = 512;               // a multiple of 32
 constexpr int REFINE_MOST = 4 * REFINE_SCAN;   // queries of a workgroup (ca.range: a multiple of REFINE_SCAN)
+constexpr int REFINE_SHORT = 128;              // of REFINE_SCAN queries; lists no longer than this are not worth a workgroup
 
 // MASK: which queries need a cell is read from a table of bits; the keys name units of DENSE_J tiles instead of tiles.
 template <int CT, int DP, int RT, int WAVES, bool MASK>
@@ -468,8 +469,10 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     if (VOTES) every = every || (ca.vote && ca.vote[b].given_up) || (ca.earlier && gives_up(ca.earlier[b], ca.even));
     uint32_t again = 0;
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
-    const int begin = blockIdx.y * ca.range;
-    n_act = min(n_act, begin + ca.range);
+    int range = ca.range;
+    if (MASK && range < REFINE_MOST && ca.judge.marked[2 * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
+    const int begin = blockIdx.y * range;
+    n_act = min(n_act, begin + range);
     const int tile0 = (cell * WAVES + wave) * RT;
     if (n_act <= begin) return;
 
@@ -736,10 +739,10 @@ static hipError_t launch_refine_t(const SearchArgs& a, CoarseArgs ca, int batch,
     const int64_t slots = a.nq - ca.first_slot < ca.slab ? a.nq - ca.first_slot : ca.slab;
     const unsigned cells = (unsigned)((a.m_tiles + CELL - 1) / CELL);
     // Where neighbouring pixels resemble each other, what a cell is marked by lies together: a workgroup with many queries may need the
-    // cell for all of them and be what the launch waits for.  Short ranges even that out while the workgroups are few; each reads
-    // its tiles again (dense mode, fp16, 24 channels, both launches with ranges of 16384 / 4096: 512x384, features of 128 pixels
-    // 1104 / 548 us, of one 137 / 132; 1024x768 4302 / 3815 and 1085 / 1662).  Rows that cost more per product lose more to the last block of a
-    // list than they gain (fp32, 384x288, features of one pixel 356 / 794).
+    // cell for all of them and be what the launch waits for.  Short ranges even that out (dense mode, fp16, 24 channels, 512x384, features of 128
+    // pixels, both launches with ranges of 16384 / 4096: 1104 / 548 us); but each reads its tiles again and fills up its last block, so they are taken
+    // while the workgroups are few and where the samples say that the lists are long (features of one pixel, four pairs: 324 / 365 us; 1024x768
+    // 1085 / 1662).  Rows that cost more per product lose more to the last block of a list than they gain (fp32, 384x288, features of one pixel 356 / 794).
     ca.range = REFINE_MOST;
     if (MASK && CT != CT_F32 && DP <= 32)
         for (ca.range = REFINE_SCAN; ca.range < REFINE_MOST && cells * ((slots + ca.range - 1) / ca.range) * batch > 16384;) ca.range *= 2;

@@ -339,7 +339,7 @@ double dense_coarse_limit(int compute, int dp) {
 }
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2) {
     if (n < 16384 || m < 16384 || (compute != FNN_F32 && dp <= 16)) return -1e30;
-    if ((double)batch * m * (n / dense_seg_pixels(n)) * 2.0 > 4e9) return -1e30;  // the candidates' table of bounds would be too large
+    if ((double)m * (n / dense_seg_pixels(n)) * 2.0 > 4e9) return -1e30;  // the candidates' table of a pair would be too large
     const double cell = 512.0 * dense_cell_groups(n, m), row_bytes = dp * elem_size(compute);
     const double cells[2] = {m / cell, (double)n / dense_seg_pixels(n)};
     const double again = coarse_cells_again(cells[0], d, l2) / cells[0] + coarse_cells_again(cells[1], d, l2) / cells[1];

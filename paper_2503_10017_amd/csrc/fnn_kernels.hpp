@@ -212,7 +212,8 @@ struct CoarseArgs {
     int32_t cell_shift;    // a cell is 2^cell_shift workgroups of the second step
     const uint64_t* mask;  // launch_refine: [batch][n_cells][slab / 64] the slots that need a cell, instead of the bounds
     DenseJudge judge;      // launch_refine: pairs to leave alone
-    int32_t range;         // (the launchers set these) queries that a workgroup of the second step looks at
+    int32_t side;          // ... and whose samples the marks are: image 1's or 2's
+    int32_t range;         // (the launchers set these) queries that a workgroup of the second step looks at, or fewer
     int32_t first_slot;
     int32_t min_live;      // fewer live queries of a pair than this: its cells are refined for every query
     SearchVote* vote;      // [batch] (0 on entry), or NULL: scores in 8 bits whatever the maps hold

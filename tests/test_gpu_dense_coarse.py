@@ -158,3 +158,23 @@ def test_maps_without_contrast_take_no_longer_than_one_step(kind):
         return min(times)
 
     assert least(ws) < 1.4 * least(small)
+
+
+def test_pairs_in_groups_that_share_their_tables():
+    """The candidates' table covers as many pairs at a time as 512 MB hold: 38 pairs of 120000 pixels (14 MB each), so that 40 are two groups of 20.  A
+    workspace that grew with batch x pixels x segments took 2.7 times as much for 64 pairs."""
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    n, m, batch = 118000, 120000, 40
+    a = torch.nn.functional.normalize(torch.randn((batch, n, 24), generator=gen, device="cuda:0"), dim=2).half()
+    b = torch.nn.functional.normalize(torch.randn((batch, m, 24), generator=gen, device="cuda:0"), dim=2).half()
+    b[:, :n // 2] = a[:, :n // 2]
+    for p in (1, 19, 20, 39):   # in either group, and next to the line between them
+        a[p] = _alike("rank 3", n, gen).half()
+    _, names = same(a, b, "f16")
+    assert names.count("dense_alike_kernel") == 2
+
+    def size(pairs):
+        return fnn.fnn_workspace_bytes(pairs, n, m, 24, 0, "f16") - one_step_bytes(pairs, n, m, 24, "f16")
+
+    per_pair = 36 * 2 * 122880 + 4096 * 24 * 2 * 30        # 8-bit maps and what little else every pair has
+    assert size(64) - size(32) < 32 * per_pair + (64 << 20)
