@@ -859,7 +859,6 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         wa.bstride1 = bs1;
         wa.bstride2 = bs2;
         wa.rows1 = (int32_t)L.maps.n_pad;
-        wa.rows2 = (int32_t)L.maps.m_pad;
         wa.n = (int32_t)n;
         wa.m = (int32_t)m;
         wa.n_words = (int32_t)L.st.n_words;

@@ -304,7 +304,7 @@ struct WalkArgs {
     const char* p1;        // prepared maps of both images
     const char* p2;
     int64_t bstride1, bstride2;  // bytes per pair
-    int32_t rows1, rows2;  // rows per pair (row indices are clamped to them)
+    int32_t rows1;         // rows per pair of image 1 (the seeds are clamped to them)
     int32_t n, m;          // valid pixels
     int32_t n_words;       // ceil(n / 32)
     const int32_t* seeds;  // [batch][n_seeds]
