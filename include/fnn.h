@@ -44,12 +44,16 @@
  *    which fills that cache.
  *  - The maps are read by the enqueued work and never written: keep them alive and unchanged
  *    until the stream has passed the call.  The searches work on a prepared copy of each map in
- *    the workspace (cast to the compute format, rows padded to whole 32-pixel tiles).  Large searches
- *    (from 2048 queries per pair, with FNN_F32 or FNN_FLAG_SPLIT from 256, against maps of at least 16384 pixels) score an
- *    8-bit copy of the maps first and multiply in the compute format only where a bound on what the 8 bits left out says
- *    that the best candidate may be, and so does fnn_mutual_dense on large maps: the same results, from a workspace of the size that fnn_workspace_bytes() returns;
- *    one that has room for the prepared maps and the call's state only is accepted as well and searched in one
- *    step.  Two cases need no separate copy pass, and results do not depend on which way a map took:
+ *    the workspace (cast to the compute format, rows padded to whole 32-pixel tiles).  Where an
+ *    estimate says that it is faster, fnn_nearest (without nq_active) and fnn_reciprocal score an
+ *    8-bit copy of the maps first and multiply in the compute format only where a bound on what
+ *    the 8 bits left out says that the best candidate may be, and so does fnn_mutual_dense: the
+ *    same results.  Considered are maps of at least 16384 pixels and prepared rows of more than
+ *    16 channels (FNN_F32: any), for searches with at least 2048 queries per pair (256 with
+ *    FNN_F32 or rows of more than 32 channels, that is FNN_FLAG_SPLIT with d > 10).  This takes a
+ *    workspace of the size that fnn_workspace_bytes() returns; one that has room for the prepared
+ *    maps and the call's state only is accepted as well and searched in one step.
+ *    Two cases need no separate copy pass, and results do not depend on which way a map took:
  *    (a) the caller's array already is what the copy would be -- stored in the compute format,
  *    d in {16, 24, 32} (16-bit formats) or a multiple of 8 (FNN_F32), row_stride == d, n a
  *    multiple of 32, 16-byte aligned, the batch's maps equally spaced in memory, no flags --
@@ -169,8 +173,10 @@ const char* fnn_status_string(int32_t status);
 
 /*
  * Bytes of device workspace sufficient for any of the three operations on `batch` pairs of
- * maps with n and m pixels, d channels, at most `n_queries` queries or seeds per pair.
- * Returns 0 when the shape is invalid.
+ * maps with n and m pixels, d channels, at most `n_queries` queries or seeds per pair (0: for
+ * fnn_mutual_dense alone).  Most of it are fnn_mutual_dense's tables where the maps are large:
+ * one 512x384 pair in FNN_F16, d = 24, 168 MB, of which 3072 seeds need 19 and fnn_mutual_dense
+ * in one step 24; 16 such pairs 1.14 GB, 64 3.2 GB.  Returns 0 when the shape is invalid.
  */
 size_t fnn_workspace_bytes(int32_t batch, int64_t n, int64_t m, int32_t d, int64_t n_queries, int32_t compute);
 /*
