@@ -302,3 +302,51 @@ def test_maps_without_contrast_are_given_up(kind, batch, step):
         return min(times)
 
     assert least(ws) < 1.45 * least(small)
+
+
+@pytest.mark.parametrize("n,m,nq,compute,stored,d", [
+    (400001, 390007, 6000, "f16", "f32", 24),
+    (300000, 410000, 9001, "bf16", "f16", 28),     # the widest rows: 28 channels and four for the norms
+])
+@pytest.mark.parametrize("op", ["nearest", "reciprocal"])
+def test_squared_distance_of_16_bit_rows_in_two_steps(op, n, m, nq, compute, stored, d):
+    test_same_bits_in_two_steps_as_in_one(op, n, m, nq, compute, stored, d, {"l2": True})
+
+
+@pytest.mark.parametrize("kw", [{}, {"split": True}])
+@pytest.mark.parametrize("stride", [28, 40])
+@pytest.mark.parametrize("op", ["nearest", "every", "reciprocal"])
+def test_rows_apart_in_memory(op, stride, kw):
+    """fp32 rows of 24 channels with others behind them are read where they are, 16 bytes at a time."""
+    n, m, nq = 66003, 70001, 7000
+    batch = enough_pairs(nq, n, m, "f16", 24, **kw)
+    gen = torch.Generator(device="cuda:0").manual_seed(stride)
+    a, b = (torch.randn((batch, rows, stride), generator=gen, device="cuda:0") for rows in (n, m))
+    a, b = a[:, :, :24], b[:, :, :24]
+    assert a.stride(1) == stride
+    q = torch.randint(0, n, (batch, nq), generator=gen, device="cuda:0", dtype=torch.int32)
+    packed = (a.contiguous(), b.contiguous())
+    name, queries = ("nearest", None) if op == "every" else (op, q)
+    got, want = same(name, a, b, queries, "f16", **kw), run(name, *packed, queries, "f16", True, **kw)
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+
+
+@pytest.mark.parametrize("kind,compute,kw", [(k, "f16", {"split": True}) for k in SPECIAL if k != "beyond bounds"] +
+                         [(k, "f32", {"l2": True}) for k in SPECIAL] +
+                         [(k, "bf16", {"l2": True}) for k in ("outlier", "zero rows", "tiny", "lengths", "not finite")])
+def test_wide_rows_that_strain_the_bounds(kind, compute, kw):
+    rng = np.random.default_rng(13)
+    n, m = (65601, 66011) if compute != "bf16" else (262200, 270011)
+    batch = enough_pairs(7500, n, m, compute, 24, **kw)
+    maps = [_special(kind, rng, n, m) for _ in range(min(batch, 2))]
+    maps = [maps[p % len(maps)] for p in range(batch)]
+    a, b = (dev(np.stack([x[i] for x in maps])) for i in (0, 1))
+    q = dev(rng.integers(0, n, size=(batch, 7500)).astype(np.int32))
+    q[:, :8] = 3
+    if kind == "not finite":
+        got = run("reciprocal", a, b, q, compute, True, **kw)
+        assert min(got["seed_i"].min(), got["seed_j"].min()) >= 0 and got["seed_i"].max() < n and got["seed_j"].max() < m
+        return
+    same("nearest", a, b, q, compute, **kw)
+    same("reciprocal", a, b, q, compute, **kw)

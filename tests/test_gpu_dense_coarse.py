@@ -178,3 +178,42 @@ def test_pairs_in_groups_that_share_their_tables():
 
     per_pair = 36 * 2 * 122880 + 4096 * 24 * 2 * 30        # 8-bit maps and what little else every pair has
     assert size(64) - size(32) < 32 * per_pair + (64 << 20)
+
+
+@pytest.mark.parametrize("n,m,compute,stored,d", [(400001, 390000, "f16", "f32", 24), (300000, 410000, "bf16", "f16", 28)])
+def test_squared_distance_of_16_bit_rows_in_two_steps(n, m, compute, stored, d):
+    test_same_bits_in_two_steps_as_in_one(n, m, 1, compute, stored, d, {"l2": True})
+
+
+@pytest.mark.parametrize("kw", [{}, {"split": True}])
+def test_rows_apart_in_memory(kw):
+    gen = torch.Generator(device="cuda:0").manual_seed(9)
+    a, b = (torch.randn((2, rows, 28), generator=gen, device="cuda:0")[:, :, :24] for rows in (131100, 90001))
+    got, _ = same(a, b, "f16", **kw)
+    want, _ = run(a.contiguous(), b.contiguous(), "f16", True, **kw)
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+
+
+@pytest.mark.parametrize("kind,compute,kw", [(k, "f16", {"split": True}) for k in SPECIAL if k not in ("beyond bounds", "not finite")] +
+                         [(k, "f32", {"l2": True}) for k in SPECIAL if k != "not finite"])
+def test_wide_rows_that_strain_the_bounds(kind, compute, kw):
+    rng = np.random.default_rng(14)
+    n, m = (66001, 66100) if compute == "f16" else (200001, 210000)
+    a, b = _special(kind, rng, n, m)
+    same(dev(a)[None], dev(b)[None], compute, **kw)
+
+
+@pytest.mark.parametrize("compute,kw", [("f16", {}), ("bf16", {}), ("f32", {}), ("f16", {"split": True})])
+def test_indices_stay_inside_maps_that_are_not_finite(compute, kw):
+    """Results are unspecified there, but every index lies in its map (or is -1) and every pair is a pair of pixels."""
+    rng = np.random.default_rng(15)
+    n, m = 131100, 133000
+    a, b = _special("not finite", rng, n, m)
+    got, _ = run(dev(a)[None], dev(b)[None], compute, True, **kw)
+    for k, most in (("nn12", m), ("nn21", n)):
+        assert got[k].min() >= -1 and got[k].max() < most
+    count = int(got["n_pairs"][0])
+    assert 0 <= count <= min(n, m)
+    pairs = got["pairs"][0, :count]
+    assert count == 0 or (pairs.min() >= 0 and pairs[:, 0].max() < n and pairs[:, 1].max() < m)

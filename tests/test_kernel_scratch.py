@@ -41,3 +41,14 @@ def test_no_scratch_memory_at_24_channels_in_16_bits(kernel, tmp_path):
               if re.match(rf"_ZN3fnn\d+{kernel}ILi[12]E" + ("Li24E" if kernel == "search_kernel" else ""), k)}
     assert len(half24) >= 2
     assert not {k: v for k, v in half24.items() if v}
+
+
+def test_no_scratch_memory_in_the_8_bit_passes(tmp_path):
+    scratch = scratch_bytes(tmp_path)
+    for kernel, count in (("coarse_kernel", 5), ("dense_coarse_kernel", 2), ("dense_select_kernel", 1), ("dense_sample_kernel", 1), ("dense_judge_kernel", 1)):
+        found = {k: v for k, v in scratch.items() if re.match(rf"_ZN3fnn\d+{kernel}[IE]", k)}
+        assert len(found) == count, (kernel, sorted(found))
+        assert not {k: v for k, v in found.items() if v}
+    for kernel in ("refine_kernel", "quantise_kernel"):   # 16-bit rows of 24 channels
+        found = {k: v for k, v in scratch.items() if re.match(rf"_ZN3fnn\d+{kernel}ILi[12]ELi24E", k)}
+        assert len(found) >= 4 and not {k: v for k, v in found.items() if v}
