@@ -257,8 +257,9 @@ def main() -> int:
             "launches_per_step": launches_per_step, "avg_launch_ms": round(avg_search_ms, 5),
             "flops_per_launch": flops_per_launch,
             "note": "algorithmic flops = 2*24*M*(active queries), averaged over all search launches of a step "
-                    "(launches after every seed has converged do no work but count); the two launches of a search in "
-                    "two steps count as one, and their 8-bit products are not counted as flops",
+                    "(launches after every seed has converged do no work but count); the launches of a search in two steps count as "
+                    "one.  Every score counts, whichever step formed it: in two steps most are one 8-bit instruction per block, so "
+                    "the fraction compares with a 16-bit pass over everything and is not the share of time that the matrix cores are busy",
         },
         "roofline_hbm": {
             "kernel": "search_kernel", "bound": "hbm", "achieved": round(achieved_gbs, 1), "peak": PEAK_HBM,
@@ -551,8 +552,8 @@ def main() -> int:
                          "unit": "TFLOP/s", "frac": round(dtf / PEAK_MFMA_16BIT, 4),
                          "traffic": traffic.get("dense_kernel_bytes_per_launch"),
                          "avg_launch_ms": round(dense_ms, 4), "flops_per_launch": dflops,
-                         "note": "algorithmic flops 2*24*N*M; pass 1 is 8-bit scores and the fp16 products that they leave over, all of "
-                                 "its launches together"},
+                         "note": "algorithmic flops 2*24*N*M, whichever step forms a score; pass 1 is 8-bit scores and the fp16 products that "
+                                 "they leave over, all of its launches together, so the fraction is not that of the 16-bit instructions issued"},
         }
 
     # ---- the large pair (configs[4]): 1024x768, dense mutual NN in bf16, then FastNN reciprocal ------

@@ -7,7 +7,8 @@
 // lower bound of its best score.  Step 2 (refine_kernel) multiplies each cell again, in the format the call asked
 // for and with the same instructions as search_kernel, but only for the queries whose upper bound there reaches
 // their lower bound; every other cell holds no candidate that could win or tie.  Of the 192 segments of a 512x384 map
-// a query needs 4 on average (unit rows, no structure; 2 where neighbouring pixels resemble each other).
+// a query needs 1 on average where it has a clear partner, 4 of maps that have nothing in common, and the more the less the descriptors
+// tell apart: 7 to 25 with features of 32 to 128 pixels, 50 with descriptors of rank 6 in 24 channels, 140 with rank 4 (24 channels, unit rows).
 //
 // The bounds.  With a row a = s q + r, q its 8-bit row, s its segment's scale, r the remainder, a product is
 //     a.b = s_a s_b (q_a.q_b) + (s_a q_a).r_b + r_a.b,     |second| + |third| <= |a| |r_b| + |r_a| (|b| + |r_b|),
@@ -651,7 +652,8 @@ hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream
 
 // The model behind the choice, in nanoseconds, fitted to calls between 16384 and a million pixels; both ways of 45 drawn calls
 // near the line, inputs not in the caches: those it takes gain 4 to 49 %, those it leaves would have gained 8 % at most (one
-// 512x384 pair of fp16 products, 263 us in one step, 274 in two).
+// 512x384 pair of fp16 products, 263 us in one step, 274 in two).  The model knows sizes only: it counts on half of the seeds in the second iteration, and
+// on maps that tell pixels apart (four 512x384 pairs of fp16 products, features of 1 pixel, whose seeds settle at once, 375 / 390; of 16 pixels 612 / 595).
 constexpr double BYTES_PER_NS = 4500.0;  // what the passes over the maps reach
 static int coarse_row_bytes(int compute, int dp) { return dp * elem_size(compute); }
 // Cells that a slot is multiplied with again: 4 of 1024 pixels for unit rows of 16 channels and more, however large the map; with few

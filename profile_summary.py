@@ -148,7 +148,8 @@ def hbm_traffic() -> None:
         # the traced steps, 2 * max_iter searches each, of which the first four are a coarse_kernel and a refine_kernel launch.
         per_step = int(round(bench["roofline"]["launches_per_step"]))
         n_steps = 1 + bench["warmup"] + 2 * bench["steps"]
-        counts = {"coarse_kernel": 4 * n_steps, "refine_kernel<1, 24, 8, 4, false>": 4 * n_steps, "search_kernel": (per_step - 4) * n_steps}
+        counts = {k: 2 * n_steps for k in sorted(per["fetch"]) if k.startswith("coarse_kernel")}  # a voting and a plain variant
+        counts.update({"refine_kernel<1, 24, 8, 4, false>": 4 * n_steps, "search_kernel": (per_step - 4) * n_steps})
         total = sum(sum(mib(run, k, c)) for run in ("fetch", "write") for k, c in counts.items())
         result["search_kernel_bytes_per_launch"] = round(total / (n_steps * per_step) * 1048576)
         alg = bench["roofline_hbm"]["bytes_per_launch"]
@@ -163,7 +164,7 @@ def hbm_traffic() -> None:
                   f"{alg/1e6:.1f} MB.  16 prepared maps are 144 MiB, their 8-bit copies 96 MiB.", ""]
     calls = len(per["fetch"].get(next((k for k in per["fetch"] if k.startswith("dense_coarse_kernel")), ""), []))
     if calls:
-        parts = ("dense_coarse_kernel", "dense_select_kernel", "refine_kernel<1, 24, 8, 4, true>")
+        parts = ("dense_sample_kernel", "dense_coarse_kernel", "dense_select_kernel", "refine_kernel<1, 24, 8, 4, true>")
         sums = {k: (sum(mib("fetch", k)) / calls, sum(mib("write", k)) / calls) for k in parts}
         result["dense_kernel_bytes_per_launch"] = round(sum(r + w for r, w in sums.values()) * 1048576)
         lines += ["## pass 1 of the dense mode (cfg 3), MiB read / written per call", "",
