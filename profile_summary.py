@@ -196,7 +196,8 @@ def mfma_utilisation() -> None:
     denses = [(k, v) for k, v in disp.items() if is_dense_pass1(k[1])]
     if not searches or not denses:
         return
-    sk, dk = searches[min(2, len(searches) - 1)], denses[-1]
+    # (the last of those that multiply: a launch of the one-step kernel may follow that leaves every pair alone)
+    sk, dk = searches[min(2, len(searches) - 1)], [x for x in denses if x[1].get("SQ_INSTS_MFMA", 0) > 0][-1]
 
     def col(kv, products):
         k, v = kv
