@@ -105,14 +105,14 @@ CoarseMap carve_coarse_map(Carver& cv, int batch, int64_t pixels, int segment = 
     return M;
 }
 // both_searched: image 1 is a map of candidates too
-CoarseLayout carve_coarse(Carver& cv, int batch, int64_t rows1, int64_t rows2, bool both_searched, int64_t nq, int searches) {
+CoarseLayout carve_coarse(Carver& cv, int batch, int64_t rows1, int64_t rows2, bool both_searched, int64_t nq, int searches, int compute) {
     CoarseLayout L;
     L.map[0] = carve_coarse_map(cv, batch, rows1);
     L.map[1] = carve_coarse_map(cv, batch, rows2);
     const int64_t segs = both_searched && L.map[0].n_segs > L.map[1].n_segs ? L.map[0].n_segs : L.map[1].n_segs;
     int64_t cells = 0;
     for (int i = both_searched ? 0 : 1; i < 2; ++i) {
-        const int64_t of_map = (int64_t)L.map[i].n_segs * coarse_cells(nq, L.map[i].n_segs, batch);
+        const int64_t of_map = (int64_t)L.map[i].n_segs * coarse_cells(nq, L.map[i].n_segs, batch, compute);
         if (of_map > cells) cells = of_map;
     }
     L.slot_pitch = round_up(nq, 64);
@@ -557,7 +557,7 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
         for (int listed = 0; listed < 2; ++listed) {
             if (!nearest_coarse_searches(batch, n, m, n_queries, listed != 0, compute, dp, d, l2)) continue;
             Carver with = cv;
-            carve_coarse(with, batch, listed ? n_queries : n, m, false, n_queries, 1);
+            carve_coarse(with, batch, listed ? n_queries : n, m, false, n_queries, 1, compute);
             if (with.used > most) most = with.used;
         }
     }
@@ -565,7 +565,7 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
         Carver cv{nullptr, 0};
         carve_recip(cv, batch, n, m, de, n_queries, compute);
         if (recip_coarse_searches(batch, n, m, n_queries, compute, dp, d, l2))
-            carve_coarse(cv, batch, n, m, true, n_queries, RECIP_COARSE_SEARCHES);
+            carve_coarse(cv, batch, n, m, true, n_queries, RECIP_COARSE_SEARCHES, compute);
         if (cv.used > most) most = cv.used;
     }
     {
@@ -628,7 +628,7 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
     const bool staged = fused || (staged_shape && L.maps.dp == 24 && opts->compute != FNN_F32);
     // ... or, where that is faster and the workspace has the room, in two steps, the first in 8 bits
     const bool listed = list_queries(q_idx, nq, n);
-    CoarseLayout C = carve_coarse(cv, batch, listed ? nq : n, m, false, nq, 1);
+    CoarseLayout C = carve_coarse(cv, batch, listed ? nq : n, m, false, nq, 1, opts->compute);
     const bool coarse = !nq_active && cv.used <= workspace_bytes &&
                         nearest_coarse_searches(batch, n, m, nq, listed, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0);
     const bool raw = coarse && raw_options(opts) && raw_rows(batch, src) && raw_rows(batch, tgt);
@@ -828,7 +828,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     const bool staged = fused || (L.maps.dp == 24 && opts->compute != FNN_F32 && first_search_applies(n_seeds, n, batch) &&
                                   first_search_applies(n_seeds, m, batch));
     // ... and large ones run in two steps, the first in 8 bits, where the workspace has the room
-    CoarseLayout C = carve_coarse(cv, batch, n, m, true, n_seeds, RECIP_COARSE_SEARCHES);
+    CoarseLayout C = carve_coarse(cv, batch, n, m, true, n_seeds, RECIP_COARSE_SEARCHES, compute);
     const int coarse_searches = walk || cv.used > workspace_bytes ? 0 : recip_coarse_searches(batch, n, m, n_seeds, compute, L.maps.dp, d,
                                                                                               (opts->flags & FNN_FLAG_L2) != 0);
     const bool coarse = coarse_searches > 0;

@@ -2,7 +2,7 @@
 //
 // Step 1 (coarse_kernel) scores every query against every candidate in 8-bit integers: one K=32 instruction per
 // 32x32 block, at the rate of a K=16 fp16 one, and eight 3-input maxima, with nothing tracked per
-// tile (25-26 ns per block and SIMD in a bare loop; search_kernel's arithmetic for 24 channels 42-47 ns).  It keeps one
+// tile (22.6 ns per block and SIMD in a bare loop; search_kernel's arithmetic for 24 channels 42-47 ns).  It keeps one
 // number per query and CELL of 512 or 1024 candidates, an upper bound of the cell's scores, and one per query, a
 // lower bound of its best score.  Step 2 (refine_kernel) multiplies each cell again, in the format the call asked
 // for and with the same instructions as search_kernel, but only for the queries whose upper bound there reaches
@@ -256,9 +256,22 @@ __device__ __forceinline__ bool gives_up(const SearchVote& v, float even) { retu
 constexpr int VOTE_CELLS = 4;  // shortest chunk that is worth it
 constexpr int VOTERS = 64;     // of a pair, about; a quarter of them may decide
 
+// fn(std::integral_constant<int, n>) for the n in 0..MOST that is `count` (uniform).
+template <int MOST, typename F>
+__device__ __forceinline__ bool with_count(int count, const F& fn) {
+    if constexpr (MOST > 0) {
+        if (count < MOST) return with_count<MOST - 1>(count, fn);
+    }
+    return fn(std::integral_constant<int, MOST>{});
+}
+
 // The four waves of a workgroup hold PAIRS pairs of query blocks each and sweep the same tiles, which reach LDS by direct loads
 // (a tile is 1 KB: one 16-byte load per lane), the next turn's while this turn's are multiplied.
-// Bound by the vector maxima and the matrix instructions, which take about the same time each.
+// Bound by the vector maxima and the matrix instructions, which take about the same time each, at the clock that the power limit leaves.
+// A product is followed by the maxima of the one before it: two products and then their sixteen maxima leave either unit
+// waiting for the other (a bare loop of such pairs 25.7 ns per block and SIMD, of this order 22.6, with operands of zeros, at the full clock, 22.5 and
+// 17.8; every pixel of one 512x384 pair 1130 -> 1035 us, 16 pairs of 3072 queries 372 -> 347).  Tests for the blocks that hold a query would
+// keep the compiler from that order, so a wave takes the loop made for its number of them.
 template <int PAIRS, int CELL_TILES, bool VOTE>
 __global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void coarse_kernel(SearchArgs a, CoarseArgs ca) {
@@ -326,13 +339,11 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
         int best[PAIRS][2];
         float low[PAIRS];        // lane l of pair p: the slot slot0 + 64 p + l
         uint32_t bound[PAIRS];
-        bool live[PAIRS];
         {
             int32_t row[2 * PAIRS];
             query_rows<2 * PAIRS>(a, qbase, slot0, n_act, c, row);
 #pragma unroll
             for (int p = 0; p < PAIRS; ++p) {
-                live[p] = slot0 + p * 64 < slot_end;  // uniform in the wave
                 const int32_t even = row[2 * p], odd = row[2 * p + 1];
                 q[p][0] = *reinterpret_cast<const i32x4*>(src + (int64_t)even * COARSE_ROW_BYTES + 16 * h);
                 q[p][1] = *reinterpret_cast<const i32x4*>(src + (int64_t)odd * COARSE_ROW_BYTES + 16 * h);
@@ -348,39 +359,48 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
             low[p] = -__builtin_inff();
         }
 
-        auto turn = [&](int k, auto slot_tag) {
-            constexpr int SLOT = decltype(slot_tag)::value;
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the turn is in LDS
-            __syncthreads();                     // everyone's is, and everyone has left the other slot
-            stage_turn(SLOT ? stage0 : stage1, k + 1);
+        // The cells of the chunk, for a wave whose first LIVE pairs hold a query; true if the pair of images is given up.
+        auto sweep = [&](auto live_tag) -> bool {
+            constexpr int LIVE = decltype(live_tag)::value, BLOCKS = 2 * LIVE;
+            auto turn = [&](int k, auto slot_tag) {
+                constexpr int SLOT = decltype(slot_tag)::value;
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the turn is in LDS
+                __syncthreads();                     // everyone's is, and everyone has left the other slot
+                stage_turn(SLOT ? stage0 : stage1, k + 1);
+                if constexpr (LIVE > 0) {
+                    auto tile = [&](int j) { return __builtin_bit_cast(i32x4, SLOT ? stage1[j][lane] : stage0[j][lane]); };
+                    i32x4 cur = tile(0);
+                    i32x16 score[2];
+                    score[0] = product8(cur, q[0][0]);
 #pragma unroll
-            for (int j = 0; j < COARSE_TURN; ++j) {
-                const i32x4 cur = __builtin_bit_cast(i32x4, SLOT ? stage1[j][lane] : stage0[j][lane]);
+                    for (int j = 0; j < COARSE_TURN; ++j) {
+                        const i32x4 next = tile(j + 1 < COARSE_TURN ? j + 1 : j);
 #pragma unroll
-                for (int p = 0; p < PAIRS; ++p) {
-                    if (__builtin_expect(live[p], 1)) {
-                        const i32x16 even = product8(cur, q[p][0]), odd = product8(cur, q[p][1]);
-                        best[p][0] = fold16i(best[p][0], even);
-                        best[p][1] = fold16i(best[p][1], odd);
+                        for (int i = 0; i < BLOCKS; ++i) {
+                            const int then = i + 1 < BLOCKS ? i + 1 : 0;
+                            if (i + 1 < BLOCKS || j + 1 < COARSE_TURN) score[(i + 1) & 1] = product8(then ? cur : next, q[then / 2][then & 1]);
+                            __builtin_amdgcn_sched_barrier(0);  // a product, then the maxima of the one before it
+                            best[i / 2][i & 1] = fold16i(best[i / 2][i & 1], score[i & 1]);
+                            asm volatile("" : "+v"(best[i / 2][i & 1]));  // ... which the optimiser would otherwise move to the end of the cell
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        cur = next;
                     }
                 }
-            }
-        };
-        bool given_up = false;
-        for (int cell = cell0; cell < cell1; ++cell) {
-            const int k = (cell - cell0) * TURNS;
+            };
+            for (int cell = cell0; cell < cell1; ++cell) {
+                const int k = (cell - cell0) * TURNS;
 #pragma unroll 1
-            for (int tt = 0; tt < TURNS; tt += 2) {
-                turn(k + tt, std::integral_constant<int, 0>{});
-                turn(k + tt + 1, std::integral_constant<int, 1>{});
-            }
-            // lanes 0..31 finish the first block of a pair, lanes 32..63 the second
-            const SegInfo si = info[cell / CELLS];
-            uint16_t* upper = ca.upper + ((int64_t)b * n_cells + cell) * ca.slab + slot0 + lane;
-            float first_up = 0.0f;
+                for (int tt = 0; tt < TURNS; tt += 2) {
+                    turn(k + tt, std::integral_constant<int, 0>{});
+                    turn(k + tt + 1, std::integral_constant<int, 1>{});
+                }
+                // lanes 0..31 finish the first block of a pair, lanes 32..63 the second
+                const SegInfo si = info[cell / CELLS];
+                uint16_t* upper = ca.upper + ((int64_t)b * n_cells + cell) * ca.slab + slot0 + lane;
+                float first_up = 0.0f;
 #pragma unroll
-            for (int p = 0; p < PAIRS; ++p) {
-                if (live[p]) {
+                for (int p = 0; p < LIVE; ++p) {
                     const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)best[p][0], (uint32_t)best[p][1], false, false);
                     const float score = (float)max((int)sw[0], (int)sw[1]) * si.scale;
                     const float error = __builtin_fmaf(__uint_as_float(bound[p] & 0xFFFF0000u), si.residual,
@@ -392,37 +412,40 @@ void coarse_kernel(SearchArgs a, CoarseArgs ca) {
                     if (slot0 + p * 64 + lane < slot_end) upper[p * 64] = (uint16_t)(__float_as_uint(up) >> 16);
                     best[p][0] = best[p][1] = -0x7FFFFFFF;
                 }
-            }
-            const int done = cell - cell0;
-            if (VOTE && done < VOTE_CELLS && cell0 + VOTE_CELLS <= cell1) {  // uniform in the workgroup
-                const bool here = slot0 + lane < slot_end;
-                uint32_t* lower = &ca.lower[(int64_t)b * ca.slot_pitch + ca.first_slot + slot0 + lane];
-                // a wave each of a few workgroups votes (see the end of refine_kernel)
-                const int apart = (units + VOTERS - 1) / VOTERS;
-                if (done == 0) {
-                    if (here) atomicMax(lower, order_bits(low[0]));
-                } else if (done == 1) {
-                    if (chunk % apart == 0 && (chunk / apart & (COARSE_WAVES - 1)) == wave) {
-                        const uint32_t known = here ? atomicMax(lower, order_bits(low[0])) : 0;
-                        const uint32_t doubt = __popcll(__ballot(here && first_up >= __builtin_fmaxf(low[0], unorder_bits(known))));
-                        if (lane == 0 && here) {
-                            u64 tally = 1ull << 48 | (u64)min(64, slot_end - slot0) << 24 | doubt;
-                            tally += atomicAdd(&ca.vote[b].tally, tally);
-                            // a query is in doubt about one more of s cells with the odds even : s - 1, where `even` cells of all leave it in doubt
-                            const float even = ca.even * n_cells, others = 2.0f * chunks - 1.0f;
-                            const float all = (float)((uint32_t)(tally >> 24) & 0xFFFFFFu), doubtful = (float)((uint32_t)tally & 0xFFFFFFu);
-                            if (tally >> 48 >= VOTERS / 4 && doubtful * (even + others) > all * even)
-                                __hip_atomic_store(&ca.vote[b].given_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int done = cell - cell0;
+                if (VOTE && done < VOTE_CELLS && cell0 + VOTE_CELLS <= cell1) {  // uniform in the workgroup
+                    const bool here = slot0 + lane < slot_end;
+                    uint32_t* lower = &ca.lower[(int64_t)b * ca.slot_pitch + ca.first_slot + slot0 + lane];
+                    // a wave each of a few workgroups votes (see the end of refine_kernel)
+                    const int apart = (units + VOTERS - 1) / VOTERS;
+                    if (done == 0) {
+                        if (here) atomicMax(lower, order_bits(low[0]));
+                    } else if (done == 1) {
+                        if (chunk % apart == 0 && (chunk / apart & (COARSE_WAVES - 1)) == wave) {
+                            const uint32_t known = here ? atomicMax(lower, order_bits(low[0])) : 0;
+                            const uint32_t doubt = __popcll(__ballot(here && first_up >= __builtin_fmaxf(low[0], unorder_bits(known))));
+                            if (lane == 0 && here) {
+                                u64 tally = 1ull << 48 | (u64)min(64, slot_end - slot0) << 24 | doubt;
+                                tally += atomicAdd(&ca.vote[b].tally, tally);
+                                // a query is in doubt about one more of s cells with the odds even : s - 1, where `even` cells of all leave it in doubt
+                                const float even = ca.even * n_cells, others = 2.0f * chunks - 1.0f;
+                                const float all = (float)((uint32_t)(tally >> 24) & 0xFFFFFFu), doubtful = (float)((uint32_t)tally & 0xFFFFFFu);
+                                if (tally >> 48 >= VOTERS / 4 && doubtful * (even + others) > all * even)
+                                    __hip_atomic_store(&ca.vote[b].given_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            }
                         }
+                    } else {
+                        if (threadIdx.x == 0) leave = __hip_atomic_load(&ca.vote[b].given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __syncthreads();  // (the next write lies behind the barriers of the next turns)
+                        if (leave) return true;
                     }
-                } else {
-                    if (threadIdx.x == 0) leave = __hip_atomic_load(&ca.vote[b].given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __syncthreads();  // (the next write lies behind the barriers of the next turns)
-                    given_up = leave;
-                    if (given_up) break;
                 }
             }
-        }
+            return false;
+        };
+        // uniform in the wave; the waves of a workgroup meet at the same number of barriers whatever their LIVE
+        const int n_live = max(0, min(PAIRS, (slot_end - slot0 + 63) / 64));
+        const bool given_up = with_count<PAIRS>(n_live, sweep);
 #pragma unroll
         for (int p = 0; p < PAIRS; ++p) {
             const int slot = slot0 + p * 64 + lane;
@@ -670,7 +693,7 @@ double coarse_gain(int64_t nq, int64_t m, int batch, int compute, int dp, int d,
     if (m < 16 * SEG_PIXELS || nq > 0x7FFFFFFF / 2 || (cheap && dp <= 16)) return -1e30;
     if (batch * m > (int64_t)1 << 26) return -1e30;  // the tables of bounds would pass 1 GB
     // what a block of 32x32 scores takes one SIMD in search_kernel, and in coarse_kernel
-    const double exact = compute == FNN_F32 ? 18.75 * dp : (cheap ? 46.0 : 1.64 * dp), coarse = 28.0;
+    const double exact = compute == FNN_F32 ? 18.75 * dp : (cheap ? 46.0 : 1.64 * dp), coarse = 26.0;
     const double blocks = (double)batch * ((nq + 31) / 32) * ((m + 31) / 32) / 1024.0;
     // (the second step runs at two thirds of search_kernel's rate)
     const double segments = (double)m / SEG_PIXELS, again = 1.5 * coarse_cells_again(segments, d, l2) / segments;
@@ -683,12 +706,36 @@ double coarse_cost(int64_t rows, int compute, int dp) {
     return 4000.0 + (double)rows * (coarse_row_bytes(compute, dp) + COARSE_ROW_BYTES + 4) / BYTES_PER_NS;
 }
 
-// Half segments balance a small search better (its workgroups get two or three cells each) and spread step 2 over more
-// workgroups; a large one saves the second half's epilogue and start-up.  The line is drawn in pairs of query blocks times segments.  Whole / half
-// segments, all of a call's time in us: 512x384, 3072 queries, 4 pairs (36864) 135 / 130, 6 178 / 172, 7 (64512) 207 / 211, 8 (73728) 225 / 238, 10 282 / 289,
-// 12 342 / 344, 16 437 / 458, seeds that walk, 6 pairs 510 / 507, 8 593 / 629; 640x480, 4800 queries, 3 pairs (67500) 193 / 186, 4 243 / 245, walking 538 / 547 and
-// 665 / 687; one 768x576 pair, 6912 queries (46656) 141 / 125; one 896x672 pair, 9408 (86436) 206 / 209, walking 566 / 596.
-int coarse_cells(int64_t nq, int64_t n_segs, int batch) { return (double)((nq + 63) / 64) * n_segs * batch < 73728.0 ? 2 : 1; }
+// What coarse_kernel's split of a search leaves to the busiest wave, times the waves that share a SIMD with it: the time of a
+// launch whose workgroups are all resident, in products of one pair of query blocks and one cell.
+static int coarse_wgs_per_pair(int resident, int batch) {
+    int wgs = resident / batch;
+    if (wgs >= 8) wgs &= ~7;  // a multiple of 8 per pair keeps the XCD renumbering a bijection
+    return wgs < 1 ? 1 : wgs;
+}
+static int64_t coarse_longest(int wide, int resident, int batch, int64_t pairs, int64_t n_cells) {
+    const int64_t wgs = coarse_wgs_per_pair(resident, batch), quads = (pairs + wide * COARSE_WAVES - 1) / (wide * COARSE_WAVES);
+    int64_t chunks = wgs / quads < n_cells ? wgs / quads : n_cells;
+    if (chunks < 1) chunks = 1;
+    const int64_t rounds = (quads * chunks + wgs - 1) / wgs;
+    const int64_t per_wave = (pairs + quads * COARSE_WAVES - 1) / (quads * COARSE_WAVES), cells = (n_cells + chunks - 1) / chunks;
+    return resident * rounds * per_wave * cells;
+}
+
+// Half segments split a small search more evenly and spread step 2 over more workgroups; whole ones read a tile a third as often and keep the pipeline
+// of products and maxima filled for longer, some 8 % of step 1.  So the split that leaves less to the busiest wave is taken, with the workgroups that 256
+// compute units hold of either kernel (a workspace is sized without a device).  Where step 2 would have few workgroups, or dear ones, half
+// segments win anyway.  Whole / half segments, all of a call's time in us: 512x384, 3072 queries, 1 pair 47.3 / 42.6, 2 60.0 / 62.0, 3 87.3 / 83.7, 4 98.9 / 104.5, 6 144 / 152,
+// 8 190 / 204, 12 282 / 307, 16 369 / 401, seeds that walk, 4 pairs 464 / 474, 6 641 / 639, 8 767 / 801; three 640x480 pairs 162 / 169; one 768x576 pair
+// 113 / 113, walking 513 / 496, 896x672 186 / 193 and 749 / 757, 1024x768 275 / 300; every pixel of 256x192 121 / 112, of 320x240 214 / 227; fp32 products, 512x384, walking, 768 seeds
+// of 2 pairs 282 / 268, of 4 379 / 374, 3072 of one 359 / 315, of 4 659 / 649; two-term rows of 4 pairs 683 / 703, of one 327 / 298.
+int coarse_cells(int64_t nq, int64_t n_segs, int batch, int compute) {
+    if (n_segs < 1 || nq < 1) return 1;
+    const int64_t pairs = (nq + 63) / 64;
+    const int64_t eight = coarse_longest(8, 512, batch, pairs, n_segs), six = coarse_longest(6, 768, batch, pairs, n_segs);
+    const double half = 0.5 * coarse_longest(2, 1280, batch, pairs, 2 * n_segs);
+    return n_segs * batch < 128 || (compute == FNN_F32 && n_segs * batch <= 1024) || 1.08 * half < (eight < six ? eight : six) ? 2 : 1;
+}
 
 int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch) {
     const int64_t most = ((int64_t)128 << 20) / ((n_segs > 0 ? n_segs : 1) * batch) / 1024 * 1024;  // 256 MB of bounds (whole segments)
@@ -697,7 +744,7 @@ int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch) {
     return all < most ? all : most;
 }
 
-// Workgroups that the current device holds at once (0: unknown), and those of a launch for each pair.
+// Workgroups that the current device holds at once (0: unknown).
 template <int PAIRS, int CELL>
 static int coarse_resident() {  // (voting costs registers, not resident workgroups)
     static DeviceCache resident_wgs;
@@ -710,21 +757,6 @@ static int coarse_resident() {  // (voting costs registers, not resident workgro
         return (long long)(per_cu > 0 ? per_cu : 1) * prop.multiProcessorCount;
     });
     return resident > 0 ? (int)resident : 0;
-}
-static int coarse_wgs_per_pair(int resident, int batch) {
-    int wgs = resident / batch;
-    if (wgs >= 8) wgs &= ~7;  // a multiple of 8 per pair keeps the XCD renumbering a bijection
-    return wgs < 1 ? 1 : wgs;
-}
-// What coarse_kernel's split of a search leaves to the busiest wave, times the waves that share a SIMD with it: the time of a
-// launch whose workgroups are all resident, in products of one pair of query blocks and one cell.
-static int64_t coarse_longest(int wide, int resident, int batch, int pairs, int n_cells) {
-    const int wgs = coarse_wgs_per_pair(resident, batch), quads = (pairs + wide * COARSE_WAVES - 1) / (wide * COARSE_WAVES);
-    int chunks = wgs / quads < n_cells ? wgs / quads : n_cells;
-    if (chunks < 1) chunks = 1;
-    const int64_t rounds = ((int64_t)quads * chunks + wgs - 1) / wgs;
-    const int per_wave = (pairs + quads * COARSE_WAVES - 1) / (quads * COARSE_WAVES), cells = (n_cells + chunks - 1) / chunks;
-    return (int64_t)resident * rounds * per_wave * cells;
 }
 template <int PAIRS, int CELL>
 static hipError_t launch_coarse_t(const SearchArgs& a, const CoarseArgs& ca, int batch, hipStream_t s) {
@@ -753,13 +785,13 @@ static hipError_t launch_refine_t(const SearchArgs& a, CoarseArgs ca, int batch,
 }
 template <int CT, int DP>
 static hipError_t launch_both_t(const SearchArgs& a, CoarseArgs ca, int batch, hipStream_t s) {
-    const bool half = coarse_cells(a.nq, ca.tgt.n_segs, batch) == 2;
+    const bool half = coarse_cells(a.nq, ca.tgt.n_segs, batch, CT) == 2;
     ca.n_cells = ca.tgt.n_segs * (half ? 2 : 1);
     ca.cell_shift = 0;
-    // Waves of up to 16 query blocks read a tile the fewest times; with up to 12 a fourth wave fits on every SIMD.  Whichever leaves less to the
-    // busiest wave is the faster, and where both leave the same to the same quads, the fourth wave is (16 / 12 blocks, fp16, 24 channels, the
-    // whole call: 16 512x384 pairs of 2300 queries 380 / 373 us, 3072 427 / 426, 3500 467 / 495, 4608 563 / 582, 7000 768 / 804; 12 pairs of 3072
-    // 322 / 335; 30 320x240 pairs of 3072 348 / 338, 4608 452 / 459; six 640x480 pairs of 4800 358 / 349; every pixel of one 512x384 pair 1102 / 1108).
+    // Waves of up to 16 query blocks read a tile the fewest times; with up to 12 a third wave fits on every SIMD.  Whichever leaves less to the
+    // busiest wave is the faster, and where both leave the same to the same quads, the third wave is (16 / 12 blocks, fp16, 24 channels, the
+    // whole call: 16 512x384 pairs of 2300 queries 316 / 315 us, 3072 369 / 368, 3500 411 / 418, 4608 522 / 502, 7000 706 / 745; 12 pairs of 3072
+    // 290 / 285; 30 320x240 pairs of 3072 312 / 316, 4608 426 / 425; six 640x480 pairs of 4800 329 / 317; every pixel of one 512x384 pair 1135 / 1085).
     bool six = false;
     if (!half) {
         const int wide = coarse_resident<8, SEG_TILES>(), narrow = coarse_resident<6, SEG_TILES>();

@@ -241,7 +241,7 @@ inline int64_t coarse_least_queries(int compute, int dp) { return compute == FNN
 inline int coarse_min_live(int compute, int dp) { return compute == FNN_F32 || dp > 32 ? 64 : 512; }
 // Slots per launch that keep the table of upper bounds small
 int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch);
-int coarse_cells(int64_t nq, int64_t n_segs, int batch);  // cells of a segment
+int coarse_cells(int64_t nq, int64_t n_segs, int batch, int compute);  // cells of a segment
 
 // Pass 2: out_keys become (best score, lowest candidate index); optionally also stored to
 // out_idx / out_score (either may be NULL).  Queries without any candidate get -1 / -inf.
