@@ -179,9 +179,10 @@ def main() -> int:
         c = searches_from_iters(seed_iter[b], n_seeds, MAX_ITER)
         per_search[:len(c)] += np.asarray(c)
     esize = 4 if compute == "f32" else 2
-    rows_per_step = int(per_search.sum())
+    lps = int(round(launches_per_step))  # the late iterations are one launch of a kernel of their own
+    rows_per_step = int(per_search[:lps].sum())
     flops_per_step = 2.0 * D * N_PIX * rows_per_step                       # D = 24, no padding counted
-    live_launches = int((per_search > 0).sum())
+    live_launches = int((per_search[:lps] > 0).sum())
     # bytes: each live search streams every pair's candidate map once, gathers its queries
     # and writes an 8-byte (index, score) result per query
     bytes_per_step = live_launches * BATCH * N_PIX * D * esize + rows_per_step * (D * esize + 8)
@@ -204,7 +205,6 @@ def main() -> int:
     # per-search view: launch i of every step has the same live query count, so average the
     # i-th search launch over the steps and set it against the roofline that bounds it
     per_search_rows = []
-    lps = int(round(launches_per_step))
     for i in range(lps):
         k_act = int(per_search[i]) if i < len(per_search) else 0
         if k_act == 0:
@@ -257,7 +257,7 @@ def main() -> int:
             "launches_per_step": launches_per_step, "avg_launch_ms": round(avg_search_ms, 5),
             "flops_per_launch": flops_per_launch,
             "note": "algorithmic flops = 2*24*M*(active queries), averaged over all search launches of a step "
-                    "(launches after every seed has converged do no work but count); the launches of a search in two steps count as "
+                    "(the searches of the late iterations are part of another launch and do not count); the launches of a search in two steps count as "
                     "one.  Every score counts, whichever step formed it: in two steps most are one 8-bit instruction per block, so "
                     "the fraction compares with a 16-bit pass over everything and is not the share of time that the matrix cores are busy",
         },

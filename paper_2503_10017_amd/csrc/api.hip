@@ -157,6 +157,19 @@ int recip_coarse_searches(int batch, int64_t n, int64_t m, int64_t n_seeds, int 
     return gain <= COARSE_LEAST_GAIN ? 0 : (second > 2.0 * COARSE_LEAST_GAIN ? RECIP_COARSE_SEARCHES : 2);
 }
 
+// The iteration from which on the rest are one launch (recip_tail_kernel), -1: none.  The first two are the ones with many seeds, whose searches the
+// launches share out better; a walk that begins with few seeds is one launch altogether.  Whole calls in us with launches only / the tail from iteration
+// 0 / 1 / 2 / 3: one 512x384 pair, features of 1 and of 4 pixels, 192 seeds 163 / 84 / 104 / 112 and 180 / 91 / 112 / 128, 352 183 / 104 / 106 / 130 and
+// 185 / 109 / 111 / 131, 768 181 / 132 / 119 / 122 and 193 / 157 / 143 / 134, 3072 236 / 249 / 206 / 183 and 267 / 277 / 236 / 204; 320x240, 300 seeds 149 / 88 / 84 / 86, 1200
+// 153 / 157 / 121 / 102; 160x120, 1200 seeds 142 / 208 / 135 / 86.  Where very many seeds are left, the launches also have the wider search; from 2 / 3 on: 1024x768, 12288
+// seeds, 1082 / - / - / 1045 / 1022 and 1169 / - / - / 1111 / 1120, 16 pairs of 3072 1304 / - / - / 1261 / 1262 and 1470 / - / - / 1442 / 1429, of 12288 (features of 32 pixels) 5479 / - / - / 5648 / 5452.
+// (Two maps that have nothing in common and features of 32 pixels keep hundreds of seeds moving for all ten iterations: 16 pairs 3019 us in launches, 3060 so; one 441 and 442.)
+int first_late_iteration(int batch, int64_t n_seeds, int32_t max_iter, bool coarse) {
+    const int from = n_seeds >= 8192 || batch * n_seeds >= 49152 ? 3 : (n_seeds > TAIL_FEW || coarse ? 2 : (n_seeds > TAIL_FEW / 2 ? 1 : 0));
+    const int least = from > 2 ? from + 2 : 4;  // (with a single iteration left, four launches are as good)
+    return max_iter >= least && max_iter <= TAIL_MOST_ITERATIONS ? from : -1;
+}
+
 struct DenseLayout {
     MapsLayout maps;
     u64* row_keys;
@@ -241,6 +254,21 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     a.sample_lower = (uint32_t*)cv.take((size_t)batch * 2 * DENSE_SAMPLES * sizeof(uint32_t));
     a.marked = (int32_t*)cv.take((size_t)batch * 2 * sizeof(int32_t));
     L.sample_words = (int64_t)((cv.used - zeros) / sizeof(uint32_t));
+    return L;
+}
+
+// Room for the late iterations in one launch, behind everything else: a workspace that ends before it has them launched one by one.
+struct TailLayout {
+    TailControl* control;
+    u64* few_keys;
+    int64_t zero_words;  // 64-bit words that start at 0, from `control` on
+};
+TailLayout carve_tail(Carver& cv, int batch) {
+    TailLayout L;
+    const size_t z0 = cv.used;
+    L.control = (TailControl*)cv.take((size_t)batch * sizeof(TailControl));
+    L.few_keys = (u64*)cv.take((size_t)batch * 3 * TAIL_FEW * sizeof(u64));
+    L.zero_words = (int64_t)((cv.used - z0) / sizeof(u64));
     return L;
 }
 
@@ -566,6 +594,7 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
         carve_recip(cv, batch, n, m, de, n_queries, compute);
         if (recip_coarse_searches(batch, n, m, n_queries, compute, dp, d, l2))
             carve_coarse(cv, batch, n, m, true, n_queries, RECIP_COARSE_SEARCHES, compute);
+        carve_tail(cv, batch);
         if (cv.used > most) most = cv.used;
     }
     {
@@ -828,10 +857,20 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     const bool staged = fused || (L.maps.dp == 24 && opts->compute != FNN_F32 && first_search_applies(n_seeds, n, batch) &&
                                   first_search_applies(n_seeds, m, batch));
     // ... and large ones run in two steps, the first in 8 bits, where the workspace has the room
-    CoarseLayout C = carve_coarse(cv, batch, n, m, true, n_seeds, RECIP_COARSE_SEARCHES, compute);
-    const int coarse_searches = walk || cv.used > workspace_bytes ? 0 : recip_coarse_searches(batch, n, m, n_seeds, compute, L.maps.dp, d,
-                                                                                              (opts->flags & FNN_FLAG_L2) != 0);
+    Carver behind = cv;
+    CoarseLayout C = carve_coarse(behind, batch, n, m, true, n_seeds, RECIP_COARSE_SEARCHES, compute);
+    const int coarse_searches = walk || behind.used > workspace_bytes ? 0 : recip_coarse_searches(batch, n, m, n_seeds, compute, L.maps.dp, d,
+                                                                                                  (opts->flags & FNN_FLAG_L2) != 0);
     const bool coarse = coarse_searches > 0;
+    if (coarse) cv = behind;
+    // the late iterations are one launch
+    const TailLayout T = carve_tail(cv, batch);
+    const int tail_from = walk || cv.used > workspace_bytes ? -1 : first_late_iteration(batch, n_seeds, opts->max_iter, coarse);
+    const bool tail = tail_from >= 0;
+    if (tail) {
+        extra.zero_more = (u64*)T.control;
+        extra.zero_more_count = T.zero_words;
+    }
     const bool raw = coarse && raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
     const bool prepared = raw || (coarse && direct1 && direct2);  // the quantise launch is the first, and takes the side jobs
     if (!prepared) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
@@ -932,8 +971,40 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         ca.min_live = k < 2 ? 0 : coarse_min_live(compute, L.maps.dp);
         return launch_coarse_search(a, ca, batch, compute, L.maps.dp, s);
     };
+    // the iterations from t0 on, for the seeds of the half that take_state() chose
+    auto late_iterations = [&](int t0) -> hipError_t {
+        TailArgs ta;
+        memset(&ta, 0, sizeof(ta));
+        ta.p1 = p1;
+        ta.p2 = p2;
+        ta.bstride1 = bs1;
+        ta.bstride2 = bs2;
+        ta.rows1 = fwd.src_rows;
+        ta.rows2 = bwd.src_rows;
+        ta.n = (int32_t)n;
+        ta.m = (int32_t)m;
+        ta.n_seeds = ns;
+        for (int w = 0; w < 2; ++w) {
+            ta.cur_u[w] = L.st.cur_u[w];
+            ta.seed_id[w] = L.st.seed_id[w];
+        }
+        ta.half = which;
+        ta.n_active = L.st.n_active[which];
+        ta.keys = L.st.keys_f;  // empty, like keys_b, of which the tail keeps V^t in the first half
+        ta.v = (int32_t*)L.st.keys_b;
+        ta.few_keys = T.few_keys;
+        ta.control = T.control;
+        ta.t0 = t0;
+        ta.max_iter = opts->max_iter;
+        ta.seed_i = seed_i;
+        ta.seed_j = seed_j;
+        ta.seed_iter = seed_iter;
+        return launch_tail(ta, batch, compute, L.maps.dp, s);
+    };
     const bool fuse_first = fused && !coarse, stage_first = staged && !coarse;
-    if (fuse_first) {
+    if (tail_from == 0) {
+        FNN_TRY(late_iterations(0));
+    } else if (fuse_first) {
         FirstSearchArgs first;  // V^0 = NN_2(U^0): queries and candidates still raw; writes the prepared image 2
         first.s = fwd;
         first.s.src_rows = (int32_t)n;  // query rows are clamped to the caller's map, which has no padding rows
@@ -956,7 +1027,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         step.mode = 2;
         FNN_TRY(launch_resolve_step(bwd, step, batch, compute, L.maps.dp, s));
     }
-    for (int t = 0; t < opts->max_iter; ++t) {
+    for (int t = 0; t < opts->max_iter && tail_from != 0; ++t) {
         const bool last = (t == opts->max_iter - 1);
         if (stage_first && t == 0) {
             FirstSearchArgs first;  // U^1 = NN_1(V^0): queries from the prepared image 2; if raw, writes the prepared image 1
@@ -972,6 +1043,10 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         FNN_TRY(launch_resolve_step(bwd, step, batch, compute, L.maps.dp, s));
         if (last) break;
         take_state(which ^ 1);
+        if (t + 1 == tail_from) {
+            FNN_TRY(late_iterations(t + 1));
+            break;
+        }
         FNN_TRY(search(fwd, 2 * t + 2));  // V^{t+1} = NN_2(U^{t+1})
         FNN_TRY(launch_resolve(fwd, batch, compute, L.maps.dp, nullptr, nullptr, step.next_active, s));
     }

@@ -74,6 +74,8 @@ struct PrepSide {
 struct PrepExtra {
     u64* zero_ptr;          // range of 64-bit words to clear (NULL: none)
     int64_t zero_count;
+    u64* zero_more;         // a second one
+    int64_t zero_more_count;
     const int32_t* seeds;   // [batch][n_seeds] (NULL: no seed initialisation)
     int32_t* cur_u;         // [batch][n_seeds] <- seeds
     int32_t* seed_id;       // [batch][n_seeds] <- 0, 1, 2, ...
@@ -322,6 +324,44 @@ hipError_t launch_walk(const WalkArgs& a, int batch, int compute, int dp, hipStr
 // true if one workgroup per 32 seeds beats the launch sequence; the outputs of the sort (pairs, n_pairs) are launch_recip_dedup's
 bool groups_apply(int64_t n, int64_t m, int64_t n_seeds, int batch, int32_t max_iter, int compute, int dp);
 hipError_t launch_groups(const WalkArgs& a, int batch, int compute, int dp, hipStream_t s);
+
+// The iterations from t0 on in one launch (tail.hip), for all seeds that still move.
+constexpr int TAIL_FEW = 512;        // seeds of a pair that every workgroup can keep
+constexpr int TAIL_MOST_WGS = 256;   // of a pair
+constexpr int TAIL_COPIES = 16;      // of the words that many workgroups read or count in, each in a cache line of its own
+constexpr int TAIL_MOST_ITERATIONS = 1 << 20;
+struct TailControl {                 // of a pair; 0 on entry
+    struct alignas(128) Word { u64 word; };
+    struct alignas(128) Count { uint32_t count; };
+    Word phase[TAIL_COPIES];         // see tail.hip
+    Count arrived[TAIL_COPIES];
+    Count few_arrived[TAIL_COPIES], few_complete[TAIL_COPIES];
+    alignas(128) uint32_t groups_arrived;
+    alignas(128) uint32_t few_groups_arrived;
+    alignas(128) uint32_t registered;
+    alignas(128) uint32_t moving;
+};
+struct TailArgs {
+    const char* p1;                  // prepared maps of both images
+    const char* p2;
+    int64_t bstride1, bstride2;
+    int32_t rows1, rows2;            // rows per pair (indices are clamped to them)
+    int32_t n, m;                    // valid pixels
+    int32_t n_seeds;
+    int32_t* cur_u[2];               // [batch][n_seeds] see RecipState
+    int32_t* seed_id[2];
+    int32_t half;                    // of the two that holds the live seeds of iteration t0
+    const int32_t* n_active;         // [batch] their number
+    u64* keys;                       // [batch][n_seeds] 0 on entry
+    int32_t* v;                      // [batch][n_seeds] scratch
+    u64* few_keys;                   // [batch][3][TAIL_FEW] 0 on entry
+    TailControl* control;
+    int32_t t0, max_iter;            // t0 < max_iter <= TAIL_MOST_ITERATIONS
+    int32_t* seed_i;
+    int32_t* seed_j;
+    int32_t* seed_iter;
+};
+hipError_t launch_tail(const TailArgs& a, int batch, int compute, int dp, hipStream_t s);
 
 // ---- dense mutual nearest neighbours -----------------------------------------------------
 struct DenseArgs {

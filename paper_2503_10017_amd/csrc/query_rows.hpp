@@ -18,12 +18,16 @@ __device__ __forceinline__ int64_t query_row(const SearchArgs& a, int64_t qbase,
 // 512x384 pair: first search 37.6 -> 33.4 us, 16 pairs with 1450 queries each 241 -> 228 us, with the
 // waits moved out of the candidate loop, see arrived()).  Slots past the live queries repeat the
 // last one; their results are dropped.
-template <int N>
+// LIVE_LIST: q_idx was written by other workgroups of the same launch, so it is read past this compute unit's and this XCD's caches.
+template <int N, bool LIVE_LIST = false>
 __device__ __forceinline__ void query_rows(const SearchArgs& a, int64_t qbase, int slot0, int n_act, int c, int32_t (&row)[N]) {
     int slot[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) slot[i] = min(slot0 + i * 32 + c, n_act - 1);
-    if (a.q_keys) {
+    if constexpr (LIVE_LIST) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) row[i] = __hip_atomic_load(a.q_idx + qbase + slot[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (a.q_keys) {
         uint32_t low[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) low[i] = reinterpret_cast<const uint32_t*>(a.q_keys + qbase + slot[i])[0];

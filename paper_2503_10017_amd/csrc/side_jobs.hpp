@@ -10,6 +10,8 @@ __device__ __forceinline__ void side_jobs(const PrepExtra& x, int batch) {
     const int64_t n_threads = (int64_t)gridDim.x * gridDim.y * blockDim.x;
     if (x.zero_ptr)
         for (int64_t i = tid; i < x.zero_count; i += n_threads) x.zero_ptr[i] = 0;
+    if (x.zero_more)
+        for (int64_t i = tid; i < x.zero_more_count; i += n_threads) x.zero_more[i] = 0;
     if (x.seeds) {
         const int64_t total = (int64_t)batch * x.n_seeds;
         for (int64_t i = tid; i < total; i += n_threads) {

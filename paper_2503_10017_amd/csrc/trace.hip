@@ -103,6 +103,7 @@ const char* fnn_trace_kind_name(int32_t kind) {
         case TK_RECIP_GROUPS: return "recip_groups_kernel";
         case TK_DENSE_SAMPLE: return "dense_sample_kernel";
         case TK_DENSE_ALIKE: return "dense_alike_kernel";
+        case TK_RECIP_TAIL: return "recip_tail_kernel";
         default: return "unknown";
     }
 }

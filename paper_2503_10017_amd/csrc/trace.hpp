@@ -29,7 +29,8 @@ enum TraceKind : int {
     TK_RECIP_GROUPS = 18,
     TK_DENSE_SAMPLE = 19,
     TK_DENSE_ALIKE = 20,
-    TK_COUNT = 21
+    TK_RECIP_TAIL = 21,
+    TK_COUNT = 22
 };
 
 // Returns false when no trace is open or it is full; otherwise hands out the next event pair.

@@ -1,0 +1,109 @@
+"""The late iterations of a walk are one launch whose workgroups meet at barriers of their own.  The same call with a
+workspace that ends where that launch's control words would begin has every iteration in launches: both must give the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_10017_amd as fnn
+from gpu_helpers import check_reciprocal_exact, dev, exact_maps, host
+from test_gpu_coarse import one_step_bytes
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def wandering_maps(seed, batch, n, m, d):
+    """Two unrelated fields that vary slowly along the pixels: seeds climb from neighbour to neighbour for several iterations."""
+    gen = torch.Generator().manual_seed(seed)
+
+    def field(pixels):
+        knots = torch.randn((batch, d, pixels // 24 + 2), generator=gen)
+        x = torch.nn.functional.interpolate(knots, size=pixels, mode="linear", align_corners=True)
+        return torch.nn.functional.normalize(x, dim=1).permute(0, 2, 1).contiguous()
+
+    return field(n).cuda(), field(m).cuda()
+
+
+def run(a, b, seeds, max_iter, compute, tail, **kw):
+    (batch, n, d), m = a.shape, b.shape[1]
+    ns = seeds.shape[1]
+    full = fnn.fnn_workspace_bytes_opts(batch, n, m, d, ns, compute, max_iter, **kw)
+    ws = torch.full((full if tail else one_step_bytes("reciprocal", batch, n, m, d, ns, compute, **kw),), 0xA5, dtype=torch.uint8, device="cuda:0")
+    fnn.fnn_trace_begin(256)
+    try:
+        out = fnn.fnn_reciprocal(a, b, seeds, max_iter, compute, workspace=ws, **kw)
+        torch.cuda.synchronize()
+    finally:
+        names = [name for name, _ in fnn.fnn_trace_end(256)]
+    assert ("recip_tail_kernel" in names) == tail
+    return {k: host(v) for k, v in out.items()}, names
+
+
+@pytest.mark.parametrize("batch,n,m,n_seeds,compute,d,max_iter,option", [
+    (1, 9001, 9333, 256, "f16", 24, 10, None),    # a walk of few seeds from the first search on; a partial tile on either side
+    (1, 9001, 20011, 257, "f16", 24, 10, None),   # from the second iteration on
+    (1, 9001, 9333, 512, "bf16", 24, 4, None),    # the most that a workgroup keeps; seeds still moving at the end
+    (1, 9001, 9333, 513, "f16", 24, 10, None),    # one more: from the third on
+    (3, 16400, 12345, 5000, "f16", 24, 10, None),  # many seeds, then few
+    (2, 9001, 9333, 8192, "f16", 24, 6, None),    # from the fourth iteration on
+    (40, 2100, 1999, 700, "f16", 24, 10, None),   # six workgroups per pair
+    (64, 1000, 777, 300, "f16", 24, 7, None),     # four
+    (1, 9001, 9333, 600, "f16", 16, 10, None),
+    (1, 9001, 9333, 600, "bf16", 32, 10, None),
+    (1, 9001, 9333, 600, "f32", 5, 10, None),
+    (1, 9001, 9333, 600, "f32", 16, 10, None),
+    (2, 9001, 9333, 600, "f32", 24, 10, None),
+    (1, 9001, 9333, 200, "f32", 30, 10, None),
+    (1, 9001, 9333, 600, "f16", 24, 10, "l2"),
+    (1, 9001, 9333, 600, "f16", 16, 10, "split"),   # rows of 48 channels
+    (1, 9001, 9333, 600, "f16", 20, 10, "split"),   # 64
+    (2, 9001, 9333, 600, "f16", 24, 10, "split"),   # 80
+    (1, 9001, 9333, 600, "f16", 32, 10, "split"),   # 96
+])
+def test_one_launch_and_many_give_the_same(batch, n, m, n_seeds, compute, d, max_iter, option):
+    a, b = wandering_maps(n_seeds + d, batch, n, m, d)
+    gen = torch.Generator().manual_seed(d)
+    seeds = torch.randint(0, n, (batch, n_seeds), generator=gen, dtype=torch.int32).cuda()
+    kw = {option: True} if option else {}
+    one, _ = run(a, b, seeds, max_iter, compute, True, **kw)
+    many, names = run(a, b, seeds, max_iter, compute, False, **kw)
+    assert names.count("resolve_step_kernel") == max_iter
+    for k in many:
+        assert np.array_equal(one[k], many[k]), (k, int(np.sum(one[k] != many[k])))
+    late = (many["seed_iter"] >= 3) | (many["seed_iter"] < 0)
+    assert late.any()  # the maps are of the kind that this is about
+
+
+@pytest.mark.parametrize("n_seeds", [300, 1100])
+def test_ties_and_rows_that_are_not_finite(n_seeds):
+    a, b = exact_maps(31, 9001, 9333, 24)
+    seeds = np.random.default_rng(n_seeds).integers(0, 9001, size=(1, n_seeds)).astype(np.int32)
+    got, _ = run(dev(a)[None], dev(b)[None], dev(seeds), 10, "f16", True)
+    check_reciprocal_exact(got, 0, oracle.reciprocal(a, b, seeds[0], 10))
+    x, y = wandering_maps(5, 1, 9001, 9333, 24)
+    x[0, ::7] = float("nan")
+    y[0, 3::11] = float("inf")
+    one, _ = run(x, y, dev(seeds), 10, "f16", True)
+    many, _ = run(x, y, dev(seeds), 10, "f16", False)
+    for k in many:
+        assert np.array_equal(one[k], many[k]), k
+
+
+def test_calls_that_share_the_device():
+    """Workgroups wait for one another only while they run, so launches of several streams may have the chip in any shares."""
+    calls = []
+    for i in range(4):
+        a, b = wandering_maps(90 + i, 1 + i, 30000, 20011, 24)
+        seeds = torch.randint(0, 30000, (1 + i, 400 + 300 * i), generator=torch.Generator().manual_seed(i), dtype=torch.int32).cuda()
+        calls.append((a, b, seeds, torch.cuda.Stream()))
+    want = [fnn.fnn_reciprocal(a, b, seeds, 10, "f16") for a, b, seeds, _ in calls]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        got = []
+        for a, b, seeds, stream in calls:
+            with torch.cuda.stream(stream):
+                got.append(fnn.fnn_reciprocal(a, b, seeds, 10, "f16"))
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            for k in w:
+                assert torch.equal(g[k], w[k]), k
