@@ -69,7 +69,36 @@ __device__ __forceinline__ void search_unit(const SearchArgs& a, const char* src
             best_tile[g][r] = 0x7FFFFFFF;
         }
 
-    for (int tb = t0; tb < t1; tb += P) {
+    int tb = t0;
+    if constexpr (!EXACT && G < 4 && O::ROW_BYTES <= 64) {
+        // Whole trips of the ring over whole tiles with every group live: a product is followed by the maxima of the one before it
+        // (see coarse_kernel; here the matrix instructions are most of the time: one 512x384 pair 195.9 -> 193.3 us, two pairs with squared distance
+        // 317.4 -> 311.1; with four groups 16 pairs 1313 -> 1324; wider rows gain nothing and spill).
+        const int whole = live[G - 1] ? min(t1, a.m / 32) : t0;  // uniform
+        constexpr int BLOCKS = G * R;
+        static_assert(BLOCKS * P % 2 == 0, "a trip starts on acc[0]");
+        f32x16 acc[2];
+        if (tb + P <= whole) acc[0] = O::mma(ring[0], q[0][0]);
+        for (; tb + P <= whole; tb += P) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+#pragma unroll
+                for (int i = 0; i < BLOCKS; ++i) {
+                    const int n = p * BLOCKS + i, g = i / R, r = i % R;
+                    if (i + 1 < BLOCKS) acc[(n + 1) & 1] = O::mma(ring[p], q[(i + 1) / R][(i + 1) % R]);
+                    else acc[(n + 1) & 1] = O::mma(ring[(p + 1) % P], q[0][0]);  // past the last trip: of a tile that the loop below takes again
+                    if (i + 2 == BLOCKS) ring[p] = O::stream_tile(tgt + (int64_t)min(tb + p + P, t1 - 1) * (32 * O::ROW_BYTES), c, h);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const float top = fold16(best[g][r], acc[n & 1]);
+                    if (top > best[g][r]) best_tile[g][r] = tb + p;
+                    best[g][r] = top;
+                    asm volatile("" : "+v"(best[g][r]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }
+    for (; tb < t1; tb += P) {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             const int t = tb + p;
