@@ -68,6 +68,7 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
                                            int c, int h) {
     using O = Ops<CT, DP>;
     using Frag = typename O::Frag;
+    constexpr bool WIDE = O::ROW_BYTES > 64 && R > 2;
     const float ninf = -__builtin_inff();
     asm volatile("" : "+v"(c), "+v"(h));  // else what hangs on the lane is kept from search to search, and spills the tiles
     Frag ring[P];
@@ -95,25 +96,49 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
             if (__builtin_expect(t < t1, 1)) {  // uniform
                 const Frag cur = ring[p];
                 if (t + P < t1) ring[p] = O::stream_tile(tgt + (int64_t)(t + P) * (32 * O::ROW_BYTES), c, h);
-                f32x16 acc[R];
+                if constexpr (!WIDE) {
+                    f32x16 acc[R];
 #pragma unroll
-                for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
-                if (__builtin_expect(t * 32 + 32 > m, 0)) {  // only the last tile of the map can be partial
-                    const int bound = m - t * 32 - 4 * h;
+                    for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
+                    if (__builtin_expect(t * 32 + 32 > m, 0)) {  // only the last tile of the map can be partial
+                        const int bound = m - t * 32 - 4 * h;
 #pragma unroll
-                    for (int r = 0; r < R; ++r)
+                        for (int r = 0; r < R; ++r)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v)
-                            if (tile_row(v, 0) >= bound) acc[r][v] = ninf;
-                }
+                            for (int v = 0; v < 16; ++v)
+                                if (tile_row(v, 0) >= bound) acc[r][v] = ninf;
+                    }
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const float top = fold16(best[r], acc[r]);
-                    const bool rose = top > best[r];  // strictly: the lowest tile wins among equal scores
-                    best_tile[r] = rose ? t : best_tile[r];
+                    for (int r = 0; r < R; ++r) {
+                        const float top = fold16(best[r], acc[r]);
+                        const bool rose = top > best[r];  // strictly: the lowest tile wins among equal scores
+                        best_tile[r] = rose ? t : best_tile[r];
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) kept[r][v] = rose ? acc[r][v] : kept[r][v];
-                    best[r] = top;
+                        for (int v = 0; v < 16; ++v) kept[r][v] = rose ? acc[r][v] : kept[r][v];
+                        best[r] = top;
+                    }
+                } else {
+                    f32x16 acc[2];  // no room for more than the product that is folded and the next one
+                    acc[0] = O::mma(cur, q[0]);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        if (r + 1 < R) acc[(r + 1) & 1] = O::mma(cur, q[r + 1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        f32x16& x = acc[r & 1];
+                        if (__builtin_expect(t * 32 + 32 > m, 0)) {
+                            const int bound = m - t * 32 - 4 * h;
+#pragma unroll
+                            for (int v = 0; v < 16; ++v)
+                                if (tile_row(v, 0) >= bound) x[v] = ninf;
+                        }
+                        const float top = fold16(best[r], x);
+                        const bool rose = top > best[r];
+                        best_tile[r] = rose ? t : best_tile[r];
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) kept[r][v] = rose ? x[v] : kept[r][v];
+                        best[r] = top;
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
         }
@@ -131,10 +156,12 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
     }
 }
 template <int CT, int DP>
-constexpr int named_blocks() { return Ops<CT, DP>::ROW_BYTES / 8 <= 8 ? 4 : 2; }  // 32 registers each besides the query
+constexpr int named_blocks() {
+    return Ops<CT, DP>::ROW_BYTES / 8 <= 8 ? 4 : (Ops<CT, DP>::ROW_BYTES / 8 <= 20 ? 3 : 2);
+}
 template <int CT, int DP, int R>
 constexpr int named_ring() {
-    constexpr int frag_regs = Ops<CT, DP>::ROW_BYTES / 8, fit = (R == 4 ? 30 : (R == 2 ? 36 : 60)) / frag_regs;
+    constexpr int frag_regs = Ops<CT, DP>::ROW_BYTES / 8, fit = (R >= 3 ? 30 : (R == 2 ? 36 : 60)) / frag_regs;
     return fit > 12 ? 12 : (fit < 2 ? 2 : fit);
 }
 
@@ -336,8 +363,8 @@ void recip_tail_kernel(TailArgs ta) {
 #pragma unroll 1
             for (int slot0 = 0; slot0 < n_act; slot0 += 32 * MOST) {
                 if (n_act - slot0 <= 32) named_unit<CT, DP, 1, named_ring<CT, DP, 1>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
-                else if (MOST == 2 || n_act - slot0 <= 64) named_unit<CT, DP, 2, named_ring<CT, DP, 2>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
-                else if constexpr (MOST > 2) named_unit<CT, DP, MOST, named_ring<CT, DP, MOST>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
+                else if (n_act - slot0 <= 64) named_unit<CT, DP, 2, named_ring<CT, DP, 2>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
+                else named_unit<CT, DP, MOST, named_ring<CT, DP, MOST>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
             }
         }
         __syncthreads();
