@@ -365,9 +365,9 @@ bool raw_rows(int32_t batch, const fnn_map* maps) {
 bool raw_options(const fnn_opts* opts) {
     return opts->flags == 0 && (opts->compute == FNN_F16 || opts->compute == FNN_BF16);
 }
-// The quantise launch of two-term rows reads the caller's rows where it can: 96 bytes instead of 160.
-bool raw_halves(int32_t batch, const fnn_map* a, const fnn_map* b, const fnn_opts* opts) {
-    return opts->flags == FNN_FLAG_SPLIT && raw_rows(batch, a) && raw_rows(batch, b);
+// Maps that the quantise launch reads where they are, and prepares on the way: the same, and with two-term rows.
+bool raw_quantise(int32_t batch, const fnn_map* a, const fnn_map* b, const fnn_opts* opts) {
+    return (raw_options(opts) || opts->flags == FNN_FLAG_SPLIT) && raw_rows(batch, a) && raw_rows(batch, b);
 }
 bool raw_first_search(int32_t batch, const fnn_map* a, const fnn_map* b, const fnn_opts* opts, int64_t n_queries) {
     return raw_options(opts) && first_search_applies(n_queries, a[0].n, batch) && first_search_applies(n_queries, b[0].n, batch) &&
@@ -660,7 +660,7 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
     CoarseLayout C = carve_coarse(cv, batch, listed ? nq : n, m, false, nq, 1, opts->compute);
     const bool coarse = !nq_active && cv.used <= workspace_bytes &&
                         nearest_coarse_searches(batch, n, m, nq, listed, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0);
-    const bool raw = coarse && raw_options(opts) && raw_rows(batch, src) && raw_rows(batch, tgt);
+    const bool raw = coarse && raw_quantise(batch, src, tgt, opts);
     const bool prepared = raw || (coarse && direct1 && direct2);  // the quantise launch is the first, and takes the side jobs
     if (!prepared) FNN_TRY(prep_both(batch, src, tgt, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
     SearchArgs sa;
@@ -680,9 +680,8 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (prepared) qa.extra = extra;
-        const bool read_raw = raw || raw_halves(batch, src, tgt, opts);
-        fill_quantise_side(qa.side[0], batch, src, read_raw, p1, bs1, L.maps.n_pad, C.map[0]);
-        fill_quantise_side(qa.side[1], batch, tgt, read_raw, p2, bs2, L.maps.m_pad, C.map[1]);
+        fill_quantise_side(qa.side[0], batch, src, raw, p1, bs1, L.maps.n_pad, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, tgt, raw, p2, bs2, L.maps.m_pad, C.map[1]);
         if (listed) {
             qa.side[0].gather = q_idx;
             qa.side[0].gather_rows = n;
@@ -694,7 +693,7 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
             }
         }
         qa.batch = batch;
-        qa.raw_rows = read_raw ? 1 : 0;
+        qa.raw_rows = raw ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = C.zero_words;
@@ -871,18 +870,17 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         extra.zero_more = (u64*)T.control;
         extra.zero_more_count = T.zero_words;
     }
-    const bool raw = coarse && raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
+    const bool raw = coarse && raw_quantise(batch, d1, d2, opts);
     const bool prepared = raw || (coarse && direct1 && direct2);  // the quantise launch is the first, and takes the side jobs
     if (!prepared) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra, false, direct1 || fused, direct2 || fused));
     if (coarse) {
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (prepared) qa.extra = extra;
-        const bool read_raw = raw || raw_halves(batch, d1, d2, opts);
-        fill_quantise_side(qa.side[0], batch, d1, read_raw, p1, bs1, L.maps.n_pad, C.map[0]);
-        fill_quantise_side(qa.side[1], batch, d2, read_raw, p2, bs2, L.maps.m_pad, C.map[1]);
+        fill_quantise_side(qa.side[0], batch, d1, raw, p1, bs1, L.maps.n_pad, C.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, raw, p2, bs2, L.maps.m_pad, C.map[1]);
         qa.batch = batch;
-        qa.raw_rows = read_raw ? 1 : 0;
+        qa.raw_rows = raw ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = C.zero_words;
@@ -1146,16 +1144,15 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
     // Large maps: 8-bit scores first, then, where the workspace has the room, the second step of the searches in both directions
     DenseCoarseLayout C = carve_dense_coarse(cv, batch, n, m, L.maps);
     if (cv.used <= workspace_bytes && dense_coarse_gain(n, m, batch, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0) > 0.0) {
-        const bool raw = raw_options(opts) && raw_rows(batch, d1) && raw_rows(batch, d2);
+        const bool raw = raw_quantise(batch, d1, d2, opts);
         if (!raw) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra));
         QuantiseArgs qa;
         memset(&qa, 0, sizeof(qa));
         if (raw) qa.extra = extra;
-        const bool read_raw = raw || raw_halves(batch, d1, d2, opts);
-        fill_quantise_side(qa.side[0], batch, d1, read_raw, (const char*)L.maps.p1, L.maps.bstride1, L.maps.n_pad, C.args.map[0]);
-        fill_quantise_side(qa.side[1], batch, d2, read_raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
+        fill_quantise_side(qa.side[0], batch, d1, raw, (const char*)L.maps.p1, L.maps.bstride1, L.maps.n_pad, C.args.map[0]);
+        fill_quantise_side(qa.side[1], batch, d2, raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
         qa.batch = batch;
-        qa.raw_rows = read_raw ? 1 : 0;
+        qa.raw_rows = raw ? 1 : 0;
         qa.seg_pixels = C.args.seg_pixels;
         qa.lower = C.args.sample_lower;
         qa.lower_count = C.sample_words;

@@ -91,13 +91,15 @@ __device__ __forceinline__ float workgroup_max(float x, float* word) {  // x >= 
 // One workgroup turns one segment of prepared rows into 8-bit rows, a thread ROWS of them.  Between the segment's largest value
 // and the rounding the rows stay in registers, or, where they are too many (RELOAD), are read a second time.
 // RAW: the rows are the caller's fp32 rows of 24 channels; they are rounded to the compute format here and the
-// prepared map is written too, or, with SPLIT, only the high halves are formed: the prepared rows exist, but are 160
-// bytes where the caller's are 96 (four pairs of 512x384, the whole call 737 -> 721 us).  Bound by memory.
+// prepared map is written too.  Two-term rows, 160 bytes each, go through LDS so that a wave writes 16 bytes of a row beside the next 16 (four pairs of
+// 512x384, the whole call: a prepare launch and a second reading of the caller's rows 627 us, every thread writing its own row 618, so 585).  Bound by memory.
 template <int CT, int DP, bool SPLIT, bool RAW, int THREADS, int ROWS, bool RELOAD>
 __global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
     using Row = PreparedRow<CT, DP, SPLIT>;
     constexpr int K = Row::CHANNELS, SEGMENT = THREADS * ROWS, KEPT = RELOAD ? 1 : ROWS;
     __shared__ float top[4];  // largest value, remainder, length, and whether a row has no bound
+    constexpr int SPLIT_QUADS = DP / 8;  // a prepared two-term row, in 16-byte pieces
+    __shared__ uint4 rows_out[RAW && SPLIT ? THREADS / 64 : 1][RAW && SPLIT ? 32 * SPLIT_QUADS : 1];  // 32 of them per wave, so that they are written side by side
     side_jobs(a.extra, a.batch);
     {
         const int64_t tid = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * THREADS + threadIdx.x;
@@ -127,6 +129,44 @@ __global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
                 const float4 v = p[q];
                 w[2 * q] = round_pair<CT>(v.x, v.y);
                 w[2 * q + 1] = round_pair<CT>(v.z, v.w);
+            }
+            if (SPLIT && write) {  // [hi, hi, lo] in image 1, [hi, lo, hi] in image 2, as the prepare pass writes them
+                uint32_t low[12];
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    const float4 v = p[q];
+                    low[2 * q] = round_pair<CT>(__fsub_rn(v.x, (float)(_Float16)v.x), __fsub_rn(v.y, (float)(_Float16)v.y));
+                    low[2 * q + 1] = round_pair<CT>(__fsub_rn(v.z, (float)(_Float16)v.z), __fsub_rn(v.w, (float)(_Float16)v.w));
+                }
+                const bool real = pixel < sd.n, second = blockIdx.y >= (unsigned)a.batch;
+                const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                const int64_t first = pixel - lane;  // the wave's 64 rows lie side by side
+                uint4* out = reinterpret_cast<uint4*>(const_cast<char*>(prepared));
+#pragma unroll
+                for (int part = 0; part < 2; ++part) {  // 32 rows at a time
+                    if (lane >> 5 == part) {
+#pragma unroll
+                        for (int q = 0; q < SPLIT_QUADS; ++q) {
+                            uint32_t o[4];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const int at = 4 * q + e, copy = at / 12, k = at % 12;
+                                o[e] = copy == 0 ? w[k] : (copy == 1 ? (second ? low[k] : w[k]) : (copy == 2 ? (second ? w[k] : low[k]) : 0));
+                                if (!real) o[e] = 0;
+                            }
+                            rows_out[wave][(lane & 31) * SPLIT_QUADS + q] = make_uint4(o[0], o[1], o[2], o[3]);
+                        }
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // only the wave itself reads them, in the order of its instructions
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int k = 0; k < SPLIT_QUADS / 2; ++k) {
+                        const int at = k * 64 + lane;
+                        if (first + 32 * part + at / SPLIT_QUADS < sd.n_pad) out[(first + 32 * part) * SPLIT_QUADS + at] = rows_out[wave][at];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                }
             }
             if (!SPLIT && write && pixel < sd.n_pad) {
                 uint4* out = reinterpret_cast<uint4*>(const_cast<char*>(prepared) + pixel * O::ROW_BYTES);
