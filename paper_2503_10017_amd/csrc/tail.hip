@@ -55,6 +55,9 @@ static_assert(TAIL_MOST_WGS < 1024 && TAIL_MOST_ITERATIONS <= (1 << 22) / 4, "th
 constexpr int TAIL_WAVES = 8;    // two for every SIMD
 constexpr int TAIL_THREADS = TAIL_WAVES * 64;
 static_assert(TAIL_FEW == TAIL_THREADS, "a thread for each of few seeds");
+// A wait longer than this (the better part of a minute) means that two calls share a workspace unordered and have overwritten each other's words: their results
+// are lost either way, and the workgroup leaves.
+constexpr uint32_t TAIL_MOST_POLLS = 1u << 26;
 constexpr int TAIL_ROUND = 256;  // queries that a workgroup resolves before it hands its moving seeds on
 
 
@@ -174,7 +177,7 @@ void recip_tail_kernel(TailArgs ta) {
     __shared__ u64 published;
     __shared__ int2 moving[TAIL_ROUND];  // (U^{t+1}, seed number)
     __shared__ int n_moving, first_pos;
-    __shared__ uint32_t my_id;
+    __shared__ uint32_t my_id, lost;
     // few seeds: U^t and V^t, the seed number of every slot, and the keys of a search
     __shared__ int32_t few_at[2][TAIL_FEW], few_sid[TAIL_FEW];
     __shared__ u64 few_keys[TAIL_FEW];
@@ -197,6 +200,7 @@ void recip_tail_kernel(TailArgs ta) {
         if (lane == 0) id = shared_add(&ctl.registered, 1u);
         id = __builtin_amdgcn_readfirstlane(id);
         if (lane == 0) my_id = id;
+        if (lane == 0) lost = 0;
         if (id == 0) {
             // the first to come opens the first search; it gives the others a few microseconds to appear, and some more while they are few
             uint32_t takers = 1;
@@ -216,8 +220,9 @@ void recip_tail_kernel(TailArgs ta) {
     for (;;) {  // ends when few are left: a phase waits for running workgroups only, and every four phases are an iteration
         if (threadIdx.x == 0) {
             u64 word;
-            while ((word = shared_load(&ctl.phase[id % TAIL_COPIES].word)) == last) __builtin_amdgcn_s_sleep(1);
-            published = word;
+            uint32_t polls = 0;
+            while ((word = shared_load(&ctl.phase[id % TAIL_COPIES].word)) == last && ++polls < TAIL_MOST_POLLS) __builtin_amdgcn_s_sleep(1);
+            published = word == last ? 0 : word;
         }
         __syncthreads();
         last = published;
@@ -383,10 +388,13 @@ void recip_tail_kernel(TailArgs ta) {
             if (__builtin_amdgcn_readfirstlane(is_last)) {
                 if (lane < TAIL_COPIES) shared_store(&ctl.few_complete[lane].count, searches);
             } else if (lane == 0) {
-                while (shared_load(&ctl.few_complete[group].count) < searches) __builtin_amdgcn_s_sleep(1);
+                uint32_t polls = 0;
+                while (shared_load(&ctl.few_complete[group].count) < searches && ++polls < TAIL_MOST_POLLS) __builtin_amdgcn_s_sleep(1);
+                if (polls >= TAIL_MOST_POLLS) lost = 1;
             }
         }
         __syncthreads();
+        if (lost) return;
         const bool here = (int)threadIdx.x < n_act;
         const int32_t found = here ? min(max(key_index(shared_load(&keys[threadIdx.x])), 0), m - 1) : 0;
         if (forward) {

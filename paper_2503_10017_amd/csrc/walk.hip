@@ -391,6 +391,9 @@ bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int c
 // and with 32 channels
 //     200 seeds, 1 pair     145 tiles  151 / 190,  43 / 49,  30 / 87    210 tiles  186 / 193,  51 / 49,  34 / 88
 //     256 seeds, 32 pairs   145 tiles  227 / 305,  68 / 75,  50 / 108
+// The sequence has its late iterations in one launch since; on maps that need no prepared copy (which keep it, and save 4 us of that) it takes, settled at once,
+//     200 seeds, 144 tiles  48 / 48    160 seeds, 224 tiles  51 to 58 / 43 to 47    190 seeds, 280 tiles  57 to 64 / 46 to 48
+// so beyond some 200 tiles it would be the better one; the lines are those of seeds that never settle.
 // A full chip sweeps a tile at two thirds of the speed of a quarter of it, and more than one workgroup per compute unit would walk
 // in turns.  fp32 products and two-term rows take several times as long per tile.  Past 256 seeds, and on maps that need no prepared
 // copy, the sequence runs as before.
