@@ -52,7 +52,10 @@
  *    16 channels (FNN_F32: any), for searches with at least 2048 queries per pair (256 with
  *    FNN_F32 or rows of more than 32 channels, that is FNN_FLAG_SPLIT with d > 10).  This takes a
  *    workspace of the size that fnn_workspace_bytes() returns; one that has room for the prepared
- *    maps and the call's state only is accepted as well and searched in one step.
+ *    maps and the call's state only is accepted as well and searched in one step.  With such a
+ *    workspace of fnn_workspace_bytes(), fnn_reciprocal also takes its late iterations in one
+ *    launch whose workgroups wait for one another, but only for such as are running: it ends
+ *    however many of them the device has room for.
  *    Two cases need no separate copy pass, and results do not depend on which way a map took:
  *    (a) the caller's array already is what the copy would be -- stored in the compute format,
  *    d in {16, 24, 32} (16-bit formats) or a multiple of 8 (FNN_F32), row_stride == d, n a
