@@ -71,8 +71,9 @@ __global__ __launch_bounds__(DEDUP_THREADS) void recip_dedup_kernel(DedupArgs a)
     }
     __syncthreads();
 
-    // contiguous run of words per thread, so that ranks ascend with the thread index
-    const int per_thread = (a.n_words + DEDUP_THREADS - 1) / DEDUP_THREADS;
+    // contiguous run of words per thread, so that ranks ascend with the thread index; an odd number of them, so that the threads' words lie in
+    // different LDS banks (1024x768, 24 words: eight threads of a wave to a bank; the whole call 980.7 -> 976.8 us with 25)
+    const int per_thread = ((a.n_words + DEDUP_THREADS - 1) / DEDUP_THREADS) | 1;
     const int w0 = min((int)threadIdx.x * per_thread, a.n_words);
     const int w1 = min(w0 + per_thread, a.n_words);
     int mine = 0;
