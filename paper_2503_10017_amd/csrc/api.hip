@@ -994,6 +994,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         ta.control = T.control;
         ta.t0 = t0;
         ta.max_iter = opts->max_iter;
+        ta.most_polls = tail_most_polls(n, m, ns);
         ta.seed_i = seed_i;
         ta.seed_j = seed_j;
         ta.seed_iter = seed_iter;

@@ -55,9 +55,6 @@ static_assert(TAIL_MOST_WGS < 1024 && TAIL_MOST_ITERATIONS <= (1 << 22) / 4, "th
 constexpr int TAIL_WAVES = 8;    // two for every SIMD
 constexpr int TAIL_THREADS = TAIL_WAVES * 64;
 static_assert(TAIL_FEW == TAIL_THREADS, "a thread for each of few seeds");
-// A wait longer than this (the better part of a minute) means that two calls share a workspace unordered and have overwritten each other's words: their results
-// are lost either way, and the workgroup leaves.
-constexpr uint32_t TAIL_MOST_POLLS = 1u << 26;
 constexpr int TAIL_ROUND = 256;  // queries that a workgroup resolves before it hands its moving seeds on
 
 
@@ -220,9 +217,9 @@ void recip_tail_kernel(TailArgs ta) {
     for (;;) {  // ends when few are left: a phase waits for running workgroups only, and every four phases are an iteration
         if (threadIdx.x == 0) {
             u64 word;
-            uint32_t polls = 0;
-            while ((word = shared_load(&ctl.phase[id % TAIL_COPIES].word)) == last && ++polls < TAIL_MOST_POLLS) __builtin_amdgcn_s_sleep(1);
-            published = word == last ? 0 : word;
+            uint64_t polls = 0;
+            while ((word = shared_load(&ctl.phase[id % TAIL_COPIES].word)) == last && ++polls < ta.most_polls) __builtin_amdgcn_s_sleep(1);
+            published = word == last ? 0 : word;  // given up (see tail_most_polls): leave
         }
         __syncthreads();
         last = published;
@@ -388,9 +385,9 @@ void recip_tail_kernel(TailArgs ta) {
             if (__builtin_amdgcn_readfirstlane(is_last)) {
                 if (lane < TAIL_COPIES) shared_store(&ctl.few_complete[lane].count, searches);
             } else if (lane == 0) {
-                uint32_t polls = 0;
-                while (shared_load(&ctl.few_complete[group].count) < searches && ++polls < TAIL_MOST_POLLS) __builtin_amdgcn_s_sleep(1);
-                if (polls >= TAIL_MOST_POLLS) lost = 1;
+                uint64_t polls = 0;
+                while (shared_load(&ctl.few_complete[group].count) < searches && ++polls < ta.most_polls) __builtin_amdgcn_s_sleep(1);
+                if (polls >= ta.most_polls) lost = 1;
             }
         }
         __syncthreads();
