@@ -869,6 +869,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
     if (tail) {
         extra.zero_more = (u64*)T.control;
         extra.zero_more_count = T.zero_words;
+        extra.seed_iter = seed_iter;  // a seed that the late iterations give up is none that the final sort looks at
     }
     const bool raw = coarse && raw_quantise(batch, d1, d2, opts);
     const bool prepared = raw || (coarse && direct1 && direct2);  // the quantise launch is the first, and takes the side jobs

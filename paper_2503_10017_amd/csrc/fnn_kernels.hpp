@@ -79,6 +79,7 @@ struct PrepExtra {
     const int32_t* seeds;   // [batch][n_seeds] (NULL: no seed initialisation)
     int32_t* cur_u;         // [batch][n_seeds] <- seeds
     int32_t* seed_id;       // [batch][n_seeds] <- 0, 1, 2, ...
+    int32_t* seed_iter;     // [batch][n_seeds] <- -1 (NULL: not written)
     int32_t* n_active;      // [batch] <- n_seeds
     int32_t n_seeds;
 };

@@ -17,6 +17,7 @@ __device__ __forceinline__ void side_jobs(const PrepExtra& x, int batch) {
         for (int64_t i = tid; i < total; i += n_threads) {
             x.cur_u[i] = x.seeds[i];
             x.seed_id[i] = (int32_t)(i % x.n_seeds);
+            if (x.seed_iter) x.seed_iter[i] = -1;
         }
         for (int64_t b = tid; b < batch; b += n_threads) x.n_active[b] = x.n_seeds;
     }

@@ -1,5 +1,7 @@
 """The late iterations of a walk are one launch whose workgroups meet at barriers of their own.  The same call with a
 workspace that ends where that launch's control words would begin has every iteration in launches: both must give the same bits."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -107,3 +109,64 @@ def test_calls_that_share_the_device():
         for g, w in zip(got, want):
             for k in w:
                 assert torch.equal(g[k], w[k]), k
+
+
+def hip():
+    """The HIP runtime that this process runs on."""
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    return ctypes.CDLL(path)
+
+
+@pytest.mark.parametrize("batch,n,m,n_seeds,option,first", [
+    (2, 9001, 9333, 700, None, "prep"),
+    (1, 9001, 9333, 600, "l2", "prep"),
+    (16, 66000, 70001, 4000, None, "quantise_kernel"),
+    (4, 66000, 70001, 4000, "split", "quantise_kernel"),
+])
+def test_seeds_that_the_launch_gives_up_are_no_matches(batch, n, m, n_seeds, option, first):
+    """A call without its late iterations (taken out of the captured call on the host, as if every workgroup had left) has no match of
+    a seed that they would have settled, whatever the caller's arrays held; with them back in, it is the call that it was."""
+    a, b = wandering_maps(n_seeds, batch, n, m, 24)
+    seeds = torch.randint(0, n, (batch, n_seeds), generator=torch.Generator().manual_seed(1), dtype=torch.int32).cuda()
+    kw = {option: True} if option else {}
+    ws = torch.empty(fnn.fnn_workspace_bytes_opts(batch, n, m, 24, n_seeds, "f16", 10, **kw), dtype=torch.uint8, device="cuda:0")
+    fnn.fnn_trace_begin(64)
+    out = fnn.fnn_reciprocal(a, b, seeds, 10, "f16", workspace=ws, **kw)
+    torch.cuda.synchronize()
+    names = [name for name, _ in fnn.fnn_trace_end(64)]
+    assert names[0].startswith(first)
+    want = {k: host(v) for k, v in out.items()}
+    tail_from = names.count("resolve_step_kernel")
+
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fnn.fnn_reciprocal(a, b, seeds, 10, "f16", out=out, workspace=ws, **kw)
+    lib, raw, count = hip(), ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert lib.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0 and count.value == len(names)
+    nodes, run_it = (ctypes.c_void_p * len(names))(), ctypes.c_void_p()
+    assert lib.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    assert lib.hipGraphInstantiate(ctypes.byref(run_it), raw, None, None, ctypes.c_size_t(0)) == 0
+    tail = ctypes.c_void_p(nodes[names.index("recip_tail_kernel")])
+    for enabled in (0, 1):
+        for k, x in (("seed_i", 5), ("seed_j", 7), ("seed_iter", 3), ("pairs", -3), ("n_pairs", -3)):
+            out[k].fill_(x)
+        assert lib.hipGraphNodeSetEnabled(run_it, tail, ctypes.c_uint(enabled)) == 0
+        torch.cuda.synchronize()
+        assert lib.hipGraphLaunch(run_it, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        torch.cuda.synchronize()
+        got = {k: host(v) for k, v in out.items()}
+        settled = (want["seed_iter"] >= 0) & (want["seed_iter"] < (10 if enabled else tail_from))
+        assert np.array_equal(got["seed_iter"], np.where(settled, want["seed_iter"], -1))
+        for p in range(batch):
+            done = settled[p]
+            for k in ("seed_i", "seed_j"):
+                assert np.array_equal(got[k][p][done], want[k][p][done]), k
+            pairs = np.unique(np.stack([want["seed_i"][p][done], want["seed_j"][p][done]], axis=1), axis=0)
+            assert np.array_equal(got["pairs"][p, :int(got["n_pairs"][p])], pairs)
+        if enabled:
+            for k in want:
+                assert np.array_equal(got[k], want[k]), k
+        else:
+            assert not settled.all()
+    assert lib.hipGraphExecDestroy(run_it) == 0
