@@ -60,7 +60,8 @@ constexpr int TAIL_ROUND = 256;  // queries that a workgroup resolves before it 
 
 // Pass 1 of few queries with the candidates named: R blocks of queries, rows at[slot] of `src` from slot0 on, against the tiles [t0, t1).
 // A lane keeps the 16 scores of its query's best tile (16 moves per block and tile: a wave has few tiles), and looks for
-// the candidate when the last one is done.  The keys are those that the resolve pass would leave, also where no score is a number.  Bound by latency: the
+// the candidate when the last one is done.  The keys are those that the resolve pass would leave, also where no score is more than minus infinity (the first such
+// in the last tile of the map) or none is a number (the last pixel).  Bound by latency: the
 // queries' rows, the tiles.  (Keeping the tile, and multiplying it again for every query of the workgroup, as a variant of this kernel: 512x384 193 -> 215 us, squared
 // distance of two pairs 312 -> 336, 16 pairs 1251 -> 1249; both ways in one kernel spilled and were slower than either.)
 template <int CT, int DP, int R, int P>
@@ -70,6 +71,7 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
     using Frag = typename O::Frag;
     constexpr bool WIDE = O::ROW_BYTES > 64 && R > 2;
     const float ninf = -__builtin_inff();
+    const int last = (m - 1) / 32;
     asm volatile("" : "+v"(c), "+v"(h));  // else what hangs on the lane is kept from search to search, and spills the tiles
     Frag ring[P];
 #pragma unroll
@@ -85,7 +87,7 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
     for (int r = 0; r < R; ++r) {
         arrived(q[r]);
         best[r] = ninf;
-        best_tile[r] = (m - 1) / 32;
+        best_tile[r] = last;
 #pragma unroll
         for (int v = 0; v < 16; ++v) kept[r][v] = 0.0f;
     }
@@ -100,13 +102,15 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
                     f32x16 acc[R];
 #pragma unroll
                     for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
-                    if (__builtin_expect(t * 32 + 32 > m, 0)) {  // only the last tile of the map can be partial
+                    if (__builtin_expect(t == last, 0)) {  // the only one that can be partial, and that which stands for scores of minus infinity
                         const int bound = m - t * 32 - 4 * h;
 #pragma unroll
                         for (int r = 0; r < R; ++r)
 #pragma unroll
-                            for (int v = 0; v < 16; ++v)
+                            for (int v = 0; v < 16; ++v) {
                                 if (tile_row(v, 0) >= bound) acc[r][v] = ninf;
+                                if (best[r] == ninf) kept[r][v] = acc[r][v];
+                            }
                     }
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
@@ -125,11 +129,13 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
                         if (r + 1 < R) acc[(r + 1) & 1] = O::mma(cur, q[r + 1]);
                         __builtin_amdgcn_sched_barrier(0);
                         f32x16& x = acc[r & 1];
-                        if (__builtin_expect(t * 32 + 32 > m, 0)) {
+                        if (__builtin_expect(t == last, 0)) {
                             const int bound = m - t * 32 - 4 * h;
 #pragma unroll
-                            for (int v = 0; v < 16; ++v)
+                            for (int v = 0; v < 16; ++v) {
                                 if (tile_row(v, 0) >= bound) x[v] = ninf;
+                                if (best[r] == ninf) kept[r][v] = x[v];
+                            }
                         }
                         const float top = fold16(best[r], x);
                         const bool rose = top > best[r];

@@ -91,6 +91,23 @@ def test_ties_and_rows_that_are_not_finite(n_seeds):
         assert np.array_equal(one[k], many[k]), k
 
 
+@pytest.mark.parametrize("not_numbers", [0, 5, 32])
+@pytest.mark.parametrize("m,n_seeds,compute,d", [(9333, 256, "f16", 24), (9344, 300, "bf16", 24), (9333, 300, "f32", 32), (9344, 60, "f16", 16)])
+def test_scores_of_minus_infinity(m, n_seeds, compute, d, not_numbers):
+    """Every score is minus infinity, or, of some rows or all of the last tile, not a number: which candidate is named does not hang on the route."""
+    x, y = wandering_maps(8, 1, 9001, m, d)
+    x[..., 0] = x[..., 0].abs() + 0.125
+    y[..., 0] = -float("inf")
+    first = (m - 1) // 32 * 32
+    y[0, first:first + not_numbers] = float("nan")
+    seeds = torch.randint(0, 9001, (1, n_seeds), generator=torch.Generator().manual_seed(d), dtype=torch.int32).cuda()
+    one, _ = run(x, y, seeds, 10, compute, True)
+    many, _ = run(x, y, seeds, 10, compute, False)
+    for k in many:
+        assert np.array_equal(one[k], many[k]), k
+    assert (many["seed_j"] == min(first + not_numbers, m - 1)).all()
+
+
 def test_calls_that_share_the_device():
     """Workgroups wait for one another only while they run, so launches of several streams may have the chip in any shares."""
     calls = []
