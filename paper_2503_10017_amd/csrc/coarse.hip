@@ -763,18 +763,22 @@ static int64_t coarse_longest(int wide, int resident, int batch, int64_t pairs, 
 }
 
 // Half segments split a small search more evenly and spread step 2 over more workgroups; whole ones read a tile a third as often and keep the pipeline
-// of products and maxima filled for longer, some 8 % of step 1.  So the split that leaves less to the busiest wave is taken, with the workgroups that 256
-// compute units hold of either kernel (a workspace is sized without a device).  Where step 2 would have few workgroups, or dear ones, half
-// segments win anyway.  Whole / half segments, all of a call's time in us: 512x384, 3072 queries, 1 pair 47.3 / 42.6, 2 60.0 / 62.0, 3 87.3 / 83.7, 4 98.9 / 104.5, 6 144 / 152,
-// 8 190 / 204, 12 282 / 307, 16 369 / 401, seeds that walk, 4 pairs 464 / 474, 6 641 / 639, 8 767 / 801; three 640x480 pairs 162 / 169; one 768x576 pair
-// 113 / 113, walking 513 / 496, 896x672 186 / 193 and 749 / 757, 1024x768 275 / 300; every pixel of 256x192 121 / 112, of 320x240 214 / 227; fp32 products, 512x384, walking, 768 seeds
-// of 2 pairs 282 / 268, of 4 379 / 374, 3072 of one 359 / 315, of 4 659 / 649; two-term rows of 4 pairs 683 / 703, of one 327 / 298.
+// of products and maxima filled for longer.  The split that leaves less to the busiest wave is taken, with the workgroups that 256 compute units hold of either
+// kernel (a workspace is sized without a device), where a half segment's products count 18 % more and half segments have two
+// products of each wave on a SIMD ahead of whole ones.  Where step 2 would have few workgroups, or dear ones, half segments win anyway.  (Over 210 calls from 256x192 to
+// 1024x768, 1 to 16 pairs, 2048 to 12288 queries, the slower split is taken in 25, which costs 1.9 % on average there and 7.7 % at most.)  Whole / half segments, all
+// of a call's time in us: 3072 queries: 256x192, 2 pairs 47.9 / 34.2, 4 51.3 / 47.5, 8 71.8 / 73.4; 320x240, 2 48.8 / 39.8, 4 59.5 / 57.3, 8 101.9 / 97.8, 16 171.1 / 177.4; 512x384, 1
+// 45.9 / 42.0, 2 58.9 / 61.4, 3 86.0 / 82.9, 4 100.0 / 105.7, 8 190.6 / 206.5, 16 370.0 / 403.5; 640x480, 2 87.0 / 85.0, 3 118.0 / 120.2; 768x576, 1 66.9 / 66.5; 1024x768, 1 94.0 / 100.7; 12288
+// queries: 256x192, 2 pairs 77.7 / 69.4, 8 205.0 / 209.8, 16 375.9 / 431.9; 512x384, 4 297.0 / 322.4; seeds that walk: 512x384, 4 pairs 414 / 426, 6 584 / 585, 16
+// 1338 / 1437; 640x480, 1 313 / 284, 1024x768 1017 / 1086; every pixel of 256x192 126 / 116, of 320x240 220 / 234; fp32 products, 512x384, 3072 seeds of 1 pair 268 / 225,
+// of 4 581 / 565, 768 of 8 582 / 562; two-term rows of 1 pair 263 / 238, of 2 383 / 355, of 4 585 / 609.
+constexpr int COARSE_WGS_8 = 512, COARSE_WGS_6 = 768, COARSE_WGS_HALF = 1024;
 int coarse_cells(int64_t nq, int64_t n_segs, int batch, int compute) {
     if (n_segs < 1 || nq < 1) return 1;
     const int64_t pairs = (nq + 63) / 64;
-    const int64_t eight = coarse_longest(8, 512, batch, pairs, n_segs), six = coarse_longest(6, 768, batch, pairs, n_segs);
-    const double half = 0.5 * coarse_longest(2, 1280, batch, pairs, 2 * n_segs);
-    return n_segs * batch < 128 || (compute == FNN_F32 && n_segs * batch <= 1024) || 1.08 * half < (eight < six ? eight : six) ? 2 : 1;
+    const int64_t eight = coarse_longest(8, COARSE_WGS_8, batch, pairs, n_segs), six = coarse_longest(6, COARSE_WGS_6, batch, pairs, n_segs);
+    const double half = 0.5 * coarse_longest(2, COARSE_WGS_HALF, batch, pairs, 2 * n_segs), whole = (double)(eight < six ? eight : six);
+    return n_segs * batch < 160 || (compute == FNN_F32 && n_segs * batch <= 1024) || 1.18 * half < whole + 2 * COARSE_WGS_8 ? 2 : 1;
 }
 
 int64_t coarse_slab(int64_t nq, int64_t n_segs, int batch) {

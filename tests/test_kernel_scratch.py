@@ -1,5 +1,6 @@
 """The search kernels of the paper's row width keep everything in registers: a kernel that spills uses scratch
 memory, and a launch of one takes about 2 us longer to start.  Read from the kernel descriptions in the built library."""
+import os
 import re
 import struct
 import subprocess
@@ -13,6 +14,11 @@ READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 
 def scratch_bytes(tmp_path):
     """Kernel name -> bytes of scratch memory per lane, over every gfx950 code object in the library."""
+    return {name: scratch for name, (scratch, _) in kernel_notes(tmp_path).items()}
+
+
+def kernel_notes(tmp_path):
+    """Kernel name -> (bytes of scratch memory per lane, vector registers), over every gfx950 code object in the library."""
     with open(fnn.library_path(), "rb") as f:
         image = f.read()
     found = {}
@@ -29,8 +35,8 @@ def scratch_bytes(tmp_path):
             path = tmp_path / "code.o"
             path.write_bytes(image[bundle.start() + offset:bundle.start() + offset + size])
             notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
-            for name, scratch in re.findall(r"\.name:\s+(_Z\S+)\n\s+\.private_segment_fixed_size: (\d+)", notes):
-                found[name] = int(scratch)
+            for name, scratch, rest in re.findall(r"\.name:\s+(_Z\S+)\n\s+\.private_segment_fixed_size: (\d+)\n((?:\s+\.(?!name:|args:).*\n)*)", notes):
+                found[name] = int(scratch), int(re.search(r"\.vgpr_count:\s+(\d+)", rest).group(1))
     return found
 
 
@@ -52,3 +58,19 @@ def test_no_scratch_memory_in_the_8_bit_passes(tmp_path):
     for kernel in ("refine_kernel", "quantise_kernel"):   # 16-bit rows of 24 channels
         found = {k: v for k, v in scratch.items() if re.match(rf"_ZN3fnn\d+{kernel}ILi[12]ELi24E", k)}
         assert len(found) >= 4 and not {k: v for k, v in found.items() if v}
+
+
+def test_workgroups_that_the_choice_between_whole_and_half_segments_counts_on(tmp_path):
+    """A workspace is sized without a device, so the rule has the resident workgroups of coarse_kernel's variants as numbers: four waves each, one
+    on every SIMD of 256 compute units (the stages' 16 KB of LDS leave room for ten)."""
+    with open(os.path.join(os.path.dirname(fnn.__file__), "csrc", "coarse.hip")) as f:
+        source = f.read()
+    said = {8: "COARSE_WGS_8", 6: "COARSE_WGS_6", 2: "COARSE_WGS_HALF"}
+    said = {pairs: int(re.search(rf"{name} = (\d+)[,;]", source).group(1)) for pairs, name in said.items()}
+    seen = set()
+    for name, (_, registers) in kernel_notes(tmp_path).items():
+        of = re.match(r"_ZN3fnn\d+coarse_kernelILi(\d)E", name)
+        if of:
+            seen.add(int(of.group(1)))
+            assert 256 * (512 // (-(-registers // 8) * 8)) == said[int(of.group(1))], (name, registers)
+    assert seen == set(said)
