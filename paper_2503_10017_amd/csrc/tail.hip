@@ -102,15 +102,13 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
                     f32x16 acc[R];
 #pragma unroll
                     for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
-                    if (__builtin_expect(t == last, 0)) {  // the only one that can be partial, and that which stands for scores of minus infinity
+                    if (__builtin_expect(t * 32 + 32 > m, 0)) {  // only the last tile of the map can be partial
                         const int bound = m - t * 32 - 4 * h;
 #pragma unroll
                         for (int r = 0; r < R; ++r)
 #pragma unroll
-                            for (int v = 0; v < 16; ++v) {
+                            for (int v = 0; v < 16; ++v)
                                 if (tile_row(v, 0) >= bound) acc[r][v] = ninf;
-                                if (best[r] == ninf) kept[r][v] = acc[r][v];
-                            }
                     }
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
@@ -129,13 +127,11 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
                         if (r + 1 < R) acc[(r + 1) & 1] = O::mma(cur, q[r + 1]);
                         __builtin_amdgcn_sched_barrier(0);
                         f32x16& x = acc[r & 1];
-                        if (__builtin_expect(t == last, 0)) {
+                        if (__builtin_expect(t * 32 + 32 > m, 0)) {
                             const int bound = m - t * 32 - 4 * h;
 #pragma unroll
-                            for (int v = 0; v < 16; ++v) {
+                            for (int v = 0; v < 16; ++v)
                                 if (tile_row(v, 0) >= bound) x[v] = ninf;
-                                if (best[r] == ninf) kept[r][v] = x[v];
-                            }
                         }
                         const float top = fold16(best[r], x);
                         const bool rose = top > best[r];
@@ -146,6 +142,24 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
+            }
+        }
+    }
+    // Where no score was more than minus infinity, the last tile of the map stands for them all.  (Kept in the loop, in each of the ring's places, that is a
+    // fifth of the kernel's code, and a call on other inputs 10 us longer.)
+    if (t1 > last) {  // uniform
+        bool none = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) none = none || best[r] == ninf;
+        if (__builtin_expect(__any(none), 0)) {
+            const Frag tile = O::stream_tile(tgt + (int64_t)last * (32 * O::ROW_BYTES), c, h);
+            const int bound = m - last * 32 - 4 * h;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const f32x16 x = O::mma(tile, q[r]);
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (best[r] == ninf) kept[r][v] = tile_row(v, 0) >= bound ? ninf : x[v];
             }
         }
     }
