@@ -449,9 +449,11 @@ static int tail_wgs_per_pair(const TailArgs& a, int batch, int compute, int dp) 
     return wgs < 1 ? 1 : wgs;
 }
 
-// Groups of query blocks per wave while many seeds move: four would leave the named search no registers.
+// Groups of query blocks per wave while many seeds move: four would leave the named search no registers, and two of rows of 96 bytes spill 17 of them (fp32 products
+// of 24 channels, two 512x384 pairs of 768 seeds that hardly settle 729 us with two, 690 with one).  Wider rows spill a few as they are, 20 of 96 two-term channels: half the
+// query blocks cost more than that (two-term rows of four pairs that hardly settle 1627 us, 1880 with two blocks and no spill).
 template <int CT, int DP>
-constexpr int tail_groups() { return search_g_limit<CT, DP>() > 2 ? 2 : search_g_limit<CT, DP>(); }
+constexpr int tail_groups() { return Ops<CT, DP>::ROW_BYTES > 64 ? 1 : (search_g_limit<CT, DP>() > 2 ? 2 : search_g_limit<CT, DP>()); }
 
 template <int CT, int DP>
 static hipError_t launch_tail_t(const TailArgs& a, int batch, hipStream_t s) {

@@ -60,6 +60,16 @@ def test_no_scratch_memory_in_the_8_bit_passes(tmp_path):
         assert len(found) >= 4 and not {k: v for k, v in found.items() if v}
 
 
+def test_scratch_memory_of_the_late_iterations(tmp_path):
+    """None for rows of up to 96 bytes; wider ones keep a few registers there, which costs less than fewer query blocks would."""
+    found = {k: v for k, v in scratch_bytes(tmp_path).items() if re.match(r"_ZN3fnn\d+recip_tail_kernelI", k)}
+    assert len(found) == 14
+    for name, scratch in found.items():
+        compute, channels = (int(x) for x in re.match(r".*recip_tail_kernelILi(\d)ELi(\d+)E", name).groups())
+        row_bytes = channels * (4 if compute == 0 else 2)
+        assert scratch <= (0 if row_bytes <= 96 else (32 if row_bytes <= 160 else 96)), (name, scratch)
+
+
 def test_workgroups_that_the_choice_between_whole_and_half_segments_counts_on(tmp_path):
     """A workspace is sized without a device, so the rule has the resident workgroups of coarse_kernel's variants as numbers: four waves each, one
     on every SIMD of 256 compute units (the stages' 16 KB of LDS leave room for ten)."""
