@@ -373,6 +373,13 @@ static size_t walk_lds_bytes(int64_t n, int64_t n_seeds, int row_bytes) {
 // fp32 products of 32 channels: 266 against 286; two blocks x 2 tiles: 303 against 223).
 // The 64x48 pair with 48 seeds (2 blocks x 96 tiles) takes 23 to 154 against 189 to 194.  With a few allowed
 // iterations the sequence is short as well: at most 100 products for each.
+// Those are figures of the sequence in launches.  With its late iterations in one launch (what it takes with a workspace of fnn_workspace_bytes()) it is
+// the faster one beyond some 60 tiles.  Walk / sequence, replayed from a graph, settled at once and live for all ten iterations:
+//     30 seeds   16 tiles  22 / 24,  92 / 98    64  24 / 25, 107 / 104    96  25 / 25, 116 / 102    175  28 / 25, 140 / 106
+//     60 seeds   32 tiles  24 / 25, 113 / 105   64  25 / 25, 124 / 106    96  26 / 25, 136 / 106    175  30 / 26, 165 / 113
+//     90 seeds   32 tiles  27 / 26              64  30 / 27, 168 / 124    87  31 / 27, 186 / 121
+//     60 seeds, 32 channels, 64 tiles  26 / 25, 134 / 104    96  28 / 25, 152 / 105    120  29 / 25, 165 / 108
+// The line still is the one against launches: on this side of it up to 14 % is given away where seeds settle and up to half where none ever does.
 bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int compute, int dp) {
     if (n_seeds < 1 || n_seeds > WALK_MAX_SEEDS || n < 1 || m < 1) return false;
     const int64_t blocks = (n_seeds + 31) / 32, tiles = ((n > m ? n : m) + 31) / 32;
@@ -391,9 +398,19 @@ bool walk_applies(int64_t n, int64_t m, int64_t n_seeds, int32_t max_iter, int c
 // and with 32 channels
 //     200 seeds, 1 pair     145 tiles  151 / 190,  43 / 49,  30 / 87    210 tiles  186 / 193,  51 / 49,  34 / 88
 //     256 seeds, 32 pairs   145 tiles  227 / 305,  68 / 75,  50 / 108
-// The sequence has its late iterations in one launch since; on maps that need no prepared copy (which keep it, and save 4 us of that) it takes, settled at once,
-//     200 seeds, 144 tiles  48 / 48    160 seeds, 224 tiles  51 to 58 / 43 to 47    190 seeds, 280 tiles  57 to 64 / 46 to 48
-// so beyond some 200 tiles it would be the better one; the lines are those of seeds that never settle.
+// Those are figures of the sequence in launches.  With its late iterations in one launch it takes the same whatever the number of blocks while they are few, and
+// (groups / sequence, settled at once, live for three and for all ten iterations)
+//     200 seeds, 1 pair     145 tiles  29 / 31,  63 / 76,  130 / 166    224 tiles  32 / 33,  72 / 81,  151 / 176    280 tiles  34 / 34,  79 / 85,  169 / 186
+//     120 seeds, 1 pair     180 tiles  30 / 28,  66 / 62,  138 / 130    224 tiles  31 / 28,  71 / 64,  150 / 135    280 tiles  34 / 29,  78 / 68,  168 / 144
+//     60 seeds, 4 pairs     180 tiles  30 / 27,  67 / 56,  138 / 114    210 tiles  32 / 27,  70 / 56,  148 / 114    280 tiles  34 / 28,  79 / 58,  168 / 119
+//     200 seeds, 4 pairs    145 tiles  29 / 33,  63 / 78,  130 / 169    210 tiles  32 / 34,  71 / 82,  149 / 179    280 tiles  36 / 36,  81 / 89,  170 / 194
+//     256 seeds, 32 pairs   100 tiles  41 / 42,  82 / 96,  157 / 204    145 tiles  46 / 45, 101 / 105, 207 / 225    210 tiles  54 / 51, 128 / 119, 272 / 253
+// and with 32 channels
+//     200 seeds, 1 pair     145 tiles  30 / 31,  71 / 75,  151 / 162    180 tiles  32 / 32,  78 / 78,  170 / 169
+//     60 seeds, 4 pairs     145 tiles  30 / 26,  71 / 54,  151 / 110    180 tiles  32 / 27,  78 / 55,  170 / 113
+//     256 seeds, 32 pairs   100 tiles  41 / 42,  90 / 96,  187 / 202    145 tiles  50 / 48, 120 / 108, 259 / 229
+// So the lines hold for pairs of 200 seeds and more (of many pairs within 8 %, with 32 channels 13 %); with 120 seeds and fewer the sequence is faster well before
+// them, by up to a fifth where seeds settle and up to half where none does.
 // A full chip sweeps a tile at two thirds of the speed of a quarter of it, and more than one workgroup per compute unit would walk
 // in turns.  fp32 products and two-term rows take several times as long per tile.  Past 256 seeds, and on maps that need no prepared
 // copy, the sequence runs as before.
