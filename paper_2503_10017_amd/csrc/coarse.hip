@@ -713,10 +713,12 @@ hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream
     return hipErrorInvalidValue;
 }
 
-// The model behind the choice, in nanoseconds, fitted to calls between 16384 and a million pixels; both ways of 45 drawn calls
-// near the line, inputs not in the caches: those it takes gain 4 to 49 %, those it leaves would have gained 8 % at most (one
-// 512x384 pair of fp16 products, 263 us in one step, 274 in two).  The model knows sizes only: it counts on half of the seeds in the second iteration, and
-// on maps that tell pixels apart (four 512x384 pairs of fp16 products, features of 1 pixel, whose seeds settle at once, 375 / 390; of 16 pixels 612 / 595).
+// The model behind the choice, in nanoseconds, fitted to calls between 16384 and a million pixels before search_unit and coarse_kernel put their products and maxima
+// in turn and the late iterations became one launch.  Both ways of 126 calls near the line with the present kernels, inputs not in the caches: the 56 that it
+// takes lose 2.6 % at worst (two 512x384 pairs of fp16 products whose seeds settle at once, 281 us in one step, 289 in two) and gain up to 63 %; the 70 that it leaves
+// would gain up to 14 % (16 pairs with squared distance 1964 / 1718; 3072 queries of one 640x480 pair 63 / 57, of two 512x384 pairs 73 / 67, of 32 channels 79 / 71; fp32
+// products, 200x150, 131 / 119), and one that it takes for two of its four searches another 27 % in all four (fp32 products, 256x192, 768 seeds, 172 / 136).  The model knows sizes
+// only: it counts on half of the seeds in the second iteration, and on maps that tell pixels apart (three 512x384 pairs, features of 1 pixel 374 / 372, of 4 418 / 413).
 constexpr double BYTES_PER_NS = 4500.0;  // what the passes over the maps reach
 static int coarse_row_bytes(int compute, int dp) { return dp * elem_size(compute); }
 // Cells that a slot is multiplied with again: 4 of 1024 pixels for unit rows of 16 channels and more, however large the map; with few

@@ -235,7 +235,7 @@ double coarse_cells_again(double cells, int d, bool l2);
 bool coarse_votes(int compute, int dp);  // whether the searches of such rows should
 double coarse_cost(int64_t rows, int compute, int dp);
 constexpr double COARSE_LEAST_GAIN = 3000.0;  // of a call
-// See CoarseArgs.even: three cells in seven.  (Of a search of 16-bit rows, 46 ns a block in one step, some 17 of 28 are still to do in 8 bits when the
+// See CoarseArgs.even: three cells in seven.  (Of a search of 16-bit rows, 46 ns a block in one step, some 17 of 26 are still to do in 8 bits when the
 // votes are in, and the second step takes 58 for every block it is left with.)
 constexpr float COARSE_EVEN = 0.75f;
 // Fewer queries per pair than this spread the second step thin: a call with so few runs in one
