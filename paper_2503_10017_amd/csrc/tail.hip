@@ -15,7 +15,12 @@
 //
 // What the workgroups hand each other is read and written with relaxed atomics of device scope only, which pass the caches that are not
 // shared; a workgroup waits until its stores have arrived (s_waitcnt) before it reports.  There is no fence: on this part one writes
-// back an XCD's whole L2.
+// back an XCD's whole L2.  The language does not promise that this is enough; it rests on three properties of gfx950 and its compiler:
+//   - such a load or store is an instruction with the sc1 bit, and such a read-modify-write is performed for the whole device, so each acts where all XCDs see
+//     it (tests/test_kernel_scratch.py looks for the bit in the built kernels: a plain access is one of a map or of a final result);
+//   - s_waitcnt with all counts at 0 returns when the wave's earlier stores and read-modify-writes have acted, and the compiler moves no access over the
+//     empty asm statements on either side of it;
+//   - a wave issues its loads in the order of the program, and none ahead of the s_barrier behind which its workgroup's word has been seen.
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
 #include "search_unit.hpp"

@@ -10,6 +10,7 @@ import pytest
 import paper_2503_10017_amd as fnn
 
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
 
 def scratch_bytes(tmp_path):
@@ -17,11 +18,10 @@ def scratch_bytes(tmp_path):
     return {name: scratch for name, (scratch, _) in kernel_notes(tmp_path).items()}
 
 
-def kernel_notes(tmp_path):
-    """Kernel name -> (bytes of scratch memory per lane, vector registers), over every gfx950 code object in the library."""
+def code_objects(tmp_path):
+    """Every gfx950 code object in the library, each as a file."""
     with open(fnn.library_path(), "rb") as f:
         image = f.read()
-    found = {}
     for bundle in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", image):
         at = bundle.end()
         count, = struct.unpack_from("<Q", image, at)
@@ -34,9 +34,16 @@ def kernel_notes(tmp_path):
                 continue
             path = tmp_path / "code.o"
             path.write_bytes(image[bundle.start() + offset:bundle.start() + offset + size])
-            notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
-            for name, scratch, rest in re.findall(r"\.name:\s+(_Z\S+)\n\s+\.private_segment_fixed_size: (\d+)\n((?:\s+\.(?!name:|args:).*\n)*)", notes):
-                found[name] = int(scratch), int(re.search(r"\.vgpr_count:\s+(\d+)", rest).group(1))
+            yield str(path)
+
+
+def kernel_notes(tmp_path):
+    """Kernel name -> (bytes of scratch memory per lane, vector registers)."""
+    found = {}
+    for path in code_objects(tmp_path):
+        notes = subprocess.run([READELF, "--notes", path], capture_output=True, text=True, check=True).stdout
+        for name, scratch, rest in re.findall(r"\.name:\s+(_Z\S+)\n\s+\.private_segment_fixed_size: (\d+)\n((?:\s+\.(?!name:|args:).*\n)*)", notes):
+            found[name] = int(scratch), int(re.search(r"\.vgpr_count:\s+(\d+)", rest).group(1))
     return found
 
 
@@ -84,3 +91,22 @@ def test_workgroups_that_the_choice_between_whole_and_half_segments_counts_on(tm
             seen.add(int(of.group(1)))
             assert 256 * (512 // (-(-registers // 8) * 8)) == said[int(of.group(1))], (name, registers)
     assert seen == set(said)
+
+
+def test_what_workgroups_hand_each_other_passes_the_caches_of_their_xcds(tmp_path):
+    """The late iterations' shared words are read and written by instructions with the sc1 bit; what has none is a fragment of a map (16 bytes, or 16 and 8) or one
+    of the three results, in the two places that write them."""
+    kernels = 0
+    for path in code_objects(tmp_path):
+        with open(path, "rb") as f:
+            if b"recip_tail_kernel" not in f.read():
+                continue
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", path], capture_output=True, text=True, check=True).stdout
+        for name, body in re.findall(r"<(_ZN3fnn\d+recip_tail_kernel\w+)>:\n(.*?)(?=\n\n|\Z)", text, re.S):
+            kernels += 1
+            plain = [op for op, rest in re.findall(r"^\s+((?:global|flat|buffer)_(?:load|store)\w*)\s+(.*)$", body, re.M) if "sc1" not in rest]
+            assert {op for op in plain if "load" in op} <= {"global_load_dwordx4", "global_load_dwordx2"}, name
+            eight = plain.count("global_load_dwordx2")
+            assert eight == (plain.count("global_load_dwordx4") if re.search(r"ILi[12]ELi24E", name) else 0), name
+            assert [op for op in plain if "store" in op] == ["global_store_dword"] * 6, name
+    assert kernels == 14
