@@ -59,6 +59,7 @@ def same(a, b, compute, **kw):
     (400001, 390000, 1, "f32", "f32", 16, {"l2": True}),
     (66000, 65600, 1, "f16", "f32", 24, {"split": True}),
     (66000, 71000, 1, "f16", "f32", 11, {"split": True}),
+    (300801, 310777, 1, "f16", "f32", 24, {"split": True}),     # segments of 4096 pixels that the quantise launch prepares, a wave's rows past the map
     (200000, 200001, 2, "f16", "f32", 9, {"split": True}),
     (90000, 404000, 1, "f16", "f32", 24, {"normalize": True}),  # wide cells
     (404123, 17000, 2, "f32", "f32", 24, {}),
