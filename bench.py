@@ -222,6 +222,14 @@ def main() -> int:
             "queries": k_act, "us": round(us, 1), "bytes": by, "TFLOP/s": round(fl / us / 1e6, 1), "GB/s": round(by / us / 1e3, 1),
             "bound": "mfma" if t_mfma >= t_hbm else "hbm", "frac_of_bound": round(max(t_mfma, t_hbm) / us, 3)})
 
+    # the searches of the late iterations, all in one launch: each that finds a live seed streams every pair's map once more
+    late_ms = by_kernel.get("recip_tail_kernel", [])
+    late_us = sum(late_ms) / args.steps * 1e3
+    late_live = [int(k) for k in per_search[lps:] if k > 0]
+    late_bytes = len(late_live) * BATCH * N_PIX * D * esize + sum(late_live) * (D * esize + 8)
+    all_flops = 2.0 * D * N_PIX * int(per_search.sum())
+    all_us = sum(search_ms) / args.steps * 1e3 + late_us
+
     hbm_rows = [r for r in per_search_rows if r["bound"] == "hbm"]
     hbm_bytes = sum(r["bytes"] for r in hbm_rows)
     hbm_us = sum(r["us"] for r in hbm_rows)
@@ -271,6 +279,15 @@ def main() -> int:
             "us_per_step": round(hbm_us, 1),
             "note": "sum of algorithmic bytes / sum of durations over the search launches of a step whose bound is HBM "
                     "(few live queries: streaming the candidate maps takes longer than the matrix work at peak)",
+        },
+        "late_iterations": {
+            "kernel": "recip_tail_kernel", "us_per_step": round(late_us, 1), "live_searches": len(late_live), "queries": sum(late_live),
+            "bound": "hbm", "bytes_per_step": late_bytes, "GB/s": round(late_bytes / late_us / 1e3, 1) if late_us > 0 else 0.0,
+            "frac_of_hbm": round(late_bytes / late_us / 1e3 / PEAK_HBM, 4) if late_us > 0 else 0.0,
+            "all_searches_frac_of_mfma": round(all_flops / all_us / 1e6 / peak, 4) if all_us > 0 else 0.0,
+            "note": "searches of a few live seeds, which stream the maps, and the barriers that their workgroups meet at.  "
+                    "all_searches_frac_of_mfma sets the flops of every search of a step against the time of the search launches and of this one, "
+                    "the figure that `roofline` has for the search launches alone",
         },
         "input_generation_s": round(gen_s, 1),
     }
