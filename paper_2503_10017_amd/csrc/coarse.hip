@@ -293,6 +293,8 @@ __device__ __forceinline__ bool gives_up(const SearchVote& v, float even) { retu
 // in two without this / with it, fp16, 24 channels, 512x384: 16 pairs of 3072 seeds, rank 4 1663 / 2651 / 2059, one descriptor throughout 1466 / 2641 /
 // 1872, features of 4 pixels 1615 / 1474 / 1420; the seeds' one search, rank 4 461 / 802 / 723, features of 4 pixels 468 / 445 / 433; every
 // pixel of one pair, rank 4 1654 / 2670 / 1973.
+// (Those were taken before products and maxima came in turn.  In one step / with votes since, image 2 a permutation of image 1: 16 pairs of 3072 seeds, rank 4 1113 / 1411, one
+// descriptor throughout 1433 / 1802, full rank 992 / 817; the seeds' one search 493 / 683, 382 / 564 and 494 / 407; every pixel of one pair 1671 / 1946, 1280 / 1528 and 1653 / 995.)
 constexpr int VOTE_CELLS = 4;  // shortest chunk that is worth it
 constexpr int VOTERS = 64;     // of a pair, about; a quarter of them may decide
 
