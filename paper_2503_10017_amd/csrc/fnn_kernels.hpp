@@ -359,6 +359,7 @@ struct TailArgs {
     TailControl* control;
     int32_t t0, max_iter;            // t0 < max_iter <= TAIL_MOST_ITERATIONS
     uint64_t most_polls;             // looks at a word before a wait is given up
+    uint32_t few_wgs;                // workgroups of a pair that go on when few seeds are left, at most
     int32_t* seed_i;
     int32_t* seed_j;
     int32_t* seed_iter;

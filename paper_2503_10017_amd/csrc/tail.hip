@@ -209,7 +209,9 @@ void recip_tail_kernel(TailArgs ta) {
     const int b = blockIdx.y;
     const int64_t base = (int64_t)b * ta.n_seeds;
     const uint32_t n_first = (uint32_t)min(max(ta.n_active[b], 0), ta.n_seeds);
-    if (n_first == 0) return;
+    // (beside a thousand seeds and fewer the others would cost the barriers more than they take off the searches: one 640x480 pair 371 -> 376 us)
+    const uint32_t most = n_first <= 2 * (uint32_t)TAIL_FEW ? ta.few_wgs : gridDim.x;
+    if (n_first == 0 || blockIdx.x >= most) return;
     TailControl& ctl = ta.control[b];
     const char* p1 = ta.p1 + (int64_t)b * ta.bstride1;
     const char* p2 = ta.p2 + (int64_t)b * ta.bstride2;
@@ -226,12 +228,12 @@ void recip_tail_kernel(TailArgs ta) {
         if (id == 0) {
             // the first to come opens the first search; it gives the others a few microseconds to appear, and some more while they are few
             uint32_t takers = 1;
-            for (int i = 0; i < 64 && (takers < gridDim.x / 4 || (i < 8 && takers < gridDim.x)); ++i) {
+            for (int i = 0; i < 64 && (takers < most / 4 || (i < 8 && takers < most)); ++i) {
                 uint32_t seen = 0;
                 if (lane == 0) seen = shared_load(&ctl.registered);
                 takers = __builtin_amdgcn_readfirstlane(seen);
             }
-            publish(Phase::pack(0, min(max(takers, 1u), gridDim.x), n_first));
+            publish(Phase::pack(0, min(max(takers, 1u), most), n_first));
         }
     }
     __syncthreads();
@@ -343,9 +345,10 @@ void recip_tail_kernel(TailArgs ta) {
                     if (kind == 3) live_next = shared_load(&ctl.moving);
                     if (kind & 1) takers_next = shared_load(&ctl.registered);  // a search is dealt to all that are there, and resolved by the same
                 }
-                takers_next = min((uint32_t)__builtin_amdgcn_readfirstlane(takers_next), gridDim.x);
+                takers_next = min((uint32_t)__builtin_amdgcn_readfirstlane(takers_next), most);
                 live_next = __builtin_amdgcn_readfirstlane(live_next);
                 if (kind == 3 && t + 1 >= ta.max_iter) live_next = 0;
+                if (kind == 3 && live_next <= (uint32_t)TAIL_FEW) takers_next = min(takers_next, ta.few_wgs);
                 stores_arrived();
                 if (lane < TAIL_COPIES) shared_store(&ctl.arrived[lane].count, 0u);
                 if (lane == 0) shared_store(&ctl.groups_arrived, 0u);
@@ -442,16 +445,15 @@ void recip_tail_kernel(TailArgs ta) {
     }
 }
 
-// Workgroups per pair: one for every compute unit, dealt to the pairs, but few enough that a wave has six tiles of a map, or three
+// Workgroups per pair: one for every compute unit, dealt to the pairs.  When few seeds are left no more go on than leave a wave six tiles of a map, or three
 // dearer ones: every workgroup more makes the barriers longer, and the keys that a query's slot has to take one after the other.  Whole calls of one pair
 // with 32 / 64 / 128 / 256 workgroups: 160x120 79 / 80 / 83 / 91 us, 256x192 89 / 87 / 90 / 97, 320x240 104 / 101 / 101 / 108, 512x384 238 / 214 / 203 / 209, its
 // two-term rows 368 / 308 / 285 / 291, fp32 products 251 / 207 / 188 / 185, 1024x768 1494 / 1274 / 1168 / 1130.
-static int tail_wgs_per_pair(const TailArgs& a, int batch, int compute, int dp) {
+static int tail_wgs_per_pair(int batch) { return TAIL_MOST_WGS / batch < 1 ? 1 : TAIL_MOST_WGS / batch; }
+static int tail_few_wgs_per_pair(const TailArgs& a, int batch, int compute, int dp) {
     const int tiles = ((a.n > a.m ? a.n : a.m) + 31) / 32, per_wg = compute == FNN_F32 || dp > 32 ? 24 : 48;
-    int wgs = TAIL_MOST_WGS / batch;
-    const int enough = tiles / per_wg > 32 ? tiles / per_wg : 32;
-    if (wgs > enough) wgs = enough;
-    return wgs < 1 ? 1 : wgs;
+    const int enough = tiles / per_wg > 32 ? tiles / per_wg : 32, wgs = tail_wgs_per_pair(batch);
+    return wgs < enough ? wgs : enough;
 }
 
 // Groups of query blocks per wave while many seeds move: four would leave the named search no registers, and two of rows of 96 bytes spill 17 of them (fp32 products
@@ -461,8 +463,9 @@ template <int CT, int DP>
 constexpr int tail_groups() { return Ops<CT, DP>::ROW_BYTES > 64 ? 1 : (search_g_limit<CT, DP>() > 2 ? 2 : search_g_limit<CT, DP>()); }
 
 template <int CT, int DP>
-static hipError_t launch_tail_t(const TailArgs& a, int batch, hipStream_t s) {
-    return launch(TK_RECIP_TAIL, recip_tail_kernel<CT, DP, tail_groups<CT, DP>()>, dim3(tail_wgs_per_pair(a, batch, CT, DP), batch), dim3(TAIL_THREADS), 0, s, a);
+static hipError_t launch_tail_t(TailArgs a, int batch, hipStream_t s) {
+    a.few_wgs = tail_few_wgs_per_pair(a, batch, CT, DP);
+    return launch(TK_RECIP_TAIL, recip_tail_kernel<CT, DP, tail_groups<CT, DP>()>, dim3(tail_wgs_per_pair(batch), batch), dim3(TAIL_THREADS), 0, s, a);
 }
 hipError_t launch_tail(const TailArgs& a, int batch, int compute, int dp, hipStream_t s) {
     if (compute == FNN_F16) {
