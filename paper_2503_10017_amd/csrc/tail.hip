@@ -150,8 +150,8 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
             }
         }
     }
-    // Where no score was more than minus infinity, the last tile of the map stands for them all.  (Kept in the loop, in each of the ring's places, that is a
-    // fifth of the kernel's code, and a call on other inputs 10 us longer.)
+    // Where no score was more than minus infinity, the last tile of the map stands for them all.  (Kept in the loop, in each of the ring's places, that makes the
+    // kernel 63 KB of code instead of 55.)
     if (t1 > last) {  // uniform
         bool none = false;
 #pragma unroll
