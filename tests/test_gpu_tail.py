@@ -48,6 +48,7 @@ def run(a, b, seeds, max_iter, compute, tail, **kw):
     (1, 9001, 9333, 513, "f16", 24, 10, None),    # one more: from the third on
     (3, 16400, 12345, 5000, "f16", 24, 10, None),  # many seeds, then few
     (2, 9001, 9333, 8192, "f16", 24, 6, None),    # from the fourth iteration on
+    (1, 30000, 20011, 4000, "f16", 24, 10, None),  # 256 workgroups while many seeds move, 32 for few
     (40, 2100, 1999, 700, "f16", 24, 10, None),   # six workgroups per pair
     (64, 1000, 777, 300, "f16", 24, 7, None),     # four
     (1, 9001, 9333, 600, "f16", 16, 10, None),
