@@ -367,12 +367,12 @@ struct TailArgs {
 hipError_t launch_tail(const TailArgs& a, int batch, int compute, int dp, hipStream_t s);
 // A wait of recip_tail_kernel lasts one phase at most: a search of all seeds that are left, or its resolve pass, by the workgroups that take part, which
 // may be a single one (the others came later, and wait until it is done).  A workgroup alone takes 0.2 us at most for a block of 32x32 scores (the dearest
-// products, of 32 fp32 channels, 600 ns of one of its four SIMDs; fewer bytes than that has time to load) and 2 us for a query of the resolve pass; a look takes at least
-// 0.2 us.  Sixteen times that, and never less than 2^26 looks: a wait that is longer means that two calls share a workspace unordered and
-// have overwritten each other's words.
+// products, of 32 fp32 channels, 600 ns of one of its four SIMDs; fewer bytes than that has time to load) and 2 us for a query of the resolve pass; a look takes 0.13 us (at one
+// word, by 1, 16 and 256 workgroups).  Twenty times that, and never less than 2^26 looks (9 s): a wait that is longer means that two calls share a workspace
+// unordered and have overwritten each other's words.
 inline uint64_t tail_most_polls(int64_t n, int64_t m, int64_t n_seeds) {
     const uint64_t tiles = (uint64_t)((n > m ? n : m) + 31) / 32, blocks = (uint64_t)((n_seeds + 31) / 32) * tiles;
-    return ((uint64_t)1 << 26) + 16 * blocks + 160 * (uint64_t)n_seeds;
+    return ((uint64_t)1 << 26) + 32 * blocks + 320 * (uint64_t)n_seeds;
 }
 
 // ---- dense mutual nearest neighbours -----------------------------------------------------
