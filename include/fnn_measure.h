@@ -23,7 +23,7 @@ extern "C" {
  * four 32-query blocks a wave keeps resident, plus 100 when the kernel that stages the candidate
  * tiles through LDS ran; for the 8-bit step of a search in two steps the number of 32-query blocks a wave
  * keeps resident; for the dense pass-1 kernel 1 when the variant that stages the query
- * blocks through LDS ran, 2 when it scored in 8 bits; 0 otherwise) to HOST
+ * blocks through LDS ran, 2 when it scored in 8 bits, 3 when it did and kept one maximum for three candidates; 0 otherwise) to HOST
  * arrays and closes the trace.  The trace is process-wide state and not thread-safe, and must
  * not be open during HIP graph capture.
  */

@@ -220,7 +220,7 @@ struct DenseCoarseLayout {
     int64_t sample_words;  // 32-bit words that start at 0, from args.sample_lower on
     char* swept;   // image 1 of a group as the dense kernels read it
 };
-DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m, const MapsLayout& maps) {
+DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m, const MapsLayout& maps, int compute) {
     DenseCoarseLayout L;
     memset(&L, 0, sizeof(L));
     DenseCoarseArgs& a = L.args;
@@ -229,12 +229,17 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     a.map[1] = carve_coarse_map(cv, batch, round_up(m, DENSE_SB_PIXELS), a.seg_pixels);
     a.n_tiles[0] = (int32_t)((n + 31) / 32);
     a.n_tiles[1] = (int32_t)((m + 31) / 32);
-    a.cell_groups = dense_cell_groups(n, m);
-    a.n_cells = (int32_t)((m + 512 * a.cell_groups - 1) / (512 * a.cell_groups));
+    a.cell_runs = dense_cell_runs(n, m);
+    a.grouped = dense_grouped(n, compute, maps.dp) ? 1 : 0;
+    const int64_t cell = DENSE_CELL_PIXELS * a.cell_runs, col_cell = a.seg_pixels >> a.grouped;
+    a.n_cells = (int32_t)((m + cell - 1) / cell);
+    a.n_col_cells = (int32_t)((n + col_cell - 1) / col_cell);
     // Tables of scores: the candidates' of as many pairs at a time as 512 MB hold (all of a pair's), their queries' a run of 128 MB at a time.  (Groups
     // of four 512x384 pairs instead of eight cost 1 %.)
-    const size_t pixels2 = (size_t)a.map[1].n_segs * a.seg_pixels, cols = a.map[0].n_segs * pixels2 * sizeof(uint16_t);
-    const int64_t together = cols > 0 && cols < ((size_t)512 << 20) ? (int64_t)(((size_t)512 << 20) / cols) : 1;
+    const size_t pixels2 = (size_t)a.map[1].n_segs * a.seg_pixels, col_cells = (size_t)a.map[0].n_segs << a.grouped;
+    const size_t cols = col_cells * (a.grouped ? pixels2 / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS : pixels2) * sizeof(uint16_t);
+    const size_t scores = a.map[0].n_segs * pixels2 * sizeof(uint16_t);  // one for every candidate and segment
+    const int64_t together = scores > 0 && scores < ((size_t)512 << 20) ? (int64_t)(((size_t)512 << 20) / scores) : 1;
     const int64_t groups = (batch + together - 1) / together;
     L.group = (int32_t)((batch + groups - 1) / groups);
     const int64_t per_sb = L.group * a.n_cells * (int64_t)DENSE_SB_PIXELS * (int64_t)sizeof(uint16_t);
@@ -246,12 +251,13 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     a.best[0] = (uint16_t*)cv.take((size_t)per_sb * L.slab);
     a.best[1] = (uint16_t*)cv.take((size_t)L.group * cols);
     a.mask[0] = (uint64_t*)cv.take((size_t)per_sb * L.slab / 16);
-    a.mask[1] = (uint64_t*)cv.take((size_t)L.group * cols / 16);
+    a.mask[1] = (uint64_t*)cv.take((size_t)L.group * col_cells * pixels2 / 8);
+    if (a.grouped) a.least = (float*)cv.take((size_t)L.group * (pixels2 / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS) * sizeof(float));
     L.swept = (char*)cv.take((size_t)L.group * maps.bstride1);
     a.pixels[0] = n;
     a.pixels[1] = m;
     a.sample_upper[0] = (float*)cv.take((size_t)batch * a.n_cells * DENSE_SAMPLES * sizeof(float));
-    a.sample_upper[1] = (float*)cv.take((size_t)batch * a.map[0].n_segs * DENSE_SAMPLES * sizeof(float));
+    a.sample_upper[1] = (float*)cv.take((size_t)batch * a.n_col_cells * DENSE_SAMPLES * sizeof(float));
     const size_t zeros = cv.used;
     a.sample_lower = (uint32_t*)cv.take((size_t)batch * 2 * DENSE_SAMPLES * sizeof(uint32_t));
     a.marked = (int32_t*)cv.take((size_t)batch * 2 * sizeof(int32_t));
@@ -436,24 +442,30 @@ hipError_t dense_group(const DenseCoarseLayout& C, const DenseLayout& L, const S
         da.n_sb = C.n_sb - sb < C.slab ? C.n_sb - sb : C.slab;
         da.swept = sb == 0 ? swept : none;
         e = launch_dense_coarse(da, pairs, s);
-        if (e == hipSuccess) e = launch_dense_select(da, 0, at_once ? 2 : 1, pairs, s);
+        if (e == hipSuccess) e = launch_dense_select(da, 0, at_once ? 2 : 1, nullptr, pairs, s);
         ca.mask = da.mask[0];
         ca.slab = da.n_sb * DENSE_SB_PIXELS;
         ca.n_cells = da.n_cells;
-        ca.cell_shift = da.cell_groups == 8 ? 2 : (da.cell_groups == 4 ? 1 : 0);
+        ca.cell_shift = da.cell_runs == 4 ? 2 : (da.cell_runs == 2 ? 1 : 0);
         ca.first_slot = sb * DENSE_SB_PIXELS;
         ca.side = 0;
         if (e == hipSuccess) e = launch_refine(rows, ca, pairs, compute, L.maps.dp, s);
         if (e != hipSuccess) return e;
     }
-    if (!at_once) e = launch_dense_select(da, 1, 1, pairs, s);
+    if (!at_once) e = launch_dense_select(da, 1, 1, nullptr, pairs, s);
     ca.mask = da.mask[1];
     ca.slab = da.map[1].n_segs * da.seg_pixels;
-    ca.n_cells = da.map[0].n_segs;
-    ca.cell_shift = da.seg_pixels == 4096 ? 2 : 1;
+    ca.n_cells = da.map[0].n_segs << da.grouped;
+    ca.cell_shift = (da.seg_pixels == 4096 ? 2 : 1) - da.grouped;
+    ca.grouped = da.grouped;
     ca.first_slot = 0;
     ca.side = 1;
     if (e == hipSuccess) e = launch_refine(cols, ca, pairs, compute, L.maps.dp, s);
+    if (da.grouped) {
+        if (e == hipSuccess) e = launch_dense_select(da, 1, 1, cols.out_keys, pairs, s);
+        ca.range = 1;
+        if (e == hipSuccess) e = launch_refine(cols, ca, pairs, compute, L.maps.dp, s);
+    }
     sweep.d1 = C.swept;
     if (e == hipSuccess) e = launch_dense_pass1(sweep, pairs, compute, L.maps.dp, s);
     return e;
@@ -487,10 +499,10 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
 
     DenseCoarseArgs da = C.args;
     hipError_t e = launch_dense_sample(da, batch, s);
-    const double limit = dense_coarse_limit(compute, L.maps.dp) * DENSE_SAMPLES;
+    const double limit = dense_coarse_limit(n, compute, L.maps.dp) * DENSE_SAMPLES;
     da.judge.marked = da.marked;
     da.judge.weight[0] = (float)(1.0 / (limit * da.n_cells));
-    da.judge.weight[1] = (float)(1.0 / (limit * da.map[0].n_segs));
+    da.judge.weight[1] = (float)(1.0 / (limit * da.n_col_cells));
     // a launch that leaves every pair alone costs its workgroups' start: no more of them than fill the chip a few times
     auto wgs = [&]() { return (int64_t)C.group * sweep.n_sb * ((sweep.m_tiles + DENSE_TILES_PER_GROUP * sweep.groups_per_wg - 1) / (DENSE_TILES_PER_GROUP * sweep.groups_per_wg)); };
     while (wgs() > 4096) sweep.groups_per_wg *= 2;
@@ -603,7 +615,7 @@ size_t fnn_workspace_bytes_opts(int32_t batch, int64_t n, int64_t m, int32_t d, 
         Carver cv{nullptr, 0};
         const DenseLayout D = carve_dense(cv, batch, n, m, de, compute);
         if (n <= MAX_DENSE_PIXELS && m <= MAX_DENSE_PIXELS && dense_coarse_gain(n, m, batch, compute, dp, d, l2) > 0.0)
-            carve_dense_coarse(cv, batch, n, m, D.maps);
+            carve_dense_coarse(cv, batch, n, m, D.maps, compute);
         if (cv.used > most) most = cv.used;
     }
     return most + WS_ALIGN;
@@ -1146,7 +1158,7 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
     da.groups_per_wg = (int32_t)groups_per_wg;
 
     // Large maps: 8-bit scores first, then, where the workspace has the room, the second step of the searches in both directions
-    DenseCoarseLayout C = carve_dense_coarse(cv, batch, n, m, L.maps);
+    DenseCoarseLayout C = carve_dense_coarse(cv, batch, n, m, L.maps, opts->compute);
     if (cv.used <= workspace_bytes && dense_coarse_gain(n, m, batch, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0) > 0.0) {
         const bool raw = raw_quantise(batch, d1, d2, opts);
         if (!raw) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra));

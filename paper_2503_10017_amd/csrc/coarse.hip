@@ -29,7 +29,6 @@ namespace fnn {
 
 // ---- the 8-bit maps ------------------------------------------------------------------------------
 constexpr float ROUNDING = 2e-5f;          // of a row's length, on top of its remainder
-constexpr float UNBOUNDED = 1e18f;         // the "bound" of a row that has none; its square is still a number
 constexpr float LEAST_SQUARE = 1e-30f;     // |x|^2 of a row that the bounds hold for
 constexpr float LARGEST_SQUARE = 1e30f;
 // fp16 values below 2^-14 may count as 0 in the matrix instructions.  Where a step of the scale is wider than twice
@@ -535,6 +534,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     if (VOTES) every = every || (ca.vote && ca.vote[b].given_up) || (ca.earlier && gives_up(ca.earlier[b], ca.even));
     uint32_t again = 0;
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
+    if (MASK && ca.grouped) n_act = min((n_act + DENSE_CELL_PIXELS - 1) & ~(DENSE_CELL_PIXELS - 1), ca.slab);  // bits that stand for no candidate are 0
     int range = ca.range;
     if (MASK && range < REFINE_MOST && ca.judge.marked[2 * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
     const int begin = blockIdx.y * range;
@@ -590,7 +590,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
                         if (up >= unorder_bits(lw)) need |= 1u << i;
                     }
                 }
-                if (n_act - slot < PER) need &= (1u << (n_act - slot)) - 1;
+                if (!(MASK && ca.grouped) && n_act - slot < PER) need &= (1u << (n_act - slot)) - 1;
             }
             // a prefix sum over the wave, one LDS atomic for its total
             const int mine = __popc(need);
@@ -605,7 +605,8 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
             if (lane == 0 && count) at = atomicAdd(&n_list, count);
             at = __shfl(at, 0) + upto - mine;
             for (; need; need &= need - 1, ++at) {
-                const int found = slot + __builtin_ctz(need);
+                int found = slot + __builtin_ctz(need);
+                if (MASK && ca.grouped) found = (found & ~(DENSE_CELL_PIXELS - 1)) + mask_candidate(found & (DENSE_CELL_PIXELS - 1));
                 list_slot[at] = (uint16_t)(found - begin);
                 list_row[at] = (int)query_row(a, qbase, found);
             }
@@ -825,8 +826,9 @@ static hipError_t launch_refine_t(const SearchArgs& a, CoarseArgs ca, int batch,
     // pixels, both launches with ranges of 16384 / 4096: 1104 / 548 us); but each reads its tiles again and fills up its last block, so they are taken
     // while the workgroups are few and where the samples say that the lists are long (features of one pixel, four pairs: 324 / 365 us; 1024x768
     // 1085 / 1662).  Rows that cost more per product lose more to the last block of a list than they gain (fp32, 384x288, features of one pixel 356 / 794).
+    const bool short_lists = ca.range != 0;
     ca.range = REFINE_MOST;
-    if (MASK && CT != CT_F32 && DP <= 32)
+    if (MASK && CT != CT_F32 && DP <= 32 && !short_lists)
         for (ca.range = REFINE_SCAN; ca.range < REFINE_MOST && cells * ((slots + ca.range - 1) / ca.range) * batch > 16384;) ca.range *= 2;
     const unsigned ranges = (unsigned)((slots + ca.range - 1) / ca.range);
     return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES, MASK>, dim3(cells, ranges, batch), dim3(64 * WAVES), 0, s, a, ca);

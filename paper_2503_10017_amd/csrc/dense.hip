@@ -733,7 +733,8 @@ void dense_resolve_rows_kernel(ResolveSide a) {
                 if (x[jt][v] == top) row = jt * 32 + tile_row(v, h);
         row = min(row, __shfl_xor(row, 32));
         if (h == 0 && i >= 0 && i < a.n) {
-            a.idx[(int64_t)b * a.n + i] = row < J * 32 ? tbase * 32 + row : -1;
+            // (no score above minus infinity: the last unit, whose padding equals it)
+            a.idx[(int64_t)b * a.n + i] = row < J * 32 && tbase * 32 + row < a.m ? tbase * 32 + row : -1;
             if (a.score) a.score[(int64_t)b * a.n + i] = top;
         }
     }

@@ -1,8 +1,14 @@
 // Pass 1 of the dense mode in 8-bit integers: the same sweep as dense_kernel -- every 32x32 block of scores formed once and
 // folded into the best candidate of its queries and the best query of its candidates -- with one matrix
 // instruction per block, nothing located and nothing masked (rows past a map repeat its last one).  What is kept are the
-// maxima per query and cell of candidates and per candidate and segment of queries; bounds on what the 8 bits left out say
+// maxima per query and cell of candidates, and per candidate, or GROUP of three candidates, and cell of queries; bounds on what the 8 bits left out say
 // which cells the second step of the searches (coarse.hip) has to multiply again, in both directions.
+//
+// Why groups.  The sweep is bound by its vector maxima.  A maximum of every candidate and one of every query take 16 three-input maxima per block; with
+// the maxima of three candidates formed first (5, and one candidate is left over), six values go on into the queries' maximum (3) and six into the
+// candidates' (3): 11.  A group's maximum bounds each of its candidates from above, but says of none of them how good its best is at
+// least.  That comes from the products themselves: the GROUP_TOP cells with the group's largest bounds are multiplied first, and what a
+// candidate scored there rules out cells in a second round (of 192 cells, 1 to 5 are left; with bounds of its own a candidate needs 2 to 3.3 in all).
 #include <type_traits>
 
 #include "coarse_device.hpp"
@@ -12,8 +18,7 @@
 
 namespace fnn {
 
-constexpr int DC_J = 4;                                  // candidate tiles resident per wave
-constexpr int DC_GROUP = COARSE_WAVES * DC_J;            // tiles of a workgroup: 512 candidates
+constexpr int CELL_TILES = DENSE_CELL_PIXELS / 32;
 constexpr int DC_TURNS = DENSE_SB_PIXELS / 32 / COARSE_TURN;  // turns of a sweep
 constexpr int DC_STEPS = COARSE_TURN / 2;                // steps of a turn, two query blocks each
 static_assert(DC_TURNS % 2 == 0, "a sweep is an even number of turns, so it starts on stage slot 0");
@@ -49,6 +54,18 @@ __device__ __forceinline__ int transpose_max16_int(const int (&x)[16], int lane)
     return max((int)sw[0], (int)sw[1]);
 }
 
+// The 16 scores of a lane's candidates become six groups: registers 3k, 3k+1, 3k+2, and the last one alone.  Of the DENSE_CELL_PIXELS candidates
+// that a workgroup holds, the 320 triples lie side by side in the table, and then the 64 single ones.
+constexpr int GROUPS = 6;  // of a tile's half
+constexpr int CELL_TRIPLES = CELL_TILES * 2 * (GROUPS - 1);
+static_assert(CELL_TRIPLES + CELL_TILES * 2 == DENSE_CELL_GROUPS && CELL_TRIPLES % 64 == 0, "groups are taken 64 at a time");
+__device__ __forceinline__ void group_maxima(const i32x16& x, int (&g)[GROUPS]) {
+#pragma unroll
+    for (int k = 0; k < GROUPS - 1; ++k) g[k] = max3i(x[3 * k], x[3 * k + 1], x[3 * k + 2]);
+    g[GROUPS - 1] = x[15];
+}
+__device__ __forceinline__ int group_entry(int tile, int h, int k) { return k < GROUPS - 1 ? (tile * 2 + h) * (GROUPS - 1) + k : CELL_TRIPLES + tile * 2 + h; }
+
 // The prepared rows of image 1 of a pair, in the order that the dense kernels sweep: a thread of a two-dimensional grid copies 16 bytes at a time.
 __device__ __forceinline__ void dense_permute(const DenseSwept& w, int b) {
     const uint4* from = reinterpret_cast<const uint4*>(w.from + (int64_t)b * w.from_bstride);
@@ -59,32 +76,40 @@ __device__ __forceinline__ void dense_permute(const DenseSwept& w, int b) {
         to[i] = from[slot_pixel(i / words) * words + i % words];
 }
 
-// A workgroup sweeps one run of queries past a few cells of candidates, a group of 16 tiles after the other.  At the end of every
-// SEGMENT of queries the candidates' maxima are reduced over the lanes and kept.
-// Bound by the vector unit: 16 three-input maxima per block, 16.8 instructions in all, that is 67 cycles beside 32 of the
-// matrix instruction.  A bare loop of them takes 35.7 ns per block and SIMD, the kernel 38 to 40 (dense_staged_kernel 56).
-template <int SEGMENT>
-__global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(3)))
-void dense_coarse_kernel(DenseCoarseArgs a) {
+// A workgroup sweeps one run of queries past a few cells of candidates.  At the end of every cell of queries the candidates' maxima, or those of
+// their groups, are reduced over the lanes and kept.
+// Bound by the vector unit: in groups 11 three-input maxima per block, 11.8 instructions in all, 47 cycles beside 32 of the matrix instruction, at the clock that the power
+// limit leaves.  A product is followed by the maxima of the one before it, as in coarse_kernel.  One 512x384 pair / a third of 1024x768: a maximum for every candidate
+// (16 per block; 35.7 ns per block and SIMD in a bare loop, here 43) 1601 / 7745 us, groups of three 1281 / 6340, with the order of products and maxima 1207 / 6240, with eight
+// resident tiles instead of four 1154 / 5950 (31 ns).  Larger groups, in the compiler's order and with four tiles: of five 1212 / 6040, of a whole half tile 1125 / 5785; but of 192
+// cells groups of five leave 25 to multiply again, half tiles 60.  Without groups the order of products and maxima and more tiles have no registers and gain nothing.
+template <int SEGMENT, bool GROUPED>
+__device__ __forceinline__ void dense_sweep(const DenseCoarseArgs& a) {
+    constexpr int DC_J = GROUPED ? 8 : 4;          // candidate tiles resident per wave
+    constexpr int DC_GROUP = COARSE_WAVES * DC_J;  // tiles of a workgroup
+    constexpr int DC_KEPT = GROUPED ? GROUPS : 16; // maxima of a tile that a lane keeps
+    constexpr int CELL_GROUPS = CELL_TILES / DC_GROUP;
+    static_assert(CELL_GROUPS * DC_GROUP == CELL_TILES, "a cell is whole groups of tiles");
     __shared__ uint4 stage0[COARSE_TURN][64], stage1[COARSE_TURN][64];  // two variables, see dense_staged_kernel
     __shared__ int row_best[DENSE_SB_PIXELS];                           // best score of every query in the cell
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int held = held_register(lane);
     const int cell0 = blockIdx.x * a.cells_per_wg, sb = blockIdx.y, b = blockIdx.z;
     if (a.judge.alike(b)) {
         if (a.swept.to) dense_permute(a.swept, b);
         return;
     }
-    constexpr int SEGS = DENSE_SB_PIXELS / SEGMENT, SEG_TURNS = DC_TURNS / SEGS;
+    constexpr int COL_CELL = GROUPED ? SEGMENT / 2 : SEGMENT, COL_CELLS = DENSE_SB_PIXELS / COL_CELL, COL_TURNS = DC_TURNS / COL_CELLS;
+    static_assert(COL_TURNS % 2 == 0, "a cell starts on stage slot 0");
     const int64_t pixels1 = (int64_t)a.map[0].n_segs * SEGMENT, pixels2 = (int64_t)a.map[1].n_segs * SEGMENT;
     const char* blocks = a.map[0].rows + ((int64_t)b * pixels1 + (int64_t)(a.first_sb + sb) * DENSE_SB_PIXELS) * COARSE_ROW_BYTES;
     const char* tiles = a.map[1].rows + (int64_t)b * pixels2 * COARSE_ROW_BYTES;
     uint16_t* rows = a.best[0] + ((int64_t)b * a.n_cells + cell0) * ((int64_t)a.n_sb * DENSE_SB_PIXELS) + (int64_t)sb * DENSE_SB_PIXELS;
-    uint16_t* cols = a.best[1] + ((int64_t)b * a.map[0].n_segs + (int64_t)(a.first_sb + sb) * SEGS) * pixels2;
+    const int64_t col_pitch = GROUPED ? pixels2 / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS : pixels2;
+    uint16_t* cols = a.best[1] + ((int64_t)b * a.map[0].n_segs * (SEGMENT / COL_CELL) + (int64_t)(a.first_sb + sb) * COL_CELLS) * col_pitch;
     // groups of this workgroup's cells that hold a pixel of image 2 (uniform)
-    const int group0 = cell0 * a.cell_groups;
-    const int n_groups = min(a.cells_per_wg * a.cell_groups, (a.n_tiles[1] + DC_GROUP - 1) / DC_GROUP - group0);
+    const int cell_groups = CELL_GROUPS * a.cell_runs, group0 = cell0 * cell_groups;
+    const int n_groups = min(a.cells_per_wg * cell_groups, (a.n_tiles[1] + DC_GROUP - 1) / DC_GROUP - group0);
     if (n_groups <= 0) return;
     const int total = n_groups * DC_TURNS;
 
@@ -104,13 +129,13 @@ void dense_coarse_kernel(DenseCoarseArgs a) {
     for (int g = 0; g < n_groups; ++g) {
         const int tile0 = (group0 + g) * DC_GROUP + wave * DC_J;
         i32x4 cand[DC_J];
-        int best[DC_J][16];
+        int best[DC_J][DC_KEPT];
 #pragma unroll
         for (int j = 0; j < DC_J; ++j) {
             cand[j] = *reinterpret_cast<const i32x4*>(tiles + (int64_t)(tile0 + j) * TILE_BYTES + c * COARSE_ROW_BYTES + 16 * h);
             arrived(cand[j]);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) best[j][v] = LOWEST;
+            for (int v = 0; v < DC_KEPT; ++v) best[j][v] = LOWEST;
         }
         auto turn = [&](int tt, auto slot_tag) {
             constexpr int SLOT = decltype(slot_tag)::value;
@@ -118,44 +143,95 @@ void dense_coarse_kernel(DenseCoarseArgs a) {
             __syncthreads();                     // everyone's is, and everyone has left the other slot
             stage_turn(SLOT ? stage0 : stage1, k + tt + 1);
             int found[DC_STEPS];  // best score of a step's queries (lanes 0..31 its first block, 32..63 its second)
+            auto block = [&](int i) { return __builtin_bit_cast(i32x4, SLOT ? stage1[i][lane] : stage0[i][lane]); };
+            if constexpr (GROUPED) {
+                // product number i: step i / (2 DC_J), tile i / 2 % DC_J, the first or second of the step's blocks
+                constexpr int STEP = 2 * DC_J, PRODUCTS = DC_STEPS * STEP;
+                i32x4 q[2][2];
+                q[0][0] = block(0);
+                q[0][1] = block(1);
+                i32x16 score[2];
+                score[0] = product8(cand[0], q[0][0]);
+                int row[2], first[GROUPS];
 #pragma unroll
-            for (int s = 0; s < DC_STEPS; ++s) {
-                const i32x4 qa = __builtin_bit_cast(i32x4, SLOT ? stage1[2 * s][lane] : stage0[2 * s][lane]);
-                const i32x4 qb = __builtin_bit_cast(i32x4, SLOT ? stage1[2 * s + 1][lane] : stage0[2 * s + 1][lane]);
-                int ra = LOWEST, rb = LOWEST;
+                for (int i = 0; i < PRODUCTS; ++i) {
+                    const int s = i / STEP, j = i / 2 % DC_J, e = i & 1, then = i + 1;
+                    if (i % STEP == 0) {
+                        row[0] = row[1] = LOWEST;
+                        if (s + 1 < DC_STEPS) {
+                            q[(s + 1) & 1][0] = block(2 * s + 2);
+                            q[(s + 1) & 1][1] = block(2 * s + 3);
+                        }
+                    }
+                    if (then < PRODUCTS) score[then & 1] = product8(cand[then / 2 % DC_J], q[then / STEP & 1][then & 1]);
+                    __builtin_amdgcn_sched_barrier(0);  // a product, then the maxima of the one before it
+                    int group[GROUPS];
+                    group_maxima(score[e], group);
+                    row[e] = max3i(max3i(row[e], group[0], group[1]), max3i(group[2], group[3], group[4]), group[5]);
+                    asm volatile("" : "+v"(row[e]));  // ... which the optimiser would otherwise move to the end of the turn
 #pragma unroll
-                for (int j = 0; j < DC_J; ++j) {
-                    const i32x16 pa = product8(cand[j], qa), pb = product8(cand[j], qb);
-                    ra = fold16i(ra, pa);
-                    rb = fold16i(rb, pb);
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) best[j][v] = max3i(best[j][v], pa[v], pb[v]);
+                    for (int v = 0; v < GROUPS; ++v) {
+                        if (e == 0) {
+                            first[v] = group[v];
+                        } else {
+                            best[j][v] = max3i(best[j][v], first[v], group[v]);
+                            asm volatile("" : "+v"(best[j][v]));
+                        }
+                    }
+                    if (i % STEP == STEP - 1) {
+                        const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)row[0], (uint32_t)row[1], false, false);
+                        found[s] = max((int)sw[0], (int)sw[1]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)ra, (uint32_t)rb, false, false);
-                found[s] = max((int)sw[0], (int)sw[1]);
-                __builtin_amdgcn_sched_barrier(0);  // steps are scheduled one by one: more products in flight would spill
+            } else {
+#pragma unroll
+                for (int s = 0; s < DC_STEPS; ++s) {
+                    const i32x4 qa = block(2 * s), qb = block(2 * s + 1);
+                    int ra = LOWEST, rb = LOWEST;
+#pragma unroll
+                    for (int j = 0; j < DC_J; ++j) {
+                        const i32x16 pa = product8(cand[j], qa), pb = product8(cand[j], qb);
+                        ra = fold16i(ra, pa);
+                        rb = fold16i(rb, pb);
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) best[j][v] = max3i(best[j][v], pa[v], pb[v]);
+                    }
+                    const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)ra, (uint32_t)rb, false, false);
+                    found[s] = max((int)sw[0], (int)sw[1]);
+                    __builtin_amdgcn_sched_barrier(0);  // steps are scheduled one by one: more products in flight would spill
+                }
             }
 #pragma unroll
             for (int s = 0; s < DC_STEPS; ++s) atomicMax(&row_best[(tt * COARSE_TURN + 2 * s) * 32 + lane], found[s]);
         };
 #pragma unroll 1
-        for (int seg = 0; seg < SEGS; ++seg) {
+        for (int cc = 0; cc < COL_CELLS; ++cc) {
 #pragma unroll 1
-            for (int tt = seg * SEG_TURNS; tt < (seg + 1) * SEG_TURNS; tt += 2) {
+            for (int tt = cc * COL_TURNS; tt < (cc + 1) * COL_TURNS; tt += 2) {
                 turn(tt, std::integral_constant<int, 0>{});
                 turn(tt + 1, std::integral_constant<int, 1>{});
             }
+            int fresh = lane;
+            asm volatile("" : "+v"(fresh));  // else what hangs on it is kept over the sweep
+            const int held = held_register(fresh), half = fresh >> 5;
 #pragma unroll
-            for (int j = 0; j < DC_J; ++j) {
-                const int top = transpose_max16_int(best[j], lane);
-                if ((lane & 16) == 0)
-                    cols[seg * pixels2 + (int64_t)(tile0 + j) * 32 + tile_row(held, h)] = (uint16_t)(top >> KEPT_SHIFT);
+            for (int r = 0; r < DC_J * DC_KEPT; r += 16) {  // sixteen registers at a time; of groups, across the tiles
+                int x[16];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) best[j][v] = LOWEST;
+                for (int v = 0; v < 16; ++v) x[v] = best[(r + v) / DC_KEPT][(r + v) % DC_KEPT];
+                const int top = transpose_max16_int(x, fresh);
+                uint16_t* to = cols + cc * col_pitch + (GROUPED ? (int64_t)(group0 + g) * DENSE_CELL_GROUPS : (int64_t)(tile0 + r / 16) * 32);  // uniform
+                const uint32_t at = GROUPED ? group_entry(wave * DC_J + (r + held) / GROUPS, half, (r + held) % GROUPS) : tile_row(held, half);
+                if ((fresh & 16) == 0) to[at] = (uint16_t)(top >> KEPT_SHIFT);
             }
+#pragma unroll
+            for (int j = 0; j < DC_J; ++j)
+#pragma unroll
+                for (int v = 0; v < DC_KEPT; ++v) best[j][v] = LOWEST;
         }
         k += DC_TURNS;
-        if ((g + 1) % a.cell_groups == 0 || g + 1 == n_groups) {  // the end of a cell (uniform)
+        if ((g + 1) % cell_groups == 0 || g + 1 == n_groups) {  // the end of a cell (uniform)
             __syncthreads();
             for (int i = threadIdx.x * 2; i < DENSE_SB_PIXELS; i += COARSE_WAVES * 128) {
                 const int2 two = *reinterpret_cast<const int2*>(&row_best[i]);
@@ -167,6 +243,14 @@ void dense_coarse_kernel(DenseCoarseArgs a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // the turn past the last one has landed too
 }
+// a maximum for every candidate
+template <int SEGMENT>
+__global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(3)))
+void dense_coarse_kernel(DenseCoarseArgs a) { dense_sweep<SEGMENT, false>(a); }
+// one for every group
+template <int SEGMENT>
+__global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
+void dense_groups_kernel(DenseCoarseArgs a) { dense_sweep<SEGMENT, true>(a); }
 
 // Which cells may hold the best partner of a slot: the bounds that turn 8-bit scores into products (coarse.hip) give every slot a
 // lower bound of its best score, and a cell whose upper bound reaches it is marked.  A lane takes SELECT_SLOTS slots,
@@ -176,65 +260,69 @@ constexpr int SELECT_WAVES = 4;
 constexpr int SELECT_SLOTS = 4;
 constexpr int SELECT_DEEP = 6;  // cells in flight per wave
 struct SelectSide {
-    const uint16_t* best;       // [batch][n_cells][pitch]
-    uint64_t* mask;             // [batch][n_cells][pitch / 64]
-    int32_t n_cells;
-    int64_t pitch;              // a multiple of 64
+    const uint16_t* best;       // [batch][table_cells][pitch, or the groups of so many slots]
+    int64_t table_cells;
+    uint64_t* mask;             // [batch][table_cells][pitch / 64]
+    int32_t n_cells;            // that hold a pixel
+    int64_t pitch;              // slots, a multiple of 1024
     int32_t cells_per_seg;      // of the other map
     const uint32_t* row_bound;  // of the slots, [batch][bound_pitch]
     int64_t bound_pitch;
     const SegInfo* seg;         // of the other map, [batch][n_segs]
     int32_t n_segs;
+    // groups of slots
+    int32_t grouped;
+    float* least;               // [batch][entries of a cell] the smallest upper bound of the first round's cells
+    const u64* keys;            // the second round: [batch][n_keys] what the first left
+    int64_t n_keys;
+    const SegInfo* own_seg;     // of the slots, [batch][own_n_segs]
+    int32_t own_n_segs;
+    int32_t own_seg_pixels;
 };
 struct SelectArgs {
     SelectSide side[2];     // blockIdx.z
     DenseJudge judge;
 };
-__global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectArgs args) {
-    const SelectSide a = blockIdx.z ? args.side[1] : args.side[0];  // (an index would hide from the compiler that the pointers are global)
-    if (args.judge.alike(blockIdx.y)) return;
-    if ((int64_t)blockIdx.x * (64 * SELECT_SLOTS) >= a.pitch) return;  // uniform: the sides differ in size
-    __shared__ float low[SELECT_WAVES][SELECT_SLOTS][64];
+// visit(cell, 8-bit scores of N entries of a lane, 64 apart, their segment) for this wave's cells
+template <int N, int DEEP, typename F>
+__device__ __forceinline__ void for_cells(const SelectSide& a, const uint16_t* column, int64_t row_entries, const SegInfo* seg, int wave, const F& visit) {
+    for (int cell0 = wave; cell0 < a.n_cells; cell0 += SELECT_WAVES * DEEP) {
+        int kept[DEEP][N];
+#pragma unroll
+        for (int i = 0; i < DEEP; ++i)
+#pragma unroll
+            for (int e = 0; e < N; ++e) kept[i][e] = (int16_t)column[(int64_t)min(cell0 + i * SELECT_WAVES, a.n_cells - 1) * row_entries + 64 * e];
+#pragma unroll
+        for (int i = 0; i < DEEP; ++i) {
+            const int cell = cell0 + i * SELECT_WAVES;
+            if (cell < a.n_cells) visit(cell, kept[i], seg[cell / a.cells_per_seg]);  // uniform
+        }
+    }
+}
+__device__ __forceinline__ float bound_error(uint32_t bound, const SegInfo& si) {
+    return __builtin_fmaf(__uint_as_float(bound & 0xFFFF0000u), si.residual, __uint_as_float(bound << 16) * si.length);
+}
+__device__ __forceinline__ float upper_score(int kept, const SegInfo& si, float error) {
+    return __builtin_fmaf((float)((kept + 1) * (1 << KEPT_SHIFT)), si.scale, error);  // the same wherever it is formed: two rounds share the cells by it
+}
+
+__device__ __forceinline__ void select_slots(const SelectSide& a, int b, float (&low)[SELECT_WAVES][SELECT_SLOTS][64]) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = blockIdx.y;
-    const int64_t slot0 = (int64_t)blockIdx.x * (64 * SELECT_SLOTS);  // whole 64s past the pitch do not exist
-    const uint16_t* column = a.best + (int64_t)b * a.n_cells * a.pitch + slot0 + lane;
-    uint64_t* mask = a.mask + ((int64_t)b * a.n_cells * a.pitch + slot0) / 64;
+    const int64_t slot0 = (int64_t)blockIdx.x * (64 * SELECT_SLOTS);
+    const uint16_t* column = a.best + (int64_t)b * a.table_cells * a.pitch + slot0 + lane;
+    uint64_t* mask = a.mask + ((int64_t)b * a.table_cells * a.pitch + slot0) / 64;
     const SegInfo* seg = a.seg + (int64_t)b * a.n_segs;
-    bool here[SELECT_SLOTS];
-    float length[SELECT_SLOTS], residual[SELECT_SLOTS], best[SELECT_SLOTS];
+    uint32_t bound[SELECT_SLOTS];
+    float best[SELECT_SLOTS];
 #pragma unroll
     for (int e = 0; e < SELECT_SLOTS; ++e) {
-        here[e] = slot0 + 64 * e < a.pitch;  // uniform
-        const uint32_t bound = here[e] ? a.row_bound[(int64_t)b * a.bound_pitch + slot0 + 64 * e + lane] : 0;
-        length[e] = __uint_as_float(bound & 0xFFFF0000u);
-        residual[e] = __uint_as_float(bound << 16);
+        bound[e] = a.row_bound[(int64_t)b * a.bound_pitch + slot0 + 64 * e + lane];
         best[e] = -__builtin_inff();
     }
-    // visit(cell, slot, 8-bit score, its segment) for this wave's cells
-    auto sweep = [&](auto visit) {
-        for (int cell0 = wave; cell0 < a.n_cells; cell0 += SELECT_WAVES * SELECT_DEEP) {
-            int kept[SELECT_DEEP][SELECT_SLOTS];
+    for_cells<SELECT_SLOTS, SELECT_DEEP>(a, column, a.pitch, seg, wave, [&](int, const int (&v)[SELECT_SLOTS], const SegInfo& si) {
 #pragma unroll
-            for (int i = 0; i < SELECT_DEEP; ++i)
-#pragma unroll
-                for (int e = 0; e < SELECT_SLOTS; ++e)
-                    kept[i][e] = (int16_t)column[(int64_t)min(cell0 + i * SELECT_WAVES, a.n_cells - 1) * a.pitch + (here[e] ? 64 * e : 0)];
-#pragma unroll
-            for (int i = 0; i < SELECT_DEEP; ++i) {
-                const int cell = cell0 + i * SELECT_WAVES;
-                if (cell < a.n_cells) {  // uniform
-                    const SegInfo si = seg[cell / a.cells_per_seg];
-#pragma unroll
-                    for (int e = 0; e < SELECT_SLOTS; ++e) visit(cell, e, kept[i][e], si);
-                }
-            }
-        }
-    };
-    auto error = [&](int e, const SegInfo& si) { return __builtin_fmaf(length[e], si.residual, residual[e] * si.length); };
-    sweep([&](int, int e, int v, const SegInfo& si) {
-        best[e] = __builtin_fmaxf(best[e], (float)(v * (1 << KEPT_SHIFT)) * si.scale - error(e, si));
+        for (int e = 0; e < SELECT_SLOTS; ++e) best[e] = __builtin_fmaxf(best[e], (float)(v[e] * (1 << KEPT_SHIFT)) * si.scale - bound_error(bound[e], si));
     });
 #pragma unroll
     for (int e = 0; e < SELECT_SLOTS; ++e) low[wave][e][lane] = best[e];
@@ -243,10 +331,136 @@ __global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectA
     for (int e = 0; e < SELECT_SLOTS; ++e)
 #pragma unroll
         for (int w = 0; w < SELECT_WAVES; ++w) best[e] = __builtin_fmaxf(best[e], low[w][e][lane]);
-    sweep([&](int cell, int e, int v, const SegInfo& si) {
-        const uint64_t need = __ballot((float)((v + 1) * (1 << KEPT_SHIFT)) * si.scale + error(e, si) >= best[e]);
-        if (lane == 0 && here[e]) mask[(int64_t)cell * (a.pitch / 64) + e] = need;
+    for_cells<SELECT_SLOTS, SELECT_DEEP>(a, column, a.pitch, seg, wave, [&](int cell, const int (&v)[SELECT_SLOTS], const SegInfo& si) {
+        uint64_t mine = 0;  // a cell's words are written side by side
+#pragma unroll
+        for (int e = 0; e < SELECT_SLOTS; ++e) {
+            const uint64_t need = __ballot(upper_score(v[e], si, bound_error(bound[e], si)) >= best[e]);
+            mine = lane == e ? need : mine;
+        }
+        if (lane < SELECT_SLOTS) mask[(int64_t)cell * (a.pitch / 64) + lane] = mine;
     });
+}
+
+// The same for groups of slots.  The first round marks the GROUP_TOP cells with a group's largest upper bounds; the second, when those have been multiplied, the
+// others whose upper bound reaches a slot's best product.  A lane takes a group of each of SELECT_SETS runs of 64; the bits of a cell
+// are in the order of mask_candidate: three words for 64 triples, one for 64 single slots.  (512x384 / 1024x768, the two rounds: a lane for every slot, three of which read the same
+// entry, 83 + 76 / 282 + 516 us; so, but with the first round's cells looked up in its words instead of by their bounds, 75 + 86 / 218 + 421.)
+constexpr int SELECT_SETS = 2, SELECT_SETS_DEEP = 8;
+constexpr int TRIPLE_SETS = CELL_TRIPLES / 64;
+constexpr int SELECT_PARTS = DENSE_CELL_GROUPS / (64 * SELECT_SETS);  // workgroups for a run of DENSE_CELL_PIXELS slots
+static_assert(SELECT_PARTS * 64 * SELECT_SETS == DENSE_CELL_GROUPS, "whole runs of 64");
+constexpr int GROUP_TOP = 6, GROUP_TOP_FEW = 3, FEW_CELLS = 32;       // (of a small map's few cells, fewer)
+__device__ __forceinline__ void select_groups(const SelectSide& a, int b, float (&handed)[SELECT_WAVES][SELECT_SETS][GROUP_TOP][64]) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int run = blockIdx.x / SELECT_PARTS, set0 = blockIdx.x % SELECT_PARTS * SELECT_SETS;  // of the run's sets of 64 groups
+    const int64_t slot0 = (int64_t)run * DENSE_CELL_PIXELS, row_entries = a.pitch / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS;
+    const uint16_t* column = a.best + (int64_t)b * a.table_cells * row_entries + (int64_t)run * DENSE_CELL_GROUPS + 64 * set0 + lane;
+    uint64_t* mask = a.mask + ((int64_t)b * a.table_cells * a.pitch + slot0) / 64 + 3 * set0;
+    float* least_of = a.least + (int64_t)b * row_entries + (int64_t)run * DENSE_CELL_GROUPS + 64 * set0 + lane;
+    const SegInfo* seg = a.seg + (int64_t)b * a.n_segs;
+    int64_t slot[SELECT_SETS][3];
+    uint32_t bound[SELECT_SETS];  // the group's worst length and remainder
+#pragma unroll
+    for (int e = 0; e < SELECT_SETS; ++e) {
+        bound[e] = 0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const bool single = set0 + e == TRIPLE_SETS;  // uniform
+            slot[e][k] = slot0 + mask_candidate((3 * (set0 + e) + (single ? 0 : k)) * 64 + lane);
+            const uint32_t own = a.row_bound[(int64_t)b * a.bound_pitch + slot[e][k]];
+            bound[e] = max(bound[e] & 0xFFFF0000u, own & 0xFFFF0000u) | max(bound[e] & 0xFFFFu, own & 0xFFFFu);  // not negative: they order like integers
+        }
+    }
+    const bool last_single = set0 + SELECT_SETS == TRIPLE_SETS + 1;  // uniform: the last of the sets is the single slots
+    // a cell's words, side by side; marked(e, k): whether slot k of this lane's group of set e is
+    auto write = [&](int cell, auto marked) {
+        uint64_t mine = 0;
+#pragma unroll
+        for (int e = 0; e < SELECT_SETS; ++e)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const uint64_t need = __ballot(marked(e, k));
+                mine = lane == 3 * e + k ? need : mine;
+            }
+        if (lane < (last_single ? 3 * SELECT_SETS - 2 : 3 * SELECT_SETS)) mask[(int64_t)cell * (a.pitch / 64) + lane] = mine;
+    };
+    if (a.keys) {
+        // Products are compared with bounds times the scale of the slots' segment; a group with a row that has no bounds, or of a segment of zeros, needs every cell, and so do
+        // all slots a cell with such a row (a product of infinity is reached by no bound, but others may equal it).
+        const float scale = a.own_seg[(int64_t)b * a.own_n_segs + slot0 / a.own_seg_pixels].scale;
+        float product[SELECT_SETS][3], least[SELECT_SETS];
+        bool every[SELECT_SETS];
+#pragma unroll
+        for (int e = 0; e < SELECT_SETS; ++e) {
+            least[e] = least_of[64 * e];
+            every[e] = !(scale > 0.0f) || __uint_as_float(bound[e] & 0xFFFF0000u) >= 0.5f * UNBOUNDED;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) product[e][k] = slot[e][k] < a.n_keys ? key_score(a.keys[(int64_t)b * a.n_keys + slot[e][k]]) : 0.0f;
+        }
+        for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a, column, row_entries, seg, wave, [&](int cell, const int (&v)[SELECT_SETS], const SegInfo& si) {
+            float upper[SELECT_SETS];
+            bool all[SELECT_SETS], left[SELECT_SETS];
+#pragma unroll
+            for (int e = 0; e < SELECT_SETS; ++e) {
+                upper[e] = upper_score(v[e], si, bound_error(bound[e], si));
+                left[e] = upper[e] < least[e];  // not one of the first round's
+                all[e] = every[e] || si.residual >= 0.5f * UNBOUNDED;
+            }
+            write(cell, [&](int e, int k) { return slot[e][k] < a.n_keys && left[e] && (all[e] || upper[e] * scale >= product[e][k]); });
+        });
+        return;
+    }
+    float most[SELECT_SETS][GROUP_TOP];  // the largest upper bounds, in order
+    auto put = [](float (&t)[GROUP_TOP], float x) {
+#pragma unroll
+        for (int i = GROUP_TOP - 1; i > 0; --i) t[i] = __builtin_amdgcn_fmed3f(x, t[i - 1], t[i]);
+        t[0] = __builtin_fmaxf(t[0], x);
+    };
+#pragma unroll
+    for (int e = 0; e < SELECT_SETS; ++e)
+#pragma unroll
+        for (int i = 0; i < GROUP_TOP; ++i) most[e][i] = -__builtin_inff();
+    for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a, column, row_entries, seg, wave, [&](int, const int (&v)[SELECT_SETS], const SegInfo& si) {
+#pragma unroll
+        for (int e = 0; e < SELECT_SETS; ++e) put(most[e], upper_score(v[e], si, bound_error(bound[e], si)));
+    });
+#pragma unroll
+    for (int e = 0; e < SELECT_SETS; ++e)
+#pragma unroll
+        for (int i = 0; i < GROUP_TOP; ++i) handed[wave][e][i][lane] = most[e][i];
+    __syncthreads();
+    float least[SELECT_SETS];
+#pragma unroll
+    for (int e = 0; e < SELECT_SETS; ++e) {
+#pragma unroll
+        for (int w = 1; w < SELECT_WAVES; ++w)
+#pragma unroll
+            for (int i = 0; i < GROUP_TOP; ++i) put(most[e], handed[(wave + w) % SELECT_WAVES][e][i][lane]);
+        least[e] = a.n_cells < FEW_CELLS ? most[e][GROUP_TOP_FEW - 1] : most[e][GROUP_TOP - 1];
+        if (wave == 0) least_of[64 * e] = least[e];
+    }
+    for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a, column, row_entries, seg, wave, [&](int cell, const int (&v)[SELECT_SETS], const SegInfo& si) {
+        bool top[SELECT_SETS];
+#pragma unroll
+        for (int e = 0; e < SELECT_SETS; ++e) top[e] = upper_score(v[e], si, bound_error(bound[e], si)) >= least[e];
+        write(cell, [&](int e, int k) { return top[e] && slot[e][k] < a.n_keys; });
+    });
+}
+__global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectArgs args) {
+    const SelectSide a = blockIdx.z ? args.side[1] : args.side[0];  // (an index would hide from the compiler that the pointers are global)
+    if (args.judge.alike(blockIdx.y)) return;
+    __shared__ union {
+        float low[SELECT_WAVES][SELECT_SLOTS][64];
+        float handed[SELECT_WAVES][SELECT_SETS][GROUP_TOP][64];
+    } lds;
+    // uniform: the sides differ in size
+    if (a.grouped) {
+        if ((int64_t)(blockIdx.x / SELECT_PARTS) * DENSE_CELL_PIXELS < a.pitch) select_groups(a, blockIdx.y, lds.handed);
+    } else if ((int64_t)blockIdx.x * (64 * SELECT_SLOTS) < a.pitch) {
+        select_slots(a, blockIdx.y, lds.low);
+    }
 }
 
 // Whether the 8-bit scores of a pair tell enough apart.  How many cells the bounds leave over is a matter of what the maps hold (a
@@ -259,8 +473,16 @@ __global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectA
 constexpr int SAMPLE_BLOCKS = DENSE_SAMPLES / 32;
 constexpr int SAMPLE_WAVES = 8;
 constexpr int SAMPLE_TILES = 8;  // in flight per wave
-__device__ __forceinline__ int64_t sample_pixel(int k, int64_t n) { return (int64_t)(((uint64_t)((uint32_t)k * 0x9E3779B1u) * (uint64_t)n) >> 32); }
-__device__ __forceinline__ int sample_cells(const DenseCoarseArgs& a, int side) { return side == 0 ? a.n_cells : a.map[0].n_segs; }
+__device__ __forceinline__ int64_t spread_pixel(int k, int64_t n) { return (int64_t)(((uint64_t)((uint32_t)k * 0x9E3779B1u) * (uint64_t)n) >> 32); }
+// Where the maxima are those of groups, whole groups.
+constexpr int SAMPLE_GROUP = 3;
+__device__ __forceinline__ int64_t sample_pixel(int k, int64_t n, bool grouped) {
+    if (!grouped) return spread_pixel(k, n);
+    const int g = k / SAMPLE_GROUP;
+    const int64_t at = (spread_pixel(g, n) & ~(int64_t)31) + tile_row(SAMPLE_GROUP * (g / 2 % (GROUPS - 1)) + k % SAMPLE_GROUP, g & 1);
+    return at < n ? at : n - 1;
+}
+__device__ __forceinline__ int sample_cells(const DenseCoarseArgs& a, int side) { return side == 0 ? a.n_cells : a.n_col_cells; }
 // A workgroup scores the samples of one image against one cell of the other.  Bound by the latency of its loads.
 __global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCoarseArgs a) {
     __shared__ int best[DENSE_SAMPLES];
@@ -271,16 +493,17 @@ __global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCo
     const CoarseMap& own = a.map[side];
     const CoarseMap& other = a.map[side ^ 1];
     const int64_t own_row0 = (int64_t)b * own.n_segs * a.seg_pixels;
-    const int cell_pixels = side == 0 ? 512 * a.cell_groups : a.seg_pixels;  // 1024 to 4096
+    const bool grouped = side == 1 && a.grouped;
+    const int cell_pixels = side == 0 ? DENSE_CELL_PIXELS * a.cell_runs : a.seg_pixels >> a.grouped;  // 1024 to 4096
     const char* tiles = other.rows + ((int64_t)b * other.n_segs * a.seg_pixels + (int64_t)cell * cell_pixels) * COARSE_ROW_BYTES;
-    const int64_t mine = sample_pixel(threadIdx.x & (DENSE_SAMPLES - 1), a.pixels[side]);
+    const int64_t mine = sample_pixel(threadIdx.x & (DENSE_SAMPLES - 1), a.pixels[side], grouped);
     const uint32_t bound = own.row_bound[own_row0 + mine];
     const SegInfo si = other.seg[(int64_t)b * other.n_segs + (int64_t)cell * cell_pixels / a.seg_pixels];
     if (threadIdx.x < DENSE_SAMPLES) best[threadIdx.x] = LOWEST;
     i32x4 q[SAMPLE_BLOCKS];
 #pragma unroll
     for (int k = 0; k < SAMPLE_BLOCKS; ++k)
-        q[k] = *reinterpret_cast<const i32x4*>(own.rows + (own_row0 + sample_pixel(k * 32 + c, a.pixels[side])) * COARSE_ROW_BYTES + 16 * h);
+        q[k] = *reinterpret_cast<const i32x4*>(own.rows + (own_row0 + sample_pixel(k * 32 + c, a.pixels[side], grouped)) * COARSE_ROW_BYTES + 16 * h);
     int top[SAMPLE_BLOCKS];
 #pragma unroll
     for (int k = 0; k < SAMPLE_BLOCKS; ++k) top[k] = LOWEST;
@@ -302,8 +525,13 @@ __global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCo
     __syncthreads();
     if (threadIdx.x < DENSE_SAMPLES) {
         const int k = threadIdx.x, kept = best[k] >> KEPT_SHIFT;
+        int top = kept;
+        if (grouped) {  // a group's maximum stands for each of its candidates
+            const int first = k / SAMPLE_GROUP * SAMPLE_GROUP;
+            for (int i = first; i < first + SAMPLE_GROUP && i < DENSE_SAMPLES; ++i) top = max(top, best[i] >> KEPT_SHIFT);
+        }
         const float error = __builtin_fmaf(__uint_as_float(bound & 0xFFFF0000u), si.residual, __uint_as_float(bound << 16) * si.length);
-        a.sample_upper[side][((int64_t)b * sample_cells(a, side) + cell) * DENSE_SAMPLES + k] = (float)((kept + 1) * (1 << KEPT_SHIFT)) * si.scale + error;
+        a.sample_upper[side][((int64_t)b * sample_cells(a, side) + cell) * DENSE_SAMPLES + k] = (float)((top + 1) * (1 << KEPT_SHIFT)) * si.scale + error;
         atomicMax(&a.sample_lower[(b * 2 + side) * DENSE_SAMPLES + k], order_bits((float)(kept * (1 << KEPT_SHIFT)) * si.scale - error));
     }
 }
@@ -327,29 +555,38 @@ __global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseA
 // 371712 6.10 / 5.88, 442368 8.43 / 8.16, 786432 26.4 / 24.9.
 constexpr int64_t DENSE_WIDE_PIXELS = 300000;
 int dense_seg_pixels(int64_t n) { return n > DENSE_WIDE_PIXELS ? 4096 : 2048; }
-int dense_cell_groups(int64_t n, int64_t m) { return m > DENSE_WIDE_PIXELS ? dense_seg_pixels(n) / 512 : 2; }  // a cell lies in one segment
+int dense_cell_runs(int64_t n, int64_t m) { return m > DENSE_WIDE_PIXELS ? dense_seg_pixels(n) / DENSE_CELL_PIXELS : 1; }  // a cell lies in one segment
 // What a block of 32x32 scores takes one SIMD in the dense kernels, in dense_coarse_kernel, and in the second step
 static double dense_exact(int compute, int dp) { return compute == FNN_F32 ? 15.8 * dp : (dp <= 32 ? 2.33 * dp : 1.83 * dp); }
-constexpr double DENSE_COARSE = 38.0;
+constexpr double DENSE_COARSE = 38.0, DENSE_COARSE_GROUPS = 29.0;
 static double dense_second(int compute, int dp) { return compute == FNN_F32 ? 18.75 * dp : (dp <= 32 ? 46.0 : 1.64 * dp); }
+// Groups of candidates leave some GROUP_TOP cells more of them to the second step, which is dear where products are (fp32, 24 channels, a maximum for every candidate / groups:
+// 320x240 839 / 911 us, four pairs of 256x192 and 320x240 1613 / 1978; two-term rows, 384x288 894 / 865).
+static double first_round(double cells) { return cells < FEW_CELLS ? GROUP_TOP_FEW : GROUP_TOP; }
+bool dense_grouped(int64_t n, int compute, int dp) {
+    const double cells = 2.0 * n / dense_seg_pixels(n);
+    return dense_second(compute, dp) * (first_round(cells) + 2.0) < (DENSE_COARSE - DENSE_COARSE_GROUPS) * cells;
+}
+static double dense_coarse_block(int64_t n, int compute, int dp) { return dense_grouped(n, compute, dp) ? DENSE_COARSE_GROUPS : DENSE_COARSE; }
 // ... there with its lists and what their uneven lengths leave idle: one 512x384 pair of 16-bit rows loses from a share of about 0.26 on
 // (0.24 0.97 of the one step's time, 0.25 0.99), 384x288 in fp32 is at 0.87 with 0.61
-double dense_coarse_limit(int compute, int dp) {
-    return 0.85 * (dense_exact(compute, dp) - DENSE_COARSE) / (compute != FNN_F32 && dp <= 32 ? 58.0 : dense_second(compute, dp));
+double dense_coarse_limit(int64_t n, int compute, int dp) {
+    return 0.85 * (dense_exact(compute, dp) - dense_coarse_block(n, compute, dp)) / (compute != FNN_F32 && dp <= 32 ? 58.0 : dense_second(compute, dp));
 }
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2) {
     if (n < 16384 || m < 16384 || (compute != FNN_F32 && dp <= 16)) return -1e30;
     if ((double)m * (n / dense_seg_pixels(n)) * 2.0 > 4e9) return -1e30;  // the candidates' table of a pair would be too large
-    const double cell = 512.0 * dense_cell_groups(n, m), row_bytes = dp * elem_size(compute);
-    const double cells[2] = {m / cell, (double)n / dense_seg_pixels(n)};
-    const double again = coarse_cells_again(cells[0], d, l2) / cells[0] + coarse_cells_again(cells[1], d, l2) / cells[1];
+    const bool grouped = dense_grouped(n, compute, dp);
+    const double cell = (double)DENSE_CELL_PIXELS * dense_cell_runs(n, m), row_bytes = dp * elem_size(compute);
+    const double cells[2] = {m / cell, (grouped ? 2.0 : 1.0) * n / dense_seg_pixels(n)};
+    const double again = coarse_cells_again(cells[0], d, l2) / cells[0] + ((grouped ? first_round(cells[1]) : 0.0) + coarse_cells_again(cells[1], d, l2)) / cells[1];
     const double blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
     const double bytes = batch * ((double)(n + m) * (2.0 * row_bytes + 40.0) + 8.0 * n * (m / cell) + 8.0 * m * ((double)n / dense_seg_pixels(n)));
-    return blocks * (dense_exact(compute, dp) - DENSE_COARSE - dense_second(compute, dp) * again) - 45000.0 - bytes / 4500.0 - batch * (double)(n + m) * 0.1;
+    return blocks * (dense_exact(compute, dp) - dense_coarse_block(n, compute, dp) - dense_second(compute, dp) * again) - 45000.0 - bytes / 4500.0 - batch * (double)(n + m) * 0.1;
 }
 
 hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s) {
-    const int cells = a.n_cells > a.map[0].n_segs ? a.n_cells : a.map[0].n_segs;
+    const int cells = a.n_cells > a.n_col_cells ? a.n_cells : a.n_col_cells;
     const hipError_t e = launch(TK_DENSE_SAMPLE, dense_sample_kernel, dim3(cells, 2, batch), dim3(SAMPLE_WAVES * 64), 0, s, a);
     if (e != hipSuccess) return e;
     return launch(TK_DENSE_SAMPLE, dense_judge_kernel, dim3((cells + JUDGE_CELLS - 1) / JUDGE_CELLS, 2, batch), dim3(DENSE_SAMPLES), 0, s, a);
@@ -360,36 +597,48 @@ hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s) {
     const int64_t cells = (int64_t)a.n_cells * a.n_sb * batch;
     while (a.cells_per_wg < 4 && cells / (a.cells_per_wg * 2) >= 4608) a.cells_per_wg *= 2;
     const dim3 grid((a.n_cells + a.cells_per_wg - 1) / a.cells_per_wg, a.n_sb, batch);
+    if (a.grouped) {
+        if (a.seg_pixels == 2048) return launch_detail(TK_DENSE, 3, dense_groups_kernel<2048>, grid, dim3(COARSE_WAVES * 64), 0, s, a);
+        return launch_detail(TK_DENSE, 3, dense_groups_kernel<4096>, grid, dim3(COARSE_WAVES * 64), 0, s, a);
+    }
     if (a.seg_pixels == 2048) return launch_detail(TK_DENSE, 2, dense_coarse_kernel<2048>, grid, dim3(COARSE_WAVES * 64), 0, s, a);
     return launch_detail(TK_DENSE, 2, dense_coarse_kernel<4096>, grid, dim3(COARSE_WAVES * 64), 0, s, a);
 }
 
-static SelectSide select_side(const DenseCoarseArgs& a, int side) {
-    SelectSide sa;
+static SelectSide select_side(const DenseCoarseArgs& a, int side, const u64* keys) {
+    SelectSide sa = {};
     const CoarseMap& own = a.map[side];
     const CoarseMap& other = a.map[side ^ 1];
     sa.best = a.best[side];
     sa.mask = a.mask[side];
-    sa.n_cells = side == 0 ? a.n_cells : a.map[0].n_segs;
+    sa.table_cells = side == 0 ? a.n_cells : (int64_t)a.map[0].n_segs << a.grouped;
+    sa.n_cells = side == 0 ? a.n_cells : a.n_col_cells;
     sa.pitch = side == 0 ? (int64_t)a.n_sb * DENSE_SB_PIXELS : (int64_t)own.n_segs * a.seg_pixels;
-    sa.cells_per_seg = side == 0 ? a.seg_pixels / (512 * a.cell_groups) : 1;
+    sa.cells_per_seg = side == 0 ? a.seg_pixels / (DENSE_CELL_PIXELS * a.cell_runs) : 1 << a.grouped;
     sa.row_bound = own.row_bound + (side == 0 ? (int64_t)a.first_sb * DENSE_SB_PIXELS : 0);
     sa.bound_pitch = (int64_t)own.n_segs * a.seg_pixels;
     sa.seg = other.seg;
     sa.n_segs = other.n_segs;
+    sa.grouped = side == 1 && a.grouped;
+    sa.least = a.least;
+    sa.keys = keys;
+    sa.n_keys = a.pixels[side];
+    sa.own_seg = own.seg;
+    sa.own_n_segs = own.n_segs;
+    sa.own_seg_pixels = a.seg_pixels;
     return sa;
 }
-hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, int batch, hipStream_t s) {
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, const u64* col_keys, int batch, hipStream_t s) {
     SelectArgs args;
     args.judge = a.judge;
-    int64_t pitch = 0;
+    int64_t wgs = 0;
     for (int i = 0; i < sides; ++i) {
-        args.side[i] = select_side(a, first_side + i);
-        if (args.side[i].pitch > pitch) pitch = args.side[i].pitch;
+        args.side[i] = select_side(a, first_side + i, col_keys);
+        const int64_t pitch = args.side[i].pitch, need = args.side[i].grouped ? pitch / DENSE_CELL_PIXELS * SELECT_PARTS : pitch / (64 * SELECT_SLOTS);
+        if (need > wgs) wgs = need;
     }
     if (sides == 1) args.side[1] = args.side[0];
-    const int64_t per_wg = 64 * SELECT_SLOTS;
-    return launch(TK_DENSE_SELECT, dense_select_kernel, dim3((unsigned)((pitch + per_wg - 1) / per_wg), batch, sides), dim3(SELECT_WAVES * 64), 0, s, args);
+    return launch(TK_DENSE_SELECT, dense_select_kernel, dim3((unsigned)wgs, batch, sides), dim3(SELECT_WAVES * 64), 0, s, args);
 }
 
 }  // namespace fnn

@@ -167,6 +167,8 @@ struct DenseJudge {
 constexpr int SEG_TILES = 32;
 constexpr int SEG_PIXELS = 32 * SEG_TILES;
 constexpr int DENSE_SB_PIXELS = 4096;  // the dense mode sweeps so many queries at a time: one or two segments of its maps
+constexpr int DENSE_CELL_PIXELS = 1024;  // ... past so many candidates
+constexpr int DENSE_CELL_GROUPS = 384;   // ... of which it keeps a maximum each, or one for so many groups
 constexpr int COARSE_ROW_BYTES = 32;  // one K=32 matrix instruction
 struct SegInfo {
     float scale;     // a row is about scale * its 8-bit row
@@ -214,9 +216,10 @@ struct CoarseArgs {
     int32_t n_cells;       // of a pair
     int32_t cell_shift;    // a cell is 2^cell_shift workgroups of the second step
     const uint64_t* mask;  // launch_refine: [batch][n_cells][slab / 64] the slots that need a cell, instead of the bounds
+    int32_t grouped;       // ... the bits of every 1024 slots in the order of mask_candidate()
     DenseJudge judge;      // launch_refine: pairs to leave alone
     int32_t side;          // ... and whose samples the marks are: image 1's or 2's
-    int32_t range;         // (the launchers set these) queries that a workgroup of the second step looks at, or fewer
+    int32_t range;         // (the launchers set these; 0 on entry, or 1: lists are short) queries that a workgroup of the second step looks at, or fewer
     int32_t first_slot;
     int32_t min_live;      // fewer live queries of a pair than this: its cells are refined for every query
     SearchVote* vote;      // [batch] (0 on entry), or NULL: scores in 8 bits whatever the maps hold
@@ -417,18 +420,21 @@ struct DenseSwept {
     int32_t row_bytes; // a multiple of 16
 };
 // Pass 1 in 8 bits (dense_coarse.hip), on maps quantised in segments of seg_pixels: the largest 8-bit score of every query in
-// every cell of candidates, and of every candidate in every segment of queries.
+// every cell of candidates, and of every candidate, or group of candidates, in every cell of queries.
 struct DenseCoarseArgs {
     CoarseMap map[2];      // images 1 and 2
     int32_t n_tiles[2];    // tiles of each that hold a pixel
     int32_t seg_pixels;    // 2048 or 4096
     int32_t first_sb;      // the runs of DENSE_SB_PIXELS of image 1 that this launch takes
     int32_t n_sb;
-    int32_t cell_groups;   // groups of 512 candidates in a cell: 2, 4 or 8
+    int32_t cell_runs;     // runs of DENSE_CELL_PIXELS candidates in a cell: 1, 2 or 4
+    int32_t grouped;       // 1: the maxima of candidates are those of groups, and their cells half segments of queries; 0: whole segments
     int32_t n_cells;       // of image 2
+    int32_t n_col_cells;   // of image 1, those that hold a pixel
     int32_t cells_per_wg;  // (set by the launcher)
-    uint16_t* best[2];     // [batch][n_cells][n_sb * 4096] of the queries; [batch][map[0].n_segs][pixels of map[1]] of the candidates
-    uint64_t* mask[2];     // the same, a bit per score: cells that may hold the slot's best partner
+    uint16_t* best[2];     // [batch][n_cells][n_sb * 4096] of the queries; [batch][map[0].n_segs << grouped][pixels or groups of map[1]] of the candidates
+    uint64_t* mask[2];     // [batch][the same cells], a bit for every query and every candidate: cells that may hold its best partner
+    float* least;          // [batch][groups of map[1]] the second round's limit: see select_groups
     int64_t pixels[2];
     float* sample_upper[2];  // [batch][cells of the other image][DENSE_SAMPLES]
     uint32_t* sample_lower;  // [batch][2][DENSE_SAMPLES] order_bits (0 on entry)
@@ -441,11 +447,13 @@ constexpr int DENSE_SAMPLES = 128;  // pixels of either image
 hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s);
 hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s);
 // From best[side] to mask[side] for one or both sides.  0: the queries of this launch's runs; 1: the candidates, once every run is done.
-hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, int batch, hipStream_t s);
-int dense_cell_groups(int64_t n, int64_t m);
+// Groups of candidates take two rounds, the second with what the first left in their keys (col_keys, NULL: the first).
+hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, const u64* col_keys, int batch, hipStream_t s);
+int dense_cell_runs(int64_t n, int64_t m);
+bool dense_grouped(int64_t n, int compute, int dp);  // whether the candidates' maxima are those of groups
 int dense_seg_pixels(int64_t n);
 // Share of the cells, of both directions together, that may be multiplied again before the dense kernels are faster
-double dense_coarse_limit(int compute, int dp);
+double dense_coarse_limit(int64_t n, int compute, int dp);
 // Nanoseconds that a call gains this way
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2);
 

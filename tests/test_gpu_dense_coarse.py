@@ -218,3 +218,46 @@ def test_indices_stay_inside_maps_that_are_not_finite(compute, kw):
     assert 0 <= count <= min(n, m)
     pairs = got["pairs"][0, :count]
     assert count == 0 or (pairs.min() >= 0 and pairs[:, 0].max() < n and pairs[:, 1].max() < m)
+
+
+def pass1_detail(a, b, compute, **kw):
+    """Which 8-bit pass ran: 2 keeps a maximum for every candidate, 3 one for three."""
+    fnn.fnn_trace_begin(256)
+    try:
+        fnn.fnn_mutual_dense(a, b, compute, **kw)
+        torch.cuda.synchronize()
+    finally:
+        entries = fnn.fnn_trace_end(256, details=True)
+    return {detail for name, _, detail in entries if name == "dense_kernel"}
+
+
+@pytest.mark.parametrize("n,m,batch,compute,d,kw,grouped", [
+    (122881, 131073, 1, "f16", 24, {}, True),              # one pixel in the last cell of queries and in the last run of 1024 candidates
+    (126976, 131071, 1, "bf16", 24, {}, True),             # the last group lacks a candidate
+    (123904, 132064, 1, "f16", 24, {}, True),              # one tile in the last run
+    (43008, 524288, 1, "f16", 24, {}, True),               # as few cells of queries as groups are taken for, wide cells of candidates
+    (300001, 200100, 1, "bf16", 32, {}, True),             # cells of 2048 queries
+    (131072, 131072, 1, "f16", 24, {"split": True}, True),
+    (110000, 131072, 1, "f16", 24, {"split": True}, False),
+    (131072, 70000, 1, "f32", 24, {}, False),
+])
+def test_maxima_of_three_candidates(n, m, batch, compute, d, kw, grouped):
+    """A group's candidates have their partners in different cells, equal rows in different cells tie, and rows that are not finite are
+    multiplied with everything."""
+    gen = torch.Generator(device="cuda:0").manual_seed(n + 7 * m)
+    a = torch.nn.functional.normalize(torch.randn((batch, n, d), generator=gen, device="cuda:0"), dim=2)
+    b = torch.nn.functional.normalize(torch.randn((batch, m, d), generator=gen, device="cuda:0"), dim=2)
+    at = torch.randperm(n, generator=gen, device="cuda:0")[:min(n, m) // 2]
+    b[:, 1:2 * at.numel():2] = torch.nn.functional.normalize(a[:, at] + 0.3 * b[:, 1:2 * at.numel():2], dim=2)   # every second candidate
+    a[:, n - 3000:n - 2000] = a[:, 1000:2000]                                    # the same row in two cells: the lower index wins
+    b[:, m - 1] = a[:, 1500]
+    got, _ = same(a, b, compute, **kw)
+    assert pass1_detail(a, b, compute, **kw) == {3 if grouped else 2}
+    assert (got["nn21"][:, m - 1] == 1500).all()
+    # a product of infinity is reached by no bound, and the lowest of two is the match
+    a, b = a.abs() + 0.01, b.abs() + 0.01  # no channel is 0: 0 times infinity is no number
+    a[:, 5000] = a[:, n - 5] = float("inf")
+    b[:, 77] = b[:, m - 40] = float("inf")
+    got, _ = same(a, b, compute, **kw) if not kw else (None, None)
+    if got:
+        assert (got["nn21"] == 5000).sum() >= batch * (m - 2) and (got["nn12"] == 77).sum() >= batch * (n - 2)
