@@ -161,13 +161,15 @@ int recip_coarse_searches(int batch, int64_t n, int64_t m, int64_t n_seeds, int 
 // launches share out better; a walk that begins with few seeds is one launch altogether.  Whole calls in us with launches only / the tail from iteration
 // 0 / 1 / 2 / 3: one 512x384 pair, features of 1 and of 4 pixels, 192 seeds 163 / 84 / 104 / 112 and 180 / 91 / 112 / 128, 352 183 / 104 / 106 / 130 and
 // 185 / 109 / 111 / 131, 768 181 / 132 / 119 / 122 and 193 / 157 / 143 / 134, 3072 236 / 249 / 206 / 183 and 267 / 277 / 236 / 204; 320x240, 300 seeds 149 / 88 / 84 / 86, 1200
-// 153 / 157 / 121 / 102; 160x120, 1200 seeds 142 / 208 / 135 / 86.  Where very many seeds are left, the launches also have the wider search; from 2 / 3 on: 1024x768, 12288
-// seeds, 1082 / - / - / 1045 / 1022 and 1169 / - / - / 1111 / 1120, 16 pairs of 3072 1304 / - / - / 1261 / 1262 and 1470 / - / - / 1442 / 1429, of 12288 (features of 32 pixels) 5479 / - / - / 5648 / 5452.
-// Two maps that have nothing in common and features of 32 pixels keep hundreds of seeds moving for many iterations.  In launches only / so: one 512x384 pair 418 / 396, 16 pairs 3134 /
-// 3134, 1024x768 2526 / 2468, 16 256x192 pairs 490 / 459; with every fourth pixel a seed, 320x240 328 / 350, four of them 727 / 767, 400x300 557 / 603, 64 160x120 pairs 1020 / 1136: the price
-// of what such calls gain where features of 4 pixels let seeds settle (202 / 156, 384 / 354, 290 / 253, 564 / 516).
+// 153 / 157 / 121 / 102; 160x120, 1200 seeds 142 / 208 / 135 / 86.  Where very many seeds are left, the launches also have the wider search; from 2 / 3 on,
+// with the present kernels: 1024x768, 12288 seeds, features of 1, 4 and 32 pixels 991 / 1003, 1076 / 1100 and 2308 / 2315; 16 pairs of 3072
+// 1309 / 1353, 1469 / 1468 and 2942 / 2942, of 12288 3725 / 3699, 4305 / 4313 and 10140 / 9540; 1024x768, 49152 seeds, 3597 / 3597 and, of 32 pixels, 8210 / 8075.
+// Two maps that have nothing in common and features of 32 pixels keep hundreds of seeds moving for many iterations.  In launches only / so, before few seeds were dealt to
+// the waves block by block: one 512x384 pair 418 / 396 (since: 362), 16 pairs 3134 / 3134 (2942), 1024x768 2526 / 2468 (2310), 16 256x192 pairs 490 / 459; with every fourth pixel a seed, 320x240 328 / 350
+// (322), four of them 727 / 767, 400x300 557 / 603, 64 160x120 pairs 1020 / 1136: the price of what such calls gain where features of 4 pixels let seeds settle (202 / 156 (141), 384 / 354, 290 /
+// 253, 564 / 516).
 int first_late_iteration(int batch, int64_t n_seeds, int32_t max_iter, bool coarse) {
-    const int from = n_seeds >= 8192 || batch * n_seeds >= 49152 ? 3 : (n_seeds > TAIL_FEW || coarse ? 2 : (n_seeds > TAIL_FEW / 2 ? 1 : 0));
+    const int from = n_seeds >= 32768 || batch * n_seeds > 49152 ? 3 : (n_seeds > TAIL_FEW || coarse ? 2 : (n_seeds > TAIL_FEW / 2 ? 1 : 0));
     const int least = from > 2 ? from + 2 : 4;  // (with a single iteration left, four launches are as good)
     return max_iter >= least && max_iter <= TAIL_MOST_ITERATIONS ? from : -1;
 }
@@ -275,7 +277,7 @@ TailLayout carve_tail(Carver& cv, int batch) {
     TailLayout L;
     const size_t z0 = cv.used;
     L.control = (TailControl*)cv.take((size_t)batch * sizeof(TailControl));
-    L.few_keys = (u64*)cv.take((size_t)batch * 3 * TAIL_FEW * sizeof(u64));
+    L.few_keys = (u64*)cv.take((size_t)batch * 3 * TAIL_KEY_COPIES * TAIL_FEW * sizeof(u64));
     L.zero_words = (int64_t)((cv.used - z0) / sizeof(u64));
     return L;
 }

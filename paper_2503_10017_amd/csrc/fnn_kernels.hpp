@@ -333,6 +333,7 @@ hipError_t launch_groups(const WalkArgs& a, int batch, int compute, int dp, hipS
 constexpr int TAIL_FEW = 512;        // seeds of a pair that every workgroup can keep
 constexpr int TAIL_MOST_WGS = 256;   // of a pair
 constexpr int TAIL_COPIES = 16;      // of the words that many workgroups read or count in, each in a cache line of its own
+constexpr int TAIL_KEY_COPIES = 8;   // of few seeds' keys: additions to one word are served one after the other
 constexpr int TAIL_MOST_ITERATIONS = 1 << 20;
 struct TailControl {                 // of a pair; 0 on entry
     struct alignas(128) Word { u64 word; };
@@ -358,7 +359,7 @@ struct TailArgs {
     const int32_t* n_active;         // [batch] their number
     u64* keys;                       // [batch][n_seeds] 0 on entry
     int32_t* v;                      // [batch][n_seeds] scratch
-    u64* few_keys;                   // [batch][3][TAIL_FEW] 0 on entry
+    u64* few_keys;                   // [batch][3][TAIL_KEY_COPIES][TAIL_FEW] 0 on entry
     TailControl* control;
     int32_t t0, max_iter;            // t0 < max_iter <= TAIL_MOST_ITERATIONS
     uint64_t most_polls;             // looks at a word before a wait is given up

@@ -64,17 +64,16 @@ constexpr int TAIL_ROUND = 256;  // queries that a workgroup resolves before it 
 
 
 // Pass 1 of few queries with the candidates named: R blocks of queries, rows at[slot] of `src` from slot0 on, against the tiles [t0, t1).
-// A lane keeps the 16 scores of its query's best tile (16 moves per block and tile: a wave has few tiles), and looks for
-// the candidate when the last one is done.  The keys are those that the resolve pass would leave, also where no score is more than minus infinity (the first such
+// A lane keeps the 16 scores of its query's best tile (16 moves, where any lane of the wave has found a better one), and looks for
+// the candidate when the last one is done.  Scores count from low[slot] on, which some candidate exceeds.  The keys are those that the resolve pass would leave, also where no score is more than minus infinity (the first such
 // in the last tile of the map) or none is a number (the last pixel).  Bound by latency: the
 // queries' rows, the tiles.  (Keeping the tile, and multiplying it again for every query of the workgroup, as a variant of this kernel: 512x384 193 -> 215 us, squared
 // distance of two pairs 312 -> 336, 16 pairs 1251 -> 1249; both ways in one kernel spilled and were slower than either.)
 template <int CT, int DP, int R, int P>
-__device__ __forceinline__ void named_unit(const int32_t* at, const char* src, int src_rows, const char* tgt, int n_act, int slot0, int t0, int t1, int m, u64* keys,
-                                           int c, int h) {
+__device__ __forceinline__ void named_unit(const int32_t* at, const char* src, int src_rows, const char* tgt, int n_act, int slot0, int t0, int t1, int m, const float* low,
+                                           u64* keys, int c, int h) {
     using O = Ops<CT, DP>;
     using Frag = typename O::Frag;
-    constexpr bool WIDE = O::ROW_BYTES > 64 && R > 2;
     const float ninf = -__builtin_inff();
     const int last = (m - 1) / 32;
     asm volatile("" : "+v"(c), "+v"(h));  // else what hangs on the lane is kept from search to search, and spills the tiles
@@ -83,7 +82,7 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
     for (int p = 0; p < P; ++p)
         if (p == 0 || t0 + p < t1) ring[p] = O::stream_tile(tgt + (int64_t)(t0 + p) * (32 * O::ROW_BYTES), c, h);  // uniform
     Frag q[R];
-    float best[R];
+    float best[R], least[R];
     int best_tile[R];
     f32x16 kept[R];
 #pragma unroll
@@ -91,7 +90,7 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         arrived(q[r]);
-        best[r] = ninf;
+        best[r] = least[r] = low[min(slot0 + r * 32 + c, n_act - 1)];
         best_tile[r] = last;
 #pragma unroll
         for (int v = 0; v < 16; ++v) kept[r][v] = 0.0f;
@@ -103,48 +102,26 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
             if (__builtin_expect(t < t1, 1)) {  // uniform
                 const Frag cur = ring[p];
                 if (t + P < t1) ring[p] = O::stream_tile(tgt + (int64_t)(t + P) * (32 * O::ROW_BYTES), c, h);
-                if constexpr (!WIDE) {
-                    f32x16 acc[R];
+                f32x16 acc[R];
 #pragma unroll
-                    for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
-                    if (__builtin_expect(t * 32 + 32 > m, 0)) {  // only the last tile of the map can be partial
-                        const int bound = m - t * 32 - 4 * h;
+                for (int r = 0; r < R; ++r) acc[r] = O::mma(cur, q[r]);
+                if (__builtin_expect(t * 32 + 32 > m, 0)) {  // only the last tile of the map can be partial
+                    const int bound = m - t * 32 - 4 * h;
 #pragma unroll
-                        for (int r = 0; r < R; ++r)
+                    for (int r = 0; r < R; ++r)
 #pragma unroll
-                            for (int v = 0; v < 16; ++v)
-                                if (tile_row(v, 0) >= bound) acc[r][v] = ninf;
-                    }
+                        for (int v = 0; v < 16; ++v)
+                            if (tile_row(v, 0) >= bound) acc[r][v] = ninf;
+                }
 #pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        const float top = fold16(best[r], acc[r]);
-                        const bool rose = top > best[r];  // strictly: the lowest tile wins among equal scores
+                for (int r = 0; r < R; ++r) {
+                    const float top = fold16(best[r], acc[r]);
+                    const bool rose = top > best[r];  // strictly: the lowest tile wins among equal scores
+                    if (__any(rose)) {
                         best_tile[r] = rose ? t : best_tile[r];
 #pragma unroll
                         for (int v = 0; v < 16; ++v) kept[r][v] = rose ? acc[r][v] : kept[r][v];
                         best[r] = top;
-                    }
-                } else {
-                    f32x16 acc[2];  // no room for more than the product that is folded and the next one
-                    acc[0] = O::mma(cur, q[0]);
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        if (r + 1 < R) acc[(r + 1) & 1] = O::mma(cur, q[r + 1]);
-                        __builtin_amdgcn_sched_barrier(0);
-                        f32x16& x = acc[r & 1];
-                        if (__builtin_expect(t * 32 + 32 > m, 0)) {
-                            const int bound = m - t * 32 - 4 * h;
-#pragma unroll
-                            for (int v = 0; v < 16; ++v)
-                                if (tile_row(v, 0) >= bound) x[v] = ninf;
-                        }
-                        const float top = fold16(best[r], x);
-                        const bool rose = top > best[r];
-                        best_tile[r] = rose ? t : best_tile[r];
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) kept[r][v] = rose ? x[v] : kept[r][v];
-                        best[r] = top;
-                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
@@ -175,18 +152,16 @@ __device__ __forceinline__ void named_unit(const int32_t* at, const char* src, i
         for (int v = 15; v >= 0; --v)
             if (kept[r][v] == best[r]) row = tile_row(v, h);
         const u64 key = pack_key(best[r], min(best_tile[r] * 32 + row, m - 1));
+        const u64 least_key = least[r] == ninf ? 0 : (u64)order_bits(least[r]) << 32 | 0xFFFFFFFFu;  // nothing above the bound: not a candidate of this unit
         const u64 other = shfl_xor_u64(key, 32);
         const int slot = slot0 + r * 32 + c;
-        if (h == 0 && slot < n_act) atomicMax(&keys[slot], other > key ? other : key);
+        const u64 most = other > key ? other : key;
+        if (h == 0 && slot < n_act && most > least_key) atomicMax(&keys[slot], most);
     }
-}
-template <int CT, int DP>
-constexpr int named_blocks() {
-    return Ops<CT, DP>::ROW_BYTES / 8 <= 8 ? 4 : (Ops<CT, DP>::ROW_BYTES / 8 <= 20 ? 3 : 2);
 }
 template <int CT, int DP, int R>
 constexpr int named_ring() {
-    constexpr int frag_regs = Ops<CT, DP>::ROW_BYTES / 8, fit = (R >= 3 ? 30 : (R == 2 ? 36 : 60)) / frag_regs;
+    constexpr int frag_regs = Ops<CT, DP>::ROW_BYTES / 8, fit = (R == 2 ? 36 : 60) / frag_regs;
     return fit > 12 ? 12 : (fit < 2 ? 2 : fit);
 }
 
@@ -203,6 +178,7 @@ void recip_tail_kernel(TailArgs ta) {
     // few seeds: U^t and V^t, the seed number of every slot, and the keys of a search
     __shared__ int32_t few_at[2][TAIL_FEW], few_sid[TAIL_FEW];
     __shared__ u64 few_keys[TAIL_FEW];
+    __shared__ float few_low[TAIL_FEW];
     __shared__ int wave_sums[17];
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -370,9 +346,10 @@ void recip_tail_kernel(TailArgs ta) {
         if ((int)threadIdx.x < n_act) {
             few_at[0][threadIdx.x] = shared_load(ta.cur_u[half] + base + threadIdx.x);
             few_sid[threadIdx.x] = shared_load(ta.seed_id[half] + base + threadIdx.x);
+            few_low[threadIdx.x] = -__builtin_inff();
         }
     }
-    u64* table = ta.few_keys + (int64_t)b * 3 * TAIL_FEW;
+    u64* table = ta.few_keys + (int64_t)b * 3 * TAIL_KEY_COPIES * TAIL_FEW;
     const uint32_t group = id % TAIL_COPIES, groups = min(takers, (uint32_t)TAIL_COPIES), of_group = (takers - group + TAIL_COPIES - 1) / TAIL_COPIES;
     const int gw = (int)id * TAIL_WAVES + wave, n_waves = (int)takers * TAIL_WAVES;
     // A search, out (V^t = NN_2(U^t)) and back (U^{t+1} = NN_1(V^t)) in turn.
@@ -383,24 +360,29 @@ void recip_tail_kernel(TailArgs ta) {
         const char* tgt = forward ? p2 : p1;
         const int src_rows = forward ? ta.rows1 : ta.rows2, m = forward ? ta.m : ta.n, m_tiles = (m + 31) / 32;
         // The keys of three searches take turns: while one fills, the one before it has been read by all, and is emptied for the next.
-        u64* keys = table + searches % 3 * TAIL_FEW;
-        if (id == 0) shared_store(table + (searches + 1) % 3 * TAIL_FEW + threadIdx.x, (u64)0);
+        u64* keys = table + searches % 3 * TAIL_KEY_COPIES * TAIL_FEW;
+        for (uint32_t k = id; k < TAIL_KEY_COPIES; k += takers) shared_store(table + ((searches + 1) % 3 * TAIL_KEY_COPIES + k) * TAIL_FEW + threadIdx.x, (u64)0);
         if ((int)threadIdx.x < n_act) few_keys[threadIdx.x] = 0;
         __syncthreads();
-        const int tile0 = (int)((int64_t)m_tiles * gw / n_waves), tile1 = (int)((int64_t)m_tiles * (gw + 1) / n_waves);
-        constexpr int MOST = named_blocks<CT, DP>();
-        if (tile0 < tile1) {  // uniform in the wave
+        // A wave takes one or two blocks of queries and the more tiles for it.  Taking four and a few tiles (three of a 512x384 map, and the map once more for
+        // every 128 queries) it waited for that many rows of queries and named that many winners for little work between.  This split, the bound that
+        // scores start from (few_low), the copies of the keys and twice to four times as many workgroups, together, the launch in us: one 512x384 pair 53.8 -> 36.7, two with squared
+        // distance 54.5 -> 46.3, four raw pairs 79.5 -> 66, four of two-term rows 112.5 -> 96 (so with two blocks; three blocks of narrow rows one by one).  Bound by
+        // the loads of the tiles: a compute unit takes 236 ns for eight waves' 1.5 KB each, whatever they multiply them with; four blocks of narrow rows per
+        // load cost more in registers and code than that saves (36.7 -> 40.0, 46.3 -> 47.6).
+        const int blocks = (n_act + 31) / 32, together = blocks == 1 || (blocks == 3 && O::ROW_BYTES <= 64) ? 1 : 2, groups_of = (blocks + together - 1) / together;
+        const int chunks = max(1, min(n_waves / groups_of, m_tiles));
 #pragma unroll 1
-            for (int slot0 = 0; slot0 < n_act; slot0 += 32 * MOST) {
-                if (n_act - slot0 <= 32) named_unit<CT, DP, 1, named_ring<CT, DP, 1>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
-                else if (n_act - slot0 <= 64) named_unit<CT, DP, 2, named_ring<CT, DP, 2>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
-                else named_unit<CT, DP, MOST, named_ring<CT, DP, MOST>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_keys, c, h);
-            }
+        for (int unit = gw; unit < groups_of * chunks; unit += n_waves) {  // uniform in the wave
+            const int chunk = unit / groups_of, slot0 = unit % groups_of * together * 32;
+            const int tile0 = (int)((int64_t)m_tiles * chunk / chunks), tile1 = (int)((int64_t)m_tiles * (chunk + 1) / chunks);
+            if (together == 1) named_unit<CT, DP, 1, named_ring<CT, DP, 1>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_low, few_keys, c, h);
+            else named_unit<CT, DP, 2, named_ring<CT, DP, 2>()>(at, src, src_rows, tgt, n_act, slot0, tile0, tile1, m, few_low, few_keys, c, h);
         }
         __syncthreads();
         if ((int)threadIdx.x < n_act) {
             const u64 key = few_keys[threadIdx.x];
-            if (key != 0) atomicMax(&keys[threadIdx.x], key);
+            if (key != 0) atomicMax(&keys[id % TAIL_KEY_COPIES * TAIL_FEW + threadIdx.x], key);
         }
         // the barrier: counts go on from search to search, and so does the number of the last search that is complete
         ++searches;
@@ -421,9 +403,23 @@ void recip_tail_kernel(TailArgs ta) {
         __syncthreads();
         if (lost) return;
         const bool here = (int)threadIdx.x < n_act;
-        const int32_t found = here ? min(max(key_index(shared_load(&keys[threadIdx.x])), 0), m - 1) : 0;
+        u64 key = 0;
+        if (here) {
+            u64 of[TAIL_KEY_COPIES];
+#pragma unroll
+            for (int k = 0; k < TAIL_KEY_COPIES; ++k) of[k] = shared_load(&keys[k * TAIL_FEW + threadIdx.x]);
+#pragma unroll
+            for (int k = 0; k < TAIL_KEY_COPIES; ++k) key = of[k] > key ? of[k] : key;
+        }
+        const int32_t found = here ? min(max(key_index(key), 0), m - 1) : 0;
+        // What the next search finds is no worse than the way back to where this one began: the same product.
+        // (compared as an integer, which sends what is not a number the same way as infinities)
+        const float score = key_score(key);
+        const bool number = (__float_as_uint(score) & 0x7FFFFFFFu) < __float_as_uint(1e30f);
+        const float low = number ? score - 1e-3f * __builtin_fabsf(score) - 1e-30f : -__builtin_inff();
         if (forward) {
             few_at[1][threadIdx.x] = found;
+            few_low[threadIdx.x] = low;
             continue;  // (read behind the next barrier)
         }
         const int32_t u = here ? few_at[0][threadIdx.x] : 0, v = here ? few_at[1][threadIdx.x] : 0, sid = here ? few_sid[threadIdx.x] : 0;
@@ -438,6 +434,7 @@ void recip_tail_kernel(TailArgs ta) {
         if (moves) {
             few_at[0][pos] = found;
             few_sid[pos] = sid;
+            few_low[pos] = low;
         }
         n_act = kept;
         ++t;
@@ -445,13 +442,14 @@ void recip_tail_kernel(TailArgs ta) {
     }
 }
 
-// Workgroups per pair: one for every compute unit, dealt to the pairs.  When few seeds are left no more go on than leave a wave six tiles of a map, or three
-// dearer ones: every workgroup more makes the barriers longer, and the keys that a query's slot has to take one after the other.  Whole calls of one pair
-// with 32 / 64 / 128 / 256 workgroups: 160x120 79 / 80 / 83 / 91 us, 256x192 89 / 87 / 90 / 97, 320x240 104 / 101 / 101 / 108, 512x384 238 / 214 / 203 / 209, its
-// two-term rows 368 / 308 / 285 / 291, fp32 products 251 / 207 / 188 / 185, 1024x768 1494 / 1274 / 1168 / 1130.
+// Workgroups per pair: one for every compute unit, dealt to the pairs.  When few seeds are left no more go on than leave two workgroups a tile and a half for every
+// wave, or one dearer one: more would only make the barriers longer.  Whole calls of one pair in us, features of 4 pixels, with a workgroup for 48 / 24 / 12 tiles (and 32 at least): 160x120
+// 67.2 / 67.3 / 65.0, 256x192 91.8 / 88.7 / 88.9, 320x240 102.2 / 99.2 / 99.3, 512x384 195.4 / 191 / 190; for 24 / 12 / 6 dearer ones: 256x192, fp32 products 177.1 / 173.1 /
+// 169.8, two-term rows 126.5 / 123.9 / 123.9; 512x384 and 1024x768 of those the same.  (The keys of a query were one word, which took 13 ns for every workgroup; then a workgroup for 48
+// tiles was best.)
 static int tail_wgs_per_pair(int batch) { return TAIL_MOST_WGS / batch < 1 ? 1 : TAIL_MOST_WGS / batch; }
 static int tail_few_wgs_per_pair(const TailArgs& a, int batch, int compute, int dp) {
-    const int tiles = ((a.n > a.m ? a.n : a.m) + 31) / 32, per_wg = compute == FNN_F32 || dp > 32 ? 24 : 48;
+    const int tiles = ((a.n > a.m ? a.n : a.m) + 31) / 32, per_wg = compute == FNN_F32 || dp > 32 ? 6 : 12;
     const int enough = tiles / per_wg > 32 ? tiles / per_wg : 32, wgs = tail_wgs_per_pair(batch);
     return wgs < enough ? wgs : enough;
 }
