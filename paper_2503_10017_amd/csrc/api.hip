@@ -375,9 +375,10 @@ bool raw_rows(int32_t batch, const fnn_map* maps) {
 bool raw_options(const fnn_opts* opts) {
     return opts->flags == 0 && (opts->compute == FNN_F16 || opts->compute == FNN_BF16);
 }
-// Maps that the quantise launch reads where they are, and prepares on the way: the same, and with two-term rows.
+// Maps that the quantise launch reads where they are, and prepares on the way: the same, and with two-term rows, or with rows that are to be normalised.
 bool raw_quantise(int32_t batch, const fnn_map* a, const fnn_map* b, const fnn_opts* opts) {
-    return (raw_options(opts) || opts->flags == FNN_FLAG_SPLIT) && raw_rows(batch, a) && raw_rows(batch, b);
+    const bool normalised = opts->flags == FNN_FLAG_NORMALIZE && opts->compute != FNN_F32;
+    return (raw_options(opts) || opts->flags == FNN_FLAG_SPLIT || normalised) && raw_rows(batch, a) && raw_rows(batch, b);
 }
 bool raw_first_search(int32_t batch, const fnn_map* a, const fnn_map* b, const fnn_opts* opts, int64_t n_queries) {
     return raw_options(opts) && first_search_applies(n_queries, a[0].n, batch) && first_search_applies(n_queries, b[0].n, batch) &&
@@ -710,6 +711,7 @@ int32_t fnn_nearest(int32_t batch, const fnn_map* src, const int32_t* q_idx, int
         }
         qa.batch = batch;
         qa.raw_rows = raw ? 1 : 0;
+        qa.normalize = (opts->flags & FNN_FLAG_NORMALIZE) ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = C.zero_words;
@@ -898,6 +900,7 @@ static int32_t reciprocal_impl(int32_t batch, const fnn_map* d1, const fnn_map* 
         fill_quantise_side(qa.side[1], batch, d2, raw, p2, bs2, L.maps.m_pad, C.map[1]);
         qa.batch = batch;
         qa.raw_rows = raw ? 1 : 0;
+        qa.normalize = (opts->flags & FNN_FLAG_NORMALIZE) ? 1 : 0;
         qa.seg_pixels = SEG_PIXELS;
         qa.lower = C.lower;
         qa.lower_count = C.zero_words;
@@ -1171,6 +1174,7 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
         fill_quantise_side(qa.side[1], batch, d2, raw, (const char*)L.maps.p2, L.maps.bstride2, L.maps.m_pad, C.args.map[1]);
         qa.batch = batch;
         qa.raw_rows = raw ? 1 : 0;
+        qa.normalize = (opts->flags & FNN_FLAG_NORMALIZE) ? 1 : 0;
         qa.seg_pixels = C.args.seg_pixels;
         qa.lower = C.args.sample_lower;
         qa.lower_count = C.sample_words;

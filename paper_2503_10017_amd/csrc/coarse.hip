@@ -22,6 +22,7 @@
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
 #include "query_rows.hpp"
+#include "row_norm.hpp"
 #include "side_jobs.hpp"
 #include "trace.hpp"
 
@@ -89,13 +90,15 @@ __device__ __forceinline__ float workgroup_max(float x, float* word) {  // x >= 
 
 // One workgroup turns one segment of prepared rows into 8-bit rows, a thread ROWS of them.  Between the segment's largest value
 // and the rounding the rows stay in registers, or, where they are too many (RELOAD), are read a second time.
-// RAW: the rows are the caller's fp32 rows of 24 channels; they are rounded to the compute format here and the
-// prepared map is written too.  Two-term rows, 160 bytes each, go through LDS so that a wave writes 16 bytes of a row beside the next 16 (four pairs of
+// RAW: the rows are the caller's fp32 rows of 24 channels; they are divided by their norm, if the call says so, and rounded to the compute format here, and the
+// prepared map is written too (four raw pairs of 517x389 and 433x301 pixels, normalised: a prepare launch and this one 65.7 us, this one alone 50.1).  Two-term rows, 160 bytes each, go through LDS so that a wave writes 16 bytes of a row beside the next 16 (four pairs of
 // 512x384, the whole call: a prepare launch and a second reading of the caller's rows 627 us, every thread writing its own row 618, so 585).  Bound by memory.
-template <int CT, int DP, bool SPLIT, bool RAW, int THREADS, int ROWS, bool RELOAD>
+enum QuantiseRows { ROWS_PREPARED, ROWS_RAW, ROWS_RAW_NORMALIZED };
+template <int CT, int DP, bool SPLIT, QuantiseRows FROM, int THREADS, int ROWS, bool RELOAD>
 __global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
     using Row = PreparedRow<CT, DP, SPLIT>;
     constexpr int K = Row::CHANNELS, SEGMENT = THREADS * ROWS, KEPT = RELOAD ? 1 : ROWS;
+    constexpr bool RAW = FROM != ROWS_PREPARED;
     __shared__ float top[4];  // largest value, remainder, length, and whether a row has no bound
     constexpr int SPLIT_QUADS = DP / 8;  // a prepared two-term row, in 16-byte pieces
     __shared__ uint4 rows_out[RAW && SPLIT ? THREADS / 64 : 1][RAW && SPLIT ? 32 * SPLIT_QUADS : 1];  // 32 of them per wave, so that they are written side by side
@@ -123,11 +126,26 @@ __global__ __launch_bounds__(THREADS) void quantise_kernel(QuantiseArgs a) {
             using O = Ops<CT, 24>;
             const float4* p = reinterpret_cast<const float4*>(sd.raw[b] + row * sd.raw_stride);
             uint32_t w[12];
+            if constexpr (FROM == ROWS_RAW_NORMALIZED) {
+                float r[24];
 #pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const float4 v = p[q];
-                w[2 * q] = round_pair<CT>(v.x, v.y);
-                w[2 * q + 1] = round_pair<CT>(v.z, v.w);
+                for (int q = 0; q < 6; ++q) {
+                    const float4 v = p[q];
+                    r[4 * q] = v.x;
+                    r[4 * q + 1] = v.y;
+                    r[4 * q + 2] = v.z;
+                    r[4 * q + 3] = v.w;
+                }
+                normalize_aligned_row<24>(r);
+#pragma unroll
+                for (int q = 0; q < 12; ++q) w[q] = round_pair<CT>(r[2 * q], r[2 * q + 1]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    const float4 v = p[q];
+                    w[2 * q] = round_pair<CT>(v.x, v.y);
+                    w[2 * q + 1] = round_pair<CT>(v.z, v.w);
+                }
             }
             if (SPLIT && write) {  // [hi, hi, lo] in image 1, [hi, lo, hi] in image 2, as the prepare pass writes them
                 uint32_t low[12];
@@ -679,39 +697,40 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
 }
 
 // ---- launches --------------------------------------------------------------------------------------
-template <int CT, int DP, bool SPLIT, bool RAW>
+template <int CT, int DP, bool SPLIT, QuantiseRows FROM = ROWS_PREPARED>
 static hipError_t launch_quantise_t(const QuantiseArgs& a, hipStream_t s) {
     const int segs = a.side[0].out.n_segs > a.side[1].out.n_segs ? a.side[0].out.n_segs : a.side[1].out.n_segs;
     const dim3 grid(segs, 2 * a.batch);
-    if (a.seg_pixels == 4096) return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW, 1024, 4, true>, grid, dim3(1024), 0, s, a);
-    if (a.seg_pixels == 2048) return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW, 1024, 2, false>, grid, dim3(1024), 0, s, a);
+    if (a.seg_pixels == 4096) return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, FROM, 1024, 4, true>, grid, dim3(1024), 0, s, a);
+    if (a.seg_pixels == 2048) return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, FROM, 1024, 2, false>, grid, dim3(1024), 0, s, a);
     if (a.seg_pixels != SEG_PIXELS) return hipErrorInvalidValue;
-    return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, RAW, 512, SEG_PIXELS / 512, false>, grid, dim3(512), 0, s, a);
+    return launch(TK_QUANTISE, quantise_kernel<CT, DP, SPLIT, FROM, 512, SEG_PIXELS / 512, false>, grid, dim3(512), 0, s, a);
 }
 hipError_t launch_quantise(const QuantiseArgs& a, int compute, int dp, hipStream_t s) {
-    if (a.raw_rows && a.split_d) return launch_quantise_t<CT_F16, 80, true, true>(a, s);
+    if (a.raw_rows && a.split_d) return launch_quantise_t<CT_F16, 80, true, ROWS_RAW>(a, s);
     if (a.raw_rows) {
-        if (compute == FNN_F16) return launch_quantise_t<CT_F16, 24, false, true>(a, s);
-        return launch_quantise_t<CT_BF16, 24, false, true>(a, s);
+        if (a.normalize) return compute == FNN_F16 ? launch_quantise_t<CT_F16, 24, false, ROWS_RAW_NORMALIZED>(a, s) : launch_quantise_t<CT_BF16, 24, false, ROWS_RAW_NORMALIZED>(a, s);
+        if (compute == FNN_F16) return launch_quantise_t<CT_F16, 24, false, ROWS_RAW>(a, s);
+        return launch_quantise_t<CT_BF16, 24, false, ROWS_RAW>(a, s);
     }
     if (a.split_d) {
-        if (dp == 24) return launch_quantise_t<CT_F16, 24, true, false>(a, s);
-        if (dp == 32) return launch_quantise_t<CT_F16, 32, true, false>(a, s);
-        if (dp == 48) return launch_quantise_t<CT_F16, 48, true, false>(a, s);
-        if (dp == 64) return launch_quantise_t<CT_F16, 64, true, false>(a, s);
-        if (dp == 80) return launch_quantise_t<CT_F16, 80, true, false>(a, s);
-        if (dp == 96) return launch_quantise_t<CT_F16, 96, true, false>(a, s);
+        if (dp == 24) return launch_quantise_t<CT_F16, 24, true>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_F16, 32, true>(a, s);
+        if (dp == 48) return launch_quantise_t<CT_F16, 48, true>(a, s);
+        if (dp == 64) return launch_quantise_t<CT_F16, 64, true>(a, s);
+        if (dp == 80) return launch_quantise_t<CT_F16, 80, true>(a, s);
+        if (dp == 96) return launch_quantise_t<CT_F16, 96, true>(a, s);
     } else if (compute == FNN_F16) {
-        if (dp == 24) return launch_quantise_t<CT_F16, 24, false, false>(a, s);
-        if (dp == 32) return launch_quantise_t<CT_F16, 32, false, false>(a, s);
+        if (dp == 24) return launch_quantise_t<CT_F16, 24, false>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_F16, 32, false>(a, s);
     } else if (compute == FNN_BF16) {
-        if (dp == 24) return launch_quantise_t<CT_BF16, 24, false, false>(a, s);
-        if (dp == 32) return launch_quantise_t<CT_BF16, 32, false, false>(a, s);
+        if (dp == 24) return launch_quantise_t<CT_BF16, 24, false>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_BF16, 32, false>(a, s);
     } else {
-        if (dp == 8) return launch_quantise_t<CT_F32, 8, false, false>(a, s);
-        if (dp == 16) return launch_quantise_t<CT_F32, 16, false, false>(a, s);
-        if (dp == 24) return launch_quantise_t<CT_F32, 24, false, false>(a, s);
-        if (dp == 32) return launch_quantise_t<CT_F32, 32, false, false>(a, s);
+        if (dp == 8) return launch_quantise_t<CT_F32, 8, false>(a, s);
+        if (dp == 16) return launch_quantise_t<CT_F32, 16, false>(a, s);
+        if (dp == 24) return launch_quantise_t<CT_F32, 24, false>(a, s);
+        if (dp == 32) return launch_quantise_t<CT_F32, 32, false>(a, s);
     }
     return hipErrorInvalidValue;
 }

@@ -199,6 +199,7 @@ struct QuantiseArgs {
     QuantiseSide side[2];
     int32_t batch;
     int32_t raw_rows;
+    int32_t normalize;     // (raw_rows, rows that are not two-term) rows are divided by their norm first
     int32_t seg_pixels;    // SEG_PIXELS, 2048 or 4096
     uint32_t* lower;       // bounds to clear
     int64_t lower_count;

@@ -5,6 +5,7 @@
 #include "dense_perm.hpp"
 #include "fnn_device.hpp"
 #include "fnn_kernels.hpp"
+#include "row_norm.hpp"
 #include "side_jobs.hpp"
 #include "trace.hpp"
 
@@ -46,15 +47,6 @@ __device__ __forceinline__ float squared_length(const float (&x)[M]) {
     for (int k = 0; k < N; ++k) sum = __builtin_fmaf(x[k], x[k], sum);
     return sum;
 }
-// A row's first N channels divided by `norm` (FNN_FLAG_NORMALIZE); an all-zero row stays zero.
-template <int N, int M>
-__device__ __forceinline__ void divide_row(float (&x)[M], float norm) {
-    if (norm > 0.0f) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) x[k] = __fdiv_rn(x[k], norm);
-    }
-}
-
 // The norm term of the L2 score, -1/2 |x|^2, as the norm channels hold it: a rounded value and, in a
 // 16-bit format, the rounded remainder.  fp16 ends at 65504: a longer row's term is held at the ends of
 // the two halves' ranges instead of as -inf and the +inf that remains, whose sum is not a number.
@@ -420,10 +412,7 @@ __global__ __launch_bounds__(256) void prep_rows_f32_kernel(PrepArgs a) {
                 v[4 * q + 3] = x.w;
             }
             if (a.normalize) {
-                float sum = 0.0f;
-#pragma unroll
-                for (int e = 0; e < D; ++e) sum = __fadd_rn(sum, __fmul_rn(v[e], v[e]));
-                divide_row<D>(v, __fsqrt_rn(sum));
+                normalize_aligned_row<D>(v);
             }
 #pragma unroll
             for (int e = 0; e < D; ++e) v[e] = round_to_compute(v[e], COMPUTE);

@@ -350,3 +350,29 @@ def test_wide_rows_that_strain_the_bounds(kind, compute, kw):
         return
     same("nearest", a, b, q, compute, **kw)
     same("reciprocal", a, b, q, compute, **kw)
+
+
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+@pytest.mark.parametrize("n,m,batch", [(65536, 66560, 8), (70001, 66561, 8)])
+def test_rows_that_the_quantise_launch_normalises(n, m, batch, compute):
+    """Aligned fp32 rows of 24 channels are divided by the launch that quantises them, all others by a launch of its own; the prepared
+    maps in the workspace are the same bits as those of one step."""
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    a, b = (torch.randn((batch, rows, 24), generator=gen, device="cuda:0") * torch.exp(torch.randn((batch, rows, 1), generator=gen, device="cuda:0"))
+            for rows in (n, m))
+    a[0, 7] = b[1, m - 1] = 0
+    a[1, n - 1] = 1e-30
+    seeds = torch.randint(0, n, (batch, 6000), generator=torch.Generator().manual_seed(1), dtype=torch.int32).cuda()
+    maps = 48 * batch * (up(n, 32) + up(m, 32))
+    kept = []
+    for size in (fnn.fnn_workspace_bytes_opts(batch, n, m, 24, 6000, compute, 6, normalize=True), one_step_bytes("reciprocal", batch, n, m, 24, 6000, compute)):
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda:0")
+        fnn.fnn_trace_begin(64)
+        out = fnn.fnn_reciprocal(a, b, seeds, 6, compute, workspace=ws, normalize=True)
+        torch.cuda.synchronize()
+        names = [name for name, _ in fnn.fnn_trace_end(64)]
+        kept.append((names[0], ws[:maps].clone(), {k: host(v) for k, v in out.items()}))
+    assert [k[0] for k in kept] == ["quantise_kernel", "prep_kernel"]
+    assert torch.equal(kept[0][1], kept[1][1])
+    for k in kept[0][2]:
+        assert np.array_equal(kept[0][2][k], kept[1][2][k]), k
