@@ -574,8 +574,53 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     if (threadIdx.x == 0) n_list = 0;
     for (int i = threadIdx.x; i < REFINE_PART; i += THREADS) keys[i] = 0;
     __syncthreads();
-    for (int base = begin; base < n_act; base += REFINE_SCAN) {  // uniform
-        if (!MASK && every) {
+    // Bits are looked at for the whole range at once where the list has room for what they mark (a look at a quarter of them cost a memory latency and four barriers each;
+    // the three launches of 512x384 244 -> 233 us, the five of 1024x768 1577 -> 1350)
+    bool whole = false;
+    if constexpr (MASK) {
+        constexpr int WIDE = REFINE_MOST / THREADS;  // bits of a thread, 64 or 32
+        static_assert(WIDE == 64 || WIDE == 32, "a word of the table, or half of one");
+        const int slot = begin + (int)threadIdx.x * WIDE;
+        uint64_t need = 0;
+        if (slot < n_act) {
+            const int64_t at = (((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab + slot) / WIDE;
+            if constexpr (WIDE == 64) need = ca.mask[at];
+            else need = reinterpret_cast<const uint32_t*>(ca.mask)[at];
+            if (n_act - slot < WIDE) need &= ((uint64_t)1 << (n_act - slot)) - 1;
+        }
+        const int mine = __popcll(need);
+        int upto = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(upto, d);
+            if (lane >= d) upto += y;
+        }
+        const int count = __shfl(upto, 63);
+        int at = 0;
+        if (lane == 0 && count) at = atomicAdd(&n_list, count);
+        at = __shfl(at, 0) + upto - mine;
+        __syncthreads();
+        const int total = n_list;
+        if (total == 0) return;  // uniform
+        whole = total <= REFINE_LIST;
+        __syncthreads();  // read by every wave
+        if (whole) {
+            for (; need; need &= need - 1, ++at) {
+                int found = slot + __builtin_ctzll(need);
+                if (ca.grouped) found = (found & ~(DENSE_CELL_PIXELS - 1)) + mask_candidate(found & (DENSE_CELL_PIXELS - 1));
+                list_slot[at] = (uint16_t)(found - begin);
+                list_row[at] = (int)query_row(a, qbase, found);
+            }
+        } else if (threadIdx.x == 0) {
+            n_list = 0;
+        }
+        __syncthreads();
+    }
+    const int step = whole ? REFINE_MOST : REFINE_SCAN;
+    for (int base = begin; base < n_act; base += step) {  // uniform
+        if (whole) {
+            // listed above
+        } else if (!MASK && every) {
             // listed side by side: one after the other, PER to a thread, the loads of their rows were a memory latency each (16 512x384 pairs
             // of seeds, about a hundred of each still live in the second iteration: the call 1027 -> 1005 us)
             const int count = min(REFINE_SCAN, n_act - base);
@@ -632,7 +677,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
         __syncthreads();
         const int n = n_list;
         __syncthreads();  // read by every wave before the next round adds to it
-        if (n > REFINE_LIST - REFINE_SCAN || base + REFINE_SCAN >= n_act) {  // uniform
+        if (n > REFINE_LIST - REFINE_SCAN || base + step >= n_act) {  // uniform
             again += n;
             auto sweep = [&](int part, int part_end, auto tail_tag) {
                 constexpr bool TAIL = decltype(tail_tag)::value;
