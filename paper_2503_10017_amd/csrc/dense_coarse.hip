@@ -573,6 +573,12 @@ static double dense_coarse_block(int64_t n, int compute, int dp) { return dense_
 double dense_coarse_limit(int64_t n, int compute, int dp) {
     return 0.85 * (dense_exact(compute, dp) - dense_coarse_block(n, compute, dp)) / (compute != FNN_F32 && dp <= 32 ? 58.0 : dense_second(compute, dp));
 }
+// The model behind the choice, in nanoseconds.  The one-step kernels leave their staged loop where a workgroup meets padding and have few workgroups to share what that leaves
+// uneven: maps that are not whole runs of 4096 queries and 512 candidates take 1.5 to 2.2 times a whole one's time per block, of which 1.4 are counted on.  Two steps cost 45 us of launches, more
+// on large maps.  Measured in one step / two, 16-bit rows of 24 channels: 256x192 1 pair 236 / 252 us, 2 379 / 355, 4 674 / 564, 16 2341 / 1923; 352x256 564 / 455; not whole:
+// 160x120, 16 pairs 738 / 764; 192x144 1 pair 192 / 206, 4 371 / 312, 16 1321 / 829; 224x168 241 / 223, 4 632 / 449, 16 2379 / 1469; 288x216 406 / 324, 4 1819 / 852; 32 channels, 192x144, 8 803 /
+// 515; squared distance, 320x240, 2 1233 / 1253, 256x192, 4 770 / 790; fp32, 128x128, 4 494 / 749, 192x144, 4 1409 / 713; two-term rows, 128x128, 4 253 / 322, 192x144 253 / 275.
+// (A pair that the samples leave to one step pays for them and for its 8-bit maps: some 30 us.)
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2) {
     if (n < 16384 || m < 16384 || (compute != FNN_F32 && dp <= 16)) return -1e30;
     if ((double)m * (n / dense_seg_pixels(n)) * 2.0 > 4e9) return -1e30;  // the candidates' table of a pair would be too large
@@ -581,8 +587,12 @@ double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, i
     const double cells[2] = {m / cell, (grouped ? 2.0 : 1.0) * n / dense_seg_pixels(n)};
     const double again = coarse_cells_again(cells[0], d, l2) / cells[0] + ((grouped ? first_round(cells[1]) : 0.0) + coarse_cells_again(cells[1], d, l2)) / cells[1];
     const double blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
+    const bool whole = n % DENSE_SB_PIXELS == 0 && m % (32 * DENSE_TILES_PER_GROUP) == 0;
+    const bool narrow = compute != FNN_F32 && dp <= 32 && !l2;  // (of the others the second step costs more than counted here, too)
+    const double exact = dense_exact(compute, dp) * (narrow && !whole ? 1.4 : 1.0);
     const double bytes = batch * ((double)(n + m) * (2.0 * row_bytes + 40.0) + 8.0 * n * (m / cell) + 8.0 * m * ((double)n / dense_seg_pixels(n)));
-    return blocks * (dense_exact(compute, dp) - dense_coarse_block(n, compute, dp) - dense_second(compute, dp) * again) - 45000.0 - bytes / 4500.0 - batch * (double)(n + m) * 0.1;
+    const double passes = bytes / 4500.0 + batch * (double)(n + m) * 0.1;  // over maps and tables; most of it hides behind the sweep
+    return blocks * (exact - dense_coarse_block(n, compute, dp) - dense_second(compute, dp) * again) - 45000.0 - (passes < 30000.0 ? passes : 30000.0);
 }
 
 hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s) {

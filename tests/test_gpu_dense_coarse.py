@@ -261,3 +261,27 @@ def test_maxima_of_three_candidates(n, m, batch, compute, d, kw, grouped):
     got, _ = same(a, b, compute, **kw) if not kw else (None, None)
     if got:
         assert (got["nn21"] == 5000).sum() >= batch * (m - 2) and (got["nn12"] == 77).sum() >= batch * (n - 2)
+
+
+@pytest.mark.parametrize("n,m,batch,compute,d,kw,two_steps", [
+    (27648, 27648, 4, "f16", 24, {}, True),      # maps that are not whole runs of 4096 queries
+    (27648, 27648, 1, "f16", 24, {}, False),     # ... one pair of them
+    (37632, 36864, 4, "bf16", 24, {}, True),     # a maximum for every candidate
+    (49152, 49152, 4, "f16", 24, {}, True),      # whole
+    (49152, 49152, 1, "f16", 24, {}, False),
+    (27648, 27649, 8, "f16", 32, {}, True),
+    (16384, 16384, 4, "f16", 24, {}, False),
+])
+def test_which_small_maps_take_two_steps(n, m, batch, compute, d, kw, two_steps):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + m)
+    a = torch.nn.functional.normalize(torch.randn((batch, n, d), generator=gen, device="cuda:0"), dim=2)
+    b = torch.nn.functional.normalize(torch.randn((batch, m, d), generator=gen, device="cuda:0"), dim=2)
+    k = min(n, m) // 2
+    b[:, :k] = torch.nn.functional.normalize(a[:, :k] + 0.3 * b[:, :k], dim=2)
+    if two_steps:
+        same(a, b, compute, **kw)
+    else:
+        fnn.fnn_trace_begin(64)
+        fnn.fnn_mutual_dense(a, b, compute, **kw)
+        torch.cuda.synchronize()
+        assert "dense_select_kernel" not in [name for name, _ in fnn.fnn_trace_end(64)]
