@@ -35,7 +35,7 @@ COMMANDS = {line.split()[0]: line.split(None, 1)[1] for line in __doc__.splitlin
 
 def is_dense_pass1(name):
     """The pass-1 kernel of the dense mode, whichever variant ran."""
-    return "dense_coarse_kernel<" in name or "dense_staged_kernel<" in name or "dense_kernel<" in name
+    return "dense_groups_kernel<" in name or "dense_coarse_kernel<" in name or "dense_staged_kernel<" in name or "dense_kernel<" in name
 
 
 def short(name: str) -> str:
@@ -162,14 +162,14 @@ def hbm_traffic() -> None:
         lines += [f"Average HBM bytes per search over these {n_steps * per_step} searches (read + written): "
                   f"{result['search_kernel_bytes_per_launch']/1e6:.1f} MB; algorithmic bytes per search (bench.py `roofline_hbm.bytes_per_launch`): "
                   f"{alg/1e6:.1f} MB.  16 prepared maps are 144 MiB, their 8-bit copies 96 MiB.", ""]
-    calls = len(per["fetch"].get(next((k for k in per["fetch"] if k.startswith("dense_coarse_kernel")), ""), []))
+    calls = len(per["fetch"].get(next((k for k in per["fetch"] if k.startswith("dense_groups_kernel")), ""), []))
     if calls:
-        parts = ("dense_sample_kernel", "dense_coarse_kernel", "dense_select_kernel", "refine_kernel<1, 24, 8, 4, true>")
+        parts = ("dense_sample_kernel", "dense_groups_kernel", "dense_select_kernel", "refine_kernel<1, 24, 8, 4, true>")
         sums = {k: (sum(mib("fetch", k)) / calls, sum(mib("write", k)) / calls) for k in parts}
         result["dense_kernel_bytes_per_launch"] = round(sum(r + w for r, w in sums.values()) * 1048576)
         lines += ["## pass 1 of the dense mode (cfg 3), MiB read / written per call", "",
                   "; ".join(f"{k} {r:.0f} / {w:.0f}" for k, (r, w) in sums.items()) + ".  The prepared maps are 18 MiB, their 8-bit copies 12, the tables of "
-                  "8-bit maxima 72 and 36.", ""]
+                  "8-bit maxima 72 and 27.", ""]
     sys.path.insert(0, ROOT)
     from bench import csrc_fingerprint
     result["csrc_fingerprint"] = csrc_fingerprint()
@@ -218,9 +218,9 @@ def mfma_utilisation() -> None:
              "    " + COMMANDS["mfma"], "",
              "Per dispatch.  GRBM_GUI_ACTIVE is summed over the 8 XCDs, SQ_VALU_MFMA_BUSY_CYCLES over the 1024 SIMDs; SQ_INSTS_* count wave instructions",
              "(SQ_INSTS_VALU includes the matrix instructions).  A 32x32 product = one K=32 integer matrix instruction.", "",
-             f"| quantity | {first_name}, first search of a step (16 x 3072 queries) | dense_coarse_kernel (cfg 3) |", "|---|---|---|"]
+             f"| quantity | {first_name}, first search of a step (16 x 3072 queries) | dense_groups_kernel (cfg 3) |", "|---|---|---|"]
     lines += [f"| {n} | {x} | {y} |" for n, x, y in zip(names, a, b)]
-    lines += ["", "Of the vector instructions per product, 8 (search) and 16 (dense) are the three-input maxima that fold the scores; the rest is cell",
+    lines += ["", "Of the vector instructions per product, 8 (search) and 11 (dense) are the three-input maxima that fold the scores; the rest is cell",
               "bounds, address arithmetic and (dense) the reduction of the column maxima at the end of a segment."]
     write(f"mfma_utilisation_{SUFFIX}.md", lines)
 
@@ -246,7 +246,7 @@ def lds_l2() -> None:
     kernels = [("coarse_kernel", "max", "coarse_kernel, first search of a step"), ("refine_kernel<1, 24, 8, 4, false>", "max", "refine_kernel, first search of a step"),
                ("search_kernel", "max", "search_kernel, largest launch (fifth search of a step: 16 x ~106 queries)"),
                ("resolve_kernel", "max", "resolve_kernel, first resolve of a step"),
-               ("dense_coarse_kernel<", "mean", "dense_coarse_kernel (cfg 3)"), ("quantise_kernel", "max", "quantise_kernel, largest launch (both maps of 16 pairs)")]
+               ("dense_groups_kernel<", "mean", "dense_groups_kernel (cfg 3)"), ("quantise_kernel", "max", "quantise_kernel, largest launch (both maps of 16 pairs)")]
     lines = ["# LDS and cache counters (rocprofv3 SQ / TCP / TCC counters): bench.py workloads", "", "Commands (two counter runs):", "",
              "    " + COMMANDS["lds"], "    " + COMMANDS["l2"], "",
              "Per dispatch; SQ_BUSY_CYCLES is summed over the shader engines, the cache counters over all channels.", "",
