@@ -238,10 +238,10 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     a.n_col_cells = (int32_t)((n + col_cell - 1) / col_cell);
     // Tables of scores: the candidates' of as many pairs at a time as 512 MB hold (all of a pair's), their queries' a run of 128 MB at a time.  (Groups
     // of four 512x384 pairs instead of eight cost 1 %.)
-    const size_t pixels2 = (size_t)a.map[1].n_segs * a.seg_pixels, col_cells = (size_t)a.map[0].n_segs << a.grouped;
-    const size_t cols = col_cells * (a.grouped ? pixels2 / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS : pixels2) * sizeof(uint16_t);
-    const size_t scores = a.map[0].n_segs * pixels2 * sizeof(uint16_t);  // one for every candidate and segment
-    const int64_t together = scores > 0 && scores < ((size_t)512 << 20) ? (int64_t)(((size_t)512 << 20) / scores) : 1;
+    const size_t pixels2 = (size_t)a.map[1].n_segs * a.seg_pixels;
+    const size_t cols = a.map[0].n_segs * pixels2 * sizeof(uint16_t);  // one for every candidate and segment; groups in half segments need three quarters of that
+    static_assert(2 * DENSE_CELL_GROUPS <= DENSE_CELL_PIXELS, "the groups' table fits in the other's place");
+    const int64_t together = cols > 0 && cols < ((size_t)512 << 20) ? (int64_t)(((size_t)512 << 20) / cols) : 1;
     const int64_t groups = (batch + together - 1) / together;
     L.group = (int32_t)((batch + groups - 1) / groups);
     const int64_t per_sb = L.group * a.n_cells * (int64_t)DENSE_SB_PIXELS * (int64_t)sizeof(uint16_t);
@@ -253,16 +253,18 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     a.best[0] = (uint16_t*)cv.take((size_t)per_sb * L.slab);
     a.best[1] = (uint16_t*)cv.take((size_t)L.group * cols);
     a.mask[0] = (uint64_t*)cv.take((size_t)per_sb * L.slab / 16);
-    a.mask[1] = (uint64_t*)cv.take((size_t)L.group * col_cells * pixels2 / 8);
+    a.mask[1] = (uint64_t*)cv.take((size_t)L.group * ((size_t)a.map[0].n_segs << a.grouped) * pixels2 / 8);
     if (a.grouped) a.least = (float*)cv.take((size_t)L.group * (pixels2 / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS) * sizeof(float));
     L.swept = (char*)cv.take((size_t)L.group * maps.bstride1);
     a.pixels[0] = n;
     a.pixels[1] = m;
     a.sample_upper[0] = (float*)cv.take((size_t)batch * a.n_cells * DENSE_SAMPLES * sizeof(float));
     a.sample_upper[1] = (float*)cv.take((size_t)batch * a.n_col_cells * DENSE_SAMPLES * sizeof(float));
+    if (a.grouped) a.sample_group = (float*)cv.take((size_t)batch * a.n_col_cells * DENSE_SAMPLES * sizeof(float));
     const size_t zeros = cv.used;
     a.sample_lower = (uint32_t*)cv.take((size_t)batch * 2 * DENSE_SAMPLES * sizeof(uint32_t));
-    a.marked = (int32_t*)cv.take((size_t)batch * 2 * sizeof(int32_t));
+    if (a.grouped) a.sample_best = (uint32_t*)cv.take((size_t)batch * DENSE_SAMPLES * sizeof(uint32_t));
+    a.marked = (int32_t*)cv.take((size_t)(batch + 1) * DENSE_MARKS * sizeof(int32_t));
     L.sample_words = (int64_t)((cv.used - zeros) / sizeof(uint32_t));
     return L;
 }
@@ -449,6 +451,7 @@ hipError_t dense_group(const DenseCoarseLayout& C, const DenseLayout& L, const S
         ca.mask = da.mask[0];
         ca.slab = da.n_sb * DENSE_SB_PIXELS;
         ca.n_cells = da.n_cells;
+        ca.slot_pitch = (int64_t)da.n_cells * (ca.slab / 64);
         ca.cell_shift = da.cell_runs == 4 ? 2 : (da.cell_runs == 2 ? 1 : 0);
         ca.first_slot = sb * DENSE_SB_PIXELS;
         ca.side = 0;
@@ -458,15 +461,15 @@ hipError_t dense_group(const DenseCoarseLayout& C, const DenseLayout& L, const S
     if (!at_once) e = launch_dense_select(da, 1, 1, nullptr, pairs, s);
     ca.mask = da.mask[1];
     ca.slab = da.map[1].n_segs * da.seg_pixels;
-    ca.n_cells = da.map[0].n_segs << da.grouped;
-    ca.cell_shift = (da.seg_pixels == 4096 ? 2 : 1) - da.grouped;
-    ca.grouped = da.grouped;
+    ca.n_cells = da.map[0].n_segs;
+    ca.slot_pitch = (int64_t)(da.map[0].n_segs << da.grouped) * (ca.slab / 64);
+    ca.cell_shift = da.seg_pixels == 4096 ? 2 : 1;
     ca.first_slot = 0;
     ca.side = 1;
     if (e == hipSuccess) e = launch_refine(cols, ca, pairs, compute, L.maps.dp, s);
     if (da.grouped) {
         if (e == hipSuccess) e = launch_dense_select(da, 1, 1, cols.out_keys, pairs, s);
-        ca.range = 1;
+        ca.second_round = 1;
         if (e == hipSuccess) e = launch_refine(cols, ca, pairs, compute, L.maps.dp, s);
     }
     sweep.d1 = C.swept;
@@ -477,7 +480,7 @@ hipError_t dense_group(const DenseCoarseLayout& C, const DenseLayout& L, const S
 // Both directions of the dense mode from its 8-bit maps to the keys: pass 1 range by range of image 1, the second step for the queries
 // of a range at once, for the candidates when every range is done; a group of pairs after the other.  Pairs whose samples say that this would be the slower way are swept
 // by the dense kernels of `sweep` instead.
-hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int batch, int64_t n, int64_t m, int compute, DenseArgs sweep, hipStream_t s) {
+hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int batch, int64_t n, int64_t m, int compute, bool l2, DenseArgs sweep, hipStream_t s) {
     SearchArgs rows;
     memset(&rows, 0, sizeof(rows));
     rows.src = (const char*)L.maps.p1;
@@ -502,10 +505,7 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
 
     DenseCoarseArgs da = C.args;
     hipError_t e = launch_dense_sample(da, batch, s);
-    const double limit = dense_coarse_limit(n, compute, L.maps.dp) * DENSE_SAMPLES;
-    da.judge.marked = da.marked;
-    da.judge.weight[0] = (float)(1.0 / (limit * da.n_cells));
-    da.judge.weight[1] = (float)(1.0 / (limit * da.n_col_cells));
+    da.judge = dense_judge(da, batch, compute, L.maps.dp, l2);
     // a launch that leaves every pair alone costs its workgroups' start: no more of them than fill the chip a few times
     auto wgs = [&]() { return (int64_t)C.group * sweep.n_sb * ((sweep.m_tiles + DENSE_TILES_PER_GROUP * sweep.groups_per_wg - 1) / (DENSE_TILES_PER_GROUP * sweep.groups_per_wg)); };
     while (wgs() > 4096) sweep.groups_per_wg *= 2;
@@ -525,7 +525,7 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
             map.row_bound += (int64_t)step * map.n_segs * da.seg_pixels;
             map.seg += (int64_t)step * map.n_segs;
         }
-        da.judge.marked += 2 * step;
+        da.judge.marked += DENSE_MARKS * step;
         sweep.d2 += step * sweep.d2_bstride;
         sweep.row_keys += step * n;
         sweep.col_keys += step * m;
@@ -1164,7 +1164,8 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
 
     // Large maps: 8-bit scores first, then, where the workspace has the room, the second step of the searches in both directions
     DenseCoarseLayout C = carve_dense_coarse(cv, batch, n, m, L.maps, opts->compute);
-    if (cv.used <= workspace_bytes && dense_coarse_gain(n, m, batch, opts->compute, L.maps.dp, d, (opts->flags & FNN_FLAG_L2) != 0) > 0.0) {
+    const bool l2 = (opts->flags & FNN_FLAG_L2) != 0;
+    if (cv.used <= workspace_bytes && dense_coarse_gain(n, m, batch, opts->compute, L.maps.dp, d, l2) > 0.0) {
         const bool raw = raw_quantise(batch, d1, d2, opts);
         if (!raw) FNN_TRY(prep_both(batch, d1, d2, L.maps, d, opts, s, extra));
         QuantiseArgs qa;
@@ -1180,7 +1181,7 @@ int32_t fnn_mutual_dense(int32_t batch, const fnn_map* d1, const fnn_map* d2, co
         qa.lower_count = C.sample_words;
         qa.split_d = (opts->flags & FNN_FLAG_SPLIT) ? d : 0;
         FNN_TRY(launch_quantise(qa, opts->compute, L.maps.dp, s));
-        FNN_TRY(dense_two_steps(C, L, batch, n, m, opts->compute, da, s));
+        FNN_TRY(dense_two_steps(C, L, batch, n, m, opts->compute, l2, da, s));
         FNN_TRY(launch_dense_resolve(da, batch, opts->compute, L.maps.dp, nn12, s12, nn21, s21, s));
         FNN_TRY(launch_dense_final(fa, batch, s));
         return FNN_OK;

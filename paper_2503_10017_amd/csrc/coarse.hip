@@ -544,7 +544,10 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cell = blockIdx.x, b = blockIdx.z;
-    if (MASK && ca.judge.alike(b)) return;
+    const DenseWay way = MASK ? ca.judge.way(b) : DENSE_ONE_STEP;
+    if (MASK && (way == DENSE_ONE_STEP || (ca.second_round && way != DENSE_GROUPS))) return;
+    const bool grouped = MASK && ca.side == 1 && way == DENSE_GROUPS;
+    const int cell_shift = ca.cell_shift - (grouped ? 1 : 0);
     int n_act = a.nq;
     if (a.nq_active) n_act = min(max(a.nq_active[b], 0), a.nq);
     bool every = n_act < ca.min_live;             // step 1 left these queries to this kernel
@@ -552,9 +555,9 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     if (VOTES) every = every || (ca.vote && ca.vote[b].given_up) || (ca.earlier && gives_up(ca.earlier[b], ca.even));
     uint32_t again = 0;
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
-    if (MASK && ca.grouped) n_act = min((n_act + DENSE_CELL_PIXELS - 1) & ~(DENSE_CELL_PIXELS - 1), ca.slab);  // bits that stand for no candidate are 0
+    if (grouped) n_act = min((n_act + DENSE_CELL_PIXELS - 1) & ~(DENSE_CELL_PIXELS - 1), ca.slab);  // bits that stand for no candidate are 0
     int range = ca.range;
-    if (MASK && range < REFINE_MOST && ca.judge.marked[2 * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
+    if (MASK && range < REFINE_MOST && ca.judge.marked[DENSE_MARKS * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
     const int begin = blockIdx.y * range;
     n_act = min(n_act, begin + range);
     const int tile0 = (cell * WAVES + wave) * RT;
@@ -565,6 +568,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     const int64_t qbase = (int64_t)b * a.nq + ca.first_slot;
     const float ninf = -__builtin_inff();
     const uint16_t* upper = ca.upper + ((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab;
+    const int64_t bits = b * ca.slot_pitch * 64 + (int64_t)(cell >> cell_shift) * ca.slab;  // (MASK)
     const uint32_t* lower = ca.lower + (int64_t)b * ca.slot_pitch + ca.first_slot;
     Frag cand[RT];
 #pragma unroll
@@ -583,7 +587,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
         const int slot = begin + (int)threadIdx.x * WIDE;
         uint64_t need = 0;
         if (slot < n_act) {
-            const int64_t at = (((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab + slot) / WIDE;
+            const int64_t at = (bits + slot) / WIDE;
             if constexpr (WIDE == 64) need = ca.mask[at];
             else need = reinterpret_cast<const uint32_t*>(ca.mask)[at];
             if (n_act - slot < WIDE) need &= ((uint64_t)1 << (n_act - slot)) - 1;
@@ -607,7 +611,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
         if (whole) {
             for (; need; need &= need - 1, ++at) {
                 int found = slot + __builtin_ctzll(need);
-                if (ca.grouped) found = (found & ~(DENSE_CELL_PIXELS - 1)) + mask_candidate(found & (DENSE_CELL_PIXELS - 1));
+                if (grouped) found = (found & ~(DENSE_CELL_PIXELS - 1)) + mask_candidate(found & (DENSE_CELL_PIXELS - 1));
                 list_slot[at] = (uint16_t)(found - begin);
                 list_row[at] = (int)query_row(a, qbase, found);
             }
@@ -635,7 +639,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
             if (slot < n_act) {
                 if constexpr (MASK) {
                     static_assert(PER <= 16, "a thread's bits lie in one 16-bit word");
-                    const int64_t word = (((int64_t)b * ca.n_cells + (cell >> ca.cell_shift)) * ca.slab + slot) / 16;
+                    const int64_t word = (bits + slot) / 16;
                     need = (uint32_t)reinterpret_cast<const uint16_t*>(ca.mask)[word] >> (slot & 15) & ((1u << PER) - 1);
                 } else {
                     // the tables' rows hold whole 64s of slots: all PER are there
@@ -653,7 +657,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
                         if (up >= unorder_bits(lw)) need |= 1u << i;
                     }
                 }
-                if (!(MASK && ca.grouped) && n_act - slot < PER) need &= (1u << (n_act - slot)) - 1;
+                if (!grouped && n_act - slot < PER) need &= (1u << (n_act - slot)) - 1;
             }
             // a prefix sum over the wave, one LDS atomic for its total
             const int mine = __popc(need);
@@ -669,7 +673,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
             at = __shfl(at, 0) + upto - mine;
             for (; need; need &= need - 1, ++at) {
                 int found = slot + __builtin_ctz(need);
-                if (MASK && ca.grouped) found = (found & ~(DENSE_CELL_PIXELS - 1)) + mask_candidate(found & (DENSE_CELL_PIXELS - 1));
+                if (grouped) found = (found & ~(DENSE_CELL_PIXELS - 1)) + mask_candidate(found & (DENSE_CELL_PIXELS - 1));
                 list_slot[at] = (uint16_t)(found - begin);
                 list_row[at] = (int)query_row(a, qbase, found);
             }
@@ -890,9 +894,8 @@ static hipError_t launch_refine_t(const SearchArgs& a, CoarseArgs ca, int batch,
     // pixels, both launches with ranges of 16384 / 4096: 1104 / 548 us); but each reads its tiles again and fills up its last block, so they are taken
     // while the workgroups are few and where the samples say that the lists are long (features of one pixel, four pairs: 324 / 365 us; 1024x768
     // 1085 / 1662).  Rows that cost more per product lose more to the last block of a list than they gain (fp32, 384x288, features of one pixel 356 / 794).
-    const bool short_lists = ca.range != 0;
     ca.range = REFINE_MOST;
-    if (MASK && CT != CT_F32 && DP <= 32 && !short_lists)
+    if (MASK && CT != CT_F32 && DP <= 32 && !ca.second_round)  // (what the second round lists is little)
         for (ca.range = REFINE_SCAN; ca.range < REFINE_MOST && cells * ((slots + ca.range - 1) / ca.range) * batch > 16384;) ca.range *= 2;
     const unsigned ranges = (unsigned)((slots + ca.range - 1) / ca.range);
     return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES, MASK>, dim3(cells, ranges, batch), dim3(64 * WAVES), 0, s, a, ca);

@@ -243,7 +243,7 @@ template <int CT, int DP>
 __global__ __launch_bounds__(DENSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<CT, DP>())))
 void dense_kernel(DenseArgs a) {
     extern __shared__ u64 lds[];
-    if (a.judge.marked && !a.judge.alike(blockIdx.z)) return;
+    if (a.judge.way(blockIdx.z) != DENSE_ONE_STEP) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     u64* col_keys = lds + (size_t)a.sb_per_wg * DENSE_S * 32;
     dense_workgroup<CT, DP>(a, lds, col_keys + wave * (DENSE_J * 32),
@@ -416,7 +416,7 @@ __device__ __forceinline__ void dense_sweep_staged(const DenseArgs& a, const typ
 template <int CT>
 __global__ __launch_bounds__(DENSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void dense_staged_kernel(DenseArgs a) {
-    if (a.judge.marked && !a.judge.alike(blockIdx.z)) return;
+    if (a.judge.way(blockIdx.z) != DENSE_ONE_STEP) return;
     using O = Ops<CT, 24>;
     using Frag = typename O::Frag;
     constexpr int J = DENSE_J, S = DENSE_S;

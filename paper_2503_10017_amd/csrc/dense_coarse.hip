@@ -83,22 +83,24 @@ __device__ __forceinline__ void dense_permute(const DenseSwept& w, int b) {
 // (16 per block; 35.7 ns per block and SIMD in a bare loop, here 43) 1601 / 7745 us, groups of three 1281 / 6340, with the order of products and maxima 1207 / 6240, with eight
 // resident tiles instead of four 1154 / 5950 (31 ns).  Larger groups, in the compiler's order and with four tiles: of five 1212 / 6040, of a whole half tile 1125 / 5785; but of 192
 // cells groups of five leave 25 to multiply again, half tiles 60.  Without groups the order of products and maxima and more tiles have no registers and gain nothing.
+struct SweepLds {  // (two variables for the stage, see dense_staged_kernel)
+    uint4 (&stage0)[COARSE_TURN][64];
+    uint4 (&stage1)[COARSE_TURN][64];
+    int (&row_best)[DENSE_SB_PIXELS];  // best score of every query in the cell
+};
 template <int SEGMENT, bool GROUPED>
-__device__ __forceinline__ void dense_sweep(const DenseCoarseArgs& a) {
+__device__ __forceinline__ void dense_sweep(const DenseCoarseArgs& a, const SweepLds& lds) {
     constexpr int DC_J = GROUPED ? 8 : 4;          // candidate tiles resident per wave
     constexpr int DC_GROUP = COARSE_WAVES * DC_J;  // tiles of a workgroup
     constexpr int DC_KEPT = GROUPED ? GROUPS : 16; // maxima of a tile that a lane keeps
     constexpr int CELL_GROUPS = CELL_TILES / DC_GROUP;
     static_assert(CELL_GROUPS * DC_GROUP == CELL_TILES, "a cell is whole groups of tiles");
-    __shared__ uint4 stage0[COARSE_TURN][64], stage1[COARSE_TURN][64];  // two variables, see dense_staged_kernel
-    __shared__ int row_best[DENSE_SB_PIXELS];                           // best score of every query in the cell
+    auto& stage0 = lds.stage0;
+    auto& stage1 = lds.stage1;
+    auto& row_best = lds.row_best;
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cell0 = blockIdx.x * a.cells_per_wg, sb = blockIdx.y, b = blockIdx.z;
-    if (a.judge.alike(b)) {
-        if (a.swept.to) dense_permute(a.swept, b);
-        return;
-    }
     constexpr int COL_CELL = GROUPED ? SEGMENT / 2 : SEGMENT, COL_CELLS = DENSE_SB_PIXELS / COL_CELL, COL_TURNS = DC_TURNS / COL_CELLS;
     static_assert(COL_TURNS % 2 == 0, "a cell starts on stage slot 0");
     const int64_t pixels1 = (int64_t)a.map[0].n_segs * SEGMENT, pixels2 = (int64_t)a.map[1].n_segs * SEGMENT;
@@ -106,7 +108,7 @@ __device__ __forceinline__ void dense_sweep(const DenseCoarseArgs& a) {
     const char* tiles = a.map[1].rows + (int64_t)b * pixels2 * COARSE_ROW_BYTES;
     uint16_t* rows = a.best[0] + ((int64_t)b * a.n_cells + cell0) * ((int64_t)a.n_sb * DENSE_SB_PIXELS) + (int64_t)sb * DENSE_SB_PIXELS;
     const int64_t col_pitch = GROUPED ? pixels2 / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS : pixels2;
-    uint16_t* cols = a.best[1] + ((int64_t)b * a.map[0].n_segs * (SEGMENT / COL_CELL) + (int64_t)(a.first_sb + sb) * COL_CELLS) * col_pitch;
+    uint16_t* cols = a.best[1] + b * (a.map[0].n_segs * pixels2) + (int64_t)(a.first_sb + sb) * COL_CELLS * col_pitch;
     // groups of this workgroup's cells that hold a pixel of image 2 (uniform)
     const int cell_groups = CELL_GROUPS * a.cell_runs, group0 = cell0 * cell_groups;
     const int n_groups = min(a.cells_per_wg * cell_groups, (a.n_tiles[1] + DC_GROUP - 1) / DC_GROUP - group0);
@@ -243,14 +245,36 @@ __device__ __forceinline__ void dense_sweep(const DenseCoarseArgs& a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // the turn past the last one has landed too
 }
+#define FNN_SWEEP_LDS                                                   \
+    __shared__ uint4 stage0[COARSE_TURN][64], stage1[COARSE_TURN][64]; \
+    __shared__ int row_best[DENSE_SB_PIXELS];                          \
+    const SweepLds lds = {stage0, stage1, row_best}
 // a maximum for every candidate
 template <int SEGMENT>
 __global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(3)))
-void dense_coarse_kernel(DenseCoarseArgs a) { dense_sweep<SEGMENT, false>(a); }
-// one for every group
+void dense_coarse_kernel(DenseCoarseArgs a) {
+    FNN_SWEEP_LDS;
+    if (a.judge.way(blockIdx.z) == DENSE_ONE_STEP) {
+        if (a.swept.to) dense_permute(a.swept, blockIdx.z);
+    } else {
+        dense_sweep<SEGMENT, false>(a, lds);
+    }
+}
+// one for every group, or for every candidate: a pair has the way that its samples say
 template <int SEGMENT>
 __global__ __launch_bounds__(COARSE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
-void dense_groups_kernel(DenseCoarseArgs a) { dense_sweep<SEGMENT, true>(a); }
+void dense_groups_kernel(DenseCoarseArgs a) {
+    FNN_SWEEP_LDS;
+    const DenseWay way = a.judge.way(blockIdx.z);
+    if (way == DENSE_ONE_STEP) {
+        if (a.swept.to) dense_permute(a.swept, blockIdx.z);
+    } else if (way == DENSE_GROUPS) {
+        dense_sweep<SEGMENT, true>(a, lds);
+    } else {
+        dense_sweep<SEGMENT, false>(a, lds);
+    }
+}
+#undef FNN_SWEEP_LDS
 
 // Which cells may hold the best partner of a slot: the bounds that turn 8-bit scores into products (coarse.hip) give every slot a
 // lower bound of its best score, and a cell whose upper bound reaches it is marked.  A lane takes SELECT_SLOTS slots,
@@ -260,9 +284,10 @@ constexpr int SELECT_WAVES = 4;
 constexpr int SELECT_SLOTS = 4;
 constexpr int SELECT_DEEP = 6;  // cells in flight per wave
 struct SelectSide {
-    const uint16_t* best;       // [batch][table_cells][pitch, or the groups of so many slots]
-    int64_t table_cells;
-    uint64_t* mask;             // [batch][table_cells][pitch / 64]
+    const uint16_t* best;       // [n_cells][pitch, or the groups of so many slots] of every pair,
+    int64_t best_pitch;         // ... so many entries apart
+    uint64_t* mask;             // [n_cells][pitch / 64]
+    int64_t mask_pitch;
     int32_t n_cells;            // that hold a pixel
     int64_t pitch;              // slots, a multiple of 1024
     int32_t cells_per_seg;      // of the other map
@@ -271,7 +296,8 @@ struct SelectSide {
     const SegInfo* seg;         // of the other map, [batch][n_segs]
     int32_t n_segs;
     // groups of slots
-    int32_t grouped;
+    int32_t grouped;            // of the pairs that are DENSE_GROUPS; their cells are half as large
+    int32_t n_group_cells;
     float* least;               // [batch][entries of a cell] the smallest upper bound of the first round's cells
     const u64* keys;            // the second round: [batch][n_keys] what the first left
     int64_t n_keys;
@@ -285,22 +311,25 @@ struct SelectArgs {
 };
 // visit(cell, 8-bit scores of N entries of a lane, 64 apart, their segment) for this wave's cells
 template <int N, int DEEP, typename F>
-__device__ __forceinline__ void for_cells(const SelectSide& a, const uint16_t* column, int64_t row_entries, const SegInfo* seg, int wave, const F& visit) {
-    for (int cell0 = wave; cell0 < a.n_cells; cell0 += SELECT_WAVES * DEEP) {
+__device__ __forceinline__ void for_cells(int n_cells, int cells_per_seg, const uint16_t* column, int64_t row_entries, const SegInfo* seg, int wave, const F& visit) {
+    for (int cell0 = wave; cell0 < n_cells; cell0 += SELECT_WAVES * DEEP) {
         int kept[DEEP][N];
 #pragma unroll
         for (int i = 0; i < DEEP; ++i)
 #pragma unroll
-            for (int e = 0; e < N; ++e) kept[i][e] = (int16_t)column[(int64_t)min(cell0 + i * SELECT_WAVES, a.n_cells - 1) * row_entries + 64 * e];
+            for (int e = 0; e < N; ++e) kept[i][e] = (int16_t)column[(int64_t)min(cell0 + i * SELECT_WAVES, n_cells - 1) * row_entries + 64 * e];
 #pragma unroll
         for (int i = 0; i < DEEP; ++i) {
             const int cell = cell0 + i * SELECT_WAVES;
-            if (cell < a.n_cells) visit(cell, kept[i], seg[cell / a.cells_per_seg]);  // uniform
+            if (cell < n_cells) visit(cell, kept[i], seg[cell / cells_per_seg]);  // uniform
         }
     }
 }
 __device__ __forceinline__ float bound_error(uint32_t bound, const SegInfo& si) {
     return __builtin_fmaf(__uint_as_float(bound & 0xFFFF0000u), si.residual, __uint_as_float(bound << 16) * si.length);
+}
+__device__ __forceinline__ uint32_t worst_bound(uint32_t a, uint32_t b) {  // lengths and remainders are not negative: they order like integers
+    return max(a & 0xFFFF0000u, b & 0xFFFF0000u) | max(a & 0xFFFFu, b & 0xFFFFu);
 }
 __device__ __forceinline__ float upper_score(int kept, const SegInfo& si, float error) {
     return __builtin_fmaf((float)((kept + 1) * (1 << KEPT_SHIFT)), si.scale, error);  // the same wherever it is formed: two rounds share the cells by it
@@ -310,8 +339,8 @@ __device__ __forceinline__ void select_slots(const SelectSide& a, int b, float (
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t slot0 = (int64_t)blockIdx.x * (64 * SELECT_SLOTS);
-    const uint16_t* column = a.best + (int64_t)b * a.table_cells * a.pitch + slot0 + lane;
-    uint64_t* mask = a.mask + ((int64_t)b * a.table_cells * a.pitch + slot0) / 64;
+    const uint16_t* column = a.best + b * a.best_pitch + slot0 + lane;
+    uint64_t* mask = a.mask + b * a.mask_pitch + slot0 / 64;
     const SegInfo* seg = a.seg + (int64_t)b * a.n_segs;
     uint32_t bound[SELECT_SLOTS];
     float best[SELECT_SLOTS];
@@ -320,7 +349,7 @@ __device__ __forceinline__ void select_slots(const SelectSide& a, int b, float (
         bound[e] = a.row_bound[(int64_t)b * a.bound_pitch + slot0 + 64 * e + lane];
         best[e] = -__builtin_inff();
     }
-    for_cells<SELECT_SLOTS, SELECT_DEEP>(a, column, a.pitch, seg, wave, [&](int, const int (&v)[SELECT_SLOTS], const SegInfo& si) {
+    for_cells<SELECT_SLOTS, SELECT_DEEP>(a.n_cells, a.cells_per_seg, column, a.pitch, seg, wave, [&](int, const int (&v)[SELECT_SLOTS], const SegInfo& si) {
 #pragma unroll
         for (int e = 0; e < SELECT_SLOTS; ++e) best[e] = __builtin_fmaxf(best[e], (float)(v[e] * (1 << KEPT_SHIFT)) * si.scale - bound_error(bound[e], si));
     });
@@ -331,7 +360,7 @@ __device__ __forceinline__ void select_slots(const SelectSide& a, int b, float (
     for (int e = 0; e < SELECT_SLOTS; ++e)
 #pragma unroll
         for (int w = 0; w < SELECT_WAVES; ++w) best[e] = __builtin_fmaxf(best[e], low[w][e][lane]);
-    for_cells<SELECT_SLOTS, SELECT_DEEP>(a, column, a.pitch, seg, wave, [&](int cell, const int (&v)[SELECT_SLOTS], const SegInfo& si) {
+    for_cells<SELECT_SLOTS, SELECT_DEEP>(a.n_cells, a.cells_per_seg, column, a.pitch, seg, wave, [&](int cell, const int (&v)[SELECT_SLOTS], const SegInfo& si) {
         uint64_t mine = 0;  // a cell's words are written side by side
 #pragma unroll
         for (int e = 0; e < SELECT_SLOTS; ++e) {
@@ -356,8 +385,8 @@ __device__ __forceinline__ void select_groups(const SelectSide& a, int b, float 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int run = blockIdx.x / SELECT_PARTS, set0 = blockIdx.x % SELECT_PARTS * SELECT_SETS;  // of the run's sets of 64 groups
     const int64_t slot0 = (int64_t)run * DENSE_CELL_PIXELS, row_entries = a.pitch / DENSE_CELL_PIXELS * DENSE_CELL_GROUPS;
-    const uint16_t* column = a.best + (int64_t)b * a.table_cells * row_entries + (int64_t)run * DENSE_CELL_GROUPS + 64 * set0 + lane;
-    uint64_t* mask = a.mask + ((int64_t)b * a.table_cells * a.pitch + slot0) / 64 + 3 * set0;
+    const uint16_t* column = a.best + b * a.best_pitch + (int64_t)run * DENSE_CELL_GROUPS + 64 * set0 + lane;
+    uint64_t* mask = a.mask + b * a.mask_pitch + slot0 / 64 + 3 * set0;
     float* least_of = a.least + (int64_t)b * row_entries + (int64_t)run * DENSE_CELL_GROUPS + 64 * set0 + lane;
     const SegInfo* seg = a.seg + (int64_t)b * a.n_segs;
     int64_t slot[SELECT_SETS][3];
@@ -370,7 +399,7 @@ __device__ __forceinline__ void select_groups(const SelectSide& a, int b, float 
             const bool single = set0 + e == TRIPLE_SETS;  // uniform
             slot[e][k] = slot0 + mask_candidate((3 * (set0 + e) + (single ? 0 : k)) * 64 + lane);
             const uint32_t own = a.row_bound[(int64_t)b * a.bound_pitch + slot[e][k]];
-            bound[e] = max(bound[e] & 0xFFFF0000u, own & 0xFFFF0000u) | max(bound[e] & 0xFFFFu, own & 0xFFFFu);  // not negative: they order like integers
+            bound[e] = worst_bound(bound[e], own);
         }
     }
     const bool last_single = set0 + SELECT_SETS == TRIPLE_SETS + 1;  // uniform: the last of the sets is the single slots
@@ -399,7 +428,7 @@ __device__ __forceinline__ void select_groups(const SelectSide& a, int b, float 
 #pragma unroll
             for (int k = 0; k < 3; ++k) product[e][k] = slot[e][k] < a.n_keys ? key_score(a.keys[(int64_t)b * a.n_keys + slot[e][k]]) : 0.0f;
         }
-        for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a, column, row_entries, seg, wave, [&](int cell, const int (&v)[SELECT_SETS], const SegInfo& si) {
+        for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a.n_group_cells, 2, column, row_entries, seg, wave, [&](int cell, const int (&v)[SELECT_SETS], const SegInfo& si) {
             float upper[SELECT_SETS];
             bool all[SELECT_SETS], left[SELECT_SETS];
 #pragma unroll
@@ -422,7 +451,7 @@ __device__ __forceinline__ void select_groups(const SelectSide& a, int b, float 
     for (int e = 0; e < SELECT_SETS; ++e)
 #pragma unroll
         for (int i = 0; i < GROUP_TOP; ++i) most[e][i] = -__builtin_inff();
-    for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a, column, row_entries, seg, wave, [&](int, const int (&v)[SELECT_SETS], const SegInfo& si) {
+    for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a.n_group_cells, 2, column, row_entries, seg, wave, [&](int, const int (&v)[SELECT_SETS], const SegInfo& si) {
 #pragma unroll
         for (int e = 0; e < SELECT_SETS; ++e) put(most[e], upper_score(v[e], si, bound_error(bound[e], si)));
     });
@@ -438,10 +467,10 @@ __device__ __forceinline__ void select_groups(const SelectSide& a, int b, float 
         for (int w = 1; w < SELECT_WAVES; ++w)
 #pragma unroll
             for (int i = 0; i < GROUP_TOP; ++i) put(most[e], handed[(wave + w) % SELECT_WAVES][e][i][lane]);
-        least[e] = a.n_cells < FEW_CELLS ? most[e][GROUP_TOP_FEW - 1] : most[e][GROUP_TOP - 1];
+        least[e] = a.n_group_cells < FEW_CELLS ? most[e][GROUP_TOP_FEW - 1] : most[e][GROUP_TOP - 1];
         if (wave == 0) least_of[64 * e] = least[e];
     }
-    for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a, column, row_entries, seg, wave, [&](int cell, const int (&v)[SELECT_SETS], const SegInfo& si) {
+    for_cells<SELECT_SETS, SELECT_SETS_DEEP>(a.n_group_cells, 2, column, row_entries, seg, wave, [&](int cell, const int (&v)[SELECT_SETS], const SegInfo& si) {
         bool top[SELECT_SETS];
 #pragma unroll
         for (int e = 0; e < SELECT_SETS; ++e) top[e] = upper_score(v[e], si, bound_error(bound[e], si)) >= least[e];
@@ -450,31 +479,33 @@ __device__ __forceinline__ void select_groups(const SelectSide& a, int b, float 
 }
 __global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectArgs args) {
     const SelectSide a = blockIdx.z ? args.side[1] : args.side[0];  // (an index would hide from the compiler that the pointers are global)
-    if (args.judge.alike(blockIdx.y)) return;
+    const DenseWay way = args.judge.way(blockIdx.y);
+    if (way == DENSE_ONE_STEP) return;
     __shared__ union {
         float low[SELECT_WAVES][SELECT_SLOTS][64];
         float handed[SELECT_WAVES][SELECT_SETS][GROUP_TOP][64];
     } lds;
     // uniform: the sides differ in size
-    if (a.grouped) {
+    if (a.grouped && way == DENSE_GROUPS) {
         if ((int64_t)(blockIdx.x / SELECT_PARTS) * DENSE_CELL_PIXELS < a.pitch) select_groups(a, blockIdx.y, lds.handed);
-    } else if ((int64_t)blockIdx.x * (64 * SELECT_SLOTS) < a.pitch) {
+    } else if (!a.keys && (int64_t)blockIdx.x * (64 * SELECT_SLOTS) < a.pitch) {
         select_slots(a, blockIdx.y, lds.low);
     }
 }
 
-// Whether the 8-bit scores of a pair tell enough apart.  How many cells the bounds leave over is a matter of what the maps hold (a
-// textureless wall, descriptors of few dimensions or of very different lengths leave most of them), so DENSE_SAMPLES pixels of
-// either image, spread over it, are scored against every cell of the other first: what they need is counted, and the launches of
-// the two steps, or else those of the one-step sweep, leave the pair alone.  One 512x384 pair, fp16, 24 channels, the whole call in one
-// step / in two without this / with it (17 us for pairs that keep two steps): features of 1 pixel 2.16 / 1.69 / 1.71 ms, of 64 2.05 / 2.26 / 1.89
-// (short ranges, see launch_refine_t), rank 6 2.13 / 2.82 / 2.17, rank 4 2.12 / 4.60 / 2.15, lengths spread by exp(N(0, 1)) 2.20 / 3.58 / 2.23,
-// one descriptor throughout 1.93 / 4.32 / 1.95.
+// Which way of a pair is the fastest.  How many cells the bounds leave over is a matter of what the maps hold (a textureless wall, descriptors of few
+// dimensions or of very different lengths leave most of them), so DENSE_SAMPLES pixels of either image, spread over it, are scored against every
+// cell of the other first, what they need is counted (dense_judge), and every launch takes the pairs that are its own.  A group's bound is that of its longest row,
+// which reaches past the best of the others where lengths differ; what the samples' groups mark says so.  Whole calls in us, fp16, 24 channels, in one step / with a maximum for every
+// candidate / for three / as the samples say.  One 512x384 pair: features of 1 pixel 2246 / 1769 / 1565 / 1567, of 64 2134 / 1972 / 1801 / 1812, of 128 2121 / 2142 / 2083 / 2074; rank 8
+// 2231 / 2486 / 2188 / 2181, rank 7 2242 / 3009 / 2561 / 2288; lengths spread by exp(0.3 N(0, 1)) 2265 / 1753 / 2206 / 1754, by exp(N(0, 1)) 2291 / 3439 / 3273 / 2351.  Four of 192x144:
+// features of 4 pixels 375 / 310 / 305 / 305, of 32 372 / 320 / 334 / 335, rank 8 386 / 370 / 418 / 403.
+// A pair that is left to one step pays 30 to 60 us (four 512x384 pairs 3 %) for its 8-bit maps, the samples and the launches that leave it alone.
 constexpr int SAMPLE_BLOCKS = DENSE_SAMPLES / 32;
 constexpr int SAMPLE_WAVES = 8;
 constexpr int SAMPLE_TILES = 8;  // in flight per wave
 __device__ __forceinline__ int64_t spread_pixel(int k, int64_t n) { return (int64_t)(((uint64_t)((uint32_t)k * 0x9E3779B1u) * (uint64_t)n) >> 32); }
-// Where the maxima are those of groups, whole groups.
+// Where groups are possible, whole groups.
 constexpr int SAMPLE_GROUP = 3;
 __device__ __forceinline__ int64_t sample_pixel(int k, int64_t n, bool grouped) {
     if (!grouped) return spread_pixel(k, n);
@@ -486,6 +517,7 @@ __device__ __forceinline__ int sample_cells(const DenseCoarseArgs& a, int side) 
 // A workgroup scores the samples of one image against one cell of the other.  Bound by the latency of its loads.
 __global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCoarseArgs a) {
     __shared__ int best[DENSE_SAMPLES];
+    __shared__ uint32_t bounds[DENSE_SAMPLES];
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cell = blockIdx.x, side = blockIdx.y, b = blockIdx.z;
@@ -499,7 +531,10 @@ __global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCo
     const int64_t mine = sample_pixel(threadIdx.x & (DENSE_SAMPLES - 1), a.pixels[side], grouped);
     const uint32_t bound = own.row_bound[own_row0 + mine];
     const SegInfo si = other.seg[(int64_t)b * other.n_segs + (int64_t)cell * cell_pixels / a.seg_pixels];
-    if (threadIdx.x < DENSE_SAMPLES) best[threadIdx.x] = LOWEST;
+    if (threadIdx.x < DENSE_SAMPLES) {
+        best[threadIdx.x] = LOWEST;
+        bounds[threadIdx.x] = bound;
+    }
     i32x4 q[SAMPLE_BLOCKS];
 #pragma unroll
     for (int k = 0; k < SAMPLE_BLOCKS; ++k)
@@ -525,29 +560,60 @@ __global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCo
     __syncthreads();
     if (threadIdx.x < DENSE_SAMPLES) {
         const int k = threadIdx.x, kept = best[k] >> KEPT_SHIFT;
-        int top = kept;
-        if (grouped) {  // a group's maximum stands for each of its candidates
+        const int64_t at = ((int64_t)b * sample_cells(a, side) + cell) * DENSE_SAMPLES + k;
+        const float score = (float)(kept * (1 << KEPT_SHIFT)) * si.scale, error = bound_error(bound, si);
+        a.sample_upper[side][at] = upper_score(kept, si, error);
+        atomicMax(&a.sample_lower[(b * 2 + side) * DENSE_SAMPLES + k], order_bits(score - error));
+        if (grouped) {  // a group's maximum stands for each of its candidates, with the group's worst length and remainder
             const int first = k / SAMPLE_GROUP * SAMPLE_GROUP;
-            for (int i = first; i < first + SAMPLE_GROUP && i < DENSE_SAMPLES; ++i) top = max(top, best[i] >> KEPT_SHIFT);
+            int top = kept;
+            uint32_t worst = bound;
+            for (int i = first; i < first + SAMPLE_GROUP && i < DENSE_SAMPLES; ++i) {
+                top = max(top, best[i] >> KEPT_SHIFT);
+                worst = worst_bound(worst, bounds[i]);
+            }
+            a.sample_group[at] = upper_score(top, si, bound_error(worst, si));
+            atomicMax(&a.sample_best[b * DENSE_SAMPLES + k], order_bits(score));
         }
-        const float error = __builtin_fmaf(__uint_as_float(bound & 0xFFFF0000u), si.residual, __uint_as_float(bound << 16) * si.length);
-        a.sample_upper[side][((int64_t)b * sample_cells(a, side) + cell) * DENSE_SAMPLES + k] = (float)((top + 1) * (1 << KEPT_SHIFT)) * si.scale + error;
-        atomicMax(&a.sample_lower[(b * 2 + side) * DENSE_SAMPLES + k], order_bits((float)(kept * (1 << KEPT_SHIFT)) * si.scale - error));
     }
 }
 constexpr int JUDGE_CELLS = 16;  // of a workgroup
+static_assert(JUDGE_CELLS % 2 == 0, "both halves of a segment");
 __global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseArgs a) {
     const int k = threadIdx.x, side = blockIdx.y, b = blockIdx.z, cells = sample_cells(a, side), first = blockIdx.x * JUDGE_CELLS;
-    const float* upper = a.sample_upper[side] + (int64_t)b * cells * DENSE_SAMPLES + k;
+    const bool grouped = side == 1 && a.grouped;
+    auto take = [&](const float* table, float (&up)[JUDGE_CELLS]) {
+#pragma unroll
+        for (int i = 0; i < JUDGE_CELLS; ++i) up[i] = table[((int64_t)b * cells + min(first + i, cells - 1)) * DENSE_SAMPLES + k];
+    };
     const float lower = unorder_bits(a.sample_lower[(b * 2 + side) * DENSE_SAMPLES + k]);
     float up[JUDGE_CELLS];
-#pragma unroll
-    for (int i = 0; i < JUDGE_CELLS; ++i) up[i] = upper[(int64_t)min(first + i, cells - 1) * DENSE_SAMPLES];
+    take(a.sample_upper[side], up);
+    const bool speaks = (k & 63) == 0;
     int marks = 0;
 #pragma unroll
+    for (int i = 0; i < JUDGE_CELLS; ++i) {
+        // where cells are half segments, those of single candidates are two of them (cells past the last repeat it)
+        if (grouped && i % 2) continue;
+        const float most = grouped ? __builtin_fmaxf(up[i], up[i + 1 - i % 2]) : up[i];
+        if (first + i < cells) marks += __popcll(__ballot(most >= lower));  // uniform
+    }
+    auto file = [&](int what, int count) {
+        if (speaks && count) {
+            atomicAdd(&a.marked[DENSE_MARKS * b + what], count);
+            atomicAdd(&a.marked[DENSE_MARKS * gridDim.z + what], count);
+        }
+    };
+    file(side == 0 ? MARKS_ROWS : MARKS_SINGLES, marks);
+    if (!grouped) return;
+    // What the second round of a group's cells is about: its bound against each candidate's best product, for which the 8-bit score stands here.
+    const float best = unorder_bits(a.sample_best[b * DENSE_SAMPLES + k]);
+    take(a.sample_group, up);
+    marks = 0;
+#pragma unroll
     for (int i = 0; i < JUDGE_CELLS; ++i)
-        if (first + i < cells) marks += __popcll(__ballot(up[i] >= lower));  // uniform
-    if ((threadIdx.x & 63) == 0 && marks) atomicAdd(&a.marked[b * 2 + side], marks);
+        if (first + i < cells) marks += __popcll(__ballot(up[i] >= best));  // uniform
+    file(MARKS_GROUPS, marks);
 }
 
 // Wider cells keep the table of a large map small, narrower ones leave less to multiply again.  Segments of 2048 pixels and cells of 1024 against 4096 and
@@ -562,37 +628,71 @@ constexpr double DENSE_COARSE = 38.0, DENSE_COARSE_GROUPS = 29.0;
 static double dense_second(int compute, int dp) { return compute == FNN_F32 ? 18.75 * dp : (dp <= 32 ? 46.0 : 1.64 * dp); }
 // Groups of candidates leave some GROUP_TOP cells more of them to the second step, which is dear where products are (fp32, 24 channels, a maximum for every candidate / groups:
 // 320x240 839 / 911 us, four pairs of 256x192 and 320x240 1613 / 1978; two-term rows, 384x288 894 / 865).
+// ... there with its lists and what their uneven lengths leave idle, per share of the cells that the samples mark (one 512x384 pair of 16-bit rows 45 to 58, 32 channels 66; two-term rows 121)
+static double dense_second_listed(int compute, int dp) { return compute != FNN_F32 && dp <= 32 ? (dp <= 24 ? 58.0 : 66.0) : dense_second(compute, dp); }
 static double first_round(double cells) { return cells < FEW_CELLS ? GROUP_TOP_FEW : GROUP_TOP; }
 bool dense_grouped(int64_t n, int compute, int dp) {
     const double cells = 2.0 * n / dense_seg_pixels(n);
     return dense_second(compute, dp) * (first_round(cells) + 2.0) < (DENSE_COARSE - DENSE_COARSE_GROUPS) * cells;
 }
 static double dense_coarse_block(int64_t n, int compute, int dp) { return dense_grouped(n, compute, dp) ? DENSE_COARSE_GROUPS : DENSE_COARSE; }
-// ... there with its lists and what their uneven lengths leave idle: one 512x384 pair of 16-bit rows loses from a share of about 0.26 on
-// (0.24 0.97 of the one step's time, 0.25 0.99), 384x288 in fp32 is at 0.87 with 0.61
-double dense_coarse_limit(int64_t n, int compute, int dp) {
-    return 0.85 * (dense_exact(compute, dp) - dense_coarse_block(n, compute, dp)) / (compute != FNN_F32 && dp <= 32 ? 58.0 : dense_second(compute, dp));
-}
 // The model behind the choice, in nanoseconds.  The one-step kernels leave their staged loop where a workgroup meets padding and have few workgroups to share what that leaves
 // uneven: maps that are not whole runs of 4096 queries and 512 candidates take 1.5 to 2.2 times a whole one's time per block, of which 1.4 are counted on.  Two steps cost 45 us of launches, more
 // on large maps.  Measured in one step / two, 16-bit rows of 24 channels: 256x192 1 pair 236 / 252 us, 2 379 / 355, 4 674 / 564, 16 2341 / 1923; 352x256 564 / 455; not whole:
 // 160x120, 16 pairs 738 / 764; 192x144 1 pair 192 / 206, 4 371 / 312, 16 1321 / 829; 224x168 241 / 223, 4 632 / 449, 16 2379 / 1469; 288x216 406 / 324, 4 1819 / 852; 32 channels, 192x144, 8 803 /
 // 515; squared distance, 320x240, 2 1233 / 1253, 256x192, 4 770 / 790; fp32, 128x128, 4 494 / 749, 192x144, 4 1409 / 713; two-term rows, 128x128, 4 253 / 322, 192x144 253 / 275.
 // (A pair that the samples leave to one step pays for them and for its 8-bit maps: some 30 us.)
+struct DenseModel {
+    double blocks, exact, cell, cells[2], passes;  // cells of image 2, and of image 1 (half segments where groups are possible)
+    bool grouped;
+};
+static DenseModel dense_model(int64_t n, int64_t m, int batch, int compute, int dp, bool l2) {
+    DenseModel M;
+    M.grouped = dense_grouped(n, compute, dp);
+    M.cell = (double)DENSE_CELL_PIXELS * dense_cell_runs(n, m);
+    M.cells[0] = m / M.cell;
+    M.cells[1] = (M.grouped ? 2.0 : 1.0) * n / dense_seg_pixels(n);
+    M.blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
+    const bool whole = n % DENSE_SB_PIXELS == 0 && m % (32 * DENSE_TILES_PER_GROUP) == 0;
+    const bool narrow = compute != FNN_F32 && dp <= 32 && !l2;  // (of the others the second step costs more than counted here, too)
+    M.exact = dense_exact(compute, dp) * (narrow && !whole ? 1.4 : 1.0);
+    const double row_bytes = dp * elem_size(compute);
+    const double bytes = batch * ((double)(n + m) * (2.0 * row_bytes + 40.0) + 8.0 * n * (m / M.cell) + 8.0 * m * ((double)n / dense_seg_pixels(n)));
+    M.passes = bytes / 4500.0 + batch * (double)(n + m) * 0.1;  // over maps and tables; most of it hides behind the sweep
+    if (M.passes > 30000.0) M.passes = 30000.0;
+    return M;
+}
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2) {
     if (n < 16384 || m < 16384 || (compute != FNN_F32 && dp <= 16)) return -1e30;
     if ((double)m * (n / dense_seg_pixels(n)) * 2.0 > 4e9) return -1e30;  // the candidates' table of a pair would be too large
-    const bool grouped = dense_grouped(n, compute, dp);
-    const double cell = (double)DENSE_CELL_PIXELS * dense_cell_runs(n, m), row_bytes = dp * elem_size(compute);
-    const double cells[2] = {m / cell, (grouped ? 2.0 : 1.0) * n / dense_seg_pixels(n)};
-    const double again = coarse_cells_again(cells[0], d, l2) / cells[0] + ((grouped ? first_round(cells[1]) : 0.0) + coarse_cells_again(cells[1], d, l2)) / cells[1];
-    const double blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
-    const bool whole = n % DENSE_SB_PIXELS == 0 && m % (32 * DENSE_TILES_PER_GROUP) == 0;
-    const bool narrow = compute != FNN_F32 && dp <= 32 && !l2;  // (of the others the second step costs more than counted here, too)
-    const double exact = dense_exact(compute, dp) * (narrow && !whole ? 1.4 : 1.0);
-    const double bytes = batch * ((double)(n + m) * (2.0 * row_bytes + 40.0) + 8.0 * n * (m / cell) + 8.0 * m * ((double)n / dense_seg_pixels(n)));
-    const double passes = bytes / 4500.0 + batch * (double)(n + m) * 0.1;  // over maps and tables; most of it hides behind the sweep
-    return blocks * (exact - dense_coarse_block(n, compute, dp) - dense_second(compute, dp) * again) - 45000.0 - (passes < 30000.0 ? passes : 30000.0);
+    const DenseModel M = dense_model(n, m, batch, compute, dp, l2);
+    const double again = coarse_cells_again(M.cells[0], d, l2) / M.cells[0] + ((M.grouped ? first_round(M.cells[1]) : 0.0) + coarse_cells_again(M.cells[1], d, l2)) / M.cells[1];
+    return M.blocks * (M.exact - dense_coarse_block(n, compute, dp) - dense_second(compute, dp) * again) - 45000.0 - M.passes;
+}
+// What the samples' marks say a pair would take, in 1/1024 ns over one step.  Groups cost 3 ns a block more than the sweep's own time says (marking and a second round), and a quarter more per
+// mark (short lists fill up their last block): one 512x384 pair, modelled / measured, us over one step: features of 1 pixel -684 / -681, of 64 -432 / -333, of 128 -91 / -38, rank 10 -223 / -220,
+// rank 8 -39 / -43, lengths spread by exp(0.3 N(0, 1)) -57 / -59.
+// Pairs of one call go the same way unless one gains more than a seventh of its time by another: launches that take a part of the pairs leave the chip idle at their end (four 512x384
+// pairs whose lengths are spread by exp(0.7 N(0, 1)) 8.39 ms in one step, 8.62 with a maximum for every candidate, 9.98 where each pair went its own way).  Small pairs, which hardly fill the chip
+// one by one, always do (four of 192x144 with features of 64 pixels 368 us in one step, 369 for groups of three, 570 where two went either way).
+DenseJudge dense_judge(const DenseCoarseArgs& a, int batch, int compute, int dp, bool l2) {
+    const int64_t n = a.pixels[0], m = a.pixels[1];
+    const DenseModel M = dense_model(n, m, batch, compute, dp, l2);
+    const double blocks = M.blocks / batch, second = dense_second_listed(compute, dp);
+    auto fixed = [](double ns) { return (int64_t)(ns * 1024.0); };
+    auto each = [&](int64_t cells) { return fixed(blocks * second / (DENSE_SAMPLES * (double)cells)); };
+    DenseJudge j = {};
+    j.marked = a.marked;
+    j.all = a.marked + DENSE_MARKS * batch;
+    j.pairs = batch;
+    j.each[MARKS_ROWS] = each(a.n_cells);
+    j.each[MARKS_SINGLES] = each(a.grouped ? (a.n_col_cells + 1) / 2 : a.n_col_cells);
+    j.each[MARKS_GROUPS] = fixed(1.25 * blocks * second / (DENSE_SAMPLES * (double)a.n_col_cells));
+    j.singles = fixed((45000.0 + M.passes) / batch - blocks * (M.exact - DENSE_COARSE));
+    j.groups = a.grouped ? j.singles - fixed(blocks * (DENSE_COARSE - DENSE_COARSE_GROUPS - 3.0)) : INT64_MAX / 256;
+    j.least_groups = fixed(blocks * second * first_round(M.cells[1]) / M.cells[1]);
+    j.margin = blocks * M.exact < 1e6 ? INT64_MAX / 2 : fixed(0.15 * blocks * M.exact);
+    return j;
 }
 
 hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s) {
@@ -621,10 +721,12 @@ static SelectSide select_side(const DenseCoarseArgs& a, int side, const u64* key
     const CoarseMap& other = a.map[side ^ 1];
     sa.best = a.best[side];
     sa.mask = a.mask[side];
-    sa.table_cells = side == 0 ? a.n_cells : (int64_t)a.map[0].n_segs << a.grouped;
-    sa.n_cells = side == 0 ? a.n_cells : a.n_col_cells;
     sa.pitch = side == 0 ? (int64_t)a.n_sb * DENSE_SB_PIXELS : (int64_t)own.n_segs * a.seg_pixels;
-    sa.cells_per_seg = side == 0 ? a.seg_pixels / (DENSE_CELL_PIXELS * a.cell_runs) : 1 << a.grouped;
+    sa.n_cells = side == 0 ? a.n_cells : (int32_t)((a.pixels[0] + a.seg_pixels - 1) / a.seg_pixels);
+    sa.n_group_cells = a.n_col_cells;
+    sa.best_pitch = (side == 0 ? a.n_cells : other.n_segs) * sa.pitch;
+    sa.mask_pitch = (side == 0 ? a.n_cells : (int64_t)other.n_segs << a.grouped) * (sa.pitch / 64);
+    sa.cells_per_seg = side == 0 ? a.seg_pixels / (DENSE_CELL_PIXELS * a.cell_runs) : 1;
     sa.row_bound = own.row_bound + (side == 0 ? (int64_t)a.first_sb * DENSE_SB_PIXELS : 0);
     sa.bound_pitch = (int64_t)own.n_segs * a.seg_pixels;
     sa.seg = other.seg;
@@ -644,7 +746,8 @@ hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sid
     int64_t wgs = 0;
     for (int i = 0; i < sides; ++i) {
         args.side[i] = select_side(a, first_side + i, col_keys);
-        const int64_t pitch = args.side[i].pitch, need = args.side[i].grouped ? pitch / DENSE_CELL_PIXELS * SELECT_PARTS : pitch / (64 * SELECT_SLOTS);
+        const int64_t need = args.side[i].pitch / (64 * SELECT_SLOTS);
+        static_assert(SELECT_PARTS * 64 * SELECT_SLOTS <= DENSE_CELL_PIXELS, "enough workgroups for groups, too");
         if (need > wgs) wgs = need;
     }
     if (sides == 1) args.side[1] = args.side[0];

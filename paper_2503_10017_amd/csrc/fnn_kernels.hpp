@@ -151,13 +151,39 @@ constexpr int DENSE_J = 4;      // candidate tiles resident per wave
 constexpr int DENSE_WAVES = 4;  // waves per workgroup
 constexpr int DENSE_TILES_PER_GROUP = DENSE_J * DENSE_WAVES;
 
-// What a sample of a pair's pixels says of the dense mode's 8-bit scores: the cells that may hold a sample's best partner, both ways.
-// Where they are too many, the pair is swept in its own format instead.
+// What a sample of a pair's pixels says of the dense mode's 8-bit scores: the cells that may hold a sample's best partner, both ways, and so which way
+// of the pair is the fastest.  Every launch asks for itself, and all must get the same answer: the sums are those of integers.
+enum DenseWay { DENSE_ONE_STEP, DENSE_SINGLES, DENSE_GROUPS };  // in the call's own format; in 8 bits, a maximum for every candidate; one for three
+enum { MARKS_ROWS, MARKS_SINGLES, MARKS_GROUPS, DENSE_MARKS };
 struct DenseJudge {
-    const int32_t* marked;  // [batch][2] (NULL: every pair takes the 8-bit scores)
-    float weight[2];        // one over the marks of a side that make the two ways equally fast
-    __device__ __forceinline__ bool alike(int b) const {
-        return marked && (float)marked[2 * b] * weight[0] + (float)marked[2 * b + 1] * weight[1] > 1.0f;
+    const int32_t* marked;      // [batch][DENSE_MARKS] (NULL: every pair in one step)
+    const int32_t* all;         // [DENSE_MARKS] of the call's pairs together
+    int64_t pairs;
+    int64_t each[DENSE_MARKS];  // what a mark costs
+    int64_t singles, groups;    // ... beside the marks, over one step
+    int64_t least_groups;       // what the candidates' first round costs in groups, whatever is marked
+    int64_t margin;             // a pair that gains no more than this goes the way of the others
+    // over one step, of p pairs together
+    __device__ __forceinline__ void costs(const int32_t* m, int64_t p, int64_t (&of)[3]) const {
+        const int64_t rows = m[MARKS_ROWS] * each[MARKS_ROWS], marks = m[MARKS_GROUPS] * each[MARKS_GROUPS], least = p * least_groups;
+        of[DENSE_ONE_STEP] = 0;
+        of[DENSE_SINGLES] = p * singles + rows + m[MARKS_SINGLES] * each[MARKS_SINGLES];
+        of[DENSE_GROUPS] = p * groups + rows + (marks > least ? marks : least);
+    }
+    __device__ __forceinline__ static int cheapest(const int64_t (&of)[3]) {
+        const int two = of[DENSE_GROUPS] < of[DENSE_SINGLES] ? DENSE_GROUPS : DENSE_SINGLES;
+        return (two == DENSE_GROUPS ? of[DENSE_GROUPS] : of[DENSE_SINGLES]) < 0 ? two : DENSE_ONE_STEP;
+    }
+    __device__ __forceinline__ DenseWay way(int b) const {
+        if (!marked) return DENSE_ONE_STEP;
+        int64_t of[3];
+        costs(all, pairs, of);
+        const int common = cheapest(of);
+        costs(marked + DENSE_MARKS * b, 1, of);
+        const int own = cheapest(of);
+        const int64_t with_others = common == DENSE_GROUPS ? of[DENSE_GROUPS] : (common == DENSE_SINGLES ? of[DENSE_SINGLES] : 0);
+        const int64_t alone = own == DENSE_GROUPS ? of[DENSE_GROUPS] : (own == DENSE_SINGLES ? of[DENSE_SINGLES] : 0);
+        return (DenseWay)(with_others - alone > margin ? own : common);
     }
 };
 
@@ -216,11 +242,12 @@ struct CoarseArgs {
     int64_t slot_pitch;    // queries of a pair, rounded up to whole 64s
     int32_t n_cells;       // of a pair
     int32_t cell_shift;    // a cell is 2^cell_shift workgroups of the second step
-    const uint64_t* mask;  // launch_refine: [batch][n_cells][slab / 64] the slots that need a cell, instead of the bounds
-    int32_t grouped;       // ... the bits of every 1024 slots in the order of mask_candidate()
+    const uint64_t* mask;  // launch_refine: the slots that need a cell, instead of the bounds: [n_cells][slab / 64] of every pair, slot_pitch words
+                           // apart.  Of a pair's candidates in groups: twice as many cells, the bits of every 1024 slots in the order of mask_candidate()
     DenseJudge judge;      // launch_refine: pairs to leave alone
-    int32_t side;          // ... and whose samples the marks are: image 1's or 2's
-    int32_t range;         // (the launchers set these; 0 on entry, or 1: lists are short) queries that a workgroup of the second step looks at, or fewer
+    int32_t side;          // ... and whose slots they are: image 1's (queries) or 2's (candidates)
+    int32_t second_round;  // ... of the candidates in groups: pairs without them are left alone
+    int32_t range;         // (the launchers set these) queries that a workgroup of the second step looks at, or fewer
     int32_t first_slot;
     int32_t min_live;      // fewer live queries of a pair than this: its cells are refined for every query
     SearchVote* vote;      // [batch] (0 on entry), or NULL: scores in 8 bits whatever the maps hold
@@ -403,7 +430,7 @@ struct DenseArgs {
     int32_t* lists;        // [batch][rows_cap + cols_cap] pixels grouped by unit, buckets start on multiples of 32
     int32_t* chunk_unit;   // [batch][(rows_cap + cols_cap) / 32] unit of every chunk of 32 list positions
     int32_t* chunk_totals; // [batch][2] chunks in use per side
-    DenseJudge judge;      // launch_dense_pass1: the pairs to take (no marks: all)
+    DenseJudge judge;      // launch_dense_pass1: takes the pairs that are DENSE_ONE_STEP
 };
 // Pass 1 (both maxima with coarse locations) and pass 2 (exact indices and scores into
 // nn12/s12/nn21/s21; s12, s21 may be NULL).
@@ -430,17 +457,21 @@ struct DenseCoarseArgs {
     int32_t first_sb;      // the runs of DENSE_SB_PIXELS of image 1 that this launch takes
     int32_t n_sb;
     int32_t cell_runs;     // runs of DENSE_CELL_PIXELS candidates in a cell: 1, 2 or 4
-    int32_t grouped;       // 1: the maxima of candidates are those of groups, and their cells half segments of queries; 0: whole segments
+    int32_t grouped;       // pairs may keep the maxima of groups of candidates, whose cells are half segments of queries instead of whole ones (DENSE_GROUPS)
     int32_t n_cells;       // of image 2
-    int32_t n_col_cells;   // of image 1, those that hold a pixel
+    int32_t n_col_cells;   // of image 1, those that hold a pixel: half segments where `grouped`, else whole ones
     int32_t cells_per_wg;  // (set by the launcher)
-    uint16_t* best[2];     // [batch][n_cells][n_sb * 4096] of the queries; [batch][map[0].n_segs << grouped][pixels or groups of map[1]] of the candidates
-    uint64_t* mask[2];     // [batch][the same cells], a bit for every query and every candidate: cells that may hold its best partner
+    uint16_t* best[2];     // [batch][n_cells][n_sb * 4096] of the queries; [map[0].n_segs][pixels of map[1]], or [2 map[0].n_segs][its groups], of the candidates,
+                           // pairs map[0].n_segs * pixels apart
+    uint64_t* mask[2];     // [batch][the same cells], a bit for every query and every candidate: cells that may hold its best partner; of the
+                           // candidates, pairs (map[0].n_segs << grouped) * pixels bits apart
     float* least;          // [batch][groups of map[1]] the second round's limit: see select_groups
     int64_t pixels[2];
     float* sample_upper[2];  // [batch][cells of the other image][DENSE_SAMPLES]
+    float* sample_group;     // (grouped) [batch][n_col_cells][DENSE_SAMPLES]
     uint32_t* sample_lower;  // [batch][2][DENSE_SAMPLES] order_bits (0 on entry)
-    int32_t* marked;         // [batch][2] (0 on entry): see DenseJudge
+    uint32_t* sample_best;   // (grouped) [batch][DENSE_SAMPLES] order_bits (0 on entry)
+    int32_t* marked;         // [batch + 1][DENSE_MARKS] (0 on entry), the last for all pairs: see DenseJudge
     DenseJudge judge;
     DenseSwept swept;
 };
@@ -452,10 +483,9 @@ hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s);
 // Groups of candidates take two rounds, the second with what the first left in their keys (col_keys, NULL: the first).
 hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sides, const u64* col_keys, int batch, hipStream_t s);
 int dense_cell_runs(int64_t n, int64_t m);
-bool dense_grouped(int64_t n, int compute, int dp);  // whether the candidates' maxima are those of groups
+bool dense_grouped(int64_t n, int compute, int dp);  // whether the candidates' maxima may be those of groups
 int dense_seg_pixels(int64_t n);
-// Share of the cells, of both directions together, that may be multiplied again before the dense kernels are faster
-double dense_coarse_limit(int64_t n, int compute, int dp);
+DenseJudge dense_judge(const DenseCoarseArgs& a, int batch, int compute, int dp, bool l2);
 // Nanoseconds that a call gains this way
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2);
 

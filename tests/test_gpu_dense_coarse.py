@@ -220,15 +220,31 @@ def test_indices_stay_inside_maps_that_are_not_finite(compute, kw):
     assert count == 0 or (pairs.min() >= 0 and pairs[:, 0].max() < n and pairs[:, 1].max() < m)
 
 
-def pass1_detail(a, b, compute, **kw):
-    """Which 8-bit pass ran: 2 keeps a maximum for every candidate, 3 one for three."""
+def traced(a, b, compute, **kw):
+    fnn.fnn_mutual_dense(a, b, compute, **kw)
+    torch.cuda.synchronize()
     fnn.fnn_trace_begin(256)
     try:
         fnn.fnn_mutual_dense(a, b, compute, **kw)
         torch.cuda.synchronize()
     finally:
-        entries = fnn.fnn_trace_end(256, details=True)
-    return {detail for name, _, detail in entries if name == "dense_kernel"}
+        return fnn.fnn_trace_end(256, details=True)
+
+
+def pass1_detail(a, b, compute, **kw):
+    """Which 8-bit pass was launched: 2 keeps a maximum for every candidate, 3 one for three (or, pair by pair, for every candidate)."""
+    return {detail for name, _, detail in traced(a, b, compute, **kw) if name == "dense_kernel"}
+
+
+def ways(a, b, compute, **kw):
+    """What the pairs of a call in two steps did there.  A launch without a pair of its own takes 4 us; the sweeps and lists of these sizes take 20 and more."""
+    entries = traced(a, b, compute, **kw)
+    took = {kind: [ms * 1e3 for name, ms, _ in entries if name == kind] for kind in ("dense_kernel", "dense_alike_kernel", "refine_kernel")}
+    groups = {detail for name, _, detail in entries if name == "dense_kernel"} == {3}
+    done = {"one step"} if max(took["dense_alike_kernel"]) > 15 else set()
+    if max(took["dense_kernel"]) > 15:
+        done.add("groups" if groups and took["refine_kernel"][-1] > 12 else "singles")
+    return done
 
 
 @pytest.mark.parametrize("n,m,batch,compute,d,kw,grouped", [
@@ -254,13 +270,97 @@ def test_maxima_of_three_candidates(n, m, batch, compute, d, kw, grouped):
     got, _ = same(a, b, compute, **kw)
     assert pass1_detail(a, b, compute, **kw) == {3 if grouped else 2}
     assert (got["nn21"][:, m - 1] == 1500).all()
-    # a product of infinity is reached by no bound, and the lowest of two is the match
+    assert ways(a, b, compute, **kw) == ({"groups"} if grouped else {"singles"})
+    # a product of infinity is reached by no bound, and the lowest of two is the match (most of these maps, crowded in one orthant, are left to one
+    # step; infinities in two steps: test_rows_without_bounds_among_rows_that_have_them)
     a, b = a.abs() + 0.01, b.abs() + 0.01  # no channel is 0: 0 times infinity is no number
     a[:, 5000] = a[:, n - 5] = float("inf")
     b[:, 77] = b[:, m - 40] = float("inf")
     got, _ = same(a, b, compute, **kw) if not kw else (None, None)
     if got:
         assert (got["nn21"] == 5000).sum() >= batch * (m - 2) and (got["nn12"] == 77).sum() >= batch * (n - 2)
+
+
+@pytest.mark.parametrize("n,m,compute,d,kind,way", [
+    (122881, 131073, "f16", 24, "infinite", "groups"),
+    (300001, 200100, "bf16", 32, "infinite", "groups"),      # cells of 2048 queries
+    (43008, 524288, "bf16", 24, "beyond bounds", "groups"),
+    (126976, 131071, "bf16", 24, "beyond bounds", "groups"),
+    (131072, 70000, "f32", 24, "beyond bounds", "singles"),
+])
+def test_rows_without_bounds_among_rows_that_have_them(n, m, compute, d, kind, way):
+    """Two equal rows of either image have no bounds, in different cells, and win wherever a product with them is positive: the lower index is the match.  The rest
+    keep the bounds that they have, so the pair stays in two steps."""
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    a, b = (torch.nn.functional.normalize(torch.randn((1, rows, d), generator=gen, device="cuda:0"), dim=2) for rows in (n, m))
+    k = min(n, m) // 2
+    b[:, :k] = torch.nn.functional.normalize(a[:, :k] + 0.3 * b[:, :k], dim=2)
+    a[..., 0] += 0.002 * (a[..., 0] >= 0) - 0.001   # no row's channel 0 is 0, also in 16 bits: 0 times infinity is no number
+    b[..., 0] += 0.002 * (b[..., 0] >= 0) - 0.001
+    for x, at in ((a, (5000, n - 5)), (b, (77, m - 40))):
+        row = x[0, at[0]].clone()
+        if kind == "infinite":
+            row[0] = float("inf")
+        else:
+            row *= 3e15 / row.abs().max()   # a square past the largest that the bounds hold for
+        x[0, list(at)] = row
+    assert ways(a, b, compute) == {way}
+    got, _ = same(a, b, compute)
+    for key, x, y, index, special in (("nn12", a, b[0, 77], 77, (5000, n - 5)), ("nn21", b, a[0, 5000], 5000, (77, m - 40))):
+        x, y = (z.to({"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[compute]).double() for z in (x[0], y))
+        positive = (x[:, 0] > 0) if kind == "infinite" else (x @ y > 1e12)   # far above any other product
+        positive[list(special)] = False   # ... but theirs with one another
+        assert positive.sum() > x.shape[0] // 3 and (got[key][0][positive.cpu().numpy()] == index).all(), key
+
+
+@pytest.mark.parametrize("n,m,compute,d,kw", [
+    (196608, 196608, "f16", 24, {}),
+    (122881, 131073, "bf16", 24, {}),
+    (43008, 524288, "f16", 24, {}),       # wide cells of candidates
+    (300001, 200100, "bf16", 32, {}),     # cells of 2048 queries
+    (131072, 131072, "f16", 24, {"split": True}),
+])
+def test_rows_whose_lengths_vary_keep_a_maximum_for_every_candidate(n, m, compute, d, kw):
+    """A group's bound is that of its longest row, which reaches past the best of the others."""
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    a, b = (torch.nn.functional.normalize(torch.randn((1, rows, d), generator=gen, device="cuda:0"), dim=2) for rows in (n, m))
+    k = min(n, m) // 2
+    b[:, :k] = torch.nn.functional.normalize(a[:, :k] + 0.3 * b[:, :k], dim=2)
+    assert ways(a, b, compute, **kw) == {"groups"}
+    for x in (a, b):
+        x *= torch.exp(0.4 * torch.randn(x.shape[:2] + (1,), generator=gen, device="cuda:0"))
+    assert ways(a, b, compute, **kw) == {"singles"}
+    same(a, b, compute, **kw)
+
+
+@pytest.mark.parametrize("n,batch,few,want", [
+    (27648, 4, (0, 2), {"one step"}),        # half of the call would take two steps
+    (27648, 16, (3,), {"groups"}),
+    (196608, 3, (1,), {"one step", "groups"}),   # large pairs go their own way where that gains much
+])
+def test_small_pairs_of_a_call_go_the_same_way(n, batch, few, want):
+    """Launches that take a part of a call's small pairs leave most of the chip idle."""
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    a, b = (torch.nn.functional.normalize(torch.randn((batch, n, 24), generator=gen, device="cuda:0"), dim=2) for _ in range(2))
+    b[:, :n // 2] = torch.nn.functional.normalize(a[:, :n // 2] + 0.3 * b[:, :n // 2], dim=2)
+    for p in few:
+        a[p] = _alike("rank 3", n, gen)
+        b[p] = a[p, torch.randperm(n, generator=gen, device="cuda:0")]
+    assert ways(a, b, "f16") == want
+    same(a, b, "f16")
+
+
+def test_pairs_whose_lengths_vary_beside_pairs_that_do_not():
+    """Every way of a large pair, in one call."""
+    n, gen = 196608, torch.Generator(device="cuda:0").manual_seed(4)
+    a, b = (torch.nn.functional.normalize(torch.randn((3, n, 24), generator=gen, device="cuda:0"), dim=2) for _ in range(2))
+    b[:, :n // 2] = torch.nn.functional.normalize(a[:, :n // 2] + 0.3 * b[:, :n // 2], dim=2)
+    for x in (a, b):
+        x[1] *= torch.exp(0.4 * torch.randn((n, 1), generator=gen, device="cuda:0"))
+    a[2] = _alike("rank 3", n, gen)
+    b[2] = a[2, torch.randperm(n, generator=gen, device="cuda:0")]
+    assert ways(a, b, "bf16") == {"one step", "groups"}
+    same(a, b, "bf16")
 
 
 @pytest.mark.parametrize("n,m,batch,compute,d,kw,two_steps", [
