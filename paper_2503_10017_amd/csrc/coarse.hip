@@ -526,7 +526,8 @@ constexpr int refine_waves() { return Ops<CT, DP>::ROW_BYTES <= 48 ? 4 : (Ops<CT
 constexpr int REFINE_SCAN = 4096;             // queries looked at between two looks at the list's length
 constexpr int REFINE_LIST = REFINE_SCAN + 1024;
 constexpr int REFINE_PART = 512;               // a multiple of 32
-constexpr int REFINE_MOST = 4 * REFINE_SCAN;   // queries of a workgroup (ca.range: a multiple of REFINE_SCAN)
+constexpr int REFINE_MOST = 4 * REFINE_SCAN;   // queries of a workgroup, at the most
+constexpr int REFINE_LEAST = 1024;             // (ca.range: whole 1024s, whose bits may be in an order of their own)
 constexpr int REFINE_SHORT = 128;              // of REFINE_SCAN queries; lists no longer than this are not worth a workgroup
 
 // MASK: which queries need a cell is read from a table of bits; the keys name units of DENSE_J tiles instead of tiles.
@@ -891,12 +892,13 @@ static hipError_t launch_refine_t(const SearchArgs& a, CoarseArgs ca, int batch,
     const unsigned cells = (unsigned)((a.m_tiles + CELL - 1) / CELL);
     // Where neighbouring pixels resemble each other, what a cell is marked by lies together: a workgroup with many queries may need the
     // cell for all of them and be what the launch waits for.  Short ranges even that out (dense mode, fp16, 24 channels, 512x384, features of 128
-    // pixels, both launches with ranges of 16384 / 4096: 1104 / 548 us); but each reads its tiles again and fills up its last block, so they are taken
+    // pixels, both launches with ranges of 16384 / 4096: 1104 / 548 us), shorter ones where workgroups are fewer (the whole call, features of 32 pixels, ranges of 4096 / 2048 / 1024: four pairs
+    // of 192x144 405 / 363 / 335, of 224x168 642 / 536 / 538, one of 352x256 559 / 519 / 521; of one pixel the same); but each reads its tiles again and fills up its last block, so they are taken
     // while the workgroups are few and where the samples say that the lists are long (features of one pixel, four pairs: 324 / 365 us; 1024x768
     // 1085 / 1662).  Rows that cost more per product lose more to the last block of a list than they gain (fp32, 384x288, features of one pixel 356 / 794).
     ca.range = REFINE_MOST;
     if (MASK && CT != CT_F32 && DP <= 32 && !ca.second_round)  // (what the second round lists is little)
-        for (ca.range = REFINE_SCAN; ca.range < REFINE_MOST && cells * ((slots + ca.range - 1) / ca.range) * batch > 16384;) ca.range *= 2;
+        for (ca.range = REFINE_LEAST; ca.range < REFINE_MOST && cells * ((slots + ca.range - 1) / ca.range) * batch > (ca.range < REFINE_SCAN ? 4096 : 16384);) ca.range *= 2;
     const unsigned ranges = (unsigned)((slots + ca.range - 1) / ca.range);
     return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES, MASK>, dim3(cells, ranges, batch), dim3(64 * WAVES), 0, s, a, ca);
 }

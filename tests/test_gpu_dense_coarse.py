@@ -148,17 +148,41 @@ def test_maps_without_contrast_take_no_longer_than_one_step(kind):
     out = fnn.fnn_mutual_dense(a, b, "f16", workspace=ws)
 
     def least(workspace):
-        times = []
-        for _ in range(6):
-            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            start.record()
-            fnn.fnn_mutual_dense(a, b, "f16", out=out, workspace=workspace)
-            end.record()
-            torch.cuda.synchronize()
-            times.append(start.elapsed_time(end))
-        return min(times)
+        return least_ms(lambda: fnn.fnn_mutual_dense(a, b, "f16", out=out, workspace=workspace))
 
     assert least(ws) < 1.4 * least(small)
+
+
+def least_ms(call):
+    times = []
+    for _ in range(6):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        call()
+        end.record()
+        torch.cuda.synchronize()
+        times.append(start.elapsed_time(end))
+    return min(times)
+
+
+@pytest.mark.parametrize("w,h,batch", [(224, 168, 4), (192, 144, 4)])
+def test_lists_that_lie_together(w, h, batch):
+    """Neighbouring pixels need the same cells where a map's features are large, so some workgroups of the second step have long lists; shared out in short
+    ranges they do not hold up a small call (0.89 of what one step takes; in ranges of 4096 queries 1.02 and 1.04)."""
+    n, gen = w * h, torch.Generator(device="cuda:0").manual_seed(w)
+
+    def field():
+        coarse = torch.randn((batch, 24, h // 32 + 2, w // 32 + 2), generator=gen, device="cuda:0")
+        x = torch.nn.functional.interpolate(coarse, size=(h, w), mode="bilinear", align_corners=True)
+        return torch.nn.functional.normalize(x, dim=1).permute(0, 2, 3, 1).reshape(batch, n, 24).contiguous()
+
+    a = field()
+    b = torch.nn.functional.normalize(a.roll(w * 11 + 17, 1) + 0.1 * torch.randn(a.shape, generator=gen, device="cuda:0"), dim=2)
+    same(a, b, "f16")
+    ws = torch.empty(fnn.fnn_workspace_bytes(batch, n, n, 24, 0, "f16"), dtype=torch.uint8, device="cuda:0")
+    small, out = ws[:one_step_bytes(batch, n, n, 24, "f16")], fnn.fnn_mutual_dense(a, b, "f16", workspace=ws)
+    two, one = (least_ms(lambda: fnn.fnn_mutual_dense(a, b, "f16", out=out, workspace=x)) for x in (ws, small))
+    assert two < 0.97 * one
 
 
 def test_pairs_in_groups_that_share_their_tables():
