@@ -369,8 +369,10 @@ void recip_tail_kernel(TailArgs ta) {
         // scores start from (few_low), the copies of the keys and twice to four times as many workgroups, together, the launch in us: one 512x384 pair 53.8 -> 36.7, two with squared
         // distance 54.5 -> 46.3, four raw pairs 79.5 -> 66, four of two-term rows 112.5 -> 96 (so with two blocks; three blocks of narrow rows one by one).  Bound by
         // the loads of the tiles: a compute unit takes 236 ns for eight waves' 1.5 KB each, whatever they multiply them with; four blocks of narrow rows per
-        // load cost more in registers and code than that saves (36.7 -> 40.0, 46.3 -> 47.6).
-        const int blocks = (n_act + 31) / 32, together = blocks == 1 || (blocks == 3 && O::ROW_BYTES <= 64) ? 1 : 2, groups_of = (blocks + together - 1) / together;
+        // load cost more in registers and code than that saves (36.7 -> 40.0, 46.3 -> 47.6).  Products in fp32 cost more than the loads: an odd number of blocks is taken one
+        // by one there, where by twos half of a pair is padding (whole calls, features of 4 pixels, 24 channels, by twos / one by one: 16 pairs of 256x192 433 / 418 us, four of 320x240
+        // 241 / 232, of 512x384 with every 16th pixel a seed 366 / 360; features of 1 pixel the same).
+        const int blocks = (n_act + 31) / 32, together = blocks == 1 || (blocks == 3 && O::ROW_BYTES <= 64) || (CT == CT_F32 && blocks % 2) ? 1 : 2, groups_of = (blocks + together - 1) / together;
         const int chunks = max(1, min(n_waves / groups_of, m_tiles));
 #pragma unroll 1
         for (int unit = gw; unit < groups_of * chunks; unit += n_waves) {  // uniform in the wave

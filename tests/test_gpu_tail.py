@@ -80,8 +80,8 @@ def test_one_launch_and_many_give_the_same(batch, n, m, n_seeds, compute, d, max
 @pytest.mark.parametrize("n_seeds", [1, 32, 33, 64, 65, 96, 97, 129, 225])
 @pytest.mark.parametrize("compute,option,scale", [("f16", None, 1.0), ("f16", "split", 1.0), ("f32", None, 1e-12), ("f16", "l2", 1.0)])
 def test_blocks_of_queries_dealt_to_the_waves(n_seeds, compute, option, scale):
-    """One, two, three (by ones where rows are narrow, by twos where they are wide) and more blocks of queries, whole ones and one more query; scores
-    of every sign and size start from what the search before found."""
+    """One, two, three (by ones where rows are narrow or products in fp32, by twos where rows are wide) and more blocks of queries (of fp32, odd numbers
+    by ones), whole ones and one more query; scores of every sign and size start from what the search before found."""
     a, b = (x * scale for x in wandering_maps(n_seeds, 2, 9001, 9333, 24))
     seeds = torch.randint(0, 9001, (2, n_seeds), generator=torch.Generator().manual_seed(n_seeds), dtype=torch.int32).cuda()
     kw = {option: True} if option else {}
