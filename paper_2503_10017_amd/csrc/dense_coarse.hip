@@ -495,7 +495,7 @@ __global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectA
 
 // Which way of a pair is the fastest.  How many cells the bounds leave over is a matter of what the maps hold (a textureless wall, descriptors of few
 // dimensions or of very different lengths leave most of them), so DENSE_SAMPLES pixels of either image, spread over it, are scored against every
-// cell of the other first, what they need is counted (dense_judge), and every launch takes the pairs that are its own.  A group's bound is that of its longest row,
+// cell of the other first, what they need is counted (dense_costs), and every launch takes the pairs that are its own.  A group's bound is that of its longest row,
 // which reaches past the best of the others where lengths differ; what the samples' groups mark says so.  Whole calls in us, fp16, 24 channels, in one step / with a maximum for every
 // candidate / for three / as the samples say.  One 512x384 pair: features of 1 pixel 2246 / 1769 / 1565 / 1567, of 64 2134 / 1972 / 1801 / 1812, of 128 2121 / 2142 / 2083 / 2074; rank 8
 // 2231 / 2486 / 2188 / 2181, rank 7 2242 / 3009 / 2561 / 2288; lengths spread by exp(0.3 N(0, 1)) 2265 / 1753 / 2206 / 1754, by exp(N(0, 1)) 2291 / 3439 / 3273 / 2351.  Four of 192x144:
@@ -579,7 +579,10 @@ __global__ __launch_bounds__(SAMPLE_WAVES * 64) void dense_sample_kernel(DenseCo
 }
 constexpr int JUDGE_CELLS = 16;  // of a workgroup
 static_assert(JUDGE_CELLS % 2 == 0, "both halves of a segment");
-__global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseArgs a) {
+// The last workgroup to file its marks decides.
+__global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseArgs a, DenseCosts costs) {
+    __shared__ int32_t all[DENSE_MARKS];
+    __shared__ uint32_t filed;
     const int k = threadIdx.x, side = blockIdx.y, b = blockIdx.z, cells = sample_cells(a, side), first = blockIdx.x * JUDGE_CELLS;
     const bool grouped = side == 1 && a.grouped;
     auto take = [&](const float* table, float (&up)[JUDGE_CELLS]) {
@@ -599,21 +602,36 @@ __global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseA
         if (first + i < cells) marks += __popcll(__ballot(most >= lower));  // uniform
     }
     auto file = [&](int what, int count) {
-        if (speaks && count) {
-            atomicAdd(&a.marked[DENSE_MARKS * b + what], count);
-            atomicAdd(&a.marked[DENSE_MARKS * gridDim.z + what], count);
-        }
+        if (speaks && count) atomicAdd(&a.marked[DENSE_MARKS * b + what], count);
     };
     file(side == 0 ? MARKS_ROWS : MARKS_SINGLES, marks);
-    if (!grouped) return;
-    // What the second round of a group's cells is about: its bound against each candidate's best product, for which the 8-bit score stands here.
-    const float best = unorder_bits(a.sample_best[b * DENSE_SAMPLES + k]);
-    take(a.sample_group, up);
-    marks = 0;
+    if (grouped) {
+        // What the second round of a group's cells is about: its bound against each candidate's best product, for which the 8-bit score stands here.
+        const float best = unorder_bits(a.sample_best[b * DENSE_SAMPLES + k]);
+        take(a.sample_group, up);
+        marks = 0;
 #pragma unroll
-    for (int i = 0; i < JUDGE_CELLS; ++i)
-        if (first + i < cells) marks += __popcll(__ballot(up[i] >= best));  // uniform
-    file(MARKS_GROUPS, marks);
+        for (int i = 0; i < JUDGE_CELLS; ++i)
+            if (first + i < cells) marks += __popcll(__ballot(up[i] >= best));  // uniform
+        file(MARKS_GROUPS, marks);
+    }
+    if (k < DENSE_MARKS) all[k] = 0;
+    __syncthreads();  // the marks come before the count, and the counts of all before what the last one reads
+    if (k == 0) filed = __hip_atomic_fetch_add(a.filed, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (filed + 1 != gridDim.x * gridDim.y * gridDim.z) return;  // uniform
+    static_assert(FNN_MAX_BATCH <= DENSE_SAMPLES, "a thread for every pair");
+    const bool here = k < (int)gridDim.z;
+    int32_t own[DENSE_MARKS], sum[DENSE_MARKS];
+#pragma unroll
+    for (int w = 0; w < DENSE_MARKS; ++w) {
+        own[w] = here ? __hip_atomic_load(&a.marked[DENSE_MARKS * k + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        if (here) atomicAdd(&all[w], own[w]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < DENSE_MARKS; ++w) sum[w] = all[w];
+    if (here) a.ways[k] = costs.way(own, sum);
 }
 
 // Wider cells keep the table of a large map small, narrower ones leave less to multiply again.  Segments of 2048 pixels and cells of 1024 against 4096 and
@@ -675,15 +693,13 @@ double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, i
 // Pairs of one call go the same way unless one gains more than a seventh of its time by another: launches that take a part of the pairs leave the chip idle at their end (four 512x384
 // pairs whose lengths are spread by exp(0.7 N(0, 1)) 8.39 ms in one step, 8.62 with a maximum for every candidate, 9.98 where each pair went its own way).  Small pairs, which hardly fill the chip
 // one by one, always do (four of 192x144 with features of 64 pixels 368 us in one step, 369 for groups of three, 570 where two went either way).
-DenseJudge dense_judge(const DenseCoarseArgs& a, int batch, int compute, int dp, bool l2) {
+DenseCosts dense_costs(const DenseCoarseArgs& a, int batch, int compute, int dp, bool l2) {
     const int64_t n = a.pixels[0], m = a.pixels[1];
     const DenseModel M = dense_model(n, m, batch, compute, dp, l2);
     const double blocks = M.blocks / batch, second = dense_second_listed(compute, dp);
     auto fixed = [](double ns) { return (int64_t)(ns * 1024.0); };
     auto each = [&](int64_t cells) { return fixed(blocks * second / (DENSE_SAMPLES * (double)cells)); };
-    DenseJudge j = {};
-    j.marked = a.marked;
-    j.all = a.marked + DENSE_MARKS * batch;
+    DenseCosts j = {};
     j.pairs = batch;
     j.each[MARKS_ROWS] = each(a.n_cells);
     j.each[MARKS_SINGLES] = each(a.grouped ? (a.n_col_cells + 1) / 2 : a.n_col_cells);
@@ -695,11 +711,11 @@ DenseJudge dense_judge(const DenseCoarseArgs& a, int batch, int compute, int dp,
     return j;
 }
 
-hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s) {
+hipError_t launch_dense_sample(const DenseCoarseArgs& a, const DenseCosts& costs, int batch, hipStream_t s) {
     const int cells = a.n_cells > a.n_col_cells ? a.n_cells : a.n_col_cells;
     const hipError_t e = launch(TK_DENSE_SAMPLE, dense_sample_kernel, dim3(cells, 2, batch), dim3(SAMPLE_WAVES * 64), 0, s, a);
     if (e != hipSuccess) return e;
-    return launch(TK_DENSE_SAMPLE, dense_judge_kernel, dim3((cells + JUDGE_CELLS - 1) / JUDGE_CELLS, 2, batch), dim3(DENSE_SAMPLES), 0, s, a);
+    return launch(TK_DENSE_SAMPLE, dense_judge_kernel, dim3((cells + JUDGE_CELLS - 1) / JUDGE_CELLS, 2, batch), dim3(DENSE_SAMPLES), 0, s, a, costs);
 }
 hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s) {
     // six workgroups for every resident one (three per compute unit), so that the last ones leave little of the chip idle

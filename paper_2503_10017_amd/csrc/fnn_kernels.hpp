@@ -152,19 +152,23 @@ constexpr int DENSE_WAVES = 4;  // waves per workgroup
 constexpr int DENSE_TILES_PER_GROUP = DENSE_J * DENSE_WAVES;
 
 // What a sample of a pair's pixels says of the dense mode's 8-bit scores: the cells that may hold a sample's best partner, both ways, and so which way
-// of the pair is the fastest.  Every launch asks for itself, and all must get the same answer: the sums are those of integers.
+// of the pair is the fastest.  It is decided once, at the end of the samples' launch: where every workgroup of the later launches did these sums for itself, they took 5 to 10 us
+// longer each where workgroups are many.
 enum DenseWay { DENSE_ONE_STEP, DENSE_SINGLES, DENSE_GROUPS };  // in the call's own format; in 8 bits, a maximum for every candidate; one for three
 enum { MARKS_ROWS, MARKS_SINGLES, MARKS_GROUPS, DENSE_MARKS };
 struct DenseJudge {
-    const int32_t* marked;      // [batch][DENSE_MARKS] (NULL: every pair in one step)
-    const int32_t* all;         // [DENSE_MARKS] of the call's pairs together
+    const int32_t* ways;        // [batch] (NULL: every pair in one step)
+    const int32_t* marked;      // [batch][DENSE_MARKS]
+    __device__ __forceinline__ DenseWay way(int b) const { return ways ? (DenseWay)ways[b] : DENSE_ONE_STEP; }
+};
+struct DenseCosts {
     int64_t pairs;
     int64_t each[DENSE_MARKS];  // what a mark costs
     int64_t singles, groups;    // ... beside the marks, over one step
     int64_t least_groups;       // what the candidates' first round costs in groups, whatever is marked
     int64_t margin;             // a pair that gains no more than this goes the way of the others
     // over one step, of p pairs together
-    __device__ __forceinline__ void costs(const int32_t* m, int64_t p, int64_t (&of)[3]) const {
+    __device__ __forceinline__ void costs(const int32_t (&m)[DENSE_MARKS], int64_t p, int64_t (&of)[3]) const {
         const int64_t rows = m[MARKS_ROWS] * each[MARKS_ROWS], marks = m[MARKS_GROUPS] * each[MARKS_GROUPS], least = p * least_groups;
         of[DENSE_ONE_STEP] = 0;
         of[DENSE_SINGLES] = p * singles + rows + m[MARKS_SINGLES] * each[MARKS_SINGLES];
@@ -174,12 +178,12 @@ struct DenseJudge {
         const int two = of[DENSE_GROUPS] < of[DENSE_SINGLES] ? DENSE_GROUPS : DENSE_SINGLES;
         return (two == DENSE_GROUPS ? of[DENSE_GROUPS] : of[DENSE_SINGLES]) < 0 ? two : DENSE_ONE_STEP;
     }
-    __device__ __forceinline__ DenseWay way(int b) const {
-        if (!marked) return DENSE_ONE_STEP;
+    // the way of a pair from its marks and those of the call's pairs together
+    __device__ __forceinline__ DenseWay way(const int32_t (&marked)[DENSE_MARKS], const int32_t (&all)[DENSE_MARKS]) const {
         int64_t of[3];
         costs(all, pairs, of);
         const int common = cheapest(of);
-        costs(marked + DENSE_MARKS * b, 1, of);
+        costs(marked, 1, of);
         const int own = cheapest(of);
         const int64_t with_others = common == DENSE_GROUPS ? of[DENSE_GROUPS] : (common == DENSE_SINGLES ? of[DENSE_SINGLES] : 0);
         const int64_t alone = own == DENSE_GROUPS ? of[DENSE_GROUPS] : (own == DENSE_SINGLES ? of[DENSE_SINGLES] : 0);
@@ -471,13 +475,15 @@ struct DenseCoarseArgs {
     float* sample_group;     // (grouped) [batch][n_col_cells][DENSE_SAMPLES]
     uint32_t* sample_lower;  // [batch][2][DENSE_SAMPLES] order_bits (0 on entry)
     uint32_t* sample_best;   // (grouped) [batch][DENSE_SAMPLES] order_bits (0 on entry)
-    int32_t* marked;         // [batch + 1][DENSE_MARKS] (0 on entry), the last for all pairs: see DenseJudge
+    int32_t* marked;         // [batch][DENSE_MARKS] (0 on entry): see DenseJudge
+    uint32_t* filed;         // workgroups that have counted their marks (0 on entry)
+    int32_t* ways;           // [batch]
     DenseJudge judge;
     DenseSwept swept;
 };
 constexpr int DENSE_SAMPLES = 128;  // pixels of either image
 // Counts the marks of the samples.
-hipError_t launch_dense_sample(const DenseCoarseArgs& a, int batch, hipStream_t s);
+hipError_t launch_dense_sample(const DenseCoarseArgs& a, const DenseCosts& costs, int batch, hipStream_t s);
 hipError_t launch_dense_coarse(DenseCoarseArgs a, int batch, hipStream_t s);
 // From best[side] to mask[side] for one or both sides.  0: the queries of this launch's runs; 1: the candidates, once every run is done.
 // Groups of candidates take two rounds, the second with what the first left in their keys (col_keys, NULL: the first).
@@ -485,7 +491,7 @@ hipError_t launch_dense_select(const DenseCoarseArgs& a, int first_side, int sid
 int dense_cell_runs(int64_t n, int64_t m);
 bool dense_grouped(int64_t n, int compute, int dp);  // whether the candidates' maxima may be those of groups
 int dense_seg_pixels(int64_t n);
-DenseJudge dense_judge(const DenseCoarseArgs& a, int batch, int compute, int dp, bool l2);
+DenseCosts dense_costs(const DenseCoarseArgs& a, int batch, int compute, int dp, bool l2);
 // Nanoseconds that a call gains this way
 double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, int d, bool l2);
 
