@@ -558,7 +558,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
     if (grouped) n_act = min((n_act + DENSE_CELL_PIXELS - 1) & ~(DENSE_CELL_PIXELS - 1), ca.slab);  // bits that stand for no candidate are 0
     int range = ca.range;
-    if (MASK && range < REFINE_MOST && ca.judge.marked[DENSE_MARKS * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
+    if (MASK && !ca.second_round && range < REFINE_MOST && ca.judge.marked[DENSE_MARKS * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
     const int begin = blockIdx.y * range;
     n_act = min(n_act, begin + range);
     const int tile0 = (cell * WAVES + wave) * RT;
@@ -893,11 +893,15 @@ static hipError_t launch_refine_t(const SearchArgs& a, CoarseArgs ca, int batch,
     // Where neighbouring pixels resemble each other, what a cell is marked by lies together: a workgroup with many queries may need the
     // cell for all of them and be what the launch waits for.  Short ranges even that out (dense mode, fp16, 24 channels, 512x384, features of 128
     // pixels, both launches with ranges of 16384 / 4096: 1104 / 548 us), shorter ones where workgroups are fewer (the whole call, features of 32 pixels, ranges of 4096 / 2048 / 1024: four pairs
-    // of 192x144 405 / 363 / 335, of 224x168 642 / 536 / 538, one of 352x256 559 / 519 / 521; of one pixel the same); but each reads its tiles again and fills up its last block, so they are taken
+    // of 192x144 400 / 358 / 330, of 224x168 641 / 540 / 540, one of 288x216 474 / 394 / 357; of one pixel 313 / 320 / 325, 463 / 452 / 453, 325 / 318 / 324); but each reads its tiles again and fills up its last block, so they are taken
     // while the workgroups are few and where the samples say that the lists are long (features of one pixel, four pairs: 324 / 365 us; 1024x768
     // 1085 / 1662).  Rows that cost more per product lose more to the last block of a list than they gain (fp32, 384x288, features of one pixel 356 / 794).
+    // What the candidates' second round lists is little, but few workgroups would take it one after the other: their ranges are halved until there are four for every compute unit (one pair of 288x216
+    // in ranges of 16384 / 2048, features of 1, 4, 64 and 128 pixels 323 / 314, 332 / 334, 432 / 380 and 579 / 423 us; twice as many workgroups 321, 340, 379 and 407; two-term rows, 400x300 859 / 881).
     ca.range = REFINE_MOST;
-    if (MASK && CT != CT_F32 && DP <= 32 && !ca.second_round)  // (what the second round lists is little)
+    if (MASK && CT != CT_F32 && DP <= 32 && ca.second_round)
+        for (; ca.range > REFINE_LEAST && cells * ((slots + ca.range - 1) / ca.range) * batch < 1024;) ca.range /= 2;
+    else if (MASK && CT != CT_F32 && DP <= 32)
         for (ca.range = REFINE_LEAST; ca.range < REFINE_MOST && cells * ((slots + ca.range - 1) / ca.range) * batch > (ca.range < REFINE_SCAN ? 4096 : 16384);) ca.range *= 2;
     const unsigned ranges = (unsigned)((slots + ca.range - 1) / ca.range);
     return launch(TK_REFINE, refine_kernel<CT, DP, RT, WAVES, MASK>, dim3(cells, ranges, batch), dim3(64 * WAVES), 0, s, a, ca);

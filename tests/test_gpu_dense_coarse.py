@@ -165,14 +165,15 @@ def least_ms(call):
     return min(times)
 
 
-@pytest.mark.parametrize("w,h,batch", [(224, 168, 4), (192, 144, 4)])
-def test_lists_that_lie_together(w, h, batch):
+@pytest.mark.parametrize("w,h,batch,feature,most", [(224, 168, 4, 32, 0.97), (192, 144, 4, 32, 0.97), (288, 216, 1, 128, 1.15)])
+def test_lists_that_lie_together(w, h, batch, feature, most):
     """Neighbouring pixels need the same cells where a map's features are large, so some workgroups of the second step have long lists; shared out in short
-    ranges they do not hold up a small call (0.89 of what one step takes; in ranges of 4096 queries 1.02 and 1.04)."""
+    ranges they do not hold up a small call (0.89 and 0.87 of what one step takes; in ranges of 4096 queries 1.02 and 1.04; the last 1.04 to 1.12, with whole ranges in the
+    candidates' second round 1.34)."""
     n, gen = w * h, torch.Generator(device="cuda:0").manual_seed(w)
 
     def field():
-        coarse = torch.randn((batch, 24, h // 32 + 2, w // 32 + 2), generator=gen, device="cuda:0")
+        coarse = torch.randn((batch, 24, h // feature + 2, w // feature + 2), generator=gen, device="cuda:0")
         x = torch.nn.functional.interpolate(coarse, size=(h, w), mode="bilinear", align_corners=True)
         return torch.nn.functional.normalize(x, dim=1).permute(0, 2, 3, 1).reshape(batch, n, 24).contiguous()
 
@@ -182,7 +183,7 @@ def test_lists_that_lie_together(w, h, batch):
     ws = torch.empty(fnn.fnn_workspace_bytes(batch, n, n, 24, 0, "f16"), dtype=torch.uint8, device="cuda:0")
     small, out = ws[:one_step_bytes(batch, n, n, 24, "f16")], fnn.fnn_mutual_dense(a, b, "f16", workspace=ws)
     two, one = (least_ms(lambda: fnn.fnn_mutual_dense(a, b, "f16", out=out, workspace=x)) for x in (ws, small))
-    assert two < 0.97 * one
+    assert two < most * one
 
 
 def test_pairs_in_groups_that_share_their_tables():
