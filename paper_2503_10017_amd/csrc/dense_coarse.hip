@@ -497,10 +497,11 @@ __global__ __launch_bounds__(SELECT_WAVES * 64) void dense_select_kernel(SelectA
 // dimensions or of very different lengths leave most of them), so DENSE_SAMPLES pixels of either image, spread over it, are scored against every
 // cell of the other first, what they need is counted (dense_costs), and every launch takes the pairs that are its own.  A group's bound is that of its longest row,
 // which reaches past the best of the others where lengths differ; what the samples' groups mark says so.  Whole calls in us, fp16, 24 channels, in one step / with a maximum for every
-// candidate / for three / as the samples say.  One 512x384 pair: features of 1 pixel 2246 / 1769 / 1565 / 1567, of 64 2134 / 1972 / 1801 / 1812, of 128 2121 / 2142 / 2083 / 2074; rank 8
-// 2231 / 2486 / 2188 / 2181, rank 7 2242 / 3009 / 2561 / 2288; lengths spread by exp(0.3 N(0, 1)) 2265 / 1753 / 2206 / 1754, by exp(N(0, 1)) 2291 / 3439 / 3273 / 2351.  Four of 192x144:
-// features of 4 pixels 375 / 310 / 305 / 305, of 32 372 / 320 / 334 / 335, rank 8 386 / 370 / 418 / 403.
-// A pair that is left to one step pays 30 to 60 us (four 512x384 pairs 3 %) for its 8-bit maps, the samples and the launches that leave it alone.
+// candidate / for three; as the samples say is within 2 % of the fastest.  One 512x384 pair: features of 1 pixel 2192 / 1709 / 1543, of 64 2097 / 1888 / 1784, of 128 2080 / 2078 / 2046; rank 8
+// 2195 / 2149 / 1824, rank 7 2189 / 2496 / 2064; lengths spread by exp(0.2 N(0, 1)) 2197 / 1736 / 2259, by exp(0.7 N(0, 1)) 2234 / 2665 / 2803.  Four of 192x144: features of 4 pixels 391 /
+// 301 / 302, of 128 386 / 333 / 351, rank 7 392 / 366 / 353, lengths spread by exp(0.2 N(0, 1)) 394 / 292 / 342.
+// A pair that is left to one step pays 25 to 40 us for its 8-bit maps, the samples and the launches that leave it alone: rank 6, four of 192x144 368 / 394 without / with them, one of 352x256 547 /
+// 577, of 512x384 2148 / 2191.
 constexpr int SAMPLE_BLOCKS = DENSE_SAMPLES / 32;
 constexpr int SAMPLE_WAVES = 8;
 constexpr int SAMPLE_TILES = 8;  // in flight per wave
@@ -646,8 +647,6 @@ constexpr double DENSE_COARSE = 38.0, DENSE_COARSE_GROUPS = 29.0;
 static double dense_second(int compute, int dp) { return compute == FNN_F32 ? 18.75 * dp : (dp <= 32 ? 46.0 : 1.64 * dp); }
 // Groups of candidates leave some GROUP_TOP cells more of them to the second step, which is dear where products are (fp32, 24 channels, a maximum for every candidate / groups:
 // 320x240 839 / 911 us, four pairs of 256x192 and 320x240 1613 / 1978; two-term rows, 384x288 894 / 865).
-// ... there with its lists and what their uneven lengths leave idle, per share of the cells that the samples mark (one 512x384 pair of 16-bit rows 45 to 58, 32 channels 66; two-term rows 121)
-static double dense_second_listed(int compute, int dp) { return compute != FNN_F32 && dp <= 32 ? (dp <= 24 ? 58.0 : 66.0) : dense_second(compute, dp); }
 static double first_round(double cells) { return cells < FEW_CELLS ? GROUP_TOP_FEW : GROUP_TOP; }
 bool dense_grouped(int64_t n, int compute, int dp) {
     const double cells = 2.0 * n / dense_seg_pixels(n);
@@ -659,10 +658,9 @@ static double dense_coarse_block(int64_t n, int compute, int dp) { return dense_
 // on large maps.  Measured in one step / two, 16-bit rows of 24 channels: 256x192 1 pair 236 / 252 us, 2 379 / 355, 4 674 / 564, 16 2341 / 1923; 352x256 564 / 455; not whole:
 // 160x120, 16 pairs 738 / 764; 192x144 1 pair 192 / 206, 4 371 / 312, 16 1321 / 829; 224x168 241 / 223, 4 632 / 449, 16 2379 / 1469; 288x216 406 / 324, 4 1819 / 852; 32 channels, 192x144, 8 803 /
 // 515; squared distance, 320x240, 2 1233 / 1253, 256x192, 4 770 / 790; fp32, 128x128, 4 494 / 749, 192x144, 4 1409 / 713; two-term rows, 128x128, 4 253 / 322, 192x144 253 / 275.
-// (A pair that the samples leave to one step pays for them and for its 8-bit maps: some 30 us.)
 struct DenseModel {
     double blocks, exact, cell, cells[2], passes;  // cells of image 2, and of image 1 (half segments where groups are possible)
-    bool grouped;
+    bool grouped, whole;
 };
 static DenseModel dense_model(int64_t n, int64_t m, int batch, int compute, int dp, bool l2) {
     DenseModel M;
@@ -671,9 +669,9 @@ static DenseModel dense_model(int64_t n, int64_t m, int batch, int compute, int 
     M.cells[0] = m / M.cell;
     M.cells[1] = (M.grouped ? 2.0 : 1.0) * n / dense_seg_pixels(n);
     M.blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
-    const bool whole = n % DENSE_SB_PIXELS == 0 && m % (32 * DENSE_TILES_PER_GROUP) == 0;
+    M.whole = n % DENSE_SB_PIXELS == 0 && m % (32 * DENSE_TILES_PER_GROUP) == 0;
     const bool narrow = compute != FNN_F32 && dp <= 32 && !l2;  // (of the others the second step costs more than counted here, too)
-    M.exact = dense_exact(compute, dp) * (narrow && !whole ? 1.4 : 1.0);
+    M.exact = dense_exact(compute, dp) * (narrow && !M.whole ? 1.4 : 1.0);
     const double row_bytes = dp * elem_size(compute);
     const double bytes = batch * ((double)(n + m) * (2.0 * row_bytes + 40.0) + 8.0 * n * (m / M.cell) + 8.0 * m * ((double)n / dense_seg_pixels(n)));
     M.passes = bytes / 4500.0 + batch * (double)(n + m) * 0.1;  // over maps and tables; most of it hides behind the sweep
@@ -687,26 +685,41 @@ double dense_coarse_gain(int64_t n, int64_t m, int batch, int compute, int dp, i
     const double again = coarse_cells_again(M.cells[0], d, l2) / M.cells[0] + ((M.grouped ? first_round(M.cells[1]) : 0.0) + coarse_cells_again(M.cells[1], d, l2)) / M.cells[1];
     return M.blocks * (M.exact - dense_coarse_block(n, compute, dp) - dense_second(compute, dp) * again) - 45000.0 - M.passes;
 }
-// What the samples' marks say a pair would take, in 1/1024 ns over one step.  Groups cost 3 ns a block more than the sweep's own time says (marking and a second round), and a quarter more per
-// mark (short lists fill up their last block): one 512x384 pair, modelled / measured, us over one step: features of 1 pixel -684 / -681, of 64 -432 / -333, of 128 -91 / -38, rank 10 -223 / -220,
-// rank 8 -39 / -43, lengths spread by exp(0.3 N(0, 1)) -57 / -59.
+// What the samples' marks say a pair would take, in 1/1024 ns over one step, from here on: the 8-bit maps and the samples are paid for either way, and so are launches that leave
+// every pair alone.  For 16-bit rows of up to 32 channels the numbers are fitted to what 324 calls took each way (192x144 to 640x480, 1 to 16 pairs; features of 1 to 128 pixels, rank 7 to 10, lengths
+// spread by exp(0.2 N(0, 1)) to exp(0.7 N(0, 1))): the way they name takes 0.2 % more than the fastest of the three on average, 8 % at the most; the numbers behind
+// dense_coarse_gain, which count what is paid already and one step too low, 2.2 and 35 % (four 192x144 pairs, exp(0.2 N(0, 1)), one step / a maximum for every candidate 392 / 290 us).
+// Most of what is left are features of 64 pixels and more, whose lists lie together.
+// Wider rows and fp32 have those numbers (one 512x384 pair, modelled / measured, us over one step: lengths spread by exp(0.3 N(0, 1)) -57 / -59), a quarter more per group's mark and 3 ns a block for the second round.
 // Pairs of one call go the same way unless one gains more than a seventh of its time by another: launches that take a part of the pairs leave the chip idle at their end (four 512x384
 // pairs whose lengths are spread by exp(0.7 N(0, 1)) 8.39 ms in one step, 8.62 with a maximum for every candidate, 9.98 where each pair went its own way).  Small pairs, which hardly fill the chip
 // one by one, always do (four of 192x144 with features of 64 pixels 368 us in one step, 369 for groups of three, 570 where two went either way).
 DenseCosts dense_costs(const DenseCoarseArgs& a, int batch, int compute, int dp, bool l2) {
     const int64_t n = a.pixels[0], m = a.pixels[1];
     const DenseModel M = dense_model(n, m, batch, compute, dp, l2);
-    const double blocks = M.blocks / batch, second = dense_second_listed(compute, dp);
+    double exact = M.exact, second = dense_second(compute, dp), singles = DENSE_COARSE, groups = DENSE_COARSE_GROUPS + 3.0, per_group = 1.25, first = 1.0;  // per block; over a single one's, per group's mark and of the first round's cells
+    double fixed_singles = (45000.0 + M.passes) / batch, fixed_groups = fixed_singles;
+    if (compute != FNN_F32 && dp <= 32) {
+        exact = 1.085 * dense_exact(compute, dp) * (M.whole ? 1.0 : ((n < m ? n : m) < 100000 ? 1.6 : 1.4));
+        second = l2 ? 78.0 : (dp <= 24 ? 46.0 : 64.0);
+        singles = 40.5;
+        groups = 35.0;
+        per_group = 1.2;
+        first = 0.8;
+        fixed_singles = 25000.0 / batch + 0.125 * (double)(n + m);
+        fixed_groups = fixed_singles + 20000.0 / batch;
+    }
+    const double blocks = M.blocks / batch;
     auto fixed = [](double ns) { return (int64_t)(ns * 1024.0); };
     auto each = [&](int64_t cells) { return fixed(blocks * second / (DENSE_SAMPLES * (double)cells)); };
     DenseCosts j = {};
     j.pairs = batch;
     j.each[MARKS_ROWS] = each(a.n_cells);
     j.each[MARKS_SINGLES] = each(a.grouped ? (a.n_col_cells + 1) / 2 : a.n_col_cells);
-    j.each[MARKS_GROUPS] = fixed(1.25 * blocks * second / (DENSE_SAMPLES * (double)a.n_col_cells));
-    j.singles = fixed((45000.0 + M.passes) / batch - blocks * (M.exact - DENSE_COARSE));
-    j.groups = a.grouped ? j.singles - fixed(blocks * (DENSE_COARSE - DENSE_COARSE_GROUPS - 3.0)) : INT64_MAX / 256;
-    j.least_groups = fixed(blocks * second * first_round(M.cells[1]) / M.cells[1]);
+    j.each[MARKS_GROUPS] = fixed(per_group * blocks * second / (DENSE_SAMPLES * (double)a.n_col_cells));
+    j.singles = fixed(fixed_singles - blocks * (exact - singles));
+    j.groups = a.grouped ? fixed(fixed_groups - blocks * (exact - groups)) : INT64_MAX / 256;  // (a call has 64 pairs at the most)
+    j.least_groups = fixed(first * blocks * second * first_round(M.cells[1]) / M.cells[1]);
     j.margin = blocks * M.exact < 1e6 ? INT64_MAX / 2 : fixed(0.15 * blocks * M.exact);
     return j;
 }
