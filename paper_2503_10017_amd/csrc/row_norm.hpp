@@ -12,13 +12,13 @@ __device__ __forceinline__ void divide_row(float (&x)[M], float norm) {
         for (int k = 0; k < N; ++k) x[k] = __fdiv_rn(x[k], norm);
     }
 }
-// FNN_FLAG_NORMALIZE on aligned fp32 rows (see the header's note on them): the fusing is the compiler's, the root the hardware's.  prep_rows_f32_kernel and
-// quantise_kernel divide alike, whichever of them prepares a call's maps.
+// FNN_FLAG_NORMALIZE on aligned fp32 rows (see the header's note on them): one product and fused steps, written out, and the hardware's root.  prep_rows_f32_kernel and
+// quantise_kernel, which may read a row twice, must divide alike to the last place: left to the compiler, `sum + x * x` may be fused in one kernel and not in another.
 template <int N, int M>
 __device__ __forceinline__ void normalize_aligned_row(float (&x)[M]) {
-    float sum = 0.0f;
+    float sum = __fmul_rn(x[0], x[0]);
 #pragma unroll
-    for (int k = 0; k < N; ++k) sum = __fadd_rn(sum, __fmul_rn(x[k], x[k]));
+    for (int k = 1; k < N; ++k) sum = __builtin_fmaf(x[k], x[k], sum);
     divide_row<N>(x, __fsqrt_rn(sum));
 }
 

@@ -80,6 +80,20 @@ def test_same_bits_in_two_steps_as_in_one(n, m, batch, compute, stored, d, kw):
     same(a.to(kind), b.to(kind), compute, **kw)
 
 
+@pytest.mark.parametrize("n,m,compute", [(300801, 30001, "f16"), (307201, 17000, "bf16")])
+def test_raw_rows_normalised_where_they_are_read_twice(n, m, compute):
+    """Segments of 4096 pixels: the quantise launch divides a row for its segment's scale and once more for the prepared map."""
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    a, b = (torch.nn.functional.normalize(torch.randn((1, rows, 24), generator=gen, device="cuda:0"), dim=2) for rows in (n, m))
+    b[:, :m // 2] = torch.nn.functional.normalize(a[:, 7:7 + m // 2] + 0.3 * b[:, :m // 2], dim=2)
+    for x in (a, b):
+        x *= torch.exp(4.0 * torch.randn(x.shape[:2] + (1,), generator=gen, device="cuda:0"))
+        x[:, 4095] = 0.0
+        x[:, -1] = 0.0
+    _, names = same(a, b, compute, normalize=True)
+    assert "quantise_kernel" in names and not [name for name in names if name.startswith("prep")]
+
+
 def test_ranges_of_segments_in_launches_of_their_own():
     """The table of bounds covers as many segments of image 1 as 128 MB hold."""
     gen = torch.Generator(device="cuda:0").manual_seed(5)
