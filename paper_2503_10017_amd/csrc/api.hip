@@ -161,15 +161,17 @@ int recip_coarse_searches(int batch, int64_t n, int64_t m, int64_t n_seeds, int 
 // launches share out better; a walk that begins with few seeds is one launch altogether.  Whole calls in us with launches only / the tail from iteration
 // 0 / 1 / 2 / 3: one 512x384 pair, features of 1 and of 4 pixels, 192 seeds 163 / 84 / 104 / 112 and 180 / 91 / 112 / 128, 352 183 / 104 / 106 / 130 and
 // 185 / 109 / 111 / 131, 768 181 / 132 / 119 / 122 and 193 / 157 / 143 / 134, 3072 236 / 249 / 206 / 183 and 267 / 277 / 236 / 204; 320x240, 300 seeds 149 / 88 / 84 / 86, 1200
-// 153 / 157 / 121 / 102; 160x120, 1200 seeds 142 / 208 / 135 / 86.  Where very many seeds are left, the launches also have the wider search; from 2 / 3 on,
-// with the present kernels: 1024x768, 12288 seeds, features of 1, 4 and 32 pixels 991 / 1003, 1076 / 1100 and 2308 / 2315; 16 pairs of 3072
-// 1309 / 1353, 1469 / 1468 and 2942 / 2942, of 12288 3725 / 3699, 4305 / 4313 and 10140 / 9540; 1024x768, 49152 seeds, 3597 / 3597 and, of 32 pixels, 8210 / 8075.
-// Two maps that have nothing in common and features of 32 pixels keep hundreds of seeds moving for many iterations.  In launches only / so, before few seeds were dealt to
-// the waves block by block: one 512x384 pair 418 / 396 (since: 362), 16 pairs 3134 / 3134 (2942), 1024x768 2526 / 2468 (2310), 16 256x192 pairs 490 / 459; with every fourth pixel a seed, 320x240 328 / 350
-// (322), four of them 727 / 767, 400x300 557 / 603, 64 160x120 pairs 1020 / 1136: the price of what such calls gain where features of 4 pixels let seeds settle (202 / 156 (141), 384 / 354, 290 /
-// 253, 564 / 516).
+// 153 / 157 / 121 / 102; 160x120, 1200 seeds 142 / 208 / 135 / 86.  Where very many seeds are left, the launches also have the wider search; from 2 / 3 on, features of 1, 4 and
+// 32 pixels, and of 4 and 32 in maps that have nothing in common: 12 pairs of 512x384, 3072 seeds 968 / 981, 1096 / 1127, 1341 / 1394, 1199 / 1201, 2209 / 2213; 24 of them 1840 / 1836,
+// 2066 / 2100, 2588 / 2723, 2327 / 2315, 4432 / 4550; 48 3659 / 3656, 4097 / 4118, 5101 / 5498, 4629 / 4616, 8901 / 9487; four of 1024x768, 12288 seeds 3396 / 3366, 3849 / 3975,
+// 5124 / 5301, 4351 / 4364, 8221 / 8224; one, 49152 seeds 3162 / 3171, 3500 / 3514, 4621 / 4643, 4038 / 4059, 7922 / 7918; 64 of 256x192, 3072 seeds 1417 / 1433, 1593 / 1596, 1974 / 1995,
+// 1864 / 1838, 3855 / 3759; 48 of 160x120, 4800 seeds 1048 / 1073, 1151 / 1173, 1428 / 1417, 1360 / 1344, 3066 / 2836.  So the line lies where the last kind begins to lose more than the
+// others gain, between 48 x 3072 and 64 x 3072.
+// Two maps that have nothing in common and features of 32 pixels keep hundreds of seeds moving for many iterations.  In launches only / so: one 512x384 pair 410 / 351, 16 pairs 3084 /
+// 3008, 1024x768 2455 / 2336, 16 256x192 pairs 496 / 444; with every fourth pixel a seed, 320x240 316 / 299, four of them 703 / 698, 400x300 505 / 483, but 64 160x120 pairs 985 / 1042: the price
+// of what such calls gain where features of 4 pixels let seeds settle (195 / 139, 380 / 331, 294 / 232, 552 / 481).
 int first_late_iteration(int batch, int64_t n_seeds, int32_t max_iter, bool coarse) {
-    const int from = n_seeds >= 32768 || batch * n_seeds > 49152 ? 3 : (n_seeds > TAIL_FEW || coarse ? 2 : (n_seeds > TAIL_FEW / 2 ? 1 : 0));
+    const int from = batch * n_seeds > 147456 ? 3 : (n_seeds > TAIL_FEW || coarse ? 2 : (n_seeds > TAIL_FEW / 2 ? 1 : 0));
     const int least = from > 2 ? from + 2 : 4;  // (with a single iteration left, four launches are as good)
     return max_iter >= least && max_iter <= TAIL_MOST_ITERATIONS ? from : -1;
 }

@@ -26,11 +26,11 @@ def wandering_maps(seed, batch, n, m, d):
     return field(n).cuda(), field(m).cuda()
 
 
-def run(a, b, seeds, max_iter, compute, tail, **kw):
+def run(a, b, seeds, max_iter, compute, tail, full=None, **kw):
     (batch, n, d), m = a.shape, b.shape[1]
     ns = seeds.shape[1]
-    full = fnn.fnn_workspace_bytes_opts(batch, n, m, d, ns, compute, max_iter, **kw)
-    ws = torch.full((full if tail else one_step_bytes("reciprocal", batch, n, m, d, ns, compute, **kw),), 0xA5, dtype=torch.uint8, device="cuda:0")
+    whole = fnn.fnn_workspace_bytes_opts(batch, n, m, d, ns, compute, max_iter, **kw)
+    ws = torch.full((whole if full or tail else one_step_bytes("reciprocal", batch, n, m, d, ns, compute, **kw),), 0xA5, dtype=torch.uint8, device="cuda:0")
     fnn.fnn_trace_begin(256)
     try:
         out = fnn.fnn_reciprocal(a, b, seeds, max_iter, compute, workspace=ws, **kw)
@@ -47,8 +47,8 @@ def run(a, b, seeds, max_iter, compute, tail, **kw):
     (1, 9001, 9333, 512, "bf16", 24, 4, None),    # the most that a workgroup keeps; seeds still moving at the end
     (1, 9001, 9333, 513, "f16", 24, 10, None),    # one more: from the third on
     (3, 16400, 12345, 5000, "f16", 24, 10, None),  # many seeds, then few
-    (2, 9001, 9333, 8192, "f16", 24, 6, None),    # from the fourth iteration on
-    (1, 30000, 20011, 4000, "f16", 24, 10, None),  # 256 workgroups while many seeds move, 32 for few
+    (2, 9001, 9333, 8192, "f16", 24, 6, None),
+    (1, 30000, 20011, 4000, "f16", 24, 10, None),  # 256 workgroups while many seeds move, 78 for few (above, 32: the least)
     (40, 2100, 1999, 700, "f16", 24, 10, None),   # six workgroups per pair
     (64, 1000, 777, 300, "f16", 24, 7, None),     # four
     (1, 9001, 9333, 600, "f16", 16, 10, None),
@@ -75,6 +75,29 @@ def test_one_launch_and_many_give_the_same(batch, n, m, n_seeds, compute, d, max
         assert np.array_equal(one[k], many[k]), (k, int(np.sum(one[k] != many[k])))
     late = (many["seed_iter"] >= 3) | (many["seed_iter"] < 0)
     assert late.any()  # the maps are of the kind that this is about
+
+
+@pytest.mark.parametrize("batch,n_seeds,max_iter,launched", [
+    (1, 256, 10, 0),
+    (1, 257, 10, 1),
+    (1, 512, 10, 1),
+    (1, 513, 10, 2),
+    (48, 3072, 10, 2),
+    (48, 3073, 10, 3),
+    (48, 3073, 5, 3),     # two iterations are left
+    (48, 3073, 4, None),  # one: four launches are as good
+    (1, 513, 4, 2),
+    (1, 513, 3, None),
+])
+def test_the_iteration_that_the_launch_begins_with(batch, n_seeds, max_iter, launched):
+    n = 9001 if batch == 1 else 2100
+    a, b = wandering_maps(n_seeds, batch, n, n - 101, 24)
+    seeds = torch.randint(0, n, (batch, n_seeds), generator=torch.Generator().manual_seed(batch), dtype=torch.int32).cuda()
+    one, names = run(a, b, seeds, max_iter, "f16", launched is not None, full=True)
+    assert names.count("resolve_step_kernel") == (max_iter if launched is None else launched)
+    many, _ = run(a, b, seeds, max_iter, "f16", False)
+    for k in many:
+        assert np.array_equal(one[k], many[k]), (k, int(np.sum(one[k] != many[k])))
 
 
 @pytest.mark.parametrize("n_seeds", [1, 32, 33, 64, 65, 96, 97, 129, 225])
