@@ -367,7 +367,9 @@ void recip_tail_kernel(TailArgs ta) {
         // A wave takes one or two blocks of queries and the more tiles for it.  Taking four and a few tiles (three of a 512x384 map, and the map once more for
         // every 128 queries) it waited for that many rows of queries and named that many winners for little work between.  This split, the bound that
         // scores start from (few_low), the copies of the keys and twice to four times as many workgroups, together, the launch in us: one 512x384 pair 53.8 -> 36.7, two with squared
-        // distance 54.5 -> 46.3, four raw pairs 79.5 -> 66, four of two-term rows 112.5 -> 96 (so with two blocks; three blocks of narrow rows one by one).  Bound by
+        // distance 54.5 -> 46.3, four raw pairs 79.5 -> 66, four of two-term rows 112.5 -> 96 (so with two blocks; three blocks of narrow rows one by one).  One of them taken back, whole calls, features of
+        // 1, 4 and 32 pixels, one 512x384 pair 162, 178 and 203 us: without the bound 163, 181 and 208, with one copy of the keys 165, 181 and 206, with a workgroup for 48 tiles 164, 182 and 216; four raw
+        // pairs 391, 430 and 523: without the bound 394, 435 and 534, the other two the same.  Bound by
         // the loads of the tiles: a compute unit takes 236 ns for eight waves' 1.5 KB each, whatever they multiply them with; four blocks of narrow rows per
         // load cost more in registers and code than that saves (36.7 -> 40.0, 46.3 -> 47.6).  Products in fp32 cost more than the loads: an odd number of blocks is taken one
         // by one there, where by twos half of a pair is padding (whole calls, features of 4 pixels, 24 channels, by twos / one by one: 16 pairs of 256x192 433 / 418 us, four of 320x240
