@@ -78,7 +78,7 @@ __device__ __forceinline__ void dense_permute(const DenseSwept& w, int b) {
 
 // A workgroup sweeps one run of queries past a few cells of candidates.  At the end of every cell of queries the candidates' maxima, or those of
 // their groups, are reduced over the lanes and kept.
-// Bound by the vector unit: in groups 11 three-input maxima per block, 11.8 instructions in all, 47 cycles beside 32 of the matrix instruction, at the clock that the power
+// Bound by the vector unit: in groups 11 three-input maxima per block, 12.4 instructions in all, 50 cycles beside 32 of the matrix instruction, at the clock that the power
 // limit leaves.  A product is followed by the maxima of the one before it, as in coarse_kernel.  One 512x384 pair / a third of 1024x768: a maximum for every candidate
 // (16 per block; 35.7 ns per block and SIMD in a bare loop, here 43) 1601 / 7745 us, groups of three 1281 / 6340, with the order of products and maxima 1207 / 6240, with eight
 // resident tiles instead of four 1154 / 5950 (31 ns).  Larger groups, in the compiler's order and with four tiles: of five 1212 / 6040, of a whole half tile 1125 / 5785; but of 192

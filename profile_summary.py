@@ -244,7 +244,7 @@ def lds_l2() -> None:
                 return max(v[counter]) if how == "max" else sum(v[counter]) / len(v[counter])
         return float("nan")
     kernels = [("coarse_kernel", "max", "coarse_kernel, first search of a step"), ("refine_kernel<1, 24, 8, 4, false>", "max", "refine_kernel, first search of a step"),
-               ("search_kernel", "max", "search_kernel, largest launch (fifth search of a step: 16 x ~106 queries)"),
+               ("recip_tail_kernel", "max", "recip_tail_kernel, the late iterations of a step"),
                ("resolve_kernel", "max", "resolve_kernel, first resolve of a step"),
                ("dense_groups_kernel<", "mean", "dense_groups_kernel (cfg 3)"), ("quantise_kernel", "max", "quantise_kernel, largest launch (both maps of 16 pairs)")]
     lines = ["# LDS and cache counters (rocprofv3 SQ / TCP / TCC counters): bench.py workloads", "", "Commands (two counter runs):", "",
