@@ -177,8 +177,8 @@ const char* fnn_status_string(int32_t status);
  * Bytes of device workspace sufficient for any of the three operations on `batch` pairs of
  * maps with n and m pixels, d channels, at most `n_queries` queries or seeds per pair (0: for
  * fnn_mutual_dense alone).  Most of it are fnn_mutual_dense's tables where the maps are large:
- * one 512x384 pair in FNN_F16, d = 24, 168 MB, of which 3072 seeds need 19 and fnn_mutual_dense
- * in one step 24; 16 such pairs 1.14 GB, 64 3.2 GB.  Returns 0 when the shape is invalid.
+ * one 512x384 pair in FNN_F16, d = 24, 171 MB, of which 3072 seeds need 19 and fnn_mutual_dense
+ * in one step 24; 16 such pairs 1.17 GB, 64 3.27 GB.  Returns 0 when the shape is invalid.
  */
 size_t fnn_workspace_bytes(int32_t batch, int64_t n, int64_t m, int32_t d, int64_t n_queries, int32_t compute);
 /*
