@@ -617,7 +617,8 @@ __global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseA
         file(MARKS_GROUPS, marks);
     }
     if (k < DENSE_MARKS) all[k] = 0;
-    __syncthreads();  // the marks come before the count, and the counts of all before what the last one reads
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's marks have arrived
+    __syncthreads();                     // everyone's have: the marks come before the count, and the counts of all before what the last one reads
     if (k == 0) filed = __hip_atomic_fetch_add(a.filed, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (filed + 1 != gridDim.x * gridDim.y * gridDim.z) return;  // uniform
