@@ -655,7 +655,9 @@ bool dense_grouped(int64_t n, int compute, int dp) {
 }
 static double dense_coarse_block(int64_t n, int compute, int dp) { return dense_grouped(n, compute, dp) ? DENSE_COARSE_GROUPS : DENSE_COARSE; }
 // The model behind the choice, in nanoseconds.  The one-step kernels leave their staged loop where a workgroup meets padding and have few workgroups to share what that leaves
-// uneven: maps that are not whole runs of 4096 queries and 512 candidates take 1.5 to 2.2 times a whole one's time per block, of which 1.4 are counted on.  Two steps cost 45 us of launches, more
+// uneven: maps of image 1 that are not whole runs of 4096 queries take 1.4 to 1.8 times a whole one's time per block, of which 1.4 are counted on (fp16, 24 channels, ns per block beside 50 us: 28672 / 27648 queries on
+// 196608 candidates, four pairs 68 / 97, 61440 / 62208 queries on 61440, four 66 / 85, 122880 / 120000 on 196608 59 / 86).  Candidates that are not whole runs of 512 cost little: 196608 queries on 28672 / 30000, four pairs
+// 66 / 65, 61440 on 61440 / 90000 66 / 68, 122880 on 28672 / 45000 65 / 69.  Two steps cost 45 us of launches, more
 // on large maps.  Measured in one step / two, 16-bit rows of 24 channels: 256x192 1 pair 236 / 252 us, 2 379 / 355, 4 674 / 564, 16 2341 / 1923; 352x256 564 / 455; not whole:
 // 160x120, 16 pairs 738 / 764; 192x144 1 pair 192 / 206, 4 371 / 312, 16 1321 / 829; 224x168 241 / 223, 4 632 / 449, 16 2379 / 1469; 288x216 406 / 324, 4 1819 / 852; 32 channels, 192x144, 8 803 /
 // 515; squared distance, 320x240, 2 1233 / 1253, 256x192, 4 770 / 790; fp32, 128x128, 4 494 / 749, 192x144, 4 1409 / 713; two-term rows, 128x128, 4 253 / 322, 192x144 253 / 275.
@@ -670,7 +672,7 @@ static DenseModel dense_model(int64_t n, int64_t m, int batch, int compute, int 
     M.cells[0] = m / M.cell;
     M.cells[1] = (M.grouped ? 2.0 : 1.0) * n / dense_seg_pixels(n);
     M.blocks = (double)batch * ((n + 31) / 32) * ((m + 31) / 32) / 1024.0;
-    M.whole = n % DENSE_SB_PIXELS == 0 && m % (32 * DENSE_TILES_PER_GROUP) == 0;
+    M.whole = n % DENSE_SB_PIXELS == 0;
     const bool narrow = compute != FNN_F32 && dp <= 32 && !l2;  // (of the others the second step costs more than counted here, too)
     M.exact = dense_exact(compute, dp) * (narrow && !M.whole ? 1.4 : 1.0);
     const double row_bytes = dp * elem_size(compute);
@@ -701,7 +703,7 @@ DenseCosts dense_costs(const DenseCoarseArgs& a, int batch, int compute, int dp,
     double exact = M.exact, second = dense_second(compute, dp), singles = DENSE_COARSE, groups = DENSE_COARSE_GROUPS + 3.0, per_group = 1.25, first = 1.0;  // per block; over a single one's, per group's mark and of the first round's cells
     double fixed_singles = (45000.0 + M.passes) / batch, fixed_groups = fixed_singles;
     if (compute != FNN_F32 && dp <= 32) {
-        exact = 1.085 * dense_exact(compute, dp) * (M.whole ? 1.0 : ((n < m ? n : m) < 100000 ? 1.6 : 1.4));
+        exact = 1.085 * dense_exact(compute, dp) * (M.whole ? 1.0 : (n < 100000 ? 1.6 : 1.4));
         second = l2 ? 78.0 : (dp <= 24 ? 46.0 : 64.0);
         singles = 40.5;
         groups = 35.0;
