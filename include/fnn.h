@@ -116,7 +116,8 @@ typedef struct {
  * (norm2 <- fma(x[k], x[k], norm2), rounded once), y[k] = x[k] / sqrt(norm2) with correctly
  * rounded fp32 sqrt and division; an all-zero descriptor stays zero.  One exception: where all
  * maps that a call prepares are fp32 with rows on 16-byte boundaries and d is a multiple of 8, and
- * FNN_FLAG_SPLIT is not set, the square root is the hardware's, off by one unit in the last place for some rows; there
+ * FNN_FLAG_SPLIT is not set, norm2 begins as fma(x[0], x[0], x[1]*x[1]), which rounds the second square instead of the first,
+ * and the square root is the hardware's, off by one unit in the last place for some rows; there
  * a few norms in a hundred differ from the above in the last place (and, in a 16-bit compute format,
  * fewer than one prepared value in 10^5 lies one step beside).  The step is fused into the prepare pass.
  */

@@ -7,6 +7,8 @@ stored in another order -- of a super-block of 4096 pixels; and the exactly repr
 SPLIT against the oracle.  Normalised rows are compared channel by channel with the oracle's, on Gaussian
 rows whose sums round at every step (the header's exception, the norms of aligned fp32 rows, is held to
 its bound).  Squared lengths likewise, against 64 bits."""
+import hashlib
+
 import numpy as np
 import pytest
 import torch
@@ -99,3 +101,14 @@ def test_squared_lengths_in_fp32(n, d):
         # against a zero row the score is the length's own term: d squares and d sums, each rounded at most once
         score = host(fnn.fnn_nearest(stored(x, torch.float32, stride, offset), zero, compute="f32", l2=True)[1])[0]
         assert (np.abs(score - want) <= np.abs(want) * 2 * d * 2.0**-24).all(), (stride, offset)
+
+
+@pytest.mark.parametrize("d,digest", [(8, "f13ff72d1ab3a37a"), (16, "2098f6af11ee0c18"), (24, "cdf7abc18f34556b"), (32, "8875f89e7abb8ea3")])
+def test_last_places_of_aligned_rows_stay(d, digest):
+    """The header's exception: the second square is rounded, the others are fused steps on top of it, and the root is the hardware's.  Another order of the sum changes the
+    last place of some rows and passes every bound, so the scores of these rows are pinned by their bits."""
+    x = (np.random.default_rng(d).integers(-999, 1000, size=(20000, d)) / np.float32(997)).astype(np.float32)
+    one_hot = np.eye(d, dtype=np.float32)   # length 1 exactly: the score is the largest channel of the normalised row
+    idx, score = (host(y)[0] for y in fnn.fnn_nearest(dev(x)[None], dev(one_hot)[None], compute="f32", normalize=True))
+    assert np.array_equal(idx, x.argmax(axis=1))
+    assert hashlib.sha1(score.tobytes()).hexdigest()[:16] == digest
