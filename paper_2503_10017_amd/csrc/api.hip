@@ -266,10 +266,9 @@ DenseCoarseLayout carve_dense_coarse(Carver& cv, int batch, int64_t n, int64_t m
     const size_t zeros = cv.used;
     a.sample_lower = (uint32_t*)cv.take((size_t)batch * 2 * DENSE_SAMPLES * sizeof(uint32_t));
     if (a.grouped) a.sample_best = (uint32_t*)cv.take((size_t)batch * DENSE_SAMPLES * sizeof(uint32_t));
-    a.marked = (int32_t*)cv.take((size_t)batch * DENSE_MARKS * sizeof(int32_t));
+    a.marked = (int32_t*)cv.take((size_t)batch * DENSE_RECORD * sizeof(int32_t));
     a.filed = (uint32_t*)cv.take(sizeof(uint32_t));
     L.sample_words = (int64_t)((cv.used - zeros) / sizeof(uint32_t));
-    a.ways = (int32_t*)cv.take((size_t)batch * sizeof(int32_t));
     return L;
 }
 
@@ -509,7 +508,7 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
 
     DenseCoarseArgs da = C.args;
     hipError_t e = launch_dense_sample(da, dense_costs(da, batch, compute, L.maps.dp, l2), batch, s);
-    da.judge = {da.ways, da.marked};
+    da.judge = {da.marked};
     // a launch that leaves every pair alone costs its workgroups' start: no more of them than fill the chip a few times
     auto wgs = [&]() { return (int64_t)C.group * sweep.n_sb * ((sweep.m_tiles + DENSE_TILES_PER_GROUP * sweep.groups_per_wg - 1) / (DENSE_TILES_PER_GROUP * sweep.groups_per_wg)); };
     while (wgs() > 4096) sweep.groups_per_wg *= 2;
@@ -529,8 +528,7 @@ hipError_t dense_two_steps(const DenseCoarseLayout& C, const DenseLayout& L, int
             map.row_bound += (int64_t)step * map.n_segs * da.seg_pixels;
             map.seg += (int64_t)step * map.n_segs;
         }
-        da.judge.ways += step;
-        da.judge.marked += DENSE_MARKS * step;
+        da.judge.marked += DENSE_RECORD * step;
         sweep.d2 += step * sweep.d2_bstride;
         sweep.row_keys += step * n;
         sweep.col_keys += step * m;

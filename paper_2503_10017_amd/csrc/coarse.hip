@@ -558,7 +558,7 @@ void refine_kernel(SearchArgs a, CoarseArgs ca) {
     n_act = min(n_act - ca.first_slot, ca.slab);  // slots are counted from first_slot on
     if (grouped) n_act = min((n_act + DENSE_CELL_PIXELS - 1) & ~(DENSE_CELL_PIXELS - 1), ca.slab);  // bits that stand for no candidate are 0
     int range = ca.range;
-    if (MASK && !ca.second_round && range < REFINE_MOST && ca.judge.marked[DENSE_MARKS * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
+    if (MASK && !ca.second_round && range < REFINE_MOST && ca.judge.marked[DENSE_RECORD * b + ca.side] * (REFINE_SCAN / DENSE_SAMPLES) < REFINE_SHORT * ca.n_cells) range = REFINE_MOST;
     const int begin = blockIdx.y * range;
     n_act = min(n_act, begin + range);
     const int tile0 = (cell * WAVES + wave) * RT;

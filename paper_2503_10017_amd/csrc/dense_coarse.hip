@@ -603,7 +603,7 @@ __global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseA
         if (first + i < cells) marks += __popcll(__ballot(most >= lower));  // uniform
     }
     auto file = [&](int what, int count) {
-        if (speaks && count) atomicAdd(&a.marked[DENSE_MARKS * b + what], count);
+        if (speaks && count) atomicAdd(&a.marked[DENSE_RECORD * b + what], count);
     };
     file(side == 0 ? MARKS_ROWS : MARKS_SINGLES, marks);
     if (grouped) {
@@ -627,13 +627,13 @@ __global__ __launch_bounds__(DENSE_SAMPLES) void dense_judge_kernel(DenseCoarseA
     int32_t own[DENSE_MARKS], sum[DENSE_MARKS];
 #pragma unroll
     for (int w = 0; w < DENSE_MARKS; ++w) {
-        own[w] = here ? __hip_atomic_load(&a.marked[DENSE_MARKS * k + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        own[w] = here ? __hip_atomic_load(&a.marked[DENSE_RECORD * k + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
         if (here) atomicAdd(&all[w], own[w]);
     }
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < DENSE_MARKS; ++w) sum[w] = all[w];
-    if (here) a.ways[k] = costs.way(own, sum);
+    if (here) a.marked[DENSE_RECORD * k + PAIR_WAY] = costs.way(own, sum);
 }
 
 // Wider cells keep the table of a large map small, narrower ones leave less to multiply again.  Segments of 2048 pixels and cells of 1024 against 4096 and

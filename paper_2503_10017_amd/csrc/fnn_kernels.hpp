@@ -155,11 +155,11 @@ constexpr int DENSE_TILES_PER_GROUP = DENSE_J * DENSE_WAVES;
 // of the pair is the fastest.  It is decided once, at the end of the samples' launch: where every workgroup of the later launches did these sums for itself, they took 5 to 10 us
 // longer each where workgroups are many.
 enum DenseWay { DENSE_ONE_STEP, DENSE_SINGLES, DENSE_GROUPS };  // in the call's own format; in 8 bits, a maximum for every candidate; one for three
-enum { MARKS_ROWS, MARKS_SINGLES, MARKS_GROUPS, DENSE_MARKS };
+enum { MARKS_ROWS, MARKS_SINGLES, MARKS_GROUPS, DENSE_MARKS, PAIR_WAY = DENSE_MARKS, DENSE_RECORD };  // the words of a pair's record
 struct DenseJudge {
-    const int32_t* ways;        // [batch] (NULL: every pair in one step)
-    const int32_t* marked;      // [batch][DENSE_MARKS]
-    __device__ __forceinline__ DenseWay way(int b) const { return ways ? (DenseWay)ways[b] : DENSE_ONE_STEP; }
+    const int32_t* marked;      // [batch][DENSE_RECORD] (NULL: every pair in one step).  (With the ways in an array of their own dense_kernel keeps 284 bytes of scratch for rows of 32
+                                // channels instead of 276, and one step of such rows took up to 4 % longer.)
+    __device__ __forceinline__ DenseWay way(int b) const { return marked ? (DenseWay)marked[DENSE_RECORD * b + PAIR_WAY] : DENSE_ONE_STEP; }
 };
 struct DenseCosts {
     int64_t pairs;
@@ -475,9 +475,8 @@ struct DenseCoarseArgs {
     float* sample_group;     // (grouped) [batch][n_col_cells][DENSE_SAMPLES]
     uint32_t* sample_lower;  // [batch][2][DENSE_SAMPLES] order_bits (0 on entry)
     uint32_t* sample_best;   // (grouped) [batch][DENSE_SAMPLES] order_bits (0 on entry)
-    int32_t* marked;         // [batch][DENSE_MARKS] (0 on entry): see DenseJudge
+    int32_t* marked;         // [batch][DENSE_RECORD] (0 on entry): see DenseJudge
     uint32_t* filed;         // workgroups that have counted their marks (0 on entry)
-    int32_t* ways;           // [batch]
     DenseJudge judge;
     DenseSwept swept;
 };
